@@ -64,30 +64,6 @@ def sym_gemm_flops(n: int) -> float:
     return float(n) * (n + 1) * n
 
 
-def newton_gemm_counts(iters: int, j64: int, jlow: int, xt_lowp: bool):
-    """(fp32 GEMMs, fp64 GEMMs, split-fp16 GEMMs) a factor executed: iteration k < iters does
-    X <- X T (except k = 0, where X_1 is written by the start kernel), and for k < iters - 1 also
-    the M-chain T^2, T^4 and T^4 M; the chain runs on the fp64 matrices for k < j64 and on the fp16
-    cores (two-term split operands) for k >= jlow; X <- X T runs there too when xt_lowp, else with its iteration's
-    tier (fp32 at least)."""
-    g32 = g64 = g16 = 0
-    for k in range(iters):
-        chain = 3 if k < iters - 1 else 0
-        lowp = k >= max(jlow, j64)
-        if k < j64:
-            g64 += chain
-        elif lowp:
-            g16 += chain
-        else:
-            g32 += chain
-        if k > 0:
-            if xt_lowp or lowp:
-                g16 += 1
-            else:
-                g32 += 1
-    return g32, g64, g16
-
-
 class RootRun:
     """One inverse-root workload: statistics, roots and preconditioned gradients of a list of blocks,
     timed stage by stage with events on the stream the library launches on, every grouped-GEMM
@@ -135,27 +111,21 @@ class RootRun:
             self.step()
             torch.cuda.synchronize()
             log(f"[bench] {tag} warmup {w}: {1e3 * (time.time() - t):.0f} ms")
-        j64, jlow, xt_lowp = self.plan
         evs = [[torch.cuda.Event(enable_timing=True) for _ in range(4)] for _ in range(steps)]
         ast.profile_enable(200000)
-        flops = {"fp32": 0.0, "fp64": 0.0, "fp16": 0.0}
         torch.cuda.synchronize()
         t_wall = time.time()
         for s in range(steps):
             self.step(evs[s])
             torch.cuda.synchronize()          # step boundary (also lets the iteration counts be read)
-            for n, c in zip(self.fsize, self.iters.cpu().numpy()):
-                g32, g64, g16 = newton_gemm_counts(int(c), j64, jlow, xt_lowp)
-                flops["fp32"] += g32 * sym_gemm_flops(n)
-                flops["fp64"] += g64 * sym_gemm_flops(n)
-                flops["fp16"] += g16 * sym_gemm_flops(n)
             log(f"[bench] {tag} step {s}: {evs[s][0].elapsed_time(evs[s][3]):.0f} ms")
         wall_ms = 1e3 * (time.time() - t_wall)
-        i8f = ast.profile_i8_flops()         # fp64-iteration products by where the device sent them
+        i8f = ast.profile_i8_flops()         # products of the prefix by where the device sent them
+        pair_flops, i8_ops = ast.profile_root_work()
         prof = ast.profile_collect(200000)
         ms = lambda a, b: sum(e[a].elapsed_time(e[b]) for e in evs) / steps
         return dict(stats_ms=ms(0, 1), refresh_ms=ms(1, 2), precond_ms=ms(2, 3), step_ms=ms(0, 3), wall_ms=wall_ms,
-                    prof=prof, flops=flops, i8_flops=i8f, info=self.info.cpu().numpy(), iters=self.iters.cpu().numpy())
+                    prof=prof, pair_flops=pair_flops, i8_ops=i8_ops, i8_flops=i8f, info=self.info.cpu().numpy(), iters=self.iters.cpu().numpy())
 
 
 def gemm_rooflines(res, steps, step_ms):
@@ -165,30 +135,19 @@ def gemm_rooflines(res, steps, step_ms):
     does no work; such launches are counted and their (microsecond) durations left out of the rates.
     `avg_launch_ms` is the mean over the launches that worked, `avg_launch_ms_all` the mean over every launch
     (what a profiler's per-kernel average shows)."""
-    prof, flops, i8f = res["prof"], res["flops"], res["i8_flops"]
+    prof, pair_flops, i8_ops, i8f = res["prof"], res["pair_flops"], res["i8_ops"], res["i8_flops"]
     def split(kinds):
         ms = [t for t, k in prof if k in kinds]
         top = max(ms, default=0.0)
         work = [t for t in ms if t > 0.05 * top]          # an empty grid takes ~0.1 ms, a working launch 5 - 50
         return ms, work
     out, shares = {}, {}
-    # fp64-iteration products: the device counted where each went
+    # every product is counted on the device where it ran (runs with pinned precision options are not)
     f64_cores, f_i8_4, f_i8_5 = i8f
-    if f64_cores + f_i8_4 + f_i8_5 == 0.0:                # int8 path off: the plan's fp64 products ran on the fp64 cores
-        f64_cores = flops["fp64"]
-    all32, w32 = split((0,))
     all64, w64 = split((1,))
     all16, w16 = split((224,))
     all8, w8 = split((304, 305))
-    t32, t64, t16, t8 = (sum(x) * 1e-3 for x in (w32, w64, w16, w8))
-    if w32 and flops["fp32"] > 0:
-        tf = flops["fp32"] / t32 / 1e12
-        out["roofline_fp32"] = {"kernel": "gemm_grouped_kernel<float> (symmetric fp32-MFMA products of the root iteration)",
-                                "bound": "mfma", "achieved": round(tf, 2), "peak": PEAK_F32_MFMA, "unit": "TFLOP/s",
-                                "frac": round(tf / PEAK_F32_MFMA, 4), "traffic": stored_traffic("traffic_bytes_per_launch_fp32"),
-                                "launches": len(all32), "working_launches": len(w32),
-                                "avg_launch_ms": round(1e3 * t32 / len(w32), 4), "avg_launch_ms_all": round(sum(all32) / len(all32), 4), "flops_per_launch": round(flops["fp32"] / len(w32), 1)}
-        shares["roofline_fp32"] = t32
+    t64, t16, t8 = (sum(x) * 1e-3 for x in (w64, w16, w8))
     if w64 and f64_cores > 0:
         tf = f64_cores / t64 / 1e12
         out["roofline_fp64"] = {"kernel": "gemm_grouped_kernel<double> (products of the leading root iterations on the fp64 matrix cores)",
@@ -198,33 +157,36 @@ def gemm_rooflines(res, steps, step_ms):
                                 "launches": len(all64), "working_launches": len(w64),
                                 "avg_launch_ms": round(1e3 * t64 / len(w64), 4), "avg_launch_ms_all": round(sum(all64) / len(all64), 4), "flops_per_launch": round(f64_cores / len(w64), 1)}
         shares["roofline_fp64"] = t64
-    if w16 and flops["fp16"] > 0:
-        tf = flops["fp16"] / t16 / 1e12
+    if w16 and pair_flops > 0:
+        tf = pair_flops / t16 / 1e12
         out["roofline_split_fp16"] = {
-            "kernel": "gemm_bf16_grouped_kernel<float, float, 2, 2, fp16> (X updates and the root iterations after the fp64 "
-                      "prefix: fp32 operands split in two fp16 terms, 3 fp16 MFMA passes per product)",
+            "kernel": "pair_product_kernel (X updates and the root iterations after the prefix: operands stored as two fp16 "
+                      "terms, 3 fp16 MFMA passes per product)",
             "bound": "mfma", "achieved": round(3 * tf, 2), "peak": PEAK_BF16_MFMA, "unit": "TFLOP/s (fp16 MFMA issued)",
             "frac": round(3 * tf / PEAK_BF16_MFMA, 4),
             "fp32_equivalent_tflops": round(tf, 2), "useful_frac": round(tf / PEAK_BF16_MFMA, 4),
             "traffic": stored_traffic("traffic_bytes_per_launch_fp16"), "launches": len(all16), "working_launches": len(w16),
-            "avg_launch_ms": round(1e3 * t16 / len(w16), 4), "avg_launch_ms_all": round(sum(all16) / len(all16), 4), "flops_per_launch": round(3 * flops["fp16"] / len(w16), 1)}
+            "avg_launch_ms": round(1e3 * t16 / len(w16), 4), "avg_launch_ms_all": round(sum(all16) / len(all16), 4), "flops_per_launch": round(3 * pair_flops / len(w16), 1)}
         shares["roofline_split_fp16"] = t16
     if w8 and f_i8_4 + f_i8_5 > 0:
-        ops = 10.0 * f_i8_4 + 15.0 * f_i8_5                # int8 MFMA passes per product: 10 with 4 slices, 15 with 5
+        ops = i8_ops                                       # 10 or 13 int8 MFMA passes per product with 4 digits, 15 or 19 with 5
         useful = f_i8_4 + f_i8_5
         out["roofline_int8_slices"] = {
-            "kernel": "gemm_i8_grouped_kernel<4 | 5 slices> (products of the fp64 iterations: each fp64 operand as its diagonal "
-                      "plus 7-bit slices, 10 | 15 int8 MFMA passes per product, exact int32 sums, fp64 assembly; the slice count "
-                      "is chosen per factor and product on the device and counted there)",
+            "kernel": "digit_product_kernel<4 | 5> (products of the leading iterations: operands as 32- or 40-bit integers in "
+                      "base-256 digits, 10 to 19 int8 MFMA passes per product, exact int32 sums, fp64 assembly; digits and levels "
+                      "are chosen per factor on the device and the work counted there)",
             "bound": "mfma", "achieved": round(ops / t8 / 1e12, 2), "peak": PEAK_I8_MFMA, "unit": "TOP/s (int8 MFMA issued)",
             "frac": round(ops / t8 / 1e12 / PEAK_I8_MFMA, 4),
             "fp64_equivalent_tflops": round(useful / t8 / 1e12, 2), "useful_frac": round(useful / t8 / 1e12 / PEAK_I8_MFMA, 4),
-            "flops_share_4_slices": round(f_i8_4 / useful, 4), "flops_share_5_slices": round(f_i8_5 / useful, 4),
+            "flops_share_4_digits": round(f_i8_4 / useful, 4), "flops_share_5_digits": round(f_i8_5 / useful, 4),
             "flops_share_declined_to_fp64_cores": round(f64_cores / (useful + f64_cores), 6),
             "traffic": stored_traffic("traffic_bytes_per_launch_int8"), "launches": len(all8), "working_launches": len(w8),
             "avg_launch_ms": round(1e3 * t8 / len(w8), 4), "avg_launch_ms_all": round(sum(all8) / len(all8), 4), "flops_per_launch": round(ops / len(w8), 1)}
         shares["roofline_int8_slices"] = t8
     out["gemm_time_share_ms_per_step"] = {k.replace("roofline_", ""): round(1e3 * v / steps, 1) for k, v in shares.items()}
+    if not shares:                                        # pinned precision options
+        out["refresh_mfma"] = None
+        return out
     dominant = max(shares, key=shares.get)
     out["roofline"] = dict(out[dominant], time_share_of_step=round(1e3 * shares[dominant] / steps / step_ms, 4))
     # the refresh as a whole: every kernel's fraction of its own peak weighted by its time, the time
@@ -341,13 +303,13 @@ def main() -> int:
         "config": {"workload": "1.1B LLaMA-style model, all 2-D grads blocked at <=1024 (1184 blocks, 2368 factors), "
                                "bf16 power-law gradients, fp32 statistics, eps=1e-6*lambda_max, beta=0.95",
                    "blocks": len(shapes), "factors": nf,
-                   "arithmetic": "fp32 storage; statistics: bf16 MFMA, fp32 sums; roots: the leading fp64 iterations as diagonal + "
-                                 "7-bit integer slices on the int8 MFMA with exact int32 sums and fp64 assembly, the rest and every "
-                                 "X update as two fp16 terms per fp32 operand on the fp16 MFMA (3 passes, fp32 sums); "
+                   "arithmetic": "fp32 storage; statistics: bf16 MFMA, fp32 sums; roots: the leading iterations as 32- or 40-bit "
+                                 "integers on the int8 MFMA with exact int32 sums and fp64 assembly, the rest and every "
+                                 "X update as two fp16 terms per entry on the fp16 MFMA (3 passes, fp32 sums); "
                                  "preconditioned gradient: two bf16 terms per fp32 operand on the bf16 MFMA",
                    "fp64_prefix_iters": j64,
                    "fp64_prefix_products": ("fp64 cores" if args.int8_slices == 0 else
-                                            "int8 cores, diagonal + 7-bit slices (fp64 cores where the device-side estimate declines)"),
+                                            "int8 cores, base-256 digits (fp64 cores where the device-side estimate declines)"),
                    "fp16_split_from_iter": jlow, "x_update_on_fp16_cores": xt_lowp,
                    "schedule": "interval-adapted" if args.schedule == 1 else "classical Newton",
                    "workspace_gib": round(run.ws_bytes / 2**30, 1)},

@@ -165,13 +165,10 @@ typedef struct asteria_root_opts {
                               after the fp64 prefix, n <= 16384; never for absolute eps),
                               >= max_iters = never                                                      */
     int32_t int8_slices;   /* how the products of the fp64 iterations are computed: 0 = on the fp64 matrix
-                              cores; 4 or 5 = on the int8 matrix cores, each fp64 operand held as its
-                              diagonal plus that many 7-bit slices below a per-row exponent (29 / 36 bits),
-                              integer accumulation exact, result assembled in fp64 - per factor and
-                              product, and only where the part this drops is estimated on the device to
-                              stay below a fixed fraction (2e-5, shared among the fp64 iterations) of the
-                              bottom of M's spectrum; otherwise that product runs on the fp64 cores;
-                              -1 = 5 (default)                                                         */
+                              cores; 4 or 5 = on the int8 matrix cores with at most that many digits per
+                              operand - per factor, and only where what this drops is estimated on the
+                              device to stay below a fixed fraction of the bottom of M's spectrum;
+                              otherwise on the fp64 cores; -1 = 5 (default)                            */
 } asteria_root_opts;
 
 void asteria_root_opts_default(asteria_root_opts *opts);
@@ -223,15 +220,26 @@ asteria_status asteria_sym_unpack(const asteria_sympair *items, int nitems, void
  *                       A v per step): the largest Ritz value, stopped per factor when it has settled
  *   scaling             s = 1 / ((1 + margin) lambda_max + eps); M_0 = s (A + eps I), X_0 = s^(1/root) I;
  *                       the spectrum of M_0 is taken to lie in [eps s / 2, 1]
- *   iteration           T = a I - g M, X <- X T, M <- T^root M; (a, g) per factor and iteration from
- *                       the interval that holds M's spectrum (`schedule` = 1) or the Newton values
+ *   iteration           X <- X T, M <- T^root M with a polynomial T of M chosen per factor and iteration from
+ *                       the interval that holds M's spectrum (`schedule` = 1: linear, or of degree 2 or 3
+ *                       where that takes fewer products), or Newton's T = ((root + 1) I - M) / root
  *   stop (per factor)   one more X update follows once ||M - I||_F < stop_resid, or once the interval
  *                       predicted for M's spectrum is within 1 +- 1e-2 and the measured residual is
  *                       consistent with it; under the automatic precision rules already when the image
  *                       of that interval under the next update is within 1 +- 3e-3
  *
- *   iterations          matrices  products run on
- *   ------------------  --------  ----------------------------------------------------------------
+ *   automatic precision rules (relative eps, root 4, schedule 1, fp64_iters = lowp_from = -1, n <= 16384)
+ *   iterations          storage of M and of the powers of T   products run on
+ *   ------------------  ------------------------------------  ---------------------------------------
+ *   first fp64_iters    32- or 40-bit integers against a      int8 matrix cores (base-256 digits, exact
+ *   (fewer where the    bound on the largest diagonal entry,  integer sums, fp64 assembly), or fp64 matrix
+ *   device finds the    or fp64: per factor, by an estimate   cores
+ *   next tier enough)   of what the integers lose
+ *   then                two fp16 terms per entry (22 bits),   fp16 matrix cores, three passes, fp32 sums
+ *                       scaled by powers of two from bounds
+ *   X, throughout       two fp16 terms; the last X in fp32    the same
+ *
+ *   otherwise
  *   first fp64_iters    fp64      int8 matrix cores (diagonal + 7-bit slices, exact integer sums, fp64
  *                                 assembly) or fp64 matrix cores, per factor and product: `int8_slices`
  *   up to lowp_from     fp32      fp32 matrix cores
@@ -242,7 +250,8 @@ asteria_status asteria_sym_unpack(const asteria_sympair *items, int nitems, void
  * What the interval-based choices rely on.  A is positive semi-definite up to round-off: eigenvalues
  * down to -eps / 2 are covered by the lower end eps s / 2 (statistics accumulated in fp32 can fall
  * further below zero when eps is of the order of 1e-8 lambda_max: accumulate those with
- * ASTERIA_ACC_F64).  The largest Ritz value never exceeds lambda_max and reaches it to a few 1e-7 on
+ * ASTERIA_ACC_F64), and no entry exceeds the largest diagonal entry by more than 2 % (a factor where one
+ * does reports ASTERIA_INFO_NOT_PD).  The largest Ritz value never exceeds lambda_max and reaches it to a few 1e-7 on
  * every workload tested (leading eigenvalues 0.4 % apart included); it stalls below only if the start
  * vector has no component along the leading eigenvectors, and `lambda_margin` (1 %) is the allowance
  * for that.  If
@@ -428,14 +437,18 @@ asteria_status asteria_soap_reproject(const asteria_rblock *blocks, int nblocks,
  * k-major; 32..255 the 16-bit kernel, 32 + (2 = A operand bf16 in memory) + (4 = B operand bf16 in
  * memory) + (64 = A split into two terms) + (128 = B split into two terms), so 224 = both operands
  * fp32 split in two terms and 96 = A split, B one term; 256..299 the guard-free kernels (512 the
- * statistics, 513 the 256 x 256 split x split products); 300 + NS the int8-slice kernel whose planes
- * hold NS slices (304, 305).  Not thread safe.                                                    */
+ * statistics, 513 the 256 x 256 split x split products); 300 + NS the int8 kernels on NS
+ * slices or digits (304, 305).  Not thread safe.                                                    */
 asteria_status asteria_profile_enable(int max_launches);
 int asteria_profile_collect(float *ms, int32_t *kind, int cap);
 /* Algorithmic flops (n^2 (n + 1) per symmetric product) of the products of the fp64 iterations since
  * the last asteria_profile_enable, by where the device-side decision sent them: out3[0] fp64 matrix
  * cores, out3[1] int8 cores with 4 slices, out3[2] with 5.  Waits for the device.               */
 asteria_status asteria_profile_i8_flops(double *out3);
+/* Of the inverse roots under the automatic precision rules since then: out2[0] algorithmic flops of the
+ * products on two-term fp16 storage, out2[1] int8 multiply-adds x 2 issued for the flops out3[1] + out3[2].
+ * Waits for the device.                                                                           */
+asteria_status asteria_profile_root_work(double *out2);
 
 #ifdef __cplusplus
 }

@@ -162,6 +162,8 @@ def lib():
             fn.argtypes = [POINTER(_SymPair), c_int, c_void_p]
         L.asteria_profile_i8_flops.restype = c_int
         L.asteria_profile_i8_flops.argtypes = [POINTER(ctypes.c_double)]
+        L.asteria_profile_root_work.restype = c_int
+        L.asteria_profile_root_work.argtypes = [POINTER(ctypes.c_double)]
         _lib = L
     return _lib
 
@@ -560,6 +562,14 @@ def profile_i8_flops():
     (fp64 cores, int8 cores with 4 slices, int8 cores with 5 slices).  Waits for the device."""
     out = (ctypes.c_double * 3)()
     _check(lib().asteria_profile_i8_flops(out), "asteria_profile_i8_flops")
+    return tuple(out)
+
+
+def profile_root_work():
+    """(algorithmic flops of the products on fp16 pair planes, int8 operations issued by the products on digit
+    planes) of the inverse roots since profile_enable.  Waits for the device."""
+    out = (ctypes.c_double * 2)()
+    _check(lib().asteria_profile_root_work(out), "asteria_profile_root_work")
     return tuple(out)
 
 

@@ -44,7 +44,7 @@ struct ProfileState {
 } g_prof;
 }  // namespace
 
-static __device__ double g_i8_flops[3];
+static __device__ double g_i8_flops[5];
 static double *g_i8_flops_ptr[asteria::MAX_DEVICES];   // device address of g_i8_flops, per device
 
 static double *i8_flops_ptr()
@@ -86,7 +86,7 @@ extern "C" asteria_status asteria_profile_enable(int max_launches)
 {
     if (max_launches <= 0 || g_prof.on) return ASTERIA_INVALID_ARG;
     if (double *c = i8_flops_ptr()) {
-        if (hipMemset(c, 0, 3 * sizeof(double)) != hipSuccess) return ASTERIA_HIP_ERROR;   // synchronous: measurement aid
+        if (hipMemset(c, 0, 5 * sizeof(double)) != hipSuccess) return ASTERIA_HIP_ERROR;   // synchronous: measurement aid
     }
     g_prof.on = true;
     g_prof.cap = max_launches;
@@ -121,5 +121,14 @@ extern "C" asteria_status asteria_profile_i8_flops(double *out3)
     double *c = i8_flops_ptr();
     if (!c) return ASTERIA_HIP_ERROR;
     ASTERIA_HIP_TRY(hipMemcpy(out3, c, 3 * sizeof(double), hipMemcpyDeviceToHost));   // waits for the device
+    return ASTERIA_OK;
+}
+
+extern "C" asteria_status asteria_profile_root_work(double *out2)
+{
+    if (!out2) return ASTERIA_INVALID_ARG;
+    double *c = i8_flops_ptr();
+    if (!c) return ASTERIA_HIP_ERROR;
+    ASTERIA_HIP_TRY(hipMemcpy(out2, c + 3, 2 * sizeof(double), hipMemcpyDeviceToHost));   // waits for the device
     return ASTERIA_OK;
 }

@@ -16,6 +16,12 @@ namespace asteria {
         if (e__ != hipSuccess) return ASTERIA_HIP_ERROR; \
     } while (0)
 
+#define ASTERIA_TRY(expr)                              \
+    do {                                               \
+        asteria_status s__ = (expr);                   \
+        if (s__ != ASTERIA_OK) return s__;             \
+    } while (0)
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Sequential carving of a caller-owned workspace into 256-byte aligned pieces.

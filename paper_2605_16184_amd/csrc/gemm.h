@@ -48,6 +48,7 @@ enum : int {
     GEMM_C_F32 = 16,     // C is stored as fp32 (fp64 compute only): read, combined in fp64, rounded once
     GEMM_EPI_HANDOVER = 32,  // root epilogue of the last fp64 iteration: C and C2 are not stored (nothing reads the
                              // fp64 M and T again), C goes to C4 in fp32 instead (C3, the fp32 T, as usual)
+    GEMM_EPI_RESID = 128,    // partial[tile] = sum (C - I)^2
     GEMM_C_PACKED = 64   // symmetric C in packed lower-tile storage (see packed_off); ldc unused, nothing above the diagonal tiles
 };
 
@@ -87,13 +88,16 @@ struct GemmProblem {
     float ep_a, ep_g;
     int flags;
     float sa, sb;       // fp16-split kernel: powers of two the operands are multiplied by before the split
+    const double *coefd; // fp64 compute: C = coefd[0] own + coefd[2] A B (own: row-major like C), or null
+    const double *own;
 };
 
 // Measurement aid (see asteria_profile_enable): bracket a launch with HIP events on its stream.
 void profile_begin(int kind, hipStream_t stream);
 void profile_end(hipStream_t stream);
-// While recording: device array of 3 doubles in which the int8 decision kernel adds up the algorithmic
-// flops of the products it sends to the fp64 cores [0], to 4 slices [1] and to 5 slices [2]; else null.
+// While recording: device array of 5 doubles: algorithmic flops of the prefix products that the device sends to
+// the fp64 cores [0], to 4 slices or digits [1] and to 5 [2]; plane path: flops of the pair products [3], int8
+// operations issued [4]; else null.
 double *profile_i8_counters();
 
 // The dynamic-LDS limit of a kernel is an attribute per device: a launcher remembers, per device,
@@ -476,6 +480,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmProblem &P, typename MM:
     const int M = P.M, N = P.N;
     const bool sym = (flags & GEMM_SYM) != 0;
     const bool root = (flags & GEMM_EPI_ROOT) != 0;
+    bool resid = false;                         // fp64 compute only
+    if constexpr (sizeof(TC) == 8) resid = (flags & GEMM_EPI_RESID) != 0;
     const TC alpha = (TC)P.alpha, beta = (TC)P.beta;
     // coefficients of T = a I - g C: per-problem device values (coef[0], coef[1]) or the table's
     const float *coef = root ? P.coef : nullptr;
@@ -567,6 +573,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmProblem &P, typename MM:
                 if (row >= M || col >= N) continue;
                 if (sym && row < col) continue;   // the mirror of (col, row) covers it
                 TC val = alpha * acc[i][j][v];
+                if constexpr (sizeof(TC) == 8) {
+                    if (P.coefd) val = P.coefd[0] * P.own[(size_t)row * ldc + col] + P.coefd[2] * acc[i][j][v];
+                }
                 const size_t at_n = off_n + (size_t)(row - br) * ld_c + (size_t)(col - bc);
                 const size_t at_t = off_t + (size_t)(col - bc) * ld_c + (size_t)(row - br);
                 const size_t at = (flags & GEMM_STORE_T) ? at_t : at_n;
@@ -591,11 +600,14 @@ __device__ __forceinline__ void gemm_epilogue(const GemmProblem &P, typename MM:
                     }
                     const float e = (float)(val - d);
                     rsum += (sym && row != col) ? 2.0f * e * e : e * e;
+                } else if (resid) {
+                    const float e = (float)(val - ((row == col) ? (TC)1 : (TC)0));
+                    rsum += (sym && row != col) ? 2.0f * e * e : e * e;
                 }
             }
         }
     }
-    if (root) {
+    if (root || resid) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) rsum += __shfl_xor(rsum, off, 64);
         if (lane == 0) red[wave] = rsum;

@@ -37,72 +37,26 @@
 #include "gemm.h"
 #include "gemm_bf16.h"
 #include "gemm_i8.h"
+#include "root_factor.h"
+#include "root_products.h"
 #include "root_schedule.h"
 
 using namespace asteria;
 
+namespace asteria {
+inline size_t plane_small_bytes(int n);      // root_plane_path.h
+}
+
 namespace {
 
 constexpr int PM_ROWS = 32;   // rows of A per mat-vec workgroup (8 per wavefront)
-constexpr int LZ_MAX = 128;   // most Lanczos steps of the lambda_max estimate (size of the recurrence kept per factor)
-
-enum : int { ST_RUN = 0, ST_LAST = 1, ST_DONE = 2, ST_FAIL = 3 };
-
 // spectrum of M within 1 +- ROOT_STOP_DEV: one more X update finishes the factor
 constexpr float ROOT_STOP_DEV = 1e-2f;
 // accepted truncation error of the result per eigen-direction (a third of the 2e-3 accuracy bar
 // on the relative Frobenius error, which averages over directions)
 constexpr float ROOT_X_TOL = 7e-4f;
 
-struct FactorDev {
-    const float *A;
-    float *Xout;
-    float *X32b;        // second fp32 X buffer (workspace); X is kept in fp32 in every precision tier
-    float *M32[2];
-    float *T32;
-    float *T432;
-    double *M64[2];
-    double *T64;
-    double *T464;
-    float *pv[3];       // Lanczos vectors: the current one, the one before it, and A times the current one
-    float2 *pm_partial; // per mat-vec workgroup: (sum y^2, sum y v)
-    float2 *pm_partial2; // per mat-vec workgroup, first step only: (sum a_ij^2, sum a_ii)
-    float *partial;     // per lower-triangle tile: sum (M - I)^2 (2 ntri entries: a second one per tile for kernels that split tiles)
-    int n, lda, ldx;
-    int ld32, ld64;
-    int ntri;           // lower-triangle tiles
-    int tile_start;     // first tile of this factor in tile-indexed launches
-    int pm_blocks;
-    int pm_block_start;
-    float eps_in;
-    int a_packed;       // A lies in packed lower tiles (gemm.h, packed_off): lda unused
-    float *pm_tile;     // packed A: per lower tile 2 x 128 partial products of the mat-vec and (sum a^2, trace part)
-};
 constexpr int PM_TILE_WORDS = 2 * PACK_T + 2;   // floats per tile in pm_tile
-
-struct FactorScal {
-    float lam;       // lambda_max estimate
-    float eps;       // absolute eps used
-    float scale;     // s
-    float resid;     // last ||M - I||_F
-    float inv_norm;  // 1 / ||v|| of the current Lanczos vector (the vectors are stored unnormalised)
-    float inv_prev;  // the same for the vector before it
-    float rho;       // largest Ritz value so far: the lambda_max estimate
-    int lz_small;    // consecutive steps that moved the estimate by less than the tolerance
-    int iters;       // X updates performed / scheduled
-    int xloc;        // 0: current fp32 X in Xout, 1: in X32b
-    int info;
-    int pm_done;
-    float lo, hi;    // interval assumed to contain the spectrum of the current M
-    float ca, cg;    // coefficients of the current T = ca I - cg M
-    float coef_next[2];   // coefficients the M-update epilogue uses for the next T
-    float fro2, trace;    // ||A||_F^2 and tr(A), gathered during the first mat-vec of the lambda_max estimate
-    float x_scale;        // power of two that brings X into the fp16 range for the 16-bit products
-    // (lo, hi) of the M the current iteration starts from and the g of its T: lo, hi, ca, cg above
-    // are advanced to the next iteration's before the products of the current one run
-    float lo_cur, hi_cur, cg_cur;
-    float lz_a[LZ_MAX], lz_b[LZ_MAX];   // the Lanczos recurrence: diagonal and off-diagonal of the tridiagonal matrix
-};
 
 // Scale of M, T, T^2, T^4 in the fp16-split products: their entries stay below a^4 < 23 (a <= 2.2),
 // so 2^10 keeps them under 2^15 with the fp16 range ending at 65504.
@@ -820,7 +774,7 @@ size_t factor_small_bytes(int n)
     return 3 * Carver::need((size_t)ld4(n), sizeof(float)) + 2 * Carver::need((size_t)pmb, sizeof(float2)) +
            Carver::need(2 * (size_t)tri_tiles(n), sizeof(float)) + Carver::need((size_t)tri_tiles(n) * PM_TILE_WORDS, sizeof(float)) +
            sizeof(FactorDev) + sizeof(FactorScal) +
-           2 * sizeof(int) + 16 * sizeof(GemmProblem);
+           2 * sizeof(int) + 16 * sizeof(GemmProblem) + plane_small_bytes(n);
 }
 
 size_t fixed_bytes() { return 64 * 256; }   // alignment slack of the shared arrays + coefficient table
@@ -978,13 +932,197 @@ __global__ void root_tables_kernel(const FactorDev *__restrict__ fd, FactorScal 
     }
 }
 
-// one pass over factors [first, first + cnt) of the size-sorted order
-asteria_status run_pass(const asteria_factor *f, const std::vector<int> &order, int first, int cnt,
-                        int root, asteria_eps_mode mode, const float *eps, int eps_count, const Plan &pl,
-                        int32_t *info, int32_t *iters, float *resid, float *lambda_max,
-                        void *ws, hipStream_t stream, bool outputs_permuted, int *perm_dev_unused)
+// the lambda_max estimate of every factor of a pass
+asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int cnt, const Plan &pl, bool any_full, bool any_packed,
+                                   int pm_blocks_max, int tri_max, int n_max, hipStream_t stream)
 {
-    (void)outputs_permuted; (void)perm_dev_unused;
+    hipLaunchKernelGGL(pm_init_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs);
+    const int lz_steps = std::min(pl.power_iters, LZ_MAX);
+    for (int it = 0; it < lz_steps; ++it) {
+        // the three vectors rotate: v_j in src, A v_j (then v_{j+1}) in dst, v_{j-1} in prev
+        const int src = it % 3, dst = (it + 1) % 3, prev = (it + 2) % 3, first = it == 0 ? 1 : 0;
+        if (any_full)
+            hipLaunchKernelGGL(pm_matvec_kernel, dim3(pm_blocks_max, cnt), dim3(256), 0, stream, d_fd, d_fs, cnt, src, dst, first);
+        if (any_packed) {
+            hipLaunchKernelGGL(pm_packed_tile_kernel, dim3(tri_max, cnt), dim3(256), 0, stream, d_fd, d_fs, src, first);
+            hipLaunchKernelGGL(pm_packed_reduce_kernel, dim3((n_max + PACK_T - 1) / PACK_T, cnt), dim3(PACK_T), 0, stream, d_fd, d_fs, src, dst, first);
+        }
+        hipLaunchKernelGGL(pm_lanczos_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, pl.power_tol * pl.power_tol, it,
+                           src, dst, prev, first, it + 1 == lz_steps ? 1 : 0);
+    }
+    ASTERIA_HIP_TRY(hipGetLastError());
+    return ASTERIA_OK;
+}
+
+}  // namespace
+#include "root_plane_path.h"
+namespace {
+
+// The plane path serves the fully automatic precision rules; everything pinned, absolute eps, square roots and
+// the classical schedule take run_pass below.
+bool plane_path(const Plan &pl, asteria_eps_mode mode, int n_max)
+{
+    return pl.xt_lowp && mode == ASTERIA_EPS_RELATIVE && pl.root == 4 && pl.adapted && n_max <= 16384;
+}
+
+// Whether a factor's digits can turn out too coarse (largest possible diagonal of M_0: 1)
+bool plane_needs_f64(const Plan &pl, double lo0, int n_max)
+{
+    if (pl.fp64_iters <= 0) return false;
+    if (pl.i8_slices < 5 || digit_rounding(n_max, 5, 1.0, lo0) > DIGIT_ROUNDING) return true;
+    // E4 <= a^4 <= 2^7 on M <= 2^1 with 6 levels of 5 digits, against a bottom lifted at least tenfold
+    return digit_dropped(n_max, 5, 6, 7, 1) / (10.0 * lo0) > DIGIT_DROPPED;
+}
+
+// tiles of 128 below which a pass takes 64 x 64 tiles for its pair products: fewer workgroups than the chip holds
+constexpr int PLANE_SMALL_TILES = 512;
+
+asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, const float *eps, int eps_count, const Plan &pl, bool f64,
+                               int32_t *info, int32_t *iters, float *resid, float *lambda_max, void *ws, hipStream_t stream)
+{
+    Carver cv(ws);
+    FactorDev *d_fd = cv.take<FactorDev>(cnt);
+    FactorScal *d_fs = cv.take<FactorScal>(cnt);
+    int *d_state = cv.take<int>(cnt);
+    int *d_flags = cv.take<int>(cnt);
+    std::vector<FactorDev> fd(cnt);
+    int tri_total = 0, tri64_total = 0, pm_blocks_max = 0, tri_max = 0, n_max = 0;
+    bool any_packed = false, any_full = false;
+    double a_min = 1.0;
+    const bool prefix = pl.fp64_iters > 0;
+    for (int i = 0; i < cnt; ++i) {
+        const asteria_factor &a = f[first + i];
+        FactorDev &F = fd[i];
+        memset(&F, 0, sizeof(F));
+        const int n = a.n;
+        n_max = std::max(n_max, n);
+        F.A = a.A; F.Xout = a.X; F.n = n; F.lda = a.lda; F.ldx = a.ldx;
+        F.rowb = pair_row_bytes(n); F.ld64 = ld2(n);
+        F.ntri = tri_tiles(n);
+        F.tile_start = tri_total; tri_total += F.ntri;
+        F.tile_start64 = tri64_total; tri64_total += tri_tiles64(n);
+        F.npart = std::max(2 * F.ntri, tri_tiles64(n));
+        F.flags = d_flags + i;
+        F.a_packed = a.a_layout == ASTERIA_LAYOUT_PACKED ? 1 : 0;
+        F.pm_blocks = F.a_packed ? (n + PACK_T - 1) / PACK_T : (n + PM_ROWS - 1) / PM_ROWS;
+        if (F.a_packed) { any_packed = true; tri_max = std::max(tri_max, F.ntri); }
+        else { any_full = true; pm_blocks_max = std::max(pm_blocks_max, F.pm_blocks); }
+        F.eps_in = eps[eps_count == 1 ? 0 : first + i];
+        const double er = (double)F.eps_in;
+        a_min = std::min(a_min, er / (1.0 + (double)pl.margin + er));
+        for (int v = 0; v < 3; ++v) F.pv[v] = cv.take<float>(ld4(n));
+        F.pm_partial = cv.take<float2>((n + PM_ROWS - 1) / PM_ROWS);
+        F.pm_partial2 = cv.take<float2>((n + PM_ROWS - 1) / PM_ROWS);
+        F.pm_tile = cv.take<float>((size_t)F.ntri * PM_TILE_WORDS);
+        F.partial = cv.take<float>(F.npart);
+        const size_t pair = (size_t)n * F.rowb, slot = plane_slot_bytes(n, prefix, f64);
+        for (int v = 0; v < 2; ++v) F.X[v] = cv.take<char>(pair);
+        F.P[1] = cv.take<char>(pair);
+        F.P[2] = cv.take<char>(pair);
+        char *region = cv.take<char>((prefix ? 4 : 2) * slot);
+        if (prefix) {
+            for (int v = 0; v < 4; ++v) { F.D[v] = region + v * slot; F.F[v] = reinterpret_cast<double *>(region + v * slot); }
+            F.P[0] = region + 2 * slot; F.P[3] = region + 3 * slot;
+        } else {
+            F.P[0] = region; F.P[3] = region + slot;
+        }
+    }
+    const bool small = tri_total < PLANE_SMALL_TILES;
+    uint2 *d_map = cv.take<uint2>(tri_total), *d_map64 = small ? cv.take<uint2>(tri64_total) : nullptr;
+    PlaneF64Tables ft = {};
+    if (f64)
+        for (int pa = 0; pa < 2; ++pa)
+            for (int o = 0; o < 4; ++o) ft.t[pa][o] = cv.take<GemmProblem>(cnt);
+
+    // degrees of T by iteration and the iteration budget: the sequence for the smallest eps, then a few more for a
+    // factor whose spectrum left the interval the sequence is made for
+    const double lo0 = 0.5 * a_min;
+    std::vector<int> deg;
+    if (pl.fp64_iters <= 2)
+        for (const char *q = root_degrees(lo0); *q; ++q) deg.push_back(*q - '0');
+    int K;
+    if (!deg.empty()) {
+        for (int e = 0; e < 3; ++e) deg.push_back(2);
+        K = (int)deg.size();
+    } else {
+        int it = 0, lead = 0;
+        simulate_schedule(lo0, n_max, 4, true, (double)pl.stop_resid, 0.0, pl.max_iters, &it, &lead);
+        K = it + 2;
+    }
+    K = std::min(K, pl.max_iters);
+    deg.resize(K + 1, 1);
+    const int J = std::min(pl.fp64_iters, K);
+    const bool linear0 = deg[0] == 1;
+
+    ASTERIA_HIP_TRY(upload_async(d_fd, fd.data(), sizeof(FactorDev) * cnt, stream));
+    if (f64)
+        hipLaunchKernelGGL(plane_f64_tables_kernel, dim3((cnt + 127) / 128), dim3(128), 0, stream, d_fd, d_fs, cnt, linear0 ? 1 : 0, ft);
+    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, pl, any_full, any_packed, pm_blocks_max, tri_max, n_max, stream));
+
+    // intervals and T of a factor that follows the schedule (the device works in fp32 for the scaling: 1e-5 of slack)
+    std::vector<PlaneControl> ctl(K + 1);
+    {
+        double lo = lo0 * (1.0 - 1e-5), hi = 1.0;
+        for (int k = 0; k <= K; ++k) {
+            ctl[k].lo = lo; ctl[k].hi = hi;
+            ctl[k].T = root_poly(lo, hi, deg[k]);
+            lo = ctl[k].T.image.lo; hi = ctl[k].T.image.hi;
+        }
+    }
+    auto control = [&](int k) {
+        PlaneControl &c = ctl[k];
+        c.k = k; c.degree = deg[k]; c.next_linear = (k + 1 < K && deg[k + 1] == 1) ? 1 : 0;
+        c.prefix = J; c.wide_next = (k + 1 < J && deg[k + 1] <= 2) ? 1 : 0;
+        c.digits_max = pl.i8_slices; c.final_pass = k == K ? 1 : 0; c.stop_resid = pl.stop_resid;
+        c.counters = profile_i8_counters();
+        return c;
+    };
+    hipLaunchKernelGGL(plane_setup_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, d_state, pl.margin, control(0), d_map, d_map64);
+    hipLaunchKernelGGL(plane_init_kernel, dim3(tri_total), dim3(256), 0, stream, d_fd, d_fs, d_state, d_map, linear0 ? 1 : 0);
+    ASTERIA_HIP_TRY(hipGetLastError());
+    for (int k = 0; k < K; ++k) {
+        if (k > 0) hipLaunchKernelGGL(plane_control_kernel, dim3(cnt), dim3(64), 0, stream, d_fd, d_fs, d_state, control(k));
+        const int d = deg[k];
+        const bool pre = k < J;
+        auto pair = [&](int op0, int op1) -> hipError_t {
+            if (small) return launch_pair_product<1, 4>(d_fd, d_fs, d_state, d_map64, tri64_total, op0, op1, k, d, stream);
+            return launch_pair_product<2, 2>(d_fd, d_fs, d_state, d_map, tri_total, op0, op1, k, d, stream);
+        };
+        auto chain = [&](int op, int tab) -> hipError_t {       // digit and fp64 products of the prefix
+            hipError_t e = hipSuccess;
+            if (pl.i8_slices > 0) e = launch_digit_product<4>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
+            if (e == hipSuccess && pl.i8_slices > 4) e = launch_digit_product<5>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
+            if (e == hipSuccess && f64)
+                e = launch_gemm_grouped<double, double, double, false, false>(ft.t[k & 1][tab], cnt, tri_total, d_state, stream);
+            return e;
+        };
+        auto from_f64 = [&](int what) {
+            if (f64)
+                hipLaunchKernelGGL(plane_from_f64_kernel, dim3((unsigned)(((size_t)n_max * plane_groups(n_max) * 2 + 255) / 256), (unsigned)cnt),
+                                   dim3(256), 0, stream, d_fd, d_fs, d_state, k, what);
+        };
+        if (pre && d == 2) { ASTERIA_HIP_TRY(chain(OP_SQ, 0)); from_f64(0); }
+        if (d == 2) ASTERIA_HIP_TRY(pair(OP_SQ, -1));
+        if (d == 3) { ASTERIA_HIP_TRY(pair(OP_SQ3, -1)); ASTERIA_HIP_TRY(pair(OP_CUBE, -1)); }
+        if (pre) ASTERIA_HIP_TRY(chain(OP_E2, 1));
+        if (k > 0) ASTERIA_HIP_TRY(pair(OP_E2, OP_X));
+        else ASTERIA_HIP_TRY(pair(OP_E2, -1));
+        if (pre) ASTERIA_HIP_TRY(chain(OP_E4, 2));
+        ASTERIA_HIP_TRY(pair(OP_E4, -1));
+        if (pre) { ASTERIA_HIP_TRY(chain(OP_M, 3)); from_f64(1); }
+        ASTERIA_HIP_TRY(pair(OP_M, -1));
+        ASTERIA_HIP_TRY(hipGetLastError());
+    }
+    hipLaunchKernelGGL(plane_control_kernel, dim3(cnt), dim3(64), 0, stream, d_fd, d_fs, d_state, control(K));
+    hipLaunchKernelGGL(plane_finalize_kernel, dim3(64, (unsigned)cnt), dim3(256), 0, stream, d_fd, d_fs, d_state, first, info, iters, resid, lambda_max);
+    ASTERIA_HIP_TRY(hipGetLastError());
+    return ASTERIA_OK;
+}
+
+// one pass over factors [first, first + cnt)
+asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, asteria_eps_mode mode, const float *eps, int eps_count,
+                        const Plan &pl, int32_t *info, int32_t *iters, float *resid, float *lambda_max, void *ws, hipStream_t stream)
+{
     Carver cv(ws);
     FactorDev *d_fd = cv.take<FactorDev>(cnt);
     FactorScal *d_fs = cv.take<FactorScal>(cnt);
@@ -1006,7 +1144,7 @@ asteria_status run_pass(const asteria_factor *f, const std::vector<int> &order, 
     int n_max = 0;
     double a_min = 1.0;
     for (int i = 0; i < cnt; ++i) {
-        const asteria_factor &a = f[order[first + i]];
+        const asteria_factor &a = f[first + i];
         FactorDev &F = fd[i];
         memset(&F, 0, sizeof(F));
         const int n = a.n;
@@ -1023,7 +1161,7 @@ asteria_status run_pass(const asteria_factor *f, const std::vector<int> &order, 
         F.pm_block_start = pm_total; pm_total += F.pm_blocks;
         if (F.a_packed) { any_packed = true; tri_max = std::max(tri_max, F.ntri); }
         else { any_full = true; pm_blocks_max = std::max(pm_blocks_max, F.pm_blocks); }
-        F.eps_in = eps[eps_count == 1 ? 0 : order[first + i]];
+        F.eps_in = eps[eps_count == 1 ? 0 : first + i];
         if (mode == ASTERIA_EPS_RELATIVE) {
             const double er = (double)F.eps_in;
             a_min = std::min(a_min, er / (1.0 + (double)pl.margin + er));
@@ -1100,21 +1238,8 @@ asteria_status run_pass(const asteria_factor *f, const std::vector<int> &order, 
     ASTERIA_HIP_TRY(hipGetLastError());
 
     // 1. lambda_max
-    hipLaunchKernelGGL(pm_init_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs);
+    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, pl, any_full, any_packed, pm_blocks_max, tri_max, n_max, stream));
     const int ctl_blocks = (cnt + 127) / 128;
-    const int lz_steps = std::min(pl.power_iters, LZ_MAX);
-    for (int it = 0; it < lz_steps; ++it) {
-        // the three vectors rotate: v_j in src, A v_j (then v_{j+1}) in dst, v_{j-1} in prev
-        const int src = it % 3, dst = (it + 1) % 3, prev = (it + 2) % 3, first = it == 0 ? 1 : 0;
-        if (any_full)
-            hipLaunchKernelGGL(pm_matvec_kernel, dim3(pm_blocks_max, cnt), dim3(256), 0, stream, d_fd, d_fs, cnt, src, dst, first);
-        if (any_packed) {
-            hipLaunchKernelGGL(pm_packed_tile_kernel, dim3(tri_max, cnt), dim3(256), 0, stream, d_fd, d_fs, src, first);
-            hipLaunchKernelGGL(pm_packed_reduce_kernel, dim3((n_max + PACK_T - 1) / PACK_T, cnt), dim3(PACK_T), 0, stream, d_fd, d_fs, src, dst, first);
-        }
-        hipLaunchKernelGGL(pm_lanczos_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, pl.power_tol * pl.power_tol, it,
-                           src, dst, prev, first, it + 1 == lz_steps ? 1 : 0);
-    }
     // 2. scaling, start
     hipLaunchKernelGGL(root_setup_kernel, dim3(ctl_blocks), dim3(128), 0, stream, d_fd, d_fs, d_state, cnt,
                        mode == ASTERIA_EPS_RELATIVE ? 1 : 0, pl.margin, root, pl.adapted ? 1 : 0);
@@ -1191,6 +1316,29 @@ asteria_status run_pass(const asteria_factor *f, const std::vector<int> &order, 
     return ASTERIA_OK;
 }
 
+// Which path a call takes and the workspace its factors need.  A call is accepted where its largest factor fits
+// the workspace on the fp32 / fp64 path; the plane path is taken where that factor fits it too.
+struct PassBytes {
+    const Plan &pl;
+    bool planes = false, f64 = false, fits = true;
+    PassBytes(const asteria_factor *f, int nf, asteria_eps_mode mode, const float *eps, int eps_count, const Plan &p, size_t ws_bytes) : pl(p)
+    {
+        int n_max = 0;
+        for (int i = 0; i < nf; ++i) n_max = std::max(n_max, f[i].n);
+        double a_min = 1.0;
+        for (int i = 0; i < eps_count; ++i) a_min = std::min(a_min, (double)eps[i] / (1.0 + (double)pl.margin + (double)eps[i]));
+        fits = fixed_bytes() + of(n_max) <= ws_bytes;
+        planes = plane_path(pl, mode, n_max);
+        f64 = planes && plane_needs_f64(pl, 0.5 * a_min, n_max);
+        if (planes && fixed_bytes() + of(n_max) > ws_bytes) planes = f64 = false;
+    }
+    size_t of(int n) const
+    {
+        return factor_small_bytes(n) + (planes ? plane_factor_bytes(n, pl.fp64_iters > 0, f64)
+                                               : factor_matrix_bytes(n, pl.use64, pl.use32) + factor_i8_bytes(n, pl.i8_slices));
+    }
+};
+
 }  // namespace
 
 extern "C" asteria_status asteria_inverse_root_plan(int root, asteria_eps_mode mode, const float *eps, int eps_count,
@@ -1225,8 +1373,11 @@ extern "C" size_t asteria_inverse_root_workspace_bytes(const asteria_factor *f, 
     size_t total = fixed_bytes(), biggest = 0;
     for (int i = 0; i < nfactors; ++i) {
         if (f[i].n <= 0) return 0;
-        const size_t b = factor_matrix_bytes(f[i].n, use64, use32) + factor_small_bytes(f[i].n) +
-                         factor_i8_bytes(f[i].n, use64 ? (o.int8_slices < 0 ? 5 : o.int8_slices) : 0);
+        // the call takes one of two paths (eps and root decide): room for either
+        const size_t b = factor_small_bytes(f[i].n) +
+                         std::max(factor_matrix_bytes(f[i].n, use64, use32) +
+                                      factor_i8_bytes(f[i].n, use64 ? (o.int8_slices < 0 ? 5 : o.int8_slices) : 0),
+                                  plane_factor_bytes(f[i].n, true, true));
         total += b;
         biggest = std::max(biggest, b);
     }
@@ -1250,25 +1401,23 @@ extern "C" asteria_status asteria_inverse_root(const asteria_factor *f, int nfac
     if (reinterpret_cast<uintptr_t>(ws) & 255u) return ASTERIA_INVALID_ARG;   // workspace must be 256-byte aligned
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_);
 
-    // Passes are formed over the caller's order (outputs are indexed by caller position, and a
-    // pass covers a contiguous index range), largest pass that fits the workspace.
-    std::vector<int> order(nfactors);
-    for (int i = 0; i < nfactors; ++i) order[i] = i;
+    // Passes cover contiguous index ranges of the caller's order (outputs are indexed by caller position), each the
+    // largest that fits the workspace.
+    const PassBytes pb(f, nfactors, mode, eps, eps_count, pl, ws_bytes);
+    if (!pb.fits) return ASTERIA_WORKSPACE_TOO_SMALL;
     int first = 0;
     while (first < nfactors) {
         size_t used = fixed_bytes();
         int cnt = 0;
         while (first + cnt < nfactors && cnt < 65535) {   // 65535: y extent of the mat-vec grid
-            const int n = f[first + cnt].n;
-            const size_t b = factor_matrix_bytes(n, pl.use64, pl.use32) + factor_small_bytes(n) +
-                             factor_i8_bytes(n, pl.i8_slices);
+            const size_t b = pb.of(f[first + cnt].n);
             if (used + b > ws_bytes) break;
             used += b;
             ++cnt;
         }
         if (cnt == 0) return ASTERIA_WORKSPACE_TOO_SMALL;
-        st = run_pass(f, order, first, cnt, root, mode, eps, eps_count, pl, info, iters, resid, lambda_max,
-                      ws, stream, false, nullptr);
+        if (pb.planes) st = run_pass_planes(f, first, cnt, eps, eps_count, pl, pb.f64, info, iters, resid, lambda_max, ws, stream);
+        else st = run_pass(f, first, cnt, root, mode, eps, eps_count, pl, info, iters, resid, lambda_max, ws, stream);
         if (st != ASTERIA_OK) return st;
         first += cnt;
     }
@@ -1301,12 +1450,7 @@ extern "C" asteria_status asteria_inverse_root_static(const asteria_factor *f, i
     st = make_plan(opts, mode, eps, eps_count, root, pl);
     if (st != ASTERIA_OK) return st;
     // every factor must fit the array by itself (the call works through the batch in passes)
-    for (int i = 0; i < nfactors; ++i) {
-        const int n = f[i].n;
-        const size_t b = fixed_bytes() + factor_matrix_bytes(n, pl.use64, pl.use32) + factor_small_bytes(n) +
-                         factor_i8_bytes(n, pl.i8_slices);
-        if (b > STATIC_SCRATCH_BYTES) return ASTERIA_EXCEEDS_STATIC_SCRATCH;
-    }
+    if (!PassBytes(f, nfactors, mode, eps, eps_count, pl, STATIC_SCRATCH_BYTES).fits) return ASTERIA_EXCEEDS_STATIC_SCRATCH;
     int dev = -1;
     ASTERIA_HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= STATIC_SCRATCH_MAX_DEVICES) return ASTERIA_UNSUPPORTED;

@@ -1,0 +1,87 @@
+// Per-factor device state of asteria_inverse_root, shared by its kernels.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace asteria {
+
+constexpr int LZ_MAX = 128;   // most Lanczos steps of the lambda_max estimate (size of the recurrence kept per factor)
+
+enum : int { ST_RUN = 0, ST_LAST = 1, ST_DONE = 2, ST_FAIL = 3 };
+// what the chain products of a factor run on in the current iteration
+enum : int { TIER_F64 = 0, TIER_DIGIT = 1, TIER_PAIR = 2 };
+
+struct FactorDev {
+    const float *A;
+    float *Xout;
+    // plane path
+    char *X[2];         // pair planes: X_k in X[k & 1]
+    char *P[4];         // pair planes of the chain, slots as in root_products.h
+    char *D[4];         // digit planes of the chain, the same slots
+    double *F[4];       // fp64 matrices of the chain, the same slots
+    int *flags;         // [0]: an entry left the range of its digits
+    int rowb;           // bytes of a pair plane row
+    int npart;          // entries of `partial`
+    int tile_start64;   // first tile of this factor in launches of 64 x 64 tiles
+    // fp32 / fp64 path
+    float *X32b;        // second fp32 X buffer (workspace); X is kept in fp32 in every precision tier
+    float *M32[2];
+    float *T32;
+    float *T432;
+    double *M64[2];
+    double *T64;
+    double *T464;
+    // both
+    float *pv[3];       // Lanczos vectors: the current one, the one before it, and A times the current one
+    float2 *pm_partial; // per mat-vec workgroup: (sum y^2, sum y v)
+    float2 *pm_partial2; // per mat-vec workgroup, first step only: (sum a_ij^2, sum a_ii)
+    float *partial;     // per lower-triangle tile: sum (M - I)^2 (2 ntri entries: a second one per tile for kernels that split tiles)
+    int n, lda, ldx;
+    int ld32, ld64;
+    int ntri;           // lower-triangle tiles
+    int tile_start;     // first tile of this factor in tile-indexed launches
+    int pm_blocks;
+    int pm_block_start;
+    float eps_in;
+    int a_packed;       // A lies in packed lower tiles (gemm.h, packed_off): lda unused
+    float *pm_tile;     // packed A: per lower tile 2 x 128 partial products of the mat-vec and (sum a^2, trace part)
+};
+
+// coefficients of one product of the plane path: C = own1 O1 + own2 O2 + gam A B, in values
+struct RootProd { double own1, own2, gam; };
+
+struct FactorScal {
+    float lam;       // lambda_max estimate
+    float eps;       // absolute eps used
+    float scale;     // s
+    float resid;     // last ||M - I||_F
+    float inv_norm;  // 1 / ||v|| of the current Lanczos vector (the vectors are stored unnormalised)
+    float inv_prev;  // the same for the vector before it
+    float rho;       // largest Ritz value so far: the lambda_max estimate
+    int lz_small;    // consecutive steps that moved the estimate by less than the tolerance
+    int iters;       // X updates performed / scheduled
+    int xloc;        // 0: current fp32 X in Xout, 1: in X32b (plane path: 1 + parity: in X[parity])
+    int info;
+    int pm_done;
+    float lo, hi;    // interval assumed to contain the spectrum of the current M
+    float ca, cg;    // coefficients of the current T = ca I - cg M
+    float coef_next[2];   // coefficients the M-update epilogue uses for the next T
+    float fro2, trace;    // ||A||_F^2 and tr(A), gathered during the first mat-vec of the lambda_max estimate
+    float x_scale;        // power of two that brings X into the fp16 range for the 16-bit products
+    // (lo, hi) of the M the current iteration starts from and the g of its T: lo, hi, ca, cg above
+    // are advanced to the next iteration's before the products of the current one run
+    float lo_cur, hi_cur, cg_cur;
+    float lz_a[LZ_MAX], lz_b[LZ_MAX];   // the Lanczos recurrence: diagonal and off-diagonal of the tridiagonal matrix
+    // plane path
+    int tier, next_tier;
+    int ns, levels;       // digits of this factor's digit planes (4 or 5), digit-product levels kept in this iteration
+    int handover;         // the M-update of this iteration writes pair planes for the next one
+    int pair_m;           // ... and pair planes beside the digits (the next T is linear: X' = a X - b X M)
+    int dexp[5];          // exponents of the digit planes' quanta by slot; 4: the next M
+    double lo_d, hi_d;    // interval of the current M
+    double dmax;          // bound on the largest diagonal entry of M
+    float x1a, x1s, x1b;  // X_1 = x1a I - x1s E (times x_scale); E = x1b M where T is linear
+    RootProd prod[7];     // by RootOp
+};
+
+}  // namespace asteria

@@ -1,0 +1,486 @@
+// The plane path of asteria_inverse_root: the coupled iteration on plane storage (planes.h), taken under the
+// fully automatic precision rules (relative eps, root 4, interval-adapted schedule, n <= 16384).
+//
+//   T = c0 I - E,  E = -(c1 M + c2 M^2 + c3 M^3)   degree 1, 2 or 3 by iteration (root_degrees)
+//   E2 = 2 c0 E - E E      (T^2 = c0^2 I - E2)
+//   E4 = 2 c0^2 E2 - E2 E2 (T^4 = c0^4 I - E4)
+//   M' = c0^4 M - E4 M,    X' = c0 X - X E
+//
+// Neither T nor its powers are stored, only their complements: those have the small diagonals of M (entries of
+// a statistic with a decaying spectrum are of the size of its mean eigenvalue), which is what a fixed number of
+// bits is measured against, and every product reads its linear term from an operand it has streamed anyway.
+//
+// While the bottom of M's spectrum is below ROOT_LOWP_FLOOR the chain runs on digit planes (int8 matrix cores,
+// 32 or 40 bits against a uniform quantum), or, where the device finds 40 bits too few or the caller asked for
+// it, on fp64 matrices; afterwards on pair planes.  X is kept in pair planes throughout, the last update writes
+// the caller's fp32 matrix.
+#pragma once
+
+namespace asteria {
+
+// Errors allowed in the bottom `lo` of M's spectrum, relative to it (a quarter reaches the root there):
+//   rounding of M to 2^-8NS of a bound d on its diagonal, an error matrix of norm below n^(1/2) 2^-8NS d;
+//   the digit products beyond the kept levels, per entry (2 n^(1/2) of it in norm) about (pairs of the first
+//   dropped level x n)^(1/2) 128^2 / 3 quanta of that level, for the product E4 M, which dominates, against
+//   the bottom of M'.
+// Measured against the same iteration on fp64 matrices (power law, rank 32 + noise, log-spaced over 12 and 16
+// decades, two levels; n = 96 .. 1024): at these limits the root differs by less than 1.5e-4.
+constexpr double DIGIT_ROUNDING = 9e-4;
+constexpr double DIGIT_DROPPED = 3e-3;
+
+__host__ __device__ inline double digit_rounding(int n, int ns, double d, double lo) { return sqrt((double)n) * ldexp(1.0, -8 * ns) * d / lo; }
+// ranges: 2^ea, 2^eb bound the operands
+__host__ __device__ inline double digit_dropped(int n, int ns, int levels, int ea, int eb)
+{
+    const int pairs = 2 * ns - 1 - levels;              // digit pairs s + t = levels
+    if (pairs <= 0) return 0.0;
+    return 2.0 * n * sqrt((double)pairs) * 5461.0 * ldexp(1.0, ea + eb - 2 * (8 * ns - 1) + 8 * (2 * (ns - 1) - levels));
+}
+
+// diagonal of M_0 above which a second prefix iteration of degree 2 is kept on digits: two fp16 terms are too
+// coarse for entries of that size while the spectrum still reaches down to 4e-5
+constexpr double DIGIT_WIDE_DIAG = 0.25;
+
+struct PlaneControl {
+    int k, degree, next_linear, prefix;   // prefix: iterations that may run on digits or in fp64
+    int wide_next;                        // the next iteration has digit products (degree <= 2, inside the prefix)
+    int digits_max;                       // 0, 4 or 5
+    int final_pass;
+    float stop_resid;
+    // the host's T for this iteration, made for an interval a little wider than the one every factor of the common
+    // eps arrives with: taken where it covers the factor's interval closely
+    double lo, hi;
+    RootPoly T;
+    double *counters;                     // measurement aid (profile_i8_counters), or null
+};
+
+// Decide about iteration k of one factor and leave its coefficients (one thread).
+__device__ inline void plane_advance(const FactorDev &F, FactorScal &S, int *state, float resid, const PlaneControl &c)
+{
+    int st = *state;
+    S.resid = resid;
+    const double lo0 = S.lo_d, hi0 = S.hi_d;
+    const double dev = fmax(1.0 - lo0, hi0 - 1.0);
+    // every |mu - 1| is at most the measured residual: tighten the predicted interval
+    double lo = lo0, hi = hi0;
+    const double rb = (double)resid * 1.001 + 1e-5;
+    if (1.0 - rb > lo) lo = 1.0 - rb;
+    if (1.0 + rb < hi) hi = 1.0 + rb;
+    if (!(hi > lo)) { lo = 1.0 - rb; hi = 1.0 + rb; }
+    const RootPoly T = (lo >= c.lo && hi <= c.hi && lo <= 1.001 * c.lo) ? c.T : root_poly(lo, hi, c.degree);
+    // one more X update finishes the factor: see root_control_kernel for the three tests and what they rely on
+    const bool consistent = (double)resid < 1.5 * sqrt((double)F.n) * dev + 2e-3;
+    const double dev_next = fmax(1.0 - T.image.lo, T.image.hi - 1.0);
+    const bool ends = resid < c.stop_resid || (consistent && dev < (double)ROOT_STOP_DEV) ||
+                      (consistent && dev_next <= 4.0 * (double)ROOT_X_TOL);
+    if (c.final_pass) {
+        S.info = ASTERIA_INFO_NOT_CONVERGED;
+        return;
+    }
+    if (ends) st = ST_LAST;
+    S.iters += 1;
+    S.xloc = (st == ST_LAST && c.k > 0) ? 0 : 1 + ((c.k + 1) & 1);
+    const int p = c.k & 1;
+    // T = a I - E; what M carries into the products where T is linear
+    const double a = T.c[0], b = -T.c[1];
+    const bool lin = c.degree == 1;
+    S.prod[OP_SQ] = {b, 0.0, -T.c[2]};
+    S.prod[OP_SQ3] = {0.0, 0.0, 1.0};
+    S.prod[OP_CUBE] = {b, -T.c[2], -T.c[3]};
+    S.prod[OP_E2] = lin ? RootProd{2.0 * a * b, 0.0, -b * b} : RootProd{2.0 * a, 0.0, -1.0};
+    S.prod[OP_E4] = {2.0 * a * a, 0.0, -1.0};
+    S.prod[OP_M] = {a * a * a * a, 0.0, -1.0};
+    S.prod[OP_X] = lin ? RootProd{a, 0.0, -b} : RootProd{a, 0.0, -1.0};
+    if (c.k == 0) {
+        const double xs = sqrt(sqrt((double)S.scale)) * (double)S.x_scale;
+        S.x1a = (float)(xs * a); S.x1s = (float)xs; S.x1b = (float)b;
+    }
+    // bounds on the diagonals (E <= b M, E2 <= 2 a E, E4 <= 2 a^2 E2, M' <= a^4 M in the order of symmetric
+    // matrices, and every norm by the scalar map) and from them the quanta of the digits
+    const double dm = S.dmax, de = lin ? dm : fmin(b * dm, a), de2 = fmin(2.0 * a * (lin ? b * dm : de), a * a), de4 = fmin(2.0 * a * a * de2, a * a * a * a);
+    const double dm1 = fmin(a * a * a * a * dm, T.image.hi * 1.001);
+    const int ge = (int)ceil(log2(de * 1.02)), ge2 = (int)ceil(log2(de2 * 1.02)), ge4 = (int)ceil(log2(de4 * 1.02));
+    const int gm1 = (int)ceil(log2(dm1 * 1.02));
+    int gm = (int)ceil(log2(dm * 1.02));
+    if (c.k > 0 && S.next_tier == TIER_DIGIT) gm = S.dexp[4] + 8 * S.ns - 1;      // the range the last M-update was stored with
+    // error of the dropped levels of E4 M relative to the bottom of M'
+    auto dropped = [&](int ns, int levels) { return digit_dropped(F.n, ns, levels, ge4, gm) / T.image.lo; };
+    if (c.k == 0) {
+        S.tier = TIER_PAIR;
+        S.ns = 4;
+        if (c.prefix > 0 && lo < ROOT_LOWP_FLOOR) {
+            S.tier = TIER_F64;
+            if (c.digits_max >= 4 && digit_rounding(F.n, 4, dm, lo) <= DIGIT_ROUNDING && dropped(4, 5) <= DIGIT_DROPPED) S.tier = TIER_DIGIT;
+            else if (c.digits_max >= 5 && digit_rounding(F.n, 5, dm, lo) <= DIGIT_ROUNDING && dropped(5, 6) <= DIGIT_DROPPED) {
+                S.tier = TIER_DIGIT;
+                S.ns = 5;
+            }
+        }
+    } else {
+        S.tier = S.next_tier;
+    }
+    if (S.tier == TIER_DIGIT) {
+        const int bits = 8 * S.ns - 1;
+        S.levels = dropped(S.ns, S.ns) <= (S.ns == 4 ? DIGIT_DROPPED : 0.2 * DIGIT_DROPPED) ? S.ns : S.ns + 1;
+        S.dexp[p] = gm - bits; S.dexp[2] = ge - bits; S.dexp[p ^ 1] = ge2 - bits; S.dexp[3] = ge4 - bits; S.dexp[4] = gm1 - bits;
+    }
+    if (c.counters) {
+        // flops of this iteration's chain by where they run, of all pair products, and int8 operations issued
+        const double one = (double)F.n * (double)F.n * (double)(F.n + 1);
+        const double chain = one * (double)(c.degree - 1 + (st == ST_LAST ? 0 : 3)), x = c.k > 0 ? one : 0.0;
+        const int passes = S.ns == 4 ? (S.levels == 4 ? 10 : 13) : (S.levels == 5 ? 15 : 19);
+        if (S.tier == TIER_F64) atomicAdd(&c.counters[0], chain);
+        if (S.tier == TIER_DIGIT) { atomicAdd(&c.counters[S.ns - 3], chain); atomicAdd(&c.counters[4], chain * passes); }
+        atomicAdd(&c.counters[3], x + (S.tier == TIER_PAIR ? chain : 0.0));
+    }
+    const bool wide = c.wide_next && dm > DIGIT_WIDE_DIAG && c.k == 0;
+    const bool to_pair = S.tier == TIER_PAIR || c.k + 1 >= c.prefix || (T.image.lo >= ROOT_LOWP_FLOOR && !wide);
+    S.next_tier = to_pair ? TIER_PAIR : S.tier;
+    S.handover = to_pair ? 1 : 0;
+    S.pair_m = c.next_linear;
+    S.dmax = dm1;
+    S.lo_d = T.image.lo; S.hi_d = T.image.hi;
+    *state = st;
+}
+
+// One workgroup per factor: scaling, start of the interval, and the decision about iteration 0.
+__global__ __launch_bounds__(256) void plane_setup_kernel(const FactorDev *fd, FactorScal *fs, int *state, float margin, PlaneControl c,
+                                                          uint2 *map128, uint2 *map64)
+{
+    const int f = blockIdx.x;
+    const FactorDev &F = fd[f];
+    FactorScal &S = fs[f];
+    const int tid = threadIdx.x, n = F.n;
+    __shared__ double red[3][4];
+    // factor and tile of every workgroup of the tile-indexed launches
+    for (int t = tid; t < F.ntri; t += 256) {
+        int ti, tj;
+        tri_decode(t, ti, tj);
+        map128[F.tile_start + t] = make_uint2((unsigned)f, ((unsigned)ti << 16) | (unsigned)tj);
+    }
+    if (map64) {
+        const int t64 = (n + 63) / 64, nt = t64 * (t64 + 1) / 2;
+        for (int t = tid; t < nt; t += 256) {
+            int ti, tj;
+            tri_decode(t, ti, tj);
+            map64[F.tile_start64 + t] = make_uint2((unsigned)f, ((unsigned)ti << 16) | (unsigned)tj);
+        }
+    }
+    for (int t = tid; t < F.npart; t += 256) F.partial[t] = 0.0f;
+    double mx = 0.0, tr = 0.0;
+    for (int i = tid; i < n; i += 256) {
+        const double d = (double)F.A[F.a_packed ? packed_off(i, i) : (size_t)i * F.lda + i];
+        mx = fmax(mx, d);
+        tr += d;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) { mx = fmax(mx, __shfl_xor(mx, off, 64)); tr += __shfl_xor(tr, off, 64); }
+    if ((tid & 63) == 0) { red[0][tid >> 6] = mx; red[1][tid >> 6] = tr; }
+    __syncthreads();
+    if (tid != 0) return;
+    mx = fmax(fmax(red[0][0], red[0][1]), fmax(red[0][2], red[0][3]));
+    tr = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    const float lam = S.rho;
+    S.lam = lam; S.iters = 0; S.xloc = 0; S.resid = 0.0f;
+    F.flags[0] = 0;
+    const float eps = F.eps_in * lam;
+    S.eps = eps;
+    const float denom = (1.0f + margin) * lam + eps;
+    const bool ok = (lam == lam) && (lam >= 0.0f) && (lam < 3.0e38f) && (denom > 0.0f) && (denom < 3.0e38f);
+    if (!ok) {
+        S.scale = 0.0f; S.info = ASTERIA_INFO_NOT_PD; S.tier = TIER_PAIR;
+        state[f] = ST_FAIL;
+        return;
+    }
+    S.scale = 1.0f / denom;
+    S.info = ASTERIA_INFO_OK;
+    state[f] = ST_RUN;
+    const double sc = (double)S.scale, e = (double)eps;
+    // spectrum of M_0 = s (A + eps I): at most 1 by the scaling; at least eps s for a positive semi-definite A
+    // (halved: round-off in the statistics may push eigenvalues slightly below 0)
+    double lo = 0.5 * e / (double)denom;
+    if (!(lo > 1e-12)) lo = 1e-12;
+    // ||M_0 - I||_F bounds every |mu - 1|: a well-conditioned factor gets a much tighter interval
+    const double f2 = (double)S.fro2 + 2.0 * e * tr + n * e * e;
+    double r2 = sc * sc * f2 - 2.0 * sc * (tr + n * e) + n;
+    const double rs = r2 * (1.0 + 1e-3) + 1e-6 * n;                  // slack for the fp32 sums
+    if (rs > 0.0 && rs < 1.0) { const double l1 = 1.0 - sqrt(rs); if (l1 > lo) lo = l1; }
+    if (!(r2 > 1e-6 * n)) r2 = 1e-6 * n;
+    // |X_k| <= xs (2 / lo)^(1/4) for every iterate (see root_setup_kernel): the fp16 terms of X are scaled by the
+    // largest power of two that keeps this below 30000
+    const double bound = sqrt(sqrt(sc)) * sqrt(sqrt(2.0 / lo));
+    int ex = (int)floor(log2(30000.0 / bound));
+    ex = ex < -60 ? -60 : (ex > 60 ? 60 : ex);
+    S.x_scale = (float)ldexp(1.0, ex);
+    S.dmax = fmax(sc * (mx + e), 1e-30);
+    S.lo_d = lo; S.hi_d = 1.0;
+    plane_advance(F, S, &state[f], (float)sqrt(r2), c);
+}
+
+// One wavefront per factor before iteration k >= 1 and after the last one.
+__global__ __launch_bounds__(64) void plane_control_kernel(const FactorDev *fd, FactorScal *fs, int *state, PlaneControl c)
+{
+    const int f = blockIdx.x;
+    const int st = state[f];
+    if (st == ST_DONE || st == ST_FAIL) return;
+    if (st == ST_LAST) {
+        if (threadIdx.x == 0) state[f] = ST_DONE;
+        return;
+    }
+    const FactorDev &F = fd[f];
+    FactorScal &S = fs[f];
+    float r2 = 0.0f;
+    for (int i = threadIdx.x; i < F.npart; i += 64) {
+        r2 += F.partial[i];
+        F.partial[i] = 0.0f;
+    }
+    r2 = wave_sum(r2);
+    if (threadIdx.x != 0) return;
+    if (!(r2 == r2) || !(r2 < 3.0e38f) || F.flags[0]) {
+        S.info = ASTERIA_INFO_NOT_PD;
+        S.resid = sqrtf(r2);
+        state[f] = ST_FAIL;
+        return;
+    }
+    plane_advance(F, S, &state[f], sqrtf(r2), c);
+}
+
+// M_0 = s (A + eps I) of one 128 x 128 tile and its mirror image in the storage of the factor's tier, and where T
+// is linear X_1 = X_0 T_0.  64 x 64 sub-tiles of A and of its transposed position through LDS; a thread then owns
+// 16 consecutive columns of a row.  HBM-bound: 4 bytes read, 4 or 5 written per element (8 or 9 with X_1).
+__global__ __launch_bounds__(256) void plane_init_kernel(const FactorDev *fd, const FactorScal *fs, const int *state, const uint2 *map, int linear)
+{
+    const uint2 tile = map[blockIdx.x];
+    const int f = (int)tile.x;
+    if (state[f] == ST_FAIL) return;
+    const FactorDev &F = fd[f];
+    const FactorScal &S = fs[f];
+    const int ti = (int)(tile.y >> 16), tj = (int)(tile.y & 0xffffu);
+    const int n = F.n, lda = F.lda, tid = threadIdx.x;
+    const double s = (double)S.scale, eps = (double)S.eps;
+    const int tier = S.tier, ns = S.ns;
+    const double inv_q = tier == TIER_DIGIT ? ldexp(1.0, -S.dexp[0]) : 0.0;
+    const float x1a = S.x1a, x1e = S.x1s * S.x1b;
+    const bool packed = F.a_packed != 0;
+    const float *Ap = packed ? F.A + (size_t)(ti * (ti + 1) / 2 + tj) * PACK_T * PACK_T : nullptr;
+    const bool vec = packed || ((lda & 3) == 0 && (reinterpret_cast<uintptr_t>(F.A) & 15u) == 0);
+    __shared__ float Pw[64][65], Qw[64][65];
+    bool over = false;
+    // 16 columns c0 .. of row r of the symmetrised matrix: get(e) is the entry of A
+    auto emit = [&](int r, int c0, auto get) {
+        if (r >= n || c0 >= plane_groups(n) * 32) return;
+        double m[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) m[e] = (c0 + e < n) ? s * (get(e) + (r == c0 + e ? eps : 0.0)) : 0.0;
+        uint32_t w[16];
+        const int grp = c0 >> 5, hf = (c0 >> 4) & 1;
+        auto put_pair = [&](char *M) {
+            char *d = M + (size_t)r * F.rowb + grp * 128 + hf * 32;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                u32x4 hi, lo;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    hi[e] = __builtin_amdgcn_perm(w[8 * q + 2 * e + 1], w[8 * q + 2 * e], 0x05040100u);
+                    lo[e] = __builtin_amdgcn_perm(w[8 * q + 2 * e + 1], w[8 * q + 2 * e], 0x07060302u);
+                }
+                *(ASTERIA_GLOBAL u32x4 *)(d + q * 16) = hi;
+                *(ASTERIA_GLOBAL u32x4 *)(d + 64 + q * 16) = lo;
+            }
+        };
+        if (tier == TIER_DIGIT) {
+            uint32_t t;
+            u32x4 top = {0u, 0u, 0u, 0u};
+            if (ns == 4) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) w[e] = digit_word<4>(rint(m[e] * inv_q), t, over);
+                store_digit_chunk<4>(F.D[0] + (size_t)r * digit_row_bytes(n, 4) + grp * 128 + hf * 16, w, top);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) { w[e] = digit_word<5>(rint(m[e] * inv_q), t, over); top[e >> 2] |= t << (8 * (e & 3)); }
+                store_digit_chunk<5>(F.D[0] + (size_t)r * digit_row_bytes(n, 5) + grp * 160 + hf * 16, w, top);
+            }
+        } else if (tier == TIER_F64) {
+            double *d = F.F[0] + (size_t)r * F.ld64 + c0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) if (c0 + e < n) d[e] = m[e];
+        }
+        if (tier == TIER_PAIR || linear) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) w[e] = pair_word((float)(m[e] * (double)PAIR_SCALE_M));
+            // a linear T reads M as pair planes in the X update, from the second iteration on: M_0 itself is needed by the chain only
+            if (tier == TIER_PAIR) put_pair(F.P[0]);
+        }
+        if (linear) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                w[e] = c0 + e < n ? pair_word((float)((r == c0 + e ? (double)x1a : 0.0) - (double)x1e * m[e])) : 0u;
+            put_pair(F.X[1]);
+        }
+    };
+    for (int sub = 0; sub < 4; ++sub) {
+        const int si = sub >> 1, sj = sub & 1;
+        if (ti == tj && si < sj) continue;                       // covered by the mirrored sub-tile
+        const int r0 = ti * 128 + si * 64, c0 = tj * 128 + sj * 64;
+        if (r0 >= n || c0 >= n) continue;
+        __syncthreads();
+        {
+            const int g = tid & 15, rw = tid >> 4;               // 16 groups of 4 columns x 16 rows
+            for (int rr = rw; rr < 64; rr += 16) {
+                // P[rr][..] = A(r0 + rr, c0 ..), Q[rr][..] = A(c0 + rr, r0 ..)
+                const int pr = r0 + rr, pc = c0 + 4 * g, qr = c0 + rr, qc = r0 + 4 * g;
+                const float *ps = packed ? Ap + (size_t)(si * 64 + rr) * PACK_T + sj * 64 + 4 * g : F.A + (size_t)pr * lda + pc;
+                if (vec && pr < n && pc + 4 <= n) {
+                    const float4 v = *reinterpret_cast<const float4 *>(ps);
+                    Pw[rr][4 * g] = v.x; Pw[rr][4 * g + 1] = v.y; Pw[rr][4 * g + 2] = v.z; Pw[rr][4 * g + 3] = v.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) Pw[rr][4 * g + e] = (pr < n && pc + e < n) ? ps[e] : 0.0f;
+                }
+                if (!packed) {
+                    const float *qs = F.A + (size_t)qr * lda + qc;
+                    if (vec && qr < n && qc + 4 <= n) {
+                        const float4 v = *reinterpret_cast<const float4 *>(qs);
+                        Qw[rr][4 * g] = v.x; Qw[rr][4 * g + 1] = v.y; Qw[rr][4 * g + 2] = v.z; Qw[rr][4 * g + 3] = v.w;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) Qw[rr][4 * g + e] = (qr < n && qc + e < n) ? qs[e] : 0.0f;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        const int rr = tid >> 2, cg = (tid & 3) * 16;
+        emit(r0 + rr, c0 + cg, [&](int e) {
+            return packed ? (double)Pw[rr][cg + e] : 0.5 * ((double)Pw[rr][cg + e] + (double)Qw[cg + e][rr]);
+        });
+        if (!(ti == tj && si == sj))
+            emit(c0 + rr, r0 + cg, [&](int e) {
+                return packed ? (double)Pw[cg + e][rr] : 0.5 * ((double)Pw[cg + e][rr] + (double)Qw[rr][cg + e]);
+            });
+    }
+    if (over) F.flags[0] = 1;
+}
+
+// Pair planes of a factor whose chain runs on fp64 matrices.  what 0: E (the first iteration's becomes X_1),
+// 1: the next M, where the next iteration reads it as pair planes.
+__global__ __launch_bounds__(256) void plane_from_f64_kernel(const FactorDev *fd, const FactorScal *fs, const int *state, int k, int what)
+{
+    const int f = blockIdx.y;
+    const FactorScal &S = fs[f];
+    if (S.tier != TIER_F64) return;
+    const int st = state[f];
+    if (st != ST_RUN && !(st == ST_LAST && what == 0)) return;
+    if (what == 1 && !S.handover && !S.pair_m) return;
+    const FactorDev &F = fd[f];
+    const int n = F.n, per = plane_groups(n) * 2;
+    const int id = blockIdx.x * 256 + threadIdx.x, r = id / per, c0 = (id % per) * 16;
+    if (r >= n) return;
+    const int slot = what == 0 ? 2 : ((k & 1) ^ 1);
+    const double *src = F.F[slot] + (size_t)r * F.ld64 + c0;
+    const bool x1 = what == 0 && k == 0;
+    uint32_t w[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        double v = c0 + e < n ? src[e] : 0.0;
+        if (x1) v = (r == c0 + e ? (double)S.x1a : 0.0) - (double)S.x1s * v;
+        else v *= what == 0 ? (double)PAIR_SCALE_E : (double)PAIR_SCALE_M;
+        w[e] = c0 + e < n ? pair_word((float)v) : 0u;
+    }
+    char *d = (x1 ? F.X[1] : F.P[slot]) + (size_t)r * F.rowb + (c0 >> 5) * 128 + ((c0 >> 4) & 1) * 32;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        u32x4 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            hi[e] = __builtin_amdgcn_perm(w[8 * q + 2 * e + 1], w[8 * q + 2 * e], 0x05040100u);
+            lo[e] = __builtin_amdgcn_perm(w[8 * q + 2 * e + 1], w[8 * q + 2 * e], 0x07060302u);
+        }
+        *(ASTERIA_GLOBAL u32x4 *)(d + q * 16) = hi;
+        *(ASTERIA_GLOBAL u32x4 *)(d + 64 + q * 16) = lo;
+    }
+}
+
+// Problem tables of the fp64 chain: [parity][E | E2 | E4 | M'], one thread per factor.
+struct PlaneF64Tables { GemmProblem *t[2][4]; };
+__global__ void plane_f64_tables_kernel(const FactorDev *fd, FactorScal *fs, int cnt, int linear, PlaneF64Tables T)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= cnt) return;
+    const FactorDev F = fd[i];
+    const int ops[4] = {OP_SQ, OP_E2, OP_E4, OP_M};
+    GemmProblem p = {};
+    p.M = p.N = p.K = F.n;
+    p.state_idx = i; p.state_mask = 1 << ST_RUN;
+    p.alpha = 1.0f; p.beta = 0.0f;
+    p.lda = p.ldb = p.ldc = F.ld64;
+    p.tile_start = F.tile_start;
+    p.gate = &fs[i].tier;                            // TIER_F64 = 0
+    p.partial = F.partial;
+    for (int pa = 0; pa < 2; ++pa)
+        for (int o = 0; o < 4; ++o) {
+            const RootOperands r = root_operands(ops[o], pa, linear != 0);
+            GemmProblem q = p;
+            q.A = F.F[r.A]; q.B = F.F[r.B]; q.C = F.F[r.C]; q.own = F.F[r.O1];
+            q.coefd = &fs[i].prod[ops[o]].own1;
+            q.flags = GEMM_SYM | (ops[o] == OP_M ? GEMM_EPI_RESID : 0);
+            if (ops[o] == OP_SQ) q.state_mask |= 1 << ST_LAST;
+            T.t[pa][o][i] = q;
+        }
+}
+
+// Outcome of every factor; X from its pair planes where the last update did not write the caller's matrix (a
+// factor that ended with its first update, or ran out of iterations).  Grid: x = groups of 256 pieces of 16
+// columns, y = factor.
+__global__ __launch_bounds__(256) void plane_finalize_kernel(const FactorDev *fd, const FactorScal *fs, const int *state, int first,
+                                                             int32_t *info, int32_t *iters, float *resid, float *lambda_max)
+{
+    const int f = blockIdx.y;
+    const FactorScal &S = fs[f];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (info) info[first + f] = S.info;
+        if (iters) iters[first + f] = S.iters;
+        if (resid) resid[first + f] = S.resid;
+        if (lambda_max) lambda_max[first + f] = S.lam;
+    }
+    if (state[f] == ST_FAIL || S.xloc == 0) return;
+    const FactorDev &F = fd[f];
+    const int n = F.n, per = plane_groups(n) * 2;
+    const float inv = 1.0f / S.x_scale;
+    const char *X = F.X[S.xloc - 1];
+    for (int id = blockIdx.x * 256 + threadIdx.x; id < n * per; id += gridDim.x * 256) {
+        const int r = id / per, c0 = (id % per) * 16;
+        const char *s = X + (size_t)r * F.rowb + (c0 >> 5) * 128 + ((c0 >> 4) & 1) * 32;
+        for (int e = 0; e < 16 && c0 + e < n; ++e) {
+            const float hi = (float)reinterpret_cast<const _Float16 *>(s)[e], lo = (float)reinterpret_cast<const _Float16 *>(s + 64)[e];
+            F.Xout[(size_t)r * F.ldx + c0 + e] = (hi + lo) * inv;
+        }
+    }
+}
+
+// ---- host --------------------------------------------------------------------------------------------
+inline int tri_tiles64(int n) { const int t = (n + 63) / 64; return t * (t + 1) / 2; }
+
+// bytes of one chain slot: digits (5 at most), fp64 where that tier can occur, pairs without a prefix
+inline size_t plane_slot_bytes(int n, bool prefix, bool f64)
+{
+    const size_t pair = Carver::need((size_t)n * pair_row_bytes(n), 1);
+    size_t b = pair;
+    if (prefix) b = std::max(b, Carver::need((size_t)n * digit_row_bytes(n, 5), 1));
+    if (prefix && f64) b = std::max(b, Carver::need((size_t)n * ((n + 1) & ~1), sizeof(double)));
+    return b;
+}
+// X_k, X_{k+1}, the pair planes of slots 1 and 2, and the four chain slots (without a prefix: slots 0 and 3); the
+// pair planes of slots 0 and 3 lie over chain slots 2 and 3: when they are written, E (the former) and E4 of
+// the prefix are dead
+inline size_t plane_factor_bytes(int n, bool prefix, bool f64)
+{
+    return 4 * Carver::need((size_t)n * pair_row_bytes(n), 1) + (prefix ? 4 : 2) * plane_slot_bytes(n, prefix, f64);
+}
+inline size_t plane_small_bytes(int n)
+{
+    return Carver::need(std::max(2 * (size_t)tri_tiles(n), (size_t)tri_tiles64(n)), sizeof(float)) + 256 +
+           ((size_t)tri_tiles(n) + (size_t)tri_tiles64(n)) * sizeof(uint2);
+}
+
+}  // namespace asteria

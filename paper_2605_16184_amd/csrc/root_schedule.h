@@ -72,4 +72,126 @@ ASTERIA_HD inline RootInterval root_image(double lo, double hi, int p, double a,
 
 constexpr double ROOT_THETA = 0.1;   // safety margin of T's positivity: zero of T >= 1.1 hi
 
+// ---- T of degree d <= 3 ---------------------------------------------------------------------------
+// T = c0 I - c1 M (+ c2 M^2 - c3 M^3) moves every eigenvalue by f(mu) = T(mu)^4 mu.  The best T on [lo, hi]
+// brings T(mu) mu^(1/4) as close to 1 as possible: the relative minimax approximation of mu^(-1/4), found by
+// the Remez exchange.  Its extremes are lo, hi and the d roots of T + 4 mu T' in between; from Chebyshev nodes
+// the exchange settles in at most 5 steps for every hi / lo up to 1e9.  T is scaled so that f ranges over
+// 1 -+ E.  What a degree costs and lifts (ratio lo / hi per iteration, small lo): degree 1 4 products (T^2, T^4,
+// T^4 M, X T), 12 x; degree 2 5 products, 36 x; degree 3 6 products, 74 x.
+struct RootPoly {
+    double c[4];          // T(mu) = c[0] + c[1] mu + c[2] mu^2 + c[3] mu^3
+    RootInterval image;   // f([lo, hi])
+};
+
+ASTERIA_HD inline double root_t(const double *c, int d, double x)
+{
+    double t = c[d];
+    for (int i = d - 1; i >= 0; --i) t = t * x + c[i];
+    return t;
+}
+
+ASTERIA_HD inline RootPoly root_poly(double lo, double hi, int d)
+{
+    RootPoly P;
+    P.c[0] = P.c[1] = P.c[2] = P.c[3] = 0.0;
+    if (d == 1) {
+        double a, g;
+        root_coefficients(lo, hi, 4, true, 0.1, a, g);
+        P.c[0] = a; P.c[1] = -g;
+        P.image = root_image(lo, hi, 4, a, g);
+        return P;
+    }
+    // a nearly flat spectrum: the polynomial of a wider interval is accurate enough (deviation 4e-6) and keeps
+    // the exchange away from cancellation
+    const double l = lo < 0.9 * hi ? lo : 0.9 * hi;
+    double x[5], w[5];
+    x[0] = l; x[d + 1] = hi;
+    for (int j = 1; j <= d; ++j) {
+        // cos(pi j / (d + 1)) for d = 2, 3
+        const double cj = d == 2 ? (j == 1 ? 0.5 : -0.5) : (j == 1 ? 0.70710678118654752 : (j == 2 ? 0.0 : -0.70710678118654752));
+        x[j] = l + (hi - l) * 0.5 * (1.0 - cj);
+    }
+    double dd[5] = {0, 0, 0, 0, 0}, e = 0.0;
+    for (int it = 0; it < 6; ++it) {
+        // T(x_i) = (1 + s_i e) w_i with s = -, +, -, ...: the divided difference over all d + 2 points vanishes
+        double num = 0.0, den = 0.0, sg = -1.0;
+        for (int i = 0; i <= d + 1; ++i) {
+            w[i] = 1.0 / sqrt(sqrt(x[i]));
+            double pr = 1.0;
+            for (int j = 0; j <= d + 1; ++j)
+                if (j != i) pr *= x[i] - x[j];
+            const double q = w[i] / pr;
+            num -= q; den += sg * q;
+            sg = -sg;
+        }
+        e = num / den;
+        sg = -1.0;
+        for (int i = 0; i <= d; ++i) { dd[i] = (1.0 + sg * e) * w[i]; sg = -sg; }
+        // Newton's form on x_0 .. x_d, then powers of mu
+        for (int j = 1; j <= d; ++j)
+            for (int i = d; i >= j; --i) dd[i] = (dd[i] - dd[i - 1]) / (x[i] - x[i - j]);
+        double c[4] = {dd[d], 0.0, 0.0, 0.0};
+        for (int i = d - 1; i >= 0; --i) {
+            for (int j = d - i; j > 0; --j) c[j] = c[j - 1] - c[j] * x[i];
+            c[0] = dd[i] - c[0] * x[i];
+        }
+        for (int j = 0; j <= d; ++j) P.c[j] = c[j];
+        // interior extremes of T mu^(1/4): roots of q(mu) = sum (1 + 4 j) c_j mu^j
+        if (d == 2) {
+            const double q0 = c[0], q1 = 5.0 * c[1], q2 = 9.0 * c[2];
+            const double disc = q1 * q1 - 4.0 * q2 * q0;
+            if (!(disc > 0.0)) break;
+            const double s = sqrt(disc), big = -q1 + s;      // c1 < 0, c2 > 0
+            x[2] = big / (2.0 * q2);
+            x[1] = 2.0 * q0 / big;
+        } else {
+            // Newton from the points so far, each root deflated by nothing: they are well apart
+            const double q[4] = {c[0], 5.0 * c[1], 9.0 * c[2], 13.0 * c[3]};
+            for (int j = 1; j <= 3; ++j) {
+                double y = x[j];
+                for (int t = 0; t < 4; ++t) {
+                    const double fv = ((q[3] * y + q[2]) * y + q[1]) * y + q[0], fd = (3.0 * q[3] * y + 2.0 * q[2]) * y + q[1];
+                    if (fd == 0.0) break;
+                    double z = y - fv / fd;
+                    const double a = 0.5 * (x[j - 1] + y), b = 0.5 * (y + x[j + 1]);   // stay between the neighbours
+                    z = z < a ? a : (z > b ? b : z);
+                    y = z;
+                }
+                x[j] = y;
+            }
+        }
+    }
+    // f at the ends and at the interior extremes, whatever the exchange has reached
+    double fmin = 1e300, fmax = -1e300;
+    for (int i = 0; i <= d + 1; ++i) {
+        const double t = root_t(P.c, d, x[i]), f = t * t * t * t * x[i];
+        fmin = f < fmin ? f : fmin; fmax = f > fmax ? f : fmax;
+    }
+    const double s4 = 2.0 / (fmin + fmax), s = sqrt(sqrt(s4));
+    for (int j = 0; j <= d; ++j) P.c[j] *= s;
+    P.image.lo = fmin * s4; P.image.hi = fmax * s4;
+    return P;
+}
+
+// Degrees of T by iteration for a spectrum of M_0 in [lo0, 1]: the sequence of least cost (a product counts 1,
+// in the fp64 iterations, of degree 2 at most, 1.5) whose last image lies within 1 -+ 2.6e-3, from an exhaustive
+// search.  `from`:
+// the sequence holds from this lo0 up to the next entry's.  Below the first entry (three and more fp64
+// iterations) T stays linear.
+struct RootDegrees { double from; const char *deg; };
+inline const char *root_degrees(double lo0)
+{
+    static const RootDegrees tab[] = {
+        {1.3e-7, "112233"}, {2.0e-7, "22333"}, {4.0e-7, "22233"}, {8.0e-7, "22223"}, {2.0e-6, "22222"}, {2.6e-6, "12223"},
+        {6.4e-6, "2333"}, {1.3e-5, "2233"}, {3.0e-5, "2223"}, {4.1e-5, "1233"}, {8.0e-5, "2222"}, {1.05e-4, "1223"},
+        {2.0e-4, "1222"}, {2.6e-4, "333"}, {5.1e-4, "233"}, {1.05e-3, "223"}, {2.6e-3, "222"}, {3.3e-3, "123"},
+        {6.4e-3, "122"}, {1.05e-2, "113"}, {1.6e-2, "33"}, {3.2e-2, "23"}, {6.4e-2, "22"}, {8.2e-2, "13"}, {0.17, "12"},
+        {0.41, "3"}, {0.64, "2"}};
+    const char *d = "";
+    for (const RootDegrees &e : tab)
+        if (lo0 >= e.from) d = e.deg;
+    return d;
+}
+
 }  // namespace asteria
