@@ -38,6 +38,7 @@
 #include "gemm_bf16.h"
 #include "gemm_i8.h"
 #include "root_factor.h"
+#include "root_lanczos.h"
 #include "root_products.h"
 #include "root_schedule.h"
 
@@ -49,7 +50,6 @@ inline size_t plane_small_bytes(int n);      // root_plane_path.h
 
 namespace {
 
-constexpr int PM_ROWS = 32;   // rows of A per mat-vec workgroup (8 per wavefront)
 // spectrum of M within 1 +- ROOT_STOP_DEV: one more X update finishes the factor
 constexpr float ROOT_STOP_DEV = 1e-2f;
 // accepted truncation error of the result per eigen-direction (a third of the 2e-3 accuracy bar
@@ -62,13 +62,6 @@ constexpr int PM_TILE_WORDS = 2 * PACK_T + 2;   // floats per tile in pm_tile
 // so 2^10 keeps them under 2^15 with the fp16 range ending at 65504.
 constexpr float ROOT_F16_SCALE = 1024.0f;
 
-__device__ __forceinline__ float hash_unit(uint32_t f, uint32_t j)
-{
-    uint32_t x = j * 0x9E3779B1u + f * 0x85EBCA77u + 0x165667B1u;
-    x ^= x >> 15; x *= 0x2C1B3C6Du; x ^= x >> 12; x *= 0x297A2D39u; x ^= x >> 15;
-    return (float)(x >> 8) * (1.0f / 8388608.0f) - 1.0f;   // [-1, 1)
-}
-
 __device__ __forceinline__ float wave_sum(float v)
 {
 #pragma unroll
@@ -76,14 +69,7 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// ---- lambda_max: Lanczos process --------------------------------------------------------------
-// v_0 a fixed pseudo-random vector; step j: y = A v_j (the mat-vec kernels below), alpha_j = v_j^T y,
-// w = y - alpha_j v_j - beta_{j-1} v_{j-1}, beta_j = ||w||, v_{j+1} = w / beta_j.  The estimate is the
-// largest eigenvalue of the tridiagonal matrix (alpha, beta) of the steps so far: it rises monotonically
-// to lambda_max and gets there in about 1 / sqrt(gap) steps where plain power iteration needs 1 / gap (a
-// statistic whose leading eigenvalues lie 1 % apart: 30 - 40 steps for 1e-5, against 2e-3 after 256 power
-// steps).  No re-orthogonalisation: what fp32 round-off does to the later vectors produces copies of
-// converged Ritz values, never one above lambda_max by more than round-off.
+// ---- lambda_max of large packed statistics (root_lanczos.h has the process and the other kernels) ---------
 // one workgroup (256 threads) per factor: start vector and its norm
 __global__ __launch_bounds__(256) void pm_init_kernel(const FactorDev *fd, FactorScal *fs)
 {
@@ -110,43 +96,29 @@ __global__ __launch_bounds__(256) void pm_init_kernel(const FactorDev *fd, Facto
     }
 }
 
-// y = A v for PM_ROWS rows of one factor; v = v_raw * inv_norm on the fly.
-// Grid: x = row block, y = factor - a finished factor's workgroups leave after two loads, which
-// keeps the launches that follow a factor's convergence cheap.
-__global__ __launch_bounds__(256) void pm_matvec_kernel(const FactorDev *fd, const FactorScal *fs,
-                                                        int nf, int src, int dst, int first)
+// y = A v for LZ_ROWS rows of one factor in full storage, for batches that mix both storages and for factors
+// whose vectors do not fit LDS.
+__global__ __launch_bounds__(256) void pm_matvec_kernel(const FactorDev *fd, const FactorScal *fs, int src, int dst, int first)
 {
-    const int lo = blockIdx.y;
-    if (fs[lo].pm_done) return;
-    const FactorDev &F = fd[lo];
-    if (F.a_packed) return;                  // packed statistics take the tile kernels below
+    const int f = blockIdx.y;
+    if (fs[f].pm_done) return;
+    const FactorDev &F = fd[f];
     const int blk = (int)blockIdx.x;
-    if (blk >= F.pm_blocks) return;
-    const int n = F.n, lda = F.lda;
+    if (F.a_packed || blk >= F.pm_blocks) return;
+    const int n = F.n;
     const float *__restrict__ v = F.pv[src];
     float *__restrict__ y = F.pv[dst];
-    const float inv = fs[lo].inv_norm;
+    const float inv = fs[f].inv_norm;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool vec_ok = ((reinterpret_cast<uintptr_t>(F.A) & 15u) == 0) && ((lda & 3) == 0);
     __shared__ float red[4][4];
     float syy = 0.0f, syv = 0.0f, saa = 0.0f, str = 0.0f;
-    for (int rr = 0; rr < PM_ROWS / 4; ++rr) {
-        const int row = blk * PM_ROWS + wave * (PM_ROWS / 4) + rr;
+    for (int rr = 0; rr < LZ_ROWS / 4; ++rr) {
+        const int row = blk * LZ_ROWS + wave * (LZ_ROWS / 4) + rr;
         if (row >= n) break;
-        const float *__restrict__ a = F.A + (size_t)row * lda;
-        float s = 0.0f, q = 0.0f;   // q: sum of squares of the row (first step only uses it)
-        if (vec_ok) {
-            const int n4 = n >> 2;
-            for (int j = lane; j < n4; j += 64) {
-                const float4 av = reinterpret_cast<const float4 *>(a)[j];
-                const float4 vv = reinterpret_cast<const float4 *>(v)[j];
-                s += av.x * vv.x + av.y * vv.y + av.z * vv.z + av.w * vv.w;
-                q += av.x * av.x + av.y * av.y + av.z * av.z + av.w * av.w;
-            }
-            for (int j = (n4 << 2) + lane; j < n; j += 64) { s += a[j] * v[j]; q += a[j] * a[j]; }
-        } else {
-            for (int j = lane; j < n; j += 64) { s += a[j] * v[j]; q += a[j] * a[j]; }
-        }
+        const float *__restrict__ a = F.A + (size_t)row * F.lda;
+        float s = 0.0f, q = 0.0f;
+#pragma unroll 4
+        for (int j = lane; j < n; j += 64) { s += a[j] * v[j]; q += a[j] * a[j]; }
         s = wave_sum(s) * inv;
         if (first) q = wave_sum(q);
         if (lane == 0) {
@@ -160,15 +132,13 @@ __global__ __launch_bounds__(256) void pm_matvec_kernel(const FactorDev *fd, con
     if (lane == 0) { red[0][wave] = syy; red[1][wave] = syv; red[2][wave] = saa; red[3][wave] = str; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        F.pm_partial[blk] = make_float2(red[0][0] + red[0][1] + red[0][2] + red[0][3],
-                                        red[1][0] + red[1][1] + red[1][2] + red[1][3]);
+        F.pm_partial[blk] = make_float2(red[0][0] + red[0][1] + red[0][2] + red[0][3], red[1][0] + red[1][1] + red[1][2] + red[1][3]);
         if (first)
-            F.pm_partial2[blk] = make_float2(red[2][0] + red[2][1] + red[2][2] + red[2][3],
-                                             red[3][0] + red[3][1] + red[3][2] + red[3][3]);
+            F.pm_partial2[blk] = make_float2(red[2][0] + red[2][1] + red[2][2] + red[2][3], red[3][0] + red[3][1] + red[3][2] + red[3][3]);
     }
 }
 
-// ---- the same mat-vec for statistics in packed lower tiles -----------------------------------
+// y = A v for statistics in packed lower tiles.
 // One workgroup per stored tile (ti, tj), tj <= ti: it serves both the rows of block ti (T v_tj) and,
 // off the diagonal, the rows of block tj (T^T v_ti), so every element is read once.  The partial
 // products go to the factor's pm_tile array and are summed in a fixed order by pm_packed_reduce_kernel
@@ -260,35 +230,9 @@ __global__ __launch_bounds__(PACK_T) void pm_packed_reduce_kernel(const FactorDe
     }
 }
 
-// Largest eigenvalue of the symmetric tridiagonal matrix with diagonal a[0 .. m) and off-diagonal
-// b[0 .. m - 1), by bisection on the number of eigenvalues below x (signs of the pivots of T - x I).
-__device__ double tridiag_largest(const float *a, const float *b, int m)
-{
-    double lo = (double)a[0], hi = lo;
-    for (int i = 0; i < m; ++i) {
-        const double r = (i > 0 ? fabs((double)b[i - 1]) : 0.0) + (i + 1 < m ? fabs((double)b[i]) : 0.0);
-        lo = fmax(lo, (double)a[i]);               // the largest eigenvalue is at least every diagonal entry
-        hi = fmax(hi, (double)a[i] + r);           // ... and at most the largest Gershgorin bound
-    }
-    if (m == 1 || !(hi > lo)) return lo;
-    for (int it = 0; it < 48; ++it) {
-        const double x = 0.5 * (lo + hi);
-        int below = 0;
-        double d = 1.0;
-        for (int i = 0; i < m; ++i) {
-            const double bb = i > 0 ? (double)b[i - 1] * (double)b[i - 1] : 0.0;
-            d = (double)a[i] - x - (i > 0 ? bb / d : 0.0);
-            if (d == 0.0) d = -1e-300;
-            if (d < 0.0) ++below;
-        }
-        if (below == m) hi = x; else lo = x;
-    }
-    return 0.5 * (lo + hi);
-}
-
 // One workgroup per factor, after the mat-vec of step `it` (y = A v in pv[dst], v in pv[src], the vector
 // before it in pv[prev]): alpha, the next Lanczos vector (over y, unnormalised), beta, the estimate, the stop.
-// A factor stops once two consecutive steps have raised the estimate by less than tol2 of it (or the
+// A factor stops once three consecutive steps have raised the estimate by less than tol2 of it (or the
 // recurrence ends: beta = 0, an invariant subspace, where the estimate is exact).
 __global__ __launch_bounds__(256) void pm_lanczos_kernel(const FactorDev *fd, FactorScal *fs, float tol2, int it,
                                                          int src, int dst, int prev, int first, int last)
@@ -336,20 +280,20 @@ __global__ __launch_bounds__(256) void pm_lanczos_kernel(const FactorDev *fd, Fa
         }
     }
     block_sum4(ww, z1, z2, z3);
-    if (tid != 0) return;
-    if (first) { S.fro2 = (float)aa; S.trace = (float)tr; }
-    if (!finite) { S.rho = NAN; S.pm_done = 1; return; }
+    if (first && tid == 0) { S.fro2 = (float)aa; S.trace = (float)tr; }
+    if (!finite) {
+        if (tid == 0) { S.rho = NAN; S.pm_done = 1; }
+        return;
+    }
     const float beta = (float)sqrt(ww);
-    S.lz_a[it] = alpha;
-    S.lz_b[it] = beta;
-    const double theta = tridiag_largest(S.lz_a, S.lz_b, it + 1);
-    const double before = (double)S.rho;
-    S.rho = (float)theta;
-    // breakdown: A v stayed in the span of the vectors so far (a multiple of the identity, a start vector
-    // that is an eigenvector, rank deficiency exhausted): the largest Ritz value is an eigenvalue
-    const bool ended = !(beta > 1e-7f * fabsf((float)theta)) || !(beta > 0.0f);
-    if (it > 0 && theta - before <= (double)tol2 * fabs(theta)) S.lz_small += 1; else S.lz_small = 0;
-    if (ended || S.lz_small >= 2 || last) { S.pm_done = 1; return; }
+    __shared__ float la[LZ_MAX], lb[LZ_MAX];
+    if (tid < it) { la[tid] = S.lz_a[tid]; lb[tid] = S.lz_b[tid]; }
+    if (tid == 0) { S.lz_a[it] = la[it] = alpha; S.lz_b[it] = lb[it] = beta; }
+    __syncthreads();
+    if (wave != 0) return;
+    const bool stop = lanczos_advance(S, la, lb, it, beta, tol2);
+    if (lane != 0) return;
+    if (stop || last) { S.pm_done = 1; return; }
     S.inv_prev = inv;
     S.inv_norm = 1.0f / beta;
 }
@@ -770,8 +714,8 @@ size_t factor_i8_bytes(int n, int ns)
 
 size_t factor_small_bytes(int n)
 {
-    const int pmb = (n + PM_ROWS - 1) / PM_ROWS;
-    return 3 * Carver::need((size_t)ld4(n), sizeof(float)) + 2 * Carver::need((size_t)pmb, sizeof(float2)) +
+    const int pmb = (n + LZ_ROWS - 1) / LZ_ROWS;
+    return 5 * Carver::need((size_t)ld4(n), sizeof(float)) + 2 * Carver::need(2 * (size_t)pmb, sizeof(float2)) +
            Carver::need(2 * (size_t)tri_tiles(n), sizeof(float)) + Carver::need((size_t)tri_tiles(n) * PM_TILE_WORDS, sizeof(float)) +
            sizeof(FactorDev) + sizeof(FactorScal) +
            2 * sizeof(int) + 16 * sizeof(GemmProblem) + plane_small_bytes(n);
@@ -932,23 +876,61 @@ __global__ void root_tables_kernel(const FactorDev *__restrict__ fd, FactorScal 
     }
 }
 
-// the lambda_max estimate of every factor of a pass
-asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int cnt, const Plan &pl, bool any_full, bool any_packed,
-                                   int pm_blocks_max, int tri_max, int n_max, hipStream_t stream)
+// The lambda_max estimate of every factor of a pass.  Small factors and full batches: one workgroup per factor, one
+// launch.  Otherwise one launch per step - 32 of them, then one workgroup per factor takes what has not settled
+// (a step of n = 1000 costs it about 35 us against 8 for a launch, but most spectra settle in 8 to 30 steps, and a
+// launch that finds nothing to do costs 2.5); from n = 2048 on launches throughout.
+bool lanczos_by_factor(int cnt, int n_max, bool any_packed)
 {
+    return n_max <= LZ_WG_N || (cnt >= LZ_WG_BATCH && n_max <= LZ_WG_MAX_N && !any_packed);
+}
+constexpr int LZ_LAUNCHES = 32, LZ_LAUNCH_N = 2048;
+
+asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int cnt, const Plan &pl, bool any_full, bool any_packed,
+                                   int tri_max, int n_max, hipStream_t stream)
+{
+    const int steps = std::min(pl.power_iters, LZ_MAX);
+    const float tol2 = pl.power_tol * pl.power_tol;
+    const int ld = (n_max + 255) & ~255;
+    const size_t lds = 3 * (size_t)ld * sizeof(float);
+    static bool cfg_f[MAX_DEVICES] = {}, cfg_s[MAX_DEVICES] = {};
+    if (lanczos_by_factor(cnt, n_max, any_packed)) {
+        if (any_packed) hipLaunchKernelGGL(lanczos_unpack_kernel, dim3(tri_max, cnt), dim3(256), 0, stream, d_fd);
+        if (n_max <= 256) {
+            hipLaunchKernelGGL(lanczos_factor_kernel<true>, dim3(cnt), dim3(LZ_THREADS), lds, stream, d_fd, d_fs, tol2, steps, -1, ld);
+        } else {
+            ASTERIA_HIP_TRY(ensure_dynamic_lds(reinterpret_cast<const void *>(lanczos_factor_kernel<false>), 3 * sizeof(float) * LZ_WG_MAX_N, cfg_f));
+            hipLaunchKernelGGL(lanczos_factor_kernel<false>, dim3(cnt), dim3(LZ_THREADS), lds, stream, d_fd, d_fs, tol2, steps, -1, ld);
+        }
+        ASTERIA_HIP_TRY(hipGetLastError());
+        return ASTERIA_OK;
+    }
+    if (!any_packed && n_max <= 16384) {
+        const int blocks = (n_max + LZ_ROWS - 1) / LZ_ROWS;
+        const size_t lds1 = (size_t)ld * sizeof(float);
+        ASTERIA_HIP_TRY(ensure_dynamic_lds(reinterpret_cast<const void *>(lanczos_step_kernel), 16384 * sizeof(float), cfg_s));
+        const int launches = n_max < LZ_LAUNCH_N ? std::min(steps, LZ_LAUNCHES) : steps;
+        for (int j = 0; j < launches; ++j)
+            hipLaunchKernelGGL(lanczos_step_kernel, dim3(blocks + 1, cnt), dim3(256), lds1, stream, d_fd, d_fs, tol2, j, blocks);
+        if (launches < steps || n_max <= LZ_WG_MAX_N) {
+            // the last launch's y is in place, its alpha is not: one workgroup per factor goes on from there
+            ASTERIA_HIP_TRY(ensure_dynamic_lds(reinterpret_cast<const void *>(lanczos_factor_kernel<false>), 3 * sizeof(float) * LZ_WG_MAX_N, cfg_f));
+            hipLaunchKernelGGL(lanczos_factor_kernel<false>, dim3(cnt), dim3(LZ_THREADS), lds, stream, d_fd, d_fs, tol2, steps, launches, ld);
+        }
+        ASTERIA_HIP_TRY(hipGetLastError());
+        return ASTERIA_OK;
+    }
     hipLaunchKernelGGL(pm_init_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs);
-    const int lz_steps = std::min(pl.power_iters, LZ_MAX);
-    for (int it = 0; it < lz_steps; ++it) {
+    for (int it = 0; it < steps; ++it) {
         // the three vectors rotate: v_j in src, A v_j (then v_{j+1}) in dst, v_{j-1} in prev
         const int src = it % 3, dst = (it + 1) % 3, prev = (it + 2) % 3, first = it == 0 ? 1 : 0;
         if (any_full)
-            hipLaunchKernelGGL(pm_matvec_kernel, dim3(pm_blocks_max, cnt), dim3(256), 0, stream, d_fd, d_fs, cnt, src, dst, first);
+            hipLaunchKernelGGL(pm_matvec_kernel, dim3((n_max + LZ_ROWS - 1) / LZ_ROWS, cnt), dim3(256), 0, stream, d_fd, d_fs, src, dst, first);
         if (any_packed) {
             hipLaunchKernelGGL(pm_packed_tile_kernel, dim3(tri_max, cnt), dim3(256), 0, stream, d_fd, d_fs, src, first);
             hipLaunchKernelGGL(pm_packed_reduce_kernel, dim3((n_max + PACK_T - 1) / PACK_T, cnt), dim3(PACK_T), 0, stream, d_fd, d_fs, src, dst, first);
         }
-        hipLaunchKernelGGL(pm_lanczos_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, pl.power_tol * pl.power_tol, it,
-                           src, dst, prev, first, it + 1 == lz_steps ? 1 : 0);
+        hipLaunchKernelGGL(pm_lanczos_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, tol2, it, src, dst, prev, first, it + 1 == steps ? 1 : 0);
     }
     ASTERIA_HIP_TRY(hipGetLastError());
     return ASTERIA_OK;
@@ -986,7 +968,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     int *d_state = cv.take<int>(cnt);
     int *d_flags = cv.take<int>(cnt);
     std::vector<FactorDev> fd(cnt);
-    int tri_total = 0, tri64_total = 0, pm_blocks_max = 0, tri_max = 0, n_max = 0;
+    int tri_total = 0, tri64_total = 0, tri_max = 0, n_max = 0;
     bool any_packed = false, any_full = false;
     double a_min = 1.0;
     const bool prefix = pl.fp64_iters > 0;
@@ -1004,19 +986,23 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         F.npart = std::max(2 * F.ntri, tri_tiles64(n));
         F.flags = d_flags + i;
         F.a_packed = a.a_layout == ASTERIA_LAYOUT_PACKED ? 1 : 0;
-        F.pm_blocks = F.a_packed ? (n + PACK_T - 1) / PACK_T : (n + PM_ROWS - 1) / PM_ROWS;
+        F.pm_blocks = F.a_packed ? (n + PACK_T - 1) / PACK_T : (n + LZ_ROWS - 1) / LZ_ROWS;
+        F.Aw = a.A; F.ldw = a.lda;
         if (F.a_packed) { any_packed = true; tri_max = std::max(tri_max, F.ntri); }
-        else { any_full = true; pm_blocks_max = std::max(pm_blocks_max, F.pm_blocks); }
+        else any_full = true;
         F.eps_in = eps[eps_count == 1 ? 0 : first + i];
         const double er = (double)F.eps_in;
         a_min = std::min(a_min, er / (1.0 + (double)pl.margin + er));
         for (int v = 0; v < 3; ++v) F.pv[v] = cv.take<float>(ld4(n));
-        F.pm_partial = cv.take<float2>((n + PM_ROWS - 1) / PM_ROWS);
-        F.pm_partial2 = cv.take<float2>((n + PM_ROWS - 1) / PM_ROWS);
+        for (int v = 0; v < 2; ++v) F.py[v] = cv.take<float>(ld4(n));
+        F.pm_partial = cv.take<float2>(2 * (size_t)((n + LZ_ROWS - 1) / LZ_ROWS));
+        F.pm_partial2 = cv.take<float2>((n + LZ_ROWS - 1) / LZ_ROWS);
         F.pm_tile = cv.take<float>((size_t)F.ntri * PM_TILE_WORDS);
         F.partial = cv.take<float>(F.npart);
         const size_t pair = (size_t)n * F.rowb, slot = plane_slot_bytes(n, prefix, f64);
         for (int v = 0; v < 2; ++v) F.X[v] = cv.take<char>(pair);
+        // a full copy of packed statistics lies where X_0 would (never written)
+        if (F.a_packed) { F.Aw = reinterpret_cast<const float *>(F.X[0]); F.ldw = F.rowb / 4; }
         F.P[1] = cv.take<char>(pair);
         F.P[2] = cv.take<char>(pair);
         char *region = cv.take<char>((prefix ? 4 : 2) * slot);
@@ -1039,7 +1025,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     const double lo0 = 0.5 * a_min;
     std::vector<int> deg;
     if (pl.fp64_iters <= 2)
-        for (const char *q = root_degrees(lo0); *q; ++q) deg.push_back(*q - '0');
+        for (const char *q = root_degrees(lo0 / ROOT_TOP); *q; ++q) deg.push_back(*q - '0');
     int K;
     if (!deg.empty()) {
         for (int e = 0; e < 3; ++e) deg.push_back(2);
@@ -1057,12 +1043,12 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     ASTERIA_HIP_TRY(upload_async(d_fd, fd.data(), sizeof(FactorDev) * cnt, stream));
     if (f64)
         hipLaunchKernelGGL(plane_f64_tables_kernel, dim3((cnt + 127) / 128), dim3(128), 0, stream, d_fd, d_fs, cnt, linear0 ? 1 : 0, ft);
-    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, pl, any_full, any_packed, pm_blocks_max, tri_max, n_max, stream));
+    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, pl, any_full, any_packed, tri_max, n_max, stream));
 
     // intervals and T of a factor that follows the schedule (the device works in fp32 for the scaling: 1e-5 of slack)
     std::vector<PlaneControl> ctl(K + 1);
     {
-        double lo = lo0 * (1.0 - 1e-5), hi = 1.0;
+        double lo = lo0 * (1.0 - 1e-5), hi = ROOT_TOP;
         for (int k = 0; k <= K; ++k) {
             ctl[k].lo = lo; ctl[k].hi = hi;
             ctl[k].T = root_poly(lo, hi, deg[k]);
@@ -1139,7 +1125,7 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
 
     std::vector<FactorDev> fd(cnt);
     std::vector<int> sq(cnt);
-    int tri_total = 0, sq_total = 0, pm_total = 0, pm_blocks_max = 0, tri_max = 0;
+    int tri_total = 0, sq_total = 0, tri_max = 0;
     bool any_packed = false, any_full = false;
     int n_max = 0;
     double a_min = 1.0;
@@ -1156,19 +1142,20 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
         const int tpr = (n + BM - 1) / BM;
         sq[i] = sq_total; sq_total += tpr * tpr;
         F.a_packed = a.a_layout == ASTERIA_LAYOUT_PACKED ? 1 : 0;
-        // partial sums of the mat-vec: per block of PM_ROWS rows, or per block of 128 rows for packed tiles
-        F.pm_blocks = F.a_packed ? (n + PACK_T - 1) / PACK_T : (n + PM_ROWS - 1) / PM_ROWS;
-        F.pm_block_start = pm_total; pm_total += F.pm_blocks;
+        // partial sums of the mat-vec: per block of LZ_ROWS rows, or per block of 128 rows for packed tiles
+        F.pm_blocks = F.a_packed ? (n + PACK_T - 1) / PACK_T : (n + LZ_ROWS - 1) / LZ_ROWS;
+        F.Aw = a.A; F.ldw = a.lda;
         if (F.a_packed) { any_packed = true; tri_max = std::max(tri_max, F.ntri); }
-        else { any_full = true; pm_blocks_max = std::max(pm_blocks_max, F.pm_blocks); }
+        else any_full = true;
         F.eps_in = eps[eps_count == 1 ? 0 : first + i];
         if (mode == ASTERIA_EPS_RELATIVE) {
             const double er = (double)F.eps_in;
             a_min = std::min(a_min, er / (1.0 + (double)pl.margin + er));
         }
         for (int v = 0; v < 3; ++v) F.pv[v] = cv.take<float>(ld4(n));
-        F.pm_partial = cv.take<float2>((n + PM_ROWS - 1) / PM_ROWS);
-        F.pm_partial2 = cv.take<float2>((n + PM_ROWS - 1) / PM_ROWS);
+        for (int v = 0; v < 2; ++v) F.py[v] = cv.take<float>(ld4(n));
+        F.pm_partial = cv.take<float2>(2 * (size_t)((n + LZ_ROWS - 1) / LZ_ROWS));
+        F.pm_partial2 = cv.take<float2>((n + LZ_ROWS - 1) / LZ_ROWS);
         F.pm_tile = cv.take<float>((size_t)F.ntri * PM_TILE_WORDS);
         F.partial = cv.take<float>(2 * (size_t)F.ntri);
     }
@@ -1196,6 +1183,7 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
         FactorDev &F = fd[i];
         const size_t e32 = (size_t)F.n * F.ld32, e64 = (size_t)F.n * F.ld64;
         F.X32b = cv.take<float>(e32);
+        if (F.a_packed) { F.Aw = F.X32b; F.ldw = F.ld32; }      // room for a full copy while X is not there yet
         F.T32 = cv.take<float>(e32);
         unsigned char *shared = cv.take<unsigned char>(shared_region_bytes(F.n, pl.use64, pl.use32));
         if (pl.use32) {
@@ -1238,7 +1226,7 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
     ASTERIA_HIP_TRY(hipGetLastError());
 
     // 1. lambda_max
-    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, pl, any_full, any_packed, pm_blocks_max, tri_max, n_max, stream));
+    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, pl, any_full, any_packed, tri_max, n_max, stream));
     const int ctl_blocks = (cnt + 127) / 128;
     // 2. scaling, start
     hipLaunchKernelGGL(root_setup_kernel, dim3(ctl_blocks), dim3(128), 0, stream, d_fd, d_fs, d_state, cnt,

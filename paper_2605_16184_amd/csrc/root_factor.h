@@ -32,8 +32,11 @@ struct FactorDev {
     double *T64;
     double *T464;
     // both
-    float *pv[3];       // Lanczos vectors: the current one, the one before it, and A times the current one
-    float2 *pm_partial; // per mat-vec workgroup: (sum y^2, sum y v)
+    const float *Aw;    // A in full storage as the lambda_max estimate reads it: A, or a copy of packed statistics
+    int ldw;
+    float *pv[3];       // Lanczos vectors (packed statistics: the current one, the one before it, A times the current one)
+    float *py[2];       // A times the vectors of the last two steps
+    float2 *pm_partial; // per mat-vec workgroup: (sum y^2, sum y v); two steps' in turn
     float2 *pm_partial2; // per mat-vec workgroup, first step only: (sum a_ij^2, sum a_ii)
     float *partial;     // per lower-triangle tile: sum (M - I)^2 (2 ntri entries: a second one per tile for kernels that split tiles)
     int n, lda, ldx;
@@ -41,7 +44,6 @@ struct FactorDev {
     int ntri;           // lower-triangle tiles
     int tile_start;     // first tile of this factor in tile-indexed launches
     int pm_blocks;
-    int pm_block_start;
     float eps_in;
     int a_packed;       // A lies in packed lower tiles (gemm.h, packed_off): lda unused
     float *pm_tile;     // packed A: per lower tile 2 x 128 partial products of the mat-vec and (sum a^2, trace part)

@@ -1,0 +1,461 @@
+// lambda_max of every factor by a Lanczos process.
+//
+// v_0 a fixed pseudo-random vector; step j: y = A v_j, alpha_j = v_j^T y, w = y - alpha_j v_j - beta_{j-1} v_{j-1},
+// beta_j = ||w||, v_{j+1} = w / beta_j.  The estimate is the largest eigenvalue of the tridiagonal matrix
+// (alpha, beta) of the steps so far: it rises monotonically to lambda_max and gets there in about 1 / sqrt(gap)
+// steps where plain power iteration needs 1 / gap.  No re-orthogonalisation: what fp32 round-off does to the
+// later vectors produces copies of converged Ritz values, never one above lambda_max by more than round-off.
+// A factor stops once three consecutive steps have raised the estimate by less than tol2 of it, or where the
+// recurrence ends (beta = 0, an invariant subspace: the estimate is exact).
+//
+// Who computes a step:
+//   lanczos_factor_kernel   one workgroup per factor takes all steps in one launch: n <= 256 with the matrix in
+//                           registers, larger ones streamed.  For small factors, and for batches that keep every
+//                           CU busy anyway.
+//   lanczos_step_kernel     one launch per step, a factor's rows spread over workgroups: few large factors.  Every
+//                           workgroup forms the next vector by itself from the previous step's y (n elements, against
+//                           n rows of n), so a step is one launch; an extra workgroup keeps the recurrence.
+//   pm_packed_* + pm_lanczos_kernel  large factors in packed lower tiles: every stored tile is read once.
+#pragma once
+#include "gemm.h"
+#include "root_factor.h"
+
+namespace asteria {
+
+constexpr int LZ_ROWS = 32;      // rows of A per workgroup of lanczos_step_kernel
+constexpr int LZ_WG_N = 512;     // largest n that lanczos_factor_kernel takes in any batch
+constexpr int LZ_WG_BATCH = 192; // batch from which it takes every n: the device is full of factors
+constexpr int LZ_WG_MAX_N = 8192;   // its vectors fit LDS
+
+__device__ __forceinline__ float hash_unit(uint32_t f, uint32_t j)
+{
+    uint32_t x = j * 0x9E3779B1u + f * 0x85EBCA77u + 0x165667B1u;
+    x ^= x >> 15; x *= 0x2C1B3C6Du; x ^= x >> 12; x *= 0x297A2D39u; x ^= x >> 15;
+    return (float)(x >> 8) * (1.0f / 8388608.0f) - 1.0f;   // [-1, 1)
+}
+
+// One wavefront: largest eigenvalue of the symmetric tridiagonal matrix with diagonal a[0 .. m) and off-diagonal
+// b[0 .. m - 1), given `before`, that of the leading m - 1 rows (ignored for m = 1).  It lies in
+// [max(before, a_m), max(before, a_m) + |b_{m-1}|]; every lane tests one point of the bracket (all leading minors
+// of x I - T positive, by the three-term recurrence of the characteristic polynomials), so a round narrows it
+// 65-fold: 4 or 5 rounds to 1e-8 instead of 40 bisections.
+__device__ inline double tridiag_largest(const float *a, const float *b, int m, double before)
+{
+    const int lane = threadIdx.x & 63;
+    if (m == 1) return (double)a[0];
+    double lo = fmax(before, (double)a[m - 1]), hi = lo + fabs((double)b[m - 2]);
+    if (!(hi > lo) || !(hi < 1e300) || !(hi > 0.0)) return lo;
+    hi += 1e-9 * hi;
+    const double inv = 1.0 / hi;
+    for (int round = 0; round < 7 && hi - lo > 1e-8 * hi; ++round) {
+        const double x = lo + (hi - lo) * ((double)(lane + 1) * (1.0 / 65.0)), xs = x * inv;
+        double p = 1.0, q = 0.0, b2 = 0.0;             // minors of x I - T, of order i and i - 1
+        bool above = true;
+        for (int i = 0; i < m; ++i) {
+            const double t = (xs - (double)a[i] * inv) * p - b2 * q;
+            q = p; p = t;
+            above = above && p > 0.0;
+            const double bi = (double)b[i] * inv;
+            b2 = bi * bi;
+            if ((i & 15) == 15 && fabs(p) < 1e-60 && fabs(q) < 1e-60) { p *= 1e60; q *= 1e60; }
+        }
+        const uint64_t mask = __ballot(above);
+        const int first = mask ? __ffsll((long long)mask) - 1 : 64;     // first point at or above the largest eigenvalue
+        const double d = (hi - lo) * (1.0 / 65.0);
+        if (first < 64) hi = lo + d * (first + 1);
+        lo = lo + d * first;
+    }
+    return 0.5 * (lo + hi);
+}
+
+// After step j: a, b hold the recurrence up to alpha_j, beta_j (in LDS: every lane walks through it).  One
+// wavefront; returns whether the factor is finished.
+__device__ inline bool lanczos_advance(FactorScal &S, const float *a, const float *b, int j, float beta, float tol2)
+{
+    const double before = j > 0 ? (double)S.rho : 0.0;
+    const double theta = tridiag_largest(a, b, j + 1, before);
+    const bool ended = !(beta > 1e-7f * fabsf((float)theta)) || !(beta > 0.0f);
+    int small = S.lz_small;
+    small = (j > 0 && theta - before <= (double)tol2 * fabs(theta)) ? small + 1 : 0;
+    if ((threadIdx.x & 63) == 0) { S.rho = (float)theta; S.lz_small = small; }
+    return ended || small >= 3;
+}
+
+// ---- one workgroup per factor --------------------------------------------------------------------------
+constexpr int LZ_THREADS = 1024, LZ_WAVES = LZ_THREADS / 64;
+
+__device__ __forceinline__ float row_sum16(float v)       // sum over 16 consecutive lanes
+{
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// RESIDENT: every factor has n <= 256 and is held in registers.  resume >= 0: continue after that many launches
+// of lanczos_step_kernel.
+template <bool RESIDENT>
+__global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const FactorDev *fd, FactorScal *fs, float tol2, int steps, int resume, int ld)
+{
+    const int f = blockIdx.x;
+    FactorScal &S = fs[f];
+    if (resume >= 0 && S.pm_done) return;
+    const FactorDev &F = fd[f];
+    const int n = F.n, lda = F.ldw;
+    const float *__restrict__ A = F.Aw;
+    extern __shared__ __align__(16) float lz_smem[];
+    float *v = lz_smem, *vp = v + ld, *y = vp + ld;          // ld: n of the largest factor, padded to 256
+    __shared__ float red[2][LZ_WAVES];
+    __shared__ double redd[2][LZ_WAVES];
+    __shared__ float la[LZ_MAX], lb[LZ_MAX];
+    __shared__ int done;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool vec = ((reinterpret_cast<uintptr_t>(A) & 15u) == 0) && ((lda & 3) == 0);
+    auto block_sum = [&](double x) -> double {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        __syncthreads();
+        if (lane == 0) redd[0][wave] = x;
+        __syncthreads();
+        double t = 0.0;
+        for (int w = 0; w < LZ_WAVES; ++w) t += redd[0][w];
+        return t;
+    };
+    // n <= 256: lane group g of 16 in wavefront w holds rows 16 w + 4 g .. + 3, lane c of it the columns 4 (c + 16 i) .. + 3
+    float ar[RESIDENT ? 4 : 1][16];
+    const int rg = 16 * wave + 4 * (lane >> 4), cl = lane & 15;
+    if constexpr (RESIDENT) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = rg + q, c = 4 * (cl + 16 * i);
+                if (vec && r < n && c + 4 <= n) {
+                    const float4 t = *reinterpret_cast<const float4 *>(A + (size_t)r * lda + c);
+                    ar[q][4 * i] = t.x; ar[q][4 * i + 1] = t.y; ar[q][4 * i + 2] = t.z; ar[q][4 * i + 3] = t.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ar[q][4 * i + e] = (r < n && c + e < n) ? A[(size_t)r * lda + c + e] : 0.0f;
+                }
+            }
+    }
+    int j0 = 0;
+    float beta_p = 0.0f;
+    if (tid == 0) done = 0;
+    if (resume < 0) {
+        double s = 0.0;
+        for (int i = tid; i < ld; i += LZ_THREADS) {
+            // the same start vector for every factor: a factor's result does not depend on its place in the batch
+            const float x = i < n ? hash_unit(0u, (uint32_t)i) : 0.0f;
+            v[i] = x; vp[i] = 0.0f;
+            s += (double)x * (double)x;
+        }
+        s = block_sum(s);
+        const float inv = s > 0.0 ? (float)(1.0 / sqrt(s)) : 0.0f;
+        for (int i = tid; i < ld; i += LZ_THREADS) v[i] *= inv;
+        double saa = 0.0, str = 0.0;
+        if constexpr (RESIDENT) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) saa += (double)(ar[q][e] * ar[q][e]);
+        }
+        for (int i = tid; i < n; i += LZ_THREADS) str += (double)A[(size_t)i * lda + i];
+        saa = block_sum(saa);                                // streamed factors: gathered in the first product
+        str = block_sum(str);
+        if (tid == 0) { S.fro2 = (float)saa; S.trace = (float)str; S.rho = 0.0f; S.lz_small = 0; S.pm_done = 0; }
+    } else {
+        j0 = resume - 1;                                     // its y is there, its alpha is not
+        for (int i = tid; i < ld; i += LZ_THREADS) {
+            v[i] = i < n ? F.pv[j0 % 3][i] : 0.0f;
+            vp[i] = (i < n && j0 > 0) ? F.pv[(j0 + 2) % 3][i] : 0.0f;
+            y[i] = i < n ? F.py[j0 & 1][i] : 0.0f;
+        }
+        beta_p = j0 > 0 ? S.lz_b[j0 - 1] : 0.0f;
+        if (tid < j0) { la[tid] = S.lz_a[tid]; lb[tid] = S.lz_b[tid]; }
+    }
+    __syncthreads();
+    bool stop = false;                                       // wavefront 0: the recurrence so far has settled
+    for (int j = j0; j < steps; ++j) {
+        float yv = 0.0f;
+        if (j == j0 && resume >= 0) {
+            for (int i = tid; i < n; i += LZ_THREADS) yv += y[i] * v[i];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) yv += __shfl_xor(yv, off, 64);
+        } else if constexpr (RESIDENT) {
+            float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (16 * wave < n) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float4 x = *reinterpret_cast<const float4 *>(v + 4 * (cl + 16 * i));
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        s[q] += ar[q][4 * i] * x.x + ar[q][4 * i + 1] * x.y + ar[q][4 * i + 2] * x.z + ar[q][4 * i + 3] * x.w;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s[q] = row_sum16(s[q]);
+            if (cl == 0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { y[rg + q] = s[q]; yv += s[q] * v[rg + q]; }
+            }
+            yv += __shfl_xor(yv, 16, 64);
+            yv += __shfl_xor(yv, 32, 64);
+        } else {
+            double saa = 0.0;
+            auto product = [&](auto first) {
+                for (int r0 = 4 * wave; r0 < n; r0 += 4 * LZ_WAVES) {
+                    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f}, q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                    const float *ap[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ap[e] = A + (size_t)min(r0 + e, n - 1) * lda;
+                    int c0 = 0;
+                    if (vec) {
+                        const int n4 = n >> 2;
+#pragma unroll 2
+                        for (int c = lane; c < n4; c += 64) {
+                            const float4 x = reinterpret_cast<const float4 *>(v)[c];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float4 t = reinterpret_cast<const float4 *>(ap[e])[c];
+                                s[e] += t.x * x.x + t.y * x.y + t.z * x.z + t.w * x.w;
+                                if constexpr (decltype(first)::value) q[e] += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
+                            }
+                        }
+                        c0 = n4 << 2;
+                    }
+#pragma unroll 4
+                    for (int c = c0 + lane; c < n; c += 64) {
+                        const float x = v[c];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float t = ap[e][c];
+                            s[e] += t * x;
+                            if constexpr (decltype(first)::value) q[e] += t * t;
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                        for (int off = 32; off > 0; off >>= 1) s[e] += __shfl_xor(s[e], off, 64);
+                        if (r0 + e < n) {
+                            if (lane == 0) y[r0 + e] = s[e];
+                            yv += s[e] * v[r0 + e];
+                            if constexpr (decltype(first)::value) saa += (double)q[e];
+                        }
+                    }
+                }
+            };
+            if (j == 0) {
+                product(std::true_type{});
+                saa = block_sum(saa);
+                if (tid == 0) S.fro2 = (float)saa;
+            } else product(std::false_type{});
+        }
+        if (lane == 0) red[0][wave] = yv;
+        if (tid == 0 && stop) done = 1;
+        __syncthreads();
+        if (done) break;
+        double alpha_d = 0.0;
+        for (int w = 0; w < LZ_WAVES; ++w) alpha_d += (double)red[0][w];
+        const float alpha = (float)alpha_d;
+        float ww = 0.0f;
+        for (int i = tid; i < n; i += LZ_THREADS) {
+            const float x = y[i] - alpha * v[i] - beta_p * vp[i];
+            y[i] = x;
+            ww += x * x;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) ww += __shfl_xor(ww, off, 64);
+        if (lane == 0) red[1][wave] = ww;
+        __syncthreads();
+        double ww_d = 0.0;
+        for (int w = 0; w < LZ_WAVES; ++w) ww_d += (double)red[1][w];
+        const float beta = (float)sqrt(ww_d);
+        if (!(beta < 3.0e38f) || !(fabsf(alpha) < 3.0e38f)) {         // non-finite input (uniform)
+            if (tid == 0) S.rho = NAN;
+            break;
+        }
+        const float inv = beta > 0.0f ? 1.0f / beta : 0.0f;
+        for (int i = tid; i < n; i += LZ_THREADS) {
+            const float t = v[i];
+            v[i] = y[i] * inv;
+            vp[i] = t;
+        }
+        beta_p = beta;
+        if (tid == 0) { la[j] = alpha; lb[j] = beta; }
+        __syncthreads();
+        // the recurrence is looked at by one wavefront while the others go on to the next product: they stop one
+        // step later than they could
+        if (wave == 0) stop = lanczos_advance(S, la, lb, j, beta, tol2);
+    }
+    if (tid == 0) S.pm_done = 1;
+}
+
+// ---- one launch per step -------------------------------------------------------------------------------
+// Grid: x = row block, plus one that keeps the recurrence; y = factor.  Launch j: v_j from step j - 1, y_j = A v_j.
+__global__ __launch_bounds__(256) void lanczos_step_kernel(const FactorDev *fd, FactorScal *fs, float tol2, int j, int blocks)
+{
+    const int f = blockIdx.y;
+    FactorScal &S = fs[f];
+    if (j > 0 && S.pm_done) return;
+    const FactorDev &F = fd[f];
+    const bool keeper = (int)blockIdx.x == blocks;
+    if (!keeper && (int)blockIdx.x >= F.pm_blocks) return;
+    const int n = F.n, lda = F.ldw;
+    extern __shared__ __align__(16) float lz_smem[];
+    float *v = lz_smem;
+    __shared__ double redd[4];
+    __shared__ float red[2][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto block_sum = [&](double x) -> double {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        __syncthreads();
+        if (lane == 0) redd[wave] = x;
+        __syncthreads();
+        return redd[0] + redd[1] + redd[2] + redd[3];
+    };
+    float alpha = 0.0f, beta = 0.0f;
+    double ww = 0.0;
+    if (j == 0) {
+        for (int i = tid; i < n; i += 256) { const float x = hash_unit(0u, (uint32_t)i); v[i] = x; ww += (double)x * (double)x; }
+    } else {
+        double yv = 0.0;
+        for (int b = tid; b < F.pm_blocks; b += 256) yv += (double)F.pm_partial[((j - 1) & 1) * F.pm_blocks + b].y;
+        alpha = (float)block_sum(yv);
+        const float *__restrict__ y = F.py[(j - 1) & 1], *__restrict__ v1 = F.pv[(j - 1) % 3], *__restrict__ v2 = F.pv[(j + 1) % 3];
+        const float beta_p = j > 1 ? S.lz_b[j - 2] : 0.0f;
+        for (int i = tid; i < n; i += 256) {
+            float x = y[i] - alpha * v1[i];
+            if (j > 1) x -= beta_p * v2[i];
+            v[i] = x;
+            ww += (double)x * (double)x;
+        }
+    }
+    ww = block_sum(ww);
+    beta = (float)sqrt(ww);
+    const float inv = beta > 0.0f ? 1.0f / beta : 0.0f;
+    for (int i = tid; i < n; i += 256) v[i] *= inv;
+    __syncthreads();
+    if (keeper) {
+        for (int i = tid; i < n; i += 256) F.pv[j % 3][i] = v[i];
+        if (j == 0) {
+            if (tid == 0) { S.rho = 0.0f; S.lz_small = 0; S.pm_done = 0; }
+            return;
+        }
+        if (j == 1) {
+            double aa = 0.0, tr = 0.0;
+            for (int b = tid; b < F.pm_blocks; b += 256) { const float2 q = F.pm_partial2[b]; aa += (double)q.x; tr += (double)q.y; }
+            aa = block_sum(aa);
+            tr = block_sum(tr);
+            if (tid == 0) { S.fro2 = (float)aa; S.trace = (float)tr; }
+        }
+        if (!(beta < 3.0e38f) || !(fabsf(alpha) < 3.0e38f)) {
+            if (tid == 0) { S.rho = NAN; S.pm_done = 1; }
+            return;
+        }
+        __shared__ float la[LZ_MAX], lb[LZ_MAX];
+        if (tid < j - 1) { la[tid] = S.lz_a[tid]; lb[tid] = S.lz_b[tid]; }
+        if (tid == 0) { S.lz_a[j - 1] = la[j - 1] = alpha; S.lz_b[j - 1] = lb[j - 1] = beta; }
+        __syncthreads();
+        if (wave == 0) {
+            const bool stop = lanczos_advance(S, la, lb, j - 1, beta, tol2);
+            if (lane == 0 && stop) S.pm_done = 1;
+        }
+        return;
+    }
+    const float *__restrict__ A = F.Aw;
+    const bool vec = ((reinterpret_cast<uintptr_t>(A) & 15u) == 0) && ((lda & 3) == 0);
+    float syv = 0.0f, saa = 0.0f, str = 0.0f;
+    const int base = blockIdx.x * LZ_ROWS + wave * (LZ_ROWS / 4);
+#pragma unroll 1
+    for (int rr = 0; rr < LZ_ROWS / 4; rr += 4) {
+        const int r0 = base + rr;
+        if (r0 >= n) break;
+        float s[4] = {0.0f, 0.0f, 0.0f, 0.0f}, q = 0.0f;
+        const float *a0 = A + (size_t)r0 * lda, *a1 = A + (size_t)min(r0 + 1, n - 1) * lda;
+        const float *a2 = A + (size_t)min(r0 + 2, n - 1) * lda, *a3 = A + (size_t)min(r0 + 3, n - 1) * lda;
+        const float m1 = r0 + 1 < n ? 1.0f : 0.0f, m2 = r0 + 2 < n ? 1.0f : 0.0f, m3 = r0 + 3 < n ? 1.0f : 0.0f;
+        int c0 = 0;
+        if (vec) {
+            const int n4 = n >> 2;
+#pragma unroll 2
+            for (int c = lane; c < n4; c += 64) {
+                const float4 x = reinterpret_cast<const float4 *>(v)[c];
+                const float4 t0 = reinterpret_cast<const float4 *>(a0)[c], t1 = reinterpret_cast<const float4 *>(a1)[c];
+                const float4 t2 = reinterpret_cast<const float4 *>(a2)[c], t3 = reinterpret_cast<const float4 *>(a3)[c];
+                s[0] += t0.x * x.x + t0.y * x.y + t0.z * x.z + t0.w * x.w;
+                s[1] += t1.x * x.x + t1.y * x.y + t1.z * x.z + t1.w * x.w;
+                s[2] += t2.x * x.x + t2.y * x.y + t2.z * x.z + t2.w * x.w;
+                s[3] += t3.x * x.x + t3.y * x.y + t3.z * x.z + t3.w * x.w;
+                if (j == 0)
+                    q += t0.x * t0.x + t0.y * t0.y + t0.z * t0.z + t0.w * t0.w + m1 * (t1.x * t1.x + t1.y * t1.y + t1.z * t1.z + t1.w * t1.w) +
+                         m2 * (t2.x * t2.x + t2.y * t2.y + t2.z * t2.z + t2.w * t2.w) + m3 * (t3.x * t3.x + t3.y * t3.y + t3.z * t3.z + t3.w * t3.w);
+            }
+            c0 = n4 << 2;
+        }
+#pragma unroll 4
+        for (int c = c0 + lane; c < n; c += 64) {
+            const float x = v[c];
+            s[0] += a0[c] * x; s[1] += a1[c] * x; s[2] += a2[c] * x; s[3] += a3[c] * x;
+            if (j == 0) q += a0[c] * a0[c] + m1 * a1[c] * a1[c] + m2 * a2[c] * a2[c] + m3 * a3[c] * a3[c];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) s[e] += __shfl_xor(s[e], off, 64);
+            if (r0 + e < n) {
+                syv += s[e] * v[r0 + e];
+                if (lane == 0) F.py[j & 1][r0 + e] = s[e];
+                if (j == 0) str += A[(size_t)(r0 + e) * lda + r0 + e];
+            }
+        }
+        if (j == 0) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off, 64);
+            saa += q;
+        }
+    }
+    if (lane == 0) red[0][wave] = syv;
+    __syncthreads();
+    if (tid == 0) F.pm_partial[(j & 1) * F.pm_blocks + blockIdx.x] = make_float2(0.0f, red[0][0] + red[0][1] + red[0][2] + red[0][3]);
+    if (j == 0) {
+        __syncthreads();
+        if (lane == 0) { red[0][wave] = saa; red[1][wave] = str; }
+        __syncthreads();
+        if (tid == 0)
+            F.pm_partial2[blockIdx.x] = make_float2(red[0][0] + red[0][1] + red[0][2] + red[0][3], red[1][0] + red[1][1] + red[1][2] + red[1][3]);
+    }
+}
+
+// Full copy of packed statistics for the workgroup-per-factor kernel: 128 x 128 stored tiles, their mirror images
+// through LDS.  Grid: x = lower tile, y = factor.
+__global__ __launch_bounds__(256) void lanczos_unpack_kernel(const FactorDev *fd)
+{
+    const FactorDev &F = fd[blockIdx.y];
+    if (!F.a_packed || (int)blockIdx.x >= F.ntri) return;
+    int ti, tj;
+    tri_decode((int)blockIdx.x, ti, tj);
+    const float *tile = F.A + (size_t)blockIdx.x * PACK_T * PACK_T;
+    float *dst = const_cast<float *>(F.Aw);
+    const int n = F.n, ld = F.ldw, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    __shared__ float s[32][33];
+    for (int sub = 0; sub < 16; ++sub) {
+        const int r0 = (sub >> 2) * 32, c0 = (sub & 3) * 32;
+        __syncthreads();
+        for (int r = ty; r < 32; r += 8) {
+            const float x = tile[(r0 + r) * PACK_T + c0 + tx];
+            s[r][tx] = x;
+            const int gr = ti * PACK_T + r0 + r, gc = tj * PACK_T + c0 + tx;
+            if (gr < n && gc < n) dst[(size_t)gr * ld + gc] = x;
+        }
+        __syncthreads();
+        if (ti != tj)
+            for (int r = ty; r < 32; r += 8) {
+                const int gr = tj * PACK_T + c0 + r, gc = ti * PACK_T + r0 + tx;
+                if (gr < n && gc < n) dst[(size_t)gr * ld + gc] = s[tx][r];
+            }
+    }
+}
+
+}  // namespace asteria

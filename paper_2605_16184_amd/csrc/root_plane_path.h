@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256) void plane_setup_kernel(const FactorDev *fd, F
     ex = ex < -60 ? -60 : (ex > 60 ? 60 : ex);
     S.x_scale = (float)ldexp(1.0, ex);
     S.dmax = fmax(sc * (mx + e), 1e-30);
-    S.lo_d = lo; S.hi_d = 1.0;
+    S.lo_d = lo; S.hi_d = ROOT_TOP;
     plane_advance(F, S, &state[f], (float)sqrt(r2), c);
 }
 

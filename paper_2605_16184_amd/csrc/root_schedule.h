@@ -174,7 +174,13 @@ ASTERIA_HD inline RootPoly root_poly(double lo, double hi, int d)
     return P;
 }
 
-// Degrees of T by iteration for a spectrum of M_0 in [lo0, 1]: the sequence of least cost (a product counts 1,
+// The schedule starts from [lo0, ROOT_TOP]: an estimate of the largest eigenvalue up to 5 % low (beyond the scaling's
+// own margin) stays inside the interval.  A T of even degree grows beyond it, 20-fold per iteration; Lanczos from one
+// start vector is that low where the vector hardly meets the top eigenvector and the gap below it is a few per cent
+// (one factor in about 1e4 at a gap of 1 %).
+constexpr double ROOT_TOP = 1.05;
+
+// Degrees of T by iteration for a spectrum of M_0 in [lo0, 1] (relative to its top): the sequence of least cost (a product counts 1,
 // in the fp64 iterations, of degree 2 at most, 1.5) whose last image lies within 1 -+ 2.6e-3, from an exhaustive
 // search.  `from`:
 // the sequence holds from this lo0 up to the next entry's.  Below the first entry (three and more fp64
