@@ -13,14 +13,11 @@
 //              thin QR factor of Z with diag(R) > 0 - the same Q a Householder QR with that sign
 //              convention returns, since the factorisation is unique - by block Gram-Schmidt
 //              with re-orthogonalisation: panels of 128 columns; each panel is projected twice
-//              against all finished panels (two grouped fp32-MFMA GEMMs per projection, so the
-//              O(n^3) work runs on the matrix cores), then orthonormalised by Cholesky QR applied
-//              twice: Gram matrix of the panel on the fp64 matrix cores, 128 x 128 Cholesky
-//              factor and its inverse in LDS (fp64), panel <- L^-1 panel on the fp32 matrix
-//              cores.  The second application removes the cond^2 * 2^-24 loss of the first, so
-//              ||Q^T Q - I|| ends at round-off level as long as cond(Z) * 2^-24 < 1, and L's
-//              positive diagonal gives the diag(R) > 0 convention.  A transposing write-back
-//              stores Q.
+//              against all finished panels (two grouped products on the fp16 matrix cores per
+//              projection, so the O(n^3) work runs there), then orthonormalised by Cholesky QR
+//              applied twice (soap_panel.h).  The second application removes the cond^2 * 2^-24
+//              loss of the first, so ||Q^T Q - I|| ends at round-off level as long as
+//              cond(Z) * 2^-24 < 1, and L's positive diagonal gives the diag(R) > 0 convention.
 #include <algorithm>
 #include <vector>
 
@@ -28,6 +25,7 @@
 #include "gemm.h"
 #include "gemm_bf16.h"
 #include "pgemm.h"
+#include "soap_panel.h"
 
 using namespace asteria;
 
@@ -106,37 +104,7 @@ __global__ __launch_bounds__(256) void transpose_f32_kernel(const TransposeF32Jo
 }
 
 // ---------------------------------------------------------------------------------------------
-// Orthonormalisation of Z^T (row c of Zt = column c of Z), in place.
-struct QrFactor {
-    float *Zt;      // n x ldz; rows become the orthonormal columns of Q, in order
-    float *Qout;    // caller's Q (n x ldq)
-    double *gram;   // QR_PANEL x QR_PANEL: Gram matrix of the current panel
-    float *winv;    // QR_PANEL x QR_PANEL: inverse Cholesky factor of the current panel
-    int n, ldz, ldq;
-    int pad0_;
-    int bad;        // set to 1 when a column could not be normalised
-    // Two words the grouped launches read as their per-problem state (a problem runs while its word
-    // is 0): `run` stays 0; `skip3` is 1 unless the second sweep over the current panel found a row
-    // that needs a third one.
-    int run, skip3;
-    int out_index;  // position of this factor in the caller's arrays
-    int pad_;
-    // Powers of two that bring the rows of the current panel into the fp16 range for the projection
-    // coefficients computed on the fp16 cores: a_scale for rows of Z^T as they come out of Q^T A
-    // (bounded by tr A), 2^14 once a sweep has normalised them; p_scale is the one in force.
-    float a_scale, p_scale;
-    const float *A;  // the statistic (read for its trace)
-    int lda, pad2_;
-    float *cbuf;     // QR_PANEL x ldz: projection coefficients of the current panel
-    // Where Q^T stands when a round starts (rows q_i^T: the k-contiguous operand of Z^T = Q^T A): the
-    // caller's Q buffer, transposed in place, or a buffer of the caller that holds Q^T beside Q
-    float *Qt;
-    int ldqt, pad3_;
-    double *est;     // n estimated eigenvalues q_i^T A q_i (column order of the refresh's input)
-    int *perm;       // n: perm[r] = input column that becomes column r
-    int *perm_out;   // the caller's slice of the permutation output, or null
-};
-constexpr float QR_UNIT_SCALE = 16384.0f;
+// Eigenbasis refresh (panel steps: soap_panel.h)
 constexpr int QR_STATE_STRIDE = (int)(sizeof(QrFactor) / sizeof(int));
 static_assert(sizeof(QrFactor) % sizeof(int) == 0, "state words are addressed as ints inside the factor array");
 
@@ -161,175 +129,7 @@ __global__ __launch_bounds__(64) void qr_scale_kernel(QrFactor *fs, int nf)
     }
 }
 
-constexpr int QR_PANEL = 128;
 constexpr int QR_MAXN = 1 << 20;
-
-// One workgroup per (factor, panel).  In: the fp64 Gram matrix G = P P^T of the panel's rows
-// (rows x rows, leading dimension QR_PANEL).  Out: W = L^-1 in fp32, where G = L L^T is the
-// Cholesky factorisation (positive diagonal), so that W P has orthonormal rows and P = L (W P)
-// is the QR relation with a positive diagonal.  Everything runs in LDS in fp64: a right-looking
-// Cholesky on a 16 x 16 thread grid, then the triangular inverse in place, row by row (row i of
-// W needs row i of L and the rows of W above it; one thread per column).
-constexpr int CHOL_THREADS = 256;
-// Sweeps and failure reporting.  A pivot that is not positive (a zero row cannot be normalised)
-// fails the factor.  In the second sweep over a panel (sweep = 1) the rows are those the first
-// sweep normalised, projected once more: a pivot far below 1 there means that a row was
-// numerically dependent - the first normalisation blew round-off up to unit length, most of which
-// lay in the span of the rows before it - and this sweep's normalisation amplifies what the
-// projection left by 1 / sqrt(pivot).  Such a factor takes a third sweep (skip3 = 0), which only
-// its workgroups run; a pivot that small in the third sweep fails the factor.
-constexpr double CHOL_REPEAT_MIN = 0.1;
-constexpr int CHOL_NB = 16;                                   // block size of the factorisation and the inverse
-constexpr int CHOL_PITCH = QR_PANEL + 1;
-// LDS: the matrix (QR_PANEL x CHOL_PITCH doubles) and a block row of CHOL_NB x QR_PANEL doubles
-constexpr size_t CHOL_LDS_BYTES = sizeof(double) * ((size_t)QR_PANEL * CHOL_PITCH + (size_t)CHOL_NB * QR_PANEL);
-
-// Both phases work on blocks of 16 so that the workgroup meets at a barrier a few times per block
-// instead of a few times per column: per block column of the Cholesky factorisation one wavefront
-// factors the 16 x 16 diagonal block (its lanes stay in step through LDS, which a wavefront accesses in
-// order), every row below solves against it, and the trailing matrix takes a rank-16 update; the
-// inverse is formed from the inverses of the diagonal blocks, block row by block row.
-__global__ __launch_bounds__(CHOL_THREADS) void panel_chol_inverse_kernel(QrFactor *fs, int panel, int sweep)
-{
-    QrFactor &F = fs[blockIdx.x];                   // the factors that have this panel are the first ones (sorted by size)
-    if (sweep == 2 && F.skip3) return;              // uniform over the workgroup
-    const int rows = min(QR_PANEL, F.n - panel * QR_PANEL);
-    extern __shared__ __align__(16) unsigned char chol_smem[];
-    double *L = reinterpret_cast<double *>(chol_smem);            // rows x rows, pitch QR_PANEL + 1
-    double *S = L + (size_t)QR_PANEL * CHOL_PITCH;                // CHOL_NB x QR_PANEL
-    constexpr int PITCH = CHOL_PITCH;
-    constexpr int NB = CHOL_NB;
-    __shared__ int bad_flag;
-    const int tid = threadIdx.x;
-    const int ti = tid >> 4, tj = tid & 15;
-    const int lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) bad_flag = 0;
-    // rows and columns beyond `rows` are those of the identity: the blocks need no edge cases
-    for (int i = ti; i < QR_PANEL; i += 16)
-        for (int j = tj; j < QR_PANEL; j += 16)
-            L[i * PITCH + j] = (i < rows && j < rows) ? F.gram[(size_t)i * QR_PANEL + j] : (i == j ? 1.0 : 0.0);
-    __syncthreads();
-    const int nblk = (rows + NB - 1) / NB;
-
-    // ---- Cholesky factorisation, lower triangle in place
-    for (int kb = 0; kb < nblk; ++kb) {
-        const int k0 = kb * NB;
-        if (wave == 0) {
-            // diagonal block: lane -> elements (i, j) = (e / 16, e % 16), e = lane + 64 q
-            for (int k = 0; k < NB; ++k) {
-                double piv = L[(k0 + k) * PITCH + k0 + k];
-                if (k0 + k < rows) {
-                    if (!(piv > 0.0) || !(piv < 1e300)) {        // not positive definite: keep going with a tiny pivot
-                        if (lane == 0) bad_flag = 1;
-                        piv = 1e-300;
-                    } else if (sweep > 0 && piv < CHOL_REPEAT_MIN) {
-                        if (lane == 0) bad_flag = 2;
-                    }
-                }
-                const double d = sqrt(piv), rd = 1.0 / d;          // one division per column: the rest multiplies
-                if (lane == 0) S[k0 + k] = rd;                     // 1 / L_kk, read by the solves below and by the inverse
-                double colv[4], rowv[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int e = lane + 64 * q, i = e >> 4, j = e & 15;
-                    colv[q] = L[(k0 + i) * PITCH + k0 + k];      // L[i][k] before scaling
-                    rowv[q] = L[(k0 + j) * PITCH + k0 + k];      // L[j][k] before scaling
-                }
-                __builtin_amdgcn_wave_barrier();                 // all reads of column k precede its rewrite
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int e = lane + 64 * q, i = e >> 4, j = e & 15;
-                    if (j == k && i >= k) L[(k0 + i) * PITCH + k0 + k] = (i == k) ? d : colv[q] * rd;
-                    else if (j > k && j <= i) L[(k0 + i) * PITCH + k0 + j] -= (colv[q] * rd) * (rowv[q] * rd);
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
-        __syncthreads();
-        // rows below: L21 = A21 L11^-T, one thread per row
-        for (int i = k0 + NB + tid; i < rows; i += CHOL_THREADS) {
-            double x[NB];
-#pragma unroll
-            for (int j = 0; j < NB; ++j) x[j] = L[i * PITCH + k0 + j];
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                double v = x[j];
-#pragma unroll
-                for (int m = 0; m < j; ++m) v -= x[m] * L[(k0 + j) * PITCH + k0 + m];
-                x[j] = v * S[k0 + j];
-            }
-#pragma unroll
-            for (int j = 0; j < NB; ++j) L[i * PITCH + k0 + j] = x[j];
-        }
-        __syncthreads();
-        // trailing matrix: A22 -= L21 L21^T (lower triangle)
-        for (int i = k0 + NB + ti; i < rows; i += 16) {
-            double li[NB];
-#pragma unroll
-            for (int m = 0; m < NB; ++m) li[m] = L[i * PITCH + k0 + m];
-            for (int j = k0 + NB + tj; j <= i; j += 16) {
-                double acc = 0.0;
-#pragma unroll
-                for (int m = 0; m < NB; ++m) acc += li[m] * L[j * PITCH + k0 + m];
-                L[i * PITCH + j] -= acc;
-            }
-        }
-        __syncthreads();
-    }
-
-    // ---- W = L^-1 over L.  Diagonal blocks first: lane j of a 16-lane group owns column j of its block.
-    {
-        const int grp = tid >> 4;                                 // 16 groups of 16 lanes, one block each
-        if (grp < nblk) {
-            const int k0 = grp * NB, j = tj;
-            double w[NB];
-#pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                double sum = (i == j) ? 1.0 : 0.0;
-#pragma unroll
-                for (int k = 0; k < i; ++k)
-                    if (k >= j) sum -= L[(k0 + i) * PITCH + k0 + k] * w[k];
-                w[i] = (i >= j) ? sum * S[k0 + i] : 0.0;
-            }
-            __builtin_amdgcn_wave_barrier();                      // the group's reads of the block precede the rewrite
-#pragma unroll
-            for (int i = 0; i < NB; ++i)
-                if (i >= j) L[(k0 + i) * PITCH + k0 + j] = w[i];
-        }
-    }
-    __syncthreads();
-    // Block rows: W_ij = -W_ii (sum_{k = j}^{i - 1} L_ik W_kj), j < i; rows above i already hold W.
-    for (int ib = 1; ib < nblk; ++ib) {
-        const int i0 = ib * NB;
-        // S[ti][c] = sum over k in [c, i0) of L[i0 + ti][k] W[k][c] (W is lower triangular; above its
-        // diagonal the array still holds the input), c < i0: thread (ti, tj) takes the columns
-        // c = tj, tj + 16, ...
-        for (int c = tj; c < i0; c += 16) {
-            double acc = 0.0;
-            for (int k = c; k < i0; ++k) acc += L[(i0 + ti) * PITCH + k] * L[k * PITCH + c];
-            S[ti * QR_PANEL + c] = acc;
-        }
-        __syncthreads();
-        for (int c = tj; c < i0; c += 16) {
-            double acc = 0.0;
-#pragma unroll
-            for (int m = 0; m < NB; ++m)
-                if (m <= ti) acc += L[(i0 + ti) * PITCH + i0 + m] * S[m * QR_PANEL + c];   // W_ii is lower triangular
-            L[(i0 + ti) * PITCH + c] = -acc;
-        }
-        __syncthreads();
-    }
-    for (int i = ti; i < rows; i += 16)
-        for (int j = tj; j < rows; j += 16)
-            F.winv[(size_t)i * QR_PANEL + j] = (j <= i) ? (float)L[i * PITCH + j] : 0.0f;
-    if (tid == 0) {
-        if (bad_flag == 1 || (bad_flag == 2 && sweep == 2)) F.bad = 1;
-        if (sweep == 0) { F.skip3 = 1; F.p_scale = QR_UNIT_SCALE; }       // the rows are normalised now
-        // after the last sweep of a panel the scale goes back to that of the rows of Z^T (the next panel)
-        if (sweep == 1) { if (bad_flag == 2) F.skip3 = 0; else F.p_scale = F.a_scale; }
-        if (sweep == 2) F.p_scale = F.a_scale;
-    }
-}
 
 __global__ void qr_info_kernel(const QrFactor *fs, int nf, int32_t *info)
 {
@@ -364,29 +164,6 @@ __global__ __launch_bounds__(256) void transpose_inplace_kernel(const QrFactor *
     }
 }
 
-// Q[i][c] = Zt[c][i] for the rows c of one finished panel: 32 x 32 tiles through LDS.  Grid:
-// x = tile of the 128 x n strip, y = factor (the first ones of the group have the panel).  The caller's Q thus fills up
-// panel by panel, and the next panels read the finished columns from it with k contiguous.
-__global__ __launch_bounds__(256) void transpose_panel_kernel(const QrFactor *fs, int panel)
-{
-    const QrFactor &F = fs[blockIdx.y];
-    const int tpr = (F.n + 31) / 32;
-    const int ti = (int)blockIdx.x / tpr, tj = (int)blockIdx.x % tpr;   // tile row inside the panel, tile column
-    const int c0 = panel * QR_PANEL + ti * 32;
-    if (ti >= QR_PANEL / 32 || c0 >= F.n) return;
-    __shared__ float tile[32][33];
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int r = ty; r < 32; r += 8) {
-        const int c = c0 + r, i = tj * 32 + tx;
-        tile[r][tx] = (c < F.n && i < F.n) ? F.Zt[(size_t)c * F.ldz + i] : 0.0f;
-    }
-    __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const int i = tj * 32 + r, c = c0 + tx;
-        if (i < F.n && c < F.n) F.Qout[(size_t)i * F.ldq + c] = tile[tx][r];
-    }
-}
-
 // Q = I for every factor of the group (the refresh then starts from the identity)
 __global__ __launch_bounds__(256) void set_identity_kernel(const QrFactor *fs)
 {
@@ -398,11 +175,9 @@ __global__ __launch_bounds__(256) void set_identity_kernel(const QrFactor *fs)
     }
 }
 
-// Q^T kept beside Q by the caller.  mode 0: Qt <- Q^T (the buffer does not hold it yet), 32 x 32 tiles
-// through LDS; mode 1: Qt <- Zt (the rows of Z^T are the new basis vectors when a round ends), a plain
-// copy.  Grid: x = 32 x 32 tile of the largest factor's tile grid, y = factor; factors without such a
-// buffer do nothing.
-__global__ __launch_bounds__(256) void keep_qt_kernel(const QrFactor *fs, int mode)
+// Qt <- Q^T where the caller keeps Q^T beside Q and the buffer does not hold it yet: 32 x 32 tiles through LDS.
+// Grid: x = tile of the largest factor's tile grid, y = factor; factors without such a buffer do nothing.
+__global__ __launch_bounds__(256) void keep_qt_kernel(const QrFactor *fs)
 {
     const QrFactor &F = fs[blockIdx.y];
     if (F.Qt == F.Qout) return;
@@ -410,20 +185,6 @@ __global__ __launch_bounds__(256) void keep_qt_kernel(const QrFactor *fs, int mo
     const int ti = (int)blockIdx.x / tmax, tj = (int)blockIdx.x % tmax;
     if (ti >= tpr || tj >= tpr) return;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    if (mode == 1) {
-        // one 16-byte piece per thread where the caller's buffer allows it (the workspace rows always do)
-        const bool vec = ((reinterpret_cast<uintptr_t>(F.Qt) & 15u) == 0) && ((F.ldqt & 3) == 0);
-        const int i = ti * 32 + (int)(threadIdx.x >> 3), c = tj * 32 + 4 * (int)(threadIdx.x & 7);
-        if (i >= F.n || c >= F.n) return;
-        const float *src = F.Zt + (size_t)i * F.ldz + c;
-        float *dst = F.Qt + (size_t)i * F.ldqt + c;
-        if (vec && c + 4 <= F.n) {
-            *reinterpret_cast<float4 *>(dst) = *reinterpret_cast<const float4 *>(src);
-        } else {
-            for (int e = 0; e < 4 && c + e < F.n; ++e) dst[e] = src[e];
-        }
-        return;
-    }
     __shared__ float tile[32][33];
     for (int r = ty; r < 32; r += 8) {
         const int i = ti * 32 + r, c = tj * 32 + tx;
@@ -495,8 +256,8 @@ __global__ __launch_bounds__(256) void sort_gather_kernel(const QrFactor *fs, in
 // count_j of the group and the entry of factor i in any table of panel j is entry i of that panel's run.
 struct RefreshTables {
     GemmProblem *z;                    // Z^T = Q^T A: one entry per factor
-    GemmProblem *t1, *t2, *t3, *t4;    // projection coefficients, projection, Gram matrix, application of L^-1
-    const int *off;                    // np + 1: start of panel j's run in t1 .. t4
+    GemmProblem *t1, *t2;              // projection coefficients, projection
+    const int *off;                    // np + 1: start of panel j's run in t1, t2
     const int *pt;                     // cnt + 1: tile columns (ceil(n / 128)) of the factors before i
     const int *pz;                     // cnt + 1: tiles of the Z product (ceil(n / 128)^2) of the factors before i
 };
@@ -526,22 +287,9 @@ __global__ __launch_bounds__(128) void refresh_tables_kernel(QrFactor *fs, int c
     const int e = T.off[j] + i;
     const int rows = min(QR_PANEL, F.n - j * QR_PANEL), done = j * QR_PANEL;
     float *Pt = F.Zt + (size_t)done * F.ldz;
+    if (j == 0) return;
     // runs while the factor's state word (`run`, or `skip3` in the third sweep) is 0
     p.state_idx = i * QR_STATE_STRIDE; p.state_mask = 1;
-    // Gram matrix of the panel rows (fp64 accumulation), one symmetric tile
-    p.flags = GEMM_SYM;
-    p.M = rows; p.N = rows; p.K = F.n;
-    p.A = Pt; p.lda = F.ldz; p.B = Pt; p.ldb = F.ldz; p.C = F.gram; p.ldc = QR_PANEL;
-    p.tile_start = i;
-    T.t3[e] = p;
-    // P <- W P, in place: the single tile row reads a column range of P completely before it stores
-    // the same range
-    p.flags = 0;
-    p.M = rows; p.N = F.n; p.K = rows; p.tiles_n = tn;
-    p.A = F.winv; p.lda = QR_PANEL; p.B = Pt; p.ldb = F.ldz; p.C = Pt; p.ldc = F.ldz;
-    p.tile_start = T.pt[i];
-    T.t4[e] = p;
-    if (j == 0) return;
     // C = P Q_done^T: rows of the panel against the finished rows, contraction over n; on the fp16 cores
     // the panel rows are scaled by the factor's p_scale, the finished rows are orthonormal
     p.M = rows; p.N = done; p.K = F.n; p.tiles_n = j;
@@ -838,10 +586,10 @@ size_t refresh_factor_bytes(int n)
     const int np = (n + QR_PANEL - 1) / QR_PANEL;
     return Carver::need((size_t)n * ld4(n), sizeof(float)) +            // Z^T, becomes Q^T
            Carver::need((size_t)QR_PANEL * ld4(n), sizeof(float)) +     // projection coefficients of one panel
-           Carver::need((size_t)QR_PANEL * QR_PANEL, sizeof(double)) +  // panel Gram matrix / fp64 inverse factor
+           Carver::need(gram_doubles(n), sizeof(double)) +              // partial Gram matrices of a panel
            Carver::need((size_t)QR_PANEL * QR_PANEL, sizeof(float)) +   // fp32 inverse factor
            Carver::need((size_t)n, sizeof(double)) + Carver::need((size_t)n, sizeof(int)) +   // column estimates and order
-           (size_t)(1 + 4 * np) * sizeof(GemmProblem) + (size_t)(np + 2) * sizeof(int) + sizeof(QrFactor);
+           (size_t)(1 + 2 * np) * sizeof(GemmProblem) + (size_t)(np + 2) * sizeof(int) + sizeof(QrFactor);
 }
 
 // The factors of a call can be dealt to up to this many groups, each enqueued as a whole on an
@@ -919,9 +667,6 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
     // the first factor must fit: checked before anything touches the device
     if (refresh_fixed_bytes(n_all) + refresh_factor_bytes(f[0].n) > ws_bytes) return ASTERIA_WORKSPACE_TOO_SMALL;
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_);
-    constexpr size_t chol_lds = CHOL_LDS_BYTES;
-    static bool chol_configured[MAX_DEVICES] = {};
-    ASTERIA_HIP_TRY(ensure_dynamic_lds(reinterpret_cast<const void *>(panel_chol_inverse_kernel), chol_lds, chol_configured));
 
     // the caller's permutation array holds the factors' orders one after the other
     std::vector<size_t> perm_offset(nfactors, 0);
@@ -966,7 +711,7 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             memset(&F, 0, sizeof(F));
             F.Zt = cv.take<float>((size_t)n * ldz);
             F.cbuf = cv.take<float>((size_t)QR_PANEL * ldz);
-            F.gram = cv.take<double>((size_t)QR_PANEL * QR_PANEL);
+            F.gram = cv.take<double>(gram_doubles(n));
             F.winv = cv.take<float>((size_t)QR_PANEL * QR_PANEL);
             F.Qout = a.X; F.n = n; F.ldz = ldz; F.ldq = a.ldx; F.bad = 0; F.run = 0; F.skip3 = 1;
             F.out_index = idx[i];
@@ -987,7 +732,6 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         RefreshTables rt;
         rt.z = cv.take<GemmProblem>(cnt);
         rt.t1 = cv.take<GemmProblem>(entries); rt.t2 = cv.take<GemmProblem>(entries);
-        rt.t3 = cv.take<GemmProblem>(entries); rt.t4 = cv.take<GemmProblem>(entries);
         int *d_ints = cv.take<int>(ints.size());
         rt.off = d_ints; rt.pt = d_ints + np_max + 1; rt.pz = rt.pt + cnt + 1;
         GemmProblem *d_g = rt.z;
@@ -998,10 +742,8 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         // panel j: count[j] entries per table; tile counts of its four launches
         auto T1 = [&](int j) { return rt.t1 + off[j]; };
         auto T2 = [&](int j) { return rt.t2 + off[j]; };
-        auto T3 = [&](int j) { return rt.t3 + off[j]; };
-        auto T4 = [&](int j) { return rt.t4 + off[j]; };
         auto tiles1 = [&](int j) { return count[j] * j; };
-        auto tiles24 = [&](int j) { return pt[count[j]]; };
+        auto tiles2 = [&](int j) { return pt[count[j]]; };
         hipLaunchKernelGGL(qr_scale_kernel, dim3(cnt), dim3(64), 0, stream, d_q, cnt);
         if (o.from_identity)
             hipLaunchKernelGGL(set_identity_kernel, dim3((unsigned)std::min<size_t>(((size_t)n_max * n_max + 255) / 256, 4096), (unsigned)cnt),
@@ -1010,7 +752,7 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         // a kept Q^T that the caller has not filled (or a start from the identity, which the kernel above
         // wrote to both buffers) is made from Q once; every round then leaves the new one there
         if (any_qt && !o.xt_in && !o.from_identity)
-            hipLaunchKernelGGL(keep_qt_kernel, dim3(tpr32 * tpr32, (unsigned)cnt), dim3(256), 0, stream, d_q, 0);
+            hipLaunchKernelGGL(keep_qt_kernel, dim3(tpr32 * tpr32, (unsigned)cnt), dim3(256), 0, stream, d_q);
         for (int round = 0; round < o.rounds; ++round) {
         hipLaunchKernelGGL(transpose_inplace_kernel, dim3(tpr32 * tpr32, (unsigned)cnt), dim3(256), 0, stream, d_q);
         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(d_g, cnt, tiles, nullptr, stream)));
@@ -1044,25 +786,22 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
                     // rows, 2^-11 of the coefficients, is what the second sweep removes at full accuracy
                     if (sweep == 0) {
                         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 1, 1, true>(T1(j), count[j], tiles1(j), st, stream)));
-                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 1, 2, true>(T2(j), count[j], tiles24(j), st, stream)));
+                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 1, 2, true>(T2(j), count[j], tiles2(j), st, stream)));
                     } else if (sweep == 1) {
                         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T1(j), count[j], tiles1(j), st, stream)));
-                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T2(j), count[j], tiles24(j), st, stream)));
+                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T2(j), count[j], tiles2(j), st, stream)));
                     } else {
                         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T1(j), count[j], tiles1(j), st, stream)));
-                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T2(j), count[j], tiles24(j), st, stream)));
+                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T2(j), count[j], tiles2(j), st, stream)));
                     }
                 }
-                ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, false, false>(T3(j), count[j], count[j], st, stream)));
-                hipLaunchKernelGGL(panel_chol_inverse_kernel, dim3((unsigned)count[j]), dim3(CHOL_THREADS), chol_lds, stream, d_q, j, sweep);
-                ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true>(T4(j), count[j], tiles24(j), st, stream)));
+                const unsigned nfac = (unsigned)count[j];
+                hipLaunchKernelGGL(panel_gram_kernel, dim3((unsigned)gram_splits(n_max), nfac), dim3(256), 0, stream, d_q, j, sweep);
+                hipLaunchKernelGGL(panel_chol_kernel, dim3(nfac), dim3(256), 0, stream, d_q, j, sweep);
+                hipLaunchKernelGGL(panel_apply_kernel, dim3((unsigned)((n_max + 127) / 128), nfac), dim3(256), 0, stream, d_q, j, sweep);
+                ASTERIA_HIP_TRY(hipGetLastError());
             }
-            // the finished panel goes to the caller's Q as columns
-            hipLaunchKernelGGL(transpose_panel_kernel, dim3((QR_PANEL / 32) * ((n_max + 31) / 32), (unsigned)count[j]),
-                               dim3(256), 0, stream, d_q, j);
         }
-        if (any_qt)
-            hipLaunchKernelGGL(keep_qt_kernel, dim3(tpr32 * tpr32, (unsigned)cnt), dim3(256), 0, stream, d_q, 1);
         }   // rounds
         hipLaunchKernelGGL(qr_info_kernel, dim3((cnt + 127) / 128), dim3(128), 0, stream, d_q, cnt, info);
         ASTERIA_HIP_TRY(hipGetLastError());

@@ -1,0 +1,80 @@
+"""Kernels at the sizes where their tiles, remainders and dispatch lines lie, against fp64 results."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_16184_amd as ast
+from paper_2605_16184_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _with_spectrum(n, lam, *key):
+    U = W.haar(n, DEV, *key, dtype=torch.float64)
+    A = (U * lam) @ U.T.contiguous()
+    return (0.5 * (A + A.T)).float().contiguous()
+
+
+def _spectrum(kind, n):
+    if kind == "flat":
+        return torch.linspace(1.0, 0.9, n, device=DEV, dtype=torch.float64)
+    if kind == "power":
+        return 0.05 * W.powerlaw_sigma(n, DEV).double() ** 2
+    return 0.05 * W.logspaced_sigma(n, 8.0, DEV).double() ** 2
+
+
+def _root_error(A, X, eps):
+    w, V = torch.linalg.eigh(A.double())
+    e = eps * float(w[-1])
+    ref = (V * (w + e).clamp_min(1e-3 * e).pow(-0.25)) @ V.T.contiguous()
+    return float(torch.linalg.norm(X.double() - ref) / torch.linalg.norm(ref)), float(w[-1])
+
+
+@pytest.mark.parametrize("kind", ["flat", "power", "log"])
+@pytest.mark.parametrize("eps", [1e-3, 1e-6, 1e-8])
+@pytest.mark.parametrize("sizes", [
+    [1, 2, 31, 33, 64, 65, 127, 128, 129, 255, 256, 257],       # 64-wide tiles; recurrence in registers and streamed
+    [513, 640],                                                 # one launch per step of the recurrence
+    [130] * 190 + [97, 128, 256],                               # 128-wide tiles
+    [514] * 192,                                                # a batch whose recurrences run one workgroup each
+])
+def test_roots_at_the_edges(kind, eps, sizes):
+    made = {}
+    for n in sizes:
+        if n not in made:
+            made[n] = _with_spectrum(n, _spectrum(kind, n), 7, n)
+    As = [made[n] for n in sizes]
+    Xs = [torch.full_like(A, float("nan")) for A in As]
+    lam = torch.zeros(len(As), device=DEV)
+    info = torch.full((len(As),), -1, dtype=torch.int32, device=DEV)
+    ast.inverse_root(list(zip(As, Xs)), eps, info=info, lambda_max=lam)
+    torch.cuda.synchronize()
+    assert bool((info == 0).all())
+    last = {n: i for i, n in enumerate(sizes)}
+    for n, i in last.items():
+        err, top = _root_error(As[i], Xs[i], eps)
+        # eps = 1e-8 is below the fp32 rounding of the statistic: the root itself is known to a few per cent only
+        assert err <= (2e-3 if eps >= 1e-6 else 0.2), (n, err)
+        assert abs(float(lam[i]) - top) <= 1e-4 * top, (n, float(lam[i]), top)
+        assert bool((Xs[i] == Xs[i].T).all())
+        first = sizes.index(n)
+        assert torch.equal(Xs[first], Xs[i])                    # the same factor anywhere in the batch
+
+
+@pytest.mark.parametrize("sizes", [[1, 2, 15, 16, 17, 33, 48], [127, 128, 129, 191, 192, 193], [385, 1153]])
+def test_refresh_at_the_edges(sizes):
+    As = [_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n) for n in sizes]
+    Q0 = [W.haar(n, DEV, 11, n) for n in sizes]
+    Qs, Qt = [q.clone() for q in Q0], [torch.zeros(n, n, device=DEV) for n in sizes]
+    info = torch.full((len(sizes),), -1, dtype=torch.int32, device=DEV)
+    ast.soap_refresh(list(zip(As, Qs)), info=info, qt=Qt)
+    torch.cuda.synchronize()
+    assert bool((info == 0).all())
+    for n, A, q0, q, qt in zip(sizes, As, Q0, Qs, Qt):
+        assert torch.equal(qt, q.T)
+        Q, Z = q.double().cpu().numpy(), (A.double() @ q0.double()).cpu().numpy()
+        R = Q.T @ Z
+        assert np.linalg.norm(Q.T @ Q - np.eye(n)) / np.sqrt(n) <= 1e-5, n
+        assert np.linalg.norm(np.tril(R, -1)) <= 1e-5 * np.linalg.norm(Z), n
+        assert np.all(np.diag(R) >= 0), n
