@@ -806,7 +806,7 @@ inline hipError_t launch_gemm_grouped(const GemmProblem *probs, int nprobs, int 
     return hipGetLastError();
 }
 
-inline int tri_tiles(int n)
+__host__ __device__ inline int tri_tiles(int n)
 {
     const int t = (n + BM - 1) / BM;
     return t * (t + 1) / 2;

@@ -3,13 +3,10 @@
 //
 // Both products are symmetric grouped GEMMs on the matrix cores with the EMA fused in the
 // epilogue; only tiles on/below the diagonal are computed and mirrored.
-//   bf16 gradients: bf16 MFMA (products exact in fp32), guard-free kernel of pgemm.h (16-byte row
-//     pieces, LDS-staged epilogue with vector loads of the old L / R).  G G^T reads G as is
-//     (k-contiguous).  G^T G reads G as is too when G is 16-byte aligned and fills whole tiles:
-//     its operands are then k-major, staged as they lie and transposed by the LDS transpose reads
-//     of gfx950.  Otherwise a transposed bf16 copy of G, zero-padded to whole tiles, is written to
-//     the workspace first and read k-contiguous.  A G G^T whose operand is unaligned or ragged
-//     takes the guarded kernel.
+//   bf16 gradients: bf16 MFMA (products exact in fp32), kernel of stats_product.h, both products read
+//     G as it is when its rows are 16-byte aligned and hold whole 16-byte pieces.  Otherwise a
+//     transposed bf16 copy of G, zero-padded, is written to the workspace for G^T G, and G G^T takes
+//     the guarded kernel.
 //   fp32 gradients: fp32 MFMA; G^T G reads G k-major, no copy.
 //   Blocks that ask for fp64 accumulation (acc = ASTERIA_ACC_F64): products and sums on the fp64
 //     matrix cores from the bf16 / fp32 data (every product exact, sums to 2^-53), the EMA in fp64
@@ -19,7 +16,7 @@
 #include "common.h"
 #include "gemm.h"
 #include "gemm_bf16.h"
-#include "pgemm.h"
+#include "stats_product.h"
 
 using namespace asteria;
 
@@ -27,10 +24,7 @@ namespace {
 
 inline int pad_to(int n, int q) { return (n + q - 1) / q * q; }
 
-// guard-free kernel for the statistics: one bf16 term per operand, 128 x 128 tiles, slabs of 64
-using StatsShape = PgShape<1, 1, PG_PAIRS_1, 2, 2, 2, 2, 64, 1, 0, false, false, true>;
-constexpr int ST_TILE = StatsShape::TM;   // 128
-constexpr int ST_BK = StatsShape::BK;     // 64
+constexpr int ST_PAD_COLS = 128, ST_PAD_K = 64;   // what the transposed copies are padded to
 
 // G^T for a batch of bf16 blocks: 64 x 64 tiles through LDS, reads and writes along rows.  The
 // destination is padded to n_pad x m_pad (whole tiles of the consumer) and the padding is zero.
@@ -72,37 +66,20 @@ struct StatsTables {
     int tilesL[2] = {0, 0}, tilesR[2] = {0, 0};
     std::vector<GemmProblem> L64[2], R64[2];   // by dtype: fp64 accumulation
     int tilesL64[2] = {0, 0}, tilesR64[2] = {0, 0};
-    std::vector<PlaneProblem> fast;        // bf16 problems for the guard-free kernel (L and R sides)
+    std::vector<StatsEntry> fast;          // bf16 blocks and transposed copies for stats_product_kernel
     int tiles_fast = 0;
 };
 
-// G itself can feed the guard-free kernel: 16-byte aligned rows, whole tiles and slabs
-inline bool fast_operand(const void *p, int rows, int k, int ld)
+inline StatsEntry fast_entry(const asteria_block &k, const void *G, int ldg, bool left, bool right, int flags, int tile_start)
 {
-    return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld % 8) == 0 && (rows % ST_TILE) == 0 && (k % ST_BK) == 0;
-}
-
-// G can feed G^T G directly (k-major operands): columns fill whole tiles, rows whole slabs
-inline bool kmajor_operand(const void *p, int m, int n, int ld)
-{
-    return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld % 8) == 0 && (n % ST_TILE) == 0 && (m % ST_BK) == 0;
-}
-
-inline PlaneProblem fast_problem(const void *G, int rows, int k, int ld, float *C, int ldc, float beta, int tile_start,
-                                 bool packed = false)
-{
-    PlaneProblem q;
-    memset(&q, 0, sizeof(q));
-    q.A = reinterpret_cast<const uint16_t *>(G); q.B = q.A;
-    q.lda = ld; q.ldb = ld;
-    q.C32 = C; q.ldc32 = ldc;
-    q.M = rows; q.N = rows; q.K = k;
-    q.tile_start = tile_start;
-    q.state_idx = -1; q.state_mask = ~0;
-    q.alpha = 1.0f - beta; q.beta = beta;
-    q.flags = GEMM_SYM | (packed ? GEMM_C_PACKED : 0);
-   
-    return q;
+    StatsEntry e;
+    memset(&e, 0, sizeof(e));
+    e.G = reinterpret_cast<const uint16_t *>(G);
+    e.L = left ? k.L : nullptr; e.R = right ? k.R : nullptr;
+    e.m = k.m; e.n = k.n; e.ldg = ldg; e.ldl = k.ldl; e.ldr = k.ldr;
+    e.flags = flags | (k.lr_layout == ASTERIA_LAYOUT_PACKED ? STATS_PACKED : 0);
+    e.tile_start = tile_start;
+    return e;
 }
 
 asteria_status validate(const asteria_block *b, int nblocks, float beta)
@@ -154,18 +131,18 @@ void build(const asteria_block *b, int nblocks, float beta, StatsTables &t)
             }
             continue;
         }
-        if (k.L) {
-            if (d == ASTERIA_BF16 && fast_operand(k.G, k.m, k.n, k.ldg)) {
-                t.fast.push_back(fast_problem(k.G, k.m, k.n, k.ldg, k.L, k.ldl, beta, t.tiles_fast, packed));
-                t.tiles_fast += pg_tri_tiles(k.m, ST_TILE);
-            } else {
-                p.C = k.L; p.ldc = k.ldl; p.M = k.m; p.N = k.m; p.K = k.n;
-                p.tile_start = t.tilesL[d];
-                t.tilesL[d] += tri_tiles(k.m);
-                t.L[d].push_back(p);
-            }
+        if (d == ASTERIA_BF16 && stats_operand_ok(k.G, k.m, k.n, k.ldg)) {
+            t.fast.push_back(fast_entry(k, k.G, k.ldg, k.L != nullptr, k.R != nullptr, 0, t.tiles_fast));
+            t.tiles_fast += (k.L ? tri_tiles(k.m) : 0) + (k.R ? tri_tiles(k.n) : 0);
+            continue;
         }
-        if (k.R && d != ASTERIA_BF16) {      // bf16: the transposed padded copy always feeds the guard-free kernel
+        if (k.L) {
+            p.C = k.L; p.ldc = k.ldl; p.M = k.m; p.N = k.m; p.K = k.n;
+            p.tile_start = t.tilesL[d];
+            t.tilesL[d] += tri_tiles(k.m);
+            t.L[d].push_back(p);
+        }
+        if (k.R && d != ASTERIA_BF16) {      // bf16: from the transposed copy
             p.C = k.R; p.ldc = k.ldr; p.M = k.n; p.N = k.n; p.K = k.m;
             p.tile_start = t.tilesR[d];
             t.tilesR[d] += tri_tiles(k.n);
@@ -180,12 +157,12 @@ extern "C" size_t asteria_stats_update_workspace_bytes(const asteria_block *bloc
 {
     if (!blocks || nblocks <= 0) return 0;
     size_t bytes = 4 * Carver::need((size_t)nblocks, sizeof(GemmProblem)) +
-                   Carver::need(2 * (size_t)nblocks, sizeof(PlaneProblem)) +
+                   Carver::need(2 * (size_t)nblocks, sizeof(StatsEntry)) +
                    Carver::need((size_t)nblocks, sizeof(TransposeJob)) + 8 * 256;
     for (int i = 0; i < nblocks; ++i)
         if (blocks[i].g_dtype == ASTERIA_BF16 && blocks[i].acc != ASTERIA_ACC_F64 && blocks[i].R && blocks[i].m > 0 &&
-            blocks[i].n > 0 && !kmajor_operand(blocks[i].G, blocks[i].m, blocks[i].n, blocks[i].ldg))
-            bytes += Carver::need((size_t)pad_to(blocks[i].n, ST_TILE) * pad_to(blocks[i].m, ST_BK), sizeof(uint16_t));
+            blocks[i].n > 0 && !stats_operand_ok(blocks[i].G, blocks[i].m, blocks[i].n, blocks[i].ldg))
+            bytes += Carver::need((size_t)pad_to(blocks[i].n, ST_PAD_COLS) * pad_to(blocks[i].m, ST_PAD_K), sizeof(uint16_t));
     return bytes;
 }
 
@@ -209,14 +186,8 @@ extern "C" asteria_status asteria_stats_update(const asteria_block *blocks, int 
         for (int i = 0; i < nblocks; ++i) {
             const asteria_block &k = blocks[i];
             if (k.g_dtype != ASTERIA_BF16 || !k.R || k.acc == ASTERIA_ACC_F64) continue;
-            if (kmajor_operand(k.G, k.m, k.n, k.ldg)) {
-                PlaneProblem q = fast_problem(k.G, k.n, k.m, k.ldg, k.R, k.ldr, beta, t.tiles_fast, k.lr_layout == ASTERIA_LAYOUT_PACKED);
-                q.flags |= PG_KMAJOR;
-                t.fast.push_back(q);
-                t.tiles_fast += pg_tri_tiles(k.n, ST_TILE);
-                continue;
-            }
-            const int n_pad = pad_to(k.n, ST_TILE), m_pad = pad_to(k.m, ST_BK);
+            if (stats_operand_ok(k.G, k.m, k.n, k.ldg)) continue;
+            const int n_pad = pad_to(k.n, ST_PAD_COLS), m_pad = pad_to(k.m, ST_PAD_K);
             uint16_t *Gt = cv.take<uint16_t>((size_t)n_pad * m_pad);
             TransposeJob j;
             memset(&j, 0, sizeof(j));
@@ -226,9 +197,21 @@ extern "C" asteria_status asteria_stats_update(const asteria_block *blocks, int 
             j.tile_start = tiles;
             tiles += (m_pad / 64) * (n_pad / 64);
             jobs.push_back(j);
-            // the R problem of this block reads G^T with k (= m) contiguous
-            t.fast.push_back(fast_problem(Gt, k.n, k.m, m_pad, k.R, k.ldr, beta, t.tiles_fast, k.lr_layout == ASTERIA_LAYOUT_PACKED));
-            t.tiles_fast += pg_tri_tiles(k.n, ST_TILE);
+            // the R product of this block reads G^T with k (= m) contiguous
+            if (stats_operand_ok(Gt, n_pad, m_pad, m_pad)) {
+                t.fast.push_back(fast_entry(k, Gt, m_pad, false, true, STATS_TRANSPOSED, t.tiles_fast));
+                t.tiles_fast += tri_tiles(k.n);
+            } else {                                             // beyond 31-bit offsets
+                GemmProblem p;
+                memset(&p, 0, sizeof(p));
+                p.A = Gt; p.B = Gt; p.lda = m_pad; p.ldb = m_pad; p.C = k.R; p.ldc = k.ldr; p.M = k.n; p.N = k.n; p.K = k.m;
+                p.state_idx = -1; p.state_mask = ~0;
+                p.alpha = 1.0f - beta; p.beta = beta;
+                p.flags = GEMM_SYM | (k.lr_layout == ASTERIA_LAYOUT_PACKED ? GEMM_C_PACKED : 0);
+                p.tile_start = t.tilesR[1];
+                t.tilesR[1] += tri_tiles(k.n);
+                t.R[1].push_back(p);
+            }
         }
         if (!jobs.empty()) {
             ASTERIA_HIP_TRY(upload_async(d_jobs, jobs.data(), jobs.size() * sizeof(TransposeJob), stream));
@@ -237,9 +220,13 @@ extern "C" asteria_status asteria_stats_update(const asteria_block *blocks, int 
         }
     }
     if (!t.fast.empty()) {
-        PlaneProblem *dF = cv.take<PlaneProblem>(t.fast.size());
-        ASTERIA_HIP_TRY(upload_async(dF, t.fast.data(), t.fast.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<StatsShape>(dF, (int)t.fast.size(), t.tiles_fast, nullptr, stream, 512)));
+        StatsEntry *dF = cv.take<StatsEntry>(t.fast.size());
+        ASTERIA_HIP_TRY(upload_async(dF, t.fast.data(), t.fast.size() * sizeof(StatsEntry), stream));
+        const int per_xcd = (t.tiles_fast + NUM_XCD - 1) / NUM_XCD;
+        profile_begin(512, stream);
+        hipLaunchKernelGGL(stats_product_kernel<1>, dim3(per_xcd * NUM_XCD), dim3(256), 0, stream, dF, (int)t.fast.size(), t.tiles_fast, beta);
+        profile_end(stream);
+        ASTERIA_HIP_TRY(hipGetLastError());
     }
     for (int d = 0; d < 2; ++d) {
         GemmProblem *dL = nullptr, *dR = nullptr;

@@ -1,0 +1,278 @@
+// L <- beta L + (1 - beta) G G^T and R <- beta R + (1 - beta) G^T G of bf16 gradients on the bf16 matrix cores.
+#pragma once
+#include "planes.h"
+
+namespace asteria {
+
+typedef __bf16 st_bf16x8 __attribute__((ext_vector_type(8)));
+
+// One gradient block with the statistics this launch updates (null: not this one).
+struct StatsEntry {
+    const uint16_t *G;      // m x n, or n x m (transposed copy) when STATS_TRANSPOSED: then only R is updated
+    float *L, *R;
+    int m, n, ldg, ldl, ldr;
+    int flags;
+    int tile_start;         // first tile of the entry in the launch: those of L, then those of R
+    int pad_;
+};
+enum : int { STATS_TRANSPOSED = 1, STATS_PACKED = 2 };
+
+// Operands the kernel reads in place: 16-byte aligned rows of whole 16-byte pieces, offsets within 31 bits
+inline bool stats_operand_ok(const void *p, int rows, int cols, int ld)
+{
+    return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld % 8) == 0 && (cols % 8) == 0 && (size_t)rows * (size_t)ld * 2 < 0x70000000u;
+}
+
+// The K loop: acc += A B^T over the rows row0 .. and col0 .. of an operand of n rows (columns when KM), K long.
+template <int ST, bool KM>
+__device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16_t *G, int ldg, int n, int K, int row0, int col0,
+                                             ASTERIA_LDS char *lds, int wave, int lane)
+{
+    constexpr int OP = 128 * 128, STAGE = 2 * OP;             // bytes of an operand's slab, of a stage
+    const bool diag = row0 == col0;
+    const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
+    // wavefront w stages instructions 4 w .. 4 w + 3 of each operand's 16 (64 chunks of 16 bytes each)
+    constexpr uint32_t OUTSIDE = 0x7ffffff0u;
+    const uint32_t ldb = (uint32_t)ldg * 2u;
+    const i32x4 rs = buffer_rsrc(G, (uint32_t)((KM ? K : n) - 1) * ldb + (uint32_t)(KM ? n : (K + 7) / 8 * 8) * 2u);   // whole pieces: a copy is padded
+    uint32_t va[4], vb[4];
+    int kof[4];                                               // k of the chunk within the slab
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int p = (wave * 4 + v) * 64 + lane;
+        if constexpr (KM) {
+            const int k = p >> 4, c16 = p & 15, c = ((((c16 >> 2) ^ (k & 3)) << 2) | (c16 & 3)) * 8;
+            kof[v] = k;
+            va[v] = (uint32_t)k * ldb + (uint32_t)min(row0 + c, n - 8) * 2u;
+            vb[v] = (uint32_t)k * ldb + (uint32_t)min(col0 + c, n - 8) * 2u;
+        } else {
+            const int rr = p >> 3, c = ((p & 7) ^ plane_swz<8>(rr)) * 8;
+            kof[v] = c;
+            va[v] = (uint32_t)min(row0 + rr, n - 1) * ldb + (uint32_t)c * 2u;
+            vb[v] = (uint32_t)min(col0 + rr, n - 1) * ldb + (uint32_t)c * 2u;
+        }
+    }
+    const uint32_t slab_bytes = KM ? 64u * ldb : 128u;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds + (uint32_t)wave * 4096u;
+    auto issue = [&](uint32_t stage, int slab) __attribute__((always_inline)) {
+        const uint32_t off = (uint32_t)slab * slab_bytes;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const bool in = slab * 64 + kof[v] < K;
+            load_to_lds(rs, lds0 + stage + (uint32_t)v * 1024u, in ? va[v] + off : OUTSIDE, 0u);
+            if (!diag) load_to_lds(rs, lds0 + stage + OP + (uint32_t)v * 1024u, in ? vb[v] + off : OUTSIDE, 0u);
+        }
+    };
+    const int nk = (K + 63) / 64;
+    const uint32_t bo = diag ? 0u : (uint32_t)OP;
+    const int diag_d = diag ? wm - wn : 1;                    // < 0: above the diagonal, 0: on it
+    auto multiply = [&](const u32x4 (&af)[2], const u32x4 (&bf)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (!(i == 0 && j == 1 && diag_d == 0))
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(st_bf16x8, af[i]), __builtin_bit_cast(st_bf16x8, bf[j]),
+                                                                        acc[i][j], 0, 0, 0);
+    };
+    uint32_t fa[2], fb[2];
+    const int sw = plane_swz<8>(r);
+    {
+        const int g = lane >> 4, e = (lane >> 2) & 3, q = lane & 3;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if constexpr (KM) {
+                const uint32_t rc = (uint32_t)((8 * (g >> 1) + e) * 256 + (16 * (g & 1) + 4 * q) * 2);
+                fa[i] = rc + ((uint32_t)((wm * 2 + i) ^ e) << 6);
+                fb[i] = bo + rc + ((uint32_t)((wn * 2 + i) ^ e) << 6);
+            } else {
+                fa[i] = (uint32_t)((wm * 64 + i * 32 + r) * 128);
+                fb[i] = bo + (uint32_t)((wn * 64 + i * 32 + r) * 128);
+            }
+        }
+    }
+    auto compute = [&](uint32_t stage) __attribute__((always_inline)) {
+        if constexpr (KM) {
+            auto frag = [&](uint32_t off) __attribute__((always_inline)) {
+                typedef short s16x4 __attribute__((ext_vector_type(4)));
+                typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+                const u2 a = __builtin_bit_cast(u2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ASTERIA_LDS s16x4 *)(lds + off)));
+                const u2 b = __builtin_bit_cast(u2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ASTERIA_LDS s16x4 *)(lds + off + 1024)));
+                return (u32x4){a[0], a[1], b[0], b[1]};
+            };
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                u32x4 af[2], bf[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) { af[i] = frag(stage + fa[i] + s * 4096); bf[i] = frag(stage + fb[i] + s * 4096); }
+                multiply(af, bf);
+                __builtin_amdgcn_sched_barrier(0);        // the fragments of one step at a time: four would spill
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                u32x4 af[2], bf[2];
+                const uint32_t c = (uint32_t)(((s * 2 + h) ^ sw) * 16);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    af[i] = *(const ASTERIA_LDS u32x4 *)(lds + stage + fa[i] + c);
+                    bf[i] = *(const ASTERIA_LDS u32x4 *)(lds + stage + fb[i] + c);
+                }
+                multiply(af, bf);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    if constexpr (ST == 1) {
+        for (int kt = 0; kt < nk; ++kt) {
+            issue(0u, kt);
+            wait_lds_loads<0>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");                    // the reads stay behind the barrier
+            if (diag_d >= 0) compute(0u);
+            wait_lds_loads<0>();                              // this wavefront has read the slab
+            __builtin_amdgcn_s_barrier();
+        }
+    } else {
+        issue(0u, 0);
+        for (int kt = 0; kt < nk; ++kt) {
+            wait_lds_loads<0>();
+            __builtin_amdgcn_s_barrier();
+            if (kt + 1 < nk) issue((uint32_t)((kt + 1) & 1) * STAGE, kt + 1);
+            if (diag_d >= 0) compute((uint32_t)(kt & 1) * STAGE);
+        }
+    }
+}
+
+// A 128 x 128 tile of a symmetric product per workgroup, 2 x 2 wavefronts of 2 x 2 MFMA blocks, slabs of 64 k.
+//   G G^T: both operands k-contiguous, LDS rows of 128 bytes.  G^T G: both k-major, LDS row = k, 256 bytes; the
+//   MFMA operands (8 consecutive k of one column per lane) come out through ds_read_b64_tr_b16, which transposes
+//   within 16 lanes: lane 4 e + q supplies the address of elements 4 q .. 4 q + 3 of row k0 + e, and lane j
+//   receives element j of rows k0 .. k0 + 3.
+// Operands go from memory to LDS without registers; rows and columns beyond the matrix repeat the last one (never
+// stored), k beyond its end reads as zero through the bounds check of the buffer loads.
+//
+// At n = 1024 a tile moves 128 KiB of statistics (256 in full storage) for 34 MFLOP, so both pipes matter and the
+// epilogue has to overlap other tiles' K loops: one slab of LDS and 128 registers, four workgroups per CU, rather
+// than a deeper pipeline and two.  The accumulators meet the old statistics in registers - a half wavefront covers
+// 128 consecutive bytes of a row, the mirror image is four consecutive floats per lane -, no pass through LDS.
+template <int ST>
+__global__ __launch_bounds__(256, ST == 1 ? 4 : 2) void stats_product_kernel(const StatsEntry *__restrict__ entries, int count, int total,
+                                                                             float beta)
+{
+    __shared__ __align__(16) unsigned char smem[ST * 32768];
+    ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem;
+    const int per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
+    const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
+    if (t >= total) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the entry of tile t: 64 candidates at a time
+    int lo = 0, len = count;
+    while (len > 1) {
+        const int step = (len + 63) / 64, c = lo + lane * step;
+        const bool le = lane * step < len && entries[c].tile_start <= t;
+        const int last = 63 - __builtin_clzll(__ballot(le));
+        lo += last * step;
+        len = min(step, len - last * step);
+    }
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    const StatsEntry E = entries[lo];
+    int lt = t - E.tile_start;
+    const int tl = E.L ? tri_tiles(E.m) : 0;
+    const bool left = lt < tl;
+    if (!left) lt -= tl;
+    int ti, tj;
+    tri_decode(lt, ti, tj);
+    const int n = left ? E.m : E.n, K = left ? E.n : E.m;
+    const bool kmajor = !left && !(E.flags & STATS_TRANSPOSED), packed = (E.flags & STATS_PACKED) != 0;
+    const int row0 = ti * 128, col0 = tj * 128;
+    const bool diag = ti == tj;
+    const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
+
+    floatx16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+    if (kmajor) stats_k_loop<ST, true>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
+    else stats_k_loop<ST, false>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
+    const int diag_d = diag ? wm - wn : 1;                    // < 0: above the diagonal
+    if (diag_d < 0) return;
+
+    // ---- old statistics in, new ones out
+    const float alpha = 1.0f - beta;
+    const int ldc = packed ? PACK_T : (left ? E.ldl : E.ldr);
+    ASTERIA_GLOBAL float *C = (ASTERIA_GLOBAL float *)(left ? E.L : E.R);
+    if (packed) C += ((size_t)ti * (ti + 1) / 2 + tj) * PACK_T * PACK_T - ((size_t)row0 * PACK_T + col0);   // of (0, 0) of the tile's frame
+    const bool vec = (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(left ? E.L : E.R) & 15u) == 0;
+    const bool read = beta != 0.0f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int br = row0 + (wm * 2 + i) * 32, bc = col0 + (wn * 2 + j) * 32;
+            if (br < bc || br >= n || bc >= n) continue;      // blocks above the diagonal are mirror images
+            const int col = bc + r;
+            {
+                ASTERIA_GLOBAL float *cu = C + (size_t)br * ldc + bc;         // uniform, beside a 32-bit lane offset
+                const uint32_t lo4 = (uint32_t)(4 * h) * (uint32_t)ldc + (uint32_t)r;
+                if (br + 32 <= n && bc + 32 <= n) {
+                    float o[16];
+                    if (read) {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) o[v] = (cu + (size_t)(8 * (v >> 2) + (v & 3)) * ldc)[lo4];
+                    }
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const float p = alpha * acc[i][j][v];
+                        (cu + (size_t)(8 * (v >> 2) + (v & 3)) * ldc)[lo4] = read ? p + beta * o[v] : p;
+                    }
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
+                        if (row < n && col < n) {
+                            ASTERIA_GLOBAL float *cc = cu + (size_t)(8 * (v >> 2) + (v & 3)) * ldc + lo4;
+                            const float p = alpha * acc[i][j][v];
+                            *cc = read ? p + beta * *cc : p;
+                        }
+                    }
+                }
+            }
+            // mirror image: a diagonal block holds both triangles itself (the products commute, so they agree bit for
+            // bit); packed storage has none outside the diagonal tiles
+            if (br == bc || (packed && !diag) || col >= n) continue;
+            ASTERIA_GLOBAL float *c = C + (size_t)col * ldc + br + 4 * h;
+            if (vec && br + 32 <= n) {
+                floatx4 o[4];
+                if (read) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) o[g] = *(ASTERIA_GLOBAL floatx4 *)(c + 8 * g);
+                }
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    floatx4 w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float p = alpha * acc[i][j][4 * g + e];
+                        w[e] = read ? p + beta * o[g][e] : p;
+                    }
+                    *(ASTERIA_GLOBAL floatx4 *)(c + 8 * g) = w;
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int d = 8 * (v >> 2) + (v & 3);
+                    if (br + 4 * h + d < n) {
+                        const float p = alpha * acc[i][j][v];
+                        c[d] = read ? p + beta * c[d] : p;
+                    }
+                }
+            }
+        }
+}
+
+}  // namespace asteria
