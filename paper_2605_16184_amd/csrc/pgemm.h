@@ -38,7 +38,8 @@ struct PlaneProblem {
     int tiles_n;            // tile columns (non-symmetric problems)
     int state_idx, state_mask;
     float alpha, beta;
-    int flags;              // GEMM_SYM, GEMM_C_PACKED, GEMM_STORE_T (output stored transposed, no beta), PG_KMAJOR
+    int flags;              // GEMM_SYM, GEMM_C_PACKED, GEMM_STORE_T (output stored transposed, no beta), PG_KMAJOR,
+                            // GEMM_C_BF16 (C32 is a bf16 matrix, no beta)
 };
 
 // pair (ta, tb) of an NTA x NTB split product is issued iff bit ta * 2 + tb of PAIRS is set
@@ -196,6 +197,20 @@ __device__ __forceinline__ void pg_emit(const PlaneProblem &P, int grow, int gco
                                         float *ctile = nullptr)
 {
     if (grow >= rlim) return;
+    if (P.flags & GEMM_C_BF16) {
+        uint16_t *c = reinterpret_cast<uint16_t *>(P.C32) + (size_t)grow * P.ldc32 + gcol;
+        u32x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = pg_pack_bf16(val[2 * e], val[2 * e + 1]);
+        if (gcol + 8 <= clim && (P.ldc32 & 7) == 0 && (reinterpret_cast<uintptr_t>(P.C32) & 15u) == 0) {
+            *(ASTERIA_GLOBAL u32x4 *)c = w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (gcol + e < clim) c[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+        }
+        return;
+    }
     float *c = ctile ? ctile + (size_t)(grow % PACK_T) * PACK_T + (gcol % PACK_T) : P.C32 + (size_t)grow * P.ldc32 + gcol;
     const bool vec = (gcol + 8 <= clim) && (ctile || (P.ldc32 & 3) == 0) && ((reinterpret_cast<uintptr_t>(P.C32) & 15u) == 0);
     if (vec) {
@@ -582,11 +597,38 @@ __global__ __launch_bounds__(S::NTHR) void pgemm_kernel(const PlaneProblem *__re
 // rotations whose shapes fill whole tiles
 using PgF32x2 = PgShape<2, 2, PG_PAIRS_2x2, 2, 4, 4, 2, 32, 1, 1, true, true>;
 
+// the same with a bf16 matrix as B (16-bit gradients against a root or a basis, two passes): slabs of 32, as
+// two stages of 64 (192 KiB) exceed the LDS; the gradient's 64-byte row pieces are a third of what it loads.
+// Bound by the alternation of fragment reads and MFMAs, as PgF32x2.  With it and the bf16 store, against the guarded
+// 128 x 128 kernel: both products of 64 blocks of 1024 x 1024 809 -> 735 us, bf16 output 841 -> 713 us
+using PgF32xB = PgShape<2, 1, PG_PAIRS_2x1, 2, 4, 4, 2, 32, 1, 1, true, false>;
+
 // a plain fp32 matrix can feed PgF32x2: 16-byte aligned rows, whole tiles and slabs
 inline bool pg_f32_operand_ok(const void *p, int rows, int k, int ld)
 {
     return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld % 4) == 0 && (rows % PgF32x2::TM) == 0 &&
            (k % PgF32x2::BK) == 0;
+}
+
+// a bf16 matrix can be B of PgF32xB
+inline bool pg_bf16_operand_ok(const void *p, int rows, int k, int ld)
+{
+    return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld % 8) == 0 && (rows % PgF32xB::TN) == 0 &&
+           (k % PgF32xB::BK) == 0;
+}
+
+// Whether the whole-tile blocks of a call run on 256 x 256 tiles (one workgroup per CU, 256 at a time) or on
+// the 128 x 128 ones of gemm_bf16.h (four times as many, 512 at a time); `tiles`: 256 x 256 tiles of the call,
+// `tiles_k`: their sum of K.  A round of 512 small tiles takes 0.56 of a round of 256 large ones from K = 512 on,
+// so whole rounds decide.  Measured, small / large time of precondition (fp32 out) and of soap_step, K = 1024:
+// 64 tiles 0.53 0.52, 128: 0.71 0.73, 160: 1.01 1.07, 256: 1.18 1.14, 320: 0.87 0.90, 512: 1.10 1.10, 1024: 1.10
+// 1.09 (K = 2048: 192: 1.10 1.10, 320: 0.85 0.87).  At K = 256 the wide stores of the large tiles' epilogue count
+// for more and last rounds for less: 64: 0.79 0.80, 96: 0.88 0.98, 128: 0.98 1.05, 160: 1.20 1.25, 320: 1.22 1.13.
+inline bool pg_take_large_tiles(long long tiles, long long tiles_k)
+{
+    if (tiles_k < 512 * tiles) return tiles > 112;
+    const long long large = (tiles + 255) / 256, small = (tiles + 127) / 128;
+    return 25 * large < 14 * small;
 }
 
 inline int pg_tri_tiles(int n, int tile)

@@ -6,8 +6,9 @@
 //   bf16 gradients (the training case): bf16 matrix cores with the fp32 operands split into
 //     hi + lo bf16 terms on the fly (about 16 bits kept):
 //       U^T = X_R G^T   (X_R split, G exact: 2 MFMA passes; both operands k-contiguous)
-//       P   = X_L U     (X_L and U^T split: 3 MFMA passes; both operands k-contiguous); blocks whose
-//                       shapes fill whole 256 x 256 tiles take the 8-wavefront kernel of pgemm.h
+//       P   = X_L U     (X_L and U^T split: 3 MFMA passes; both operands k-contiguous); either product of
+//                       blocks whose shapes fill whole 256 x 256 tiles takes the 8-wavefront kernel of pgemm.h
+//                       (PgF32xB, PgF32x2) where the call has enough such tiles (pg_take_large_tiles)
 //   fp32 gradients: fp32 matrix cores,  U = G X_R  then  P = X_L U  (U read k-major).
 #include <vector>
 
@@ -67,8 +68,21 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
     GemmProblem *d1 = cv.take<GemmProblem>(nblocks);
     GemmProblem *d2 = cv.take<GemmProblem>(nblocks);
     PlaneProblem *d2f = cv.take<PlaneProblem>(nblocks);
-    std::vector<PlaneProblem> p2f;       // second product of bf16 blocks that fill whole 256 x 256 tiles
-    int tiles2f = 0;
+    std::vector<PlaneProblem> p1f, p2f;  // products of bf16 blocks that fill whole 256 x 256 tiles
+    int tiles1f = 0, tiles2f = 0;
+    long long t1 = 0, tk1 = 0, t2 = 0, tk2 = 0;    // 256 x 256 tiles the call offers, and their sum of K
+    auto whole1 = [](const asteria_pblock &k) {
+        return k.g_dtype == ASTERIA_BF16 && pg_f32_operand_ok(k.XR, k.n, k.n, k.ldxr) && pg_bf16_operand_ok(k.G, k.m, k.n, k.ldg);
+    };
+    auto whole2 = [](const asteria_pblock &k) {   // U^T lies in the workspace: aligned, k contiguous
+        return k.g_dtype == ASTERIA_BF16 && pg_f32_operand_ok(k.XL, k.m, k.m, k.ldxl) && (k.n % PgF32x2::TN) == 0;
+    };
+    for (int i = 0; i < nblocks; ++i) {
+        const long long t = (long long)(blocks[i].m / PgF32x2::TM) * (blocks[i].n / PgF32x2::TN);
+        if (whole1(blocks[i])) { t1 += t; tk1 += t * blocks[i].n; }
+        if (whole2(blocks[i])) { t2 += t; tk2 += t * blocks[i].m; }
+    }
+    const bool use1 = pg_take_large_tiles(t1, tk1), use2 = pg_take_large_tiles(t2, tk2);
     // problems are grouped by gradient dtype: one launch per stage and dtype
     std::vector<GemmProblem> p1[2], p2[2];
     int tiles1[2] = {0, 0}, tiles2[2] = {0, 0};
@@ -85,16 +99,28 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
             float *Ut = cv.take<float>((size_t)k.n * ldu);
             // U^T = X_R G^T : rows of X_R against rows of G, contraction over n
             p.M = k.n; p.N = k.m; p.K = k.n; p.tiles_n = tm;
-            p.A = k.XR; p.lda = k.ldxr; p.B = k.G; p.ldb = k.ldg; p.C = Ut; p.ldc = ldu; p.flags = 0;
-            p.tile_start = tiles1[d]; tiles1[d] += tn * tm;
-            p1[d].push_back(p);
+            if (use1 && whole1(k)) {
+                PlaneProblem q;
+                memset(&q, 0, sizeof(q));
+                q.A = k.XR; q.lda = k.ldxr; q.B = k.G; q.ldb = k.ldg; q.C32 = Ut; q.ldc32 = ldu;
+                q.M = k.n; q.N = k.m; q.K = k.n;
+                q.tiles_n = k.m / PgF32xB::TN;
+                q.tile_start = tiles1f; tiles1f += (k.n / PgF32xB::TM) * q.tiles_n;
+                q.state_idx = -1; q.state_mask = ~0; q.alpha = 1.0f; q.beta = 0.0f;
+                p1f.push_back(q);
+            } else {
+                p.A = k.XR; p.lda = k.ldxr; p.B = k.G; p.ldb = k.ldg; p.C = Ut; p.ldc = ldu; p.flags = 0;
+                p.tile_start = tiles1[d]; tiles1[d] += tn * tm;
+                p1[d].push_back(p);
+            }
             // P = X_L U : rows of X_L against rows of U^T, contraction over m
             p.M = k.m; p.N = k.n; p.K = k.m; p.tiles_n = tn;
-            if (k.p_dtype == ASTERIA_F32 && pg_f32_operand_ok(k.XL, k.m, k.m, k.ldxl) && pg_f32_operand_ok(Ut, k.n, k.m, ldu)) {
+            if (use2 && whole2(k)) {
                 PlaneProblem q;
                 memset(&q, 0, sizeof(q));
                 q.A = k.XL; q.lda = k.ldxl; q.B = Ut; q.ldb = ldu;
                 q.C32 = reinterpret_cast<float *>(k.P); q.ldc32 = k.ldp;
+                q.flags = (k.p_dtype == ASTERIA_BF16) ? GEMM_C_BF16 : 0;
                 q.M = k.m; q.N = k.n; q.K = k.m;
                 q.tiles_n = k.n / PgF32x2::TN;
                 q.tile_start = tiles2f; tiles2f += (k.m / PgF32x2::TM) * q.tiles_n;
@@ -130,14 +156,18 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
         ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(d1, (int)p1[0].size(), tiles1[0], nullptr, stream)));
         ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true>(d2, (int)p2[0].size(), tiles2[0], nullptr, stream)));
     }
-    if (!p1[1].empty()) {
-        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, bf16_t, 2, 1>(d1b, (int)p1[1].size(), tiles1[1], nullptr, stream)));
-        if (!p2[1].empty())
-            ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d2b, (int)p2[1].size(), tiles2[1], nullptr, stream)));
-        if (!p2f.empty()) {
-            ASTERIA_HIP_TRY(upload_async(d2f, p2f.data(), p2f.size() * sizeof(PlaneProblem), stream));
-            ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d2f, (int)p2f.size(), tiles2f, nullptr, stream, 513)));
-        }
+    ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, bf16_t, 2, 1>(d1b, (int)p1[1].size(), tiles1[1], nullptr, stream)));
+    if (!p1f.empty()) {
+        // every block has one entry for its first product, of either kind: the region of d1 holds them all
+        static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
+        PlaneProblem *d1f = reinterpret_cast<PlaneProblem *>(d1b + p1[1].size());
+        ASTERIA_HIP_TRY(upload_async(d1f, p1f.data(), p1f.size() * sizeof(PlaneProblem), stream));
+        ASTERIA_HIP_TRY((launch_pgemm<PgF32xB>(d1f, (int)p1f.size(), tiles1f, nullptr, stream, 514)));
+    }
+    ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d2b, (int)p2[1].size(), tiles2[1], nullptr, stream)));
+    if (!p2f.empty()) {
+        ASTERIA_HIP_TRY(upload_async(d2f, p2f.data(), p2f.size() * sizeof(PlaneProblem), stream));
+        ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d2f, (int)p2f.size(), tiles2f, nullptr, stream, 513)));
     }
     return ASTERIA_OK;
 }

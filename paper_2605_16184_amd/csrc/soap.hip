@@ -413,7 +413,7 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
     TransposeF32Job *d_tj = cv.take<TransposeF32Job>(2 * (size_t)nblocks);
     PlaneProblem *d_f[3];
     for (int i = 0; i < 3; ++i) d_f[i] = cv.take<PlaneProblem>(nblocks);
-    std::vector<PlaneProblem> f2, f3, f4;   // products 2-4 of blocks that fill whole 256 x 256 tiles
+    std::vector<PlaneProblem> f1, f2, f3, f4;   // products of blocks that fill whole 256 x 256 tiles (the first one: bf16 gradients)
     int tilesf = 0;
     std::vector<GemmProblem> g1[2], g2, g3, g4;
     // one-sided blocks (Q_L or Q_R absent = the identity on that side, e.g. a dimension above the
@@ -422,7 +422,21 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
     int tL1[2] = {0, 0}, tL2 = 0, tR1[2] = {0, 0}, tR2 = 0;
     std::vector<AdamBlock> ab;
     std::vector<TransposeF32Job> tj;
-    int tiles1[2] = {0, 0}, tiles = 0, tilesT = 0, rows = 0, ttiles = 0;
+    int tiles1[2] = {0, 0}, tiles1f = 0, tiles = 0, tilesT = 0, rows = 0, ttiles = 0;
+    // 256 x 256 tiles the call offers to the kernels of pgemm.h, and their sum of K (transposes made here lie aligned in the workspace)
+    long long t1 = 0, tk1 = 0, t2 = 0, tk2 = 0;
+    auto whole1 = [](const asteria_sblock &k) {
+        return k.QL && k.QR && k.g_dtype == ASTERIA_BF16 && pg_bf16_operand_ok(k.G, k.m, k.n, k.ldg) &&
+               (k.n % PgF32xB::TM) == 0 && (!k.QRt || pg_f32_operand_ok(k.QRt, k.n, k.n, k.ldqrt));
+    };
+    for (int i = 0; i < nblocks; ++i) {
+        const asteria_sblock &k = blocks[i];
+        if (!k.QL || !k.QR || k.m % PgF32x2::TM || k.n % PgF32x2::TN) continue;
+        const long long t = (long long)(k.m / PgF32x2::TM) * (k.n / PgF32x2::TN);
+        if (whole1(k)) { t1 += t; tk1 += t * k.n; }
+        t2 += t; tk2 += t * (k.m + k.n) / 2;
+    }
+    const bool use1 = pg_take_large_tiles(t1, tk1), use2 = pg_take_large_tiles(t2, tk2);
     for (int i = 0; i < nblocks; ++i) {
         const asteria_sblock &k = blocks[i];
         const int ldw = ld4(k.n), ldt = ld4(k.m);
@@ -484,11 +498,22 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
         memset(&p, 0, sizeof(p));
         p.state_idx = -1; p.state_mask = ~0; p.alpha = 1.0f; p.beta = 0.0f;
         // 1: (G Q_R)^T:   A' = G (m x n), B' = Q_R^T (B'(j, k) = Q_R[k][j]); m x n result stored transposed
+        // (whole-tile blocks with bf16 gradients: (G Q_R)^T = Q_R^T G^T, A' = Q_R^T, B' = G)
         p.M = k.m; p.N = k.n; p.K = k.n; p.tiles_n = tn;
-        p.A = k.G; p.lda = k.ldg; p.B = QRt; p.ldb = ldqrt; p.C = Tt; p.ldc = ldt; p.flags = GEMM_STORE_T;
-        p.tile_start = tiles1[k.g_dtype]; tiles1[k.g_dtype] += tm * tn;
-        g1[k.g_dtype].push_back(p);
-        const bool fast = pg_f32_operand_ok(QLt, k.m, k.m, ldqlt) && pg_f32_operand_ok(Tt, k.n, k.m, ldt) &&
+        if (use1 && whole1(k)) {
+            PlaneProblem q;
+            memset(&q, 0, sizeof(q));
+            q.A = QRt; q.lda = ldqrt; q.B = k.G; q.ldb = k.ldg; q.C32 = Tt; q.ldc32 = ldt;
+            q.M = k.n; q.N = k.m; q.K = k.n; q.tiles_n = k.m / PgF32xB::TN;
+            q.tile_start = tiles1f; tiles1f += (k.n / PgF32xB::TM) * q.tiles_n;
+            q.state_idx = -1; q.state_mask = ~0; q.alpha = 1.0f; q.beta = 0.0f;
+            f1.push_back(q);
+        } else {
+            p.A = k.G; p.lda = k.ldg; p.B = QRt; p.ldb = ldqrt; p.C = Tt; p.ldc = ldt; p.flags = GEMM_STORE_T;
+            p.tile_start = tiles1[k.g_dtype]; tiles1[k.g_dtype] += tm * tn;
+            g1[k.g_dtype].push_back(p);
+        }
+        const bool fast = use2 && pg_f32_operand_ok(QLt, k.m, k.m, ldqlt) && pg_f32_operand_ok(Tt, k.n, k.m, ldt) &&
                           pg_f32_operand_ok(Np, k.m, k.n, ldw) && pg_f32_operand_ok(k.QR, k.n, k.n, k.ldqr) &&
                           pg_f32_operand_ok(k.QL, k.m, k.m, k.ldql);
         if (fast) {
@@ -563,6 +588,13 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[0], (int)g1[0].size(), tiles1[0], nullptr, stream)));
     if (!g1[1].empty())
         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<bf16_t, float, 1, 2>(d_g1b, (int)g1[1].size(), tiles1[1], nullptr, stream)));
+    if (!f1.empty()) {
+        // a two-sided block has one entry for its first product, of either kind: the region of d_g[0] holds them all
+        static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
+        PlaneProblem *d_f1 = reinterpret_cast<PlaneProblem *>(d_g1b + g1[1].size());
+        ASTERIA_HIP_TRY(upload_async(d_f1, f1.data(), f1.size() * sizeof(PlaneProblem), stream));
+        ASTERIA_HIP_TRY((launch_pgemm<PgF32xB>(d_f1, (int)f1.size(), tiles1f, nullptr, stream, 514)));
+    }
     if (!g2.empty()) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[1], (int)g2.size(), tiles, nullptr, stream)));
     if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[0], (int)f2.size(), tilesf, nullptr, stream, 513)));
     const float c1 = 1.0f - powf(beta1, (float)step_t), c2 = 1.0f - powf(beta2, (float)step_t);

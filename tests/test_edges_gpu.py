@@ -78,3 +78,39 @@ def test_refresh_at_the_edges(sizes):
         assert np.linalg.norm(Q.T @ Q - np.eye(n)) / np.sqrt(n) <= 1e-5, n
         assert np.linalg.norm(np.tril(R, -1)) <= 1e-5 * np.linalg.norm(Z), n
         assert np.all(np.diag(R) >= 0), n
+
+
+@pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("blocks", [
+    [(256, 256)] * 3 + [(250, 256)],                            # too few whole tiles: 128-wide tiles
+    [(256, 512)] * 48 + [(512, 256)] * 48 + [(257, 260)],       # whole tiles, and a ragged block beside them
+    [(256, 256)] * 112, [(256, 256)] * 113,                     # either side of the dispatch line, short K
+    [(512, 512)] * 32, [(512, 512)] * 33, [(512, 512)] * 65,    # K = 512: one round, a round and a remainder
+])
+def test_two_sided_products_at_the_edges(blocks, out):
+    g = torch.Generator(device=DEV).manual_seed(5)
+
+    def mk(m, n, dt=torch.float32):
+        return torch.randn(m, n, generator=g, device=DEV).to(dt)
+
+    def sym(n):                                                 # roots are symmetric
+        a = mk(n, n)
+        return (a + a.T).contiguous()
+
+    items = []
+    for i, (m, n) in enumerate(blocks):
+        # every third output is a view with a row pitch that is no multiple of 8
+        P = torch.full((m, n + (3 if i % 3 == 0 else 0)), float("nan"), device=DEV, dtype=out)[:, :n]
+        items.append((sym(m), mk(m, n, torch.bfloat16), sym(n), P))
+    ast.precondition(items)
+    steps = [(G, mk(*XL.shape) / XL.shape[0] ** 0.5, mk(*XR.shape) / XR.shape[0] ** 0.5, torch.zeros(P.shape, device=DEV), torch.ones(P.shape, device=DEV),
+              torch.empty(P.shape, device=DEV)) for XL, G, XR, P in items]
+    ast.soap_step(steps, 0.0, 0.5, 1e-8, 100)
+    torch.cuda.synchronize()
+    for (XL, G, XR, P), (_, QL, QR, M, _, _) in zip(items, steps):
+        ref = XL.double() @ G.double() @ XR.double()
+        # two bf16 terms of every fp32 operand keep 16 bits, in three operands; a bf16 result adds 2^-9
+        tol = 3 * 2.0 ** -16 + (2.0 ** -9 if out == torch.bfloat16 else 0.0)
+        assert float(torch.linalg.norm(P.double() - ref) / torch.linalg.norm(ref)) <= tol, P.shape
+        rot = QL.double().T.contiguous() @ G.double() @ QR.double()      # beta1 = 0: the first moment is G'
+        assert float(torch.linalg.norm(M.double() - rot) / torch.linalg.norm(rot)) <= 3 * 2.0 ** -16, P.shape
