@@ -941,11 +941,10 @@ asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int 
 namespace {
 
 // The plane path serves the fully automatic precision rules; everything pinned, absolute eps, square roots and
-// the classical schedule take run_pass below, and so does an fp64 prefix that the caller wants without int8
-// products: on planes it would need 48 bytes per element, there 40.
+// the classical schedule take run_pass below.
 bool plane_path(const Plan &pl, asteria_eps_mode mode, int n_max)
 {
-    return pl.xt_lowp && !(pl.fp64_iters > 0 && pl.i8_slices == 0) && mode == ASTERIA_EPS_RELATIVE && pl.root == 4 && pl.adapted && n_max <= 16384;
+    return pl.xt_lowp && mode == ASTERIA_EPS_RELATIVE && pl.root == 4 && pl.adapted && n_max <= 16384;
 }
 
 // Whether a factor's digits can turn out too coarse (largest possible diagonal of M_0: 1)
@@ -1365,7 +1364,7 @@ extern "C" size_t asteria_inverse_root_workspace_bytes(const asteria_factor *f, 
         // the call takes one of two paths (eps and root decide; pinned precision options never the second): room for either
         size_t b = factor_matrix_bytes(f[i].n, use64, use32) +
                    factor_i8_bytes(f[i].n, use64 ? (o.int8_slices < 0 ? 5 : o.int8_slices) : 0);
-        if (o.fp64_iters < 0 && o.lowp_from < 0) b = std::max(b, plane_factor_bytes(f[i].n, o.int8_slices != 0, o.int8_slices != 0));
+        if (o.fp64_iters < 0 && o.lowp_from < 0) b = std::max(b, plane_factor_bytes(f[i].n, true, true));
         b += factor_small_bytes(f[i].n);
         total += b;
         biggest = std::max(biggest, b);

@@ -11,7 +11,8 @@
 // bits is measured against, and every product reads its linear term from an operand it has streamed anyway.
 //
 // While the bottom of M's spectrum is below ROOT_LOWP_FLOOR the chain runs on digit planes (int8 matrix cores,
-// 32 or 40 bits against a uniform quantum), or, where the device finds 40 bits too few, on fp64 matrices;
+// 32 or 40 bits against a uniform quantum), or, where the device finds 40 bits too few or the caller asked for
+// it, on fp64 matrices;
 // afterwards on pair planes.  X is kept in pair planes throughout, the last update writes
 // the caller's fp32 matrix.
 #pragma once
