@@ -56,13 +56,13 @@ constexpr float ROOT_STOP_DEV = 1e-2f;
 // on the relative Frobenius error, which averages over directions)
 constexpr float ROOT_X_TOL = 7e-4f;
 
-constexpr int PM_TILE_WORDS = 2 * PACK_T + 2;   // floats per tile in pm_tile
+constexpr int PM_TILE_WORDS = 2 * PACK_T + 4;   // floats per tile in pm_tile: two vectors, a double, a float, padding
 
 // Scale of M, T, T^2, T^4 in the fp16-split products: their entries stay below a^4 < 23 (a <= 2.2),
 // so 2^10 keeps them under 2^15 with the fp16 range ending at 65504.
 constexpr float ROOT_F16_SCALE = 1024.0f;
 
-__device__ __forceinline__ float wave_sum(float v)
+template <typename T> __device__ __forceinline__ T wave_sum(T v)
 {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -70,7 +70,7 @@ __device__ __forceinline__ float wave_sum(float v)
 }
 
 // ---- lambda_max of large packed statistics (root_lanczos.h has the process and the other kernels) ---------
-// one workgroup (256 threads) per factor: start vector and its norm
+// one workgroup (256 threads) per factor: the unit start vector
 __global__ __launch_bounds__(256) void pm_init_kernel(const FactorDev *fd, FactorScal *fs)
 {
     const int f = blockIdx.x;
@@ -86,10 +86,9 @@ __global__ __launch_bounds__(256) void pm_init_kernel(const FactorDev *fd, Facto
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
+    const float t = red[0] + red[1] + red[2] + red[3], inv = t > 0.0f ? rsqrtf(t) : 0.0f;
+    for (int j = threadIdx.x; j < F.n; j += 256) F.pv[0][j] *= inv;      // the entries this thread has written
     if (threadIdx.x == 0) {
-        const float t = red[0] + red[1] + red[2] + red[3];
-        fs[f].inv_norm = t > 0.0f ? rsqrtf(t) : 0.0f;
-        fs[f].inv_prev = 0.0f;
         fs[f].rho = 0.0f;
         fs[f].lz_small = 0;
         fs[f].pm_done = 0;
@@ -108,33 +107,32 @@ __global__ __launch_bounds__(256) void pm_matvec_kernel(const FactorDev *fd, con
     const int n = F.n;
     const float *__restrict__ v = F.pv[src];
     float *__restrict__ y = F.pv[dst];
-    const float inv = fs[f].inv_norm;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __shared__ float red[4][4];
-    float syy = 0.0f, syv = 0.0f, saa = 0.0f, str = 0.0f;
+    __shared__ float red[4];
+    __shared__ double redd[2][4];
+    float syv = 0.0f;
+    double saa = 0.0, str = 0.0;                      // saa: every lane its part
     for (int rr = 0; rr < LZ_ROWS / 4; ++rr) {
         const int row = blk * LZ_ROWS + wave * (LZ_ROWS / 4) + rr;
         if (row >= n) break;
         const float *__restrict__ a = F.A + (size_t)row * F.lda;
-        float s = 0.0f, q = 0.0f;
+        float s = 0.0f;
 #pragma unroll 4
-        for (int j = lane; j < n; j += 64) { s += a[j] * v[j]; q += a[j] * a[j]; }
-        s = wave_sum(s) * inv;
-        if (first) q = wave_sum(q);
+        for (int j = lane; j < n; j += 64) { s += a[j] * v[j]; if (first) saa += (double)a[j] * (double)a[j]; }
+        s = wave_sum(s);
         if (lane == 0) {
             y[row] = s;
-            syy += s * s;
-            syv += s * (v[row] * inv);
-            saa += q;
-            str += a[row];
+            syv += s * v[row];
+            str += (double)a[row];
         }
     }
-    if (lane == 0) { red[0][wave] = syy; red[1][wave] = syv; red[2][wave] = saa; red[3][wave] = str; }
+    if (first) saa = wave_sum(saa);
+    if (lane == 0) { red[wave] = syv; redd[0][wave] = saa; redd[1][wave] = str; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        F.pm_partial[blk] = make_float2(red[0][0] + red[0][1] + red[0][2] + red[0][3], red[1][0] + red[1][1] + red[1][2] + red[1][3]);
+        F.pm_partial[blk] = red[0] + red[1] + red[2] + red[3];
         if (first)
-            F.pm_partial2[blk] = make_float2(red[2][0] + red[2][1] + red[2][2] + red[2][3], red[3][0] + red[3][1] + red[3][2] + red[3][3]);
+            F.pm_partial2[blk] = make_double2(redd[0][0] + redd[0][1] + redd[0][2] + redd[0][3], redd[1][0] + redd[1][1] + redd[1][2] + redd[1][3]);
     }
 }
 
@@ -158,10 +156,12 @@ __global__ __launch_bounds__(256) void pm_packed_tile_kernel(const FactorDev *fd
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c0 = tj * PACK_T + 2 * lane, r0 = ti * PACK_T;
     __shared__ float colp[4][PACK_T];
-    __shared__ float red[2][4];
+    __shared__ double redd[4];
+    __shared__ float redt[4];
     // this lane's two columns of the tile: entries of v_tj, zero beyond n
     const float vj0 = c0 < n ? v[c0] : 0.0f, vj1 = c0 + 1 < n ? v[c0 + 1] : 0.0f;
-    float cs0 = 0.0f, cs1 = 0.0f, saa = 0.0f, str = 0.0f;
+    float cs0 = 0.0f, cs1 = 0.0f, str = 0.0f;
+    double saa = 0.0;
     for (int rr = 0; rr < PACK_T / 4; ++rr) {
         const int r = wave * (PACK_T / 4) + rr, gr = r0 + r;
         float2 a = *reinterpret_cast<const float2 *>(tile + (size_t)r * PACK_T + 2 * lane);
@@ -173,28 +173,28 @@ __global__ __launch_bounds__(256) void pm_packed_tile_kernel(const FactorDev *fd
         const float vi = gr < n ? v[gr] : 0.0f;
         cs0 += a.x * vi; cs1 += a.y * vi;                       // column part: (T^T v_ti)[c]
         if (first) {
-            saa += a.x * a.x + a.y * a.y;
+            saa += (double)a.x * (double)a.x + (double)a.y * (double)a.y;
             if (ti == tj) { if (gr == c0) str += a.x; if (gr == c0 + 1) str += a.y; }
         }
     }
     colp[wave][2 * lane] = cs0; colp[wave][2 * lane + 1] = cs1;
     if (first) {
         saa = wave_sum(saa); str = wave_sum(str);
-        if (lane == 0) { red[0][wave] = saa; red[1][wave] = str; }
+        if (lane == 0) { redd[wave] = saa; redt[wave] = str; }
     }
     __syncthreads();
     if (threadIdx.x < PACK_T)
         out[PACK_T + threadIdx.x] = colp[0][threadIdx.x] + colp[1][threadIdx.x] + colp[2][threadIdx.x] + colp[3][threadIdx.x];
     if (first && threadIdx.x == 0) {
         // an off-diagonal tile stands for its mirror image too
-        const float w = ti == tj ? 1.0f : 2.0f;
-        out[2 * PACK_T] = w * (red[0][0] + red[0][1] + red[0][2] + red[0][3]);
-        out[2 * PACK_T + 1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+        const double w = ti == tj ? 1.0 : 2.0;
+        *reinterpret_cast<double *>(out + 2 * PACK_T) = w * (redd[0] + redd[1] + redd[2] + redd[3]);
+        out[2 * PACK_T + 2] = redt[0] + redt[1] + redt[2] + redt[3];
     }
 }
 
 // y[rows of block I] = sum over tj <= I of the row parts of tile (I, tj) + sum over ti > I of the column
-// parts of tile (ti, I), scaled by 1 / ||v||; per block the same partial sums pm_matvec_kernel leaves.
+// parts of tile (ti, I); per block the same partial sums pm_matvec_kernel leaves.
 __global__ __launch_bounds__(PACK_T) void pm_packed_reduce_kernel(const FactorDev *fd, const FactorScal *fs, int src, int dst, int first)
 {
     const int f = blockIdx.y;
@@ -203,35 +203,33 @@ __global__ __launch_bounds__(PACK_T) void pm_packed_reduce_kernel(const FactorDe
     const int T = (F.n + PACK_T - 1) / PACK_T, I = (int)blockIdx.x;
     if (!F.a_packed || I >= T) return;
     const int i = threadIdx.x, row = I * PACK_T + i;
-    const float inv = fs[f].inv_norm;
     const float *__restrict__ v = F.pv[src];
-    float s = 0.0f, saa = 0.0f, str = 0.0f;
+    float s = 0.0f;
+    double saa = 0.0, str = 0.0;
     for (int tj = 0; tj <= I; ++tj) {
         const float *p = F.pm_tile + (size_t)(I * (I + 1) / 2 + tj) * PM_TILE_WORDS;
         s += p[i];
-        if (first && i == 0) { saa += p[2 * PACK_T]; str += p[2 * PACK_T + 1]; }
+        if (first && i == 0) { saa += *reinterpret_cast<const double *>(p + 2 * PACK_T); str += (double)p[2 * PACK_T + 2]; }
     }
     for (int ti = I + 1; ti < T; ++ti) s += F.pm_tile[(size_t)(ti * (ti + 1) / 2 + I) * PM_TILE_WORDS + PACK_T + i];
-    s *= inv;
-    float syy = 0.0f, syv = 0.0f;
+    float syv = 0.0f;
     if (row < F.n) {
         F.pv[dst][row] = s;
-        syy = s * s;
-        syv = s * (v[row] * inv);
+        syv = s * v[row];
     }
-    __shared__ float red[2][PACK_T / 64];
-    syy = wave_sum(syy); syv = wave_sum(syv);
-    if ((i & 63) == 0) { red[0][i >> 6] = syy; red[1][i >> 6] = syv; }
+    __shared__ float red[PACK_T / 64];
+    syv = wave_sum(syv);
+    if ((i & 63) == 0) red[i >> 6] = syv;
     __syncthreads();
     if (i == 0) {
-        F.pm_partial[I] = make_float2(red[0][0] + red[0][1], red[1][0] + red[1][1]);
+        F.pm_partial[I] = red[0] + red[1];
         // the off-diagonal tiles of the block rows below this one were counted there (weight 2)
-        if (first) F.pm_partial2[I] = make_float2(saa, str);
+        if (first) F.pm_partial2[I] = make_double2(saa, str);
     }
 }
 
 // One workgroup per factor, after the mat-vec of step `it` (y = A v in pv[dst], v in pv[src], the vector
-// before it in pv[prev]): alpha, the next Lanczos vector (over y, unnormalised), beta, the estimate, the stop.
+// before it in pv[prev]): alpha, the next Lanczos vector (over y), beta, the estimate, the stop.
 // A factor stops once three consecutive steps have raised the estimate by less than tol2 of it (or the
 // recurrence ends: beta = 0, an invariant subspace, where the estimate is exact).
 __global__ __launch_bounds__(256) void pm_lanczos_kernel(const FactorDev *fd, FactorScal *fs, float tol2, int it,
@@ -242,60 +240,54 @@ __global__ __launch_bounds__(256) void pm_lanczos_kernel(const FactorDev *fd, Fa
     if (S.pm_done) return;
     const FactorDev &F = fd[f];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float inv = S.inv_norm, inv_p = S.inv_prev;
     const float beta_p = it > 0 ? S.lz_b[it - 1] : 0.0f;
-    __shared__ double red[4][4];
+    __shared__ double red[3][4];
     // sums the mat-vec workgroups left per block of rows, in a fixed order
-    double yy = 0.0, yv = 0.0, aa = 0.0, tr = 0.0;
+    double yv = 0.0, aa = 0.0, tr = 0.0;
     for (int b = tid; b < F.pm_blocks; b += 256) {
-        const float2 p = F.pm_partial[b];
-        yy += (double)p.x; yv += (double)p.y;
-        if (first) { const float2 q = F.pm_partial2[b]; aa += (double)q.x; tr += (double)q.y; }
+        yv += (double)F.pm_partial[b];
+        if (first) { const double2 q = F.pm_partial2[b]; aa += q.x; tr += q.y; }
     }
-    auto block_sum4 = [&](double &x0, double &x1, double &x2, double &x3) {
+    auto block_sum3 = [&](double &x0, double &x1, double &x2) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
-            x0 += __shfl_xor(x0, off, 64); x1 += __shfl_xor(x1, off, 64);
-            x2 += __shfl_xor(x2, off, 64); x3 += __shfl_xor(x3, off, 64);
+            x0 += __shfl_xor(x0, off, 64); x1 += __shfl_xor(x1, off, 64); x2 += __shfl_xor(x2, off, 64);
         }
         __syncthreads();
-        if (lane == 0) { red[0][wave] = x0; red[1][wave] = x1; red[2][wave] = x2; red[3][wave] = x3; }
+        if (lane == 0) { red[0][wave] = x0; red[1][wave] = x1; red[2][wave] = x2; }
         __syncthreads();
         x0 = red[0][0] + red[0][1] + red[0][2] + red[0][3]; x1 = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-        x2 = red[2][0] + red[2][1] + red[2][2] + red[2][3]; x3 = red[3][0] + red[3][1] + red[3][2] + red[3][3];
+        x2 = red[2][0] + red[2][1] + red[2][2] + red[2][3];
     };
-    block_sum4(yy, yv, aa, tr);
-    const bool finite = (yy == yy) && (yy < 3.0e38);
+    block_sum3(yv, aa, tr);
     const float alpha = (float)yv;                    // v is a unit vector: alpha = v^T A v
     // w = y - alpha v - beta_{j-1} v_{j-1}, written over y
     const float *__restrict__ v = F.pv[src], *__restrict__ vp = F.pv[prev];
     float *__restrict__ w = F.pv[dst];
-    double ww = 0.0, z1 = 0.0, z2 = 0.0, z3 = 0.0;
-    if (finite) {
-        for (int i = tid; i < F.n; i += 256) {
-            float x = w[i] - alpha * (v[i] * inv);
-            if (it > 0) x -= beta_p * (vp[i] * inv_p);
-            w[i] = x;
-            ww += (double)x * (double)x;
-        }
+    double ww = 0.0, z1 = 0.0, z2 = 0.0;
+    for (int i = tid; i < F.n; i += 256) {
+        float x = w[i] - alpha * v[i];
+        if (it > 0) x -= beta_p * vp[i];
+        w[i] = x;
+        ww += (double)x * (double)x;
     }
-    block_sum4(ww, z1, z2, z3);
-    if (first && tid == 0) { S.fro2 = (float)aa; S.trace = (float)tr; }
-    if (!finite) {
+    block_sum3(ww, z1, z2);
+    if (first && tid == 0) { S.fro2 = aa; S.trace = tr; }
+    const float beta = (float)sqrt(ww);
+    if (!(beta < 3.0e38f) || !(fabsf(alpha) < 3.0e38f)) {
         if (tid == 0) { S.rho = NAN; S.pm_done = 1; }
         return;
     }
-    const float beta = (float)sqrt(ww);
+    // unit vectors throughout: A times an unnormalised one would be of the size of A squared
+    const float inv = beta > 0.0f ? 1.0f / beta : 0.0f;
+    for (int i = tid; i < F.n; i += 256) w[i] *= inv;
     __shared__ float la[LZ_MAX], lb[LZ_MAX];
     if (tid < it) { la[tid] = S.lz_a[tid]; lb[tid] = S.lz_b[tid]; }
     if (tid == 0) { S.lz_a[it] = la[it] = alpha; S.lz_b[it] = lb[it] = beta; }
     __syncthreads();
     if (wave != 0) return;
     const bool stop = lanczos_advance(S, la, lb, it, beta, tol2);
-    if (lane != 0) return;
-    if (stop || last) { S.pm_done = 1; return; }
-    S.inv_prev = inv;
-    S.inv_norm = 1.0f / beta;
+    if (lane == 0 && (stop || last)) S.pm_done = 1;
 }
 
 // ---- scaling and start of the coupled iteration ---------------------------------------------
@@ -331,8 +323,8 @@ __global__ void root_setup_kernel(const FactorDev *fd, FactorScal *fs, int *stat
         // ||M_0 - I||_F^2 = s^2 ||A + eps I||_F^2 - 2 s tr(A + eps I) + n bounds every |mu - 1|:
         // a well-conditioned factor gets a much tighter interval than [eps s, 1]
         const double sc = 1.0 / (double)denom, e = (double)eps, n = (double)fd[f].n;
-        const double f2 = (double)S.fro2 + 2.0 * e * (double)S.trace + n * e * e;
-        const double tr = (double)S.trace + n * e;
+        const double f2 = S.fro2 + 2.0 * e * S.trace + n * e * e;
+        const double tr = S.trace + n * e;
         double r2 = sc * sc * f2 - 2.0 * sc * tr + n;
         r2 = r2 * (1.0 + 1e-3) + 1e-6 * n;           // slack for the fp32 sums
         if (r2 > 0.0 && r2 < 1.0) { const double l1 = 1.0 - sqrt(r2); if (l1 > lo) lo = l1; }
@@ -715,7 +707,8 @@ size_t factor_i8_bytes(int n, int ns)
 size_t factor_small_bytes(int n)
 {
     const int pmb = (n + LZ_ROWS - 1) / LZ_ROWS;
-    return 5 * Carver::need((size_t)ld4(n), sizeof(float)) + 2 * Carver::need(2 * (size_t)pmb, sizeof(float2)) +
+    return 5 * Carver::need((size_t)ld4(n), sizeof(float)) + Carver::need(2 * (size_t)pmb, sizeof(float)) +
+           Carver::need((size_t)pmb, sizeof(double2)) +
            Carver::need(2 * (size_t)tri_tiles(n), sizeof(float)) + Carver::need((size_t)tri_tiles(n) * PM_TILE_WORDS, sizeof(float)) +
            sizeof(FactorDev) + sizeof(FactorScal) +
            2 * sizeof(int) + 16 * sizeof(GemmProblem) + plane_small_bytes(n);
@@ -995,8 +988,8 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         a_min = std::min(a_min, er / (1.0 + (double)pl.margin + er));
         for (int v = 0; v < 3; ++v) F.pv[v] = cv.take<float>(ld4(n));
         for (int v = 0; v < 2; ++v) F.py[v] = cv.take<float>(ld4(n));
-        F.pm_partial = cv.take<float2>(2 * (size_t)((n + LZ_ROWS - 1) / LZ_ROWS));
-        F.pm_partial2 = cv.take<float2>((n + LZ_ROWS - 1) / LZ_ROWS);
+        F.pm_partial = cv.take<float>(2 * (size_t)((n + LZ_ROWS - 1) / LZ_ROWS));
+        F.pm_partial2 = cv.take<double2>((n + LZ_ROWS - 1) / LZ_ROWS);
         F.pm_tile = cv.take<float>((size_t)F.ntri * PM_TILE_WORDS);
         F.partial = cv.take<float>(F.npart);
         const size_t pair = (size_t)n * F.rowb, slot = plane_slot_bytes(n, prefix, f64);
@@ -1154,8 +1147,8 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
         }
         for (int v = 0; v < 3; ++v) F.pv[v] = cv.take<float>(ld4(n));
         for (int v = 0; v < 2; ++v) F.py[v] = cv.take<float>(ld4(n));
-        F.pm_partial = cv.take<float2>(2 * (size_t)((n + LZ_ROWS - 1) / LZ_ROWS));
-        F.pm_partial2 = cv.take<float2>((n + LZ_ROWS - 1) / LZ_ROWS);
+        F.pm_partial = cv.take<float>(2 * (size_t)((n + LZ_ROWS - 1) / LZ_ROWS));
+        F.pm_partial2 = cv.take<double2>((n + LZ_ROWS - 1) / LZ_ROWS);
         F.pm_tile = cv.take<float>((size_t)F.ntri * PM_TILE_WORDS);
         F.partial = cv.take<float>(2 * (size_t)F.ntri);
     }

@@ -36,8 +36,8 @@ struct FactorDev {
     int ldw;
     float *pv[3];       // Lanczos vectors (packed statistics: the current one, the one before it, A times the current one)
     float *py[2];       // A times the vectors of the last two steps
-    float2 *pm_partial; // per mat-vec workgroup: (sum y^2, sum y v); two steps' in turn
-    float2 *pm_partial2; // per mat-vec workgroup, first step only: (sum a_ij^2, sum a_ii)
+    float *pm_partial;  // per mat-vec workgroup: sum y v; two steps' in turn
+    double2 *pm_partial2; // per mat-vec workgroup, first step only: (sum a_ij^2, sum a_ii)
     float *partial;     // per lower-triangle tile: sum (M - I)^2 (2 ntri entries: a second one per tile for kernels that split tiles)
     int n, lda, ldx;
     int ld32, ld64;
@@ -46,7 +46,7 @@ struct FactorDev {
     int pm_blocks;
     float eps_in;
     int a_packed;       // A lies in packed lower tiles (gemm.h, packed_off): lda unused
-    float *pm_tile;     // packed A: per lower tile 2 x 128 partial products of the mat-vec and (sum a^2, trace part)
+    float *pm_tile;     // packed A: per lower tile 2 x 128 partial products of the mat-vec and (sum a^2 as a double, trace part)
 };
 
 // coefficients of one product of the plane path: C = own1 O1 + own2 O2 + gam A B, in values
@@ -57,8 +57,6 @@ struct FactorScal {
     float eps;       // absolute eps used
     float scale;     // s
     float resid;     // last ||M - I||_F
-    float inv_norm;  // 1 / ||v|| of the current Lanczos vector (the vectors are stored unnormalised)
-    float inv_prev;  // the same for the vector before it
     float rho;       // largest Ritz value so far: the lambda_max estimate
     int lz_small;    // consecutive steps that moved the estimate by less than the tolerance
     int iters;       // X updates performed / scheduled
@@ -68,7 +66,9 @@ struct FactorScal {
     float lo, hi;    // interval assumed to contain the spectrum of the current M
     float ca, cg;    // coefficients of the current T = ca I - cg M
     float coef_next[2];   // coefficients the M-update epilogue uses for the next T
-    float fro2, trace;    // ||A||_F^2 and tr(A), gathered during the first mat-vec of the lambda_max estimate
+    // ||A||_F^2 and tr(A), gathered during the first mat-vec of the lambda_max estimate; squares of fp32 numbers do
+    // not fit fp32 for statistics of the size of 1e-20
+    double fro2, trace;
     float x_scale;        // power of two that brings X into the fp16 range for the 16-bit products
     // (lo, hi) of the M the current iteration starts from and the g of its T: lo, hi, ca, cg above
     // are advanced to the next iteration's before the products of the current one run

@@ -34,6 +34,11 @@ __device__ __forceinline__ float hash_unit(uint32_t f, uint32_t j)
     return (float)(x >> 8) * (1.0f / 8388608.0f) - 1.0f;   // [-1, 1)
 }
 
+__device__ __forceinline__ double square_sum(const float4 &t)
+{
+    return (double)t.x * (double)t.x + (double)t.y * (double)t.y + (double)t.z * (double)t.z + (double)t.w * (double)t.w;
+}
+
 // One wavefront: largest eigenvalue of the symmetric tridiagonal matrix with diagonal a[0 .. m) and off-diagonal
 // b[0 .. m - 1), given `before`, that of the leading m - 1 rows (ignored for m = 1).  It lies in
 // [max(before, a_m), max(before, a_m) + |b_{m-1}|]; every lane tests one point of the bracket (all leading minors
@@ -104,7 +109,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
     const float *__restrict__ A = F.Aw;
     extern __shared__ __align__(16) float lz_smem[];
     float *v = lz_smem, *vp = v + ld, *y = vp + ld;          // ld: n of the largest factor, padded to 256
-    __shared__ float red[2][LZ_WAVES];
+    __shared__ float red[LZ_WAVES];
     __shared__ double redd[2][LZ_WAVES];
     __shared__ float la[LZ_MAX], lb[LZ_MAX];
     __shared__ int done;
@@ -157,12 +162,12 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) saa += (double)(ar[q][e] * ar[q][e]);
+                for (int e = 0; e < 16; ++e) saa += (double)ar[q][e] * (double)ar[q][e];
         }
         for (int i = tid; i < n; i += LZ_THREADS) str += (double)A[(size_t)i * lda + i];
         saa = block_sum(saa);                                // streamed factors: gathered in the first product
         str = block_sum(str);
-        if (tid == 0) { S.fro2 = (float)saa; S.trace = (float)str; S.rho = 0.0f; S.lz_small = 0; S.pm_done = 0; }
+        if (tid == 0) { S.fro2 = saa; S.trace = str; S.rho = 0.0f; S.lz_small = 0; S.pm_done = 0; }
     } else {
         j0 = resume - 1;                                     // its y is there, its alpha is not
         for (int i = tid; i < ld; i += LZ_THREADS) {
@@ -204,7 +209,8 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
             double saa = 0.0;
             auto product = [&](auto first) {
                 for (int r0 = 4 * wave; r0 < n; r0 += 4 * LZ_WAVES) {
-                    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f}, q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                    double q[4] = {0.0, 0.0, 0.0, 0.0};
                     const float *ap[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) ap[e] = A + (size_t)min(r0 + e, n - 1) * lda;
@@ -218,7 +224,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
                             for (int e = 0; e < 4; ++e) {
                                 const float4 t = reinterpret_cast<const float4 *>(ap[e])[c];
                                 s[e] += t.x * x.x + t.y * x.y + t.z * x.z + t.w * x.w;
-                                if constexpr (decltype(first)::value) q[e] += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
+                                if constexpr (decltype(first)::value) q[e] += square_sum(t);
                             }
                         }
                         c0 = n4 << 2;
@@ -230,7 +236,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
                         for (int e = 0; e < 4; ++e) {
                             const float t = ap[e][c];
                             s[e] += t * x;
-                            if constexpr (decltype(first)::value) q[e] += t * t;
+                            if constexpr (decltype(first)::value) q[e] += (double)t * (double)t;
                         }
                     }
 #pragma unroll
@@ -240,7 +246,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
                         if (r0 + e < n) {
                             if (lane == 0) y[r0 + e] = s[e];
                             yv += s[e] * v[r0 + e];
-                            if constexpr (decltype(first)::value) saa += (double)q[e];
+                            if constexpr (decltype(first)::value) saa += q[e];
                         }
                     }
                 }
@@ -248,28 +254,28 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
             if (j == 0) {
                 product(std::true_type{});
                 saa = block_sum(saa);
-                if (tid == 0) S.fro2 = (float)saa;
+                if (tid == 0) S.fro2 = saa;
             } else product(std::false_type{});
         }
-        if (lane == 0) red[0][wave] = yv;
+        if (lane == 0) red[wave] = yv;
         if (tid == 0 && stop) done = 1;
         __syncthreads();
         if (done) break;
         double alpha_d = 0.0;
-        for (int w = 0; w < LZ_WAVES; ++w) alpha_d += (double)red[0][w];
+        for (int w = 0; w < LZ_WAVES; ++w) alpha_d += (double)red[w];
         const float alpha = (float)alpha_d;
-        float ww = 0.0f;
+        double ww = 0.0;
         for (int i = tid; i < n; i += LZ_THREADS) {
             const float x = y[i] - alpha * v[i] - beta_p * vp[i];
             y[i] = x;
-            ww += x * x;
+            ww += (double)x * (double)x;
         }
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) ww += __shfl_xor(ww, off, 64);
-        if (lane == 0) red[1][wave] = ww;
+        if (lane == 0) redd[1][wave] = ww;
         __syncthreads();
         double ww_d = 0.0;
-        for (int w = 0; w < LZ_WAVES; ++w) ww_d += (double)red[1][w];
+        for (int w = 0; w < LZ_WAVES; ++w) ww_d += redd[1][w];
         const float beta = (float)sqrt(ww_d);
         if (!(beta < 3.0e38f) || !(fabsf(alpha) < 3.0e38f)) {         // non-finite input (uniform)
             if (tid == 0) S.rho = NAN;
@@ -305,7 +311,7 @@ __global__ __launch_bounds__(256) void lanczos_step_kernel(const FactorDev *fd, 
     extern __shared__ __align__(16) float lz_smem[];
     float *v = lz_smem;
     __shared__ double redd[4];
-    __shared__ float red[2][4];
+    __shared__ float red[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto block_sum = [&](double x) -> double {
 #pragma unroll
@@ -321,7 +327,7 @@ __global__ __launch_bounds__(256) void lanczos_step_kernel(const FactorDev *fd, 
         for (int i = tid; i < n; i += 256) { const float x = hash_unit(0u, (uint32_t)i); v[i] = x; ww += (double)x * (double)x; }
     } else {
         double yv = 0.0;
-        for (int b = tid; b < F.pm_blocks; b += 256) yv += (double)F.pm_partial[((j - 1) & 1) * F.pm_blocks + b].y;
+        for (int b = tid; b < F.pm_blocks; b += 256) yv += (double)F.pm_partial[((j - 1) & 1) * F.pm_blocks + b];
         alpha = (float)block_sum(yv);
         const float *__restrict__ y = F.py[(j - 1) & 1], *__restrict__ v1 = F.pv[(j - 1) % 3], *__restrict__ v2 = F.pv[(j + 1) % 3];
         const float beta_p = j > 1 ? S.lz_b[j - 2] : 0.0f;
@@ -345,10 +351,10 @@ __global__ __launch_bounds__(256) void lanczos_step_kernel(const FactorDev *fd, 
         }
         if (j == 1) {
             double aa = 0.0, tr = 0.0;
-            for (int b = tid; b < F.pm_blocks; b += 256) { const float2 q = F.pm_partial2[b]; aa += (double)q.x; tr += (double)q.y; }
+            for (int b = tid; b < F.pm_blocks; b += 256) { const double2 q = F.pm_partial2[b]; aa += q.x; tr += q.y; }
             aa = block_sum(aa);
             tr = block_sum(tr);
-            if (tid == 0) { S.fro2 = (float)aa; S.trace = (float)tr; }
+            if (tid == 0) { S.fro2 = aa; S.trace = tr; }
         }
         if (!(beta < 3.0e38f) || !(fabsf(alpha) < 3.0e38f)) {
             if (tid == 0) { S.rho = NAN; S.pm_done = 1; }
@@ -366,16 +372,17 @@ __global__ __launch_bounds__(256) void lanczos_step_kernel(const FactorDev *fd, 
     }
     const float *__restrict__ A = F.Aw;
     const bool vec = ((reinterpret_cast<uintptr_t>(A) & 15u) == 0) && ((lda & 3) == 0);
-    float syv = 0.0f, saa = 0.0f, str = 0.0f;
+    float syv = 0.0f;
+    double saa = 0.0, str = 0.0;                             // every lane its part of the squares, lane 0 the diagonal
     const int base = blockIdx.x * LZ_ROWS + wave * (LZ_ROWS / 4);
 #pragma unroll 1
     for (int rr = 0; rr < LZ_ROWS / 4; rr += 4) {
         const int r0 = base + rr;
         if (r0 >= n) break;
-        float s[4] = {0.0f, 0.0f, 0.0f, 0.0f}, q = 0.0f;
+        float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         const float *a0 = A + (size_t)r0 * lda, *a1 = A + (size_t)min(r0 + 1, n - 1) * lda;
         const float *a2 = A + (size_t)min(r0 + 2, n - 1) * lda, *a3 = A + (size_t)min(r0 + 3, n - 1) * lda;
-        const float m1 = r0 + 1 < n ? 1.0f : 0.0f, m2 = r0 + 2 < n ? 1.0f : 0.0f, m3 = r0 + 3 < n ? 1.0f : 0.0f;
+        const double m1 = r0 + 1 < n ? 1.0 : 0.0, m2 = r0 + 2 < n ? 1.0 : 0.0, m3 = r0 + 3 < n ? 1.0 : 0.0;
         int c0 = 0;
         if (vec) {
             const int n4 = n >> 2;
@@ -388,9 +395,7 @@ __global__ __launch_bounds__(256) void lanczos_step_kernel(const FactorDev *fd, 
                 s[1] += t1.x * x.x + t1.y * x.y + t1.z * x.z + t1.w * x.w;
                 s[2] += t2.x * x.x + t2.y * x.y + t2.z * x.z + t2.w * x.w;
                 s[3] += t3.x * x.x + t3.y * x.y + t3.z * x.z + t3.w * x.w;
-                if (j == 0)
-                    q += t0.x * t0.x + t0.y * t0.y + t0.z * t0.z + t0.w * t0.w + m1 * (t1.x * t1.x + t1.y * t1.y + t1.z * t1.z + t1.w * t1.w) +
-                         m2 * (t2.x * t2.x + t2.y * t2.y + t2.z * t2.z + t2.w * t2.w) + m3 * (t3.x * t3.x + t3.y * t3.y + t3.z * t3.z + t3.w * t3.w);
+                if (j == 0) saa += square_sum(t0) + m1 * square_sum(t1) + m2 * square_sum(t2) + m3 * square_sum(t3);
             }
             c0 = n4 << 2;
         }
@@ -398,7 +403,10 @@ __global__ __launch_bounds__(256) void lanczos_step_kernel(const FactorDev *fd, 
         for (int c = c0 + lane; c < n; c += 64) {
             const float x = v[c];
             s[0] += a0[c] * x; s[1] += a1[c] * x; s[2] += a2[c] * x; s[3] += a3[c] * x;
-            if (j == 0) q += a0[c] * a0[c] + m1 * a1[c] * a1[c] + m2 * a2[c] * a2[c] + m3 * a3[c] * a3[c];
+            if (j == 0) {
+                const double t0 = (double)a0[c], t1 = (double)a1[c], t2 = (double)a2[c], t3 = (double)a3[c];
+                saa += t0 * t0 + m1 * t1 * t1 + m2 * t2 * t2 + m3 * t3 * t3;
+            }
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -407,24 +415,17 @@ __global__ __launch_bounds__(256) void lanczos_step_kernel(const FactorDev *fd, 
             if (r0 + e < n) {
                 syv += s[e] * v[r0 + e];
                 if (lane == 0) F.py[j & 1][r0 + e] = s[e];
-                if (j == 0) str += A[(size_t)(r0 + e) * lda + r0 + e];
+                if (j == 0) str += (double)A[(size_t)(r0 + e) * lda + r0 + e];
             }
         }
-        if (j == 0) {
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off, 64);
-            saa += q;
-        }
     }
-    if (lane == 0) red[0][wave] = syv;
+    if (lane == 0) red[wave] = syv;
     __syncthreads();
-    if (tid == 0) F.pm_partial[(j & 1) * F.pm_blocks + blockIdx.x] = make_float2(0.0f, red[0][0] + red[0][1] + red[0][2] + red[0][3]);
+    if (tid == 0) F.pm_partial[(j & 1) * F.pm_blocks + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
     if (j == 0) {
-        __syncthreads();
-        if (lane == 0) { red[0][wave] = saa; red[1][wave] = str; }
-        __syncthreads();
-        if (tid == 0)
-            F.pm_partial2[blockIdx.x] = make_float2(red[0][0] + red[0][1] + red[0][2] + red[0][3], red[1][0] + red[1][1] + red[1][2] + red[1][3]);
+        saa = block_sum(saa);
+        str = block_sum(lane == 0 ? str : 0.0);
+        if (tid == 0) F.pm_partial2[blockIdx.x] = make_double2(saa, str);
     }
 }
 

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(256) void plane_setup_kernel(const FactorDev *fd, F
     const float eps = F.eps_in * lam;
     S.eps = eps;
     const float denom = (1.0f + margin) * lam + eps;
-    const bool ok = (lam == lam) && (lam >= 0.0f) && (lam < 3.0e38f) && (denom > 0.0f) && (denom < 3.0e38f);
+    const bool ok = (lam == lam) && (lam >= 0.0f) && (lam < 3.0e38f) && (denom > 0.0f) && (denom < 3.0e38f) && (1.0f / denom < 3.0e38f);
     if (!ok) {
         S.scale = 0.0f; S.info = ASTERIA_INFO_NOT_PD; S.tier = TIER_PAIR;
         state[f] = ST_FAIL;
@@ -202,11 +202,14 @@ __global__ __launch_bounds__(256) void plane_setup_kernel(const FactorDev *fd, F
     double lo = 0.5 * e / (double)denom;
     if (!(lo > 1e-12)) lo = 1e-12;
     // ||M_0 - I||_F bounds every |mu - 1|: a well-conditioned factor gets a much tighter interval
-    const double f2 = (double)S.fro2 + 2.0 * e * tr + n * e * e;
+    const double f2 = S.fro2 + 2.0 * e * tr + n * e * e;
     double r2 = sc * sc * f2 - 2.0 * sc * (tr + n * e) + n;
-    const double rs = r2 * (1.0 + 1e-3) + 1e-6 * n;                  // slack for the fp32 sums
+    const double rs = r2 * (1.0 + 1e-3) + 1e-6 * n;                  // slack for the sums and for the fp32 scale
     if (rs > 0.0 && rs < 1.0) { const double l1 = 1.0 - sqrt(rs); if (l1 > lo) lo = l1; }
-    if (!(r2 > 1e-6 * n)) r2 = 1e-6 * n;
+    // the difference of large terms stands in for a measured residual only where it can be one: a clearly negative
+    // or non-finite value says nothing, and the interval is left as it is
+    if (!(r2 >= -1e-6 * n) || !(r2 < 1e300)) r2 = (double)n * ROOT_TOP * ROOT_TOP;
+    else if (r2 < 1e-6 * n) r2 = 1e-6 * n;
     // |X_k| <= xs (2 / lo)^(1/4) for every iterate (see root_setup_kernel): the fp16 terms of X are scaled by the
     // largest power of two that keeps this below 30000
     const double bound = sqrt(sqrt(sc)) * sqrt(sqrt(2.0 / lo));

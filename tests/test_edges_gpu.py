@@ -114,3 +114,37 @@ def test_two_sided_products_at_the_edges(blocks, out):
         assert float(torch.linalg.norm(P.double() - ref) / torch.linalg.norm(ref)) <= tol, P.shape
         rot = QL.double().T.contiguous() @ G.double() @ QR.double()      # beta1 = 0: the first moment is G'
         assert float(torch.linalg.norm(M.double() - rot) / torch.linalg.norm(rot)) <= 3 * 2.0 ** -16, P.shape
+
+
+@pytest.mark.parametrize("opts", [None, dict(int8_slices=0), dict(lowp_from=40)])
+@pytest.mark.parametrize("power", [-100, -80, -64, 48])
+@pytest.mark.parametrize("sizes", [
+    [33, 128, 257],                                             # one workgroup per recurrence: in registers, streamed
+    [513, 640],                                                 # one launch per step
+    [96] * 192,                                                 # a full batch
+])
+def test_roots_do_not_depend_on_the_magnitude_of_the_statistics(sizes, power, opts):
+    # squares of entries below 1e-19 and above 1e19 lie outside fp32; powers of 16 scale the root by a power of two
+    o = None if opts is None else ast.RootOpts(**opts)
+    for packed in (False, True):
+        As = [_with_spectrum(n, _spectrum("power", n), 7, n) for n in sizes]
+        if packed and len(As) > 3:
+            continue
+        got = []
+        for s in (1.0, 2.0 ** power):
+            Bs = [A * s for A in As]
+            Xs = [torch.full_like(A, float("nan")) for A in As]
+            lam = torch.zeros(len(As), device=DEV)
+            info = torch.full((len(As),), -1, dtype=torch.int32, device=DEV)
+            if packed:
+                Ps = [torch.empty(ast.packed_elems(n), device=DEV) for n in sizes]
+                ast.sym_pack(list(zip(Bs, Ps)))
+            ast.inverse_root([(b, x, 1 if packed else 0) for b, x in zip(Ps if packed else Bs, Xs)], 1e-6, opts=o, info=info, lambda_max=lam)
+            torch.cuda.synchronize()
+            assert bool((info == 0).all()), (s, info)
+            got.append((Xs, lam.double() / s))
+        assert float(((got[1][1] - got[0][1]) / got[0][1]).abs().max()) <= 1e-6
+        for x0, x1 in zip(got[0][0], got[1][0]):
+            x1 = x1.double() * 2.0 ** (power // 4)
+            # the same operations on scaled numbers: what the scale itself rounds (pow, the power of two for fp16) remains
+            assert float(torch.linalg.norm(x1 - x0.double()) / torch.linalg.norm(x0.double())) <= 1e-6
