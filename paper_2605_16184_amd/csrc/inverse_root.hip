@@ -905,8 +905,11 @@ asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int 
         const int launches = n_max < LZ_LAUNCH_N ? std::min(steps, LZ_LAUNCHES) : steps;
         for (int j = 0; j < launches; ++j)
             hipLaunchKernelGGL(lanczos_step_kernel, dim3(blocks + 1, cnt), dim3(256), lds1, stream, d_fd, d_fs, tol2, j, blocks);
-        if (launches < steps || n_max <= LZ_WG_MAX_N) {
-            // the last launch's y is in place, its alpha is not: one workgroup per factor goes on from there
+        // the last launch's y is in place, its alpha is not: one workgroup per factor goes on from there, or
+        // (no steps left) a launch of the workgroup that keeps the recurrence alone
+        if (launches == steps) {
+            hipLaunchKernelGGL(lanczos_step_kernel, dim3(1, cnt), dim3(256), lds1, stream, d_fd, d_fs, tol2, steps, 0);
+        } else {
             ASTERIA_HIP_TRY(ensure_dynamic_lds(reinterpret_cast<const void *>(lanczos_factor_kernel<false>), 3 * sizeof(float) * LZ_WG_MAX_N, cfg_f));
             hipLaunchKernelGGL(lanczos_factor_kernel<false>, dim3(cnt), dim3(LZ_THREADS), lds, stream, d_fd, d_fs, tol2, steps, launches, ld);
         }

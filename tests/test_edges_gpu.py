@@ -148,3 +148,47 @@ def test_roots_do_not_depend_on_the_magnitude_of_the_statistics(sizes, power, op
             x1 = x1.double() * 2.0 ** (power // 4)
             # the same operations on scaled numbers: what the scale itself rounds (pow, the power of two for fp16) remains
             assert float(torch.linalg.norm(x1 - x0.double()) / torch.linalg.norm(x0.double())) <= 1e-6
+
+
+def _largest_ritz_value(A, steps):
+    """After `steps` Lanczos steps in fp64 from the library's start vector."""
+    n = A.shape[0]
+    x = (np.arange(n, dtype=np.uint64) * 0x9E3779B1 + 0x165667B1) & 0xFFFFFFFF
+    x ^= x >> np.uint64(15); x = x * 0x2C1B3C6D & 0xFFFFFFFF; x ^= x >> np.uint64(12); x = x * 0x297A2D39 & 0xFFFFFFFF; x ^= x >> np.uint64(15)
+    v = torch.from_numpy((x >> np.uint64(8)).astype(np.float64) / 8388608.0 - 1.0).to(DEV)
+    v, prev, beta, a, b = v / v.norm(), torch.zeros_like(v), 0.0, [], []
+    for _ in range(steps):
+        w = A.double() @ v
+        a.append(float(w @ v))
+        w = w - a[-1] * v - beta * prev
+        beta = float(w.norm())
+        b.append(beta)
+        prev, v = v, w / beta
+    return float(np.linalg.eigvalsh(np.diag(a) + np.diag(b[:-1], 1) + np.diag(b[:-1], -1))[-1])
+
+
+@pytest.mark.parametrize("opts", [dict(), dict(lowp_from=40)])
+@pytest.mark.parametrize("steps", [1, 2, 32, 33])
+@pytest.mark.parametrize("n", [256, 257, 512, 513, 2047, 2048, 8193])
+def test_roots_with_a_bound_on_the_steps_of_the_largest_eigenvalue(n, steps, opts):
+    if n > 4096 and (opts or steps == 33):
+        pytest.skip("one size of this path is enough")
+    # spectrum in about [0.9, 1]: an estimate from one step is 5 % low at most, which the interval covers
+    g = torch.Generator(device=DEV).manual_seed(n)
+    A = torch.randn(n, n, generator=g, device=DEV)
+    A = 0.95 * torch.eye(n, device=DEV) + (0.05 / (2.0 * (2.0 * n) ** 0.5)) * (A + A.T)
+    X = torch.full_like(A, float("nan"))
+    lam = torch.zeros(1, device=DEV)
+    info = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+    o = ast.RootOpts(power_iters=steps, power_tol=1e-30, **opts)
+    ws = torch.full((ast.inverse_root_workspace_bytes([(A, X)], o)[0],), 255, dtype=torch.uint8, device=DEV)   # NaN in every format
+    ast.inverse_root([(A, X)], 1e-6, opts=o, info=info, lambda_max=lam, ws=ws)
+    torch.cuda.synchronize()
+    assert int(info[0]) == 0
+    want = _largest_ritz_value(A, steps)
+    # fp32 sums of n terms in A v and v^T A v
+    assert abs(float(lam[0]) - want) <= 1e-5 * want, (float(lam[0]), want)
+    Y = X.double()
+    Y = Y @ Y
+    E = Y @ Y @ (A.double() + 1e-6 * float(lam[0]) * torch.eye(n, device=DEV, dtype=torch.float64)) - torch.eye(n, device=DEV, dtype=torch.float64)
+    assert float(torch.linalg.norm(E)) / n ** 0.5 <= 4 * 2e-3       # four factors of the accuracy of the root
