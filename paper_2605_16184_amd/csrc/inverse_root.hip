@@ -44,10 +44,6 @@
 
 using namespace asteria;
 
-namespace asteria {
-inline size_t plane_small_bytes(int n);      // root_plane_path.h
-}
-
 namespace {
 
 // spectrum of M within 1 +- ROOT_STOP_DEV: one more X update finishes the factor
@@ -56,7 +52,7 @@ constexpr float ROOT_STOP_DEV = 1e-2f;
 // on the relative Frobenius error, which averages over directions)
 constexpr float ROOT_X_TOL = 7e-4f;
 
-constexpr int PM_TILE_WORDS = 2 * PACK_T + 4;   // floats per tile in pm_tile: two vectors, a double, a float, padding
+constexpr int PM_TILE_WORDS = 2 * PACK_T + 2;   // floats per tile in pm_tile: two vectors and a double
 
 // Scale of M, T, T^2, T^4 in the fp16-split products: their entries stay below a^4 < 23 (a <= 2.2),
 // so 2^10 keeps them under 2^15 with the fp16 range ending at 65504.
@@ -157,10 +153,9 @@ __global__ __launch_bounds__(256) void pm_packed_tile_kernel(const FactorDev *fd
     const int c0 = tj * PACK_T + 2 * lane, r0 = ti * PACK_T;
     __shared__ float colp[4][PACK_T];
     __shared__ double redd[4];
-    __shared__ float redt[4];
     // this lane's two columns of the tile: entries of v_tj, zero beyond n
     const float vj0 = c0 < n ? v[c0] : 0.0f, vj1 = c0 + 1 < n ? v[c0 + 1] : 0.0f;
-    float cs0 = 0.0f, cs1 = 0.0f, str = 0.0f;
+    float cs0 = 0.0f, cs1 = 0.0f;
     double saa = 0.0;
     for (int rr = 0; rr < PACK_T / 4; ++rr) {
         const int r = wave * (PACK_T / 4) + rr, gr = r0 + r;
@@ -172,15 +167,12 @@ __global__ __launch_bounds__(256) void pm_packed_tile_kernel(const FactorDev *fd
         if (lane == 0) out[r] = s;                              // row part: (T v_tj)[r]
         const float vi = gr < n ? v[gr] : 0.0f;
         cs0 += a.x * vi; cs1 += a.y * vi;                       // column part: (T^T v_ti)[c]
-        if (first) {
-            saa += (double)a.x * (double)a.x + (double)a.y * (double)a.y;
-            if (ti == tj) { if (gr == c0) str += a.x; if (gr == c0 + 1) str += a.y; }
-        }
+        if (first) saa += (double)a.x * (double)a.x + (double)a.y * (double)a.y;
     }
     colp[wave][2 * lane] = cs0; colp[wave][2 * lane + 1] = cs1;
     if (first) {
-        saa = wave_sum(saa); str = wave_sum(str);
-        if (lane == 0) { redd[wave] = saa; redt[wave] = str; }
+        saa = wave_sum(saa);
+        if (lane == 0) redd[wave] = saa;
     }
     __syncthreads();
     if (threadIdx.x < PACK_T)
@@ -189,7 +181,6 @@ __global__ __launch_bounds__(256) void pm_packed_tile_kernel(const FactorDev *fd
         // an off-diagonal tile stands for its mirror image too
         const double w = ti == tj ? 1.0 : 2.0;
         *reinterpret_cast<double *>(out + 2 * PACK_T) = w * (redd[0] + redd[1] + redd[2] + redd[3]);
-        out[2 * PACK_T + 2] = redt[0] + redt[1] + redt[2] + redt[3];
     }
 }
 
@@ -206,10 +197,11 @@ __global__ __launch_bounds__(PACK_T) void pm_packed_reduce_kernel(const FactorDe
     const float *__restrict__ v = F.pv[src];
     float s = 0.0f;
     double saa = 0.0, str = 0.0;
+    if (first && row < F.n) str = (double)F.A[packed_off(row, row)];
     for (int tj = 0; tj <= I; ++tj) {
         const float *p = F.pm_tile + (size_t)(I * (I + 1) / 2 + tj) * PM_TILE_WORDS;
         s += p[i];
-        if (first && i == 0) { saa += *reinterpret_cast<const double *>(p + 2 * PACK_T); str += (double)p[2 * PACK_T + 2]; }
+        if (first && i == 0) saa += *reinterpret_cast<const double *>(p + 2 * PACK_T);
     }
     for (int ti = I + 1; ti < T; ++ti) s += F.pm_tile[(size_t)(ti * (ti + 1) / 2 + I) * PM_TILE_WORDS + PACK_T + i];
     float syv = 0.0f;
@@ -218,13 +210,15 @@ __global__ __launch_bounds__(PACK_T) void pm_packed_reduce_kernel(const FactorDe
         syv = s * v[row];
     }
     __shared__ float red[PACK_T / 64];
+    __shared__ double redt[PACK_T / 64];
     syv = wave_sum(syv);
-    if ((i & 63) == 0) red[i >> 6] = syv;
+    if (first) str = wave_sum(str);
+    if ((i & 63) == 0) { red[i >> 6] = syv; redt[i >> 6] = str; }
     __syncthreads();
     if (i == 0) {
         F.pm_partial[I] = red[0] + red[1];
         // the off-diagonal tiles of the block rows below this one were counted there (weight 2)
-        if (first) F.pm_partial2[I] = make_double2(saa, str);
+        if (first) F.pm_partial2[I] = make_double2(saa, redt[0] + redt[1]);
     }
 }
 
@@ -704,17 +698,18 @@ size_t factor_i8_bytes(int n, int ns)
                 Carver::need(i8_rows(n), sizeof(double))) + Carver::need(1, sizeof(I8Factor));
 }
 
+// vectors, partial sums and tables of one factor that both paths need
 size_t factor_small_bytes(int n)
 {
     const int pmb = (n + LZ_ROWS - 1) / LZ_ROWS;
-    return 5 * Carver::need((size_t)ld4(n), sizeof(float)) + Carver::need(2 * (size_t)pmb, sizeof(float)) +
-           Carver::need((size_t)pmb, sizeof(double2)) +
-           Carver::need(2 * (size_t)tri_tiles(n), sizeof(float)) + Carver::need((size_t)tri_tiles(n) * PM_TILE_WORDS, sizeof(float)) +
-           sizeof(FactorDev) + sizeof(FactorScal) +
-           2 * sizeof(int) + 16 * sizeof(GemmProblem) + plane_small_bytes(n);
+    return 3 * Carver::need((size_t)ld4(n), sizeof(float)) + Carver::need(2 * (size_t)pmb, sizeof(float)) +
+           Carver::need((size_t)pmb, sizeof(double2)) + Carver::need((size_t)tri_tiles(n) * PM_TILE_WORDS, sizeof(float)) +
+           sizeof(FactorDev) + sizeof(FactorScal) + 2 * sizeof(int);
 }
+// ... and those of the fp32 / fp64 path alone
+size_t factor_table_bytes(int n) { return Carver::need(2 * (size_t)tri_tiles(n), sizeof(float)) + 16 * sizeof(GemmProblem); }
 
-size_t fixed_bytes() { return 64 * 256; }   // alignment slack of the shared arrays + coefficient table
+size_t fixed_bytes() { return 40 * 256; }   // alignment slack of the arrays that hold an entry per factor or tile (24 at most)
 
 asteria_status make_plan(const asteria_root_opts *opts_in, asteria_eps_mode mode, const float *eps,
                          int eps_count, int root, Plan &pl)
@@ -952,9 +947,6 @@ bool plane_needs_f64(const Plan &pl, double lo0, int n_max)
     return digit_dropped(n_max, 5, 6, 7, 1) / (10.0 * lo0) > DIGIT_DROPPED;
 }
 
-// tiles of 128 below which a pass takes 64 x 64 tiles for its pair products: fewer workgroups than the chip holds
-constexpr int PLANE_SMALL_TILES = 512;
-
 asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, const float *eps, int eps_count, const Plan &pl, bool f64,
                                int32_t *info, int32_t *iters, float *resid, float *lambda_max, void *ws, hipStream_t stream)
 {
@@ -979,7 +971,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         F.ntri = tri_tiles(n);
         F.tile_start = tri_total; tri_total += F.ntri;
         F.tile_start64 = tri64_total; tri64_total += tri_tiles64(n);
-        F.npart = std::max(2 * F.ntri, tri_tiles64(n));
+        F.npart = plane_partials(n);
         F.flags = d_flags + i;
         F.a_packed = a.a_layout == ASTERIA_LAYOUT_PACKED ? 1 : 0;
         F.pm_blocks = F.a_packed ? (n + PACK_T - 1) / PACK_T : (n + LZ_ROWS - 1) / LZ_ROWS;
@@ -990,24 +982,22 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         const double er = (double)F.eps_in;
         a_min = std::min(a_min, er / (1.0 + (double)pl.margin + er));
         for (int v = 0; v < 3; ++v) F.pv[v] = cv.take<float>(ld4(n));
-        for (int v = 0; v < 2; ++v) F.py[v] = cv.take<float>(ld4(n));
         F.pm_partial = cv.take<float>(2 * (size_t)((n + LZ_ROWS - 1) / LZ_ROWS));
         F.pm_partial2 = cv.take<double2>((n + LZ_ROWS - 1) / LZ_ROWS);
         F.pm_tile = cv.take<float>((size_t)F.ntri * PM_TILE_WORDS);
         F.partial = cv.take<float>(F.npart);
-        const size_t pair = (size_t)n * F.rowb, slot = plane_slot_bytes(n, prefix, f64);
+        const size_t pair = plane_pair_bytes(n), slot = prefix ? plane_slot_bytes(n, f64) : pair;
         for (int v = 0; v < 2; ++v) F.X[v] = cv.take<char>(pair);
-        // a full copy of packed statistics lies where X_0 would (never written)
+        // X_0 is never written: a full copy of packed statistics and two vectors of the estimate lie there
         if (F.a_packed) { F.Aw = reinterpret_cast<const float *>(F.X[0]); F.ldw = F.rowb / 4; }
-        F.P[1] = cv.take<char>(pair);
-        F.P[2] = cv.take<char>(pair);
-        char *region = cv.take<char>((prefix ? 4 : 2) * slot);
-        if (prefix) {
-            for (int v = 0; v < 4; ++v) { F.D[v] = region + v * slot; F.F[v] = reinterpret_cast<double *>(region + v * slot); }
-            F.P[0] = region + 2 * slot; F.P[3] = region + 3 * slot;
-        } else {
-            F.P[0] = region; F.P[3] = region + slot;
-        }
+        for (int v = 0; v < 2; ++v) F.py[v] = reinterpret_cast<float *>(F.X[0]) + v * ld4(n);
+        char *chain[4] = {nullptr, nullptr, cv.take<char>(std::max(slot, 2 * pair)), cv.take<char>(slot)};
+        if (prefix)
+            for (int v = 0; v < 4; ++v) {
+                if (v < 2) chain[v] = cv.take<char>(slot);
+                F.D[v] = chain[v]; F.F[v] = reinterpret_cast<double *>(chain[v]);
+            }
+        F.P[0] = chain[2]; F.P[1] = chain[2] + pair; F.P[2] = F.P[3] = chain[3];
     }
     const bool small = tri_total < PLANE_SMALL_TILES;
     uint2 *d_map = cv.take<uint2>(tri_total), *d_map64 = small ? cv.take<uint2>(tri64_total) : nullptr;
@@ -1149,7 +1139,6 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
             a_min = std::min(a_min, er / (1.0 + (double)pl.margin + er));
         }
         for (int v = 0; v < 3; ++v) F.pv[v] = cv.take<float>(ld4(n));
-        for (int v = 0; v < 2; ++v) F.py[v] = cv.take<float>(ld4(n));
         F.pm_partial = cv.take<float>(2 * (size_t)((n + LZ_ROWS - 1) / LZ_ROWS));
         F.pm_partial2 = cv.take<double2>((n + LZ_ROWS - 1) / LZ_ROWS);
         F.pm_tile = cv.take<float>((size_t)F.ntri * PM_TILE_WORDS);
@@ -1181,6 +1170,7 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
         F.X32b = cv.take<float>(e32);
         if (F.a_packed) { F.Aw = F.X32b; F.ldw = F.ld32; }      // room for a full copy while X is not there yet
         F.T32 = cv.take<float>(e32);
+        for (int v = 0; v < 2; ++v) F.py[v] = F.T32 + v * ld4(F.n);   // T_0 is not there yet either
         unsigned char *shared = cv.take<unsigned char>(shared_region_bytes(F.n, pl.use64, pl.use32));
         if (pl.use32) {
             const size_t step = Carver::need(e32, sizeof(float));
@@ -1319,7 +1309,7 @@ struct PassBytes {
     size_t of(int n) const
     {
         return factor_small_bytes(n) + (planes ? plane_factor_bytes(n, pl.fp64_iters > 0, f64)
-                                               : factor_matrix_bytes(n, pl.use64, pl.use32) + factor_i8_bytes(n, pl.i8_slices));
+                                               : factor_table_bytes(n) + factor_matrix_bytes(n, pl.use64, pl.use32) + factor_i8_bytes(n, pl.i8_slices));
     }
 };
 
@@ -1358,7 +1348,7 @@ extern "C" size_t asteria_inverse_root_workspace_bytes(const asteria_factor *f, 
     for (int i = 0; i < nfactors; ++i) {
         if (f[i].n <= 0) return 0;
         // the call takes one of two paths (eps and root decide; pinned precision options never the second): room for either
-        size_t b = factor_matrix_bytes(f[i].n, use64, use32) +
+        size_t b = factor_table_bytes(f[i].n) + factor_matrix_bytes(f[i].n, use64, use32) +
                    factor_i8_bytes(f[i].n, use64 ? (o.int8_slices < 0 ? 5 : o.int8_slices) : 0);
         if (o.fp64_iters < 0 && o.lowp_from < 0) b = std::max(b, plane_factor_bytes(f[i].n, true, true));
         b += factor_small_bytes(f[i].n);

@@ -46,7 +46,7 @@ struct FactorDev {
     int pm_blocks;
     float eps_in;
     int a_packed;       // A lies in packed lower tiles (gemm.h, packed_off): lda unused
-    float *pm_tile;     // packed A: per lower tile 2 x 128 partial products of the mat-vec and (sum a^2 as a double, trace part)
+    float *pm_tile;     // packed A: per lower tile 2 x 128 partial products of the mat-vec and the sum of a^2 as a double
 };
 
 // coefficients of one product of the plane path: C = own1 O1 + own2 O2 + gam A B, in values

@@ -465,26 +465,35 @@ __global__ __launch_bounds__(256) void plane_finalize_kernel(const FactorDev *fd
 // ---- host --------------------------------------------------------------------------------------------
 inline int tri_tiles64(int n) { const int t = (n + 63) / 64; return t * (t + 1) / 2; }
 
-// bytes of one chain slot: digits (5 at most), fp64 where that tier can occur, pairs without a prefix
-inline size_t plane_slot_bytes(int n, bool prefix, bool f64)
+// tiles of 128 below which a pass takes 64 x 64 tiles for its pair products: fewer workgroups than the chip holds
+constexpr int PLANE_SMALL_TILES = 512;
+
+inline size_t plane_pair_bytes(int n) { return Carver::need((size_t)n * pair_row_bytes(n), 1); }
+// bytes of one chain slot: digits (5 at most), fp64 where that tier can occur
+inline size_t plane_slot_bytes(int n, bool f64)
 {
-    const size_t pair = Carver::need((size_t)n * pair_row_bytes(n), 1);
-    size_t b = pair;
-    if (prefix) b = std::max(b, Carver::need((size_t)n * digit_row_bytes(n, 5), 1));
-    if (prefix && f64) b = std::max(b, Carver::need((size_t)n * ((n + 1) & ~1), sizeof(double)));
+    size_t b = std::max(plane_pair_bytes(n), Carver::need((size_t)n * digit_row_bytes(n, 5), 1));
+    if (f64) b = std::max(b, Carver::need((size_t)n * ((n + 1) & ~1), sizeof(double)));
     return b;
 }
-// X_k, X_{k+1}, the pair planes of slots 1 and 2, and the four chain slots (without a prefix: slots 0 and 3); the
-// pair planes of slots 0 and 3 lie over chain slots 2 and 3: when they are written, E (the former) and E4 of
-// the prefix are dead
+inline int plane_partials(int n)
+{
+    const int t = tri_tiles(n);
+    return t < PLANE_SMALL_TILES ? std::max(2 * t, tri_tiles64(n)) : 2 * t;
+}
+// X_k, X_{k+1} and the chain slots.  The pair planes of M lie in slot 2, those of E and E4 in slot 3, over the digit
+// or fp64 matrices of the prefix:
+//   slot 2 (E, written by the first product of a T of degree 2): the pair planes of M are written by the last
+//     product of an iteration, when E is dead, and read by one whose T is linear (no E) or that needs no prefix
+//     matrices any more
+//   slot 3 (E4, written after the X update): the pair planes of E are read by the X update last, in every tier
 inline size_t plane_factor_bytes(int n, bool prefix, bool f64)
 {
-    return 4 * Carver::need((size_t)n * pair_row_bytes(n), 1) + (prefix ? 4 : 2) * plane_slot_bytes(n, prefix, f64);
-}
-inline size_t plane_small_bytes(int n)
-{
-    return Carver::need(std::max(2 * (size_t)tri_tiles(n), (size_t)tri_tiles64(n)), sizeof(float)) + 256 +
-           ((size_t)tri_tiles(n) + (size_t)tri_tiles64(n)) * sizeof(uint2);
+    const size_t pair = plane_pair_bytes(n), slot = prefix ? plane_slot_bytes(n, f64) : pair;
+    size_t b = 2 * pair + std::max(slot, 2 * pair) + slot + (prefix ? 2 * slot : 0);
+    b += Carver::need(plane_partials(n), sizeof(float)) + 8 * sizeof(GemmProblem);
+    const size_t t = tri_tiles(n);
+    return b + (t + (t < (size_t)PLANE_SMALL_TILES ? (size_t)tri_tiles64(n) : 0)) * sizeof(uint2);
 }
 
 }  // namespace asteria

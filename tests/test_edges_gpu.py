@@ -192,3 +192,25 @@ def test_roots_with_a_bound_on_the_steps_of_the_largest_eigenvalue(n, steps, opt
     Y = Y @ Y
     E = Y @ Y @ (A.double() + 1e-6 * float(lam[0]) * torch.eye(n, device=DEV, dtype=torch.float64)) - torch.eye(n, device=DEV, dtype=torch.float64)
     assert float(torch.linalg.norm(E)) / n ** 0.5 <= 4 * 2e-3       # four factors of the accuracy of the root
+
+
+@pytest.mark.parametrize("eps", [1e-3, 1e-6, 1e-8])
+@pytest.mark.parametrize("opts", [None, dict(int8_slices=0), dict(int8_slices=4), dict(fp64_iters=0), dict(lowp_from=40)])
+@pytest.mark.parametrize("n", [1, 2, 33, 129, 513, 1025])
+def test_roots_stay_inside_the_smallest_workspace_and_do_not_depend_on_its_size(n, opts, eps):
+    o = None if opts is None else ast.RootOpts(**opts)
+    A = _with_spectrum(n, _spectrum("power", n), 7, n)
+    got = []
+    for copies in (1, 3):                                       # three factors in one pass, and one after the other
+        Xs = [torch.full_like(A, float("nan")) for _ in range(3)]
+        items = [(A, X) for X in Xs]
+        full, least = ast.inverse_root_workspace_bytes(items, o)
+        size = least if copies == 1 else full
+        assert full > least
+        buf = torch.full((size + (1 << 20),), 255, dtype=torch.uint8, device=DEV)
+        info = torch.full((3,), -1, dtype=torch.int32, device=DEV)
+        ast.inverse_root(items, eps, opts=o, info=info, ws=buf[:size])
+        torch.cuda.synchronize()
+        assert bool((info == 0).all()) and bool((buf[size:] == 255).all())
+        got += Xs
+    assert all(torch.equal(got[0], X) for X in got[1:])
