@@ -37,12 +37,17 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void *p, uint32_t bytes)
 }
 
 // 16 bytes per lane from rsrc + voff + soff to LDS at lds_off + 16 * lane (lds_off, soff wave-uniform).
-// The compiler does not see the load: wait_lds_loads counts it.
+// The compiler does not see the load: wait_lds_loads counts it.  m0 is a reserved register, never allocated to a
+// value, but the compiler writes it ahead of its own instructions that read it: the clobber keeps such a write from
+// being shared across this statement (and earns a warning about reserved registers).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(i32x4 rsrc, uint32_t lds_off, uint32_t voff, uint32_t soff)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+                 :: "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // All but the newest N vector-memory operations have arrived, and this wavefront's LDS reads are done
 // (a slab may be overwritten once every wavefront has passed the barrier that follows).
