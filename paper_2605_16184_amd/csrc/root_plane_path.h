@@ -227,12 +227,16 @@ __global__ __launch_bounds__(64) void plane_control_kernel(const FactorDev *fd, 
     const int f = blockIdx.x;
     const int st = state[f];
     if (st == ST_DONE || st == ST_FAIL) return;
-    if (st == ST_LAST) {
-        if (threadIdx.x == 0) state[f] = ST_DONE;
-        return;
-    }
     const FactorDev &F = fd[f];
     FactorScal &S = fs[f];
+    if (st == ST_LAST) {
+        if (threadIdx.x == 0) {
+            const bool over = F.flags[0] != 0;        // the last update's own products may still have run on digits
+            if (over) S.info = ASTERIA_INFO_NOT_PD;
+            state[f] = over ? ST_FAIL : ST_DONE;
+        }
+        return;
+    }
     float r2 = 0.0f;
     for (int i = threadIdx.x; i < F.npart; i += 64) {
         r2 += F.partial[i];
