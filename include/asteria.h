@@ -237,7 +237,7 @@ asteria_status asteria_sym_unpack(const asteria_sympair *items, int nitems, void
  *   next tier enough)   of what the integers lose
  *   then                two fp16 terms per entry (22 bits),   fp16 matrix cores, three passes, fp32 sums
  *                       scaled by powers of two from bounds
- *   X, throughout       two fp16 terms; the last X in fp32    the same
+ *   X, throughout       fp32                                  the same, split into two fp16 terms
  *
  *   otherwise
  *   first fp64_iters    fp64      int8 matrix cores (diagonal + 7-bit slices, exact integer sums, fp64

@@ -943,8 +943,8 @@ bool plane_needs_f64(const Plan &pl, double lo0, int n_max)
 {
     if (pl.fp64_iters <= 0) return false;
     if (pl.i8_slices < 5 || digit_rounding(n_max, 5, 1.0, lo0) > DIGIT_ROUNDING) return true;
-    // E4 <= a^4 <= 2^7 on M <= 2^1 with 6 levels of 5 digits, against a bottom lifted at least tenfold
-    return digit_dropped(n_max, 5, 6, 7, 1) / (10.0 * lo0) > DIGIT_DROPPED;
+    // E2 <= a^2 <= 2^4 on M and W <= 2^1 with 6 levels of 5 digits, against a bottom lifted at least tenfold
+    return (1.0 + 16.0) * digit_dropped(n_max, 5, 6, 4, 1) / (10.0 * lo0) > DIGIT_DROPPED;
 }
 
 asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, const float *eps, int eps_count, const Plan &pl, bool f64,
@@ -1003,15 +1003,29 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     uint2 *d_map = cv.take<uint2>(tri_total), *d_map64 = small ? cv.take<uint2>(tri64_total) : nullptr;
     PlaneF64Tables ft = {};
     if (f64)
-        for (int pa = 0; pa < 2; ++pa)
-            for (int o = 0; o < 4; ++o) ft.t[pa][o] = cv.take<GemmProblem>(cnt);
+        for (int o = 0; o < 4; ++o) ft.t[o] = cv.take<GemmProblem>(cnt);
 
     // degrees of T by iteration and the iteration budget: the sequence for the smallest eps, then a few more for a
     // factor whose spectrum left the interval the sequence is made for
     const double lo0 = 0.5 * a_min;
     std::vector<int> deg;
-    if (pl.fp64_iters <= 2)
+    if (pl.fp64_iters <= 2) {
         for (const char *q = root_degrees(lo0 / ROOT_TOP); *q; ++q) deg.push_back(*q - '0');
+    } else {
+        // a longer prefix is linear, and so is the rest but for the last two: degrees 2 and 3 take one product less
+        // than three linear ones and leave a tenth of their truncation (eps = 1e-8: 3.4e-4 of X after 10 linear, 2e-5)
+        RootInterval I = {lo0, ROOT_TOP};
+        for (int k = 0; k + 2 < pl.max_iters && deg.empty(); ++k) {
+            if (k >= pl.fp64_iters) {
+                const RootInterval two = root_poly(I.lo, I.hi, 2).image, three = root_poly(two.lo, two.hi, 3).image;
+                if (std::max(1.0 - three.lo, three.hi - 1.0) <= 4.0 * (double)ROOT_X_TOL) {
+                    deg.assign(k, 1);
+                    deg.push_back(2); deg.push_back(3);
+                }
+            }
+            I = root_poly(I.lo, I.hi, 1).image;
+        }
+    }
     int K;
     if (!deg.empty()) {
         for (int e = 0; e < 3; ++e) deg.push_back(2);
@@ -1065,7 +1079,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
             if (pl.i8_slices > 0) e = launch_digit_product<4>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
             if (e == hipSuccess && pl.i8_slices > 4) e = launch_digit_product<5>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
             if (e == hipSuccess && f64)
-                e = launch_gemm_grouped<double, double, double, false, false>(ft.t[k & 1][tab], cnt, tri_total, d_state, stream);
+                e = launch_gemm_grouped<double, double, double, false, false>(ft.t[tab], cnt, tri_total, d_state, stream);
             return e;
         };
         auto from_f64 = [&](int what) {
@@ -1079,8 +1093,8 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         if (pre) ASTERIA_HIP_TRY(chain(OP_E2, 1));
         if (k > 0) ASTERIA_HIP_TRY(pair(OP_E2, OP_X));
         else ASTERIA_HIP_TRY(pair(OP_E2, -1));
-        if (pre) ASTERIA_HIP_TRY(chain(OP_E4, 2));
-        ASTERIA_HIP_TRY(pair(OP_E4, -1));
+        if (pre) ASTERIA_HIP_TRY(chain(OP_W, 2));
+        ASTERIA_HIP_TRY(pair(OP_W, -1));
         if (pre) { ASTERIA_HIP_TRY(chain(OP_M, 3)); from_f64(1); }
         ASTERIA_HIP_TRY(pair(OP_M, -1));
         ASTERIA_HIP_TRY(hipGetLastError());

@@ -60,7 +60,7 @@ struct FactorScal {
     float rho;       // largest Ritz value so far: the lambda_max estimate
     int lz_small;    // consecutive steps that moved the estimate by less than the tolerance
     int iters;       // X updates performed / scheduled
-    int xloc;        // 0: current fp32 X in Xout, 1: in X32b (plane path: 1 + parity: in X[parity])
+    int xloc;        // 0: current fp32 X in Xout, 1: in X32b (plane path: only its lower triangle in Xout)
     int info;
     int pm_done;
     float lo, hi;    // interval assumed to contain the spectrum of the current M

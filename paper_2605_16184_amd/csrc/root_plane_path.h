@@ -3,18 +3,17 @@
 //
 //   T = c0 I - E,  E = -(c1 M + c2 M^2 + c3 M^3)   degree 1, 2 or 3 by iteration (root_degrees)
 //   E2 = 2 c0 E - E E      (T^2 = c0^2 I - E2)
-//   E4 = 2 c0^2 E2 - E2 E2 (T^4 = c0^4 I - E4)
-//   M' = c0^4 M - E4 M,    X' = c0 X - X E
+//   W = c0^2 M - E2 M,  M' = c0^2 W - E2 W,  X' = c0 X - X E
 //
-// Neither T nor its powers are stored, only their complements: those have the small diagonals of M (entries of
+// Neither T nor T^2 is stored, only their complements: those have the small diagonals of M (entries of
 // a statistic with a decaying spectrum are of the size of its mean eigenvalue), which is what a fixed number of
 // bits is measured against, and every product reads its linear term from an operand it has streamed anyway.
 //
 // While the bottom of M's spectrum is below ROOT_LOWP_FLOOR the chain runs on digit planes (int8 matrix cores,
 // 32 or 40 bits against a uniform quantum), or, where the device finds 40 bits too few or the caller asked for
 // it, on fp64 matrices;
-// afterwards on pair planes.  X is kept in pair planes throughout, the last update writes
-// the caller's fp32 matrix.
+// afterwards on pair planes.  X is kept in fp32, its lower triangle in the caller's matrix, and in pair planes as an
+// operand of the next update.
 #pragma once
 
 namespace asteria {
@@ -22,8 +21,8 @@ namespace asteria {
 // Errors allowed in the bottom `lo` of M's spectrum, relative to it (a quarter reaches the root there):
 //   rounding of M to 2^-8NS of a bound d on its diagonal, an error matrix of norm below n^(1/2) 2^-8NS d;
 //   the digit products beyond the kept levels, per entry (2 n^(1/2) of it in norm) about (pairs of the first
-//   dropped level x n)^(1/2) 128^2 / 3 quanta of that level, for the product E4 M, which dominates, against
-//   the bottom of M'.
+//   dropped level x n)^(1/2) 128^2 / 3 quanta of that level, for the products E2 W and (lifted by c0^2) E2 M,
+//   against the bottom of M'.
 // Measured against the same iteration on fp64 matrices (power law, rank 32 + noise, log-spaced over 12 and 16
 // decades, two levels; n = 96 .. 1024): at these limits the root differs by less than 1.5e-4.
 constexpr double DIGIT_ROUNDING = 9e-4;
@@ -80,8 +79,7 @@ __device__ inline void plane_advance(const FactorDev &F, FactorScal &S, int *sta
     }
     if (ends) st = ST_LAST;
     S.iters += 1;
-    S.xloc = (st == ST_LAST && c.k > 0) ? 0 : 1 + ((c.k + 1) & 1);
-    const int p = c.k & 1;
+    S.xloc = (st == ST_LAST && c.k > 0) ? 0 : 1;
     // T = a I - E; what M carries into the products where T is linear
     const double a = T.c[0], b = -T.c[1];
     const bool lin = c.degree == 1;
@@ -89,23 +87,25 @@ __device__ inline void plane_advance(const FactorDev &F, FactorScal &S, int *sta
     S.prod[OP_SQ3] = {0.0, 0.0, 1.0};
     S.prod[OP_CUBE] = {b, -T.c[2], -T.c[3]};
     S.prod[OP_E2] = lin ? RootProd{2.0 * a * b, 0.0, -b * b} : RootProd{2.0 * a, 0.0, -1.0};
-    S.prod[OP_E4] = {2.0 * a * a, 0.0, -1.0};
-    S.prod[OP_M] = {a * a * a * a, 0.0, -1.0};
+    S.prod[OP_W] = {a * a, 0.0, -1.0};
+    S.prod[OP_M] = {a * a, 0.0, -1.0};
     S.prod[OP_X] = lin ? RootProd{a, 0.0, -b} : RootProd{a, 0.0, -1.0};
     if (c.k == 0) {
         const double xs = sqrt(sqrt((double)S.scale)) * (double)S.x_scale;
         S.x1a = (float)(xs * a); S.x1s = (float)xs; S.x1b = (float)b;
     }
-    // bounds on the diagonals (E <= b M, E2 <= 2 a E, E4 <= 2 a^2 E2, M' <= a^4 M in the order of symmetric
+    // bounds on the diagonals (E <= b M, E2 <= 2 a E, W <= a^2 M, M' <= a^4 M in the order of symmetric
     // matrices, and every norm by the scalar map) and from them the quanta of the digits
-    const double dm = S.dmax, de = lin ? dm : fmin(b * dm, a), de2 = fmin(2.0 * a * (lin ? b * dm : de), a * a), de4 = fmin(2.0 * a * a * de2, a * a * a * a);
-    const double dm1 = fmin(a * a * a * a * dm, T.image.hi * 1.001);
-    const int ge = (int)ceil(log2(de * 1.02)), ge2 = (int)ceil(log2(de2 * 1.02)), ge4 = (int)ceil(log2(de4 * 1.02));
+    const double dm = S.dmax, de = lin ? dm : fmin(b * dm, a), de2 = fmin(2.0 * a * (lin ? b * dm : de), a * a);
+    const double dw = fmin(a * a * dm, sqrt(T.image.hi * hi) * 1.001), dm1 = fmin(a * a * a * a * dm, T.image.hi * 1.001);
+    const int ge = (int)ceil(log2(de * 1.02)), ge2 = (int)ceil(log2(de2 * 1.02)), gw = (int)ceil(log2(dw * 1.02));
     const int gm1 = (int)ceil(log2(dm1 * 1.02));
     int gm = (int)ceil(log2(dm * 1.02));
     if (c.k > 0 && S.next_tier == TIER_DIGIT) gm = S.dexp[4] + 8 * S.ns - 1;      // the range the last M-update was stored with
-    // error of the dropped levels of E4 M relative to the bottom of M'
-    auto dropped = [&](int ns, int levels) { return digit_dropped(F.n, ns, levels, ge4, gm) / T.image.lo; };
+    // error of the dropped levels of E2 W and E2 M relative to the bottom of M'
+    auto dropped = [&](int ns, int levels) {
+        return (digit_dropped(F.n, ns, levels, ge2, gw) + a * a * digit_dropped(F.n, ns, levels, ge2, gm)) / T.image.lo;
+    };
     if (c.k == 0) {
         S.tier = TIER_PAIR;
         S.ns = 4;
@@ -123,7 +123,7 @@ __device__ inline void plane_advance(const FactorDev &F, FactorScal &S, int *sta
     if (S.tier == TIER_DIGIT) {
         const int bits = 8 * S.ns - 1;
         S.levels = dropped(S.ns, S.ns) <= (S.ns == 4 ? DIGIT_DROPPED : 0.2 * DIGIT_DROPPED) ? S.ns : S.ns + 1;
-        S.dexp[p] = gm - bits; S.dexp[2] = ge - bits; S.dexp[p ^ 1] = ge2 - bits; S.dexp[3] = ge4 - bits; S.dexp[4] = gm1 - bits;
+        S.dexp[0] = gm - bits; S.dexp[1] = ge2 - bits; S.dexp[2] = ge - bits; S.dexp[3] = gw - bits; S.dexp[4] = gm1 - bits;
     }
     if (c.counters) {
         // flops of this iteration's chain by where they run, of all pair products, and int8 operations issued
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(256) void plane_init_kernel(const FactorDev *fd, co
     const double s = (double)S.scale, eps = (double)S.eps;
     const int tier = S.tier, ns = S.ns;
     const double inv_q = tier == TIER_DIGIT ? ldexp(1.0, -S.dexp[0]) : 0.0;
-    const float x1a = S.x1a, x1e = S.x1s * S.x1b;
+    const float x1a = S.x1a, x1e = S.x1s * S.x1b, inv_x = 1.0f / S.x_scale;
     const bool packed = F.a_packed != 0;
     const float *Ap = packed ? F.A + (size_t)(ti * (ti + 1) / 2 + tj) * PACK_T * PACK_T : nullptr;
     const bool vec = packed || ((lda & 3) == 0 && (reinterpret_cast<uintptr_t>(F.A) & 15u) == 0);
@@ -321,8 +321,11 @@ __global__ __launch_bounds__(256) void plane_init_kernel(const FactorDev *fd, co
         }
         if (linear) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                w[e] = c0 + e < n ? pair_word((float)((r == c0 + e ? (double)x1a : 0.0) - (double)x1e * m[e])) : 0u;
+            for (int e = 0; e < 16; ++e) {
+                const float x = (float)((r == c0 + e ? (double)x1a : 0.0) - (double)x1e * m[e]);
+                w[e] = c0 + e < n ? pair_word(x) : 0u;
+                if (c0 + e <= r) F.Xout[(size_t)r * F.ldx + c0 + e] = x * inv_x;
+            }
             put_pair(F.X[1]);
         }
     };
@@ -384,7 +387,7 @@ __global__ __launch_bounds__(256) void plane_from_f64_kernel(const FactorDev *fd
     const int n = F.n, per = plane_groups(n) * 2;
     const int id = blockIdx.x * 256 + threadIdx.x, r = id / per, c0 = (id % per) * 16;
     if (r >= n) return;
-    const int slot = what == 0 ? 2 : ((k & 1) ^ 1);
+    const int slot = what == 0 ? 2 : 0;
     const double *src = F.F[slot] + (size_t)r * F.ld64 + c0;
     const bool x1 = what == 0 && k == 0;
     uint32_t w[16];
@@ -394,6 +397,7 @@ __global__ __launch_bounds__(256) void plane_from_f64_kernel(const FactorDev *fd
         if (x1) v = (r == c0 + e ? (double)S.x1a : 0.0) - (double)S.x1s * v;
         else v *= what == 0 ? (double)PAIR_SCALE_E : (double)PAIR_SCALE_M;
         w[e] = c0 + e < n ? pair_word((float)v) : 0u;
+        if (x1 && c0 + e <= r) F.Xout[(size_t)r * F.ldx + c0 + e] = (float)(v / (double)S.x_scale);
     }
     char *d = (x1 ? F.X[1] : F.P[slot]) + (size_t)r * F.rowb + (c0 >> 5) * 128 + ((c0 >> 4) & 1) * 32;
 #pragma unroll
@@ -409,14 +413,14 @@ __global__ __launch_bounds__(256) void plane_from_f64_kernel(const FactorDev *fd
     }
 }
 
-// Problem tables of the fp64 chain: [parity][E | E2 | E4 | M'], one thread per factor.
-struct PlaneF64Tables { GemmProblem *t[2][4]; };
+// Problem tables of the fp64 chain: E | E2 | W | M', one thread per factor.
+struct PlaneF64Tables { GemmProblem *t[4]; };
 __global__ void plane_f64_tables_kernel(const FactorDev *fd, FactorScal *fs, int cnt, int linear, PlaneF64Tables T)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= cnt) return;
     const FactorDev F = fd[i];
-    const int ops[4] = {OP_SQ, OP_E2, OP_E4, OP_M};
+    const int ops[4] = {OP_SQ, OP_E2, OP_W, OP_M};
     GemmProblem p = {};
     p.M = p.N = p.K = F.n;
     p.state_idx = i; p.state_mask = 1 << ST_RUN;
@@ -425,21 +429,19 @@ __global__ void plane_f64_tables_kernel(const FactorDev *fd, FactorScal *fs, int
     p.tile_start = F.tile_start;
     p.gate = &fs[i].tier;                            // TIER_F64 = 0
     p.partial = F.partial;
-    for (int pa = 0; pa < 2; ++pa)
-        for (int o = 0; o < 4; ++o) {
-            const RootOperands r = root_operands(ops[o], pa, linear != 0);
-            GemmProblem q = p;
-            q.A = F.F[r.A]; q.B = F.F[r.B]; q.C = F.F[r.C]; q.own = F.F[r.O1];
-            q.coefd = &fs[i].prod[ops[o]].own1;
-            q.flags = GEMM_SYM | (ops[o] == OP_M ? GEMM_EPI_RESID : 0);
-            if (ops[o] == OP_SQ) q.state_mask |= 1 << ST_LAST;
-            T.t[pa][o][i] = q;
-        }
+    for (int o = 0; o < 4; ++o) {
+        const RootOperands r = root_operands(ops[o], linear != 0);
+        GemmProblem q = p;
+        q.A = F.F[r.A]; q.B = F.F[r.B]; q.C = F.F[r.C]; q.own = F.F[r.O1];
+        q.coefd = &fs[i].prod[ops[o]].own1;
+        q.flags = GEMM_SYM | (ops[o] == OP_M ? GEMM_EPI_RESID : 0);
+        if (ops[o] == OP_SQ) q.state_mask |= 1 << ST_LAST;
+        T.t[o][i] = q;
+    }
 }
 
-// Outcome of every factor; X from its pair planes where the last update did not write the caller's matrix (a
-// factor that ended with its first update, or ran out of iterations).  Grid: x = groups of 256 pieces of 16
-// columns, y = factor.
+// Outcome of every factor; the upper triangle of X where the last update did not complete the caller's matrix (a
+// factor that ended with its first update, or ran out of iterations).  Grid: x = groups of rows, y = factor.
 __global__ __launch_bounds__(256) void plane_finalize_kernel(const FactorDev *fd, const FactorScal *fs, const int *state, int first,
                                                              int32_t *info, int32_t *iters, float *resid, float *lambda_max)
 {
@@ -453,17 +455,9 @@ __global__ __launch_bounds__(256) void plane_finalize_kernel(const FactorDev *fd
     }
     if (state[f] == ST_FAIL || S.xloc == 0) return;
     const FactorDev &F = fd[f];
-    const int n = F.n, per = plane_groups(n) * 2;
-    const float inv = 1.0f / S.x_scale;
-    const char *X = F.X[S.xloc - 1];
-    for (int id = blockIdx.x * 256 + threadIdx.x; id < n * per; id += gridDim.x * 256) {
-        const int r = id / per, c0 = (id % per) * 16;
-        const char *s = X + (size_t)r * F.rowb + (c0 >> 5) * 128 + ((c0 >> 4) & 1) * 32;
-        for (int e = 0; e < 16 && c0 + e < n; ++e) {
-            const float hi = (float)reinterpret_cast<const _Float16 *>(s)[e], lo = (float)reinterpret_cast<const _Float16 *>(s + 64)[e];
-            F.Xout[(size_t)r * F.ldx + c0 + e] = (hi + lo) * inv;
-        }
-    }
+    const int n = F.n;
+    for (int r = blockIdx.x; r < n; r += gridDim.x)
+        for (int c = threadIdx.x; c < r; c += 256) F.Xout[(size_t)c * F.ldx + r] = F.Xout[(size_t)r * F.ldx + c];
 }
 
 // ---- host --------------------------------------------------------------------------------------------
@@ -485,17 +479,17 @@ inline int plane_partials(int n)
     const int t = tri_tiles(n);
     return t < PLANE_SMALL_TILES ? std::max(2 * t, tri_tiles64(n)) : 2 * t;
 }
-// X_k, X_{k+1} and the chain slots.  The pair planes of M lie in slot 2, those of E and E4 in slot 3, over the digit
-// or fp64 matrices of the prefix:
+// X_k, X_{k+1} and the chain slots.  The pair planes of M and E2 lie in slot 2, those of E and W in slot 3, over the
+// digit or fp64 matrices of the prefix:
 //   slot 2 (E, written by the first product of a T of degree 2): the pair planes of M are written by the last
 //     product of an iteration, when E is dead, and read by one whose T is linear (no E) or that needs no prefix
 //     matrices any more
-//   slot 3 (E4, written after the X update): the pair planes of E are read by the X update last, in every tier
+//   slot 3 (W, written after the X update): the pair planes of E are read by the X update last, in every tier
 inline size_t plane_factor_bytes(int n, bool prefix, bool f64)
 {
     const size_t pair = plane_pair_bytes(n), slot = prefix ? plane_slot_bytes(n, f64) : pair;
     size_t b = 2 * pair + std::max(slot, 2 * pair) + slot + (prefix ? 2 * slot : 0);
-    b += Carver::need(plane_partials(n), sizeof(float)) + 8 * sizeof(GemmProblem);
+    b += Carver::need(plane_partials(n), sizeof(float)) + 4 * sizeof(GemmProblem);
     const size_t t = tri_tiles(n);
     return b + (t + (t < (size_t)PLANE_SMALL_TILES ? (size_t)tri_tiles64(n) : 0)) * sizeof(uint2);
 }

@@ -11,46 +11,52 @@ namespace asteria {
 
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 
-// Which product a launch computes.  p = k & 1 is the parity of the iteration: M_k lies in slot p, the work
-// matrix of the iteration (M^2, then T^2's complement, then M_{k+1}) in slot p ^ 1, E in slot 2, E4 in slot 3.
+// Which product a launch computes.  M lies in slot 0, M^2 and then T^2's complement in slot 1, E in slot 2, T^2 M in
+// slot 3; the next M takes the slot of M.
+//
+// T^4 M is formed as T^2 (T^2 M): the same number of products as with T^4, and what the storage of its operands loses
+// is of the size of T^2 <= a^2 times the large eigenvalues of T^2 M (about 1) instead of T^4 <= a^4 = 113 times those of
+// M, against the small eigenvalues that the map lifts.  Error of the root against 64 bits that does not commute with A
+// (per eigen-direction, n = 1024, eps = 1e-8), with T^4 and so: rows scaled over 4 decades 1.2e-4 and 1.0e-5, power law
+// 1.2e-5 and 4.3e-6.
 enum RootOp : int {
     OP_SQ = 0,   // E  = b M - c M M                      (T of degree 2)
     OP_SQ3,      // M2 = M M                              (T of degree 3, first product)
     OP_CUBE,     // E  = b M - c M2 + d M2 M              (... second product)
     OP_E2,       // E2 = 2 a E - E E,    T^2 = a^2 I - E2
-    OP_E4,       // E4 = 2 a^2 E2 - E2 E2,  T^4 = a^4 I - E4
-    OP_M,        // M' = a^4 M - E4 M
+    OP_W,        // W  = a^2 M - E2 M = T^2 M
+    OP_M,        // M' = a^2 W - E2 W
     OP_X,        // X' = a X - X E
     OP_COUNT
 };
 
-// fp16 scales of the pair planes.  The spectra are bounded by M: 2.02, M^2: 4.1, E: a, E2: a^2, E4: a^4 with
-// a <= 3.6 for every coefficient set in use, and |entry| <= largest diagonal entry <= ||.||_2.
-constexpr float PAIR_SCALE_M = 8192.0f, PAIR_SCALE_M2 = 8192.0f, PAIR_SCALE_E = 8192.0f, PAIR_SCALE_E2 = 2048.0f, PAIR_SCALE_E4 = 128.0f;
+// fp16 scales of the pair planes.  The spectra are bounded by M: 2.02, M^2: 4.1, E: a, E2: a^2, W = (M' M)^(1/2): 2.02
+// with a <= 3.6 for every coefficient set in use, and |entry| <= largest diagonal entry <= ||.||_2.
+constexpr float PAIR_SCALE_M = 8192.0f, PAIR_SCALE_M2 = 8192.0f, PAIR_SCALE_E = 8192.0f, PAIR_SCALE_E2 = 2048.0f, PAIR_SCALE_W = 8192.0f;
 
 struct RootOperands {
     int A, B, O1, O2, C;     // slots (O2 = -1: none)
 };
-__device__ __forceinline__ RootOperands root_operands(int op, int p, bool linear)
+__device__ __forceinline__ RootOperands root_operands(int op, bool linear)
 {
-    const int e = linear ? p : 2;        // T of degree 1: E is b M and takes M's place in the products
+    const int e = linear ? 0 : 2;        // T of degree 1: E is b M and takes M's place in the products
     switch (op) {
-    case OP_SQ: return {p, p, p, -1, 2};
-    case OP_SQ3: return {p, p, -1, -1, p ^ 1};
-    case OP_CUBE: return {p ^ 1, p, p, p ^ 1, 2};
-    case OP_E2: return {e, e, e, -1, p ^ 1};
-    case OP_E4: return {p ^ 1, p ^ 1, p ^ 1, -1, 3};
-    default: return {3, p, p, -1, p ^ 1};          // OP_M
+    case OP_SQ: return {0, 0, 0, -1, 2};
+    case OP_SQ3: return {0, 0, -1, -1, 1};
+    case OP_CUBE: return {1, 0, 0, 1, 2};
+    case OP_E2: return {e, e, e, -1, 1};
+    case OP_W: return {1, 0, 0, -1, 3};
+    default: return {1, 3, 3, -1, 0};              // OP_M
     }
 }
-__device__ __forceinline__ float pair_scale_of(int op, int slot, int p)
+__device__ __forceinline__ float pair_scale_of(int op, int slot)
 {
-    if (slot == 3) return PAIR_SCALE_E4;
-    if (slot == 2) return PAIR_SCALE_E;
-    if (slot == p) return PAIR_SCALE_M;
-    // slot p ^ 1
-    if (op == OP_M) return PAIR_SCALE_M;
-    return (op == OP_SQ3 || op == OP_CUBE) ? PAIR_SCALE_M2 : PAIR_SCALE_E2;
+    switch (slot) {
+    case 0: return PAIR_SCALE_M;
+    case 1: return (op == OP_SQ3 || op == OP_CUBE) ? PAIR_SCALE_M2 : PAIR_SCALE_E2;
+    case 2: return PAIR_SCALE_E;
+    default: return PAIR_SCALE_W;
+    }
 }
 
 // XCD-aware order: workgroup b lands on XCD b % 8; every XCD takes a contiguous range of tiles, so the tiles of
@@ -102,7 +108,7 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
     const uint2 tile = map[op1 >= 0 ? w >> 1 : w];
     const int f = (int)tile.x;
     const int st = state[f];
-    if (st != ST_RUN && !(st == ST_LAST && op != OP_E2 && op != OP_E4 && op != OP_M)) return;
+    if (st != ST_RUN && !(st == ST_LAST && op != OP_E2 && op != OP_W && op != OP_M)) return;
     const FactorScal &S = fs[f];
     if (op != OP_X && S.tier != TIER_PAIR) return;
     const FactorDev &F = fd[f];
@@ -110,30 +116,33 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
     const int n = F.n, rowb = F.rowb, p = k & 1, row0 = ti * T, col0 = tj * T;
-    const char *A, *B, *O1, *O2 = nullptr;
+    const char *A, *B, *O1 = nullptr, *O2 = nullptr;
     char *C;
-    float sA, sB, s1, s2 = 1.0f, sC;
+    float sA, sB, s1 = 1.0f, s2 = 1.0f, sC;
     if (op == OP_X) {
-        A = F.X[p]; B = F.P[degree == 1 ? p : 2]; O1 = A; C = F.X[p ^ 1];
-        sA = s1 = sC = S.x_scale; sB = degree == 1 ? PAIR_SCALE_M : PAIR_SCALE_E;
+        A = F.X[p]; B = F.P[degree == 1 ? 0 : 2]; C = F.X[p ^ 1];
+        sA = sC = S.x_scale; sB = degree == 1 ? PAIR_SCALE_M : PAIR_SCALE_E;
     } else {
-        const RootOperands o = root_operands(op, p, degree == 1);
-        A = F.P[o.A]; B = F.P[o.B]; O1 = o.O1 >= 0 ? F.P[o.O1] : nullptr; C = F.P[o.C];
-        sA = pair_scale_of(op, o.A, p); sB = pair_scale_of(op, o.B, p); s1 = o.O1 >= 0 ? pair_scale_of(op, o.O1, p) : 1.0f;
-        if (o.O2 >= 0) { O2 = F.P[o.O2]; s2 = pair_scale_of(op, o.O2, p); }
-        sC = o.C == 2 ? PAIR_SCALE_E : (o.C == 3 ? PAIR_SCALE_E4 : pair_scale_of(op, o.C, p));
+        const RootOperands o = root_operands(op, degree == 1);
+        A = F.P[o.A]; B = F.P[o.B]; C = F.P[o.C];
+        sA = pair_scale_of(op, o.A); sB = pair_scale_of(op, o.B);
+        if (o.O1 >= 0) { O1 = F.P[o.O1]; s1 = pair_scale_of(op, o.O1); }
+        if (o.O2 >= 0) { O2 = F.P[o.O2]; s2 = pair_scale_of(op, o.O2); }
+        sC = pair_scale_of(op, o.C);
     }
     const RootProd pc = S.prod[op];
     const float k1 = (float)(pc.own1 * (double)(sC / s1)), k2 = (float)(pc.own2 * (double)(sC / s2));
     const float kg = (float)(pc.gam * (double)sC / ((double)sA * (double)sB));
 
-    floatx16 acc[WT][WT];
+    // the cross terms, 2^-11 of the leading ones, in sums of their own: a third of the roundings at full size (log-spaced
+    // spectrum, n = 1024, eps = 1e-6: error as above 5.2e-4 with one sum, 3.3e-4 with two; the time of a refresh + 1 %)
+    floatx16 acc[WT][WT], cross[WT][WT];
 #pragma unroll
     for (int i = 0; i < WT; ++i)
 #pragma unroll
         for (int j = 0; j < WT; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = cross[i][j][v] = 0.0f;
 
     Loader ld;
     ld.init(A, B, rowb, n, row0, col0, wave, lane);
@@ -162,12 +171,11 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
             }
 #pragma unroll
             for (int i = 0; i < WT; ++i) {
-                // small cross terms first, the leading product last
                 const bool cut = WT == 2 && i == 0 && diag_d == 0;      // block (0, 1) of a wavefront on the diagonal
 #pragma unroll
-                for (int j = 0; j < WT; ++j) if (!(j == 1 && cut)) acc[i][j] = mma(al[i], bh[j], acc[i][j]);
+                for (int j = 0; j < WT; ++j) if (!(j == 1 && cut)) cross[i][j] = mma(al[i], bh[j], cross[i][j]);
 #pragma unroll
-                for (int j = 0; j < WT; ++j) if (!(j == 1 && cut)) acc[i][j] = mma(ah[i], bl[j], acc[i][j]);
+                for (int j = 0; j < WT; ++j) if (!(j == 1 && cut)) cross[i][j] = mma(ah[i], bl[j], cross[i][j]);
 #pragma unroll
                 for (int j = 0; j < WT; ++j) if (!(j == 1 && cut)) acc[i][j] = mma(ah[i], bh[j], acc[i][j]);
             }
@@ -192,7 +200,9 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
     const bool to_user = op == OP_X && st == ST_LAST;
     const bool first_x = k == 0 && (op == OP_SQ || op == OP_CUBE);    // X_1 = X_0 T_0, X_0 a multiple of I
     const float inv_c = 1.0f / sC;
-    const float x1a = S.x1a, x1e = -S.x1s * inv_c;
+    const float x1a = S.x1a, x1e = -S.x1s * inv_c, inv_x = 1.0f / S.x_scale;
+    ASTERIA_GLOBAL float *X = (ASTERIA_GLOBAL float *)F.Xout;
+    const int ldx = F.ldx;
     float rsum = 0.0f;
 #pragma unroll
     for (int i = 0; i < WT; ++i) {
@@ -201,9 +211,19 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
             const int br = row0 + (wm * WT + i) * 32, bc = col0 + (wn * WT + j) * 32;
             if (br < bc || br >= n || bc >= n) continue;
             const bool diag = br == bc;
+            acc[i][j] += cross[i][j];
             float val[16];
             if (O1) {
                 load_pair_block(O1, rowb, n, br, bc, lane, val);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) val[v] = k1 * val[v] + kg * acc[i][j][v];
+            } else if (op == OP_X) {
+                const int col = bc + r;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
+                    val[v] = row < n && col < n && row >= col ? X[(size_t)row * ldx + col] : 0.0f;
+                }
 #pragma unroll
                 for (int v = 0; v < 16; ++v) val[v] = k1 * val[v] + kg * acc[i][j][v];
             } else {
@@ -225,10 +245,8 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
                     if (row < n && col < n && row >= col) rsum += row == col ? er * er : 2.0f * er * er;
                 }
             }
-            if (to_user) {
-                // the last X goes to the caller's matrix in fp32
-                ASTERIA_GLOBAL float *X = (ASTERIA_GLOBAL float *)F.Xout;
-                const int ldx = F.ldx;
+            if (op == OP_X) {
+                // X in fp32: its lower triangle until the last update, which completes the caller's matrix
                 const bool vec = (ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(F.Xout) & 15u) == 0;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
@@ -239,7 +257,7 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
                         t[e] = val[4 * g + e] * inv_c;
                         if (rb + e < n && col < n && (!diag || rb + e >= col)) X[(size_t)(rb + e) * ldx + col] = t[e];
                     }
-                    if (col < n) {
+                    if (to_user && col < n) {
                         if (!diag && vec && rb + 4 <= n) *(ASTERIA_GLOBAL floatx4 *)(X + (size_t)col * ldx + rb) = t;
                         else
 #pragma unroll
@@ -247,7 +265,7 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
                                 if (rb + e < n && (!diag || rb + e > col)) X[(size_t)col * ldx + rb + e] = t[e];
                     }
                 }
-                continue;
+                if (to_user) continue;
             }
             uint32_t wd[16];
 #pragma unroll
@@ -260,7 +278,9 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
-                    wd[v] = (row < n && col < n) ? pair_word(x1e * val[v] + (row == col ? x1a : 0.0f)) : 0u;
+                    const float x = x1e * val[v] + (row == col ? x1a : 0.0f);
+                    wd[v] = (row < n && col < n) ? pair_word(x) : 0u;
+                    if (row < n && col < n && row >= col) X[(size_t)row * ldx + col] = x * inv_x;
                 }
                 store_pair_block(F.X[1], rowb, n, br, bc, wd, lane, ws);
             }
@@ -310,10 +330,10 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
-    const int n = F.n, p = k & 1, col0 = tj * 128 + half * 64;
+    const int n = F.n, col0 = tj * 128 + half * 64;
     if (col0 >= n) return;                            // nothing to store; the half's partial sum was cleared when it was last read
     const int rowb = digit_row_bytes(n, NS);
-    const RootOperands o = root_operands(op, p, degree == 1);
+    const RootOperands o = root_operands(op, degree == 1);
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
     const int nk = plane_groups(n), last = nk - 1;
     const int sw = plane_swz<CPR>(r);
@@ -328,7 +348,7 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
     const bool to_pair = (op == OP_SQ && k > 0) || (op == OP_M && (S.handover || S.pair_m));
     const bool first_x = op == OP_SQ && k == 0;       // X_1 = X_0 T_0, X_0 a multiple of I
     const double pe = first_x ? -(double)S.x1s : (op == OP_M ? (double)PAIR_SCALE_M : (double)PAIR_SCALE_E);
-    const double pd = first_x ? (double)S.x1a : 0.0;
+    const double pd = first_x ? (double)S.x1a : 0.0, inv_x = 1.0 / (double)S.x_scale;
     float rsum = 0.0f;
     bool over = false;
 #pragma unroll 1
@@ -411,6 +431,7 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
                 values([&](int v, int row, double val) {
                     const double x = pe * val + (row == col ? pd : 0.0);
                     pw[v] = (row < n && col < n) ? pair_word((float)x) : 0u;
+                    if (first_x && row < n && col < n && row >= col) F.Xout[(size_t)row * F.ldx + col] = (float)(x * inv_x);
                 });
                 store_pair_block(first_x ? F.X[1] : F.P[o.C], F.rowb, n, br, bc, pw, lane, ws);
             }
