@@ -986,6 +986,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         F.pm_partial2 = cv.take<double2>((n + LZ_ROWS - 1) / LZ_ROWS);
         F.pm_tile = cv.take<float>((size_t)F.ntri * PM_TILE_WORDS);
         F.partial = cv.take<float>(F.npart);
+        F.qpart = cv.take<float>(F.npart);
         const size_t pair = plane_pair_bytes(n), slot = prefix ? plane_slot_bytes(n, f64) : pair;
         for (int v = 0; v < 2; ++v) F.X[v] = cv.take<char>(pair);
         // X_0 is never written: a full copy of packed statistics and two vectors of the estimate lie there

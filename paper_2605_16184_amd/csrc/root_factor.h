@@ -21,7 +21,8 @@ struct FactorDev {
     double *F[4];       // fp64 matrices of the chain, the same slots
     int *flags;         // [0]: an entry left the range of its digits
     int rowb;           // bytes of a pair plane row
-    int npart;          // entries of `partial`
+    int npart;          // entries of `partial` and `qpart`
+    float *qpart;       // per tile: sum q(M)^2 of the test before the last update
     int tile_start64;   // first tile of this factor in launches of 64 x 64 tiles
     // fp32 / fp64 path
     float *X32b;        // second fp32 X buffer (workspace); X is kept in fp32 in every precision tier
@@ -84,6 +85,24 @@ struct FactorScal {
     double dmax;          // bound on the largest diagonal entry of M
     float x1a, x1s, x1b;  // X_1 = x1a I - x1s E (times x_scale); E = x1b M where T is linear
     RootProd prod[7];     // by RootOp
+    // test before the last update (plane_advance): q = q[0] I + q[1] M + q[2] M^2 + q[3] E, bound on its squares; 0: none
+    float q[4], q_limit;
 };
+
+// Sum of `count` numbers by one wavefront, the same bits from every one.
+__device__ __forceinline__ float wave_total(const float *p, int count)
+{
+    float t = 0.0f;
+    for (int i = threadIdx.x & 63; i < count; i += 64) t += p[i];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    return t;
+}
+
+// State of a factor once the last iteration's E is there: the iteration goes on where the test does not hold.
+__device__ __forceinline__ int state_after_test(const FactorDev &F, const FactorScal &S, int st)
+{
+    return st == ST_LAST && S.q_limit > 0.0f && !(wave_total(F.qpart, F.npart) <= S.q_limit) ? ST_RUN : st;
+}
 
 }  // namespace asteria

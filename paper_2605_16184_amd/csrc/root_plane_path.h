@@ -74,7 +74,9 @@ __device__ inline void plane_advance(const FactorDev &F, FactorScal &S, int *sta
     const bool ends = resid < c.stop_resid || (consistent && dev < (double)ROOT_STOP_DEV) ||
                       (consistent && dev_next <= 4.0 * (double)ROOT_X_TOL);
     if (c.final_pass) {
-        S.info = ASTERIA_INFO_NOT_CONVERGED;
+        // eigenvalues in [0, hi] stay there, within 1 of 1; beyond that, one is negative
+        S.info = resid > 1.1f * sqrtf((float)F.n) ? ASTERIA_INFO_NOT_PD : ASTERIA_INFO_NOT_CONVERGED;
+        if (S.info == ASTERIA_INFO_NOT_PD) *state = ST_FAIL;
         return;
     }
     if (ends) st = ST_LAST;
@@ -119,6 +121,23 @@ __device__ inline void plane_advance(const FactorDev &F, FactorScal &S, int *sta
         }
     } else {
         S.tier = S.next_tier;
+    }
+    // The residual cannot tell one negative eigenvalue of M from n that deviate as they may, and after the last update
+    // nothing is measured.  So the last product of E also sums the squares of the Chebyshev polynomial of its degree for
+    // [lo, hi], which M, M^2 and E combine to: at most 1 for an eigenvalue inside, q(0)^2 or more for a negative one
+    // (3900 in the last iteration of the schedule for eps = 1e-6).  Where they are more than n the iteration goes on:
+    // eigenvalues that fell short of lo catch up, negative ones grow until they show.  A residual below 1 proves that
+    // there are none.
+    S.q_limit = 0.0f;
+    if (ends && c.degree >= 2 && S.tier == TIER_PAIR && !(resid < 0.9f)) {
+        const double m = 0.5 * (lo + hi), h = 0.5 * (hi - lo), x0 = -m / h;
+        // powers of mu in T_2(x) = 2 x^2 - 1 or T_3(x) = 4 x^3 - 3 x, x = (mu - m) / h
+        const bool cubic = c.degree == 3;
+        const double p0 = cubic ? 4.0 * x0 * x0 * x0 - 3.0 * x0 : 2.0 * x0 * x0 - 1.0, p1 = (cubic ? 12.0 * x0 * x0 - 3.0 : 4.0 * x0) / h;
+        const double p2 = (cubic ? 12.0 * x0 : 2.0) / (h * h), top = cubic ? 4.0 / (h * h * h) : p2;
+        const double e = -top / T.c[c.degree];        // the leading power comes from E = -(c1 M + c2 M^2 + c3 M^3)
+        S.q[0] = (float)p0; S.q[1] = (float)(p1 + e * T.c[1]); S.q[2] = cubic ? (float)(p2 + e * T.c[2]) : 0.0f; S.q[3] = (float)e;
+        S.q_limit = 1.05f * (float)F.n + 10.0f;
     }
     if (S.tier == TIER_DIGIT) {
         const int bits = 8 * S.ns - 1;
@@ -167,7 +186,7 @@ __global__ __launch_bounds__(256) void plane_setup_kernel(const FactorDev *fd, F
             map64[F.tile_start64 + t] = make_uint2((unsigned)f, ((unsigned)ti << 16) | (unsigned)tj);
         }
     }
-    for (int t = tid; t < F.npart; t += 256) F.partial[t] = 0.0f;
+    for (int t = tid; t < F.npart; t += 256) F.partial[t] = F.qpart[t] = 0.0f;
     double mx = 0.0, tr = 0.0;
     for (int i = tid; i < n; i += 256) {
         const double d = (double)F.A[F.a_packed ? packed_off(i, i) : (size_t)i * F.lda + i];
@@ -229,7 +248,7 @@ __global__ __launch_bounds__(64) void plane_control_kernel(const FactorDev *fd, 
     if (st == ST_DONE || st == ST_FAIL) return;
     const FactorDev &F = fd[f];
     FactorScal &S = fs[f];
-    if (st == ST_LAST) {
+    if (state_after_test(F, S, st) == ST_LAST) {
         if (threadIdx.x == 0) {
             const bool over = F.flags[0] != 0;        // the last update's own products may still have run on digits
             if (over) S.info = ASTERIA_INFO_NOT_PD;
@@ -237,12 +256,9 @@ __global__ __launch_bounds__(64) void plane_control_kernel(const FactorDev *fd, 
         }
         return;
     }
-    float r2 = 0.0f;
-    for (int i = threadIdx.x; i < F.npart; i += 64) {
-        r2 += F.partial[i];
-        F.partial[i] = 0.0f;
-    }
-    r2 = wave_sum(r2);
+    if (st == ST_LAST && threadIdx.x == 0) state[f] = ST_RUN;
+    const float r2 = wave_total(F.partial, F.npart);
+    for (int i = threadIdx.x; i < F.npart; i += 64) F.partial[i] = 0.0f;
     if (threadIdx.x != 0) return;
     if (!(r2 == r2) || !(r2 < 3.0e38f) || F.flags[0]) {
         S.info = ASTERIA_INFO_NOT_PD;
@@ -489,7 +505,7 @@ inline size_t plane_factor_bytes(int n, bool prefix, bool f64)
 {
     const size_t pair = plane_pair_bytes(n), slot = prefix ? plane_slot_bytes(n, f64) : pair;
     size_t b = 2 * pair + std::max(slot, 2 * pair) + slot + (prefix ? 2 * slot : 0);
-    b += Carver::need(plane_partials(n), sizeof(float)) + 4 * sizeof(GemmProblem);
+    b += 2 * Carver::need(plane_partials(n), sizeof(float)) + 4 * sizeof(GemmProblem);
     const size_t t = tri_tiles(n);
     return b + (t + (t < (size_t)PLANE_SMALL_TILES ? (size_t)tri_tiles64(n) : 0)) * sizeof(uint2);
 }

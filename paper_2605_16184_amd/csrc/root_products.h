@@ -107,11 +107,12 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
     const int op = (op1 >= 0 && (w & 1)) ? op1 : op0;
     const uint2 tile = map[op1 >= 0 ? w >> 1 : w];
     const int f = (int)tile.x;
-    const int st = state[f];
-    if (st != ST_RUN && !(st == ST_LAST && op != OP_E2 && op != OP_W && op != OP_M)) return;
     const FactorScal &S = fs[f];
     if (op != OP_X && S.tier != TIER_PAIR) return;
     const FactorDev &F = fd[f];
+    const bool makes_e = op == OP_SQ || op == OP_SQ3 || op == OP_CUBE;
+    const int st = makes_e ? state[f] : state_after_test(F, S, state[f]);
+    if (st != ST_RUN && !(st == ST_LAST && (makes_e || op == OP_X))) return;
     const int ti = (int)(tile.y >> 16), tj = (int)(tile.y & 0xffffu);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
@@ -203,6 +204,9 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
     const float x1a = S.x1a, x1e = -S.x1s * inv_c, inv_x = 1.0f / S.x_scale;
     ASTERIA_GLOBAL float *X = (ASTERIA_GLOBAL float *)F.Xout;
     const int ldx = F.ldx;
+    // the test before the last update, by the product that completes E
+    const bool test = st == ST_LAST && S.q_limit > 0.0f && ((op == OP_SQ && degree == 2) || op == OP_CUBE);
+    const float q1 = S.q[1] / s1, q2 = S.q[2] / s2, q3 = S.q[3] * inv_c, q0 = S.q[0];
     float rsum = 0.0f;
 #pragma unroll
     for (int i = 0; i < WT; ++i) {
@@ -212,9 +216,13 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
             if (br < bc || br >= n || bc >= n) continue;
             const bool diag = br == bc;
             acc[i][j] += cross[i][j];
-            float val[16];
+            float val[16], q[16];
             if (O1) {
                 load_pair_block(O1, rowb, n, br, bc, lane, val);
+                if (test) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) q[v] = q1 * val[v];
+                }
 #pragma unroll
                 for (int v = 0; v < 16; ++v) val[v] = k1 * val[v] + kg * acc[i][j][v];
             } else if (op == OP_X) {
@@ -235,6 +243,10 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
                 load_pair_block(O2, rowb, n, br, bc, lane, o);
 #pragma unroll
                 for (int v = 0; v < 16; ++v) val[v] += k2 * o[v];
+                if (test) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) q[v] += q2 * o[v];
+                }
             }
             const int col = bc + r;
             if (op == OP_M) {
@@ -243,6 +255,14 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
                     const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
                     const float er = val[v] * inv_c - (row == col ? 1.0f : 0.0f);
                     if (row < n && col < n && row >= col) rsum += row == col ? er * er : 2.0f * er * er;
+                }
+            }
+            if (test) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
+                    const float x = q[v] + q3 * val[v] + (row == col ? q0 : 0.0f);
+                    if (row < n && col < n && row >= col) rsum += row == col ? x * x : 2.0f * x * x;
                 }
             }
             if (op == OP_X) {
@@ -286,9 +306,9 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
             }
         }
     }
-    if (op == OP_M) {
+    if (op == OP_M || test) {
         __syncthreads();
-        store_partial(rsum, reinterpret_cast<float *>(plane_smem), F.partial + ti * (ti + 1) / 2 + tj, lane, wave, tid, 4);
+        store_partial(rsum, reinterpret_cast<float *>(plane_smem), (test ? F.qpart : F.partial) + ti * (ti + 1) / 2 + tj, lane, wave, tid, 4);
     }
 }
 

@@ -94,6 +94,26 @@ def test_round_off_of_the_roots(kind, n, eps):
     assert float(torch.linalg.norm(Y - ref) / torch.linalg.norm(ref)) <= 5e-4
 
 
+@pytest.mark.parametrize("eps", [0.1, 1e-2, 1e-4, 1e-6, 1e-8])
+@pytest.mark.parametrize("n", [16, 64, 600])
+@pytest.mark.parametrize("below, count", [(0.45, 1), (0.9, 1), (0.9, 16), (1.3, 1), (1.3, 16), (5.0, 1)])
+def test_roots_of_statistics_with_negative_eigenvalues(n, eps, below, count):
+    # eigenvalues -below * eps * lambda_max: with A + eps I positive definite the root is found, otherwise refused
+    lam = torch.linspace(1.0, 0.5, n, device=DEV, dtype=torch.float64)
+    lam[n - min(count, n // 2):] = -below * eps
+    A = torch.diag(lam).float()                                 # exact: the fp32 rounding of a dense one is of the size of eps = 1e-8
+    X = torch.empty_like(A)
+    info = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+    ast.inverse_root([(A, X)], eps, info=info)
+    torch.cuda.synchronize()
+    if below > 1.0:
+        assert int(info[0]) == ast.binding.INFO_NOT_PD
+    else:
+        assert int(info[0]) == 0
+        ref = torch.diag((torch.diagonal(A).double() + eps).pow(-0.25))
+        assert float(torch.linalg.norm(X.double() - ref) / torch.linalg.norm(ref)) <= 2e-3
+
+
 @pytest.mark.parametrize("sizes", [[1, 2, 15, 16, 17, 33, 48], [127, 128, 129, 191, 192, 193], [385, 1153]])
 def test_refresh_at_the_edges(sizes):
     As = [_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n) for n in sizes]
