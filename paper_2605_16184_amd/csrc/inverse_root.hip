@@ -864,17 +864,23 @@ __global__ void root_tables_kernel(const FactorDev *__restrict__ fd, FactorScal 
     }
 }
 
-// The lambda_max estimate of every factor of a pass.  Small factors and full batches: one workgroup per factor, one
-// launch.  Otherwise one launch per step - 32 of them, then one workgroup per factor takes what has not settled
-// (a step of n = 1000 costs it about 35 us against 8 for a launch, but most spectra settle in 8 to 30 steps, and a
-// launch that finds nothing to do costs 2.5); from n = 2048 on launches throughout.
-bool lanczos_by_factor(int cnt, int n_max, bool any_packed)
+// The lambda_max estimate of every factor of a pass.  Small factors, and batches that keep every CU busy until the
+// largest factor is done: one workgroup per factor, one launch.  Otherwise one launch per step - 32 of them, then one
+// workgroup per factor takes what has not settled; from n = 2048 on launches throughout.
+// Refresh in us at eps = 1e-6, a launch per step / a workgroup per factor, power-law spectrum (8 steps):
+//   1 factor    n = 320 488 / 486, 448 512 / 545, 512 525 / 560, 768 633 / 767 (packed ones need three launches a step)
+//   n = 1024    64 factors 9224 / 9310, 128: 17665 / 17507, 192: 26027 / 25588; n = 640 and 1536 alike
+//   200 factors of n = 128 and one of 4096: 11.6 ms / 18.2 (evenly spaced spectrum, 128 steps: 18.1 / 86.2), which is
+//   why the rule counts elements against those of the largest factor
+// 32 launches and a workgroup / launches throughout: power law n = 1024 743 / 998, 1536 1065 / 1314, 2000 1710 / 1921;
+// evenly spaced n = 1024 3762 / 3537, 1536 10374 / 6035, 2000 20121 / 7651: most spectra settle within the 32.
+bool lanczos_by_factor(double elems, int n_max, bool any_packed)
 {
-    return n_max <= LZ_WG_N || (cnt >= LZ_WG_BATCH && n_max <= LZ_WG_MAX_N && !any_packed);
+    return n_max <= LZ_WG_N || (elems >= (double)LZ_WG_BATCH * n_max * n_max && n_max <= LZ_WG_MAX_N && !any_packed);
 }
 constexpr int LZ_LAUNCHES = 32, LZ_LAUNCH_N = 2048;
 
-asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int cnt, const Plan &pl, bool any_full, bool any_packed,
+asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int cnt, double elems, const Plan &pl, bool any_full, bool any_packed,
                                    int tri_max, int n_max, hipStream_t stream)
 {
     const int steps = std::min(pl.power_iters, LZ_MAX);
@@ -882,7 +888,7 @@ asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int 
     const int ld = (n_max + 255) & ~255;
     const size_t lds = 3 * (size_t)ld * sizeof(float);
     static bool cfg_f[MAX_DEVICES] = {}, cfg_s[MAX_DEVICES] = {};
-    if (lanczos_by_factor(cnt, n_max, any_packed)) {
+    if (lanczos_by_factor(elems, n_max, any_packed)) {
         if (any_packed) hipLaunchKernelGGL(lanczos_unpack_kernel, dim3(tri_max, cnt), dim3(256), 0, stream, d_fd);
         if (n_max <= 256) {
             hipLaunchKernelGGL(lanczos_factor_kernel<true>, dim3(cnt), dim3(LZ_THREADS), lds, stream, d_fd, d_fs, tol2, steps, -1, ld);
@@ -958,7 +964,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     std::vector<FactorDev> fd(cnt);
     int tri_total = 0, tri64_total = 0, tri_max = 0, n_max = 0;
     bool any_packed = false, any_full = false;
-    double a_min = 1.0;
+    double a_min = 1.0, elems = 0.0;
     const bool prefix = pl.fp64_iters > 0;
     for (int i = 0; i < cnt; ++i) {
         const asteria_factor &a = f[first + i];
@@ -966,6 +972,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         memset(&F, 0, sizeof(F));
         const int n = a.n;
         n_max = std::max(n_max, n);
+        elems += (double)n * n;
         F.A = a.A; F.Xout = a.X; F.n = n; F.lda = a.lda; F.ldx = a.ldx;
         F.rowb = pair_row_bytes(n); F.ld64 = ld2(n);
         F.ntri = tri_tiles(n);
@@ -1044,7 +1051,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     ASTERIA_HIP_TRY(upload_async(d_fd, fd.data(), sizeof(FactorDev) * cnt, stream));
     if (f64)
         hipLaunchKernelGGL(plane_f64_tables_kernel, dim3((cnt + 127) / 128), dim3(128), 0, stream, d_fd, d_fs, cnt, linear0 ? 1 : 0, ft);
-    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, pl, any_full, any_packed, tri_max, n_max, stream));
+    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, elems, pl, any_full, any_packed, tri_max, n_max, stream));
 
     // intervals and T of a factor that follows the schedule (the device works in fp32 for the scaling: 1e-5 of slack)
     std::vector<PlaneControl> ctl(K + 1);
@@ -1129,13 +1136,14 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
     int tri_total = 0, sq_total = 0, tri_max = 0;
     bool any_packed = false, any_full = false;
     int n_max = 0;
-    double a_min = 1.0;
+    double a_min = 1.0, elems = 0.0;
     for (int i = 0; i < cnt; ++i) {
         const asteria_factor &a = f[first + i];
         FactorDev &F = fd[i];
         memset(&F, 0, sizeof(F));
         const int n = a.n;
         n_max = std::max(n_max, n);
+        elems += (double)n * n;
         F.A = a.A; F.Xout = a.X; F.n = n; F.lda = a.lda; F.ldx = a.ldx;
         F.ld32 = ld4(n); F.ld64 = ld2(n);
         F.ntri = tri_tiles(n);
@@ -1227,7 +1235,7 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
     ASTERIA_HIP_TRY(hipGetLastError());
 
     // 1. lambda_max
-    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, pl, any_full, any_packed, tri_max, n_max, stream));
+    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, elems, pl, any_full, any_packed, tri_max, n_max, stream));
     const int ctl_blocks = (cnt + 127) / 128;
     // 2. scaling, start
     hipLaunchKernelGGL(root_setup_kernel, dim3(ctl_blocks), dim3(128), 0, stream, d_fd, d_fs, d_state, cnt,

@@ -23,8 +23,9 @@
 namespace asteria {
 
 constexpr int LZ_ROWS = 32;      // rows of A per workgroup of lanczos_step_kernel
+// figures beside lanczos_by_factor
 constexpr int LZ_WG_N = 512;     // largest n that lanczos_factor_kernel takes in any batch
-constexpr int LZ_WG_BATCH = 192; // batch from which it takes every n: the device is full of factors
+constexpr int LZ_WG_BATCH = 192; // it takes every n where the batch has as many elements as this number of its largest factors
 constexpr int LZ_WG_MAX_N = 8192;   // its vectors fit LDS
 
 __device__ __forceinline__ float hash_unit(uint32_t f, uint32_t j)

@@ -114,6 +114,21 @@ def test_roots_of_statistics_with_negative_eigenvalues(n, eps, below, count):
         assert float(torch.linalg.norm(X.double() - ref) / torch.linalg.norm(ref)) <= 2e-3
 
 
+@pytest.mark.parametrize("sizes", [[128] * 200 + [1500], [700] * 191 + [513], [700] * 192, [700] * 191 + [1000]])
+def test_roots_of_uneven_batches(sizes):
+    # either side of the line between a workgroup per factor and a launch per step for the largest eigenvalue
+    made = {n: _with_spectrum(n, _spectrum("power", n), 7, n) for n in set(sizes)}
+    Xs = [torch.empty_like(made[n]) for n in sizes]
+    lam = torch.zeros(len(sizes), device=DEV)
+    ast.inverse_root([(made[n], X) for n, X in zip(sizes, Xs)], 1e-6, lambda_max=lam)
+    torch.cuda.synchronize()
+    last = {n: i for i, n in enumerate(sizes)}
+    for n, i in last.items():
+        err, top = _root_error(made[n], Xs[i], 1e-6)
+        assert err <= 2e-3 and abs(float(lam[i]) - top) <= 1e-4 * top, (n, err)
+        assert torch.equal(Xs[sizes.index(n)], Xs[i])
+
+
 @pytest.mark.parametrize("sizes", [[1, 2, 15, 16, 17, 33, 48], [127, 128, 129, 191, 192, 193], [385, 1153]])
 def test_refresh_at_the_edges(sizes):
     As = [_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n) for n in sizes]
