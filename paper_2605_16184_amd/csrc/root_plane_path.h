@@ -479,8 +479,11 @@ __global__ __launch_bounds__(256) void plane_finalize_kernel(const FactorDev *fd
 // ---- host --------------------------------------------------------------------------------------------
 inline int tri_tiles64(int n) { const int t = (n + 63) / 64; return t * (t + 1) / 2; }
 
-// tiles of 128 below which a pass takes 64 x 64 tiles for its pair products: fewer workgroups than the chip holds
-constexpr int PLANE_SMALL_TILES = 512;
+// tiles of 128 below which a pass takes 64 x 64 tiles for its pair products: fewer workgroups than the chip has places
+// for.  Refresh in us at eps = 1e-6, 128-wide / 64-wide tiles, by tiles of 128: n = 512 160 944 / 902, 320 1337 / 1327,
+// 480 1620 / 1795; n = 1024 144 1174 / 1149, 288 1721 / 1740, 432 2038 / 2288; n = 200 300 926 / 869, 450 1057 / 1097;
+// n = 2048 272 2849 / 2926, 408 3281 / 3768
+constexpr int PLANE_SMALL_TILES = 300;
 
 inline size_t plane_pair_bytes(int n) { return Carver::need((size_t)n * pair_row_bytes(n), 1); }
 // bytes of one chain slot: digits (5 at most), fp64 where that tier can occur
