@@ -114,6 +114,21 @@ def test_roots_of_statistics_with_negative_eigenvalues(n, eps, below, count):
         assert float(torch.linalg.norm(X.double() - ref) / torch.linalg.norm(ref)) <= 2e-3
 
 
+def test_roots_of_a_batch_with_an_eps_per_factor():
+    items, eps = [], []
+    for n in (130, 333, 520):
+        for kind in ("power", "graded", "log"):
+            for e in (0.3, 1e-3, 1e-4, 1e-6, 1e-8):
+                items.append((_dense(n, kind), torch.empty(n, n, device=DEV)))
+                eps.append(e)
+    info = torch.full((len(items),), -1, dtype=torch.int32, device=DEV)
+    ast.inverse_root(items, eps, info=info)
+    torch.cuda.synchronize()
+    assert bool((info == 0).all())
+    for (A, X), e in zip(items, eps):
+        assert _root_error(A, X, e)[0] <= 2e-3, (A.shape[0], e)
+
+
 @pytest.mark.parametrize("sizes", [[128] * 200 + [1500], [700] * 191 + [513], [700] * 192, [700] * 191 + [1000]])
 def test_roots_of_uneven_batches(sizes):
     # either side of the line between a workgroup per factor and a launch per step for the largest eigenvalue
@@ -127,6 +142,37 @@ def test_roots_of_uneven_batches(sizes):
         err, top = _root_error(made[n], Xs[i], 1e-6)
         assert err <= 2e-3 and abs(float(lam[i]) - top) <= 1e-4 * top, (n, err)
         assert torch.equal(Xs[sizes.index(n)], Xs[i])
+
+
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("m, n", [(8, 8), (8, 136), (120, 64), (128, 128), (136, 120), (264, 8), (7, 9), (129, 63)])
+def test_statistics_at_the_edges(m, n, packed):
+    g = torch.Generator(device=DEV).manual_seed(m * 1000 + n)
+    G = torch.randn(m, n, generator=g, device=DEV).bfloat16()
+    full, made = [], []
+    for k in (m, n):
+        a = torch.randn(k, k, generator=g, device=DEV)
+        full.append((a + a.T).contiguous())
+        made.append(full[-1].clone())
+    if packed:
+        made = [torch.empty(ast.packed_elems(k), device=DEV) for k in (m, n)]
+        ast.sym_pack(list(zip(full, made)))
+    for beta in (0.75, 0.0):
+        ast.stats_update([(G, made[0], made[1], 0, 1 if packed else 0)], beta)
+        got = made
+        if packed:
+            got = [torch.empty(k, k, device=DEV) for k in (m, n)]
+            ast.sym_unpack(list(zip(got, made)))
+        torch.cuda.synchronize()
+        H = G.double()
+        for side, a in enumerate(got):
+            P = H @ H.T.contiguous() if side == 0 else H.T.contiguous() @ H
+            ref = beta * full[side].double() + (1.0 - beta) * P
+            k = H.shape[1 - side]
+            # exact products, fp32 sums of k of them, one rounding each of the two terms and their sum
+            tol = (k + 3) * 2.0 ** -24 * (beta * full[side].double().abs() + (1.0 - beta) * (H.abs() @ H.abs().T if side == 0 else H.abs().T @ H.abs()))
+            assert bool(((a.double() - ref).abs() <= tol).all()), (m, n, side, beta)
+            full[side] = a.clone()
 
 
 @pytest.mark.parametrize("sizes", [[1, 2, 15, 16, 17, 33, 48], [127, 128, 129, 191, 192, 193], [385, 1153]])
