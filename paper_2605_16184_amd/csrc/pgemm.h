@@ -3,20 +3,15 @@
 //
 // Operands.  A real matrix enters the product as NT bf16 terms whose sum approximates it: term 0
 // is the value rounded to bf16, term 1 the rounded remainder (8 / 16 significant bits for NT = 1 /
-// 2).  An operand is either a plain bf16 matrix (NT = 1), a plain fp32 matrix that the loader cuts
-// into two terms while it stages it (FA / FB), or a matrix stored as terms: interleaved along k in
-// groups of 32, a row holds, for every 32 consecutive k, NT segments of 32 bf16 (64 bytes) - term
-// 0's values, then term 1's - so that element (r, k) of term t sits at
-// r * ld + (k / 32) * (32 NT) + t * 32 + k % 32 and, with NT = 2, one k-group of a row is one
-// 128-byte cache line (row pieces of 64 bytes run at half the load bandwidth: 17 against 34 TB/s
-// from L2).  The LDS layout is that of the stored terms in every case.  A product of two operands
-// is the sum of the term-pair products selected by a compile-time mask; every pair is an exact
-// bf16 x bf16 product accumulated in fp32.
+// 2).  An operand is either a plain bf16 matrix (NT = 1) or a plain fp32 matrix that the loader cuts
+// into two terms while it stages it (FA / FB).  An LDS row is interleaved along k in groups of 32:
+// for every 32 consecutive k, NT segments of 32 bf16 - term 0's values, then term 1's.  A product of
+// two operands is the sum of the term-pair products selected by a compile-time mask; every pair is an
+// exact bf16 x bf16 product accumulated in fp32.
 //
-// One launch walks a device table of problems  C = alpha A B^T + beta C  (A is M x K, B is
-// N x K, both k-contiguous).  Symmetric problems compute the tiles on or below the diagonal and
-// mirror them.  Operand rows are whole tiles and K whole slabs (the callers send other shapes to
-// the guarded kernels), so the K loop has no guards; the fp32 output is guarded.
+// One launch walks a device table of problems  C = A B^T  (A is M x K, B is N x K, both
+// k-contiguous).  Operand rows are whole tiles and K whole slabs (the callers send other shapes to
+// the guarded kernels), so the K loop has no guards; the output is guarded.
 #pragma once
 #include <type_traits>
 
@@ -35,28 +30,22 @@ struct PlaneProblem {
     int M, N, K;
     int lda, ldb, ldc32;    // elements
     int tile_start;
-    int tiles_n;            // tile columns (non-symmetric problems)
-    int state_idx, state_mask;
-    float alpha, beta;
-    int flags;              // GEMM_SYM, GEMM_C_PACKED, GEMM_STORE_T (output stored transposed, no beta),
-                            // GEMM_C_BF16 (C32 is a bf16 matrix, no beta)
+    int tiles_n;            // tile columns
+    int flags;              // GEMM_STORE_T (output stored transposed), GEMM_C_BF16 (C32 is a bf16 matrix)
 };
 
 // pair (ta, tb) of an NTA x NTB split product is issued iff bit ta * 2 + tb of PAIRS is set
 constexpr unsigned PG_PAIRS_2x1 = 0x1u | 0x4u;   // (0,0) (1,0)
 constexpr unsigned PG_PAIRS_2x2 = 0x7u;          // (0,0) (0,1) (1,0): 16 bits of both operands
 
-// WGM x WGN wavefronts of WTM x WTN MFMA tiles (32 x 32); K slabs of BK; DEPTH register sets
-// of global-load prefetch.
-template <int NTA_, int NTB_, unsigned PAIRS_, int WGM_, int WGN_, int WTM_, int WTN_, int BK_, int DEPTH_ = 1, int MODE_ = 0,
-          bool FA_ = false, bool FB_ = false>
+// WGM x WGN wavefronts of WTM x WTN MFMA tiles (32 x 32); K slabs of BK.
+template <int NTA_, int NTB_, unsigned PAIRS_, int WGM_, int WGN_, int WTM_, int WTN_, int BK_, bool FA_, bool FB_>
 struct PgShape {
     // FA / FB: the operand is a plain fp32 row-major matrix, split into two bf16 terms while it is
     // staged (the LDS layout is that of a two-term split matrix); it then needs NT = 2
     static constexpr bool FA = FA_, FB = FB_;
     static_assert((!FA_ || NTA_ == 2) && (!FB_ || NTB_ == 2), "fp32 sources are split into two terms");
-    static constexpr int NTA = NTA_, NTB = NTB_, DEPTH = DEPTH_;
-    static constexpr int MODE = MODE_;                   // 0: every wavefront loads and multiplies in turn; 1: two wavefront groups alternate
+    static constexpr int NTA = NTA_, NTB = NTB_;
     static constexpr unsigned PAIRS = PAIRS_;
     static constexpr int WGM = WGM_, WGN = WGN_, WTM = WTM_, WTN = WTN_, BK = BK_;
     static constexpr int TM = 32 * WTM * WGM, TN = 32 * WTN * WGN;   // workgroup tile
@@ -122,7 +111,7 @@ struct PgLoader {
     static constexpr int SRC_BYTES = F32 ? 4 : 2;
     static constexpr int SLAB_BYTES = F32 ? S::BK * 4 : S::BK * NT * 2;   // bytes of one slab piece of a row
     static_assert(S::NTHR % IPR == 0 && TROWS % RPV == 0 && RPV % 16 == 0, "loader geometry");
-    u32x4 r[S::DEPTH][NV][RPI];
+    u32x4 r[NV][RPI];
     const char *ub;      // wave-uniform base: the loads need no 64-bit vector address arithmetic
     uint32_t vo;         // per-thread byte offset
     size_t step;         // bytes between the rows of consecutive item indices
@@ -144,16 +133,16 @@ struct PgLoader {
             lds_lo = 0;
         }
     }
-    template <int SET> __device__ __forceinline__ void gload(int slab)
+    __device__ __forceinline__ void gload(int slab)
     {
         const size_t k = (size_t)slab * SLAB_BYTES;
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
             for (int e = 0; e < RPI; ++e)
-                r[SET][v][e] = *(const ASTERIA_GLOBAL u32x4 *)(ub + (v * step + k + 16 * e) + vo);
+                r[v][e] = *(const ASTERIA_GLOBAL u32x4 *)(ub + (v * step + k + 16 * e) + vo);
     }
-    template <int SET> __device__ __forceinline__ void lstore(ASTERIA_LDS uint16_t *d) const
+    __device__ __forceinline__ void lstore(ASTERIA_LDS uint16_t *d) const
     {
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
@@ -161,7 +150,7 @@ struct PgLoader {
                 u32x4 hi, lo;
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    const u32x4 x = r[SET][v][e];
+                    const u32x4 x = r[v][e];
                     const float x0 = __uint_as_float(x[0]), x1 = __uint_as_float(x[1]);
                     const float x2 = __uint_as_float(x[2]), x3 = __uint_as_float(x[3]);
                     const uint32_t h0 = pg_pack_bf16(x0, x1), h1 = pg_pack_bf16(x2, x3);
@@ -172,18 +161,15 @@ struct PgLoader {
                 *(ASTERIA_LDS u32x4 *)(d + lds_hi + v * RPV * ROW) = hi;
                 *(ASTERIA_LDS u32x4 *)(d + lds_lo + v * RPV * ROW) = lo;
             } else {
-                *(ASTERIA_LDS u32x4 *)(d + lds_hi + v * RPV * ROW) = r[SET][v][0];
+                *(ASTERIA_LDS u32x4 *)(d + lds_hi + v * RPV * ROW) = r[v][0];
             }
         }
     }
 };
 
 
-// One finished row piece of 8 values at (grow, gcol .. gcol + 7): apply beta, store.
-// `ctile`: for packed lower-tile output the base of the 128 x 128 tile this piece belongs to (row lr of
-// it, 128 floats per row), else null (row-major output at C32 + grow ldc32).
-__device__ __forceinline__ void pg_emit(const PlaneProblem &P, int grow, int gcol, int rlim, int clim, float (&val)[8],
-                                        float *ctile = nullptr)
+// One finished row piece of 8 values at (grow, gcol .. gcol + 7).
+__device__ __forceinline__ void pg_emit(const PlaneProblem &P, int grow, int gcol, int rlim, int clim, const float (&val)[8])
 {
     if (grow >= rlim) return;
     if (P.flags & GEMM_C_BF16) {
@@ -200,15 +186,9 @@ __device__ __forceinline__ void pg_emit(const PlaneProblem &P, int grow, int gco
         }
         return;
     }
-    float *c = ctile ? ctile + (size_t)(grow % PACK_T) * PACK_T + (gcol % PACK_T) : P.C32 + (size_t)grow * P.ldc32 + gcol;
-    const bool vec = (gcol + 8 <= clim) && (ctile || (P.ldc32 & 3) == 0) && ((reinterpret_cast<uintptr_t>(P.C32) & 15u) == 0);
-    if (vec) {
+    float *c = P.C32 + (size_t)grow * P.ldc32 + gcol;
+    if (gcol + 8 <= clim && (P.ldc32 & 3) == 0 && (reinterpret_cast<uintptr_t>(P.C32) & 15u) == 0) {
         ASTERIA_GLOBAL floatx4 *c4 = (ASTERIA_GLOBAL floatx4 *)c;
-        if (P.beta != 0.0f) {
-            const floatx4 o0 = c4[0], o1 = c4[1];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { val[e] += P.beta * o0[e]; val[4 + e] += P.beta * o1[e]; }
-        }
         floatx4 s0, s1;
 #pragma unroll
         for (int e = 0; e < 4; ++e) { s0[e] = val[e]; s1[e] = val[4 + e]; }
@@ -216,16 +196,12 @@ __device__ __forceinline__ void pg_emit(const PlaneProblem &P, int grow, int gco
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-            if (gcol + e < clim) {
-                if (P.beta != 0.0f) val[e] += P.beta * c[e];
-                c[e] = val[e];
-            }
+            if (gcol + e < clim) c[e] = val[e];
     }
 }
 
 template <class S>
-__global__ __launch_bounds__(S::NTHR) void pgemm_kernel(const PlaneProblem *__restrict__ probs, int nprobs,
-                                                        int total_tiles, const int *__restrict__ state)
+__global__ __launch_bounds__(S::NTHR) void pgemm_kernel(const PlaneProblem *__restrict__ probs, int nprobs, int total_tiles)
 {
     constexpr int NTA = S::NTA, NTB = S::NTB, WTM = S::WTM, WTN = S::WTN;
     constexpr int TM = S::TM, TN = S::TN, BK = S::BK;
@@ -241,15 +217,7 @@ __global__ __launch_bounds__(S::NTHR) void pgemm_kernel(const PlaneProblem *__re
         if (probs[mid].tile_start <= t_global) plo = mid; else phi = mid - 1;
     }
     const PlaneProblem P = probs[plo];   // by value: the fields stay in scalar registers across the stores below
-    if (P.state_idx >= 0) {
-        const int st = state[P.state_idx];
-        if (!((1 << st) & P.state_mask)) return;
-    }
-    const int lt = t_global - P.tile_start;
-    const bool sym = (P.flags & GEMM_SYM) != 0;
-    int ti, tj;
-    if (sym) tri_decode(lt, ti, tj);
-    else { ti = lt / P.tiles_n; tj = lt % P.tiles_n; }
+    const int lt = t_global - P.tile_start, ti = lt / P.tiles_n, tj = lt % P.tiles_n;
     const int row0 = ti * TM, col0 = tj * TN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / S::WGN, wn = wave % S::WGN;
@@ -273,28 +241,41 @@ __global__ __launch_bounds__(S::NTHR) void pgemm_kernel(const PlaneProblem *__re
         const uint32_t lds_fa = (uint32_t)((wm * WTM * 32 + r) * S::ROW_A);
         const uint32_t lds_fb = (uint32_t)(TM * S::ROW_A + (wn * WTN * 32 + r) * S::ROW_B);
         const int swa = pg_swz<S::CPR_A>(r), swb = pg_swz<S::CPR_B>(r);
-        constexpr int DEPTH = S::DEPTH;
         const int nk = (P.K + BK - 1) / BK;
 
-        // DEPTH register sets: slab j waits in set j % DEPTH from its global load until it is
-        // stored to LDS one iteration before use.
-        auto gload = [&](auto setc, int slab) {
-            constexpr int set = decltype(setc)::value;
-            la.template gload<set>(slab);
-            lb.template gload<set>(slab);
+        auto gload = [&](int slab) {
+            la.gload(slab);
+            lb.gload(slab);
         };
-        auto lstore = [&](auto setc, int stage) {
-            constexpr int set = decltype(setc)::value;
+        auto lstore = [&](int stage) {
             ASTERIA_LDS uint16_t *d = smem + stage * S::STAGE;
-            la.template lstore<set>(d);
-            lb.template lstore<set>(d + TM * S::ROW_A);
+            la.lstore(d);
+            lb.lstore(d + TM * S::ROW_A);
         };
-        auto compute = [&](int cur) {
-            const ASTERIA_LDS uint16_t *fa = smem + cur * S::STAGE + lds_fa;
-            const ASTERIA_LDS uint16_t *fb = smem + cur * S::STAGE + lds_fb;
+        // Two groups of wavefronts (one wavefront of each per SIMD) run half a period apart:
+        // while one group issues the MFMAs of a k-step from registers, the other reads its
+        // next fragments from LDS and moves the next slab global -> LDS.  Every phase ends in
+        // a workgroup barrier; the second group enters one barrier late and the first one
+        // leaves one barrier late, so all wavefronts execute the same number of barriers.
+        static_assert((S::NTHR / 64) % 2 == 0, "alternating groups: even wavefront count");
+        const int grp = __builtin_amdgcn_readfirstlane(wave) / (S::NTHR / 128);
+        u32x4 af[NTA][WTM], bf[NTB][WTN];
+        auto phase_barrier = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+            pg_lds_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        gload(0);
+        lstore(0);
+        if (1 < nk) gload(1);
+        phase_barrier();
+        if (grp == 1) phase_barrier();
+        for (int kt = 0; kt < nk; ++kt) {
+            const ASTERIA_LDS uint16_t *fa = smem + (kt & 1) * S::STAGE + lds_fa;
+            const ASTERIA_LDS uint16_t *fb = smem + (kt & 1) * S::STAGE + lds_fb;
 #pragma unroll
             for (int s = 0; s < S::STEPS; ++s) {
-                u32x4 af[NTA][WTM], bf[NTB][WTN];
+                // load phase
 #pragma unroll
                 for (int t = 0; t < NTA; ++t) {
                     const int ca = (((s / 2) * NTA + t) * S::CPG + (s % 2) * 2 + h) ^ swa;
@@ -309,6 +290,13 @@ __global__ __launch_bounds__(S::NTHR) void pgemm_kernel(const PlaneProblem *__re
                     for (int j = 0; j < WTN; ++j)
                         bf[t][j] = *(const ASTERIA_LDS u32x4 *)(fb + j * 32 * S::ROW_B + cb * 8);
                 }
+                if (s == S::STEPS - 1) {
+                    if (kt + 1 < nk) lstore((kt + 1) & 1);
+                    if (kt + 2 < nk) gload(kt + 2);
+                }
+                phase_barrier();
+                // multiply phase
+                __builtin_amdgcn_s_setprio(1);
                 // small cross terms first, the leading product last
 #pragma unroll
                 for (int order = NTA + NTB - 2; order >= 0; --order)
@@ -322,103 +310,14 @@ __global__ __launch_bounds__(S::NTHR) void pgemm_kernel(const PlaneProblem *__re
 #pragma unroll
                             for (int j = 0; j < WTN; ++j) acc[i][j] = pg_mma(af[ta][i], bf[tb][j], acc[i][j]);
                     }
-            }
-        };
-        // iteration kt: compute slab kt; store slab kt + 1 (set (kt + 1) % DEPTH) to the other
-        // stage; refill that set with slab kt + 1 + DEPTH
-        auto iteration = [&](auto setc, int kt) {
-            compute(kt & 1);
-            if (kt + 1 < nk) lstore(setc, (kt + 1) & 1);
-            if (kt + 1 + DEPTH < nk) gload(setc, kt + 1 + DEPTH);
-            pg_lds_barrier();
-        };
-
-        if constexpr (S::MODE == 1) {
-            // Two groups of wavefronts (one wavefront of each per SIMD) run half a period apart:
-            // while one group issues the MFMAs of a k-step from registers, the other reads its
-            // next fragments from LDS and moves the next slab global -> LDS.  Every phase ends in
-            // a workgroup barrier; the second group enters one barrier late and the first one
-            // leaves one barrier late, so all wavefronts execute the same number of barriers.
-            static_assert(DEPTH == 1 && (S::NTHR / 64) % 2 == 0, "alternating groups: one register set, even wavefront count");
-            using Set0 = std::integral_constant<int, 0>;
-            const int grp = __builtin_amdgcn_readfirstlane(wave) / (S::NTHR / 128);
-            u32x4 af[NTA][WTM], bf[NTB][WTN];
-            auto phase_barrier = [&]() {
-                __builtin_amdgcn_sched_barrier(0);
-                pg_lds_barrier();
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            gload(Set0{}, 0);
-            lstore(Set0{}, 0);
-            if (1 < nk) gload(Set0{}, 1);
-            phase_barrier();
-            if (grp == 1) phase_barrier();
-            for (int kt = 0; kt < nk; ++kt) {
-                const ASTERIA_LDS uint16_t *fa = smem + (kt & 1) * S::STAGE + lds_fa;
-                const ASTERIA_LDS uint16_t *fb = smem + (kt & 1) * S::STAGE + lds_fb;
-#pragma unroll
-                for (int s = 0; s < S::STEPS; ++s) {
-                    // load phase
-#pragma unroll
-                    for (int t = 0; t < NTA; ++t) {
-                        const int ca = (((s / 2) * NTA + t) * S::CPG + (s % 2) * 2 + h) ^ swa;
-#pragma unroll
-                        for (int i = 0; i < WTM; ++i)
-                            af[t][i] = *(const ASTERIA_LDS u32x4 *)(fa + i * 32 * S::ROW_A + ca * 8);
-                    }
-#pragma unroll
-                    for (int t = 0; t < NTB; ++t) {
-                        const int cb = (((s / 2) * NTB + t) * S::CPG + (s % 2) * 2 + h) ^ swb;
-#pragma unroll
-                        for (int j = 0; j < WTN; ++j)
-                            bf[t][j] = *(const ASTERIA_LDS u32x4 *)(fb + j * 32 * S::ROW_B + cb * 8);
-                    }
-                    if (s == S::STEPS - 1) {
-                        if (kt + 1 < nk) lstore(Set0{}, (kt + 1) & 1);
-                        if (kt + 2 < nk) gload(Set0{}, kt + 2);
-                    }
-                    phase_barrier();
-                    // multiply phase
-                    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-                    for (int order = NTA + NTB - 2; order >= 0; --order)
-#pragma unroll
-                        for (int ta = 0; ta < NTA; ++ta) {
-                            const int tb = order - ta;
-                            if (tb < 0 || tb >= NTB) continue;
-                            if (!((S::PAIRS >> (ta * 2 + tb)) & 1u)) continue;
-#pragma unroll
-                            for (int i = 0; i < WTM; ++i)
-#pragma unroll
-                                for (int j = 0; j < WTN; ++j) acc[i][j] = pg_mma(af[ta][i], bf[tb][j], acc[i][j]);
-                        }
-                    __builtin_amdgcn_s_setprio(0);
-                    phase_barrier();
-                }
-            }
-            if (grp == 0) phase_barrier();
-        } else {
-            gload(std::integral_constant<int, 0>{}, 0);
-            if constexpr (DEPTH > 1) { if (1 < nk) gload(std::integral_constant<int, 1>{}, 1); }
-            if constexpr (DEPTH > 2) { if (2 < nk) gload(std::integral_constant<int, 2>{}, 2); }
-            lstore(std::integral_constant<int, 0>{}, 0);
-            if (DEPTH < nk) gload(std::integral_constant<int, 0>{}, DEPTH);
-            pg_lds_barrier();
-            for (int kt0 = 0; kt0 < nk; kt0 += DEPTH) {
-                // slab kt + 1 lives in set (kt + 1) % DEPTH
-                if constexpr (DEPTH == 1) {
-                    iteration(std::integral_constant<int, 0>{}, kt0);
-                } else {
-                    iteration(std::integral_constant<int, 1>{}, kt0);
-                    if constexpr (DEPTH > 2) { if (kt0 + 1 < nk) iteration(std::integral_constant<int, 2>{}, kt0 + 1); }
-                    if (kt0 + DEPTH - 1 < nk) iteration(std::integral_constant<int, 0>{}, kt0 + DEPTH - 1);
-                }
+                __builtin_amdgcn_s_setprio(0);
+                phase_barrier();
             }
         }
+        if (grp == 0) phase_barrier();
     }
 
     // ---- epilogue: 128 x 128 quadrants through an fp32 LDS tile ----------------------------------
-    const float alpha = P.alpha;
     ASTERIA_LDS float *ct = (ASTERIA_LDS float *)smem_raw;
     constexpr int CP = S::CT_PITCH;
     constexpr int QM = TM / 128, QN = TN / 128;
@@ -429,80 +328,63 @@ __global__ __launch_bounds__(S::NTHR) void pgemm_kernel(const PlaneProblem *__re
         const int qi = q / QN, qj = q % QN;
         const int gi = ti * QM + qi, gj = tj * QN + qj;   // quadrant coordinates in units of 128
         if (gi * 128 >= P.M || gj * 128 >= P.N) continue;
-        if (sym && gi < gj) continue;
-        const bool diag = sym && gi == gj;
-        // packed lower-tile output (tiles are 128 x 128, as the quadrants): nothing is stored above the diagonal
-        const bool packed = (P.flags & GEMM_C_PACKED) != 0;
-        const bool mirror = sym && gi > gj && !packed;
-        float *ctile = packed ? P.C32 + (((size_t)gi * (gi + 1) / 2 + gj) * PACK_T * PACK_T) : nullptr;
-        const bool store_t = !sym && (P.flags & GEMM_STORE_T) != 0;   // only the transposed image is stored
+        const bool store_t = (P.flags & GEMM_STORE_T) != 0;   // the transposed image is stored
         // does this wavefront own part of the quadrant?
         const int wr0 = wm * WROWS - qi * 128, wc0 = wn * WCOLS - qj * 128;   // sub-tile origin relative to the quadrant
         const bool owns = wr0 < 128 && wr0 + WROWS > 0 && wc0 < 128 && wc0 + WCOLS > 0;
-        for (int pass = store_t ? 1 : 0; pass < ((mirror || store_t) ? 2 : 1); ++pass) {
-            if (owns) {
+        if (owns) {
 #pragma unroll
-                for (int i = 0; i < WTM; ++i) {
-                    const int br = wr0 + i * 32;
-                    if (br < 0 || br >= 128) continue;
+            for (int i = 0; i < WTM; ++i) {
+                const int br = wr0 + i * 32;
+                if (br < 0 || br >= 128) continue;
 #pragma unroll
-                    for (int j = 0; j < WTN; ++j) {
-                        const int bc = wc0 + j * 32;
-                        if (bc < 0 || bc >= 128) continue;
-                        if (pass == 0) {
+                for (int j = 0; j < WTN; ++j) {
+                    const int bc = wc0 + j * 32;
+                    if (bc < 0 || bc >= 128) continue;
+                    if (!store_t) {
 #pragma unroll
-                            for (int v = 0; v < 16; ++v)
-                                ct[(br + 8 * (v >> 2) + 4 * h + (v & 3)) * CP + bc + r] = alpha * acc[i][j][v];
-                        } else {
-                            // transposed: ct[col][row .. row + 3]
+                        for (int v = 0; v < 16; ++v)
+                            ct[(br + 8 * (v >> 2) + 4 * h + (v & 3)) * CP + bc + r] = acc[i][j][v];
+                    } else {
+                        // transposed: ct[col][row .. row + 3]
 #pragma unroll
-                            for (int g4 = 0; g4 < 4; ++g4) {
-                                floatx4 w;
+                        for (int g4 = 0; g4 < 4; ++g4) {
+                            floatx4 w;
 #pragma unroll
-                                for (int e = 0; e < 4; ++e) w[e] = alpha * acc[i][j][4 * g4 + e];
-                                *(ASTERIA_LDS floatx4 *)(ct + (bc + r) * CP + br + 8 * g4 + 4 * h) = w;
-                            }
+                            for (int e = 0; e < 4; ++e) w[e] = acc[i][j][4 * g4 + e];
+                            *(ASTERIA_LDS floatx4 *)(ct + (bc + r) * CP + br + 8 * g4 + 4 * h) = w;
                         }
                     }
                 }
             }
-            __syncthreads();
-            // pass 0 writes quadrant (gi, gj); pass 1 writes its mirror image at (gj, gi)
-            const int orow0 = (pass == 0 ? gi : gj) * 128, ocol0 = (pass == 0 ? gj : gi) * 128;
-#pragma unroll 2
-            for (int it = 0; it < ITEMS; ++it) {
-                const int item = tid + it * S::NTHR;
-                const int lr = item >> 4, lc = (item & 15) * 8;
-                float val[8];
-                if (diag) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int c = lc + e;
-                        val[e] = (lr >= c) ? ct[lr * CP + c] : ct[c * CP + lr];
-                    }
-                } else {
-                    const floatx4 v0 = *(const ASTERIA_LDS floatx4 *)(ct + lr * CP + lc);
-                    const floatx4 v1 = *(const ASTERIA_LDS floatx4 *)(ct + lr * CP + lc + 4);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) { val[e] = v0[e]; val[4 + e] = v1[e]; }
-                }
-                pg_emit(P, orow0 + lr, ocol0 + lc, pass == 0 ? P.M : P.N, pass == 0 ? P.N : P.M, val, ctile);
-            }
-            __syncthreads();
         }
+        __syncthreads();
+        const int orow0 = (store_t ? gj : gi) * 128, ocol0 = (store_t ? gi : gj) * 128;
+#pragma unroll 2
+        for (int it = 0; it < ITEMS; ++it) {
+            const int item = tid + it * S::NTHR;
+            const int lr = item >> 4, lc = (item & 15) * 8;
+            float val[8];
+            const floatx4 v0 = *(const ASTERIA_LDS floatx4 *)(ct + lr * CP + lc);
+            const floatx4 v1 = *(const ASTERIA_LDS floatx4 *)(ct + lr * CP + lc + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { val[e] = v0[e]; val[4 + e] = v1[e]; }
+            pg_emit(P, orow0 + lr, ocol0 + lc, store_t ? P.N : P.M, store_t ? P.M : P.N, val);
+        }
+        __syncthreads();
     }
 }
 
 // 256 x 256 tiles, 8 wavefronts in two alternating groups, both operands plain fp32 matrices split
 // into two bf16 terms while staged: the non-symmetric products of the precondition and of the SOAP
 // rotations whose shapes fill whole tiles
-using PgF32x2 = PgShape<2, 2, PG_PAIRS_2x2, 2, 4, 4, 2, 32, 1, 1, true, true>;
+using PgF32x2 = PgShape<2, 2, PG_PAIRS_2x2, 2, 4, 4, 2, 32, true, true>;
 
 // the same with a bf16 matrix as B (16-bit gradients against a root or a basis, two passes): slabs of 32, as
 // two stages of 64 (192 KiB) exceed the LDS; the gradient's 64-byte row pieces are a third of what it loads.
 // Bound by the alternation of fragment reads and MFMAs, as PgF32x2.  With it and the bf16 store, against the guarded
 // 128 x 128 kernel: both products of 64 blocks of 1024 x 1024 809 -> 735 us, bf16 output 841 -> 713 us
-using PgF32xB = PgShape<2, 1, PG_PAIRS_2x1, 2, 4, 4, 2, 32, 1, 1, true, false>;
+using PgF32xB = PgShape<2, 1, PG_PAIRS_2x1, 2, 4, 4, 2, 32, true, false>;
 
 // a plain fp32 matrix can feed PgF32x2: 16-byte aligned rows, whole tiles and slabs
 inline bool pg_f32_operand_ok(const void *p, int rows, int k, int ld)
@@ -533,8 +415,7 @@ inline bool pg_take_large_tiles(long long tiles, long long tiles_k)
 }
 
 template <class S>
-inline hipError_t launch_pgemm(const PlaneProblem *probs, int nprobs, int total_tiles, const int *state,
-                               hipStream_t stream, int kind = 256)
+inline hipError_t launch_pgemm(const PlaneProblem *probs, int nprobs, int total_tiles, hipStream_t stream, int kind)
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
     auto kern = pgemm_kernel<S>;
@@ -542,8 +423,7 @@ inline hipError_t launch_pgemm(const PlaneProblem *probs, int nprobs, int total_
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), S::LDS_BYTES, configured); e != hipSuccess) return e;
     const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
     profile_begin(kind, stream);
-    hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(S::NTHR), S::LDS_BYTES, stream, probs, nprobs,
-                       total_tiles, state);
+    hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(S::NTHR), S::LDS_BYTES, stream, probs, nprobs, total_tiles);
     profile_end(stream);
     return hipGetLastError();
 }

@@ -106,7 +106,6 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
                 q.M = k.n; q.N = k.m; q.K = k.n;
                 q.tiles_n = k.m / PgF32xB::TN;
                 q.tile_start = tiles1f; tiles1f += (k.n / PgF32xB::TM) * q.tiles_n;
-                q.state_idx = -1; q.state_mask = ~0; q.alpha = 1.0f; q.beta = 0.0f;
                 p1f.push_back(q);
             } else {
                 p.A = k.XR; p.lda = k.ldxr; p.B = k.G; p.ldb = k.ldg; p.C = Ut; p.ldc = ldu; p.flags = 0;
@@ -124,7 +123,6 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
                 q.M = k.m; q.N = k.n; q.K = k.m;
                 q.tiles_n = k.n / PgF32x2::TN;
                 q.tile_start = tiles2f; tiles2f += (k.m / PgF32x2::TM) * q.tiles_n;
-                q.state_idx = -1; q.state_mask = ~0; q.alpha = 1.0f; q.beta = 0.0f;
                 p2f.push_back(q);
             } else {
                 p.A = k.XL; p.lda = k.ldxl; p.B = Ut; p.ldb = ldu; p.C = k.P; p.ldc = k.ldp;
@@ -162,12 +160,12 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
         static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
         PlaneProblem *d1f = reinterpret_cast<PlaneProblem *>(d1b + p1[1].size());
         ASTERIA_HIP_TRY(upload_async(d1f, p1f.data(), p1f.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<PgF32xB>(d1f, (int)p1f.size(), tiles1f, nullptr, stream, 514)));
+        ASTERIA_HIP_TRY((launch_pgemm<PgF32xB>(d1f, (int)p1f.size(), tiles1f, stream, 514)));
     }
     ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d2b, (int)p2[1].size(), tiles2[1], nullptr, stream)));
     if (!p2f.empty()) {
         ASTERIA_HIP_TRY(upload_async(d2f, p2f.data(), p2f.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d2f, (int)p2f.size(), tiles2f, nullptr, stream, 513)));
+        ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d2f, (int)p2f.size(), tiles2f, stream, 513)));
     }
     return ASTERIA_OK;
 }

@@ -506,7 +506,6 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
             q.A = QRt; q.lda = ldqrt; q.B = k.G; q.ldb = k.ldg; q.C32 = Tt; q.ldc32 = ldt;
             q.M = k.n; q.N = k.m; q.K = k.n; q.tiles_n = k.m / PgF32xB::TN;
             q.tile_start = tiles1f; tiles1f += (k.n / PgF32xB::TM) * q.tiles_n;
-            q.state_idx = -1; q.state_mask = ~0; q.alpha = 1.0f; q.beta = 0.0f;
             f1.push_back(q);
         } else {
             p.A = k.G; p.lda = k.ldg; p.B = QRt; p.ldb = ldqrt; p.C = Tt; p.ldc = ldt; p.flags = GEMM_STORE_T;
@@ -520,7 +519,6 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
             PlaneProblem q;
             memset(&q, 0, sizeof(q));
             q.M = k.m; q.N = k.n; q.tiles_n = k.n / PgF32x2::TN; q.tile_start = tilesf;
-            q.state_idx = -1; q.state_mask = ~0; q.alpha = 1.0f; q.beta = 0.0f;
             q.K = k.m; q.A = QLt; q.lda = ldqlt; q.B = Tt; q.ldb = ldt; q.C32 = Gr; q.ldc32 = ldw; q.flags = 0;
             f2.push_back(q);
             q.K = k.n; q.A = Np; q.lda = ldw; q.B = k.QR; q.ldb = k.ldqr; q.C32 = Tt; q.ldc32 = ldt; q.flags = GEMM_STORE_T;
@@ -593,18 +591,18 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
         static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
         PlaneProblem *d_f1 = reinterpret_cast<PlaneProblem *>(d_g1b + g1[1].size());
         ASTERIA_HIP_TRY(upload_async(d_f1, f1.data(), f1.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<PgF32xB>(d_f1, (int)f1.size(), tiles1f, nullptr, stream, 514)));
+        ASTERIA_HIP_TRY((launch_pgemm<PgF32xB>(d_f1, (int)f1.size(), tiles1f, stream, 514)));
     }
     if (!g2.empty()) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[1], (int)g2.size(), tiles, nullptr, stream)));
-    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[0], (int)f2.size(), tilesf, nullptr, stream, 513)));
+    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[0], (int)f2.size(), tilesf, stream, 513)));
     const float c1 = 1.0f - powf(beta1, (float)step_t), c2 = 1.0f - powf(beta2, (float)step_t);
     hipLaunchKernelGGL(adam_rotated_kernel, dim3(rows), dim3(256), 0, stream, d_ab, nblocks, beta1, beta2,
                        adam_eps, 1.0f / c1, 1.0f / c2);
     ASTERIA_HIP_TRY(hipGetLastError());
     if (!g2.empty()) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[2], (int)g3.size(), tiles, nullptr, stream)));
-    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[1], (int)f3.size(), tilesf, nullptr, stream, 513)));
+    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[1], (int)f3.size(), tilesf, stream, 513)));
     if (!g2.empty()) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[3], (int)g4.size(), tiles, nullptr, stream)));
-    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[2], (int)f4.size(), tilesf, nullptr, stream, 513)));
+    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[2], (int)f4.size(), tilesf, stream, 513)));
     // one-sided rotations back
     ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true>(d_oL2, (int)oL2.size(), tL2, nullptr, stream)));
     ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(d_oR2, (int)oR2.size(), tR2, nullptr, stream)));

@@ -24,11 +24,11 @@ inline bool stats_operand_ok(const void *p, int rows, int cols, int ld)
 }
 
 // The K loop: acc += A B^T over the rows row0 .. and col0 .. of an operand of n rows (columns when KM), K long.
-template <int ST, bool KM>
+template <bool KM>
 __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16_t *G, int ldg, int n, int K, int row0, int col0,
                                              ASTERIA_LDS char *lds, int wave, int lane)
 {
-    constexpr int OP = 128 * 128, STAGE = 2 * OP;             // bytes of an operand's slab, of a stage
+    constexpr int OP = 128 * 128;                             // bytes of an operand's slab
     const bool diag = row0 == col0;
     const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
     // wavefront w stages instructions 4 w .. 4 w + 3 of each operand's 16 (64 chunks of 16 bytes each)
@@ -54,13 +54,13 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
     }
     const uint32_t slab_bytes = KM ? 64u * ldb : 128u;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds + (uint32_t)wave * 4096u;
-    auto issue = [&](uint32_t stage, int slab) __attribute__((always_inline)) {
+    auto issue = [&](int slab) __attribute__((always_inline)) {
         const uint32_t off = (uint32_t)slab * slab_bytes;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const bool in = slab * 64 + kof[v] < K;
-            load_to_lds(rs, lds0 + stage + (uint32_t)v * 1024u, in ? va[v] + off : OUTSIDE, 0u);
-            if (!diag) load_to_lds(rs, lds0 + stage + OP + (uint32_t)v * 1024u, in ? vb[v] + off : OUTSIDE, 0u);
+            load_to_lds(rs, lds0 + (uint32_t)v * 1024u, in ? va[v] + off : OUTSIDE, 0u);
+            if (!diag) load_to_lds(rs, lds0 + OP + (uint32_t)v * 1024u, in ? vb[v] + off : OUTSIDE, 0u);
         }
     };
     const int nk = (K + 63) / 64;
@@ -91,7 +91,7 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
             }
         }
     }
-    auto compute = [&](uint32_t stage) __attribute__((always_inline)) {
+    auto compute = [&]() __attribute__((always_inline)) {
         if constexpr (KM) {
             auto frag = [&](uint32_t off) __attribute__((always_inline)) {
                 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -104,7 +104,7 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
             for (int s = 0; s < 4; ++s) {
                 u32x4 af[2], bf[2];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) { af[i] = frag(stage + fa[i] + s * 4096); bf[i] = frag(stage + fb[i] + s * 4096); }
+                for (int i = 0; i < 2; ++i) { af[i] = frag(fa[i] + s * 4096); bf[i] = frag(fb[i] + s * 4096); }
                 multiply(af, bf);
                 __builtin_amdgcn_sched_barrier(0);        // the fragments of one step at a time: four would spill
             }
@@ -115,32 +115,22 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
                 const uint32_t c = (uint32_t)(((s * 2 + h) ^ sw) * 16);
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    af[i] = *(const ASTERIA_LDS u32x4 *)(lds + stage + fa[i] + c);
-                    bf[i] = *(const ASTERIA_LDS u32x4 *)(lds + stage + fb[i] + c);
+                    af[i] = *(const ASTERIA_LDS u32x4 *)(lds + fa[i] + c);
+                    bf[i] = *(const ASTERIA_LDS u32x4 *)(lds + fb[i] + c);
                 }
                 multiply(af, bf);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
-    if constexpr (ST == 1) {
-        for (int kt = 0; kt < nk; ++kt) {
-            issue(0u, kt);
-            wait_lds_loads<0>();
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");                    // the reads stay behind the barrier
-            if (diag_d >= 0) compute(0u);
-            wait_lds_loads<0>();                              // this wavefront has read the slab
-            __builtin_amdgcn_s_barrier();
-        }
-    } else {
-        issue(0u, 0);
-        for (int kt = 0; kt < nk; ++kt) {
-            wait_lds_loads<0>();
-            __builtin_amdgcn_s_barrier();
-            if (kt + 1 < nk) issue((uint32_t)((kt + 1) & 1) * STAGE, kt + 1);
-            if (diag_d >= 0) compute((uint32_t)(kt & 1) * STAGE);
-        }
+    for (int kt = 0; kt < nk; ++kt) {
+        issue(kt);
+        wait_lds_loads<0>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");                        // the reads stay behind the barrier
+        if (diag_d >= 0) compute();
+        wait_lds_loads<0>();                                  // this wavefront has read the slab
+        __builtin_amdgcn_s_barrier();
     }
 }
 
@@ -156,11 +146,10 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
 // epilogue has to overlap other tiles' K loops: one slab of LDS and 128 registers, four workgroups per CU, rather
 // than a deeper pipeline and two.  The accumulators meet the old statistics in registers - a half wavefront covers
 // 128 consecutive bytes of a row, the mirror image is four consecutive floats per lane -, no pass through LDS.
-template <int ST>
-__global__ __launch_bounds__(256, ST == 1 ? 4 : 2) void stats_product_kernel(const StatsEntry *__restrict__ entries, int count, int total,
+__global__ __launch_bounds__(256, 4) void stats_product_kernel(const StatsEntry *__restrict__ entries, int count, int total,
                                                                              float beta)
 {
-    __shared__ __align__(16) unsigned char smem[ST * 32768];
+    __shared__ __align__(16) unsigned char smem[32768];
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem;
     const int per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
     const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
@@ -197,8 +186,8 @@ __global__ __launch_bounds__(256, ST == 1 ? 4 : 2) void stats_product_kernel(con
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    if (kmajor) stats_k_loop<ST, true>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
-    else stats_k_loop<ST, false>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
+    if (kmajor) stats_k_loop<true>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
+    else stats_k_loop<false>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
     const int diag_d = diag ? wm - wn : 1;                    // < 0: above the diagonal
     if (diag_d < 0) return;
 
