@@ -208,6 +208,8 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
     const bool test = st == ST_LAST && S.q_limit > 0.0f && ((op == OP_SQ && degree == 2) || op == OP_CUBE);
     const float q1 = S.q[1] / s1, q2 = S.q[2] / s2, q3 = S.q[3] * inv_c, q0 = S.q[0];
     float rsum = 0.0f;
+    // X row-major: a block's base is uniform, beside a 32-bit offset of the lane
+    const uint32_t xo = (uint32_t)(4 * h) * (uint32_t)ldx + (uint32_t)r;
 #pragma unroll
     for (int i = 0; i < WT; ++i) {
 #pragma unroll
@@ -226,11 +228,17 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
 #pragma unroll
                 for (int v = 0; v < 16; ++v) val[v] = k1 * val[v] + kg * acc[i][j][v];
             } else if (op == OP_X) {
-                const int col = bc + r;
+                if (!diag && br + 32 <= n) {
+                    const ASTERIA_GLOBAL float *x = X + (size_t)br * ldx + bc;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
-                    val[v] = row < n && col < n && row >= col ? X[(size_t)row * ldx + col] : 0.0f;
+                    for (int v = 0; v < 16; ++v) val[v] = (x + (size_t)(8 * (v >> 2) + (v & 3)) * ldx)[xo];
+                } else {
+                    const int col = bc + r;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
+                        val[v] = row < n && col < n && row >= col ? X[(size_t)row * ldx + col] : 0.0f;
+                    }
                 }
 #pragma unroll
                 for (int v = 0; v < 16; ++v) val[v] = k1 * val[v] + kg * acc[i][j][v];
@@ -268,16 +276,24 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
             if (op == OP_X) {
                 // X in fp32: its lower triangle until the last update, which completes the caller's matrix
                 const bool vec = (ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(F.Xout) & 15u) == 0;
+                if (!diag && br + 32 <= n) {
+                    ASTERIA_GLOBAL float *x = X + (size_t)br * ldx + bc;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int rb = br + 8 * g + 4 * h;
-                    floatx4 t;
+                    for (int v = 0; v < 16; ++v) (x + (size_t)(8 * (v >> 2) + (v & 3)) * ldx)[xo] = val[v] * inv_c;
+                } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        t[e] = val[4 * g + e] * inv_c;
-                        if (rb + e < n && col < n && (!diag || rb + e >= col)) X[(size_t)(rb + e) * ldx + col] = t[e];
+                    for (int v = 0; v < 16; ++v) {
+                        const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
+                        if (row < n && col < n && row >= col) X[(size_t)row * ldx + col] = val[v] * inv_c;
                     }
-                    if (to_user && col < n) {
+                }
+                if (to_user && col < n) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int rb = br + 8 * g + 4 * h;
+                        floatx4 t;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) t[e] = val[4 * g + e] * inv_c;
                         if (!diag && vec && rb + 4 <= n) *(ASTERIA_GLOBAL floatx4 *)(X + (size_t)col * ldx + rb) = t;
                         else
 #pragma unroll
