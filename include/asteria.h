@@ -156,11 +156,11 @@ typedef struct asteria_root_opts {
                               0 = classical coupled Newton, a = (root+1)/root, g = 1/root              */
     float stop_resid;      /* a factor takes its last step once ||M - I||_F < stop_resid (default 1e-2;
                               the step after that squares the residual)                                */
-    float power_tol;       /* the lambda_max estimate stops once two consecutive steps have raised it by less
+    float power_tol;       /* the lambda_max estimate stops once three consecutive steps have raised it by less
                               than power_tol^2 of itself (default 1e-3, i.e. 1e-6)                     */
     float lambda_margin;   /* spectrum is scaled by 1 / ((1 + lambda_margin) lambda_max + eps)
                               (default 0.01) so an underestimated lambda_max stays inside (0, 1]      */
-    int32_t lowp_from;     /* first iteration that may run on the fp16 matrix cores with the fp32 operands
+    int32_t lowp_from;     /* first iteration that may run on the fp16 matrix cores with the operands
                               split into two fp16 terms (22 bits kept): -1 = choose from eps (default: right
                               after the fp64 prefix, n <= 16384; never for absolute eps),
                               >= max_iters = never                                                      */
@@ -186,7 +186,7 @@ const char *asteria_status_string(asteria_status s);
  * ones - what a relative eps of 1e-8 in asteria_inverse_root needs (with fp32 sums the smallest
  * eigenvalue of a rank-deficient statistic can fall to -2e-8 lambda_max, below such an eps).  At
  * about a tenth of the speed (fp64 matrix cores).  The workspace holds the problem tables and, for a bf16 block whose
- * G is not 16-byte aligned or does not fill whole 128 x 64 tiles, a transposed copy of G.
+ * G is not 16-byte aligned or whose rows are not whole 16-byte pieces, a transposed copy of G.
  * Errors: NULL G, m or n <= 0, ld too small, bad dtype, beta out of range -> INVALID_ARG.   */
 size_t asteria_stats_update_workspace_bytes(const asteria_block *blocks, int nblocks);
 asteria_status asteria_stats_update(const asteria_block *blocks, int nblocks, float beta,
@@ -254,12 +254,15 @@ asteria_status asteria_sym_unpack(const asteria_sympair *items, int nitems, void
  * does reports ASTERIA_INFO_NOT_PD).  The largest Ritz value never exceeds lambda_max and reaches it to a few 1e-7 on
  * every workload tested (leading eigenvalues 0.4 % apart included); it stalls below only if the start
  * vector has no component along the leading eigenvectors, and `lambda_margin` (1 %) is the allowance
- * for that.  If
- * either assumption fails for a factor - an eigenvalue of M_0 outside [eps s / 2, 1] - the predicted
- * interval is wrong for it: the measured residual then disagrees with the prediction, the factor
+ * for that.  If either assumption fails for a factor - an eigenvalue of M_0 outside [eps s / 2, 1] - the
+ * predicted interval is wrong for it: the measured residual then disagrees with the prediction, the factor
  * falls back to the residual rule and runs until ||M - I||_F < stop_resid or max_iters, where it
- * reports ASTERIA_INFO_NOT_CONVERGED; a residual that still agrees within its tolerance
- * (1.5 sqrt(n) times the predicted deviation + 2e-3) can hide one stray eigenvalue that far from 1.
+ * reports ASTERIA_INFO_NOT_CONVERGED.  A residual that still agrees within its tolerance
+ * (1.5 sqrt(n) times the predicted deviation + 2e-3) can hide a stray eigenvalue; under the automatic
+ * precision rules the sum of squares of a Chebyshev polynomial of M for the interval is looked at before the
+ * last update, which one eigenvalue of A below -eps makes larger than n: the iteration then goes on, to the
+ * root where A + eps I is positive definite and to ASTERIA_INFO_NOT_PD where it is not.  X of a factor that
+ * ends so is not defined (it holds an intermediate result).
  *
  *   eps        host array, eps_count entries (1 = shared by all factors, else nfactors).
  *   info       device int32[nfactors] or NULL   (ASTERIA_INFO_*)
@@ -438,9 +441,9 @@ asteria_status asteria_soap_reproject(const asteria_rblock *blocks, int nblocks,
  * cores (else fp32), 2 = A operand bf16, 4 = B operand bf16, 8 = A read k-major, 16 = B read
  * k-major; 32..255 the 16-bit kernel, 32 + (2 = A operand bf16 in memory) + (4 = B operand bf16 in
  * memory) + (64 = A split into two terms) + (128 = B split into two terms), so 224 = both operands
- * fp32 split in two terms and 96 = A split, B one term; 256..299 the guard-free kernels (512 the
- * statistics, 513 the 256 x 256 split x split products); 300 + NS the int8 kernels on NS
- * slices or digits (304, 305).  Not thread safe.                                                    */
+ * fp32 split in two terms (the products on two-term storage too) and 96 = A split, B one term; 512 the
+ * statistics; 513 and 514 the 256 x 256 tiles of a split fp32 matrix with another one or with a bf16 matrix;
+ * 300 + NS the int8 kernels on NS slices or digits (304, 305).  Not thread safe.                    */
 asteria_status asteria_profile_enable(int max_launches);
 int asteria_profile_collect(float *ms, int32_t *kind, int cap);
 /* Algorithmic flops (n^2 (n + 1) per symmetric product) of the products of the fp64 iterations since
