@@ -1095,6 +1095,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
                 hipLaunchKernelGGL(plane_from_f64_kernel, dim3((unsigned)(((size_t)n_max * plane_groups(n_max) * 2 + 255) / 256), (unsigned)cnt),
                                    dim3(256), 0, stream, d_fd, d_fs, d_state, k, what);
         };
+        if (pre && k > 0 && pl.i8_slices > 0) from_f64(2);
         if (pre && d == 2) { ASTERIA_HIP_TRY(chain(OP_SQ, 0)); from_f64(0); }
         if (d == 2) ASTERIA_HIP_TRY(pair(OP_SQ, -1));
         if (d == 3) { ASTERIA_HIP_TRY(pair(OP_SQ3, -1)); ASTERIA_HIP_TRY(pair(OP_CUBE, -1)); }

@@ -78,6 +78,8 @@ struct FactorScal {
     // plane path
     int tier, next_tier;
     int ns, levels;       // digits of this factor's digit planes (4 or 5), digit-product levels kept in this iteration
+    int from_f64;         // this iteration's digits of M are made from the fp64 one
+    int swapped;          // ... and lie in slot 1 since, E2's in slot 0
     int handover;         // the M-update of this iteration writes pair planes for the next one
     int pair_m;           // ... and pair planes beside the digits (the next T is linear: X' = a X - b X M)
     int dexp[5];          // exponents of the digit planes' quanta by slot; 4: the next M

@@ -108,19 +108,31 @@ __device__ inline void plane_advance(const FactorDev &F, FactorScal &S, int *sta
     auto dropped = [&](int ns, int levels) {
         return (digit_dropped(F.n, ns, levels, ge2, gw) + a * a * digit_dropped(F.n, ns, levels, ge2, gm)) / T.image.lo;
     };
+    // digits that are fine enough for this M: 4, 5, or 0
+    auto digits = [&]() {
+        if (c.digits_max >= 4 && digit_rounding(F.n, 4, dm, lo) <= DIGIT_ROUNDING && dropped(4, 5) <= DIGIT_DROPPED) return 4;
+        return c.digits_max >= 5 && digit_rounding(F.n, 5, dm, lo) <= DIGIT_ROUNDING && dropped(5, 6) <= DIGIT_DROPPED ? 5 : 0;
+    };
+    S.from_f64 = 0;
     if (c.k == 0) {
         S.tier = TIER_PAIR;
         S.ns = 4;
+        S.swapped = 0;
         if (c.prefix > 0 && lo < ROOT_LOWP_FLOOR) {
-            S.tier = TIER_F64;
-            if (c.digits_max >= 4 && digit_rounding(F.n, 4, dm, lo) <= DIGIT_ROUNDING && dropped(4, 5) <= DIGIT_DROPPED) S.tier = TIER_DIGIT;
-            else if (c.digits_max >= 5 && digit_rounding(F.n, 5, dm, lo) <= DIGIT_ROUNDING && dropped(5, 6) <= DIGIT_DROPPED) {
-                S.tier = TIER_DIGIT;
-                S.ns = 5;
-            }
+            const int ns = digits();
+            S.tier = ns ? TIER_DIGIT : TIER_F64;
+            if (ns) S.ns = ns;
         }
     } else {
         S.tier = S.next_tier;
+        // the bottom of the spectrum has risen: where digits are enough now, the rest of the prefix runs on them (a
+        // diagonal close to the largest eigenvalue at eps = 1e-8, 64 factors of n = 1024: 30.9 ms in fp64 throughout, 21.7)
+        if (S.tier == TIER_F64 && c.k < c.prefix && c.degree <= 2)
+            if (const int ns = digits()) {
+                S.tier = TIER_DIGIT;
+                S.ns = ns;
+                S.from_f64 = S.swapped = 1;
+            }
     }
     // The residual cannot tell one negative eigenvalue of M from n that deviate as they may, and after the last update
     // nothing is measured.  So the last product of E also sums the squares of the Chebyshev polynomial of its degree for
@@ -389,15 +401,16 @@ __global__ __launch_bounds__(256) void plane_init_kernel(const FactorDev *fd, co
     if (over) F.flags[0] = 1;
 }
 
-// Pair planes of a factor whose chain runs on fp64 matrices.  what 0: E (the first iteration's becomes X_1),
-// 1: the next M, where the next iteration reads it as pair planes.
+// Planes from the matrices of a factor whose chain runs in fp64.  what 0: pair planes of E (the first iteration's
+// becomes X_1), 1: of the next M, where the next iteration reads it so, 2: digits of M, where the chain goes over to them
+// (into slot 1: E2 is dead, and slot 0 holds the fp64 M).
 __global__ __launch_bounds__(256) void plane_from_f64_kernel(const FactorDev *fd, const FactorScal *fs, const int *state, int k, int what)
 {
     const int f = blockIdx.y;
     const FactorScal &S = fs[f];
-    if (S.tier != TIER_F64) return;
+    if (what == 2 ? !S.from_f64 : S.tier != TIER_F64) return;
     const int st = state[f];
-    if (st != ST_RUN && !(st == ST_LAST && what == 0)) return;
+    if (st != ST_RUN && !(st == ST_LAST && what != 1)) return;
     if (what == 1 && !S.handover && !S.pair_m) return;
     const FactorDev &F = fd[f];
     const int n = F.n, per = plane_groups(n) * 2;
@@ -405,6 +418,24 @@ __global__ __launch_bounds__(256) void plane_from_f64_kernel(const FactorDev *fd
     if (r >= n) return;
     const int slot = what == 0 ? 2 : 0;
     const double *src = F.F[slot] + (size_t)r * F.ld64 + c0;
+    if (what == 2) {
+        const double inv_q = ldexp(1.0, -S.dexp[0]);
+        uint32_t wd[16], t;
+        u32x4 top = {0u, 0u, 0u, 0u};
+        bool over = false;
+        const int grp = c0 >> 5, hf = (c0 >> 4) & 1;
+        if (S.ns == 4) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) wd[e] = digit_word<4>(rint((c0 + e < n ? src[e] : 0.0) * inv_q), t, over);
+            store_digit_chunk<4>(F.D[1] + (size_t)r * digit_row_bytes(n, 4) + grp * 128 + hf * 16, wd, top);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) { wd[e] = digit_word<5>(rint((c0 + e < n ? src[e] : 0.0) * inv_q), t, over); top[e >> 2] |= t << (8 * (e & 3)); }
+            store_digit_chunk<5>(F.D[1] + (size_t)r * digit_row_bytes(n, 5) + grp * 160 + hf * 16, wd, top);
+        }
+        if (over) F.flags[0] = 1;
+        return;
+    }
     const bool x1 = what == 0 && k == 0;
     uint32_t w[16];
 #pragma unroll

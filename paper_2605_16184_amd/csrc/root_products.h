@@ -370,6 +370,7 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
     if (col0 >= n) return;                            // nothing to store; the half's partial sum was cleared when it was last read
     const int rowb = digit_row_bytes(n, NS);
     const RootOperands o = root_operands(op, degree == 1);
+    auto digits_of = [&](int slot) { return F.D[slot < 2 ? slot ^ S.swapped : slot]; };
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
     const int nk = plane_groups(n), last = nk - 1;
     const int sw = plane_swz<CPR>(r);
@@ -392,7 +393,7 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
         const int row0 = ti * 128 + step * 64;
         if (row0 >= n || row0 + RB - 1 < col0) continue;              // nothing of it below the diagonal (uniform)
         Loader ld;
-        ld.init(F.D[o.A], F.D[o.B], rowb, n, row0, col0, wave, lane);
+        ld.init(digits_of(o.A), digits_of(o.B), rowb, n, row0, col0, wave, lane);
         const ASTERIA_LDS char *fa = lds + (wm * 32 * BI + r) * ROWL, *fb = lds + (RB + wn * 32 + r) * ROWL;
         i32x16 acc[L][BI];
 #pragma unroll
@@ -438,7 +439,7 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
             const int br = row0 + (wm * BI + i) * 32, bc = col0 + wn * 32;
             if (br < bc || br >= n || bc >= n) continue;
             const int col = bc + r;
-            const char *own = F.D[o.O1] + (size_t)min(col, n - 1) * rowb + (br >> 5) * (32 * NS) + 4 * h;
+            const char *own = digits_of(o.O1) + (size_t)min(col, n - 1) * rowb + (br >> 5) * (32 * NS) + 4 * h;
             // calls use(v, row, value) for the block's elements; used once per output format (the second time
             // the own digits come from L1: cheaper than holding both formats in registers)
             auto values = [&](auto use) {
@@ -460,7 +461,7 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
             if (to_digits) {
                 uint32_t wd[16], tp[16];
                 values([&](int v, int, double val) { wd[v] = digit_word<NS>(rint(val * inv_q), tp[v], over); });
-                store_digit_block<NS>(F.D[o.C], rowb, n, br, bc, wd, tp, lane, ws);
+                store_digit_block<NS>(digits_of(o.C), rowb, n, br, bc, wd, tp, lane, ws);
             }
             if (to_pair || first_x) {
                 uint32_t pw[16];

@@ -68,6 +68,13 @@ def _dense(n, kind):
         s = 10 ** (-4 * (i - 1) / (n - 1))
         A = (A @ A.T.contiguous()) * s[:, None] * s[None, :]
         return (0.5 * (A + A.T)).float().contiguous()
+    if kind == "axis":                                          # a power law close to the axes: largest diagonal entry 0.8 lambda_max
+        v = torch.ones_like(i) + 2.0 * (i == 1)
+        v = v / v.norm()
+        A = torch.diag(i ** -2.0)
+        A = A - 2.0 * torch.outer(v, v @ A)
+        A = A - 2.0 * torch.outer(A @ v, v)
+        return (0.5 * (A + A.T)).float().contiguous()
     lam = {"power": i ** -2.0, "log": 10 ** (-16 * (i - 1) / (n - 1)),
            "lowrank": torch.where(i <= 32, 1.0 / i, torch.full_like(i, 1e-5))}[kind]
     return _with_spectrum(n, 0.03 * lam, 13, n)
@@ -75,7 +82,7 @@ def _dense(n, kind):
 
 @pytest.mark.parametrize("eps", [1e-6, 1e-8])
 @pytest.mark.parametrize("n", [130, 333, 1024])
-@pytest.mark.parametrize("kind", ["power", "lowrank", "graded", "log"])
+@pytest.mark.parametrize("kind", ["power", "lowrank", "graded", "log", "axis"])
 def test_round_off_of_the_roots(kind, n, eps):
     A = _dense(n, kind)
     X = torch.empty_like(A)
