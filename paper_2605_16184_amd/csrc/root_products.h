@@ -86,7 +86,8 @@ __device__ __forceinline__ void store_partial(float rsum, float *red, float *dst
 // without passing through registers; ST stages.
 //   WT = 2, two stages: 64 KiB of LDS, two workgroups per CU, one loading or storing while the other multiplies.
 //     600 symmetric products of n = 1024: K loop 2.0 ms (1.0 PFLOP/s issued; the fp16 library product of
-//     8192^3 reaches 1.07 on the same card), against 2.6 ms when the fp32 operands are split in the loop.
+//     8192^3 reaches 1.07 on the same card), against 2.6 ms when the fp32 operands are split in the loop (both with one
+//     sum for all terms; whole launches of the refresh of the 1.1B model, as they are now: 0.71 PFLOP/s issued).
 //     256 x 256 tiles on 8 wavefronts: the same within 2 % at n = 1024 and 4 % slower at n = 512.
 //   WT = 1, four stages: for launches of too few 128-wide tiles to fill the chip; short K steps, so the loads
 //     need more than one slab of lead.
