@@ -806,6 +806,12 @@ inline hipError_t launch_gemm_grouped(const GemmProblem *probs, int nprobs, int 
     return hipGetLastError();
 }
 
+// tiles of edge x edge on or below the diagonal
+__host__ __device__ inline int tri_tiles_of(int n, int edge)
+{
+    const int t = (n + edge - 1) / edge;
+    return t * (t + 1) / 2;
+}
 __host__ __device__ inline int tri_tiles(int n)
 {
     const int t = (n + BM - 1) / BM;

@@ -962,7 +962,8 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     int *d_state = cv.take<int>(cnt);
     int *d_flags = cv.take<int>(cnt);
     std::vector<FactorDev> fd(cnt);
-    int tri_total = 0, tri64_total = 0, tri_max = 0, n_max = 0;
+    int tri_total = 0, tri256_total = 0, tri_max = 0, n_max = 0;
+    double work128 = 0.0, work256 = 0.0, rows = 0.0;
     bool any_packed = false, any_full = false;
     double a_min = 1.0, elems = 0.0;
     const bool prefix = pl.fp64_iters > 0;
@@ -977,7 +978,8 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         F.rowb = pair_row_bytes(n); F.ld64 = ld2(n);
         F.ntri = tri_tiles(n);
         F.tile_start = tri_total; tri_total += F.ntri;
-        F.tile_start64 = tri64_total; tri64_total += tri_tiles64(n);
+        tri256_total += tri_tiles_of(n, 256);
+        work128 += pair_work(n, 128); work256 += pair_work(n, 256); rows += n;
         F.npart = plane_partials(n);
         F.flags = d_flags + i;
         F.a_packed = a.a_layout == ASTERIA_LAYOUT_PACKED ? 1 : 0;
@@ -1007,8 +1009,10 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
             }
         F.P[0] = chain[2]; F.P[1] = chain[2] + pair; F.P[2] = F.P[3] = chain[3];
     }
-    const bool small = tri_total < PLANE_SMALL_TILES;
-    uint2 *d_map = cv.take<uint2>(tri_total), *d_map64 = small ? cv.take<uint2>(tri64_total) : nullptr;
+    const int edge = pair_tile_edge(tri_total, tri256_total, work128, work256, rows / cnt);
+    int pair_total = 0;
+    for (FactorDev &F : fd) { F.tile_start_p = pair_total; pair_total += tri_tiles_of(F.n, edge); }
+    uint2 *d_map = cv.take<uint2>(tri_total), *d_map_p = edge == 128 ? d_map : cv.take<uint2>(pair_total);
     PlaneF64Tables ft = {};
     if (f64)
         for (int o = 0; o < 4; ++o) ft.t[o] = cv.take<GemmProblem>(cnt);
@@ -1071,7 +1075,8 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         c.counters = profile_i8_counters();
         return c;
     };
-    hipLaunchKernelGGL(plane_setup_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, d_state, pl.margin, control(0), d_map, d_map64);
+    hipLaunchKernelGGL(plane_setup_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, d_state, pl.margin, control(0), d_map,
+                       edge == 128 ? nullptr : d_map_p, edge);
     hipLaunchKernelGGL(plane_init_kernel, dim3(tri_total), dim3(256), 0, stream, d_fd, d_fs, d_state, d_map, linear0 ? 1 : 0);
     ASTERIA_HIP_TRY(hipGetLastError());
     for (int k = 0; k < K; ++k) {
@@ -1079,8 +1084,11 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         const int d = deg[k];
         const bool pre = k < J;
         auto pair = [&](int op0, int op1) -> hipError_t {
-            if (small) return launch_pair_product<1, 4>(d_fd, d_fs, d_state, d_map64, tri64_total, op0, op1, k, d, stream);
-            return launch_pair_product<2, 2>(d_fd, d_fs, d_state, d_map, tri_total, op0, op1, k, d, stream);
+            switch (edge) {
+            case 64: return launch_pair_product<2, 2, 2, 2, 4>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
+            case 128: return launch_pair_product<2, 2, 4, 4, 2>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
+            default: return launch_pair_product<4, 2, 4, 8, 2>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
+            }
         };
         auto chain = [&](int op, int tab) -> hipError_t {       // digit and fp64 products of the prefix
             hipError_t e = hipSuccess;

@@ -213,28 +213,6 @@ __device__ __forceinline__ void store_pair_block(char *C, int rowb, int n, int b
     }
 }
 
-// The block of a symmetric pair plane at (br, bc) in accumulator order, from its mirror image (row bc + r,
-// 4 consecutive k per register group): v[4 g + e], stored domain.
-__device__ __forceinline__ void load_pair_block(const char *M, int rowb, int n, int br, int bc, int lane, float (&v)[16])
-{
-    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-    typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
-    const int r = lane & 31, h = lane >> 5;
-    const char *p = M + (size_t)min(bc + r, n - 1) * rowb + (br >> 5) * 128 + h * 8;
-    u32x2_t hi[4], lo[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        hi[g] = *(const ASTERIA_GLOBAL u32x2_t *)(p + g * 16);
-        lo[g] = *(const ASTERIA_GLOBAL u32x2_t *)(p + 64 + g * 16);
-    }
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const f16x4_t a = __builtin_bit_cast(f16x4_t, hi[g]), b = __builtin_bit_cast(f16x4_t, lo[g]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[4 * g + e] = (float)a[e] + (float)b[e];
-    }
-}
-
 // ---- digits ----------------------------------------------------------------------------------------
 // Balanced base-256 digits of an integer: adding 128 at every lower digit and flipping the top bit of the
 // bytes turns two's complement into digits in [-128, 127].  NS = 4: |v| <= 0x7f7f7f7f; NS = 5: the low

@@ -23,7 +23,7 @@ struct FactorDev {
     int rowb;           // bytes of a pair plane row
     int npart;          // entries of `partial` and `qpart`
     float *qpart;       // per tile: sum q(M)^2 of the test before the last update
-    int tile_start64;   // first tile of this factor in launches of 64 x 64 tiles
+    int tile_start_p;   // first tile of this factor in the launches of the pair products
     // fp32 / fp64 path
     float *X32b;        // second fp32 X buffer (workspace); X is kept in fp32 in every precision tier
     float *M32[2];

@@ -177,7 +177,7 @@ __device__ inline void plane_advance(const FactorDev &F, FactorScal &S, int *sta
 
 // One workgroup per factor: scaling, start of the interval, and the decision about iteration 0.
 __global__ __launch_bounds__(256) void plane_setup_kernel(const FactorDev *fd, FactorScal *fs, int *state, float margin, PlaneControl c,
-                                                          uint2 *map128, uint2 *map64)
+                                                          uint2 *map128, uint2 *map_p, int pair_tile)
 {
     const int f = blockIdx.x;
     const FactorDev &F = fd[f];
@@ -190,12 +190,12 @@ __global__ __launch_bounds__(256) void plane_setup_kernel(const FactorDev *fd, F
         tri_decode(t, ti, tj);
         map128[F.tile_start + t] = make_uint2((unsigned)f, ((unsigned)ti << 16) | (unsigned)tj);
     }
-    if (map64) {
-        const int t64 = (n + 63) / 64, nt = t64 * (t64 + 1) / 2;
+    if (map_p) {
+        const int nt = tri_tiles_of(n, pair_tile);
         for (int t = tid; t < nt; t += 256) {
             int ti, tj;
             tri_decode(t, ti, tj);
-            map64[F.tile_start64 + t] = make_uint2((unsigned)f, ((unsigned)ti << 16) | (unsigned)tj);
+            map_p[F.tile_start_p + t] = make_uint2((unsigned)f, ((unsigned)ti << 16) | (unsigned)tj);
         }
     }
     for (int t = tid; t < F.npart; t += 256) F.partial[t] = F.qpart[t] = 0.0f;
@@ -508,13 +508,26 @@ __global__ __launch_bounds__(256) void plane_finalize_kernel(const FactorDev *fd
 }
 
 // ---- host --------------------------------------------------------------------------------------------
-inline int tri_tiles64(int n) { const int t = (n + 63) / 64; return t * (t + 1) / 2; }
-
-// tiles of 128 below which a pass takes 64 x 64 tiles for its pair products: fewer workgroups than the chip has places
-// for.  Refresh in us at eps = 1e-6, 128-wide / 64-wide tiles, by tiles of 128: n = 512 160 944 / 902, 320 1337 / 1327,
-// 480 1620 / 1795; n = 1024 144 1174 / 1149, 288 1721 / 1740, 432 2038 / 2288; n = 200 300 926 / 869, 450 1057 / 1097;
-// n = 2048 272 2849 / 2926, 408 3281 / 3768
-constexpr int PLANE_SMALL_TILES = 300;
+// Edge of the tiles of a pass's pair products.  Small ones where there are fewer workgroups than the chip has places for.
+// A single product of the kind E2 in us, 64 / 128-wide tiles, by tiles of 128: n = 512 160 24 / 25, 300 37 / 36, 440 50 / 40;
+// n = 1024 144 36 / 37, 288 56 / 53; n = 200 180 17 / 18, 450 29 / 25; n = 2048 272 97 / 93.
+// Large ones (one workgroup per CU) from two and a half rounds of the chip on, for matrices that their tiles cover no worse than
+// 128-wide ones do: 128 / 256-wide, by tiles of 256: n = 1024 320 143 / 183, 640 258 / 278, 960 380 / 374, 2000 788 / 771, 6000 2311 /
+// 2249; n = 2048 288 247 / 289, 576 435 / 459, 1152 865 / 802; n = 4096 544 828 / 880, 1088 1658 / 1530; n = 900 3000 953 / 919; but
+// n = 512 1800 415 / 431 (short K: the stores weigh more), n = 640 3000 617 / 687 (a quarter more work).  Products with the X update
+// gain 3 to 8 % more.
+constexpr int PLANE_SMALL_TILES = 250, PLANE_LARGE_TILES = 700, PLANE_LARGE_N = 512;
+inline int pair_tile_edge(int tri128, int tri256, double work128, double work256, double n_mean)
+{
+    if (tri128 < PLANE_SMALL_TILES) return 64;
+    return tri256 >= PLANE_LARGE_TILES && work256 <= 1.03 * work128 && n_mean > (double)PLANE_LARGE_N ? 256 : 128;
+}
+// work of a factor's pair product in tiles of 128 x 128 x n: a diagonal tile of 256 takes three quarters of a whole one
+inline double pair_work(int n, int tile)
+{
+    const double t = (n + tile - 1) / tile;
+    return n * (tile == 256 ? 4.0 * (t * (t - 1) / 2 + 0.75 * t) : t * (t + 1) / 2);
+}
 
 inline size_t plane_pair_bytes(int n) { return Carver::need((size_t)n * pair_row_bytes(n), 1); }
 // bytes of one chain slot: digits (5 at most), fp64 where that tier can occur
@@ -527,7 +540,7 @@ inline size_t plane_slot_bytes(int n, bool f64)
 inline int plane_partials(int n)
 {
     const int t = tri_tiles(n);
-    return t < PLANE_SMALL_TILES ? std::max(2 * t, tri_tiles64(n)) : 2 * t;
+    return t < PLANE_SMALL_TILES ? std::max(2 * t, tri_tiles_of(n, 64)) : 2 * t;
 }
 // X_k, X_{k+1} and the chain slots.  The pair planes of M and E2 lie in slot 2, those of E and W in slot 3, over the
 // digit or fp64 matrices of the prefix:
@@ -541,7 +554,7 @@ inline size_t plane_factor_bytes(int n, bool prefix, bool f64)
     size_t b = 2 * pair + std::max(slot, 2 * pair) + slot + (prefix ? 2 * slot : 0);
     b += 2 * Carver::need(plane_partials(n), sizeof(float)) + 4 * sizeof(GemmProblem);
     const size_t t = tri_tiles(n);
-    return b + (t + (t < (size_t)PLANE_SMALL_TILES ? (size_t)tri_tiles64(n) : 0)) * sizeof(uint2);
+    return b + (t + (size_t)tri_tiles_of(n, t < (size_t)PLANE_SMALL_TILES ? 64 : 256)) * sizeof(uint2);
 }
 
 }  // namespace asteria

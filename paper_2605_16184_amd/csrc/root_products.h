@@ -4,6 +4,9 @@
 // with per-factor coefficients that the control kernel has left on the device; only tiles on or below the
 // diagonal are computed, their mirror images are stored with them.
 #pragma once
+#include <algorithm>
+#include <type_traits>
+
 #include "planes.h"
 #include "root_factor.h"
 
@@ -81,24 +84,66 @@ __device__ __forceinline__ void store_partial(float rsum, float *red, float *dst
 }
 
 // ---- pair planes -------------------------------------------------------------------------------------
-// A workgroup of 2 x 2 wavefronts, WT x WT MFMA blocks each (tile 64 WT), slabs of 32 k: three fp16 MFMA passes
-// per block and 16 k (lo hi, hi lo, hi hi: both operands to 2^-22), fp32 sums.  Operands go from memory to LDS
-// without passing through registers; ST stages.
-//   WT = 2, two stages: 64 KiB of LDS, two workgroups per CU, one loading or storing while the other multiplies.
-//     600 symmetric products of n = 1024: K loop 2.0 ms (1.0 PFLOP/s issued; the fp16 library product of
-//     8192^3 reaches 1.07 on the same card), against 2.6 ms when the fp32 operands are split in the loop (both with one
-//     sum for all terms; whole launches of the refresh of the 1.1B model, as they are now: 0.71 PFLOP/s issued).
-//     256 x 256 tiles on 8 wavefronts: the same within 2 % at n = 1024 and 4 % slower at n = 512.
-//   WT = 1, four stages: for launches of too few 128-wide tiles to fill the chip; short K steps, so the loads
-//     need more than one slab of lead.
-// In a diagonal tile the wavefront above the diagonal multiplies nothing, the two on it three of four blocks.
-template <int WT, int ST>
-__global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *__restrict__ fd, const FactorScal *__restrict__ fs,
+// C of one tile per workgroup of WGM x WGN wavefronts; a wavefront owns MI x NJ MFMA blocks of 16 x 16, slabs of 32 k, ST
+// stages of LDS.  Three fp16 products per block and slab (lo hi, hi lo, hi hi: both operands to 2^-22) start from zero
+// and the block's fp32 sum takes them in one addition: one rounding at full size per 32 k.
+//
+// Of a pair plane only the tiles on and below the diagonal (tiles of the launch's size, whole on the diagonal) are
+// written and read.  An operand row beyond its diagonal tile comes from the column that mirrors it: a slab is then 32
+// rows of the plane as they lie in memory, and the MFMA operands come out of LDS through transposed reads.
+//
+// Bound by power and by HBM: operands that toggle hold the clock at 1.7 GHz, and a product of n = 1024 has 80 flop per
+// byte of its matrices and fp16 pass.  Hence one triangle, and tiles of 256 x 256 on 8 wavefronts (64 x 128 each), which read
+// two thirds of the LDS bytes and half of the L2 bytes of 128 x 128 on 4.
+//   - Operands go from memory to LDS without registers.
+//   - The barrier between two slabs comes before the last column block of a slab: the next slab's first operands are
+//     read behind those products, and its loads are spread between them.
+//   - The linear term's loads are one block ahead of the arithmetic; a block goes through 4 KiB of LDS once and leaves
+//     in whole lines.
+// Measured, single product of the kind E2 (with the X update), against 128 x 128 tiles with whole planes and running sums
+// for either kind of term: 600 of n = 1024 2.20 (4.56) ms, 2.50 (5.28) before; 8 of n = 4096 1.53 (3.00), 1.87 (3.49); 900 of
+// n = 768 1.64 (3.41), 1.89 (4.24).  Of the 2.20 ms the K loop is 1.71 (1.27 PFLOP/s issued, 3900 cycles a slab for 3072 of
+// MFMA), loading the linear term 0.14, storing 0.2.  Error of the root that does not commute with A, log-spaced spectrum,
+// eps = 1e-6, n = 2048: 2.8e-4, 4.5e-4 before.
+template <int WGM, int WGN, int MI, int NJ, int ST>
+struct PairShape {
+    static constexpr int NW = WGM * WGN, TM = 16 * MI * WGM, TN = 16 * NJ * WGN;
+    static constexpr int NI = (TM + TN) / (8 * NW);          // load instructions of a wavefront per slab
+    static constexpr int H = NI >= 8 ? NI / 2 : NI;           // ... of these issued behind the last column block of a slab
+    static constexpr uint32_t STAGE = (uint32_t)TM * 128u;    // bytes per operand and stage
+    static constexpr int KR = 256 / TM;                       // rows of a transposed slab per load instruction
+    static constexpr uint32_t SCRATCH = 2u * ST * STAGE;
+    static constexpr size_t LDS = SCRATCH + NW * 4096u;
+    static_assert(TM == TN && NW % 2 == 0 && (NI & 1) == 0 && (TM / (NW / 2)) == 8 * NI, "half of the wavefronts load A, half B");
+    static_assert(MI % 2 == 0 && NJ % 2 == 0 && (ST & (ST - 1)) == 0 && KR * TM == 256, "blocks of 32 x 32; stages by mask");
+};
+
+// a value that every lane holds, in a scalar register
+__device__ __forceinline__ float uniform(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
+
+// two values (scaled) -> their hi terms and their lo terms, both rounded to nearest
+__device__ __forceinline__ void pair_words2(float a, float b, uint32_t &hi, uint32_t &lo)
+{
+    typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+    const _Float16 ha = (_Float16)a, hb = (_Float16)b;
+    hi = __builtin_bit_cast(uint32_t, (f16x2_t){ha, hb});
+    lo = __builtin_bit_cast(uint32_t, (f16x2_t){(_Float16)(a - (float)ha), (_Float16)(b - (float)hb)});
+}
+
+template <int WGM, int WGN, int MI, int NJ, int ST>
+__global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const FactorDev *__restrict__ fd, const FactorScal *__restrict__ fs,
                                                               const int *__restrict__ state, const uint2 *__restrict__ map, int total,
                                                               int op0, int op1, int k, int degree)
 {
-    constexpr int T = 64 * WT;
-    using Loader = PlaneLoader<8, T, T, 4>;
+    using SH = PairShape<WGM, WGN, MI, NJ, ST>;
+    constexpr int NW = SH::NW, NI = SH::NI, H = SH::H, TM = SH::TM, KR = SH::KR;
+    constexpr uint32_t STAGE = SH::STAGE, KROW = (uint32_t)TM * 4u;      // bytes of a row of a transposed slab
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+    typedef short s16x4_t __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(16) unsigned char plane_smem[];
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)plane_smem;
     const int all = op1 >= 0 ? 2 * total : total;
@@ -112,236 +157,449 @@ __global__ __launch_bounds__(256, 2) void pair_product_kernel(const FactorDev *_
     if (op != OP_X && S.tier != TIER_PAIR) return;
     const FactorDev &F = fd[f];
     const bool makes_e = op == OP_SQ || op == OP_SQ3 || op == OP_CUBE;
-    const int st = makes_e ? state[f] : state_after_test(F, S, state[f]);
+    const int st = __builtin_amdgcn_readfirstlane(makes_e ? state[f] : state_after_test(F, S, state[f]));
     if (st != ST_RUN && !(st == ST_LAST && (makes_e || op == OP_X))) return;
     const int ti = (int)(tile.y >> 16), tj = (int)(tile.y & 0xffffu);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
-    const int n = F.n, rowb = F.rowb, p = k & 1, row0 = ti * T, col0 = tj * T;
-    const char *A, *B, *O1 = nullptr, *O2 = nullptr;
-    char *C;
-    float sA, sB, s1 = 1.0f, s2 = 1.0f, sC;
-    if (op == OP_X) {
-        A = F.X[p]; B = F.P[degree == 1 ? 0 : 2]; C = F.X[p ^ 1];
-        sA = sC = S.x_scale; sB = degree == 1 ? PAIR_SCALE_M : PAIR_SCALE_E;
-    } else {
-        const RootOperands o = root_operands(op, degree == 1);
-        A = F.P[o.A]; B = F.P[o.B]; C = F.P[o.C];
-        sA = pair_scale_of(op, o.A); sB = pair_scale_of(op, o.B);
-        if (o.O1 >= 0) { O1 = F.P[o.O1]; s1 = pair_scale_of(op, o.O1); }
-        if (o.O2 >= 0) { O2 = F.P[o.O2]; s2 = pair_scale_of(op, o.O2); }
-        sC = pair_scale_of(op, o.C);
-    }
-    const RootProd pc = S.prod[op];
-    const float k1 = (float)(pc.own1 * (double)(sC / s1)), k2 = (float)(pc.own2 * (double)(sC / s2));
-    const float kg = (float)(pc.gam * (double)sC / ((double)sA * (double)sB));
+    // position of the wavefront in the tile; of eight, those that share a SIMD (w, w + 4) have about the same work together in
+    // a diagonal tile
+    const int wm = NW == 8 ? (0x20103132 >> (4 * wave)) & 0xf : wave / WGN, wn = NW == 8 ? (0xB8 >> wave) & 1 : wave % WGN;
+    const int n = F.n, rowb = F.rowb, p = k & 1, row0 = ti * TM, col0 = tj * TM, nk = plane_groups(n);
+    const RootOperands o = root_operands(op, degree == 1);
 
-    // the cross terms, 2^-11 of the leading ones, in sums of their own: a third of the roundings at full size (log-spaced
-    // spectrum, n = 1024, eps = 1e-6: error as above 5.2e-4 with one sum, 3.3e-4 with two; the time of a refresh + 1 %)
-    floatx16 acc[WT][WT], cross[WT][WT];
+    // ---- memory -> LDS: half of the wavefronts bring rows of A, half of B
+    const bool loads_b = wave >= NW / 2;
+    const char *src = op == OP_X ? (loads_b ? F.P[degree == 1 ? 0 : 2] : F.X[p]) : F.P[loads_b ? o.B : o.A];
+    const int panel = loads_b ? tj : ti, i0 = (wave % (NW / 2)) * NI;    // first of this wavefront's load instructions
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds, ldst = lds0 + (loads_b ? ST * STAGE : 0u) + (uint32_t)i0 * 1024u;
+    // direct: an instruction brings 8 rows, lane / 8 the row, lane % 8 the position of a 16-byte chunk (swizzle of plane_swz).
+    // Rows beyond the matrix read as zero through the bounds of the descriptor
+    const i32x4 rs_d = buffer_rsrc(src + (size_t)panel * TM * rowb, (uint32_t)min(n - panel * TM, TM) * (uint32_t)rowb);
+    const uint32_t lch0 = (uint32_t)((lane & 7) ^ (lane >> 4)) * 16u;
+    // transposed: an instruction brings KR rows of the TM columns of this panel; pieces of 32 bytes swizzled by row so that
+    // the 4 rows of a 16-lane group of a transposed read lie in distinct banks
+    const i32x4 rs_t = buffer_rsrc(src + (size_t)panel * TM * 4, (uint32_t)n * (uint32_t)rowb - (uint32_t)panel * TM * 4u);
+    const uint32_t tk = (uint32_t)(lane / (64 / KR));
+    const uint32_t off_d = (uint32_t)(i0 * 8 + (lane >> 3)) * (uint32_t)rowb + lch0;
+    const uint32_t off_t = (((uint32_t)(lane % (64 / KR)) * 16u) ^ ((tk | ((uint32_t)(i0 * KR) >> 1 & 4u)) << 5));
+    const uint32_t row_t = tk * (uint32_t)rowb;
+    const int direct_end = (panel + 1) * (TM / 32);            // slabs from here on are transposed
+    // loads v0 .. v0 + cnt - 1 of slab s (beyond the end: slab nk - 1 again, never read)
+    auto issue = [&](int s, int v0, int cnt) __attribute__((always_inline)) {
+        const int slab = min(s, nk - 1);
+        const uint32_t dst = ldst + ((uint32_t)s & (ST - 1)) * STAGE;
+        // all ones: direct.  Selected by masks, not branched on: a branch would cut the schedule of the products
+        uint32_t d = (uint32_t)__builtin_amdgcn_readfirstlane((slab - direct_end) >> 31);
+        asm("" : "+s"(d));
+        auto pick = [&](uint32_t x, uint32_t y) __attribute__((always_inline)) { return y ^ ((x ^ y) & d); };
+        i32x4 rs;
 #pragma unroll
-    for (int i = 0; i < WT; ++i)
+        for (int e = 0; e < 4; ++e) rs[e] = (int)pick((uint32_t)rs_d[e], (uint32_t)rs_t[e]);
+        uint32_t off = pick(off_d, off_t);
+        asm volatile("" : "+v"(off));                 // (the offsets of all loads are not worth registers)
+        const uint32_t first = pick((uint32_t)slab * 128u, (uint32_t)(slab * 32 + i0 * KR) * (uint32_t)rowb);
+        const uint32_t row_step = pick(8u, (uint32_t)KR) * (uint32_t)rowb;
 #pragma unroll
-        for (int j = 0; j < WT; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = cross[i][j][v] = 0.0f;
-
-    Loader ld;
-    ld.init(A, B, rowb, n, row0, col0, wave, lane);
-    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-    const int nk = plane_groups(n), last = nk - 1;
-    const int sw = plane_swz<8>(r);
-    const ASTERIA_LDS char *fa = lds + (wm * WT * 32 + r) * 128, *fb = lds + (T + wn * WT * 32 + r) * 128;
-    const int diag_d = ti == tj ? wm - wn : 1;        // < 0: above the diagonal, 0: on it
-    auto mma = [](u32x4 a, u32x4 b, floatx16 c) __attribute__((always_inline)) {
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(pl_f16x8, a), __builtin_bit_cast(pl_f16x8, b), c, 0, 0, 0);
-    };
-    auto compute = [&](uint32_t stage) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            u32x4 ah[WT], al[WT], bh[WT], bl[WT];
-            const int ch = ((s * 2 + h) ^ sw) * 16, cl = ((4 + s * 2 + h) ^ sw) * 16;
-#pragma unroll
-            for (int j = 0; j < WT; ++j) {
-                bh[j] = *(const ASTERIA_LDS u32x4 *)(fb + stage + j * 4096 + ch);
-                bl[j] = *(const ASTERIA_LDS u32x4 *)(fb + stage + j * 4096 + cl);
-            }
-#pragma unroll
-            for (int i = 0; i < WT; ++i) {
-                ah[i] = *(const ASTERIA_LDS u32x4 *)(fa + stage + i * 4096 + ch);
-                al[i] = *(const ASTERIA_LDS u32x4 *)(fa + stage + i * 4096 + cl);
-            }
-#pragma unroll
-            for (int i = 0; i < WT; ++i) {
-                const bool cut = WT == 2 && i == 0 && diag_d == 0;      // block (0, 1) of a wavefront on the diagonal
-#pragma unroll
-                for (int j = 0; j < WT; ++j) if (!(j == 1 && cut)) cross[i][j] = mma(al[i], bh[j], cross[i][j]);
-#pragma unroll
-                for (int j = 0; j < WT; ++j) if (!(j == 1 && cut)) cross[i][j] = mma(ah[i], bl[j], cross[i][j]);
-#pragma unroll
-                for (int j = 0; j < WT; ++j) if (!(j == 1 && cut)) acc[i][j] = mma(ah[i], bh[j], acc[i][j]);
-            }
+        for (int v = v0; v < v0 + cnt; ++v) {
+            const uint32_t kl = (uint32_t)v * KR, sw = pick((v & 1) * 64u, ((kl & 3u) | ((kl >> 1) & 4u)) << 5);
+            load_to_lds(rs, dst + v * 1024, (off ^ sw) + ((uint32_t)v * row_step + first) + (KR > 1 ? pick(0u, row_t) : 0u), 0u);
         }
     };
-    // The loads past the end repeat the last slab, so the number in flight is the same in every iteration.
 #pragma unroll
-    for (int q = 0; q < ST - 1; ++q) ld.issue(lds0 + q * Loader::STAGE, min(q, last));
-    uint32_t cur = 0, nxt = (ST - 1) * Loader::STAGE;
-    for (int kt = 0; kt < nk; ++kt) {
-        wait_lds_loads<Loader::NI *(ST - 2)>();
-        __builtin_amdgcn_s_barrier();                 // the slab has landed, and everyone is done with the one before
-        ld.issue(lds0 + nxt, min(kt + ST - 1, last));
-        if (diag_d >= 0) compute(cur);
-        cur = cur + Loader::STAGE == ST * Loader::STAGE ? 0u : cur + Loader::STAGE;
-        nxt = nxt + Loader::STAGE == ST * Loader::STAGE ? 0u : nxt + Loader::STAGE;
-    }
-    wait_lds_loads<0>();
-    __builtin_amdgcn_s_barrier();                     // LDS is free for the stores
+    for (int s = 0; s < ST - 1; ++s) issue(s, 0, NI);
+    issue(ST - 1, 0, H);
 
-    ASTERIA_LDS uint32_t *ws = (ASTERIA_LDS uint32_t *)(lds + wave * PLANE_SCRATCH_BYTES);
-    const bool to_user = op == OP_X && st == ST_LAST;
-    const bool first_x = k == 0 && (op == OP_SQ || op == OP_CUBE);    // X_1 = X_0 T_0, X_0 a multiple of I
-    const float inv_c = 1.0f / sC;
-    const float x1a = S.x1a, x1e = -S.x1s * inv_c, inv_x = 1.0f / S.x_scale;
-    ASTERIA_GLOBAL float *X = (ASTERIA_GLOBAL float *)F.Xout;
-    const int ldx = F.ldx;
-    // the test before the last update, by the product that completes E
-    const bool test = st == ST_LAST && S.q_limit > 0.0f && ((op == OP_SQ && degree == 2) || op == OP_CUBE);
-    const float q1 = S.q[1] / s1, q2 = S.q[2] / s2, q3 = S.q[3] * inv_c, q0 = S.q[0];
-    float rsum = 0.0f;
-    // X row-major: a block's base is uniform, beside a 32-bit offset of the lane
-    const uint32_t xo = (uint32_t)(4 * h) * (uint32_t)ldx + (uint32_t)r;
+    // ---- LDS -> registers -> products
+    const int a_end = (ti + 1) * (TM / 32), b_end = (tj + 1) * (TM / 32);
+    uint32_t fa_d, fb_d, fa_t, fb_t;
+    {
+        const int r16 = lane & 15, g16 = lane >> 4;
+        const uint32_t d = lds0 + (uint32_t)r16 * 128u + (uint32_t)((g16 ^ ((r16 >> 1) & 7)) * 16);
+        fa_d = d + (uint32_t)(wm * 16 * MI) * 128u; fb_d = d + ST * STAGE + (uint32_t)(wn * 16 * NJ) * 128u;
+        // lane 4 e + q of a 16-lane group supplies the address of rows 4 q .. of k = 8 g16 + e
+        const int e = r16 >> 2;
+        const uint32_t t = lds0 + (uint32_t)(8 * g16 + e) * KROW + (uint32_t)((e | ((g16 & 1) << 2)) << 5) + (uint32_t)(r16 & 3) * 8u;
+        const uint32_t ga = (uint32_t)(wm * MI / 2), gb = (uint32_t)(wn * NJ / 2);     // first group of 32 rows; its low bit is swizzled
+        fa_t = (t ^ ((ga & 1u) << 7)) + (ga >> 1) * 256u; fb_t = (t ^ ((gb & 1u) << 7)) + (gb >> 1) * 256u + ST * STAGE;
+    }
+    // 16 rows of an operand, hi (term 0) or lo: 8 consecutive k per lane.  x: 16-row block of the wavefront
+    auto frag_d = [](uint32_t base, int x, int term) __attribute__((always_inline)) {
+        return *(const ASTERIA_LDS u32x4 *)(uintptr_t)((term ? base ^ 64u : base) + x * 2048);
+    };
+    auto frag_t = [](uint32_t base, int x, int term) __attribute__((always_inline)) {
+        // piece of 32 bytes 4 (x / 2) + 2 term + x % 2, its low three bits swizzled
+        const int g = 4 * (x >> 1) + 2 * term + (x & 1);
+        const uint32_t a = (base ^ (uint32_t)((g & 7) << 5)) + (uint32_t)((g >> 3) * 256);
+        const u32x2_t lo = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ASTERIA_LDS s16x4_t *)(uintptr_t)a));
+        const u32x2_t hi = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ASTERIA_LDS s16x4_t *)(uintptr_t)(a + 4 * KROW)));
+        return (u32x4){lo[0], lo[1], hi[0], hi[1]};
+    };
+    // D = B-rows x A-rows: a lane then holds 4 consecutive columns of one row of C
+    auto mma = [](u32x4 a, u32x4 b, floatx4 c) __attribute__((always_inline)) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(pl_f16x8, b), __builtin_bit_cast(pl_f16x8, a), c, 0, 0, 0);
+    };
+    wait_lds_loads<(ST - 2) * NI + H>();
+    __builtin_amdgcn_s_barrier();
+
+    // The tile for a wavefront whose first JN column blocks are wanted.  A body per width instead of branches in the loop: the
+    // accumulators stay in their registers
+    auto body = [&](auto jnc) __attribute__((always_inline)) {
+        constexpr int JN = decltype(jnc)::value, JA = JN ? JN : 1;
+        floatx4 acc[MI][JA];
 #pragma unroll
-    for (int i = 0; i < WT; ++i) {
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < WT; ++j) {
-            const int br = row0 + (wm * WT + i) * 32, bc = col0 + (wn * WT + j) * 32;
-            if (br < bc || br >= n || bc >= n) continue;
-            const bool diag = br == bc;
-            acc[i][j] += cross[i][j];
-            float val[16], q[16];
-            if (O1) {
-                load_pair_block(O1, rowb, n, br, bc, lane, val);
-                if (test) {
+            for (int j = 0; j < JA; ++j) acc[i][j] = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
+        const floatx4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        u32x4 ah[MI], al[MI], b[2][2];
+        uint32_t so = 0;                              // stage of the slab being read
+        auto read_a = [&](u32x4 (&d)[MI], int term, int kt) __attribute__((always_inline)) {
+            if (kt < a_end) {
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) q[v] = q1 * val[v];
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) val[v] = k1 * val[v] + kg * acc[i][j][v];
-            } else if (op == OP_X) {
-                if (!diag && br + 32 <= n) {
-                    const ASTERIA_GLOBAL float *x = X + (size_t)br * ldx + bc;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) val[v] = (x + (size_t)(8 * (v >> 2) + (v & 3)) * ldx)[xo];
-                } else {
-                    const int col = bc + r;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
-                        val[v] = row < n && col < n && row >= col ? X[(size_t)row * ldx + col] : 0.0f;
-                    }
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) val[v] = k1 * val[v] + kg * acc[i][j][v];
+                for (int i = 0; i < MI; ++i) d[i] = frag_d(fa_d + so, i, term);
             } else {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) val[v] = kg * acc[i][j][v];
+                for (int i = 0; i < MI; ++i) d[i] = frag_t(fa_t + so, i, term);
             }
-            if (O2) {
-                float o[16];
-                load_pair_block(O2, rowb, n, br, bc, lane, o);
+        };
+        auto read_b0 = [&](u32x4 (&d)[2], int kt) __attribute__((always_inline)) {
+            if (kt < b_end) { d[0] = frag_d(fb_d + so, 0, 0); d[1] = frag_d(fb_d + so, 0, 1); }
+            else { d[0] = frag_t(fb_t + so, 0, 0); d[1] = frag_t(fb_t + so, 0, 1); }
+        };
+        // the next slab has landed and everyone has read this one
+        auto turn = [&](int kt) __attribute__((always_inline)) {
+            wait_lds_loads<(ST - 2) * NI>();
+            __builtin_amdgcn_s_barrier();
+            so = ((uint32_t)(kt + 1) & (ST - 1)) * STAGE;
+        };
+        // AT, BT: the slab's rows of A, of B come from columns.  The next slab is read as if it were of the same kind: whoever
+        // changes the kind reads again
+        auto slab = [&](int kt, auto atc, auto btc) __attribute__((always_inline)) {
+            constexpr bool AT = decltype(atc)::value, BT = decltype(btc)::value;
+            auto next_a = [&](u32x4 (&d)[MI], int term) __attribute__((always_inline)) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) val[v] += k2 * o[v];
-                if (test) {
+                for (int i = 0; i < MI; ++i) d[i] = AT ? frag_t(fa_t + so, i, term) : frag_d(fa_d + so, i, term);
+            };
+            // the sums of a column block are taken while the next one is multiplied
+            floatx4 t[2][MI];
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) q[v] += q2 * o[v];
+            for (int j = 0; j < JN; ++j) {
+                const int q = j & 1;
+                const bool end = j + 1 == JN;
+                if (!end) {
+                    b[q ^ 1][0] = BT ? frag_t(fb_t + so, j + 1, 0) : frag_d(fb_d + so, j + 1, 0);
+                    b[q ^ 1][1] = BT ? frag_t(fb_t + so, j + 1, 1) : frag_d(fb_d + so, j + 1, 1);
+                } else {
+                    turn(kt);
+                    b[q ^ 1][0] = BT ? frag_t(fb_t + so, 0, 0) : frag_d(fb_d + so, 0, 0);
+                    b[q ^ 1][1] = BT ? frag_t(fb_t + so, 0, 1) : frag_d(fb_d + so, 0, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int i = 0; i < MI; ++i) t[q][i] = mma(al[i], b[q][0], zero);
+                if (end) { __builtin_amdgcn_sched_barrier(0); next_a(al, 1); issue(kt + ST, 0, H / 2); }
+                if (H < NI && j == 0) { __builtin_amdgcn_sched_barrier(0); issue(kt + ST - 1, H, (NI - H) / 2); }
+#pragma unroll
+                for (int i = 0; i < MI; ++i) t[q][i] = mma(ah[i], b[q][1], t[q][i]);
+                if (end) { __builtin_amdgcn_sched_barrier(0); issue(kt + ST, H / 2, H - H / 2); }
+                if (H < NI && j == 0) { __builtin_amdgcn_sched_barrier(0); issue(kt + ST - 1, H + (NI - H) / 2, NI - H - (NI - H) / 2); }
+#pragma unroll
+                for (int i = 0; i < MI; ++i) t[q][i] = mma(ah[i], b[q][0], t[q][i]);
+                if (j > 0)
+#pragma unroll
+                    for (int i = 0; i < MI; ++i) acc[i][j - 1] += t[q ^ 1][i];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            next_a(ah, 0);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) acc[i][JA - 1] += t[(JA - 1) & 1][i];
+        };
+        if constexpr (JN > 0) {
+            auto read_all = [&](int kt) __attribute__((always_inline)) { read_a(al, 1, kt); read_a(ah, 0, kt); read_b0(b[0], kt); };
+            read_all(0);
+            int kt = 0;
+            for (const int end = min(b_end, nk); kt < end; ++kt) slab(kt, std::false_type{}, std::false_type{});
+            if (JN == NJ && a_end > b_end) {           // (a narrower body belongs to a diagonal tile)
+                read_all(kt);
+                for (const int end = min(a_end, nk); kt < end; ++kt) slab(kt, std::false_type{}, std::true_type{});
+            }
+            if (kt < nk) {
+                read_all(kt);
+                for (; kt < nk; ++kt) slab(kt, std::true_type{}, std::true_type{});
+            }
+        } else {
+            for (int kt = 0; kt < nk; ++kt) {
+                if (H < NI) issue(kt + ST - 1, H, NI - H);
+                turn(kt);
+                issue(kt + ST, 0, H);
+            }
+        }
+
+        // ---- the block's value and its planes; in a diagonal tile its mirror image too
+        const char *O1 = nullptr, *O2 = nullptr;
+        char *C;
+        float sA, sB, s1 = 1.0f, s2 = 1.0f, sC;
+        if (op == OP_X) {
+            C = F.X[p ^ 1];
+            sA = sC = S.x_scale; sB = degree == 1 ? PAIR_SCALE_M : PAIR_SCALE_E;
+        } else {
+            C = F.P[o.C];
+            sA = pair_scale_of(op, o.A); sB = pair_scale_of(op, o.B);
+            if (o.O1 >= 0) { O1 = F.P[o.O1]; s1 = pair_scale_of(op, o.O1); }
+            if (o.O2 >= 0) { O2 = F.P[o.O2]; s2 = pair_scale_of(op, o.O2); }
+            sC = pair_scale_of(op, o.C);
+        }
+        const RootProd pc = S.prod[op];
+        const float k1 = uniform((float)(pc.own1 * (double)(sC / s1))), k2 = uniform((float)(pc.own2 * (double)(sC / s2)));
+        const float kg = uniform((float)(pc.gam * (double)sC / ((double)sA * (double)sB)));
+        const bool to_user = op == OP_X && st == ST_LAST;
+        const bool first_x = k == 0 && (op == OP_SQ || op == OP_CUBE);    // X_1 = X_0 T_0, X_0 a multiple of I
+        const float inv_c = uniform(1.0f / sC);
+        const float x1a = S.x1a, x1e = uniform(-S.x1s * inv_c), inv_x = uniform(1.0f / S.x_scale);
+        ASTERIA_GLOBAL float *X = (ASTERIA_GLOBAL float *)F.Xout;
+        const int ldx = F.ldx;
+        const bool xvec = (ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(F.Xout) & 15u) == 0;
+        // the test before the last update, by the product that completes E
+        const bool test = st == ST_LAST && S.q_limit > 0.0f && ((op == OP_SQ && degree == 2) || op == OP_CUBE);
+        const float q1 = uniform(S.q[1] / s1), q2 = uniform(S.q[2] / s2), q3 = uniform(S.q[3] * inv_c), q0 = S.q[0];
+        float rsum = 0.0f;
+        // Element v = 4 (2 u + w) + e of a 32 x 32 block: row 16 u + r16, column 16 w + 4 g16 + e.  (The lane's part of every
+        // address is made anew for every block, not kept through the K loop.)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        int r16 = ln & 15, g16 = ln >> 4;
+        ASTERIA_LDS char *ws = lds + SH::SCRATCH + wave * 4096;
+        auto row_of = [&](int br, int v) { return br + 16 * (v >> 3) + r16; };
+        auto col_of = [&](int bc, int v) { return bc + 16 * ((v >> 2) & 1) + 4 * g16 + (v & 3); };
+        // linear term of a block: 4 columns of a row, hi in [0 .. 1], lo in [2 .. 3]
+        auto load_own = [&](const char *O, int br, int bc, uint32_t (&raw)[16]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const char *q = O + (size_t)min(br + 16 * u + r16, n - 1) * rowb + (min(bc, n - 1) >> 5) * 128 + g16 * 8;
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    const u32x2_t a = *(const ASTERIA_GLOBAL u32x2_t *)(q + w * 32), c = *(const ASTERIA_GLOBAL u32x2_t *)(q + w * 32 + 64);
+                    uint32_t *d = &raw[4 * (2 * u + w)];
+                    d[0] = a[0]; d[1] = a[1]; d[2] = c[0]; d[3] = c[1];
                 }
             }
-            const int col = bc + r;
-            if (op == OP_M) {
+        };
+        auto own_value = [&](const uint32_t (&raw)[16], int v) __attribute__((always_inline)) {
+            const uint32_t *d = &raw[v & ~3];
+            const f16x4_t a = __builtin_bit_cast(f16x4_t, (u32x2_t){d[0], d[1]}), c = __builtin_bit_cast(f16x4_t, (u32x2_t){d[2], d[3]});
+            return (float)a[v & 3] + (float)c[v & 3];
+        };
+        // fp32 X: its lower triangle until the last update, which completes the caller's matrix
+        auto load_x = [&](int br, int bc, uint32_t (&raw)[16]) __attribute__((always_inline)) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
-                    const float er = val[v] * inv_c - (row == col ? 1.0f : 0.0f);
-                    if (row < n && col < n && row >= col) rsum += row == col ? er * er : 2.0f * er * er;
+            for (int uw = 0; uw < 4; ++uw) {
+                const int row = row_of(br, 4 * uw), col = col_of(bc, 4 * uw);
+                const ASTERIA_GLOBAL float *x = X + (size_t)min(row, n - 1) * ldx + col;
+                if (br > bc && xvec) {
+                    const u32x4 t = *(const ASTERIA_GLOBAL u32x4 *)x;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) raw[4 * uw + e] = t[e];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) raw[4 * uw + e] = row < n && row >= col + e ? __builtin_bit_cast(uint32_t, x[e]) : 0u;
                 }
             }
+        };
+        auto store_x = [&](int br, int bc, const float (&x)[16], float c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int uw = 0; uw < 4; ++uw) {
+                const int row = row_of(br, 4 * uw), col = col_of(bc, 4 * uw);
+                ASTERIA_GLOBAL float *d = X + (size_t)row * ldx + col;
+                if (row >= n) continue;
+                if (br > bc && xvec) *(ASTERIA_GLOBAL floatx4 *)d = (floatx4){x[4 * uw] * c, x[4 * uw + 1] * c, x[4 * uw + 2] * c, x[4 * uw + 3] * c};
+                else
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (row >= col + e) d[e] = x[4 * uw + e] * c;
+            }
+        };
+        // Planes of a block through the scratch, one row of the block per 128 bytes: [32 hi][32 lo], chunks swizzled by row.  On the
+        // diagonal the upper triangle is taken from the lower one.  Elements beyond n are zero
+        auto store_block = [&](char *D, int br, int bc, const float (&val)[16]) __attribute__((always_inline)) {
+            const bool diag = br == bc;
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    const float *q = &val[4 * (2 * u + w)];
+                    uint32_t h0, h1, l0, l1;
+                    pair_words2(q[0], q[1], h0, l0);
+                    pair_words2(q[2], q[3], h1, l1);
+                    const int r = 16 * u + r16;
+                    if (!diag) {
+                        ASTERIA_LDS char *d = ws + r * 128 + (g16 & 1) * 8;
+                        const int ch = 2 * w + (g16 >> 1);
+                        *(ASTERIA_LDS u32x2_t *)(d + (ch ^ (r & 7)) * 16) = (u32x2_t){h0, h1};
+                        *(ASTERIA_LDS u32x2_t *)(d + ((4 + ch) ^ (r & 7)) * 16) = (u32x2_t){l0, l1};
+                    } else {
+                        const uint32_t hw[2] = {h0, h1}, lw[2] = {l0, l1};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int c = 16 * w + 4 * g16 + e;
+                            if (r < c) continue;
+                            const uint16_t hi = (uint16_t)(hw[e >> 1] >> (16 * (e & 1))), lo = (uint16_t)(lw[e >> 1] >> (16 * (e & 1)));
+                            *(ASTERIA_LDS uint16_t *)(ws + c * 128 + ((r >> 3) ^ (c & 7)) * 16 + (r & 7) * 2) = hi;
+                            *(ASTERIA_LDS uint16_t *)(ws + c * 128 + ((4 + (r >> 3)) ^ (c & 7)) * 16 + (r & 7) * 2) = lo;
+                            *(ASTERIA_LDS uint16_t *)(ws + r * 128 + ((c >> 3) ^ (r & 7)) * 16 + (c & 7) * 2) = hi;
+                            *(ASTERIA_LDS uint16_t *)(ws + r * 128 + ((4 + (c >> 3)) ^ (r & 7)) * 16 + (c & 7) * 2) = lo;
+                        }
+                    }
+                }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {                   // whole lines of 8 rows
+                const int r = q * 8 + (ln >> 3), ch = ln & 7;
+                const u32x4 t = *(const ASTERIA_LDS u32x4 *)(ws + r * 128 + ((ch ^ (r & 7)) * 16));
+                if (br + r < n) *(ASTERIA_GLOBAL u32x4 *)(D + (size_t)(br + r) * rowb + (bc >> 5) * 128 + ch * 16) = t;
+            }
+            if (ti == tj && !diag) {
+                // columns 16 (q & 1) .. of the block, hi or lo, as rows of the mirror image: a group of 16 lanes brings 8 rows of
+                // the block; lane 4 e + i of it supplies the address of columns 4 i .. of row e, lane j receives column j
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int rh = q & 1, term = q >> 1;
+                    u32x2_t t[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int r = 4 * (2 * g16 + u) + (r16 >> 2), ch = term * 4 + rh * 2 + ((r16 & 3) >> 1);
+                        t[u] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                   (ASTERIA_LDS s16x4_t *)(ws + r * 128 + ((ch ^ (r & 7)) * 16) + (r16 & 1) * 8)));
+                    }
+                    const int c = bc + 16 * rh + r16;
+                    if (c < n) *(ASTERIA_GLOBAL u32x4 *)(D + (size_t)c * rowb + (br >> 5) * 128 + term * 64 + g16 * 16) =
+                        (u32x4){t[0][0], t[0][1], t[1][0], t[1][1]};
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        };
+        constexpr int JB = JA / 2 ? JA / 2 : 1, NB = (MI / 2) * (JN / 2);
+        uint32_t ahead[16];                           // linear term of the next block
+        auto prefetch = [&](int q) __attribute__((always_inline)) {
+            const int br = row0 + wm * 16 * MI + (q / JB) * 32, bc = col0 + wn * 16 * NJ + (q % JB) * 32;
+            if (O1) load_own(O1, br, bc, ahead);
+            else if (op == OP_X) load_x(br, bc, ahead);
+        };
+        if constexpr (NB > 0) prefetch(0);
+        // one copy of the code for all blocks: only taking the sums out of their registers differs
+#pragma unroll 1
+        for (int q = 0; q < NB; ++q) {
+            const int br = row0 + wm * 16 * MI + (q / JB) * 32, bc = col0 + wn * 16 * NJ + (q % JB) * 32;
+            asm volatile("" : "+v"(ln));
+            r16 = ln & 15; g16 = ln >> 4;
+            uint32_t raw[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) raw[v] = ahead[v];
+            if (O2) load_own(O2, br, bc, ahead);      // (a second linear term takes the place of the block ahead)
+            else if (q + 1 < NB) prefetch(q + 1);
+            if (br < bc || br >= n || bc >= n) {
+                if (O2 && q + 1 < NB) prefetch(q + 1);
+                continue;
+            }
+            float val[16];
+#pragma unroll
+            for (int z = 0; z < NB; ++z)
+                if (q == z) {
+                    asm volatile("");                 // a branch, not selects
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) val[v] = kg * acc[2 * (z / JB) + (v >> 3)][2 * (z % JB) + ((v >> 2) & 1)][v & 3];
+                }
+            const bool diag = br == bc, inside = !diag && br + 32 <= n;
+            // sums over the symmetric matrix: an element below the diagonal counts twice
+            auto add_sum = [&](int v, float x) __attribute__((always_inline)) {
+                const int row = row_of(br, v), col = col_of(bc, v);
+                if (inside) rsum += 2.0f * x * x;
+                else if (row < n && row >= col) rsum += row == col ? x * x : 2.0f * x * x;
+            };
+            auto on_diag = [&](int v) { return row_of(br, v) == col_of(bc, v); };
             if (test) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
-                    const float x = q[v] + q3 * val[v] + (row == col ? q0 : 0.0f);
-                    if (row < n && col < n && row >= col) rsum += row == col ? x * x : 2.0f * x * x;
+                    const float o1 = own_value(raw, v), o2 = O2 ? own_value(ahead, v) : 0.0f;
+                    val[v] += k1 * o1 + (O2 ? k2 * o2 : 0.0f);
+                    add_sum(v, q1 * o1 + (O2 ? q2 * o2 : 0.0f) + q3 * val[v] + (on_diag(v) ? q0 : 0.0f));
                 }
-            }
-            if (op == OP_X) {
-                // X in fp32: its lower triangle until the last update, which completes the caller's matrix
-                const bool vec = (ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(F.Xout) & 15u) == 0;
-                if (!diag && br + 32 <= n) {
-                    ASTERIA_GLOBAL float *x = X + (size_t)br * ldx + bc;
+            } else if (O1) {
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) (x + (size_t)(8 * (v >> 2) + (v & 3)) * ldx)[xo] = val[v] * inv_c;
-                } else {
+                for (int v = 0; v < 16; ++v) val[v] += k1 * own_value(raw, v);
+                if (O2)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) val[v] += k2 * own_value(ahead, v);
+            } else if (op == OP_X) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) val[v] += k1 * __builtin_bit_cast(float, raw[v]);
+            }
+            if (O2 && q + 1 < NB) prefetch(q + 1);
+            if (op == OP_M)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) add_sum(v, val[v] * inv_c - (on_diag(v) ? 1.0f : 0.0f));
+            if (op == OP_X) {
+                store_x(br, bc, val, inv_c);
+                if (to_user) {
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
-                        if (row < n && col < n && row >= col) X[(size_t)row * ldx + col] = val[v] * inv_c;
+                        const int row = row_of(br, v), col = col_of(bc, v);
+                        if (row < n && row > col) X[(size_t)col * ldx + row] = val[v] * inv_c;
                     }
+                    continue;
                 }
-                if (to_user && col < n) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int rb = br + 8 * g + 4 * h;
-                        floatx4 t;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) t[e] = val[4 * g + e] * inv_c;
-                        if (!diag && vec && rb + 4 <= n) *(ASTERIA_GLOBAL floatx4 *)(X + (size_t)col * ldx + rb) = t;
-                        else
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (rb + e < n && (!diag || rb + e > col)) X[(size_t)col * ldx + rb + e] = t[e];
-                    }
-                }
-                if (to_user) continue;
             }
-            uint32_t wd[16];
+            if (br + 32 > n) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
-                wd[v] = (row < n && col < n) ? pair_word(val[v]) : 0u;
+                for (int v = 0; v < 16; ++v)
+                    if (row_of(br, v) >= n || col_of(bc, v) >= n) val[v] = 0.0f;
             }
-            store_pair_block(C, rowb, n, br, bc, wd, lane, ws);
+            store_block(C, br, bc, val);
             if (first_x) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int row = br + 8 * (v >> 2) + 4 * h + (v & 3);
-                    const float x = x1e * val[v] + (row == col ? x1a : 0.0f);
-                    wd[v] = (row < n && col < n) ? pair_word(x) : 0u;
-                    if (row < n && col < n && row >= col) X[(size_t)row * ldx + col] = x * inv_x;
+                    const int row = row_of(br, v), col = col_of(bc, v);
+                    val[v] = x1e * val[v] + (row == col && row < n ? x1a : 0.0f);
                 }
-                store_pair_block(F.X[1], rowb, n, br, bc, wd, lane, ws);
+                store_x(br, bc, val, inv_x);
+                store_block(F.X[1], br, bc, val);
             }
         }
-    }
-    if (op == OP_M || test) {
-        __syncthreads();
-        store_partial(rsum, reinterpret_cast<float *>(plane_smem), (test ? F.qpart : F.partial) + ti * (ti + 1) / 2 + tj, lane, wave, tid, 4);
-    }
+        if (op == OP_M || test) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) rsum += __shfl_xor(rsum, off, 64);
+            if (lane == 0) *(ASTERIA_LDS float *)ws = rsum;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            if (tid == 0) {
+                float sum = 0.0f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) sum += *(const ASTERIA_LDS float *)(lds + SH::SCRATCH + w * 4096);
+                (test ? F.qpart : F.partial)[ti * (ti + 1) / 2 + tj] = sum;
+            }
+        }
+    };
+    // column blocks of this wavefront with something on or below the diagonal and inside the matrix
+    const int rw = row0 + wm * 16 * MI, cw = col0 + wn * 16 * NJ;
+    const int c = rw >= n ? 0 : min(ti == tj ? rw + 16 * MI : n, n) - cw;
+    if (c <= 0) body(std::integral_constant<int, 0>{});
+    else if (NJ == 8 && c <= 64) body(std::integral_constant<int, NJ == 8 ? 4 : NJ>{});
+    else body(std::integral_constant<int, NJ>{});
+    wait_lds_loads<0>();                              // nothing may land in LDS that is no longer this workgroup's
 }
 
-template <int WT, int ST>
+template <int WGM, int WGN, int MI, int NJ, int ST>
 inline hipError_t launch_pair_product(const FactorDev *fd, const FactorScal *fs, const int *state, const uint2 *map, int total,
                                       int op0, int op1, int k, int degree, hipStream_t stream)
 {
     if (total <= 0) return hipSuccess;
-    constexpr size_t stage = ST * (size_t)PlaneLoader<8, 64 * WT, 64 * WT, 4>::STAGE, epi = 4 * (size_t)PLANE_SCRATCH_BYTES;
-    constexpr size_t lds = stage > epi ? stage : epi;
-    auto kern = pair_product_kernel<WT, ST>;
+    using SH = PairShape<WGM, WGN, MI, NJ, ST>;
+    auto kern = pair_product_kernel<WGM, WGN, MI, NJ, ST>;
     static bool configured[MAX_DEVICES] = {};
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured); e != hipSuccess) return e;
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), SH::LDS, configured); e != hipSuccess) return e;
     const int all = op1 >= 0 ? 2 * total : total, per = (all + NUM_XCD - 1) / NUM_XCD;
     profile_begin(224, stream);
-    hipLaunchKernelGGL(kern, dim3(per * NUM_XCD), dim3(256), lds, stream, fd, fs, state, map, total, op0, op1, k, degree);
+    hipLaunchKernelGGL(kern, dim3(per * NUM_XCD), dim3(64 * SH::NW), SH::LDS, stream, fd, fs, state, map, total, op0, op1, k, degree);
     profile_end(stream);
     return hipGetLastError();
 }

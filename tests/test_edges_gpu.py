@@ -38,6 +38,7 @@ def _root_error(A, X, eps):
     [513, 640],                                                 # one launch per step of the recurrence
     [130] * 190 + [97, 128, 256],                               # 128-wide tiles
     [514] * 192,                                                # a batch whose recurrences run one workgroup each
+    [761] * 118 + [33, 520, 768, 770],                          # 256-wide tiles: remainders of 249, 8 and 2, transposed panels
 ])
 def test_roots_at_the_edges(kind, eps, sizes):
     made = {}
