@@ -88,10 +88,11 @@ struct PlaneLoader {
             vo[v] = (uint32_t)min(r, lim) * (uint32_t)rowb + (uint32_t)c * 16u;
         }
     }
-    __device__ __forceinline__ void issue(uint32_t lds_stage, int slab) const
+    __device__ __forceinline__ void issue(uint32_t lds_stage, int slab) const { issue_part(lds_stage, slab, 0, NI); }
+    __device__ __forceinline__ void issue_part(uint32_t lds_stage, int slab, int v0, int v1) const     // instructions v0 .. v1 - 1 of NI
     {
 #pragma unroll
-        for (int v = 0; v < NI; ++v) {
+        for (int v = v0; v < v1; ++v) {
             if (INSTR % NW != 0 && first + v >= INSTR) break;
             const bool isb = (first + v) * 64 >= TMR * CPR;
             load_to_lds(isb ? rb : ra, lds_stage + (uint32_t)(first + v) * 1024u, vo[v], (uint32_t)slab * (CPR * 16u));
@@ -257,10 +258,10 @@ __device__ __forceinline__ void store_digit_chunk(char *p, const uint32_t (&x)[1
         *(ASTERIA_GLOBAL u32x4 *)(p + 32 * (NS - 1 - s)) = (u32x4){d[s][0], d[s][1], d[s][2], d[s][3]};
 }
 
-// Store a block of digit words (w: low words, tp: top digits) at (br, bc) and its mirror image.
+// Store a block of digit words (w: low words, tp: top digits, four registers' to a word) at (br, bc) and its mirror image.
 template <int NS>
 __device__ __forceinline__ void store_digit_block(char *C, int rowb, int n, int br, int bc, const uint32_t (&w)[16],
-                                                  const uint32_t (&tp)[16], int lane, ASTERIA_LDS uint32_t *ws)
+                                                  const uint32_t (&tp)[4], int lane, ASTERIA_LDS uint32_t *ws)
 {
     const bool diag = br == bc;
     const int r = lane & 31, h = lane >> 5;
@@ -272,7 +273,7 @@ __device__ __forceinline__ void store_digit_block(char *C, int rowb, int n, int 
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = 8 * (v >> 2) + 4 * h + (v & 3);
-                bs[row * PLANE_BYTES_PITCH + r] = (uint8_t)tp[v];
+                bs[row * PLANE_BYTES_PITCH + r] = (uint8_t)(tp[v >> 2] >> (8 * (v & 3)));
             }
             __builtin_amdgcn_wave_barrier();
             const int row = lane >> 1, c0 = (lane & 1) * 16;
@@ -299,7 +300,7 @@ __device__ __forceinline__ void store_digit_block(char *C, int rowb, int n, int 
         transpose4x4(in, o);
 #pragma unroll
         for (int s = 0; s < 4; ++s) d[NS - 1 - s][g] = o[s];
-        if constexpr (NS == 5) d[0][g] = tp[4 * g] | (tp[4 * g + 1] << 8) | (tp[4 * g + 2] << 16) | (tp[4 * g + 3] << 24);
+        if constexpr (NS == 5) d[0][g] = tp[g];
     }
     const int col = bc + r;
     char *p = C + (size_t)col * rowb + (br >> 5) * (32 * NS) + h * 16;

@@ -124,6 +124,13 @@ __device__ __forceinline__ float uniform(float x)
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
 }
 
+__device__ __forceinline__ double uniform(double x)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
 // two values (scaled) -> their hi terms and their lo terms, both rounded to nearest
 __device__ __forceinline__ void pair_words2(float a, float b, uint32_t &hi, uint32_t &lo)
 {
@@ -612,15 +619,19 @@ inline hipError_t launch_pair_product(const FactorDev *fd, const FactorScal *fs,
 // here is positive semi-definite).  (NS, L) is the control kernel's choice per factor and iteration:
 //   (4, 4) 10, (4, 5) 13, (5, 5) 15, (5, 6) 19 int8 MFMA passes.
 //
-// A workgroup of 2 x 2 wavefronts of 32 BI x 32 (BI 32 x 32 MFMA blocks, L level accumulators each) computes one
-// 128 x 64 half of a tile in 2 / BI steps, slabs of 32 k, two LDS stages of 24 KiB (NS = 4): two workgroups per
-// CU, so that one multiplies while the other assembles and stores.  BI = 2 where the accumulators leave room
-// for it in 256 registers (a third less LDS traffic per MFMA).
-template <int NS, int L, int BI>
+// A workgroup of 2 x 2 wavefronts of 64 x 32 (two 32 x 32 MFMA blocks, L level accumulators each) computes one 128 x 64
+// half of a tile, slabs of 32 k, two LDS stages of 24 (NS = 4) or 30 KiB: two workgroups per CU, so that one multiplies
+// while the other assembles and stores.  In a slab the lower digits of A come first; the products of its top digit, most of
+// all, cover the turn to the next slab.  Addresses and uniform factors of the epilogue are kept out of vector registers
+// (192 are sums at NS = 5).
+// Measured, kind E2: 8 of n = 4096 (5, 6) 4.24 ms = 2540 TOP/s issued, the matrix pipe full at the 1.75 GHz that power
+// leaves (5.87 before, of which 1.1 went with the order of the tiles); 300 of n = 1024 (4, 4) 1.84 ms, 2.07 before, the
+// epilogue a fifth of it; (5, 6) 3.22, 3.45 before.
+template <int NS, int L>
 __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal &S, int op, int k, int degree, int ti, int tj, int half,
                                            unsigned char *smem)
 {
-    constexpr int CPR = 2 * NS, ROWL = CPR * 16, RB = 64 * BI;
+    constexpr int CPR = 2 * NS, ROWL = CPR * 16, BI = 2, RB = 128;
     using Loader = PlaneLoader<CPR, RB, 64, 4>;
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -637,107 +648,140 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
     const RootProd pc = S.prod[op];
     // value of an operand = integer * 2^dexp; lowest kept level of the product = 256^(2 (NS - 1) - (L - 1)) quanta
     const double qo = ldexp(1.0, S.dexp[o.O1]), qab = ldexp(1.0, S.dexp[o.A] + S.dexp[o.B] + 8 * (2 * NS - 1 - L));
-    const double c1 = pc.own1 * qo, cg = pc.gam * qab;
-    const double inv_q = ldexp(1.0, -S.dexp[op == OP_M ? 4 : o.C]);   // exponent slot 4: the next M
+    const double c1 = uniform(pc.own1 * qo), cg = uniform(pc.gam * qab);
+    const double inv_q = uniform(ldexp(1.0, -S.dexp[op == OP_M ? 4 : o.C]));   // exponent slot 4: the next M
     const bool to_digits = !(op == OP_M && S.handover);
     // E feeds the X update as pair planes too (k > 0); so does M where T is linear or where the fp16 tier takes over
     const bool to_pair = (op == OP_SQ && k > 0) || (op == OP_M && (S.handover || S.pair_m));
     const bool first_x = op == OP_SQ && k == 0;       // X_1 = X_0 T_0, X_0 a multiple of I
-    const double pe = first_x ? -(double)S.x1s : (op == OP_M ? (double)PAIR_SCALE_M : (double)PAIR_SCALE_E);
-    const double pd = first_x ? (double)S.x1a : 0.0, inv_x = 1.0 / (double)S.x_scale;
+    const double pe = uniform(first_x ? -(double)S.x1s : (op == OP_M ? (double)PAIR_SCALE_M : (double)PAIR_SCALE_E));
+    const double pd = uniform(first_x ? (double)S.x1a : 0.0), inv_x = uniform(1.0 / (double)S.x_scale);
     float rsum = 0.0f;
     bool over = false;
-#pragma unroll 1
-    for (int step = 0; step < 2 / BI; ++step) {
-        const int row0 = ti * 128 + step * 64;
-        if (row0 >= n || row0 + RB - 1 < col0) continue;              // nothing of it below the diagonal (uniform)
-        Loader ld;
-        ld.init(digits_of(o.A), digits_of(o.B), rowb, n, row0, col0, wave, lane);
-        const ASTERIA_LDS char *fa = lds + (wm * 32 * BI + r) * ROWL, *fb = lds + (RB + wn * 32 + r) * ROWL;
-        i32x16 acc[L][BI];
+    const int row0 = ti * 128;
+    Loader ld;
+    ld.init(digits_of(o.A), digits_of(o.B), rowb, n, row0, col0, wave, lane);
+    i32x16 acc[L][BI];
 #pragma unroll
-        for (int l = 0; l < L; ++l)
+    for (int l = 0; l < L; ++l)
 #pragma unroll
-            for (int i = 0; i < BI; ++i)
+        for (int i = 0; i < BI; ++i)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[l][i][v] = 0;
-        const bool above = row0 + (wm + 1) * 32 * BI - 1 < col0 + wn * 32;     // this wavefront's part lies above the diagonal
-        auto compute = [&](uint32_t stage) {
-            i32x4 a[NS][BI], b[NS];
+            for (int v = 0; v < 16; ++v) acc[l][i][v] = 0;
+    const bool above = row0 + (wm + 1) * 32 * BI - 1 < col0 + wn * 32;     // this wavefront's part lies above the diagonal
+    // address of digit 0; digit s lies 2 s chunks on, which the swizzle of 8 chunks makes an exclusive or
+    uint32_t pa = lds0 + (uint32_t)(wm * 32 * BI + r) * ROWL + (uint32_t)((h ^ sw) * 16);
+    uint32_t pb = lds0 + (uint32_t)(RB + wn * 32 + r) * ROWL + (uint32_t)((h ^ sw) * 16);
+    auto digit = [](uint32_t p, int s, int off) __attribute__((always_inline)) {
+        return *(const ASTERIA_LDS i32x4 *)(uintptr_t)((CPR == 8 ? (p ^ (uint32_t)(32 * s)) : p + 32 * s) + off);
+    };
+    i32x4 da[2][BI], db[NS];
+    auto read_a = [&](int s) __attribute__((always_inline)) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int c = ((2 * s + h) ^ sw) * 16;
-                b[s] = *(const ASTERIA_LDS i32x4 *)(fb + stage + c);
+        for (int i = 0; i < BI; ++i) da[s & 1][i] = digit(pa, s, i * 32 * ROWL);
+    };
+    // the products of digit s of A; consecutive ones write different accumulators
+    auto times = [&](int s, int t) __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < BI; ++i) a[s][i] = *(const ASTERIA_LDS i32x4 *)(fa + stage + i * 32 * ROWL + c);
-            }
-            // consecutive MFMAs write different accumulators
-#pragma unroll
-            for (int s = 0; s < NS; ++s)
-#pragma unroll
-                for (int t = 0; t < NS; ++t) {
-                    if (s + t >= L) continue;
-#pragma unroll
-                    for (int i = 0; i < BI; ++i) acc[s + t][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][i], b[t], acc[s + t][i], 0, 0, 0);
-                }
-        };
-        ld.issue(lds0, 0);
-        uint32_t cur = 0;
+        for (int i = 0; i < BI; ++i) acc[s + t][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(da[s & 1][i], db[t], acc[s + t][i], 0, 0, 0);
+    };
+    ld.issue(lds0, 0);
+    ld.issue(lds0 + Loader::STAGE, min(1, last));
+    wait_lds_loads<0>();
+    __builtin_amdgcn_s_barrier();
+    uint32_t cur = 0;
+    if (above) {
         for (int kt = 0; kt < nk; ++kt) {
             wait_lds_loads<0>();
             __builtin_amdgcn_s_barrier();
-            const uint32_t nxt = cur ? 0u : (uint32_t)Loader::STAGE;
-            ld.issue(lds0 + nxt, min(kt + 1, last));
-            if (!above) compute(cur);
-            cur = nxt;
+            ld.issue(lds0 + cur, min(kt + 2, last));
+            cur ^= (uint32_t)Loader::STAGE;
         }
-        wait_lds_loads<0>();
-        __builtin_amdgcn_s_barrier();
+    } else {
 #pragma unroll
-        for (int i = 0; i < BI; ++i) {
-            const int br = row0 + (wm * BI + i) * 32, bc = col0 + wn * 32;
-            if (br < bc || br >= n || bc >= n) continue;
-            const int col = bc + r;
-            const char *own = digits_of(o.O1) + (size_t)min(col, n - 1) * rowb + (br >> 5) * (32 * NS) + 4 * h;
-            // calls use(v, row, value) for the block's elements; used once per output format (the second time
-            // the own digits come from L1: cheaper than holding both formats in registers)
-            auto values = [&](auto use) {
+        for (int t = 0; t < NS; ++t) db[t] = digit(pb, t, 0);
+        read_a(NS - 1);
+        for (int kt = 0; kt < nk; ++kt) {
+            // lowest digits of A first: the many products of its top digit, whose operands are all there, cover the turn
+            // to the next slab, whose B takes the place of this one's digit by digit
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    double ov[4];
-                    load_digit_group<NS>(own, g, ov);
+            for (int s = NS - 1; s > 0; --s) {
+                read_a(s - 1);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int v = 4 * g + e, row = br + 8 * g + 4 * h + e;
-                        double t = (double)acc[0][i][v];
+                for (int t = 0; t < NS; ++t)
+                    if (s + t < L) times(s, t);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            wait_lds_loads<0>();                  // the next slab has landed ...
+            __builtin_amdgcn_s_barrier();         // ... and everyone has read this one
+            const uint32_t step = cur ? 0u - (uint32_t)Loader::STAGE : (uint32_t)Loader::STAGE;
+            pa += step; pb += step;
 #pragma unroll
-                        for (int l = 1; l < L; ++l) t = t * 256.0 + (double)acc[l][i][v];
-                        const double val = c1 * ov[e] + cg * t;
-                        use(v, row, (row < n && col < n) ? val : 0.0);
-                    }
+            for (int t = 0; t < NS; ++t) {
+                times(0, t);
+                __builtin_amdgcn_sched_barrier(0);
+                db[t] = digit(pb, t, 0);
+                if (t == 0) ld.issue_part(lds0 + cur, min(kt + 2, last), 0, Loader::NI / 2);
+                if (t == 1) ld.issue_part(lds0 + cur, min(kt + 2, last), Loader::NI / 2, Loader::NI);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            read_a(NS - 1);
+            cur ^= (uint32_t)Loader::STAGE;
+        }
+    }
+    wait_lds_loads<0>();
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int i = 0; i < BI; ++i) {
+        const int br = row0 + (wm * BI + i) * 32, bc = col0 + wn * 32;
+        if (br < bc || br >= n || bc >= n) continue;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));            // addresses are made here, not kept through the K loop
+        const int r = ln & 31, h = ln >> 5;
+        const int col = bc + r;
+        const char *own = digits_of(o.O1) + (size_t)min(col, n - 1) * rowb + (br >> 5) * (32 * NS) + 4 * h;
+        // calls use(v, row, value) for the block's elements; used once per output format (the second time
+        // the own digits come from L1: cheaper than holding both formats in registers)
+        auto values = [&](auto use) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                double ov[4];
+                load_digit_group<NS>(own, g, ov);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int v = 4 * g + e, row = br + 8 * g + 4 * h + e;
+                    double t = (double)acc[0][i][v];
+#pragma unroll
+                    for (int l = 1; l < L; ++l) t = t * 256.0 + (double)acc[l][i][v];
+                    const double val = c1 * ov[e] + cg * t;
+                    use(v, row, (row < n && col < n) ? val : 0.0);
                 }
-            };
-            if (to_digits) {
-                uint32_t wd[16], tp[16];
-                values([&](int v, int, double val) { wd[v] = digit_word<NS>(rint(val * inv_q), tp[v], over); });
-                store_digit_block<NS>(digits_of(o.C), rowb, n, br, bc, wd, tp, lane, ws);
             }
-            if (to_pair || first_x) {
-                uint32_t pw[16];
-                values([&](int v, int row, double val) {
-                    const double x = pe * val + (row == col ? pd : 0.0);
-                    pw[v] = (row < n && col < n) ? pair_word((float)x) : 0u;
-                    if (first_x && row < n && col < n && row >= col) F.Xout[(size_t)row * F.ldx + col] = (float)(x * inv_x);
-                });
-                store_pair_block(first_x ? F.X[1] : F.P[o.C], F.rowb, n, br, bc, pw, lane, ws);
-            }
-            if (op == OP_M)
-                values([&](int, int row, double val) {
-                    const float er = (float)(val - (row == col ? 1.0 : 0.0));
-                    if (row < n && col < n && row >= col) rsum += row == col ? er * er : 2.0f * er * er;
-                });
+        };
+        if (to_digits) {
+            uint32_t wd[16], tp[4] = {0u, 0u, 0u, 0u};
+            values([&](int v, int, double val) {
+                uint32_t top;
+                wd[v] = digit_word<NS>(rint(val * inv_q), top, over);
+                tp[v >> 2] |= top << (8 * (v & 3));
+            });
+            store_digit_block<NS>(digits_of(o.C), rowb, n, br, bc, wd, tp, ln, ws);
         }
-        if (step + 1 < 2 / BI) __syncthreads();        // the scratch is operand space again
+        if (to_pair || first_x) {
+            uint32_t pw[16];
+            values([&](int v, int row, double val) {
+                const double x = pe * val + (row == col ? pd : 0.0);
+                pw[v] = (row < n && col < n) ? pair_word((float)x) : 0u;
+                if (first_x && row < n && col < n && row >= col) F.Xout[(size_t)row * F.ldx + col] = (float)(x * inv_x);
+            });
+            store_pair_block(first_x ? F.X[1] : F.P[o.C], F.rowb, n, br, bc, pw, ln, ws);
+        }
+        if (op == OP_M)
+            values([&](int, int row, double val) {
+                const float er = (float)(val - (row == col ? 1.0 : 0.0));
+                if (row < n && col < n && row >= col) rsum += row == col ? er * er : 2.0f * er * er;
+            });
     }
     if (over) F.flags[0] = 1;                         // an entry beyond the bound of a positive semi-definite matrix
     if (op == OP_M) {
@@ -762,11 +806,11 @@ __global__ __launch_bounds__(256, 2) void digit_product_kernel(const FactorDev *
     if (S.tier != TIER_DIGIT || S.ns != NS) return;
     const int ti = (int)(tile.y >> 16), tj = (int)(tile.y & 0xffffu), half = w & 1;
     if constexpr (NS == 4) {
-        if (S.levels == 4) digit_tile<4, 4, 2>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
-        else digit_tile<4, 5, 2>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
+        if (S.levels == 4) digit_tile<4, 4>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
+        else digit_tile<4, 5>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
     } else {
-        if (S.levels == 5) digit_tile<5, 5, 1>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
-        else digit_tile<5, 6, 1>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
+        if (S.levels == 5) digit_tile<5, 5>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
+        else digit_tile<5, 6>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
     }
 }
 
@@ -775,7 +819,7 @@ inline hipError_t launch_digit_product(const FactorDev *fd, const FactorScal *fs
                                        int op, int k, int degree, hipStream_t stream)
 {
     if (total <= 0) return hipSuccess;
-    constexpr size_t lds = 2 * (size_t)PlaneLoader<2 * NS, NS == 4 ? 128 : 64, 64, 4>::STAGE;
+    constexpr size_t lds = 2 * (size_t)PlaneLoader<2 * NS, 128, 64, 4>::STAGE;
     static_assert(lds >= 4 * (size_t)PLANE_SCRATCH_BYTES, "store scratch fits the stages");
     static bool configured[MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(digit_product_kernel<NS>), lds, configured); e != hipSuccess) return e;
