@@ -8,7 +8,7 @@
 //       U^T = X_R G^T   (X_R split, G exact: 2 MFMA passes; both operands k-contiguous)
 //       P   = X_L U     (X_L and U^T split: 3 MFMA passes; both operands k-contiguous); either product of
 //                       blocks whose shapes fill whole 256 x 256 tiles takes the 8-wavefront kernel of pgemm.h
-//                       (PgF32xB, PgF32x2) where the call has enough such tiles (pg_take_large_tiles)
+//                       (pgemm_kernel) where the call has enough such tiles (pg_take_large_tiles)
 //   fp32 gradients: fp32 matrix cores,  U = G X_R  then  P = X_L U  (U read k-major).
 #include <vector>
 
@@ -75,10 +75,10 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
         return k.g_dtype == ASTERIA_BF16 && pg_f32_operand_ok(k.XR, k.n, k.n, k.ldxr) && pg_bf16_operand_ok(k.G, k.m, k.n, k.ldg);
     };
     auto whole2 = [](const asteria_pblock &k) {   // U^T lies in the workspace: aligned, k contiguous
-        return k.g_dtype == ASTERIA_BF16 && pg_f32_operand_ok(k.XL, k.m, k.m, k.ldxl) && (k.n % PgF32x2::TN) == 0;
+        return k.g_dtype == ASTERIA_BF16 && pg_f32_operand_ok(k.XL, k.m, k.m, k.ldxl) && (k.n % PG_TILE) == 0;
     };
     for (int i = 0; i < nblocks; ++i) {
-        const long long t = (long long)(blocks[i].m / PgF32x2::TM) * (blocks[i].n / PgF32x2::TN);
+        const long long t = (long long)(blocks[i].m / PG_TILE) * (blocks[i].n / PG_TILE);
         if (whole1(blocks[i])) { t1 += t; tk1 += t * blocks[i].n; }
         if (whole2(blocks[i])) { t2 += t; tk2 += t * blocks[i].m; }
     }
@@ -104,8 +104,8 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
                 memset(&q, 0, sizeof(q));
                 q.A = k.XR; q.lda = k.ldxr; q.B = k.G; q.ldb = k.ldg; q.C32 = Ut; q.ldc32 = ldu;
                 q.M = k.n; q.N = k.m; q.K = k.n;
-                q.tiles_n = k.m / PgF32xB::TN;
-                q.tile_start = tiles1f; tiles1f += (k.n / PgF32xB::TM) * q.tiles_n;
+                q.tiles_n = k.m / PG_TILE;
+                q.tile_start = tiles1f; tiles1f += (k.n / PG_TILE) * q.tiles_n;
                 p1f.push_back(q);
             } else {
                 p.A = k.XR; p.lda = k.ldxr; p.B = k.G; p.ldb = k.ldg; p.C = Ut; p.ldc = ldu; p.flags = 0;
@@ -121,8 +121,8 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
                 q.C32 = reinterpret_cast<float *>(k.P); q.ldc32 = k.ldp;
                 q.flags = (k.p_dtype == ASTERIA_BF16) ? GEMM_C_BF16 : 0;
                 q.M = k.m; q.N = k.n; q.K = k.m;
-                q.tiles_n = k.n / PgF32x2::TN;
-                q.tile_start = tiles2f; tiles2f += (k.m / PgF32x2::TM) * q.tiles_n;
+                q.tiles_n = k.n / PG_TILE;
+                q.tile_start = tiles2f; tiles2f += (k.m / PG_TILE) * q.tiles_n;
                 p2f.push_back(q);
             } else {
                 p.A = k.XL; p.lda = k.ldxl; p.B = Ut; p.ldb = ldu; p.C = k.P; p.ldc = k.ldp;
@@ -160,12 +160,12 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
         static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
         PlaneProblem *d1f = reinterpret_cast<PlaneProblem *>(d1b + p1[1].size());
         ASTERIA_HIP_TRY(upload_async(d1f, p1f.data(), p1f.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<PgF32xB>(d1f, (int)p1f.size(), tiles1f, stream, 514)));
+        ASTERIA_HIP_TRY((launch_pgemm<1>(d1f, (int)p1f.size(), tiles1f, stream, 514)));
     }
     ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d2b, (int)p2[1].size(), tiles2[1], nullptr, stream)));
     if (!p2f.empty()) {
         ASTERIA_HIP_TRY(upload_async(d2f, p2f.data(), p2f.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d2f, (int)p2f.size(), tiles2f, stream, 513)));
+        ASTERIA_HIP_TRY((launch_pgemm<2>(d2f, (int)p2f.size(), tiles2f, stream, 513)));
     }
     return ASTERIA_OK;
 }

@@ -427,12 +427,12 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
     long long t1 = 0, tk1 = 0, t2 = 0, tk2 = 0;
     auto whole1 = [](const asteria_sblock &k) {
         return k.QL && k.QR && k.g_dtype == ASTERIA_BF16 && pg_bf16_operand_ok(k.G, k.m, k.n, k.ldg) &&
-               (k.n % PgF32xB::TM) == 0 && (!k.QRt || pg_f32_operand_ok(k.QRt, k.n, k.n, k.ldqrt));
+               (k.n % PG_TILE) == 0 && (!k.QRt || pg_f32_operand_ok(k.QRt, k.n, k.n, k.ldqrt));
     };
     for (int i = 0; i < nblocks; ++i) {
         const asteria_sblock &k = blocks[i];
-        if (!k.QL || !k.QR || k.m % PgF32x2::TM || k.n % PgF32x2::TN) continue;
-        const long long t = (long long)(k.m / PgF32x2::TM) * (k.n / PgF32x2::TN);
+        if (!k.QL || !k.QR || k.m % PG_TILE || k.n % PG_TILE) continue;
+        const long long t = (long long)(k.m / PG_TILE) * (k.n / PG_TILE);
         if (whole1(k)) { t1 += t; tk1 += t * k.n; }
         t2 += t; tk2 += t * (k.m + k.n) / 2;
     }
@@ -504,8 +504,8 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
             PlaneProblem q;
             memset(&q, 0, sizeof(q));
             q.A = QRt; q.lda = ldqrt; q.B = k.G; q.ldb = k.ldg; q.C32 = Tt; q.ldc32 = ldt;
-            q.M = k.n; q.N = k.m; q.K = k.n; q.tiles_n = k.m / PgF32xB::TN;
-            q.tile_start = tiles1f; tiles1f += (k.n / PgF32xB::TM) * q.tiles_n;
+            q.M = k.n; q.N = k.m; q.K = k.n; q.tiles_n = k.m / PG_TILE;
+            q.tile_start = tiles1f; tiles1f += (k.n / PG_TILE) * q.tiles_n;
             f1.push_back(q);
         } else {
             p.A = k.G; p.lda = k.ldg; p.B = QRt; p.ldb = ldqrt; p.C = Tt; p.ldc = ldt; p.flags = GEMM_STORE_T;
@@ -518,14 +518,16 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
         if (fast) {
             PlaneProblem q;
             memset(&q, 0, sizeof(q));
-            q.M = k.m; q.N = k.n; q.tiles_n = k.n / PgF32x2::TN; q.tile_start = tilesf;
+            q.M = k.m; q.N = k.n; q.tiles_n = k.n / PG_TILE; q.tile_start = tilesf;
             q.K = k.m; q.A = QLt; q.lda = ldqlt; q.B = Tt; q.ldb = ldt; q.C32 = Gr; q.ldc32 = ldw; q.flags = 0;
             f2.push_back(q);
-            q.K = k.n; q.A = Np; q.lda = ldw; q.B = k.QR; q.ldb = k.ldqr; q.C32 = Tt; q.ldc32 = ldt; q.flags = GEMM_STORE_T;
-            f3.push_back(q);
+            PlaneProblem q3 = q;                      // (N' Q_R^T)^T = Q_R N'^T
+            q3.M = k.n; q3.N = k.m; q3.K = k.n; q3.tiles_n = k.m / PG_TILE;
+            q3.A = k.QR; q3.lda = k.ldqr; q3.B = Np; q3.ldb = ldw; q3.C32 = Tt; q3.ldc32 = ldt;
+            f3.push_back(q3);
             q.K = k.m; q.A = k.QL; q.lda = k.ldql; q.B = Tt; q.ldb = ldt; q.C32 = k.N; q.ldc32 = k.ldn; q.flags = 0;
             f4.push_back(q);
-            tilesf += (k.m / PgF32x2::TM) * q.tiles_n;
+            tilesf += (k.m / PG_TILE) * q.tiles_n;
         } else {
             // 2: G' = Q_L^T (G Q_R):   A' = Q_L^T (m x m), B' = (G Q_R)^T (n x m)
             p.K = k.m; p.A = QLt; p.lda = ldqlt; p.B = Tt; p.ldb = ldt; p.C = Gr; p.ldc = ldw; p.flags = 0;
@@ -591,18 +593,18 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
         static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
         PlaneProblem *d_f1 = reinterpret_cast<PlaneProblem *>(d_g1b + g1[1].size());
         ASTERIA_HIP_TRY(upload_async(d_f1, f1.data(), f1.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<PgF32xB>(d_f1, (int)f1.size(), tiles1f, stream, 514)));
+        ASTERIA_HIP_TRY((launch_pgemm<1>(d_f1, (int)f1.size(), tiles1f, stream, 514)));
     }
     if (!g2.empty()) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[1], (int)g2.size(), tiles, nullptr, stream)));
-    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[0], (int)f2.size(), tilesf, stream, 513)));
+    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<2>(d_f[0], (int)f2.size(), tilesf, stream, 513)));
     const float c1 = 1.0f - powf(beta1, (float)step_t), c2 = 1.0f - powf(beta2, (float)step_t);
     hipLaunchKernelGGL(adam_rotated_kernel, dim3(rows), dim3(256), 0, stream, d_ab, nblocks, beta1, beta2,
                        adam_eps, 1.0f / c1, 1.0f / c2);
     ASTERIA_HIP_TRY(hipGetLastError());
     if (!g2.empty()) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[2], (int)g3.size(), tiles, nullptr, stream)));
-    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[1], (int)f3.size(), tilesf, stream, 513)));
+    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<2>(d_f[1], (int)f3.size(), tilesf, stream, 513)));
     if (!g2.empty()) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[3], (int)g4.size(), tiles, nullptr, stream)));
-    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<PgF32x2>(d_f[2], (int)f4.size(), tilesf, stream, 513)));
+    if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<2>(d_f[2], (int)f4.size(), tilesf, stream, 513)));
     // one-sided rotations back
     ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true>(d_oL2, (int)oL2.size(), tL2, nullptr, stream)));
     ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(d_oR2, (int)oR2.size(), tR2, nullptr, stream)));

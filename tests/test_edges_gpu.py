@@ -205,8 +205,8 @@ def test_refresh_at_the_edges(sizes):
 @pytest.mark.parametrize("blocks", [
     [(256, 256)] * 3 + [(250, 256)],                            # too few whole tiles: 128-wide tiles
     [(256, 512)] * 48 + [(512, 256)] * 48 + [(257, 260)],       # whole tiles, and a ragged block beside them
-    [(256, 256)] * 112, [(256, 256)] * 113,                     # either side of the dispatch line, short K
-    [(512, 512)] * 32, [(512, 512)] * 33, [(512, 512)] * 65,    # K = 512: one round, a round and a remainder
+    [(256, 256)] * 48, [(256, 256)] * 49,                       # either side of the dispatch line, short K
+    [(512, 512)] * 32, [(512, 512)] * 33, [(512, 512)] * 65,    # K = 512: either side of it, a round and a remainder
 ])
 def test_two_sided_products_at_the_edges(blocks, out):
     g = torch.Generator(device=DEV).manual_seed(5)
