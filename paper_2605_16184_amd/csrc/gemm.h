@@ -66,6 +66,19 @@ __host__ __device__ inline size_t packed_off(int row, int col)
     return ((ti * (ti + 1) / 2 + tj) * PACK_T + (size_t)(row % PACK_T)) * PACK_T + (size_t)(col % PACK_T);
 }
 
+// a value that every lane holds, in a scalar register
+__device__ __forceinline__ float uniform(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
+
+__device__ __forceinline__ double uniform(double x)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
 struct GemmProblem {
     const void *A;
     const void *B;

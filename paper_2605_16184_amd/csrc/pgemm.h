@@ -1,9 +1,10 @@
-// Guard-free grouped GEMM over bf16 terms on the gfx950 matrix cores (v_mfma_f32_16x16x32_bf16, fp32 accumulation).
+// Guard-free grouped GEMM over 16-bit terms on the gfx950 matrix cores (v_mfma_f32_16x16x32, fp32 accumulation).
 //
 // One launch walks a device table of problems  C = A B^T  (A is M x K, B is N x K, both k-contiguous, M and N multiples of
 // 256, K of 32: the callers send other shapes to the guarded kernels).  A is a plain fp32 matrix that the loader cuts into two
 // bf16 terms (the value rounded, the remainder rounded) while it stages it; B is the same (NTB = 2: three products per
-// block, lo hi, hi lo, hi hi, 16 bits of both operands) or a plain bf16 matrix (NTB = 1: two products).
+// block, lo hi, hi lo, hi hi, 16 bits of both operands) or a plain bf16 matrix (NTB = 1: two products).  With F16 the terms
+// are fp16 ones (22 bits) of the operands times powers of two that the problem states.
 #pragma once
 #include <type_traits>
 
@@ -12,6 +13,7 @@
 namespace asteria {
 
 typedef __bf16 pg_bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 pg_f16x8 __attribute__((ext_vector_type(8)));
 
 struct PlaneProblem {
     const void *A;          // fp32 matrix
@@ -22,6 +24,8 @@ struct PlaneProblem {
     int tile_start;
     int tiles_n;            // tile columns
     int flags;
+    float sa, sb;           // fp16 terms: powers of two the operands are multiplied by before the split,
+    const float *sa_dev, *sb_dev;   // on the device where these are not null
 };
 
 __device__ __forceinline__ uint32_t pg_pack_bf16(float a, float b)
@@ -32,6 +36,17 @@ __device__ __forceinline__ uint32_t pg_pack_bf16(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
 }
 
+// two fp16 terms of (a, b) * scale, round to nearest in both; scale is a power of two, so the fused product is exact
+__device__ __forceinline__ void pg_split_f16(float a, float b, float scale, uint32_t &hi, uint32_t &lo)
+{
+    typedef _Float16 halfx2_t __attribute__((ext_vector_type(2)));
+    typedef float floatx2_t __attribute__((ext_vector_type(2)));
+    const halfx2_t h = __builtin_convertvector(((floatx2_t){a * scale, b * scale}), halfx2_t);
+    const floatx2_t d = {fmaf(a, scale, -(float)h[0]), fmaf(b, scale, -(float)h[1])};
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(d, halfx2_t));
+}
+
 // A 256 x 256 tile per workgroup of 8 wavefronts (4 x 2), 64 x 128 each in MFMA blocks of 16 x 16; slabs of 32 k, two stages.
 // An LDS row holds 32 k of a matrix row: [32 hi][32 lo] (128 bytes, 16-byte chunks swizzled by row) or 32 bf16 (64 bytes).
 // A slab is loaded into registers a slab ahead, cut into terms and stored behind the products of the slab before its own; the
@@ -39,11 +54,12 @@ __device__ __forceinline__ uint32_t pg_pack_bf16(float a, float b)
 // are read.  So the matrix pipe waits for neither: before this, two groups of wavefronts alternated between fragment reads
 // and products at a barrier each (pipe busy 47 - 49 %).
 // Measured (this kernel, the one before): preconditioned update of the 1.1B model 10.0 ms, 12.2; SOAP step 43.9 ms, 52.6 (four
-// rotations, Adam 5.0 of it).
+// rotations, Adam 5.0 of it).  SOAP refresh of that model with its products A Q here (F16), on the 128 x 128 tiles of gemm_bf16.h:
+// 135.0 ms, 147.3.
 constexpr int PG_TILE = 256, PG_BK = 32, PG_WAVES = 8;
 constexpr size_t pg_lds_bytes(int ntb) { return 2u * (size_t)PG_TILE * (128 + 64 * ntb); }
 
-template <int NTB>
+template <int NTB, bool F16 = false>
 __global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProblem *__restrict__ probs, int nprobs, int total_tiles)
 {
     constexpr int MI = 4, NJ = 8;
@@ -88,19 +104,27 @@ __global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProb
     const uint32_t wa = lds0 + (uint32_t)(wave * 32 + (lane >> 3)) * 128u + (uint32_t)((((lane & 7) >> 1) ^ (lane >> 4)) * 16 + (lane & 1) * 8);
     const uint32_t wb = NTB == 2 ? wa + 2 * STAGE_A
                                  : lds0 + 2 * STAGE_A + (uint32_t)(wave * 32 + (lane >> 2)) * 64u + (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) * 16);
-    auto split_store = [&](uint32_t at, u32x4 x, int v) __attribute__((always_inline)) {
+    float sca = 1.0f, scb = 1.0f;
+    if (F16) { sca = uniform(P.sa_dev ? *P.sa_dev : P.sa); scb = uniform(P.sb_dev ? *P.sb_dev : P.sb); }
+    auto split_store = [&](uint32_t at, u32x4 x, int v, float scale) __attribute__((always_inline)) {
         const float x0 = __uint_as_float(x[0]), x1 = __uint_as_float(x[1]), x2 = __uint_as_float(x[2]), x3 = __uint_as_float(x[3]);
-        const uint32_t h0 = pg_pack_bf16(x0, x1), h1 = pg_pack_bf16(x2, x3);
-        const uint32_t l0 = pg_pack_bf16(x0 - __uint_as_float(h0 << 16), x1 - __uint_as_float(h0 & 0xffff0000u));
-        const uint32_t l1 = pg_pack_bf16(x2 - __uint_as_float(h1 << 16), x3 - __uint_as_float(h1 & 0xffff0000u));
+        uint32_t h0, h1, l0, l1;
+        if constexpr (F16) {
+            pg_split_f16(x0, x1, scale, h0, l0);
+            pg_split_f16(x2, x3, scale, h1, l1);
+        } else {
+            h0 = pg_pack_bf16(x0, x1); h1 = pg_pack_bf16(x2, x3);
+            l0 = pg_pack_bf16(x0 - __uint_as_float(h0 << 16), x1 - __uint_as_float(h0 & 0xffff0000u));
+            l1 = pg_pack_bf16(x2 - __uint_as_float(h1 << 16), x3 - __uint_as_float(h1 & 0xffff0000u));
+        }
         const uint32_t hi = (v & 1) ? at ^ 64u : at;
         *(ASTERIA_LDS u32x2_t *)(uintptr_t)(hi + v * 1024) = (u32x2_t){h0, h1};
         *(ASTERIA_LDS u32x2_t *)(uintptr_t)((hi ^ 64u) + v * 1024) = (u32x2_t){l0, l1};
     };
     // piece q of 4 of the loaded slab
     auto stage = [&](uint32_t oa, uint32_t ob, int q) __attribute__((always_inline)) {
-        split_store(wa + oa, ra[q], q);
-        if constexpr (NTB == 2) split_store(wb + ob, rb[q], q);
+        split_store(wa + oa, ra[q], q, sca);
+        if constexpr (NTB == 2) split_store(wb + ob, rb[q], q, scb);
         else if (q < 2) *(ASTERIA_LDS u32x4 *)(uintptr_t)(wb + ob + q * 1024) = rb[q];
     };
 
@@ -112,7 +136,9 @@ __global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProb
     auto frag = [](uint32_t p) __attribute__((always_inline)) { return *(const ASTERIA_LDS u32x4 *)(uintptr_t)p; };
     // D = B-rows x A-rows: a lane holds 4 consecutive columns of one row of C
     auto mma = [](u32x4 a, u32x4 b, floatx4 c) __attribute__((always_inline)) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pg_bf16x8, b), __builtin_bit_cast(pg_bf16x8, a), c, 0, 0, 0);
+        if constexpr (F16)
+            return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(pg_f16x8, b), __builtin_bit_cast(pg_f16x8, a), c, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pg_bf16x8, b), __builtin_bit_cast(pg_bf16x8, a), c, 0, 0, 0);
     };
     floatx4 acc[MI][NJ];
 #pragma unroll
@@ -171,6 +197,13 @@ __global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProb
     // ---- stores: 32 x 32 through 4 KiB per wavefront, whole 128-byte (bf16: 64-byte) row pieces
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
+    if constexpr (F16) {
+        const float inv = 1.0f / (sca * scb);       // powers of two: exact
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) acc[i][j] *= inv;
+    }
     ASTERIA_LDS char *ws = lds + wave * 4096;
     const bool bf16 = (P.flags & GEMM_C_BF16) != 0;
     const bool vec = (P.ldc32 & 3) == 0 && (reinterpret_cast<uintptr_t>(P.C32) & (bf16 ? 7u : 15u)) == 0;
@@ -236,11 +269,11 @@ inline bool pg_take_large_tiles(long long tiles, long long tiles_k)
     return tiles > (tiles_k < 512 * tiles ? 48 : 128);
 }
 
-template <int NTB>
+template <int NTB, bool F16 = false>
 inline hipError_t launch_pgemm(const PlaneProblem *probs, int nprobs, int total_tiles, hipStream_t stream, int kind)
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
-    auto kern = pgemm_kernel<NTB>;
+    auto kern = pgemm_kernel<NTB, F16>;
     static bool configured[MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), pg_lds_bytes(NTB), configured); e != hipSuccess) return e;
     const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;

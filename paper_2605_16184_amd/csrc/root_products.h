@@ -118,19 +118,6 @@ struct PairShape {
     static_assert(MI % 2 == 0 && NJ % 2 == 0 && (ST & (ST - 1)) == 0 && KR * TM == 256, "blocks of 32 x 32; stages by mask");
 };
 
-// a value that every lane holds, in a scalar register
-__device__ __forceinline__ float uniform(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
-}
-
-__device__ __forceinline__ double uniform(double x)
-{
-    const uint64_t b = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
-}
-
 // two values (scaled) -> their hi terms and their lo terms, both rounded to nearest
 __device__ __forceinline__ void pair_words2(float a, float b, uint32_t &hi, uint32_t &lo)
 {

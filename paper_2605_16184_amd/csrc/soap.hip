@@ -255,11 +255,13 @@ __global__ __launch_bounds__(256) void sort_gather_kernel(const QrFactor *fs, in
 // The factors of a group are sorted by size, largest first, so those that have panel j are the first
 // count_j of the group and the entry of factor i in any table of panel j is entry i of that panel's run.
 struct RefreshTables {
-    GemmProblem *z;                    // Z^T = Q^T A: one entry per factor
+    GemmProblem *z;                    // Z^T = Q^T A of the factors on 128 x 128 tiles
+    PlaneProblem *zp;                  // the same of those on 256 x 256 tiles
     GemmProblem *t1, *t2;              // projection coefficients, projection
     const int *off;                    // np + 1: start of panel j's run in t1, t2
     const int *pt;                     // cnt + 1: tile columns (ceil(n / 128)) of the factors before i
-    const int *pz;                     // cnt + 1: tiles of the Z product (ceil(n / 128)^2) of the factors before i
+    const int *pz;                     // cnt: first tile of factor i in the launch of its Z product
+    const int *slot;                   // cnt: its entry there, s in z or -1 - s in zp
 };
 
 __global__ __launch_bounds__(128) void refresh_tables_kernel(QrFactor *fs, int cnt, RefreshTables T)
@@ -275,13 +277,23 @@ __global__ __launch_bounds__(128) void refresh_tables_kernel(QrFactor *fs, int c
         // Z^T = Q^T A on the fp16 cores (two terms per operand): A'(i, k) = Q^T[i][k] - the caller's Q has
         // been transposed in place by then, or the caller keeps Q^T -, scaled by 2^14, and B'(j, k) = A[j][k] (A is symmetric),
         // scaled by the factor's a_scale; both k-contiguous
-        GemmProblem g = p;
-        g.state_idx = -1; g.state_mask = ~0;
-        g.M = g.N = g.K = F.n; g.tiles_n = tn;
-        g.A = F.Qt; g.lda = F.ldqt; g.B = F.A; g.ldb = F.lda; g.C = F.Zt; g.ldc = F.ldz;
-        g.sa = QR_UNIT_SCALE; g.sb_dev = a_scale;
-        g.tile_start = T.pz[i];
-        T.z[i] = g;
+        const int slot = T.slot[i];
+        if (slot < 0) {
+            PlaneProblem g = {};
+            g.M = g.N = g.K = F.n; g.tiles_n = F.n / PG_TILE;
+            g.A = F.Qt; g.lda = F.ldqt; g.B = F.A; g.ldb = F.lda; g.C32 = F.Zt; g.ldc32 = F.ldz;
+            g.sa = QR_UNIT_SCALE; g.sb_dev = a_scale;
+            g.tile_start = T.pz[i];
+            T.zp[-1 - slot] = g;
+        } else {
+            GemmProblem g = p;
+            g.state_idx = -1; g.state_mask = ~0;
+            g.M = g.N = g.K = F.n; g.tiles_n = tn;
+            g.A = F.Qt; g.lda = F.ldqt; g.B = F.A; g.ldb = F.lda; g.C = F.Zt; g.ldc = F.ldz;
+            g.sa = QR_UNIT_SCALE; g.sb_dev = a_scale;
+            g.tile_start = T.pz[i];
+            T.z[slot] = g;
+        }
     }
     if (F.n <= j * QR_PANEL) return;
     const int e = T.off[j] + i;
@@ -732,9 +744,9 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         QrFactor *d_q = cv.take<QrFactor>(cnt);
         std::vector<QrFactor> q;
         bool any_qt = false;                       // some factor's Q^T is kept by the caller
-        // off | pt | pz: see RefreshTables
-        std::vector<int> ints((size_t)(np_max + 1) + 2 * (size_t)(cnt + 1), 0);
-        int *off = ints.data(), *pt = off + np_max + 1, *pz = pt + cnt + 1;
+        // off | pt | pz | slot: see RefreshTables
+        std::vector<int> ints((size_t)(np_max + 1) + (size_t)(cnt + 1) + 2 * (size_t)cnt, 0);
+        int *off = ints.data(), *pt = off + np_max + 1, *pz = pt + cnt + 1, *slot = pz + cnt;
         std::vector<int> count(np_max, 0);
         for (int i = 0; i < cnt; ++i) {
             const asteria_factor &a = f[idx[i]];
@@ -756,17 +768,41 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             q.push_back(F);
             const int tn = (n + BN - 1) / BN;
             pt[i + 1] = pt[i] + tn;
-            pz[i + 1] = pz[i] + tn * tn;
             for (int j = 0; j < (n + QR_PANEL - 1) / QR_PANEL; ++j) ++count[j];
         }
         for (int j = 0; j < np_max; ++j) off[j + 1] = off[j] + count[j];
-        const int tiles = pz[cnt], entries = off[np_max];
+        // the Z products of whole-tile factors run on 256 x 256 tiles, where these fill the device
+        auto whole = [](const QrFactor &F) {
+            return pg_f32_operand_ok(F.Qt, F.n, F.n, F.ldqt) && pg_f32_operand_ok(F.A, F.n, F.n, F.lda);
+        };
+        long long large_tiles = 0, large_k = 0;
+        for (const QrFactor &F : q)
+            if (whole(F)) {
+                const long long t = (long long)(F.n / PG_TILE) * (F.n / PG_TILE);
+                large_tiles += t;
+                large_k += t * F.n;
+            }
+        const bool large = pg_take_large_tiles(large_tiles, large_k);
+        int nz = 0, nzp = 0, tiles = 0, tiles_p = 0;
+        for (int i = 0; i < cnt; ++i) {
+            const int n = q[i].n, tn = (n + BN - 1) / BN;
+            if (large && whole(q[i])) {
+                slot[i] = -1 - nzp++;
+                pz[i] = tiles_p;
+                tiles_p += (n / PG_TILE) * (n / PG_TILE);
+            } else {
+                slot[i] = nz++;
+                pz[i] = tiles;
+                tiles += tn * tn;
+            }
+        }
+        const int entries = off[np_max];
         RefreshTables rt;
-        rt.z = cv.take<GemmProblem>(cnt);
+        rt.z = cv.take<GemmProblem>(nz);
+        rt.zp = cv.take<PlaneProblem>(nzp);
         rt.t1 = cv.take<GemmProblem>(entries); rt.t2 = cv.take<GemmProblem>(entries);
         int *d_ints = cv.take<int>(ints.size());
-        rt.off = d_ints; rt.pt = d_ints + np_max + 1; rt.pz = rt.pt + cnt + 1;
-        GemmProblem *d_g = rt.z;
+        rt.off = d_ints; rt.pt = d_ints + np_max + 1; rt.pz = rt.pt + cnt + 1; rt.slot = rt.pz + cnt;
         ASTERIA_HIP_TRY(upload_async(d_q, q.data(), q.size() * sizeof(QrFactor), stream));
         ASTERIA_HIP_TRY(upload_async(d_ints, ints.data(), ints.size() * sizeof(int), stream));
         hipLaunchKernelGGL(refresh_tables_kernel, dim3((cnt + 127) / 128, np_max), dim3(128), 0, stream, d_q, cnt, rt);
@@ -787,7 +823,8 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             hipLaunchKernelGGL(keep_qt_kernel, dim3(tpr32 * tpr32, (unsigned)cnt), dim3(256), 0, stream, d_q);
         for (int round = 0; round < o.rounds; ++round) {
         hipLaunchKernelGGL(transpose_inplace_kernel, dim3(tpr32 * tpr32, (unsigned)cnt), dim3(256), 0, stream, d_q);
-        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(d_g, cnt, tiles, nullptr, stream)));
+        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(rt.z, nz, tiles, nullptr, stream)));
+        ASTERIA_HIP_TRY((launch_pgemm<2, true>(rt.zp, nzp, tiles_p, stream, 513)));
         if (o.sort) {
             // order the columns by q_i^T A q_i = (row i of Q^T) . (row i of Z^T), largest first: the rows of
             // Z^T are gathered in that order (A (Q P) = (A Q) P: sorting the basis first, as SOAP does, and

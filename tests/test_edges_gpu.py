@@ -183,7 +183,8 @@ def test_statistics_at_the_edges(m, n, packed):
             full[side] = a.clone()
 
 
-@pytest.mark.parametrize("sizes", [[1, 2, 15, 16, 17, 33, 48], [127, 128, 129, 191, 192, 193], [385, 1153]])
+@pytest.mark.parametrize("sizes", [[1, 2, 15, 16, 17, 33, 48], [127, 128, 129, 191, 192, 193], [385, 1153],
+                                   [256] * 49 + [250]])          # products on 256-wide tiles, and a ragged factor beside them
 def test_refresh_at_the_edges(sizes):
     As = [_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n) for n in sizes]
     Q0 = [W.haar(n, DEV, 11, n) for n in sizes]
