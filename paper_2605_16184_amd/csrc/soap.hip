@@ -25,6 +25,7 @@
 #include "gemm.h"
 #include "gemm_bf16.h"
 #include "pgemm.h"
+#include "panel_product.h"
 #include "soap_panel.h"
 
 using namespace asteria;
@@ -105,6 +106,10 @@ __global__ __launch_bounds__(256) void transpose_f32_kernel(const TransposeF32Jo
 
 // ---------------------------------------------------------------------------------------------
 // Eigenbasis refresh (panel steps: soap_panel.h)
+// Panels whose rows are projected together in the first sweep: what is finished before the first of them is read once for
+// all, what is finished since, once for each.  Refresh of the 1.1B model: 1 panel 128.3 ms, 2: 123.1, 3: 123.8, 4: 123.4
+// (two streams; the coefficients of each take 128 n floats).
+constexpr int QR_AHEAD = 2;
 constexpr int QR_STATE_STRIDE = (int)(sizeof(QrFactor) / sizeof(int));
 static_assert(sizeof(QrFactor) % sizeof(int) == 0, "state words are addressed as ints inside the factor array");
 
@@ -257,9 +262,15 @@ __global__ __launch_bounds__(256) void sort_gather_kernel(const QrFactor *fs, in
 struct RefreshTables {
     GemmProblem *z;                    // Z^T = Q^T A of the factors on 128 x 128 tiles
     PlaneProblem *zp;                  // the same of those on 256 x 256 tiles
-    GemmProblem *t1, *t2;              // projection coefficients, projection
-    const int *off;                    // np + 1: start of panel j's run in t1, t2
-    const int *pt;                     // cnt + 1: tile columns (ceil(n / 128)) of the factors before i
+    // projection coefficients, projection: a factor has an entry in both kinds of table, with no tiles in the one that it
+    // does not use (whole-panel factors: p1, p2)
+    GemmProblem *t1, *t2;
+    PanelProblem *f1, *f2;             // whole-panel factors, first sweep
+    PanelProblem *p1, *p2;             // the later ones
+    const int *off;                    // np + 1: start of panel j's run in the tables t1 .. p2
+    const int *whole;                  // cnt + 1: whole-panel factors before i
+    const int *pt;                     // cnt + 1: tile columns (ceil(n / 128)) of the other factors before i
+    const int *pp[2];                  // cnt + 1: tiles of 128, of 256 columns of the whole-panel factors before i
     const int *pz;                     // cnt: first tile of factor i in the launch of its Z product
     const int *slot;                   // cnt: its entry there, s in z or -1 - s in zp
 };
@@ -306,9 +317,34 @@ __global__ __launch_bounds__(128) void refresh_tables_kernel(QrFactor *fs, int c
     // the panel rows are scaled by the factor's p_scale, the finished rows are orthonormal
     p.M = rows; p.N = done; p.K = F.n; p.tiles_n = j;
     p.A = Pt; p.lda = F.ldz; p.B = F.Zt; p.ldb = F.ldz; p.C = F.cbuf; p.ldc = F.ldz;
-    p.tile_start = i * j;                      // every factor of the run has j tile columns here
+    p.tile_start = (i - T.whole[i]) * j;       // every factor of the run has j tile columns here
     p.sa_dev = p_scale; p.sb = QR_UNIT_SCALE;
     T.t1[e] = p;
+    // whole panels.  First sweep: QR_AHEAD panels at a time against what is finished before the first of them, and each
+    // of the others against those since then, `near` rows of it
+    const int near = (j % QR_AHEAD) * QR_PANEL, ahead = min(QR_AHEAD, (int)gridDim.y - j);
+    PanelProblem w = {};
+    w.ldx = F.ldz; w.Y = Pt; w.ldy = F.ldz; w.C = F.cbuf; w.ldc = F.ldz; w.K = F.n;
+    w.x_scale = QR_UNIT_SCALE; w.y_scale = p_scale; w.state_idx = i * QR_STATE_STRIDE;
+    w.X = F.Zt; w.N = done; w.panels = w.slots = 1;
+    w.start[0] = T.whole[i] * j; w.start[1] = T.whole[i] * ((j + 1) / 2);
+    T.p1[e] = w;
+    PanelProblem w2 = w;
+    w2.X = F.Qout; w2.ldx = F.ldq; w2.Y = F.cbuf; w2.C = Pt; w2.N = F.n; w2.K = done;
+    w2.subtract = 1;
+    w2.start[0] = T.pp[0][i]; w2.start[1] = T.pp[1][i];
+    T.p2[e] = w2;
+    if (near > 0) {
+        w.X = F.Zt + (size_t)(done - near) * F.ldz; w.N = near;
+        w.start[0] = T.whole[i] * (near / QR_PANEL); w.start[1] = T.whole[i] * ((near / QR_PANEL + 1) / 2);
+        w2.X = F.Qout + (done - near); w2.K = near;
+    } else {
+        w.slots = w2.slots = ahead;
+        w.panels = w2.panels = min(ahead, F.n / QR_PANEL - j);
+        w.start[0] *= ahead; w.start[1] *= ahead; w2.start[0] *= ahead; w2.start[1] *= ahead;
+    }
+    T.f1[e] = w;
+    T.f2[e] = w2;
     // P <- P - C Q_done: contraction over the finished rows, which the caller's Q already holds as
     // columns (k contiguous); the coefficients share the scale of the panel rows
     p.alpha = -1.0f; p.beta = 1.0f;
@@ -629,11 +665,11 @@ size_t refresh_factor_bytes(int n)
 {
     const int np = (n + QR_PANEL - 1) / QR_PANEL;
     return Carver::need((size_t)n * ld4(n), sizeof(float)) +            // Z^T, becomes Q^T
-           Carver::need((size_t)QR_PANEL * ld4(n), sizeof(float)) +     // projection coefficients of one panel
+           Carver::need((size_t)std::min(QR_AHEAD, np) * QR_PANEL * ld4(n), sizeof(float)) +   // projection coefficients of the panels in work
            Carver::need(gram_doubles(n), sizeof(double)) +              // partial Gram matrices of a panel
            Carver::need((size_t)QR_PANEL * QR_PANEL, sizeof(float)) +   // fp32 inverse factor
            Carver::need((size_t)n, sizeof(double)) + Carver::need((size_t)n, sizeof(int)) +   // column estimates and order
-           (size_t)(1 + 2 * np) * sizeof(GemmProblem) + (size_t)(np + 2) * sizeof(int) + sizeof(QrFactor);
+           (size_t)(1 + 2 * np) * sizeof(GemmProblem) + (size_t)(4 * np) * sizeof(PanelProblem) + (size_t)(np + 6) * sizeof(int) + sizeof(QrFactor);
 }
 
 // The factors of a call can be dealt to up to this many groups, each enqueued as a whole on an
@@ -744,9 +780,10 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         QrFactor *d_q = cv.take<QrFactor>(cnt);
         std::vector<QrFactor> q;
         bool any_qt = false;                       // some factor's Q^T is kept by the caller
-        // off | pt | pz | slot: see RefreshTables
-        std::vector<int> ints((size_t)(np_max + 1) + (size_t)(cnt + 1) + 2 * (size_t)cnt, 0);
-        int *off = ints.data(), *pt = off + np_max + 1, *pz = pt + cnt + 1, *slot = pz + cnt;
+        // off | whole | pt | pp[0] | pp[1] | pz | slot: see RefreshTables
+        std::vector<int> ints((size_t)(np_max + 1) + 4 * (size_t)(cnt + 1) + 2 * (size_t)cnt, 0);
+        int *off = ints.data(), *nwhole = off + np_max + 1, *pt = nwhole + cnt + 1, *pp0 = pt + cnt + 1, *pp1 = pp0 + cnt + 1;
+        int *pz = pp1 + cnt + 1, *slot = pz + cnt;
         std::vector<int> count(np_max, 0);
         for (int i = 0; i < cnt; ++i) {
             const asteria_factor &a = f[idx[i]];
@@ -754,7 +791,7 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             QrFactor F;
             memset(&F, 0, sizeof(F));
             F.Zt = cv.take<float>((size_t)n * ldz);
-            F.cbuf = cv.take<float>((size_t)QR_PANEL * ldz);
+            F.cbuf = cv.take<float>((size_t)std::min(QR_AHEAD, (n + QR_PANEL - 1) / QR_PANEL) * QR_PANEL * ldz);
             F.gram = cv.take<double>(gram_doubles(n));
             F.winv = cv.take<float>((size_t)QR_PANEL * QR_PANEL);
             F.Qout = a.X; F.n = n; F.ldz = ldz; F.ldq = a.ldx; F.bad = 0; F.run = 0; F.skip3 = 1;
@@ -767,7 +804,11 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             F.perm_out = perm ? perm + perm_offset[idx[i]] : nullptr;
             q.push_back(F);
             const int tn = (n + BN - 1) / BN;
-            pt[i + 1] = pt[i] + tn;
+            const bool panels = n % QR_PANEL == 0 && (a.ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15u) == 0;
+            nwhole[i + 1] = nwhole[i] + (panels ? 1 : 0);
+            pt[i + 1] = pt[i] + (panels ? 0 : tn);
+            pp0[i + 1] = pp0[i] + (panels ? tn : 0);
+            pp1[i + 1] = pp1[i] + (panels ? (tn + 1) / 2 : 0);
             for (int j = 0; j < (n + QR_PANEL - 1) / QR_PANEL; ++j) ++count[j];
         }
         for (int j = 0; j < np_max; ++j) off[j + 1] = off[j] + count[j];
@@ -801,17 +842,35 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         rt.z = cv.take<GemmProblem>(nz);
         rt.zp = cv.take<PlaneProblem>(nzp);
         rt.t1 = cv.take<GemmProblem>(entries); rt.t2 = cv.take<GemmProblem>(entries);
+        rt.f1 = cv.take<PanelProblem>(entries); rt.f2 = cv.take<PanelProblem>(entries);
+        rt.p1 = cv.take<PanelProblem>(entries); rt.p2 = cv.take<PanelProblem>(entries);
         int *d_ints = cv.take<int>(ints.size());
-        rt.off = d_ints; rt.pt = d_ints + np_max + 1; rt.pz = rt.pt + cnt + 1; rt.slot = rt.pz + cnt;
+        rt.off = d_ints; rt.whole = d_ints + (nwhole - off); rt.pt = d_ints + (pt - off);
+        rt.pp[0] = d_ints + (pp0 - off); rt.pp[1] = d_ints + (pp1 - off);
+        rt.pz = d_ints + (pz - off); rt.slot = d_ints + (slot - off);
         ASTERIA_HIP_TRY(upload_async(d_q, q.data(), q.size() * sizeof(QrFactor), stream));
         ASTERIA_HIP_TRY(upload_async(d_ints, ints.data(), ints.size() * sizeof(int), stream));
         hipLaunchKernelGGL(refresh_tables_kernel, dim3((cnt + 127) / 128, np_max), dim3(128), 0, stream, d_q, cnt, rt);
         ASTERIA_HIP_TRY(hipGetLastError());
-        // panel j: count[j] entries per table; tile counts of its four launches
-        auto T1 = [&](int j) { return rt.t1 + off[j]; };
-        auto T2 = [&](int j) { return rt.t2 + off[j]; };
-        auto tiles1 = [&](int j) { return count[j] * j; };
-        auto tiles2 = [&](int j) { return pt[count[j]]; };
+        // the two products of a projection of panel j, with `ny` fp16 terms of the panel's rows (and as many of the
+        // finished rows in the first) and `nx` of the finished rows in the second
+        auto project = [&](int j, auto ny_, auto nx_, const int *st) -> asteria_status {
+            constexpr int NY = decltype(ny_)::value, NX = decltype(nx_)::value;
+            const int c = count[j], w = nwhole[c];
+            GemmProblem *t1 = rt.t1 + off[j], *t2 = rt.t2 + off[j];
+            constexpr bool FIRST = NY == 1;
+            const PanelProblem *p1 = (FIRST ? rt.f1 : rt.p1) + off[j], *p2 = (FIRST ? rt.f2 : rt.p2) + off[j];
+            const int near = FIRST ? j % QR_AHEAD : 0, slots = FIRST && near == 0 ? std::min(QR_AHEAD, np_max - j) : 1;
+            const int c1 = near ? near : j;
+            const int narrow1 = w * c1 * slots, wide1 = w * ((c1 + 1) / 2) * slots, narrow2 = pp0[c] * slots, wide2 = pp1[c] * slots;
+            ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, NY, NY, true>(t1, c, (c - w) * j, st, stream)));
+            if (pp_take_wide_tiles(wide1)) ASTERIA_HIP_TRY((launch_panel_product<NY, NY, 4>(p1, c, wide1, st, stream)));
+            else ASTERIA_HIP_TRY((launch_panel_product<NY, NY, 2>(p1, c, narrow1, st, stream)));
+            ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, NY, NX, true>(t2, c, pt[c], st, stream)));
+            if (pp_take_wide_tiles(wide2)) ASTERIA_HIP_TRY((launch_panel_product<NY, NX, 4>(p2, c, wide2, st, stream)));
+            else ASTERIA_HIP_TRY((launch_panel_product<NY, NX, 2>(p2, c, narrow2, st, stream)));
+            return ASTERIA_OK;
+        };
         hipLaunchKernelGGL(qr_scale_kernel, dim3(cnt), dim3(64), 0, stream, d_q, cnt);
         if (o.from_identity)
             hipLaunchKernelGGL(set_identity_kernel, dim3((unsigned)std::min<size_t>(((size_t)n_max * n_max + 255) / 256, 4096), (unsigned)cnt),
@@ -853,16 +912,10 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
                     // the update (the finished rows keep both terms, so the panel stays in the span of
                     // its own rows and the finished ones to 2^-22): what this leaves along the finished
                     // rows, 2^-11 of the coefficients, is what the second sweep removes at full accuracy
-                    if (sweep == 0) {
-                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 1, 1, true>(T1(j), count[j], tiles1(j), st, stream)));
-                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 1, 2, true>(T2(j), count[j], tiles2(j), st, stream)));
-                    } else if (sweep == 1) {
-                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T1(j), count[j], tiles1(j), st, stream)));
-                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T2(j), count[j], tiles2(j), st, stream)));
-                    } else {
-                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T1(j), count[j], tiles1(j), st, stream)));
-                        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(T2(j), count[j], tiles2(j), st, stream)));
-                    }
+                    using One = std::integral_constant<int, 1>;
+                    using Two = std::integral_constant<int, 2>;
+                    const asteria_status ps = sweep == 0 ? project(j, One{}, Two{}, st) : project(j, Two{}, Two{}, st);
+                    if (ps != ASTERIA_OK) return ps;
                 }
                 const unsigned nfac = (unsigned)count[j];
                 hipLaunchKernelGGL(panel_gram_kernel, dim3((unsigned)gram_splits(n_max), nfac), dim3(256), 0, stream, d_q, j, sweep);

@@ -202,6 +202,31 @@ def test_refresh_at_the_edges(sizes):
         assert np.all(np.diag(R) >= 0), n
 
 
+# whole panels of 128 rows: one, an odd number, pairs and one over; the last fills the 256-wide tiles of the panel products
+@pytest.mark.parametrize("n,count", [(128, 2), (384, 2), (640, 3), (640, 513)])
+def test_refresh_on_whole_panels(n, count):
+    A = _with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n)
+    q0 = W.haar(n, DEV, 11, n)
+    Qs, Qt = [q0.clone() for _ in range(count)], [torch.zeros(n, n, device=DEV) for _ in range(count)]
+    other = torch.empty(n, n + 1, device=DEV)[:, :n]             # a row pitch that the general products take
+    other.copy_(q0)
+    info = torch.full((count,), -1, dtype=torch.int32, device=DEV)
+    ast.soap_refresh([(A, q) for q in Qs], info=info, qt=Qt)
+    one = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+    ast.soap_refresh([(A, other)], info=one)
+    torch.cuda.synchronize()
+    assert bool((info == 0).all()) and int(one[0]) == 0
+    for q, qt in zip(Qs, Qt):
+        assert torch.equal(q, Qs[0]) and torch.equal(qt, q.T)
+    Z = (A.double() @ q0.double()).cpu().numpy()
+    for q in (Qs[0], other):
+        Q = q.double().cpu().numpy()
+        R = Q.T @ Z
+        assert np.linalg.norm(Q.T @ Q - np.eye(n)) / np.sqrt(n) <= 1e-5
+        assert np.linalg.norm(np.tril(R, -1)) <= 1e-5 * np.linalg.norm(Z)
+        assert np.all(np.diag(R) >= 0)
+
+
 @pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("blocks", [
     [(256, 256)] * 3 + [(250, 256)],                            # too few whole tiles: 128-wide tiles
