@@ -1,5 +1,7 @@
 // L <- beta L + (1 - beta) G G^T and R <- beta R + (1 - beta) G^T G of bf16 gradients on the bf16 matrix cores.
 #pragma once
+#include <type_traits>
+
 #include "planes.h"
 
 namespace asteria {
@@ -100,25 +102,35 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
                 const u2 b = __builtin_bit_cast(u2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ASTERIA_LDS s16x4 *)(lds + off + 1024)));
                 return (u32x4){a[0], a[1], b[0], b[1]};
             };
+            u32x4 af[2][2], bf[2][2];
+            auto read = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) { af[s & 1][i] = frag(fa[i] + s * 4096); bf[s & 1][i] = frag(fb[i] + s * 4096); }
+            };
+            read(0);
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                u32x4 af[2], bf[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) { af[i] = frag(fa[i] + s * 4096); bf[i] = frag(fb[i] + s * 4096); }
-                multiply(af, bf);
-                __builtin_amdgcn_sched_barrier(0);        // the fragments of one step at a time: four would spill
+                if (s < 3) read(s + 1);
+                __builtin_amdgcn_sched_barrier(0);        // the fragments of one step ahead: four would spill
+                multiply(af[s & 1], bf[s & 1]);
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                u32x4 af[2], bf[2];
+            u32x4 af[2][2], bf[2][2];
+            auto read = [&](int s) __attribute__((always_inline)) {
                 const uint32_t c = (uint32_t)(((s * 2 + h) ^ sw) * 16);
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    af[i] = *(const ASTERIA_LDS u32x4 *)(lds + fa[i] + c);
-                    bf[i] = *(const ASTERIA_LDS u32x4 *)(lds + fb[i] + c);
+                    af[s & 1][i] = *(const ASTERIA_LDS u32x4 *)(lds + fa[i] + c);
+                    bf[s & 1][i] = *(const ASTERIA_LDS u32x4 *)(lds + fb[i] + c);
                 }
-                multiply(af, bf);
+            };
+            read(0);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (s < 3) read(s + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(af[s & 1], bf[s & 1]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -198,6 +210,66 @@ __global__ __launch_bounds__(256, 4) void stats_product_kernel(const StatsEntry 
     if (packed) C += ((size_t)ti * (ti + 1) / 2 + tj) * PACK_T * PACK_T - ((size_t)row0 * PACK_T + col0);   // of (0, 0) of the tile's frame
     const bool vec = (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(left ? E.L : E.R) & 15u) == 0;
     const bool read = beta != 0.0f;
+    if (!diag && vec && read && ldc < (1 << 24) && row0 + 128 <= n && col0 + 128 <= n) {
+        // a whole tile: pieces of 16 values of a lane (a block or its mirror image), the old values of the piece after next
+        // on their way while one is combined and stored
+        float o[2][16];
+        int ln = lane;
+        asm volatile("" : "+v"(ln));                          // addresses are made here, not kept through the K loop
+        const uint32_t rr = (uint32_t)ln & 31u, hh = (uint32_t)ln >> 5;
+        uint32_t lo4 = 16u * hh * (uint32_t)ldc + 4u * rr, lom = 4u * rr * (uint32_t)ldc + 16u * hh;     // bytes
+        auto load = [&](float (&d)[16], int b, bool mirror) __attribute__((always_inline)) {
+            const int br = row0 + (wm * 2 + (b >> 1)) * 32, bc = col0 + (wn * 2 + (b & 1)) * 32;
+            if (!mirror) {
+                const ASTERIA_GLOBAL float *cu = C + (size_t)br * ldc + bc;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) d[v] = *(const ASTERIA_GLOBAL float *)((const ASTERIA_GLOBAL char *)(cu + (size_t)(8 * (v >> 2) + (v & 3)) * ldc) + lo4);
+            } else {
+                const ASTERIA_GLOBAL float *cu = C + (size_t)bc * ldc + br;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const floatx4 t = *(const ASTERIA_GLOBAL floatx4 *)((const ASTERIA_GLOBAL char *)(cu + 8 * g) + lom);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) d[4 * g + e] = t[e];
+                }
+            }
+        };
+        auto store = [&](const float (&d)[16], int b, bool mirror) __attribute__((always_inline)) {
+            const int br = row0 + (wm * 2 + (b >> 1)) * 32, bc = col0 + (wn * 2 + (b & 1)) * 32;
+            const floatx16 &p = acc[b >> 1][b & 1];
+            if (!mirror) {
+                ASTERIA_GLOBAL float *cu = C + (size_t)br * ldc + bc;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) 
+                    *(ASTERIA_GLOBAL float *)((ASTERIA_GLOBAL char *)(cu + (size_t)(8 * (v >> 2) + (v & 3)) * ldc) + lo4) = alpha * p[v] + beta * d[v];
+            } else {
+                ASTERIA_GLOBAL float *cu = C + (size_t)bc * ldc + br;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    floatx4 w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = alpha * p[4 * g + e] + beta * d[4 * g + e];
+                    *(ASTERIA_GLOBAL floatx4 *)((ASTERIA_GLOBAL char *)(cu + 8 * g) + lom) = w;
+                }
+            }
+        };
+        auto all = [&](auto mirrors) __attribute__((always_inline)) {
+            constexpr int U = decltype(mirrors)::value ? 8 : 4;
+            load(o[0], 0, false);
+            load(o[1], U == 8 ? 0 : 1, U == 8);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("" : "+v"(lo4), "+v"(lom));      // nor kept from one piece to the next
+                store(o[u & 1], U == 8 ? u >> 1 : u, U == 8 && (u & 1));
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("" : "+v"(lo4), "+v"(lom));
+                if (u + 2 < U) load(o[u & 1], U == 8 ? (u + 2) >> 1 : u + 2, U == 8 && (u & 1));
+            }
+        };
+        if (packed) all(std::false_type{}); else all(std::true_type{});
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll

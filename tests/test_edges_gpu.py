@@ -153,7 +153,7 @@ def test_roots_of_uneven_batches(sizes):
 
 
 @pytest.mark.parametrize("packed", [False, True])
-@pytest.mark.parametrize("m, n", [(8, 8), (8, 136), (120, 64), (128, 128), (136, 120), (264, 8), (7, 9), (129, 63)])
+@pytest.mark.parametrize("m, n", [(8, 8), (8, 136), (120, 64), (128, 128), (136, 120), (264, 8), (7, 9), (129, 63), (256, 392), (384, 200)])
 def test_statistics_at_the_edges(m, n, packed):
     g = torch.Generator(device=DEV).manual_seed(m * 1000 + n)
     G = torch.randn(m, n, generator=g, device=DEV).bfloat16()
@@ -180,6 +180,7 @@ def test_statistics_at_the_edges(m, n, packed):
             # exact products, fp32 sums of k of them, one rounding each of the two terms and their sum
             tol = (k + 3) * 2.0 ** -24 * (beta * full[side].double().abs() + (1.0 - beta) * (H.abs() @ H.abs().T if side == 0 else H.abs().T @ H.abs()))
             assert bool(((a.double() - ref).abs() <= tol).all()), (m, n, side, beta)
+            assert torch.equal(a, a.T), (m, n, side, beta)
             full[side] = a.clone()
 
 
