@@ -362,3 +362,16 @@ def test_roots_stay_inside_the_smallest_workspace_and_do_not_depend_on_its_size(
         assert bool((info == 0).all()) and bool((buf[size:] == 255).all())
         got += Xs
     assert all(torch.equal(got[0], X) for X in got[1:])
+
+
+# sorted refresh: the columns' order where the ranks of one group of lanes end and the next begin
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 130, 257])
+def test_order_of_the_sorted_refresh(n):
+    lam = torch.arange(1, n + 1, device=DEV, dtype=torch.float32)
+    lam[: n // 2] = lam[n // 2]                        # ties: by index
+    shuffle = torch.randperm(n, generator=torch.Generator().manual_seed(n)).to(DEV)
+    A, Q = torch.diag(lam[shuffle]), torch.eye(n, device=DEV)
+    perm = [torch.full((n,), -1, dtype=torch.int32, device=DEV)]
+    ast.soap_refresh([(A, Q)], sort=True, perm=perm[0])
+    torch.cuda.synchronize()
+    assert torch.equal(perm[0].long(), torch.sort(-lam[shuffle], stable=True).indices)
