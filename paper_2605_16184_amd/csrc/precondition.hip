@@ -146,26 +146,24 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
         }
     }
     GemmProblem *d1b = d1 + p1[0].size(), *d2b = d2 + p2[0].size();
-    if (!p1[0].empty()) ASTERIA_HIP_TRY(upload_async(d1, p1[0].data(), p1[0].size() * sizeof(GemmProblem), stream));
-    if (!p1[1].empty()) ASTERIA_HIP_TRY(upload_async(d1b, p1[1].data(), p1[1].size() * sizeof(GemmProblem), stream));
-    if (!p2[0].empty()) ASTERIA_HIP_TRY(upload_async(d2, p2[0].data(), p2[0].size() * sizeof(GemmProblem), stream));
-    if (!p2[1].empty()) ASTERIA_HIP_TRY(upload_async(d2b, p2[1].data(), p2[1].size() * sizeof(GemmProblem), stream));
+    // every block has one entry for its first product, of either kind: the region of d1 holds them all
+    static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
+    PlaneProblem *d1f = reinterpret_cast<PlaneProblem *>(d1b + p1[1].size());
+    Uploads up(stream);
+    ASTERIA_HIP_TRY(up.add(d1, p1[0].data(), p1[0].size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.add(d1b, p1[1].data(), p1[1].size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.add(d1f, p1f.data(), p1f.size() * sizeof(PlaneProblem)));
+    ASTERIA_HIP_TRY(up.add(d2, p2[0].data(), p2[0].size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.add(d2b, p2[1].data(), p2[1].size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.add(d2f, p2f.data(), p2f.size() * sizeof(PlaneProblem)));
+    ASTERIA_HIP_TRY(up.flush());
     if (!p1[0].empty()) {
         ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(d1, (int)p1[0].size(), tiles1[0], nullptr, stream)));
         ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true>(d2, (int)p2[0].size(), tiles2[0], nullptr, stream)));
     }
     ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, bf16_t, 2, 1>(d1b, (int)p1[1].size(), tiles1[1], nullptr, stream)));
-    if (!p1f.empty()) {
-        // every block has one entry for its first product, of either kind: the region of d1 holds them all
-        static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
-        PlaneProblem *d1f = reinterpret_cast<PlaneProblem *>(d1b + p1[1].size());
-        ASTERIA_HIP_TRY(upload_async(d1f, p1f.data(), p1f.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<1>(d1f, (int)p1f.size(), tiles1f, stream, 514)));
-    }
+    ASTERIA_HIP_TRY((launch_pgemm<1>(d1f, (int)p1f.size(), tiles1f, stream, 514)));
     ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d2b, (int)p2[1].size(), tiles2[1], nullptr, stream)));
-    if (!p2f.empty()) {
-        ASTERIA_HIP_TRY(upload_async(d2f, p2f.data(), p2f.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<2>(d2f, (int)p2f.size(), tiles2f, stream, 513)));
-    }
+    ASTERIA_HIP_TRY((launch_pgemm<2>(d2f, (int)p2f.size(), tiles2f, stream, 513)));
     return ASTERIA_OK;
 }

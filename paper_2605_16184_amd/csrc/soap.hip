@@ -597,19 +597,20 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
     }
     (void)tilesT;
     GemmProblem *d_g1b = d_g[0] + g1[0].size();
-    if (!g1[0].empty()) ASTERIA_HIP_TRY(upload_async(d_g[0], g1[0].data(), g1[0].size() * sizeof(GemmProblem), stream));
-    if (!g1[1].empty()) ASTERIA_HIP_TRY(upload_async(d_g1b, g1[1].data(), g1[1].size() * sizeof(GemmProblem), stream));
-    if (!g2.empty()) {
-        ASTERIA_HIP_TRY(upload_async(d_g[1], g2.data(), g2.size() * sizeof(GemmProblem), stream));
-        ASTERIA_HIP_TRY(upload_async(d_g[2], g3.data(), g3.size() * sizeof(GemmProblem), stream));
-        ASTERIA_HIP_TRY(upload_async(d_g[3], g4.data(), g4.size() * sizeof(GemmProblem), stream));
-    }
-    if (!f2.empty()) {
-        ASTERIA_HIP_TRY(upload_async(d_f[0], f2.data(), f2.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY(upload_async(d_f[1], f3.data(), f3.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY(upload_async(d_f[2], f4.data(), f4.size() * sizeof(PlaneProblem), stream));
-    }
-    ASTERIA_HIP_TRY(upload_async(d_ab, ab.data(), ab.size() * sizeof(AdamBlock), stream));
+    // a two-sided block has one entry for its first product, of either kind: the region of d_g[0] holds them all
+    static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
+    PlaneProblem *d_f1 = reinterpret_cast<PlaneProblem *>(d_g1b + g1[1].size());
+    Uploads up(stream);
+    ASTERIA_HIP_TRY(up.add(d_g[0], g1[0].data(), g1[0].size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.add(d_g1b, g1[1].data(), g1[1].size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.add(d_f1, f1.data(), f1.size() * sizeof(PlaneProblem)));
+    ASTERIA_HIP_TRY(up.add(d_g[1], g2.data(), g2.size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.add(d_g[2], g3.data(), g3.size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.add(d_g[3], g4.data(), g4.size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.add(d_f[0], f2.data(), f2.size() * sizeof(PlaneProblem)));
+    ASTERIA_HIP_TRY(up.add(d_f[1], f3.data(), f3.size() * sizeof(PlaneProblem)));
+    ASTERIA_HIP_TRY(up.add(d_f[2], f4.data(), f4.size() * sizeof(PlaneProblem)));
+    ASTERIA_HIP_TRY(up.add(d_ab, ab.data(), ab.size() * sizeof(AdamBlock)));
     // tables of the one-sided blocks, one after the other in a region of their own
     GemmProblem *d_o = cv.take<GemmProblem>(4 * (size_t)nblocks);
     GemmProblem *d_oL1[2], *d_oR1[2], *d_oL2, *d_oR2;
@@ -618,13 +619,14 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
         auto put = [&](const std::vector<GemmProblem> &v, GemmProblem *&dst) -> hipError_t {
             dst = q;
             q += v.size();
-            return v.empty() ? hipSuccess : upload_async(dst, v.data(), v.size() * sizeof(GemmProblem), stream);
+            return up.add(dst, v.data(), v.size() * sizeof(GemmProblem));
         };
         ASTERIA_HIP_TRY(put(oL1[0], d_oL1[0])); ASTERIA_HIP_TRY(put(oL1[1], d_oL1[1])); ASTERIA_HIP_TRY(put(oL2, d_oL2));
         ASTERIA_HIP_TRY(put(oR1[0], d_oR1[0])); ASTERIA_HIP_TRY(put(oR1[1], d_oR1[1])); ASTERIA_HIP_TRY(put(oR2, d_oR2));
     }
+    ASTERIA_HIP_TRY(up.add(d_tj, tj.data(), tj.size() * sizeof(TransposeF32Job)));
+    ASTERIA_HIP_TRY(up.flush());
     if (!tj.empty()) {
-        ASTERIA_HIP_TRY(upload_async(d_tj, tj.data(), tj.size() * sizeof(TransposeF32Job), stream));
         hipLaunchKernelGGL(transpose_f32_kernel, dim3(ttiles), dim3(256), 0, stream, d_tj, (int)tj.size());
         ASTERIA_HIP_TRY(hipGetLastError());
     }
@@ -637,13 +639,7 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[0], (int)g1[0].size(), tiles1[0], nullptr, stream)));
     if (!g1[1].empty())
         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<bf16_t, float, 1, 2>(d_g1b, (int)g1[1].size(), tiles1[1], nullptr, stream)));
-    if (!f1.empty()) {
-        // a two-sided block has one entry for its first product, of either kind: the region of d_g[0] holds them all
-        static_assert(sizeof(PlaneProblem) <= sizeof(GemmProblem) && alignof(PlaneProblem) <= alignof(GemmProblem), "shared table region");
-        PlaneProblem *d_f1 = reinterpret_cast<PlaneProblem *>(d_g1b + g1[1].size());
-        ASTERIA_HIP_TRY(upload_async(d_f1, f1.data(), f1.size() * sizeof(PlaneProblem), stream));
-        ASTERIA_HIP_TRY((launch_pgemm<1>(d_f1, (int)f1.size(), tiles1f, stream, 514)));
-    }
+    if (!f1.empty()) ASTERIA_HIP_TRY((launch_pgemm<1>(d_f1, (int)f1.size(), tiles1f, stream, 514)));
     if (!g2.empty()) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[1], (int)g2.size(), tiles, nullptr, stream)));
     if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<2>(d_f[0], (int)f2.size(), tilesf, stream, 513)));
     const float c1 = 1.0f - powf(beta1, (float)step_t), c2 = 1.0f - powf(beta2, (float)step_t);
@@ -849,8 +845,10 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         rt.off = d_ints; rt.whole = d_ints + (nwhole - off); rt.pt = d_ints + (pt - off);
         rt.pp[0] = d_ints + (pp0 - off); rt.pp[1] = d_ints + (pp1 - off);
         rt.pz = d_ints + (pz - off); rt.slot = d_ints + (slot - off);
-        ASTERIA_HIP_TRY(upload_async(d_q, q.data(), q.size() * sizeof(QrFactor), stream));
-        ASTERIA_HIP_TRY(upload_async(d_ints, ints.data(), ints.size() * sizeof(int), stream));
+        Uploads up(stream);
+        ASTERIA_HIP_TRY(up.add(d_q, q.data(), q.size() * sizeof(QrFactor)));
+        ASTERIA_HIP_TRY(up.add(d_ints, ints.data(), ints.size() * sizeof(int)));
+        ASTERIA_HIP_TRY(up.flush());
         hipLaunchKernelGGL(refresh_tables_kernel, dim3((cnt + 127) / 128, np_max), dim3(128), 0, stream, d_q, cnt, rt);
         ASTERIA_HIP_TRY(hipGetLastError());
         // the two products of a projection of panel j, with `ny` fp16 terms of the panel's rows (and as many of the
@@ -1115,20 +1113,21 @@ extern "C" asteria_status asteria_soap_reproject(const asteria_rblock *blocks, i
         g[3].push_back(p);
         tiles += tm * tn;
     }
+    Uploads up(stream);
+    ASTERIA_HIP_TRY(up.add(d_pj, pj.data(), pj.size() * sizeof(PermuteJob)));
+    ASTERIA_HIP_TRY(up.add(d_tj, tj.data(), tj.size() * sizeof(TransposeF32Job)));
+    for (int i = 0; i < 4; ++i) ASTERIA_HIP_TRY(up.add(d_g[i], g[i].data(), g[i].size() * sizeof(GemmProblem)));
+    ASTERIA_HIP_TRY(up.flush());
     // V first: its copy uses the W buffer of the block
     if (!pj.empty()) {
-        ASTERIA_HIP_TRY(upload_async(d_pj, pj.data(), pj.size() * sizeof(PermuteJob), stream));
         for (int phase = 0; phase < 2; ++phase)
             hipLaunchKernelGGL(permute_moment_kernel, dim3(prow), dim3(256), 0, stream, d_pj, (int)pj.size(), phase);
         ASTERIA_HIP_TRY(hipGetLastError());
     }
     if (g[0].empty()) return ASTERIA_OK;
-    ASTERIA_HIP_TRY(upload_async(d_tj, tj.data(), tj.size() * sizeof(TransposeF32Job), stream));
     hipLaunchKernelGGL(transpose_f32_kernel, dim3(ttiles), dim3(256), 0, stream, d_tj, (int)tj.size());
     ASTERIA_HIP_TRY(hipGetLastError());
-    for (int i = 0; i < 4; ++i) {
-        ASTERIA_HIP_TRY(upload_async(d_g[i], g[i].data(), g[i].size() * sizeof(GemmProblem), stream));
+    for (int i = 0; i < 4; ++i)
         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[i], (int)g[i].size(), tiles, nullptr, stream)));
-    }
     return ASTERIA_OK;
 }

@@ -230,14 +230,16 @@ extern "C" asteria_status asteria_stats_update(const asteria_block *blocks, int 
     }
     for (int d = 0; d < 2; ++d) {
         GemmProblem *dL = nullptr, *dR = nullptr;
+        Uploads up(stream);
         if (!t.L[d].empty()) {
             dL = cv.take<GemmProblem>(t.L[d].size());
-            ASTERIA_HIP_TRY(upload_async(dL, t.L[d].data(), t.L[d].size() * sizeof(GemmProblem), stream));
+            ASTERIA_HIP_TRY(up.add(dL, t.L[d].data(), t.L[d].size() * sizeof(GemmProblem)));
         }
         if (!t.R[d].empty()) {
             dR = cv.take<GemmProblem>(t.R[d].size());
-            ASTERIA_HIP_TRY(upload_async(dR, t.R[d].data(), t.R[d].size() * sizeof(GemmProblem), stream));
+            ASTERIA_HIP_TRY(up.add(dR, t.R[d].data(), t.R[d].size() * sizeof(GemmProblem)));
         }
+        ASTERIA_HIP_TRY(up.flush());
         if (d == ASTERIA_F32) {
             if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(dL, (int)t.L[d].size(), t.tilesL[d], nullptr, stream)));
             if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, true, true>(dR, (int)t.R[d].size(), t.tilesR[d], nullptr, stream)));
@@ -249,14 +251,16 @@ extern "C" asteria_status asteria_stats_update(const asteria_block *blocks, int 
     // fp64 accumulation
     for (int d = 0; d < 2; ++d) {
         GemmProblem *dL = nullptr, *dR = nullptr;
+        Uploads up(stream);
         if (!t.L64[d].empty()) {
             dL = cv.take<GemmProblem>(t.L64[d].size());
-            ASTERIA_HIP_TRY(upload_async(dL, t.L64[d].data(), t.L64[d].size() * sizeof(GemmProblem), stream));
+            ASTERIA_HIP_TRY(up.add(dL, t.L64[d].data(), t.L64[d].size() * sizeof(GemmProblem)));
         }
         if (!t.R64[d].empty()) {
             dR = cv.take<GemmProblem>(t.R64[d].size());
-            ASTERIA_HIP_TRY(upload_async(dR, t.R64[d].data(), t.R64[d].size() * sizeof(GemmProblem), stream));
+            ASTERIA_HIP_TRY(up.add(dR, t.R64[d].data(), t.R64[d].size() * sizeof(GemmProblem)));
         }
+        ASTERIA_HIP_TRY(up.flush());
         if (d == ASTERIA_F32) {
             if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, false, false>(dL, (int)t.L64[d].size(), t.tilesL64[d], nullptr, stream)));
             if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, true, true>(dR, (int)t.R64[d].size(), t.tilesR64[d], nullptr, stream)));

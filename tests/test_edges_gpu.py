@@ -364,6 +364,24 @@ def test_roots_stay_inside_the_smallest_workspace_and_do_not_depend_on_its_size(
     assert all(torch.equal(got[0], X) for X in got[1:])
 
 
+@pytest.mark.parametrize("count", [1, 5, 28, 60])      # the tables of a call share the pieces they are uploaded in
+def test_batches_of_mixed_blocks_agree_with_single_calls(count):
+    g = torch.Generator(device=DEV).manual_seed(count)
+    items, single = [], []
+    for i in range(count):
+        m, n = 8 + i, 40 - i % 9
+        XL, XR, G = (torch.randn(a, b, generator=g, device=DEV) for a, b in ((m, m), (n, n), (m, n)))
+        G = G.bfloat16() if i % 3 else G
+        items.append((XL, G, XR, torch.empty(m, n, device=DEV)))
+        single.append(torch.empty(m, n, device=DEV))
+    ast.precondition(items)
+    for it, P in zip(items, single):
+        ast.precondition([(*it[:3], P)])
+    torch.cuda.synchronize()
+    for it, P in zip(items, single):
+        assert torch.equal(it[3], P)
+
+
 # sorted refresh: the columns' order where the ranks of one group of lanes end and the next begin
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 130, 257])
 def test_order_of_the_sorted_refresh(n):
