@@ -342,7 +342,7 @@ asteria_status asteria_precondition(const asteria_pblock *blocks, int nblocks,
  *       after everything already enqueued on `stream`, and `stream` waits for them before the call's
  *       work counts as done on it (events created and released inside the call).  A group's panel
  *       steps are a chain of small launches around a latency-bound Cholesky kernel; two chains side
- *       by side fill each other's gaps (1B-model workload: 186 ms with two streams, 205 ms on one).
+ *       by side fill each other's gaps (1B-model workload: 123 ms with two streams, 130 ms on one).
  *   sort  1: before the power iteration the columns of Q are put in the order of decreasing
  *       estimated eigenvalue q_i^T A q_i, ties by column index (the order SOAP gives its basis; the
  *       moments of asteria_soap_step then have to follow: asteria_soap_reproject).  `perm`, device

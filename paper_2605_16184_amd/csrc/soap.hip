@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256) void sort_estimate_kernel(const QrFactor *fs)
 }
 
 // rank of every estimate: the number of columns that come before it (larger estimate, or equal and a
-// lower index); perm[rank] = column.  n comparisons per column: cheap next to the products.
+// lower index); perm[rank] = column.
 // Sixteen lanes share a column: with one each, n serial comparisons (74 us at n = 1024) were as long as a panel's Gram
 // matrix, Cholesky factor and inverse.
 constexpr int RANK_LANES = 16, RANK_COLS = 256 / RANK_LANES;

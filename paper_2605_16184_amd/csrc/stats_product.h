@@ -157,7 +157,9 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
 // At n = 1024 a tile moves 128 KiB of statistics (256 in full storage) for 34 MFLOP, so both pipes matter and the
 // epilogue has to overlap other tiles' K loops: one slab of LDS and 128 registers, four workgroups per CU, rather
 // than a deeper pipeline and two.  The accumulators meet the old statistics in registers - a half wavefront covers
-// 128 consecutive bytes of a row, the mirror image is four consecutive floats per lane -, no pass through LDS.
+// 128 consecutive bytes of a row, the mirror image is four consecutive floats per lane -, no pass through LDS.  In a
+// whole tile they are read two pieces of 16 values ahead, and the fragments of a slab one step ahead: statistics of the 1.1B model,
+// packed, 3.57 -> 3.43 ms; of one layer, full storage, 239 -> 231 us.  Two stages of 32 k with loads a slab ahead: 3.59 ms, 238 us.
 __global__ __launch_bounds__(256, 4) void stats_product_kernel(const StatsEntry *__restrict__ entries, int count, int total,
                                                                              float beta)
 {
