@@ -274,6 +274,7 @@ struct RefreshTables {
     const int *pp[2];                  // cnt + 1: tiles of 128, of 256 columns of the whole-panel factors before i
     const int *pz;                     // cnt: first tile of factor i in the launch of its Z product
     const int *slot;                   // cnt: its entry there, s in z or -1 - s in zp
+    int share;                         // see refresh_shares
 };
 
 __global__ __launch_bounds__(128) void refresh_tables_kernel(QrFactor *fs, int cnt, RefreshTables T)
@@ -336,16 +337,28 @@ __global__ __launch_bounds__(128) void refresh_tables_kernel(QrFactor *fs, int c
     w2.start[0] = T.pp[0][i]; w2.start[1] = T.pp[1][i];
     T.p2[e] = w2;
     if (near > 0) {
+        if (!T.share && done > near) {
+            // no panel takes part in another's pass: this one's own part of it, in the entry that the panel before leaves free
+            static_assert(QR_AHEAD == 2, "one free entry per far part");
+            const int far = j - 1, e0 = T.off[far] + i;
+            PanelProblem v = w, v2 = w2;
+            v.N = v2.K = done - near;
+            v.start[0] = T.whole[i] * far; v.start[1] = T.whole[i] * ((far + 1) / 2);
+            T.f1[e0] = v;
+            T.f2[e0] = v2;
+        }
         w.X = F.Zt + (size_t)(done - near) * F.ldz; w.N = near;
         w.start[0] = T.whole[i] * (near / QR_PANEL); w.start[1] = T.whole[i] * ((near / QR_PANEL + 1) / 2);
         w2.X = F.Qout + (done - near); w2.K = near;
-    } else {
+    } else if (T.share) {
         w.slots = w2.slots = ahead;
         w.panels = w2.panels = min(ahead, F.n / QR_PANEL - j);
         w.start[0] *= ahead; w.start[1] *= ahead; w2.start[0] *= ahead; w2.start[1] *= ahead;
     }
-    T.f1[e] = w;
-    T.f2[e] = w2;
+    if (near > 0 || T.share) {
+        T.f1[e] = w;
+        T.f2[e] = w2;
+    }
     // P <- P - C Q_done: contraction over the finished rows, which the caller's Q already holds as
     // columns (k contiguous); the coefficients share the scale of the panel rows
     p.alpha = -1.0f; p.beta = 1.0f;
@@ -658,13 +671,21 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
 
 namespace {
 
-size_t refresh_factor_bytes(int n)
+// One region of a factor holds its projection coefficients and, between two projections, the partial Gram matrices of a
+// panel and the fp32 inverse factor.  Several panels have coefficients at a time where a pass over the finished rows
+// is shared: whole-panel factors with two panels beyond the first QR_AHEAD.
+size_t refresh_scratch_bytes(int n, bool share)
+{
+    const size_t panels = share && n % QR_PANEL == 0 && n >= 2 * QR_AHEAD * QR_PANEL ? QR_AHEAD : 1;
+    return std::max(Carver::need(panels * QR_PANEL * ld4(n), sizeof(float)),
+                    Carver::need(gram_doubles(n), sizeof(double)) + Carver::need((size_t)QR_PANEL * QR_PANEL, sizeof(float)));
+}
+
+size_t refresh_factor_bytes(int n, bool share)
 {
     const int np = (n + QR_PANEL - 1) / QR_PANEL;
     return Carver::need((size_t)n * ld4(n), sizeof(float)) +            // Z^T, becomes Q^T
-           Carver::need((size_t)std::min(QR_AHEAD, np) * QR_PANEL * ld4(n), sizeof(float)) +   // projection coefficients of the panels in work
-           Carver::need(gram_doubles(n), sizeof(double)) +              // partial Gram matrices of a panel
-           Carver::need((size_t)QR_PANEL * QR_PANEL, sizeof(float)) +   // fp32 inverse factor
+           refresh_scratch_bytes(n, share) +
            Carver::need((size_t)n, sizeof(double)) + Carver::need((size_t)n, sizeof(int)) +   // column estimates and order
            (size_t)(1 + 2 * np) * sizeof(GemmProblem) + (size_t)(4 * np) * sizeof(PanelProblem) + (size_t)(np + 6) * sizeof(int) + sizeof(QrFactor);
 }
@@ -680,6 +701,21 @@ size_t refresh_fixed_bytes(int n_max)
     return REFRESH_MAX_GROUPS * ((size_t)(5 * np + 4) * 256 + 4096);   // alignment slack of the per-panel tables, per group
 }
 
+// Whether panels share passes over the finished rows.  They do unless the workspace is too small for their coefficients, for
+// one factor or for the one pass that holds the whole batch without them; the sums of a factor and their order are the
+// same either way.
+bool refresh_shares(const asteria_factor *f, int nfactors, size_t fixed, size_t ws_bytes)
+{
+    size_t with = fixed, without = fixed, biggest = 0;
+    for (int i = 0; i < nfactors; ++i) {
+        const size_t b = refresh_factor_bytes(f[i].n, true);
+        with += b;
+        without += refresh_factor_bytes(f[i].n, false);
+        biggest = std::max(biggest, b);
+    }
+    return with <= ws_bytes || (without > ws_bytes && fixed + biggest <= ws_bytes);
+}
+
 }  // namespace
 
 extern "C" size_t asteria_soap_refresh_workspace_bytes(const asteria_factor *f, int nfactors, size_t *min_bytes)
@@ -691,8 +727,8 @@ extern "C" size_t asteria_soap_refresh_workspace_bytes(const asteria_factor *f, 
     for (int i = 0; i < nfactors; ++i) {
         const int n = f[i].n;
         if (n <= 0) return 0;
-        const size_t b = refresh_factor_bytes(n);
-        total += b;
+        const size_t b = refresh_factor_bytes(n, false);
+        total += refresh_factor_bytes(n, true);
         biggest = b > biggest ? b : biggest;
         n_max = n > n_max ? n : n_max;
     }
@@ -742,7 +778,8 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
     if (!ws) return ASTERIA_WORKSPACE_TOO_SMALL;
     if (reinterpret_cast<uintptr_t>(ws) & 255u) return ASTERIA_INVALID_ARG;   // workspace must be 256-byte aligned
     // the first factor must fit: checked before anything touches the device
-    if (refresh_fixed_bytes(n_all) + refresh_factor_bytes(f[0].n) > ws_bytes) return ASTERIA_WORKSPACE_TOO_SMALL;
+    if (refresh_fixed_bytes(n_all) + refresh_factor_bytes(f[0].n, false) > ws_bytes) return ASTERIA_WORKSPACE_TOO_SMALL;
+    const bool share = refresh_shares(f, nfactors, refresh_fixed_bytes(n_all), ws_bytes);
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_);
 
     // the caller's permutation array holds the factors' orders one after the other
@@ -755,7 +792,7 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         size_t used = refresh_fixed_bytes(n_all);
         int cnt = 0;
         while (first + cnt < nfactors) {
-            const size_t b = refresh_factor_bytes(f[first + cnt].n);
+            const size_t b = refresh_factor_bytes(f[first + cnt].n, share);
             if (used + b > ws_bytes) break;
             used += b;
             ++cnt;
@@ -788,9 +825,10 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             QrFactor F;
             memset(&F, 0, sizeof(F));
             F.Zt = cv.take<float>((size_t)n * ldz);
-            F.cbuf = cv.take<float>((size_t)std::min(QR_AHEAD, (n + QR_PANEL - 1) / QR_PANEL) * QR_PANEL * ldz);
-            F.gram = cv.take<double>(gram_doubles(n));
-            F.winv = cv.take<float>((size_t)QR_PANEL * QR_PANEL);
+            unsigned char *scratch = cv.take<unsigned char>(refresh_scratch_bytes(n, share));
+            F.cbuf = reinterpret_cast<float *>(scratch);
+            F.gram = reinterpret_cast<double *>(scratch);
+            F.winv = reinterpret_cast<float *>(scratch + Carver::need(gram_doubles(n), sizeof(double)));
             F.Qout = a.X; F.n = n; F.ldz = ldz; F.ldq = a.ldx; F.bad = 0; F.run = 0; F.skip3 = 1;
             F.out_index = idx[i];
             F.Qt = a.X; F.ldqt = a.ldx;
@@ -845,6 +883,7 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         rt.off = d_ints; rt.whole = d_ints + (nwhole - off); rt.pt = d_ints + (pt - off);
         rt.pp[0] = d_ints + (pp0 - off); rt.pp[1] = d_ints + (pp1 - off);
         rt.pz = d_ints + (pz - off); rt.slot = d_ints + (slot - off);
+        rt.share = share ? 1 : 0;
         Uploads up(stream);
         ASTERIA_HIP_TRY(up.add(d_q, q.data(), q.size() * sizeof(QrFactor)));
         ASTERIA_HIP_TRY(up.add(d_ints, ints.data(), ints.size() * sizeof(int)));
@@ -857,18 +896,25 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             constexpr int NY = decltype(ny_)::value, NX = decltype(nx_)::value;
             const int c = count[j], w = nwhole[c];
             GemmProblem *t1 = rt.t1 + off[j], *t2 = rt.t2 + off[j];
-            constexpr bool FIRST = NY == 1;
-            const PanelProblem *p1 = (FIRST ? rt.f1 : rt.p1) + off[j], *p2 = (FIRST ? rt.f2 : rt.p2) + off[j];
-            const int near = FIRST ? j % QR_AHEAD : 0, slots = FIRST && near == 0 ? std::min(QR_AHEAD, np_max - j) : 1;
-            const int c1 = near ? near : j;
-            const int narrow1 = w * c1 * slots, wide1 = w * ((c1 + 1) / 2) * slots, narrow2 = pp0[c] * slots, wide2 = pp1[c] * slots;
             ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, NY, NY, true>(t1, c, (c - w) * j, st, stream)));
-            if (pp_take_wide_tiles(wide1)) ASTERIA_HIP_TRY((launch_panel_product<NY, NY, 4>(p1, c, wide1, st, stream)));
-            else ASTERIA_HIP_TRY((launch_panel_product<NY, NY, 2>(p1, c, narrow1, st, stream)));
             ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, NY, NX, true>(t2, c, pt[c], st, stream)));
-            if (pp_take_wide_tiles(wide2)) ASTERIA_HIP_TRY((launch_panel_product<NY, NX, 4>(p2, c, wide2, st, stream)));
-            else ASTERIA_HIP_TRY((launch_panel_product<NY, NX, 2>(p2, c, narrow2, st, stream)));
-            return ASTERIA_OK;
+            // whole panels: `slots` of them against `rows` panels of finished rows
+            auto panels = [&](const PanelProblem *p1, const PanelProblem *p2, int rows, int slots) -> asteria_status {
+                const int narrow1 = w * rows * slots, wide1 = w * ((rows + 1) / 2) * slots, narrow2 = pp0[c] * slots, wide2 = pp1[c] * slots;
+                if (pp_take_wide_tiles(wide1)) ASTERIA_HIP_TRY((launch_panel_product<NY, NY, 4>(p1, c, wide1, st, stream)));
+                else ASTERIA_HIP_TRY((launch_panel_product<NY, NY, 2>(p1, c, narrow1, st, stream)));
+                if (pp_take_wide_tiles(wide2)) ASTERIA_HIP_TRY((launch_panel_product<NY, NX, 4>(p2, c, wide2, st, stream)));
+                else ASTERIA_HIP_TRY((launch_panel_product<NY, NX, 2>(p2, c, narrow2, st, stream)));
+                return ASTERIA_OK;
+            };
+            const int near = NY == 1 ? j % QR_AHEAD : 0, far = j - near;
+            if (near == 0) {
+                if (NY == 1 && share) return panels(rt.f1 + off[j], rt.f2 + off[j], j, std::min(QR_AHEAD, np_max - j));
+                return panels(rt.p1 + off[j], rt.p2 + off[j], j, 1);
+            }
+            if (!share && far > 0)
+                if (const asteria_status ps = panels(rt.f1 + off[far], rt.f2 + off[far], far, 1); ps != ASTERIA_OK) return ps;
+            return panels(rt.f1 + off[j], rt.f2 + off[j], near, 1);
         };
         hipLaunchKernelGGL(qr_scale_kernel, dim3(cnt), dim3(64), 0, stream, d_q, cnt);
         if (o.from_identity)

@@ -31,7 +31,7 @@ struct QrFactor {
     float a_scale, p_scale;
     const float *A;  // the statistic (read for its trace)
     int lda, pad2_;
-    float *cbuf;     // QR_PANEL rows x ldz for each panel in work: projection coefficients
+    float *cbuf;     // QR_PANEL rows x ldz for each panel in work: projection coefficients (gram and winv lie over them)
     // Where Q^T stands when a round starts (rows q_i^T: the k-contiguous operand of Z^T = Q^T A): the
     // caller's Q buffer, transposed in place, or a buffer of the caller that holds Q^T beside Q
     float *Qt;

@@ -228,6 +228,29 @@ def test_refresh_on_whole_panels(n, count):
         assert np.all(np.diag(R) >= 0)
 
 
+# workspaces from the smallest one to that of the whole batch: panels share passes over the finished rows where their coefficients fit
+@pytest.mark.parametrize("sizes", [(512, 640, 1024, 300, 768), (1024,), (1000, 100)])
+def test_refresh_does_not_depend_on_the_size_of_the_workspace(sizes):
+    As = [_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n) for n in sizes]
+    q0 = [W.haar(n, DEV, 11, n) for n in sizes]
+    full, least = ast.soap_refresh_workspace_bytes([(A, q) for A, q in zip(As, q0)])
+    got = []
+    for size in sorted({least, min(full, least + 600_000), max(least, full - 256), full}):
+        buf = torch.full((size + 4096,), 255, dtype=torch.uint8, device=DEV)      # NaN in whatever is read before it is written
+        Qs, info = [q.clone() for q in q0], torch.full((len(sizes),), -1, dtype=torch.int32, device=DEV)
+        ast.soap_refresh(list(zip(As, Qs)), info=info, ws=buf[:size])
+        torch.cuda.synchronize()
+        assert bool((info == 0).all()) and bool((buf[size:] == 255).all()), size
+        got.append(Qs)
+    for Qs in got[1:]:
+        assert all(torch.equal(q, r) for q, r in zip(Qs, got[0]))
+    for A, q, Q in zip(As, q0, got[0]):
+        Z = (A.double() @ q.double()).cpu().numpy()
+        Q = Q.double().cpu().numpy()
+        assert np.linalg.norm(Q.T @ Q - np.eye(len(Q))) / np.sqrt(len(Q)) <= 1e-5
+        assert np.linalg.norm(np.tril(Q.T @ Z, -1)) <= 1e-5 * np.linalg.norm(Z)
+
+
 @pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("blocks", [
     [(256, 256)] * 3 + [(250, 256)],                            # too few whole tiles: 128-wide tiles
