@@ -118,6 +118,14 @@ struct PairShape {
     static_assert(MI % 2 == 0 && NJ % 2 == 0 && (ST & (ST - 1)) == 0 && KR * TM == 256, "blocks of 32 x 32; stages by mask");
 };
 
+// Whether the 32 x 32 block at (br, bc) is one that a launch computes: on or below the diagonal and not wholly outside.  Nothing
+// is read for the others either: what lies beyond row n - 1 of the caller's X is not his matrix.
+__host__ __device__ inline bool pair_block_live(int br, int bc, int n) { return br >= bc && br < n && bc < n; }
+
+// Element v = 4 (2 u + w) + e of a lane in a 32 x 32 block: row 16 u + lane % 16, column 16 w + 4 (lane / 16) + e
+__host__ __device__ inline int pair_elem_row(int br, int v, int lane) { return br + 16 * (v >> 3) + (lane & 15); }
+__host__ __device__ inline int pair_elem_col(int bc, int v, int lane) { return bc + 16 * ((v >> 2) & 1) + 4 * (lane >> 4) + (v & 3); }
+
 // two values (scaled) -> their hi terms and their lo terms, both rounded to nearest
 __device__ __forceinline__ void pair_words2(float a, float b, uint32_t &hi, uint32_t &lo)
 {
@@ -357,14 +365,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
         const bool test = st == ST_LAST && S.q_limit > 0.0f && ((op == OP_SQ && degree == 2) || op == OP_CUBE);
         const float q1 = uniform(S.q[1] / s1), q2 = uniform(S.q[2] / s2), q3 = uniform(S.q[3] * inv_c), q0 = S.q[0];
         float rsum = 0.0f;
-        // Element v = 4 (2 u + w) + e of a 32 x 32 block: row 16 u + r16, column 16 w + 4 g16 + e.  (The lane's part of every
-        // address is made anew for every block, not kept through the K loop.)
+        // The lane's part of every address is made anew for every block, not kept through the K loop.
         int ln = lane;
         asm volatile("" : "+v"(ln));
         int r16 = ln & 15, g16 = ln >> 4;
         ASTERIA_LDS char *ws = lds + SH::SCRATCH + wave * 4096;
-        auto row_of = [&](int br, int v) { return br + 16 * (v >> 3) + r16; };
-        auto col_of = [&](int bc, int v) { return bc + 16 * ((v >> 2) & 1) + 4 * g16 + (v & 3); };
+        auto row_of = [&](int br, int v) { return pair_elem_row(br, v, ln); };
+        auto col_of = [&](int bc, int v) { return pair_elem_col(bc, v, ln); };
         // linear term of a block: 4 columns of a row, hi in [0 .. 1], lo in [2 .. 3]
         auto load_own = [&](const char *O, int br, int bc, uint32_t (&raw)[16]) __attribute__((always_inline)) {
 #pragma unroll
@@ -476,6 +483,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
         uint32_t ahead[16];                           // linear term of the next block
         auto prefetch = [&](int q) __attribute__((always_inline)) {
             const int br = row0 + wm * 16 * MI + (q / JB) * 32, bc = col0 + wn * 16 * NJ + (q % JB) * 32;
+            if (!pair_block_live(br, bc, n)) return;
             if (O1) load_own(O1, br, bc, ahead);
             else if (op == OP_X) load_x(br, bc, ahead);
         };
@@ -491,7 +499,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
             for (int v = 0; v < 16; ++v) raw[v] = ahead[v];
             if (O2) load_own(O2, br, bc, ahead);      // (a second linear term takes the place of the block ahead)
             else if (q + 1 < NB) prefetch(q + 1);
-            if (br < bc || br >= n || bc >= n) {
+            if (!pair_block_live(br, bc, n)) {
                 if (O2 && q + 1 < NB) prefetch(q + 1);
                 continue;
             }

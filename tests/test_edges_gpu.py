@@ -39,6 +39,7 @@ def _root_error(A, X, eps):
     [130] * 190 + [97, 128, 256],                               # 128-wide tiles
     [514] * 192,                                                # a batch whose recurrences run one workgroup each
     [761] * 118 + [33, 520, 768, 770],                          # 256-wide tiles: remainders of 249, 8 and 2, transposed panels
+    [76, 80, 520] * 60, [900] * 70 + [1040] * 4,                # 128- and 256-wide tiles: a block row beyond the last row
 ])
 def test_roots_at_the_edges(kind, eps, sizes):
     made = {}
