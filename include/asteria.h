@@ -347,7 +347,8 @@ asteria_status asteria_precondition(const asteria_pblock *blocks, int nblocks,
  *       estimated eigenvalue q_i^T A q_i, ties by column index (the order SOAP gives its basis; the
  *       moments of asteria_soap_step then have to follow: asteria_soap_reproject).  `perm`, device
  *       int32, the factors' orders one after the other (sum of n entries; perm[r] = input column
- *       that became column r before the QR), or NULL.
+ *       that became column r before the QR), or NULL.  It is an order of all columns whatever A and Q hold
+ *       (estimates that are not a number come last).
  *   from_identity  1: start from Q = I, whatever Q holds (first basis of a new statistic).
  *   rounds  number of (power iteration, QR) rounds in the call, >= 1: from the identity, a few
  *       sorted rounds are orthogonal iteration towards the eigenbasis - the device-side stand-in for

@@ -215,7 +215,8 @@ __global__ __launch_bounds__(256) void sort_estimate_kernel(const QrFactor *fs)
     for (int k = lane; k < F.n; k += 64) s += (double)q[k] * (double)z[k];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) F.est[row] = s;
+    // the order has to be total, or ranks collide and entries of perm stay unwritten: not a number comes last
+    if (lane == 0) F.est[row] = s == s ? s : -INFINITY;
 }
 
 // rank of every estimate: the number of columns that come before it (larger estimate, or equal and a

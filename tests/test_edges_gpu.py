@@ -417,3 +417,24 @@ def test_order_of_the_sorted_refresh(n):
     ast.soap_refresh([(A, Q)], sort=True, perm=perm[0])
     torch.cuda.synchronize()
     assert torch.equal(perm[0].long(), torch.sort(-lam[shuffle], stable=True).indices)
+
+
+# sorted refresh of statistics that are not finite: reported, in an order that still is one, beside factors that are
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_order_of_the_sorted_refresh_with_estimates_that_are_no_numbers(bad):
+    sizes = [257, 130, 256, 16, 130, 1]
+    As = [_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n) if n > 1 else torch.ones(1, 1, device=DEV) for n in sizes]
+    As[1][5, 5] = bad                                  # one element: every column of A Q
+    As[2][:] = bad
+    As[3][2, 2] = bad
+    Q = [W.haar(n, DEV, 11, n) if n != 16 else torch.eye(16, device=DEV) for n in sizes]     # identity: one column of A Q only
+    alone = [q.clone() for q in Q]
+    info = torch.full((len(sizes),), -1, dtype=torch.int32, device=DEV)
+    perm = torch.full((sum(sizes),), -1, dtype=torch.int32, device=DEV)
+    ast.soap_refresh(list(zip(As, Q)), info=info, sort=True, perm=perm)
+    ast.soap_refresh([(As[0], alone[0])], sort=True)
+    torch.cuda.synchronize()
+    assert [int(i != 0) for i in info] == [0, 1, 1, 1, 0, 0]
+    for n, p in zip(sizes, perm.split(sizes)):
+        assert torch.equal(p.long().sort().values, torch.arange(n, device=DEV)), n
+    assert torch.equal(Q[0], alone[0])
