@@ -443,7 +443,7 @@ asteria_status asteria_soap_reproject(const asteria_rblock *blocks, int nblocks,
  * k-major; 32..255 the 16-bit kernel, 32 + (2 = A operand bf16 in memory) + (4 = B operand bf16 in
  * memory) + (64 = A split into two terms) + (128 = B split into two terms), so 224 = both operands
  * fp32 split in two terms (the products on two-term storage too) and 96 = A split, B one term; 512 the
- * statistics; 513 and 514 the 256 x 256 tiles of a split fp32 matrix with another one or with a bf16 matrix, 515 the
+ * statistics; 513 and 514 whole tiles of a split fp32 matrix with another one or with a bf16 matrix, 515 the
  * panel products of the SOAP refresh;
  * 300 + NS the int8 kernels on NS slices or digits (304, 305).  Not thread safe.                    */
 asteria_status asteria_profile_enable(int max_launches);

@@ -238,21 +238,26 @@ __device__ __forceinline__ void gemm_bf16_mainloop(floatx16 (&acc)[2][2], const 
     }
 }
 
-template <typename TA, typename TB, int NTA, int NTB, bool F16 = false>
-__global__ __launch_bounds__(256, ASTERIA_BF16_MIN_WAVES) void gemm_bf16_grouped_kernel(const GemmProblem *__restrict__ probs, int nprobs,
-                                                                int total_tiles, const int *__restrict__ state)
+template <typename TA, typename TB, int NTA, int NTB>
+constexpr size_t gemm_bf16_lds()
+{
+    constexpr int BK = (NTA + NTB > 2) ? ASTERIA_SPLIT_BK : 64;
+    return sizeof(uint16_t) * ((NTA + NTB > 2) ? ASTERIA_SPLIT_STAGES : 2) *
+           (size_t)(Bf16Stage<TA, NTA, BK>::LDS_ELEMS + Bf16Stage<TB, NTB, BK>::LDS_ELEMS);
+}
+
+// tile t_global of a launch, 256 threads; gemm_bf16_lds() bytes at smem_raw
+template <typename TA, typename TB, int NTA, int NTB, bool F16>
+__device__ __forceinline__ void gemm_bf16_tile(const GemmProblem *__restrict__ probs, int nprobs, int t_global, const int *__restrict__ state,
+                                               unsigned char *smem_raw)
 {
     using MM = MmaBf16;
     constexpr int BK = (NTA + NTB > 2) ? ASTERIA_SPLIT_BK : 64;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
     ASTERIA_LDS uint16_t *smem = (ASTERIA_LDS uint16_t *)smem_raw;
     // the reduction scratch of the epilogue reuses the operand buffer (free after the K loop): with
     // no static LDS two workgroups of the split variants (64 KiB each) fit one CU's 160 KiB
     float *red = reinterpret_cast<float *>(smem_raw);
 
-    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
-    const int t_global = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
-    if (t_global >= total_tiles) return;
     int lo = 0, hi = nprobs - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -323,14 +328,23 @@ __global__ __launch_bounds__(256, ASTERIA_BF16_MIN_WAVES) void gemm_bf16_grouped
 }
 
 template <typename TA, typename TB, int NTA, int NTB, bool F16 = false>
+__global__ __launch_bounds__(256, ASTERIA_BF16_MIN_WAVES) void gemm_bf16_grouped_kernel(const GemmProblem *__restrict__ probs, int nprobs,
+                                                                int total_tiles, const int *__restrict__ state)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
+    const int t_global = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
+    if (t_global >= total_tiles) return;
+    gemm_bf16_tile<TA, TB, NTA, NTB, F16>(probs, nprobs, t_global, state, smem_raw);
+}
+
+template <typename TA, typename TB, int NTA, int NTB, bool F16 = false>
 inline hipError_t launch_gemm_bf16_grouped(const GemmProblem *probs, int nprobs, int total_tiles,
                                            const int *state, hipStream_t stream)
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
-    constexpr int BK = (NTA + NTB > 2) ? ASTERIA_SPLIT_BK : 64;
     auto kern = gemm_bf16_grouped_kernel<TA, TB, NTA, NTB, F16>;
-    constexpr size_t lds = sizeof(uint16_t) * ((NTA + NTB > 2) ? ASTERIA_SPLIT_STAGES : 2) *
-                           (size_t)(Bf16Stage<TA, NTA, BK>::LDS_ELEMS + Bf16Stage<TB, NTB, BK>::LDS_ELEMS);
+    constexpr size_t lds = gemm_bf16_lds<TA, TB, NTA, NTB>();
     static bool configured[MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured); e != hipSuccess) return e;
     const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;

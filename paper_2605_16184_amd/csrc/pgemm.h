@@ -1,7 +1,7 @@
 // Guard-free grouped GEMM over 16-bit terms on the gfx950 matrix cores (v_mfma_f32_16x16x32, fp32 accumulation).
 //
-// One launch walks a device table of problems  C = A B^T  (A is M x K, B is N x K, both k-contiguous, M and N multiples of
-// 256, K of 32: the callers send other shapes to the guarded kernels).  A is a plain fp32 matrix that the loader cuts into two
+// One launch walks a device table of problems  C = A B^T  (A is M x K, B is N x K, both k-contiguous, M and N whole
+// tiles, K a multiple of 32: the callers send other shapes to the guarded kernels).  A is a plain fp32 matrix that the loader cuts into two
 // bf16 terms (the value rounded, the remainder rounded) while it stages it; B is the same (NTB = 2: three products per
 // block, lo hi, hi lo, hi hi, 16 bits of both operands) or a plain bf16 matrix (NTB = 1: two products).  With F16 the terms
 // are fp16 ones (22 bits) of the operands times powers of two that the problem states.
@@ -56,22 +56,21 @@ __device__ __forceinline__ void pg_split_f16(float a, float b, float scale, uint
 // Measured (this kernel, the one before): preconditioned update of the 1.1B model 10.0 ms, 12.2; SOAP step 43.9 ms, 52.6 (four
 // rotations, Adam 5.0 of it).  SOAP refresh of that model with its products A Q here (F16), on the 128 x 128 tiles of gemm_bf16.h:
 // 135.0 ms, 147.3.
-constexpr int PG_TILE = 256, PG_BK = 32, PG_WAVES = 8;
-constexpr size_t pg_lds_bytes(int ntb) { return 2u * (size_t)PG_TILE * (128 + 64 * ntb); }
+// TILE = 128: 4 wavefronts (2 x 2) of 64 x 64, two workgroups on a CU, for launches too small for the large tiles.  Every element has
+// the same sums in the same order, so which of the two a launch takes does not show in its result.
+constexpr int PG_TILE = 256, PG_SMALL_TILE = 128, PG_BK = 32;
+constexpr size_t pg_lds_bytes(int ntb, int tile) { return 2u * (size_t)tile * (128 + 64 * ntb); }
 
-template <int NTB, bool F16 = false>
-__global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProblem *__restrict__ probs, int nprobs, int total_tiles)
+// tile t_global of a launch, 2 TILE threads; pg_lds_bytes at smem_raw
+template <int NTB, bool F16, int TILE>
+__device__ __forceinline__ void pgemm_tile(const PlaneProblem *__restrict__ probs, int nprobs, int t_global, unsigned char *smem_raw)
 {
-    constexpr int MI = 4, NJ = 8;
-    constexpr uint32_t ROWB = 64u * NTB, STAGE_A = PG_TILE * 128u, STAGE_B = PG_TILE * ROWB;
+    constexpr int MI = 4, NJ = TILE / 32;
+    static_assert(NJ == 8 || NJ == 4, "two columns of wavefronts, 64 rows each; four pieces to stage behind NJ - 1 blocks");
+    constexpr uint32_t ROWB = 64u * NTB, STAGE_A = TILE * 128u, STAGE_B = TILE * ROWB;
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-    extern __shared__ __align__(16) unsigned char smem_raw[];
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem_raw;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-
-    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
-    const int t_global = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
-    if (t_global >= total_tiles) return;
     int plo = 0, phi = nprobs - 1;
     while (plo < phi) {
         const int mid = (plo + phi + 1) >> 1;
@@ -79,7 +78,7 @@ __global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProb
     }
     const PlaneProblem P = probs[plo];   // by value: the fields stay in scalar registers across the stores below
     const int lt = t_global - P.tile_start, ti = lt / P.tiles_n, tj = lt % P.tiles_n;
-    const int row0 = ti * PG_TILE, col0 = tj * PG_TILE, nk = P.K / PG_BK;
+    const int row0 = ti * TILE, col0 = tj * TILE, nk = P.K / PG_BK;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
 
@@ -132,7 +131,7 @@ __global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProb
     const int r16 = lane & 15, g16 = lane >> 4;
     const uint32_t fch = (uint32_t)((g16 ^ ((r16 >> 1) & 7)) * 16);
     const uint32_t fa = lds0 + (uint32_t)(wm * 64 + r16) * 128u + fch;
-    const uint32_t fb = lds0 + 2 * STAGE_A + (uint32_t)(wn * 128 + r16) * ROWB + (NTB == 2 ? fch : (uint32_t)((g16 ^ ((r16 >> 2) & 3)) * 16));
+    const uint32_t fb = lds0 + 2 * STAGE_A + (uint32_t)(wn * 16 * NJ + r16) * ROWB + (NTB == 2 ? fch : (uint32_t)((g16 ^ ((r16 >> 2) & 3)) * 16));
     auto frag = [](uint32_t p) __attribute__((always_inline)) { return *(const ASTERIA_LDS u32x4 *)(uintptr_t)p; };
     // D = B-rows x A-rows: a lane holds 4 consecutive columns of one row of C
     auto mma = [](u32x4 a, u32x4 b, floatx4 c) __attribute__((always_inline)) {
@@ -187,8 +186,9 @@ __global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProb
                 for (int i = 0; i < MI; ++i) acc[i][j] = mma(ah[i], b[q][1], acc[i][j]);
 #pragma unroll
             for (int i = 0; i < MI; ++i) acc[i][j] = mma(ah[i], b[q][0], acc[i][j]);
-            if (j < 4) stage(na, nb, j);
-            if (j == 4) gload(kt + 2);
+            if (NJ == 8 ? j < 4 : j == 0) stage(na, nb, j);
+            if (NJ == 4 && j < 3) stage(na, nb, j + 1);
+            if (j == (NJ == 8 ? 4 : 2)) gload(kt + 2);
             __builtin_amdgcn_sched_barrier(0);
         }
         read_a(ah, 0u);
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProb
                     *(ASTERIA_LDS floatx4 *)(ws + r * 128 + (((4 * w + (ln >> 4)) ^ (r & 7)) * 16)) = acc[2 * i + u][2 * j + w];
                 }
             __builtin_amdgcn_wave_barrier();
-            const int br = row0 + wm * 64 + i * 32, bc = col0 + wn * 128 + j * 32 + 4 * e8;
+            const int br = row0 + wm * 64 + i * 32, bc = col0 + wn * 16 * NJ + j * 32 + 4 * e8;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int r = q * 8 + rr;
@@ -243,10 +243,20 @@ __global__ __launch_bounds__(64 * PG_WAVES, 2) void pgemm_kernel(const PlaneProb
         }
 }
 
-// a plain fp32 matrix can feed pgemm_kernel: 16-byte aligned rows, whole tiles and slabs
-inline bool pg_f32_operand_ok(const void *p, int rows, int k, int ld)
+template <int NTB, bool F16 = false>
+__global__ __launch_bounds__(2 * PG_TILE, 2) void pgemm_kernel(const PlaneProblem *__restrict__ probs, int nprobs, int total_tiles)
 {
-    return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld % 4) == 0 && (rows % PG_TILE) == 0 &&
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
+    const int t_global = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
+    if (t_global >= total_tiles) return;
+    pgemm_tile<NTB, F16, PG_TILE>(probs, nprobs, t_global, smem_raw);
+}
+
+// a plain fp32 matrix can feed pgemm_kernel: 16-byte aligned rows, whole tiles and slabs
+inline bool pg_f32_operand_ok(const void *p, int rows, int k, int ld, int tile = PG_TILE)
+{
+    return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld % 4) == 0 && (rows % tile) == 0 &&
            (k % PG_BK) == 0;
 }
 
@@ -274,11 +284,12 @@ inline hipError_t launch_pgemm(const PlaneProblem *probs, int nprobs, int total_
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
     auto kern = pgemm_kernel<NTB, F16>;
+    constexpr size_t lds = pg_lds_bytes(NTB, PG_TILE);
     static bool configured[MAX_DEVICES] = {};
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), pg_lds_bytes(NTB), configured); e != hipSuccess) return e;
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured); e != hipSuccess) return e;
     const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
     profile_begin(kind, stream);
-    hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(64 * PG_WAVES), pg_lds_bytes(NTB), stream, probs, nprobs, total_tiles);
+    hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(2 * PG_TILE), lds, stream, probs, nprobs, total_tiles);
     profile_end(stream);
     return hipGetLastError();
 }

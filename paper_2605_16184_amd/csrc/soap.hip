@@ -257,13 +257,44 @@ __global__ __launch_bounds__(256) void sort_gather_kernel(const QrFactor *fs, in
     for (int k = threadIdx.x; k < F.n; k += 256) dst[k] = src[k];
 }
 
+// Products of fp32 matrices over two fp16 terms each, in one launch: `tiles` small tiles of whole-tile problems, and the tiles of
+// gemm_bf16.h of those with a remainder in `ragged`.  (4 ragged tiles of n = 76 in a launch of their own: 23 us on top of the 59
+// of 456 whole ones.)
+__global__ __launch_bounds__(2 * PG_SMALL_TILE, 2) void product_f16_kernel(const PlaneProblem *__restrict__ probs, int nprobs, int tiles,
+                                                                           const GemmProblem *__restrict__ ragged, int nragged, int ragged_tiles)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int all = tiles + ragged_tiles, per_xcd = (all + NUM_XCD - 1) / NUM_XCD;
+    const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
+    if (t >= all) return;
+    if (t < tiles) pgemm_tile<2, true, PG_SMALL_TILE>(probs, nprobs, t, smem_raw);
+    else gemm_bf16_tile<float, float, 2, 2, true>(ragged, nragged, t - tiles, nullptr, smem_raw);
+}
+
+hipError_t launch_product_f16(const PlaneProblem *probs, int nprobs, int tiles, const GemmProblem *ragged, int nragged,
+                              int ragged_tiles, hipStream_t stream)
+{
+    const int all = tiles + ragged_tiles, per_xcd = (all + NUM_XCD - 1) / NUM_XCD;
+    if (all <= 0) return hipSuccess;
+    constexpr size_t lds = pg_lds_bytes(2, PG_SMALL_TILE);
+    static_assert(lds >= gemm_bf16_lds<float, float, 2, 2>(), "either kind of tile");
+    static bool configured[MAX_DEVICES] = {};
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(product_f16_kernel), lds, configured); e != hipSuccess) return e;
+    profile_begin(tiles > 0 ? 513 : 224, stream);
+    hipLaunchKernelGGL(product_f16_kernel, dim3(per_xcd * NUM_XCD), dim3(2 * PG_SMALL_TILE), lds, stream, probs, nprobs, tiles, ragged, nragged,
+                       ragged_tiles);
+    profile_end(stream);
+    return hipGetLastError();
+}
+
 // Problem tables of one group of factors, written on the device from the factor descriptors (as host
 // tables they travel as kernel arguments: about 500 upload launches per group of the 1B-model workload).
 // The factors of a group are sorted by size, largest first, so those that have panel j are the first
 // count_j of the group and the entry of factor i in any table of panel j is entry i of that panel's run.
 struct RefreshTables {
-    GemmProblem *z;                    // Z^T = Q^T A of the factors on 128 x 128 tiles
-    PlaneProblem *zp;                  // the same of those on 256 x 256 tiles
+    GemmProblem *z;                    // Z^T = Q^T A of the factors that are no whole tiles
+    PlaneProblem *zp;                  // the same of those that are, the first zp_large on large tiles
+    int zp_large;
     // projection coefficients, projection: a factor has an entry in both kinds of table, with no tiles in the one that it
     // does not use (whole-panel factors: p1, p2)
     GemmProblem *t1, *t2;
@@ -294,7 +325,7 @@ __global__ __launch_bounds__(128) void refresh_tables_kernel(QrFactor *fs, int c
         const int slot = T.slot[i];
         if (slot < 0) {
             PlaneProblem g = {};
-            g.M = g.N = g.K = F.n; g.tiles_n = F.n / PG_TILE;
+            g.M = g.N = g.K = F.n; g.tiles_n = F.n / (-1 - slot < T.zp_large ? PG_TILE : PG_SMALL_TILE);
             g.A = F.Qt; g.lda = F.ldqt; g.B = F.A; g.ldb = F.lda; g.C32 = F.Zt; g.ldc32 = F.ldz;
             g.sa = QR_UNIT_SCALE; g.sb_dev = a_scale;
             g.tile_start = T.pz[i];
@@ -848,25 +879,35 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             for (int j = 0; j < (n + QR_PANEL - 1) / QR_PANEL; ++j) ++count[j];
         }
         for (int j = 0; j < np_max; ++j) off[j + 1] = off[j] + count[j];
-        // the Z products of whole-tile factors run on 256 x 256 tiles, where these fill the device
-        auto whole = [](const QrFactor &F) {
-            return pg_f32_operand_ok(F.Qt, F.n, F.n, F.ldqt) && pg_f32_operand_ok(F.A, F.n, F.n, F.lda);
+        // The Z products of whole-tile factors run on the kernel of pgemm.h and the others on that of gemm_bf16.h, whose sums have
+        // another order: by the factor alone, so that its result does not depend on what it is batched with.  Only the
+        // width of the tiles goes by the group: large ones beyond 128, where small ones need a second round of the chip (two
+        // workgroups a CU).  Product in us, small / large tiles, by large ones: n = 256 64 19 / 28, 128: 26 / 31, 192: 36 / 35, 512:
+        // 98 / 85; n = 512 128 37 / 44, 160: 48 / 46, 256: 64 / 57, 320: 88 / 91; n = 1024 64 40 / 70, 128: 60 / 75, 160: 83 / 77, 256:
+        // 111 / 93, 320: 140 / 152, 512: 220 / 180; n = 2048 128 109 / 136, 192: 162 / 148, 512: 413 / 332.  (Small tiles of
+        // gemm_bf16.h: n = 1024 64 47, 128: 65.)
+        auto whole = [](const QrFactor &F, int edge) {
+            return pg_f32_operand_ok(F.Qt, F.n, F.n, F.ldqt, edge) && pg_f32_operand_ok(F.A, F.n, F.n, F.lda, edge);
         };
-        long long large_tiles = 0, large_k = 0;
+        long long large_tiles = 0;
+        int large = 0;
         for (const QrFactor &F : q)
-            if (whole(F)) {
-                const long long t = (long long)(F.n / PG_TILE) * (F.n / PG_TILE);
-                large_tiles += t;
-                large_k += t * F.n;
+            if (whole(F, PG_TILE)) {
+                large_tiles += (long long)(F.n / PG_TILE) * (F.n / PG_TILE);
+                ++large;
             }
-        const bool large = pg_take_large_tiles(large_tiles, large_k);
-        int nz = 0, nzp = 0, tiles = 0, tiles_p = 0;
+        if (large_tiles <= 128) large = 0;
+        int nz = 0, nl = 0, ns = large, tiles = 0, tiles_l = 0, tiles_s = 0;
         for (int i = 0; i < cnt; ++i) {
             const int n = q[i].n, tn = (n + BN - 1) / BN;
-            if (large && whole(q[i])) {
-                slot[i] = -1 - nzp++;
-                pz[i] = tiles_p;
-                tiles_p += (n / PG_TILE) * (n / PG_TILE);
+            if (large && whole(q[i], PG_TILE)) {
+                slot[i] = -1 - nl++;
+                pz[i] = tiles_l;
+                tiles_l += (n / PG_TILE) * (n / PG_TILE);
+            } else if (whole(q[i], PG_SMALL_TILE)) {
+                slot[i] = -1 - ns++;
+                pz[i] = tiles_s;
+                tiles_s += (n / PG_SMALL_TILE) * (n / PG_SMALL_TILE);
             } else {
                 slot[i] = nz++;
                 pz[i] = tiles;
@@ -876,7 +917,8 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         const int entries = off[np_max];
         RefreshTables rt;
         rt.z = cv.take<GemmProblem>(nz);
-        rt.zp = cv.take<PlaneProblem>(nzp);
+        rt.zp = cv.take<PlaneProblem>(ns);
+        rt.zp_large = large;
         rt.t1 = cv.take<GemmProblem>(entries); rt.t2 = cv.take<GemmProblem>(entries);
         rt.f1 = cv.take<PanelProblem>(entries); rt.f2 = cv.take<PanelProblem>(entries);
         rt.p1 = cv.take<PanelProblem>(entries); rt.p2 = cv.take<PanelProblem>(entries);
@@ -928,8 +970,8 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             hipLaunchKernelGGL(keep_qt_kernel, dim3(tpr32 * tpr32, (unsigned)cnt), dim3(256), 0, stream, d_q);
         for (int round = 0; round < o.rounds; ++round) {
         hipLaunchKernelGGL(transpose_inplace_kernel, dim3(tpr32 * tpr32, (unsigned)cnt), dim3(256), 0, stream, d_q);
-        ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(rt.z, nz, tiles, nullptr, stream)));
-        ASTERIA_HIP_TRY((launch_pgemm<2, true>(rt.zp, nzp, tiles_p, stream, 513)));
+        ASTERIA_HIP_TRY((launch_pgemm<2, true>(rt.zp, large, tiles_l, stream, 513)));
+        ASTERIA_HIP_TRY(launch_product_f16(rt.zp + large, ns - large, tiles_s, rt.z, nz, tiles, stream));
         if (o.sort) {
             // order the columns by q_i^T A q_i = (row i of Q^T) . (row i of Z^T), largest first: the rows of
             // Z^T are gathered in that order (A (Q P) = (A Q) P: sorting the basis first, as SOAP does, and

@@ -186,7 +186,7 @@ def test_statistics_at_the_edges(m, n, packed):
 
 
 @pytest.mark.parametrize("sizes", [[1, 2, 15, 16, 17, 33, 48], [127, 128, 129, 191, 192, 193], [385, 1153],
-                                   [256] * 49 + [250]])          # products on 256-wide tiles, and a ragged factor beside them
+                                   [256] * 49 + [250], [256] * 129 + [384]])    # products on whole tiles of 128 with a ragged factor beside them, of both
 def test_refresh_at_the_edges(sizes):
     As = [_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n) for n in sizes]
     Q0 = [W.haar(n, DEV, 11, n) for n in sizes]
@@ -250,6 +250,29 @@ def test_refresh_does_not_depend_on_the_size_of_the_workspace(sizes):
         Q = Q.double().cpu().numpy()
         assert np.linalg.norm(Q.T @ Q - np.eye(len(Q))) / np.sqrt(len(Q)) <= 1e-5
         assert np.linalg.norm(np.tril(Q.T @ Z, -1)) <= 1e-5 * np.linalg.norm(Z)
+
+
+# a batch on the large tiles of the product A Q, its parts on the small ones; factors of either kernel
+def test_refresh_does_not_depend_on_the_batch():
+    sizes = [256] * 110 + [512, 768, 300, 640, 1024]
+    made = {n: (_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n), W.haar(n, DEV, 11, n)) for n in set(sizes)}
+    As, q0 = zip(*[made[n] for n in sizes])
+    full, least = ast.soap_refresh_workspace_bytes(list(zip(As, q0)))
+    streams = [torch.cuda.Stream() for _ in range(2)]
+
+    def run(which, size=None, aux=None):
+        Qs = [q0[i].clone() for i in which]
+        ws = torch.full((size,), 255, dtype=torch.uint8, device=DEV) if size else None
+        ast.soap_refresh([(As[i], q) for i, q in zip(which, Qs)], ws=ws, aux_streams=aux)
+        torch.cuda.synchronize()
+        return Qs
+
+    every = list(range(len(sizes)))
+    want = run(every)
+    for size, aux in ((least, None), (least + (full - least) // 3, None), (full, streams)):
+        assert all(torch.equal(a, b) for a, b in zip(run(every, size, aux), want)), size
+    for i in (0, 110, 111, 112, 113, 114):
+        assert torch.equal(run([i])[0], want[i]), sizes[i]
 
 
 @pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
