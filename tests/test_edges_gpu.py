@@ -252,6 +252,25 @@ def test_refresh_does_not_depend_on_the_size_of_the_workspace(sizes):
         assert np.linalg.norm(np.tril(Q.T @ Z, -1)) <= 1e-5 * np.linalg.norm(Z)
 
 
+# a workspace for half of the batch without the coefficients that shared passes over the finished rows take: two passes, not more;
+# the product A Q is one launch a pass
+@pytest.mark.parametrize("extra,passes", [(0, 2), (-256, 4)])    # two factors a pass; just not two: one each
+def test_refresh_takes_no_more_passes_for_shared_ones(extra, passes):
+    n, count = 512, 4
+    A = _with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n)
+    Qs = [W.haar(n, DEV, 11, n) for _ in range(count)]
+    f = [(A, q) for q in Qs]
+    (full1, least), (full4, _) = ast.soap_refresh_workspace_bytes(f[:1]), ast.soap_refresh_workspace_bytes(f)
+    fixed = full1 - (full4 - full1) // (count - 1)
+    ws = torch.empty(fixed + 2 * (least - fixed) + extra, dtype=torch.uint8, device=DEV)
+    ast.profile_enable(4096)
+    ast.soap_refresh(f, ws=ws)
+    torch.cuda.synchronize()
+    kinds = [k for _, k in ast.profile_collect()]
+    assert kinds.count(513) == passes
+    assert all(torch.equal(q, Qs[0]) for q in Qs)
+
+
 # a batch on the large tiles of the product A Q, its parts on the small ones; factors of either kernel
 def test_refresh_does_not_depend_on_the_batch():
     sizes = [256] * 110 + [512, 768, 300, 640, 1024]
