@@ -126,6 +126,9 @@ __host__ __device__ inline bool pair_block_live(int br, int bc, int n) { return 
 __host__ __device__ inline int pair_elem_row(int br, int v, int lane) { return br + 16 * (v >> 3) + (lane & 15); }
 __host__ __device__ inline int pair_elem_col(int bc, int v, int lane) { return bc + 16 * ((v >> 2) & 1) + 4 * (lane >> 4) + (v & 3); }
 
+// Whether X is read 4 columns at a time in a block at column bc (rows kept inside the matrix): all of its columns are the matrix's
+__host__ __device__ inline bool pair_x_whole(int bc, int n, bool xvec) { return xvec && bc + 32 <= n; }
+
 // two values (scaled) -> their hi terms and their lo terms, both rounded to nearest
 __device__ __forceinline__ void pair_words2(float a, float b, uint32_t &hi, uint32_t &lo)
 {
@@ -169,6 +172,56 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
     const int n = F.n, rowb = F.rowb, p = k & 1, row0 = ti * TM, col0 = tj * TM, nk = plane_groups(n);
     const RootOperands o = root_operands(op, degree == 1);
 
+    const char *O1 = nullptr, *O2 = nullptr;
+    char *C = op == OP_X ? F.X[p ^ 1] : F.P[o.C];
+    if (op != OP_X && o.O1 >= 0) O1 = F.P[o.O1];
+    if (op != OP_X && o.O2 >= 0) O2 = F.P[o.O2];
+    ASTERIA_GLOBAL float *X = (ASTERIA_GLOBAL float *)F.Xout;
+    const int ldx = F.ldx;
+    const bool xvec = (ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(F.Xout) & 15u) == 0;
+    // linear term of a block: 4 columns of a row, hi in [0 .. 1], lo in [2 .. 3]
+    auto load_own = [&](const char *O, int br, int bc, int ln, uint32_t (&raw)[16]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const char *q = O + (size_t)min(br + 16 * u + (ln & 15), n - 1) * rowb + (min(bc, n - 1) >> 5) * 128 + (ln >> 4) * 8;
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                const u32x2_t a = *(const ASTERIA_GLOBAL u32x2_t *)(q + w * 32), c = *(const ASTERIA_GLOBAL u32x2_t *)(q + w * 32 + 64);
+                uint32_t *d = &raw[4 * (2 * u + w)];
+                d[0] = a[0]; d[1] = a[1]; d[2] = c[0]; d[3] = c[1];
+            }
+        }
+    };
+    // fp32 X: its lower triangle until the last update, which completes the caller's matrix.  (On the diagonal the elements above it are
+    // read with the others and not used.)
+    auto load_x = [&](int br, int bc, int ln, uint32_t (&raw)[16]) __attribute__((always_inline)) {
+        const bool whole = pair_x_whole(bc, n, xvec);
+#pragma unroll
+        for (int uw = 0; uw < 4; ++uw) {
+            const int row = pair_elem_row(br, 4 * uw, ln), col = pair_elem_col(bc, 4 * uw, ln);
+            const ASTERIA_GLOBAL float *x = X + (size_t)min(row, n - 1) * ldx + col;
+            if (whole) {
+                const u32x4 t = *(const ASTERIA_GLOBAL u32x4 *)x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) raw[4 * uw + e] = t[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) raw[4 * uw + e] = row < n && row >= col + e ? __builtin_bit_cast(uint32_t, x[e]) : 0u;
+            }
+        }
+    };
+    uint32_t ahead[16];                               // linear term of the next block
+    auto prefetch = [&](int br, int bc, int ln) __attribute__((always_inline)) {
+        if (!pair_block_live(br, bc, n)) return;
+        if (O1) load_own(O1, br, bc, ln, ahead);
+        else if (op == OP_X) load_x(br, bc, ln, ahead);
+    };
+    // that of the first block before anything else, where there are registers to hold it through the K loop: a product of a small
+    // matrix is little more than what it waits for (roots of 400 of n = 64: 670 us, 688 with the load behind the loop)
+    constexpr bool EARLY = TM < 256;
+    const int rw = row0 + wm * 16 * MI, cw = col0 + wn * 16 * NJ;
+    if (EARLY) prefetch(rw, cw, lane);
+
     // ---- memory -> LDS: half of the wavefronts bring rows of A, half of B
     const bool loads_b = wave >= NW / 2;
     const char *src = op == OP_X ? (loads_b ? F.P[degree == 1 ? 0 : 2] : F.X[p]) : F.P[loads_b ? o.B : o.A];
@@ -210,6 +263,27 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
 #pragma unroll
     for (int s = 0; s < ST - 1; ++s) issue(s, 0, NI);
     issue(ST - 1, 0, H);
+
+    // ---- what the values of the blocks are made of: loaded and worked out while the operands are on their way
+    float sA, sB, s1 = 1.0f, s2 = 1.0f, sC;
+    if (op == OP_X) {
+        sA = sC = S.x_scale; sB = degree == 1 ? PAIR_SCALE_M : PAIR_SCALE_E;
+    } else {
+        sA = pair_scale_of(op, o.A); sB = pair_scale_of(op, o.B);
+        if (O1) s1 = pair_scale_of(op, o.O1);
+        if (O2) s2 = pair_scale_of(op, o.O2);
+        sC = pair_scale_of(op, o.C);
+    }
+    const RootProd pc = S.prod[op];
+    const float k1 = uniform((float)(pc.own1 * (double)(sC / s1))), k2 = uniform((float)(pc.own2 * (double)(sC / s2)));
+    const float kg = uniform((float)(pc.gam * (double)sC / ((double)sA * (double)sB)));
+    const bool to_user = op == OP_X && st == ST_LAST;
+    const bool first_x = k == 0 && (op == OP_SQ || op == OP_CUBE);    // X_1 = X_0 T_0, X_0 a multiple of I
+    const float inv_c = uniform(1.0f / sC);
+    const float x1a = S.x1a, x1e = uniform(-S.x1s * inv_c), inv_x = uniform(1.0f / S.x_scale);
+    // the test before the last update, by the product that completes E
+    const bool test = st == ST_LAST && S.q_limit > 0.0f && ((op == OP_SQ && degree == 2) || op == OP_CUBE);
+    const float q1 = uniform(S.q[1] / s1), q2 = uniform(S.q[2] / s2), q3 = uniform(S.q[3] * inv_c), q0 = S.q[0];
 
     // ---- LDS -> registers -> products
     const int a_end = (ti + 1) * (TM / 32), b_end = (tj + 1) * (TM / 32);
@@ -338,32 +412,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
         }
 
         // ---- the block's value and its planes; in a diagonal tile its mirror image too
-        const char *O1 = nullptr, *O2 = nullptr;
-        char *C;
-        float sA, sB, s1 = 1.0f, s2 = 1.0f, sC;
-        if (op == OP_X) {
-            C = F.X[p ^ 1];
-            sA = sC = S.x_scale; sB = degree == 1 ? PAIR_SCALE_M : PAIR_SCALE_E;
-        } else {
-            C = F.P[o.C];
-            sA = pair_scale_of(op, o.A); sB = pair_scale_of(op, o.B);
-            if (o.O1 >= 0) { O1 = F.P[o.O1]; s1 = pair_scale_of(op, o.O1); }
-            if (o.O2 >= 0) { O2 = F.P[o.O2]; s2 = pair_scale_of(op, o.O2); }
-            sC = pair_scale_of(op, o.C);
-        }
-        const RootProd pc = S.prod[op];
-        const float k1 = uniform((float)(pc.own1 * (double)(sC / s1))), k2 = uniform((float)(pc.own2 * (double)(sC / s2)));
-        const float kg = uniform((float)(pc.gam * (double)sC / ((double)sA * (double)sB)));
-        const bool to_user = op == OP_X && st == ST_LAST;
-        const bool first_x = k == 0 && (op == OP_SQ || op == OP_CUBE);    // X_1 = X_0 T_0, X_0 a multiple of I
-        const float inv_c = uniform(1.0f / sC);
-        const float x1a = S.x1a, x1e = uniform(-S.x1s * inv_c), inv_x = uniform(1.0f / S.x_scale);
-        ASTERIA_GLOBAL float *X = (ASTERIA_GLOBAL float *)F.Xout;
-        const int ldx = F.ldx;
-        const bool xvec = (ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(F.Xout) & 15u) == 0;
-        // the test before the last update, by the product that completes E
-        const bool test = st == ST_LAST && S.q_limit > 0.0f && ((op == OP_SQ && degree == 2) || op == OP_CUBE);
-        const float q1 = uniform(S.q[1] / s1), q2 = uniform(S.q[2] / s2), q3 = uniform(S.q[3] * inv_c), q0 = S.q[0];
         float rsum = 0.0f;
         // The lane's part of every address is made anew for every block, not kept through the K loop.
         int ln = lane;
@@ -372,39 +420,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
         ASTERIA_LDS char *ws = lds + SH::SCRATCH + wave * 4096;
         auto row_of = [&](int br, int v) { return pair_elem_row(br, v, ln); };
         auto col_of = [&](int bc, int v) { return pair_elem_col(bc, v, ln); };
-        // linear term of a block: 4 columns of a row, hi in [0 .. 1], lo in [2 .. 3]
-        auto load_own = [&](const char *O, int br, int bc, uint32_t (&raw)[16]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const char *q = O + (size_t)min(br + 16 * u + r16, n - 1) * rowb + (min(bc, n - 1) >> 5) * 128 + g16 * 8;
-#pragma unroll
-                for (int w = 0; w < 2; ++w) {
-                    const u32x2_t a = *(const ASTERIA_GLOBAL u32x2_t *)(q + w * 32), c = *(const ASTERIA_GLOBAL u32x2_t *)(q + w * 32 + 64);
-                    uint32_t *d = &raw[4 * (2 * u + w)];
-                    d[0] = a[0]; d[1] = a[1]; d[2] = c[0]; d[3] = c[1];
-                }
-            }
-        };
         auto own_value = [&](const uint32_t (&raw)[16], int v) __attribute__((always_inline)) {
             const uint32_t *d = &raw[v & ~3];
             const f16x4_t a = __builtin_bit_cast(f16x4_t, (u32x2_t){d[0], d[1]}), c = __builtin_bit_cast(f16x4_t, (u32x2_t){d[2], d[3]});
             return (float)a[v & 3] + (float)c[v & 3];
-        };
-        // fp32 X: its lower triangle until the last update, which completes the caller's matrix
-        auto load_x = [&](int br, int bc, uint32_t (&raw)[16]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int uw = 0; uw < 4; ++uw) {
-                const int row = row_of(br, 4 * uw), col = col_of(bc, 4 * uw);
-                const ASTERIA_GLOBAL float *x = X + (size_t)min(row, n - 1) * ldx + col;
-                if (br > bc && xvec) {
-                    const u32x4 t = *(const ASTERIA_GLOBAL u32x4 *)x;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) raw[4 * uw + e] = t[e];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) raw[4 * uw + e] = row < n && row >= col + e ? __builtin_bit_cast(uint32_t, x[e]) : 0u;
-                }
-            }
         };
         auto store_x = [&](int br, int bc, const float (&x)[16], float c) __attribute__((always_inline)) {
 #pragma unroll
@@ -419,8 +438,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
                         if (row >= col + e) d[e] = x[4 * uw + e] * c;
             }
         };
-        // Planes of a block through the scratch, one row of the block per 128 bytes: [32 hi][32 lo], chunks swizzled by row.  On the
-        // diagonal the upper triangle is taken from the lower one.  Elements beyond n are zero
+        // Planes of a block through the scratch, one row of the block per 128 bytes: [32 hi][32 lo], chunks swizzled by row.  Elements
+        // beyond n are zero.  On the diagonal the upper triangle is taken from the lower one: every element from the block or from its
+        // mirror image, by row and column.  (Written there element by element, up to 64 stores of 2 bytes a lane, it lay on the
+        // critical path of small factors.  Roots of 400 of n = 64: 688 us so, 715 then.)
         auto store_block = [&](char *D, int br, int bc, const float (&val)[16]) __attribute__((always_inline)) {
             const bool diag = br == bc;
             __builtin_amdgcn_wave_barrier();
@@ -432,39 +453,25 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
                     uint32_t h0, h1, l0, l1;
                     pair_words2(q[0], q[1], h0, l0);
                     pair_words2(q[2], q[3], h1, l1);
-                    const int r = 16 * u + r16;
-                    if (!diag) {
-                        ASTERIA_LDS char *d = ws + r * 128 + (g16 & 1) * 8;
-                        const int ch = 2 * w + (g16 >> 1);
-                        *(ASTERIA_LDS u32x2_t *)(d + (ch ^ (r & 7)) * 16) = (u32x2_t){h0, h1};
-                        *(ASTERIA_LDS u32x2_t *)(d + ((4 + ch) ^ (r & 7)) * 16) = (u32x2_t){l0, l1};
-                    } else {
-                        const uint32_t hw[2] = {h0, h1}, lw[2] = {l0, l1};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int c = 16 * w + 4 * g16 + e;
-                            if (r < c) continue;
-                            const uint16_t hi = (uint16_t)(hw[e >> 1] >> (16 * (e & 1))), lo = (uint16_t)(lw[e >> 1] >> (16 * (e & 1)));
-                            *(ASTERIA_LDS uint16_t *)(ws + c * 128 + ((r >> 3) ^ (c & 7)) * 16 + (r & 7) * 2) = hi;
-                            *(ASTERIA_LDS uint16_t *)(ws + c * 128 + ((4 + (r >> 3)) ^ (c & 7)) * 16 + (r & 7) * 2) = lo;
-                            *(ASTERIA_LDS uint16_t *)(ws + r * 128 + ((c >> 3) ^ (r & 7)) * 16 + (c & 7) * 2) = hi;
-                            *(ASTERIA_LDS uint16_t *)(ws + r * 128 + ((4 + (c >> 3)) ^ (r & 7)) * 16 + (c & 7) * 2) = lo;
-                        }
-                    }
+                    const int r = 16 * u + r16, ch = 2 * w + (g16 >> 1);
+                    ASTERIA_LDS char *d = ws + r * 128 + (g16 & 1) * 8;
+                    *(ASTERIA_LDS u32x2_t *)(d + (ch ^ (r & 7)) * 16) = (u32x2_t){h0, h1};
+                    *(ASTERIA_LDS u32x2_t *)(d + ((4 + ch) ^ (r & 7)) * 16) = (u32x2_t){l0, l1};
                 }
             __builtin_amdgcn_wave_barrier();
+            if (!diag)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {                   // whole lines of 8 rows
-                const int r = q * 8 + (ln >> 3), ch = ln & 7;
-                const u32x4 t = *(const ASTERIA_LDS u32x4 *)(ws + r * 128 + ((ch ^ (r & 7)) * 16));
-                if (br + r < n) *(ASTERIA_GLOBAL u32x4 *)(D + (size_t)(br + r) * rowb + (bc >> 5) * 128 + ch * 16) = t;
-            }
-            if (ti == tj && !diag) {
+                for (int q = 0; q < 4; ++q) {                   // whole lines of 8 rows
+                    const int r = q * 8 + (ln >> 3), ch = ln & 7;
+                    const u32x4 t = *(const ASTERIA_LDS u32x4 *)(ws + r * 128 + ((ch ^ (r & 7)) * 16));
+                    if (br + r < n) *(ASTERIA_GLOBAL u32x4 *)(D + (size_t)(br + r) * rowb + (bc >> 5) * 128 + ch * 16) = t;
+                }
+            if (ti == tj) {
                 // columns 16 (q & 1) .. of the block, hi or lo, as rows of the mirror image: a group of 16 lanes brings 8 rows of
                 // the block; lane 4 e + i of it supplies the address of columns 4 i .. of row e, lane j receives column j
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int rh = q & 1, term = q >> 1;
+                    const int rh = q & 1, term = q >> 1, cl = 16 * rh + r16;
                     u32x2_t t[2];
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {
@@ -472,35 +479,38 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
                         t[u] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                                    (ASTERIA_LDS s16x4_t *)(ws + r * 128 + ((ch ^ (r & 7)) * 16) + (r16 & 1) * 8)));
                     }
-                    const int c = bc + 16 * rh + r16;
-                    if (c < n) *(ASTERIA_GLOBAL u32x4 *)(D + (size_t)c * rowb + (br >> 5) * 128 + term * 64 + g16 * 16) =
-                        (u32x4){t[0][0], t[0][1], t[1][0], t[1][1]};
+                    u32x4 out = {t[0][0], t[0][1], t[1][0], t[1][1]};
+                    if (diag) {
+                        const u32x4 own = *(const ASTERIA_LDS u32x4 *)(ws + cl * 128 + (((term * 4 + g16) ^ (cl & 7)) * 16));
+                        const int below = cl + 1 - 8 * g16;           // of the 8 columns from 8 g16 on, those on and below the diagonal
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const uint32_t m = below >= 2 * e + 2 ? ~0u : (below == 2 * e + 1 ? 0xffffu : 0u);
+                            out[e] ^= (out[e] ^ own[e]) & m;
+                        }
+                    }
+                    if (bc + cl < n) *(ASTERIA_GLOBAL u32x4 *)(D + (size_t)(bc + cl) * rowb + (br >> 5) * 128 + term * 64 + g16 * 16) = out;
                 }
             }
             __builtin_amdgcn_wave_barrier();
         };
         constexpr int JB = JA / 2 ? JA / 2 : 1, NB = (MI / 2) * (JN / 2);
-        uint32_t ahead[16];                           // linear term of the next block
-        auto prefetch = [&](int q) __attribute__((always_inline)) {
-            const int br = row0 + wm * 16 * MI + (q / JB) * 32, bc = col0 + wn * 16 * NJ + (q % JB) * 32;
-            if (!pair_block_live(br, bc, n)) return;
-            if (O1) load_own(O1, br, bc, ahead);
-            else if (op == OP_X) load_x(br, bc, ahead);
-        };
-        if constexpr (NB > 0) prefetch(0);
+        auto block_row = [&](int q) { return rw + (q / JB) * 32; };
+        auto block_col = [&](int q) { return cw + (q % JB) * 32; };
+        if constexpr (NB > 0 && !EARLY) prefetch(rw, cw, ln);
         // one copy of the code for all blocks: only taking the sums out of their registers differs
 #pragma unroll 1
         for (int q = 0; q < NB; ++q) {
-            const int br = row0 + wm * 16 * MI + (q / JB) * 32, bc = col0 + wn * 16 * NJ + (q % JB) * 32;
+            const int br = block_row(q), bc = block_col(q);
             asm volatile("" : "+v"(ln));
             r16 = ln & 15; g16 = ln >> 4;
             uint32_t raw[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) raw[v] = ahead[v];
-            if (O2) load_own(O2, br, bc, ahead);      // (a second linear term takes the place of the block ahead)
-            else if (q + 1 < NB) prefetch(q + 1);
+            if (O2) load_own(O2, br, bc, ln, ahead);      // (a second linear term takes the place of the block ahead)
+            else if (q + 1 < NB) prefetch(block_row(q + 1), block_col(q + 1), ln);
             if (!pair_block_live(br, bc, n)) {
-                if (O2 && q + 1 < NB) prefetch(q + 1);
+                if (O2 && q + 1 < NB) prefetch(block_row(q + 1), block_col(q + 1), ln);
                 continue;
             }
             float val[16];
@@ -515,8 +525,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
             // sums over the symmetric matrix: an element below the diagonal counts twice
             auto add_sum = [&](int v, float x) __attribute__((always_inline)) {
                 const int row = row_of(br, v), col = col_of(bc, v);
-                if (inside) rsum += 2.0f * x * x;
-                else if (row < n && row >= col) rsum += row == col ? x * x : 2.0f * x * x;
+                const float y = inside || (row < n && row >= col) ? x : 0.0f;
+                rsum += inside || row != col ? 2.0f * y * y : y * y;
             };
             auto on_diag = [&](int v) { return row_of(br, v) == col_of(bc, v); };
             if (test) {
@@ -536,7 +546,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
 #pragma unroll
                 for (int v = 0; v < 16; ++v) val[v] += k1 * __builtin_bit_cast(float, raw[v]);
             }
-            if (O2 && q + 1 < NB) prefetch(q + 1);
+            if (O2 && q + 1 < NB) prefetch(block_row(q + 1), block_col(q + 1), ln);
             if (op == OP_M)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) add_sum(v, val[v] * inv_c - (on_diag(v) ? 1.0f : 0.0f));
@@ -582,7 +592,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
         }
     };
     // column blocks of this wavefront with something on or below the diagonal and inside the matrix
-    const int rw = row0 + wm * 16 * MI, cw = col0 + wn * 16 * NJ;
     const int c = rw >= n ? 0 : min(ti == tj ? rw + 16 * MI : n, n) - cw;
     if (c <= 0) body(std::integral_constant<int, 0>{});
     else if (NJ == 8 && c <= 64) body(std::integral_constant<int, NJ == 8 ? 4 : NJ>{});

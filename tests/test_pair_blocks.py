@@ -25,8 +25,7 @@ static long stray(int n, unsigned char *seen)
                     for (int lane = 0; lane < 64; ++lane)
                         for (int v = 0; v < 16; ++v) {
                             const int row = pair_elem_row(br, v, lane), col = pair_elem_col(bc, v, lane);
-                            const bool whole = br > bc;               // 4 columns in one load, the row kept inside the matrix
-                            if (whole) bad += col >= n;
+                            if (pair_x_whole(bc, n, true)) bad += col >= n;    // 4 columns in one load, the row kept inside the matrix
                             if (row < n && col <= row) seen[row * n + col] = 1;
                         }
                 }
