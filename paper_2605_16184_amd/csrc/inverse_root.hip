@@ -962,7 +962,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     int *d_state = cv.take<int>(cnt);
     int *d_flags = cv.take<int>(cnt);
     std::vector<FactorDev> fd(cnt);
-    int tri_total = 0, tri256_total = 0, tri_max = 0, n_max = 0;
+    int tri_total = 0, tri64_total = 0, tri256_total = 0, tri_max = 0, n_max = 0;
     double work128 = 0.0, work256 = 0.0, rows = 0.0;
     bool any_packed = false, any_full = false;
     double a_min = 1.0, elems = 0.0;
@@ -978,7 +978,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         F.rowb = pair_row_bytes(n); F.ld64 = ld2(n);
         F.ntri = tri_tiles(n);
         F.tile_start = tri_total; tri_total += F.ntri;
-        tri256_total += tri_tiles_of(n, 256);
+        tri64_total += tri_tiles_of(n, 64); tri256_total += tri_tiles_of(n, 256);
         work128 += pair_work(n, 128); work256 += pair_work(n, 256); rows += n;
         F.npart = plane_partials(n);
         F.flags = d_flags + i;
@@ -1009,7 +1009,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
             }
         F.P[0] = chain[2]; F.P[1] = chain[2] + pair; F.P[2] = F.P[3] = chain[3];
     }
-    const int edge = pair_tile_edge(tri_total, tri256_total, work128, work256, rows / cnt);
+    const int edge = pair_tile_edge(tri64_total, tri_total, tri256_total, tri_tiles(n_max), work128, work256, rows / cnt);
     int pair_total = 0;
     for (FactorDev &F : fd) { F.tile_start_p = pair_total; pair_total += tri_tiles_of(F.n, edge); }
     uint2 *d_map = cv.take<uint2>(tri_total), *d_map_p = edge == 128 ? d_map : cv.take<uint2>(pair_total);

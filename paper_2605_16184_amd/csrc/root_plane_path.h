@@ -527,18 +527,23 @@ __global__ __launch_bounds__(256) void plane_finalize_kernel(const FactorDev *fd
 }
 
 // ---- host --------------------------------------------------------------------------------------------
-// Edge of the tiles of a pass's pair products.  Small ones where there are fewer workgroups than the chip has places for.
-// A single product of the kind E2 in us, 64 / 128-wide tiles, by tiles of 128: n = 512 160 24 / 25, 300 37 / 36, 440 50 / 40;
-// n = 1024 144 36 / 37, 288 56 / 53; n = 200 180 17 / 18, 450 29 / 25; n = 2048 272 97 / 93.
+// Edge of the tiles of a pass's pair products.  Two workgroups of either the 64- or the 128-wide tiles fit a CU, so small ones pay
+//   - where they are at most twice as many (n <= 64 and n in 129 .. 192): a large one is mostly empty;
+//   - up to three of them per CU, and up to four where the large ones are more than one per CU.
+// Roots in us at eps = 1e-6, 64 / 128-wide, by tiles of 128: n = 64 120 353 / 422, 400 616 / 687, 1000 1179 / 1352; n = 160 255 466 /
+// 558, 501 744 / 784, 999 1314 / 1371; n = 200 and 333 in equal numbers 180 762 / 794, 252 839 / 814, 279 929 / 1007, 342 1053 / 1048, 396
+// 1165 / 1116, 999 2405 / 2153; n = 512 200 859 / 884, 240 926 / 888, 280 1038 / 1130, 300 1149 / 1144, 400 1347 / 1269; n = 1024 180 1086 /
+// 1141, 216 1197 / 1152, 252 1249 / 1179, 288 1526 / 1505.
 // Large ones (one workgroup per CU) from two and a half rounds of the chip on, for matrices that their tiles cover no worse than
-// 128-wide ones do: 128 / 256-wide, by tiles of 256: n = 1024 320 143 / 183, 640 258 / 278, 960 380 / 374, 2000 788 / 771, 6000 2311 /
-// 2249; n = 2048 288 247 / 289, 576 435 / 459, 1152 865 / 802; n = 4096 544 828 / 880, 1088 1658 / 1530; n = 900 3000 953 / 919; but
-// n = 512 1800 415 / 431 (short K: the stores weigh more), n = 640 3000 617 / 687 (a quarter more work).  Products with the X update
-// gain 3 to 8 % more.
-constexpr int PLANE_SMALL_TILES = 250, PLANE_LARGE_TILES = 700, PLANE_LARGE_N = 512;
-inline int pair_tile_edge(int tri128, int tri256, double work128, double work256, double n_mean)
+// 128-wide ones do.  128 over 256-wide, by tiles of 256: n = 768 558 0.96, 600 0.99, 650 1.00, 702 1.01, 750 1.04, 798 0.97, 852 1.00,
+// 900 1.01, 1002 1.04; n = 900 560 0.97, 650 1.00, 700 1.01, 800 0.99, 850 0.99, 900 1.01, 1000 1.04; n = 1024 500 1.06, 560 0.99, 600
+// 1.00, 650 1.01, 700 1.02, 750 1.06, 800 1.01, 900 1.04, 1000 1.06; n = 2048 396 1.01, 504 1.09, 612 1.06, 684 1.07, 900 1.05; n = 4096
+// 408 1.06, 680 1.08; but n = 600 700 0.88, 1000 0.90 (a quarter more work), and n = 512 1800 0.96 (short K: the stores weigh more).
+constexpr int PLANE_SMALL_TILES = 250, PLANE_LARGE_TILES = 700, PLANE_LARGE_N = 512;   // the first: of a factor that small tiles can serve
+inline int pair_tile_edge(int tri64, int tri128, int tri256, int tri128_max, double work128, double work256, double n_mean)
 {
-    if (tri128 < PLANE_SMALL_TILES) return 64;
+    const bool small = tri64 <= 2 * tri128 || tri64 <= 768 || (tri128 > 256 && tri64 <= 1024);
+    if (small && tri128_max < PLANE_SMALL_TILES) return 64;
     return tri256 >= PLANE_LARGE_TILES && work256 <= 1.03 * work128 && n_mean > (double)PLANE_LARGE_N ? 256 : 128;
 }
 // work of a factor's pair product in tiles of 128 x 128 x n: a diagonal tile of 256 takes three quarters of a whole one

@@ -40,6 +40,7 @@ def _root_error(A, X, eps):
     [514] * 192,                                                # a batch whose recurrences run one workgroup each
     [761] * 118 + [33, 520, 768, 770],                          # 256-wide tiles: remainders of 249, 8 and 2, transposed panels
     [76, 80, 520] * 60, [900] * 70 + [1040] * 4,                # 128- and 256-wide tiles: a block row beyond the last row
+    [64, 33] * 150, [200, 333] * 32, [200, 333] * 40,           # many small tiles: as many as large ones; below four per CU; beyond
 ])
 def test_roots_at_the_edges(kind, eps, sizes):
     made = {}
@@ -61,6 +62,21 @@ def test_roots_at_the_edges(kind, eps, sizes):
         assert bool((Xs[i] == Xs[i].T).all())
         first = sizes.index(n)
         assert torch.equal(Xs[first], Xs[i])                    # the same factor anywhere in the batch
+
+
+# mostly small factors, for which small tiles pay, beside one that is too large for them
+def test_roots_of_small_factors_beside_a_large_one():
+    sizes = [2700] + [64] * 1100
+    made = {n: _with_spectrum(n, _spectrum("power", n), 7, n) for n in set(sizes)}
+    Xs = [torch.full_like(made[n], float("nan")) for n in sizes]
+    alone = {n: torch.full_like(made[n], float("nan")) for n in made}
+    info = torch.full((len(sizes),), -1, dtype=torch.int32, device=DEV)
+    ast.inverse_root([(made[n], X) for n, X in zip(sizes, Xs)], 1e-6, info=info)
+    for n in made:
+        ast.inverse_root([(made[n], alone[n])], 1e-6)
+    torch.cuda.synchronize()
+    assert bool((info == 0).all())
+    assert all(torch.equal(X, alone[n]) for n, X in zip(sizes, Xs))
 
 
 def _dense(n, kind):
