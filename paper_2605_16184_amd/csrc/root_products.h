@@ -628,14 +628,17 @@ inline hipError_t launch_pair_product(const FactorDev *fd, const FactorScal *fs,
 // while the other assembles and stores.  In a slab the lower digits of A come first; the products of its top digit, most of
 // all, cover the turn to the next slab.  Addresses and uniform factors of the epilogue are kept out of vector registers
 // (192 are sums at NS = 5).
+// Where at most 64 rows are left (BI = 1) a wavefront takes 32 of them: the epilogue of a block, an fp64 sum per level and element,
+// is longer than its products there.  A product of 226 factors of n = 64, (5, 6): 14.0 us, 20.1 with half of the wavefronts taking 64
+// rows each.
 // Measured, kind E2: 8 of n = 4096 (5, 6) 4.24 ms = 2540 TOP/s issued, the matrix pipe full at the 1.75 GHz that power
 // leaves (5.87 before, of which 1.1 went with the order of the tiles); 300 of n = 1024 (4, 4) 1.84 ms, 2.07 before, the
 // epilogue a fifth of it; (5, 6) 3.22, 3.45 before.
-template <int NS, int L>
+template <int NS, int L, int BI>
 __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal &S, int op, int k, int degree, int ti, int tj, int half,
                                            unsigned char *smem)
 {
-    constexpr int CPR = 2 * NS, ROWL = CPR * 16, BI = 2, RB = 128;
+    constexpr int CPR = 2 * NS, ROWL = CPR * 16, RB = 64 * BI;
     using Loader = PlaneLoader<CPR, RB, 64, 4>;
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -672,7 +675,8 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
         for (int i = 0; i < BI; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[l][i][v] = 0;
-    const bool above = row0 + (wm + 1) * 32 * BI - 1 < col0 + wn * 32;     // this wavefront's part lies above the diagonal
+    // this wavefront's part lies above the diagonal or beyond the last row
+    const bool above = row0 + (wm + 1) * 32 * BI - 1 < col0 + wn * 32 || row0 + wm * 32 * BI >= n;
     // address of digit 0; digit s lies 2 s chunks on, which the swizzle of 8 chunks makes an exclusive or
     uint32_t pa = lds0 + (uint32_t)(wm * 32 * BI + r) * ROWL + (uint32_t)((h ^ sw) * 16);
     uint32_t pb = lds0 + (uint32_t)(RB + wn * 32 + r) * ROWL + (uint32_t)((h ^ sw) * 16);
@@ -809,13 +813,14 @@ __global__ __launch_bounds__(256, 2) void digit_product_kernel(const FactorDev *
     const FactorScal &S = fs[f];
     if (S.tier != TIER_DIGIT || S.ns != NS) return;
     const int ti = (int)(tile.y >> 16), tj = (int)(tile.y & 0xffffu), half = w & 1;
-    if constexpr (NS == 4) {
-        if (S.levels == 4) digit_tile<4, 4>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
-        else digit_tile<4, 5>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
-    } else {
-        if (S.levels == 5) digit_tile<5, 5>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
-        else digit_tile<5, 6>(fd[f], S, op, k, degree, ti, tj, half, plane_smem);
-    }
+    const FactorDev &F = fd[f];
+    auto run = [&](auto bi) __attribute__((always_inline)) {
+        constexpr int BI = decltype(bi)::value;
+        if (S.levels == NS) digit_tile<NS, NS, BI>(F, S, op, k, degree, ti, tj, half, plane_smem);
+        else digit_tile<NS, NS + 1, BI>(F, S, op, k, degree, ti, tj, half, plane_smem);
+    };
+    if (F.n - ti * 128 <= 64) run(std::integral_constant<int, 1>{});
+    else run(std::integral_constant<int, 2>{});
 }
 
 template <int NS>

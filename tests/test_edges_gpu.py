@@ -41,6 +41,7 @@ def _root_error(A, X, eps):
     [761] * 118 + [33, 520, 768, 770],                          # 256-wide tiles: remainders of 249, 8 and 2, transposed panels
     [76, 80, 520] * 60, [900] * 70 + [1040] * 4,                # 128- and 256-wide tiles: a block row beyond the last row
     [64, 33] * 150, [200, 333] * 32, [200, 333] * 40,           # many small tiles: as many as large ones; below four per CU; beyond
+    [64, 65, 96, 97, 192, 193] * 40,                            # digit tiles with 64 rows left, one more, 32 more and less
 ])
 def test_roots_at_the_edges(kind, eps, sizes):
     made = {}
