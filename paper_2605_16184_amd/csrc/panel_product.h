@@ -12,6 +12,7 @@
 // Refresh of the 1.1B model (gemm_bf16.h: 135.0 ms): 128.3; with two panels a pass in the first sweep 123.1.
 #pragma once
 #include "gemm.h"
+#include "gemm_bf16.h"
 #include "pgemm.h"
 
 namespace asteria {
@@ -31,20 +32,18 @@ struct PanelProblem {
     int start[2];            // first tile of 128, of 256 rows of X
 };
 
+constexpr size_t pp_lds_bytes(int ny) { return 2u * PP_ROWS * 64u * (size_t)ny; }
+
+// tile t_global of a launch, 256 threads; pp_lds_bytes at smem_raw
 template <int NY, int NX, int MI>
-__global__ __launch_bounds__(256, 2) void panel_product_kernel(const PanelProblem *__restrict__ probs, int nprobs, int total_tiles,
-                                                               const int *__restrict__ state)
+__device__ __forceinline__ void panel_product_tile(const PanelProblem *__restrict__ probs, int nprobs, int t_global, const int *__restrict__ state,
+                                                   unsigned char *smem_raw)
 {
     constexpr int NJ = PP_ROWS / 16, TX = 64 * MI, WSEL = MI == 4 ? 1 : 0;
     constexpr uint32_t ROWB = 64u * NY, STAGE = PP_ROWS * ROWB;
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-    extern __shared__ __align__(16) unsigned char smem_raw[];
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem_raw;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-
-    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
-    const int t_global = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
-    if (t_global >= total_tiles) return;
     int plo = 0, phi = nprobs - 1;
     while (plo < phi) {
         const int mid = (plo + phi + 1) >> 1;
@@ -227,6 +226,30 @@ __global__ __launch_bounds__(256, 2) void panel_product_kernel(const PanelProble
         }
 }
 
+template <int NY, int NX, int MI>
+__global__ __launch_bounds__(256, 2) void panel_product_kernel(const PanelProblem *__restrict__ probs, int nprobs, int total_tiles,
+                                                               const int *__restrict__ state)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
+    const int t_global = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
+    if (t_global < total_tiles) panel_product_tile<NY, NX, MI>(probs, nprobs, t_global, state, smem_raw);
+}
+
+// `tiles` tiles of 128 rows of whole panels and the tiles of gemm_bf16.h of panels with a remainder, in one launch
+template <int NY, int NX>
+__global__ __launch_bounds__(256, 2) void joint_product_kernel(const PanelProblem *__restrict__ probs, int nprobs, int tiles,
+                                                               const GemmProblem *__restrict__ ragged, int nragged, int ragged_tiles,
+                                                               const int *__restrict__ state)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int all = tiles + ragged_tiles, per_xcd = (all + NUM_XCD - 1) / NUM_XCD;
+    const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
+    if (t >= all) return;
+    if (t < tiles) panel_product_tile<NY, NX, 2>(probs, nprobs, t, state, smem_raw);
+    else gemm_bf16_tile<float, float, NY, NX, true>(ragged, nragged, t - tiles, state, smem_raw);
+}
+
 // Whether a launch takes 256 rows of X per tile (MI = 4) or 128 (MI = 2: 150 registers, three workgroups on a CU);
 // `tiles_256`: tiles of 256.  The large ones read and cut Y half as often but pay only once two of them are on every CU.
 // SOAP refresh on small over large tiles: 8 factors of n = 2048 0.83, 32: 1.00, 48 (384 tiles of the second product): 0.99,
@@ -237,14 +260,40 @@ inline bool pp_take_wide_tiles(int tiles_256)
     return tiles_256 >= 512;
 }
 
+// Whether whole panels and panels with a remainder share a launch of `tiles` tiles of 128: while these are all on the chip at once
+// (two workgroups on a CU) a launch less counts for more than the LDS that the whole ones do not need.  SOAP refresh in us, joint / apart:
+// matrices of 899 x 1405 in blocks of 256 (38 of 256, 6 of 131, 4 of 125 each), 1: 685 / 768, 3: 613 / 695, 5: 809 / 929; 4 of 1100 x 1405 in
+// blocks of 512 1441 / 1574; 4 of 1100 x 2500 in blocks of 1024 3165 / 3454.
+inline bool pp_join(int tiles)
+{
+    return tiles <= 512;
+}
+
 template <int NY, int NX, int MI>
 inline hipError_t launch_panel_product(const PanelProblem *probs, int nprobs, int total_tiles, const int *state, hipStream_t stream)
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
-    constexpr size_t lds = 2u * PP_ROWS * 64u * NY;
+    constexpr size_t lds = pp_lds_bytes(NY);
     const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
     profile_begin(515, stream);
     hipLaunchKernelGGL((panel_product_kernel<NY, NX, MI>), dim3(per_xcd * NUM_XCD), dim3(256), lds, stream, probs, nprobs, total_tiles, state);
+    profile_end(stream);
+    return hipGetLastError();
+}
+
+template <int NY, int NX>
+inline hipError_t launch_joint_product(const PanelProblem *probs, int nprobs, int tiles, const GemmProblem *ragged, int nragged, int ragged_tiles,
+                                       const int *state, hipStream_t stream)
+{
+    const int all = tiles + ragged_tiles, per_xcd = (all + NUM_XCD - 1) / NUM_XCD;
+    if (all <= 0) return hipSuccess;
+    auto kern = joint_product_kernel<NY, NX>;
+    constexpr size_t lds = gemm_bf16_lds<float, float, NY, NX>();
+    static_assert(lds >= pp_lds_bytes(NY), "either kind of tile");
+    static bool configured[MAX_DEVICES] = {};
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured); e != hipSuccess) return e;
+    profile_begin(515, stream);
+    hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(256), lds, stream, probs, nprobs, tiles, ragged, nragged, ragged_tiles, state);
     profile_end(stream);
     return hipGetLastError();
 }

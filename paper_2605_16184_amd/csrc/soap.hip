@@ -946,12 +946,21 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         auto project = [&](int j, auto ny_, auto nx_, const int *st) -> asteria_status {
             constexpr int NY = decltype(ny_)::value, NX = decltype(nx_)::value;
             const int c = count[j], w = nwhole[c];
+            // the factors with a remainder have all of theirs in the last call for the whole panels
             GemmProblem *t1 = rt.t1 + off[j], *t2 = rt.t2 + off[j];
-            ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, NY, NY, true>(t1, c, (c - w) * j, st, stream)));
-            ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, NY, NX, true>(t2, c, pt[c], st, stream)));
+            const int ragged1 = (c - w) * j, ragged2 = pt[c];
             // whole panels: `slots` of them against `rows` panels of finished rows
-            auto panels = [&](const PanelProblem *p1, const PanelProblem *p2, int rows, int slots) -> asteria_status {
+            auto panels = [&](const PanelProblem *p1, const PanelProblem *p2, int rows, int slots, bool with_ragged) -> asteria_status {
                 const int narrow1 = w * rows * slots, wide1 = w * ((rows + 1) / 2) * slots, narrow2 = pp0[c] * slots, wide2 = pp1[c] * slots;
+                if (with_ragged && w > 0 && w < c && pp_join(narrow1 + ragged1) && pp_join(narrow2 + ragged2)) {
+                    ASTERIA_HIP_TRY((launch_joint_product<NY, NY>(p1, c, narrow1, t1, c, ragged1, st, stream)));
+                    ASTERIA_HIP_TRY((launch_joint_product<NY, NX>(p2, c, narrow2, t2, c, ragged2, st, stream)));
+                    return ASTERIA_OK;
+                }
+                if (with_ragged) {
+                    ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, NY, NY, true>(t1, c, ragged1, st, stream)));
+                    ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, NY, NX, true>(t2, c, ragged2, st, stream)));
+                }
                 if (pp_take_wide_tiles(wide1)) ASTERIA_HIP_TRY((launch_panel_product<NY, NY, 4>(p1, c, wide1, st, stream)));
                 else ASTERIA_HIP_TRY((launch_panel_product<NY, NY, 2>(p1, c, narrow1, st, stream)));
                 if (pp_take_wide_tiles(wide2)) ASTERIA_HIP_TRY((launch_panel_product<NY, NX, 4>(p2, c, wide2, st, stream)));
@@ -960,12 +969,12 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             };
             const int near = NY == 1 ? j % QR_AHEAD : 0, far = j - near;
             if (near == 0) {
-                if (NY == 1 && share) return panels(rt.f1 + off[j], rt.f2 + off[j], j, std::min(QR_AHEAD, np_max - j));
-                return panels(rt.p1 + off[j], rt.p2 + off[j], j, 1);
+                if (NY == 1 && share) return panels(rt.f1 + off[j], rt.f2 + off[j], j, std::min(QR_AHEAD, np_max - j), true);
+                return panels(rt.p1 + off[j], rt.p2 + off[j], j, 1, true);
             }
             if (!share && far > 0)
-                if (const asteria_status ps = panels(rt.f1 + off[far], rt.f2 + off[far], far, 1); ps != ASTERIA_OK) return ps;
-            return panels(rt.f1 + off[j], rt.f2 + off[j], near, 1);
+                if (const asteria_status ps = panels(rt.f1 + off[far], rt.f2 + off[far], far, 1, false); ps != ASTERIA_OK) return ps;
+            return panels(rt.f1 + off[j], rt.f2 + off[j], near, 1, true);
         };
         hipLaunchKernelGGL(qr_scale_kernel, dim3(cnt), dim3(64), 0, stream, d_q, cnt);
         if (o.from_identity)

@@ -289,8 +289,9 @@ def test_refresh_takes_no_more_passes_for_shared_ones(extra, passes):
 
 
 # a batch on the large tiles of the product A Q, its parts on the small ones; factors of either kernel
-def test_refresh_does_not_depend_on_the_batch():
-    sizes = [256] * 110 + [512, 768, 300, 640, 1024]
+# (the second has more panel tiles than whole panels and those with a remainder share a launch for)
+@pytest.mark.parametrize("sizes", [[256] * 110 + [512, 768, 300, 640, 1024], [256] * 260 + [250, 130]])
+def test_refresh_does_not_depend_on_the_batch(sizes):
     made = {n: (_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n), W.haar(n, DEV, 11, n)) for n in set(sizes)}
     As, q0 = zip(*[made[n] for n in sizes])
     full, least = ast.soap_refresh_workspace_bytes(list(zip(As, q0)))
@@ -307,7 +308,7 @@ def test_refresh_does_not_depend_on_the_batch():
     want = run(every)
     for size, aux in ((least, None), (least + (full - least) // 3, None), (full, streams)):
         assert all(torch.equal(a, b) for a, b in zip(run(every, size, aux), want)), size
-    for i in (0, 110, 111, 112, 113, 114):
+    for i in {n: k for k, n in enumerate(sizes)}.values():
         assert torch.equal(run([i])[0], want[i]), sizes[i]
 
 
