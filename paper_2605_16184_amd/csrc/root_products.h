@@ -626,8 +626,8 @@ inline hipError_t launch_pair_product(const FactorDev *fd, const FactorScal *fs,
 // A workgroup of 2 x 2 wavefronts of 64 x 32 (two 32 x 32 MFMA blocks, L level accumulators each) computes one 128 x 64
 // half of a tile, slabs of 32 k, two LDS stages of 24 (NS = 4) or 30 KiB: two workgroups per CU, so that one multiplies
 // while the other assembles and stores.  In a slab the lower digits of A come first; the products of its top digit, most of
-// all, cover the turn to the next slab.  Addresses and uniform factors of the epilogue are kept out of vector registers
-// (192 are sums at NS = 5).
+// all, cover the turn to the next slab.  Addresses and uniform factors of the epilogue are kept out of vector registers: nothing
+// spills at four digits; at five, where 192 registers are sums at L = 6, 33 do (120 bytes of scratch a lane).
 // Where at most 64 rows are left (BI = 1) a wavefront takes 32 of them: the epilogue of a block, an fp64 sum per level and element,
 // is longer than its products there.  A product of 226 factors of n = 64, (5, 6): 14.0 us, 20.1 with half of the wavefronts taking 64
 // rows each.
