@@ -355,4 +355,19 @@ inline hipError_t launch_gemm_bf16_grouped(const GemmProblem *probs, int nprobs,
     return hipGetLastError();
 }
 
+// A launch of two kinds of tiles: every XCD takes a contiguous range of the first kind and then one of the second (in one range
+// over both, all tiles of a kind that is few would lie on one XCD).  Returns the tile, or -1.
+inline int joint_grid(int first, int second)
+{
+    return ((first + NUM_XCD - 1) / NUM_XCD + (second + NUM_XCD - 1) / NUM_XCD) * NUM_XCD;
+}
+__device__ __forceinline__ int joint_tile(int first, int second, bool &is_second)
+{
+    const int per1 = (first + NUM_XCD - 1) / NUM_XCD, per2 = (second + NUM_XCD - 1) / NUM_XCD;
+    const int xcd = (int)(blockIdx.x % NUM_XCD), i = (int)(blockIdx.x / NUM_XCD);
+    is_second = i >= per1;
+    const int t = is_second ? xcd * per2 + i - per1 : xcd * per1 + i;
+    return t < (is_second ? second : first) ? t : -1;
+}
+
 }  // namespace asteria

@@ -236,18 +236,21 @@ __global__ __launch_bounds__(256, 2) void panel_product_kernel(const PanelProble
     if (t_global < total_tiles) panel_product_tile<NY, NX, MI>(probs, nprobs, t_global, state, smem_raw);
 }
 
-// `tiles` tiles of 128 rows of whole panels and the tiles of gemm_bf16.h of panels with a remainder, in one launch
-template <int NY, int NX>
+// `tiles` tiles of whole panels and the tiles of gemm_bf16.h of panels with a remainder, in one launch.  Either kind is spread over
+// the XCDs (joint_tile); the slower ones, with guards, come first.  SOAP refresh in us, joint / apart: matrices of 899 x 1405 in blocks of
+// 256 (38 of 256, 6 of 131, 4 of 125 each), 1: 685 / 768, 5: 809 / 929, 20: 1720 / 1869, 50: 4551 / 4705; of 1100 x 1405 in blocks of 512, 4: 1441
+// / 1574, 50: 5627 / 5853; of 1100 x 2500 in blocks of 1024, 4: 3165 / 3454, 40: 12409 / 12764.
+template <int NY, int NX, int MI>
 __global__ __launch_bounds__(256, 2) void joint_product_kernel(const PanelProblem *__restrict__ probs, int nprobs, int tiles,
                                                                const GemmProblem *__restrict__ ragged, int nragged, int ragged_tiles,
                                                                const int *__restrict__ state)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int all = tiles + ragged_tiles, per_xcd = (all + NUM_XCD - 1) / NUM_XCD;
-    const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
-    if (t >= all) return;
-    if (t < tiles) panel_product_tile<NY, NX, 2>(probs, nprobs, t, state, smem_raw);
-    else gemm_bf16_tile<float, float, NY, NX, true>(ragged, nragged, t - tiles, state, smem_raw);
+    bool second;
+    const int t = joint_tile(ragged_tiles, tiles, second);
+    if (t < 0) return;
+    if (second) panel_product_tile<NY, NX, MI>(probs, nprobs, t, state, smem_raw);
+    else gemm_bf16_tile<float, float, NY, NX, true>(ragged, nragged, t, state, smem_raw);
 }
 
 // Whether a launch takes 256 rows of X per tile (MI = 4) or 128 (MI = 2: 150 registers, three workgroups on a CU);
@@ -258,15 +261,6 @@ __global__ __launch_bounds__(256, 2) void joint_product_kernel(const PanelProble
 inline bool pp_take_wide_tiles(int tiles_256)
 {
     return tiles_256 >= 512;
-}
-
-// Whether whole panels and panels with a remainder share a launch of `tiles` tiles of 128: while these are all on the chip at once
-// (two workgroups on a CU) a launch less counts for more than the LDS that the whole ones do not need.  SOAP refresh in us, joint / apart:
-// matrices of 899 x 1405 in blocks of 256 (38 of 256, 6 of 131, 4 of 125 each), 1: 685 / 768, 3: 613 / 695, 5: 809 / 929; 4 of 1100 x 1405 in
-// blocks of 512 1441 / 1574; 4 of 1100 x 2500 in blocks of 1024 3165 / 3454.
-inline bool pp_join(int tiles)
-{
-    return tiles <= 512;
 }
 
 template <int NY, int NX, int MI>
@@ -281,19 +275,19 @@ inline hipError_t launch_panel_product(const PanelProblem *probs, int nprobs, in
     return hipGetLastError();
 }
 
-template <int NY, int NX>
+template <int NY, int NX, int MI>
 inline hipError_t launch_joint_product(const PanelProblem *probs, int nprobs, int tiles, const GemmProblem *ragged, int nragged, int ragged_tiles,
                                        const int *state, hipStream_t stream)
 {
-    const int all = tiles + ragged_tiles, per_xcd = (all + NUM_XCD - 1) / NUM_XCD;
-    if (all <= 0) return hipSuccess;
-    auto kern = joint_product_kernel<NY, NX>;
+    if (tiles + ragged_tiles <= 0) return hipSuccess;
+    auto kern = joint_product_kernel<NY, NX, MI>;
     constexpr size_t lds = gemm_bf16_lds<float, float, NY, NX>();
     static_assert(lds >= pp_lds_bytes(NY), "either kind of tile");
     static bool configured[MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured); e != hipSuccess) return e;
     profile_begin(515, stream);
-    hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(256), lds, stream, probs, nprobs, tiles, ragged, nragged, ragged_tiles, state);
+    hipLaunchKernelGGL(kern, dim3(joint_grid(ragged_tiles, tiles)), dim3(256), lds, stream, probs, nprobs, tiles, ragged, nragged, ragged_tiles,
+                       state);
     profile_end(stream);
     return hipGetLastError();
 }

@@ -264,24 +264,23 @@ __global__ __launch_bounds__(2 * PG_SMALL_TILE, 2) void product_f16_kernel(const
                                                                            const GemmProblem *__restrict__ ragged, int nragged, int ragged_tiles)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int all = tiles + ragged_tiles, per_xcd = (all + NUM_XCD - 1) / NUM_XCD;
-    const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
-    if (t >= all) return;
-    if (t < tiles) pgemm_tile<2, true, PG_SMALL_TILE>(probs, nprobs, t, smem_raw);
-    else gemm_bf16_tile<float, float, 2, 2, true>(ragged, nragged, t - tiles, nullptr, smem_raw);
+    bool second;
+    const int t = joint_tile(ragged_tiles, tiles, second);
+    if (t < 0) return;
+    if (second) pgemm_tile<2, true, PG_SMALL_TILE>(probs, nprobs, t, smem_raw);
+    else gemm_bf16_tile<float, float, 2, 2, true>(ragged, nragged, t, nullptr, smem_raw);
 }
 
 hipError_t launch_product_f16(const PlaneProblem *probs, int nprobs, int tiles, const GemmProblem *ragged, int nragged,
                               int ragged_tiles, hipStream_t stream)
 {
-    const int all = tiles + ragged_tiles, per_xcd = (all + NUM_XCD - 1) / NUM_XCD;
-    if (all <= 0) return hipSuccess;
+    if (tiles + ragged_tiles <= 0) return hipSuccess;
     constexpr size_t lds = pg_lds_bytes(2, PG_SMALL_TILE);
     static_assert(lds >= gemm_bf16_lds<float, float, 2, 2>(), "either kind of tile");
     static bool configured[MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(product_f16_kernel), lds, configured); e != hipSuccess) return e;
     profile_begin(tiles > 0 ? 513 : 224, stream);
-    hipLaunchKernelGGL(product_f16_kernel, dim3(per_xcd * NUM_XCD), dim3(2 * PG_SMALL_TILE), lds, stream, probs, nprobs, tiles, ragged, nragged,
+    hipLaunchKernelGGL(product_f16_kernel, dim3(joint_grid(ragged_tiles, tiles)), dim3(2 * PG_SMALL_TILE), lds, stream, probs, nprobs, tiles, ragged, nragged,
                        ragged_tiles);
     profile_end(stream);
     return hipGetLastError();
@@ -890,10 +889,11 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         // The Z products of whole-tile factors run on the kernel of pgemm.h and the others on that of gemm_bf16.h, whose sums have
         // another order: by the factor alone, so that its result does not depend on what it is batched with.  Only the
         // width of the tiles goes by the group: large ones beyond 128, where small ones need a second round of the chip (two
-        // workgroups a CU).  Product in us, small / large tiles, by large ones: n = 256 64 19 / 28, 128: 26 / 31, 192: 36 / 35, 512:
-        // 98 / 85; n = 512 128 37 / 44, 160: 48 / 46, 256: 64 / 57, 320: 88 / 91; n = 1024 64 40 / 70, 128: 60 / 75, 160: 83 / 77, 256:
-        // 111 / 93, 320: 140 / 152, 512: 220 / 180; n = 2048 128 109 / 136, 192: 162 / 148, 512: 413 / 332.  (Small tiles of
-        // gemm_bf16.h: n = 1024 64 47, 128: 65.)
+        // workgroups a CU).  Product in us, small /
+        // large tiles, by large ones: n = 256 64 19 / 28, 128: 26 / 31, 192: 36 / 35, 256: 48 / 40, 264: 50 / 58, 320: 60 / 63, 340: 66 / 65, 512:
+        // 98 / 85; n = 512 128 37 / 44, 160: 48 / 46, 256: 64 / 55, 280: 78 / 86, 320: 87 / 91, 340: 97 / 92; n = 1024 64 40 / 70, 128: 60 / 75,
+        // 160: 83 / 77, 256: 111 / 91, 272: 130 / 146, 320: 138 / 151, 336: 155 / 153, 384: 170 / 159, 512: 220 / 180; n = 2048 128 109 / 136, 192:
+        // 162 / 148, 320: 259 / 278, 512: 413 / 332.  (Small tiles of gemm_bf16.h: n = 1024 64 47, 128: 65.)
         auto whole = [](const QrFactor &F, int edge) {
             return pg_f32_operand_ok(F.Qt, F.n, F.n, F.ldqt, edge) && pg_f32_operand_ok(F.A, F.n, F.n, F.lda, edge);
         };
@@ -952,9 +952,11 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
             // whole panels: `slots` of them against `rows` panels of finished rows
             auto panels = [&](const PanelProblem *p1, const PanelProblem *p2, int rows, int slots, bool with_ragged) -> asteria_status {
                 const int narrow1 = w * rows * slots, wide1 = w * ((rows + 1) / 2) * slots, narrow2 = pp0[c] * slots, wide2 = pp1[c] * slots;
-                if (with_ragged && w > 0 && w < c && pp_join(narrow1 + ragged1) && pp_join(narrow2 + ragged2)) {
-                    ASTERIA_HIP_TRY((launch_joint_product<NY, NY>(p1, c, narrow1, t1, c, ragged1, st, stream)));
-                    ASTERIA_HIP_TRY((launch_joint_product<NY, NX>(p2, c, narrow2, t2, c, ragged2, st, stream)));
+                if (with_ragged && w > 0 && w < c) {
+                    if (pp_take_wide_tiles(wide1)) ASTERIA_HIP_TRY((launch_joint_product<NY, NY, 4>(p1, c, wide1, t1, c, ragged1, st, stream)));
+                    else ASTERIA_HIP_TRY((launch_joint_product<NY, NY, 2>(p1, c, narrow1, t1, c, ragged1, st, stream)));
+                    if (pp_take_wide_tiles(wide2)) ASTERIA_HIP_TRY((launch_joint_product<NY, NX, 4>(p2, c, wide2, t2, c, ragged2, st, stream)));
+                    else ASTERIA_HIP_TRY((launch_joint_product<NY, NX, 2>(p2, c, narrow2, t2, c, ragged2, st, stream)));
                     return ASTERIA_OK;
                 }
                 if (with_ragged) {

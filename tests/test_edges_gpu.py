@@ -289,8 +289,8 @@ def test_refresh_takes_no_more_passes_for_shared_ones(extra, passes):
 
 
 # a batch on the large tiles of the product A Q, its parts on the small ones; factors of either kernel
-# (the second has more panel tiles than whole panels and those with a remainder share a launch for)
-@pytest.mark.parametrize("sizes", [[256] * 110 + [512, 768, 300, 640, 1024], [256] * 260 + [250, 130]])
+# (the last takes 256-wide tiles for whole panels too)
+@pytest.mark.parametrize("sizes", [[256] * 110 + [512, 768, 300, 640, 1024], [256] * 260 + [250, 130], [256] * 341 + [130], [384] * 260 + [130] * 9])
 def test_refresh_does_not_depend_on_the_batch(sizes):
     made = {n: (_with_spectrum(n, _spectrum("power", n) + 1e-4, 9, n), W.haar(n, DEV, 11, n)) for n in set(sizes)}
     As, q0 = zip(*[made[n] for n in sizes])
