@@ -889,7 +889,7 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
         // The Z products of whole-tile factors run on the kernel of pgemm.h and the others on that of gemm_bf16.h, whose sums have
         // another order: by the factor alone, so that its result does not depend on what it is batched with.  Only the
         // width of the tiles goes by the group: large ones beyond 128, where small ones need a second round of the chip (two
-        // workgroups a CU).  Product in us, small /
+        // workgroups a CU), but not where a few of them would need a second round of their own (one a CU).  Product in us, small /
         // large tiles, by large ones: n = 256 64 19 / 28, 128: 26 / 31, 192: 36 / 35, 256: 48 / 40, 264: 50 / 58, 320: 60 / 63, 340: 66 / 65, 512:
         // 98 / 85; n = 512 128 37 / 44, 160: 48 / 46, 256: 64 / 55, 280: 78 / 86, 320: 87 / 91, 340: 97 / 92; n = 1024 64 40 / 70, 128: 60 / 75,
         // 160: 83 / 77, 256: 111 / 91, 272: 130 / 146, 320: 138 / 151, 336: 155 / 153, 384: 170 / 159, 512: 220 / 180; n = 2048 128 109 / 136, 192:
@@ -904,7 +904,7 @@ extern "C" asteria_status asteria_soap_refresh_ex(const asteria_factor *f, int n
                 large_tiles += (long long)(F.n / PG_TILE) * (F.n / PG_TILE);
                 ++large;
             }
-        if (large_tiles <= 128) large = 0;
+        if (large_tiles <= 128 || (large_tiles > 256 && large_tiles <= 320)) large = 0;
         int nz = 0, nl = 0, ns = large, tiles = 0, tiles_l = 0, tiles_s = 0;
         for (int i = 0; i < cnt; ++i) {
             const int n = q[i].n, tn = (n + BN - 1) / BN;
