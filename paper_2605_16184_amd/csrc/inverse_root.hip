@@ -864,7 +864,13 @@ __global__ void root_tables_kernel(const FactorDev *__restrict__ fd, FactorScal 
     }
 }
 
-// The lambda_max estimate of every factor of a pass.  Small factors, and batches that keep every CU busy until the
+// Whether the lambda_max estimate of a pass keeps its matrices in registers of several workgroups: wherever they fit, except for
+// factors that one workgroup holds by itself.  The whole refresh in us, before (the ways below) / so: 3 blocks of 777 x 1000 in blocks of 512,
+// evenly dense spectra 1650 / 1345; 6 of 1000 x 333 1197 / 1140; 1 of 512 x 400 579 / 479; 1 of 1024 x 1024 779 / 727; 100 of 512 x 300 3940 / 3920;
+// 64 of 1024 x 1024 17265 / 15980; 3 of 2000 x 1500 4095 / 3976; the 1.1B model 255.4 / 246.1 ms, packed 255.6 / 244.5.
+bool lanczos_by_cluster(int n_max) { return n_max > 256 && n_max <= LC_MAX_N; }
+
+// The others (larger factors, the general path).  Small factors, and batches that keep every CU busy until the
 // largest factor is done: one workgroup per factor, one launch.  Otherwise one launch per step - 32 of them, then one
 // workgroup per factor takes what has not settled; from n = 2048 on launches throughout.
 // Refresh in us at eps = 1e-6, a launch per step / a workgroup per factor, power-law spectrum (8 steps):
@@ -881,13 +887,20 @@ bool lanczos_by_factor(double elems, int n_max, bool any_packed)
 constexpr int LZ_LAUNCHES = 32, LZ_LAUNCH_N = 2048;
 
 asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int cnt, double elems, const Plan &pl, bool any_full, bool any_packed,
-                                   int tri_max, int n_max, hipStream_t stream)
+                                   int tri_max, int n_max, hipStream_t stream, int cluster_total = 0, uint2 *cluster_map = nullptr,
+                                   int *cluster_ticket = nullptr)      // workgroups of lanczos_cluster_kernel, 0: one of the other ways
 {
     const int steps = std::min(pl.power_iters, LZ_MAX);
     const float tol2 = pl.power_tol * pl.power_tol;
     const int ld = (n_max + 255) & ~255;
     const size_t lds = 3 * (size_t)ld * sizeof(float);
     static bool cfg_f[MAX_DEVICES] = {}, cfg_s[MAX_DEVICES] = {};
+    if (cluster_total > 0) {
+        hipLaunchKernelGGL(lanczos_prepare_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, cluster_map, cluster_ticket);
+        hipLaunchKernelGGL(lanczos_cluster_kernel, dim3(cluster_total), dim3(LC_THREADS), 0, stream, d_fd, d_fs, cluster_map, cluster_ticket, tol2, steps);
+        ASTERIA_HIP_TRY(hipGetLastError());
+        return ASTERIA_OK;
+    }
     if (lanczos_by_factor(elems, n_max, any_packed)) {
         if (any_packed) hipLaunchKernelGGL(lanczos_unpack_kernel, dim3(tri_max, cnt), dim3(256), 0, stream, d_fd);
         if (n_max <= 256) {
@@ -967,6 +980,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     bool any_packed = false, any_full = false;
     double a_min = 1.0, elems = 0.0;
     const bool prefix = pl.fp64_iters > 0;
+    int cluster_total = 0;
     for (int i = 0; i < cnt; ++i) {
         const asteria_factor &a = f[first + i];
         FactorDev &F = fd[i];
@@ -987,6 +1001,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         F.Aw = a.A; F.ldw = a.lda;
         if (F.a_packed) { any_packed = true; tri_max = std::max(tri_max, F.ntri); }
         else any_full = true;
+        F.lz_start = cluster_total; cluster_total += lanczos_members(n);
         F.eps_in = eps[eps_count == 1 ? 0 : first + i];
         const double er = (double)F.eps_in;
         a_min = std::min(a_min, er / (1.0 + (double)pl.margin + er));
@@ -1001,6 +1016,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         // X_0 is never written: a full copy of packed statistics and two vectors of the estimate lie there
         if (F.a_packed) { F.Aw = reinterpret_cast<const float *>(F.X[0]); F.ldw = F.rowb / 4; }
         for (int v = 0; v < 2; ++v) F.py[v] = reinterpret_cast<float *>(F.X[0]) + v * ld4(n);
+        F.lz_words = reinterpret_cast<uint64_t *>(F.X[0]);     // (16 n + 32 bytes a member; a row of X_0 alone has 128)
         char *chain[4] = {nullptr, nullptr, cv.take<char>(std::max(slot, 2 * pair)), cv.take<char>(slot)};
         if (prefix)
             for (int v = 0; v < 4; ++v) {
@@ -1012,6 +1028,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     const int edge = pair_tile_edge(tri64_total, tri_total, tri256_total, tri_tiles(n_max), work128, work256, rows / cnt);
     int pair_total = 0;
     for (FactorDev &F : fd) { F.tile_start_p = pair_total; pair_total += tri_tiles_of(F.n, edge); }
+    // (until the tiles are written there d_map holds the members of lanczos_cluster_kernel, fewer than tiles, and d_state its ticket)
     uint2 *d_map = cv.take<uint2>(tri_total), *d_map_p = edge == 128 ? d_map : cv.take<uint2>(pair_total);
     PlaneF64Tables ft = {};
     if (f64)
@@ -1055,7 +1072,8 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     ASTERIA_HIP_TRY(upload_async(d_fd, fd.data(), sizeof(FactorDev) * cnt, stream));
     if (f64)
         hipLaunchKernelGGL(plane_f64_tables_kernel, dim3((cnt + 127) / 128), dim3(128), 0, stream, d_fd, d_fs, cnt, linear0 ? 1 : 0, ft);
-    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, elems, pl, any_full, any_packed, tri_max, n_max, stream));
+    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, elems, pl, any_full, any_packed, tri_max, n_max, stream, lanczos_by_cluster(n_max) ? cluster_total : 0,
+                                    d_map, d_state));
 
     // intervals and T of a factor that follows the schedule (the device works in fp32 for the scaling: 1e-5 of slack)
     std::vector<PlaneControl> ctl(K + 1);

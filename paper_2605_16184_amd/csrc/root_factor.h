@@ -47,6 +47,8 @@ struct FactorDev {
     int pm_blocks;
     float eps_in;
     int a_packed;       // A lies in packed lower tiles (gemm.h, packed_off): lda unused
+    uint64_t *lz_words; // exchange of lanczos_cluster_kernel
+    int lz_start;       // first of this factor's workgroups there
     float *pm_tile;     // packed A: per lower tile 2 x 128 partial products of the mat-vec and the sum of a^2 as a double
 };
 

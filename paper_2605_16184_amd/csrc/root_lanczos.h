@@ -12,6 +12,7 @@
 //   lanczos_factor_kernel   one workgroup per factor takes all steps in one launch: n <= 256 with the matrix in
 //                           registers, larger ones streamed.  For small factors, and for batches that keep every
 //                           CU busy anyway.
+//   lanczos_cluster_kernel  several workgroups per factor, the matrix in their registers, all steps in one launch: n <= 2048
 //   lanczos_step_kernel     one launch per step, a factor's rows spread over workgroups: few large factors.  Every
 //                           workgroup forms the next vector by itself from the previous step's y (n elements, against
 //                           n rows of n), so a step is one launch; an extra workgroup keeps the recurrence.
@@ -75,16 +76,24 @@ __device__ inline double tridiag_largest(const float *a, const float *b, int m, 
 }
 
 // After step j: a, b hold the recurrence up to alpha_j, beta_j (in LDS: every lane walks through it).  One
-// wavefront; returns whether the factor is finished.
-__device__ inline bool lanczos_advance(FactorScal &S, const float *a, const float *b, int j, float beta, float tol2)
+// wavefront; rho, small: the estimate and how many steps have not moved it.  Returns whether the factor is finished.
+__device__ inline bool lanczos_advance(float &rho, int &small, const float *a, const float *b, int j, float beta, float tol2)
 {
-    const double before = j > 0 ? (double)S.rho : 0.0;
+    const double before = j > 0 ? (double)rho : 0.0;
     const double theta = tridiag_largest(a, b, j + 1, before);
     const bool ended = !(beta > 1e-7f * fabsf((float)theta)) || !(beta > 0.0f);
-    int small = S.lz_small;
     small = (j > 0 && theta - before <= (double)tol2 * fabs(theta)) ? small + 1 : 0;
-    if ((threadIdx.x & 63) == 0) { S.rho = (float)theta; S.lz_small = small; }
+    rho = (float)theta;
     return ended || small >= 3;
+}
+// ... with both kept in the factor's state
+__device__ inline bool lanczos_advance(FactorScal &S, const float *a, const float *b, int j, float beta, float tol2)
+{
+    float rho = S.rho;
+    int small = S.lz_small;
+    const bool end = lanczos_advance(rho, small, a, b, j, beta, tol2);
+    if ((threadIdx.x & 63) == 0) { S.rho = rho; S.lz_small = small; }
+    return end;
 }
 
 // ---- one workgroup per factor --------------------------------------------------------------------------
@@ -296,6 +305,304 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
         if (wave == 0) stop = lanczos_advance(S, la, lb, j, beta, tol2);
     }
     if (tid == 0) S.pm_done = 1;
+}
+
+// ---- the matrix in the registers of several workgroups ---------------------------------------------------
+// A factor's rows are dealt to lanczos_members(n) workgroups, which load them once and keep them; a step then moves n words per
+// workgroup through memory instead of the matrix.  Every member forms alpha, beta and the next vector from all of y by itself, in the
+// same order and so with the same bits: they agree on when to stop, and a step needs one exchange.
+//
+// The exchange: word i of a step holds y_i and the step's number in 64 bits, written and read by relaxed atomics of device scope, which
+// carry their own validity: no fence (which would write back the whole L2: a phase of 72 workgroups took 6 us with it) and no flag.  Two
+// buffers in turn: whoever writes step j + 2 has read all of step j + 1, which nobody publishes before having read step j.
+//
+// Progress: a workgroup takes its (factor, member) by a ticket, so whoever waits waits for the holders of tickets next to its own;
+// unfinished factors below the last ticket taken have all their members on the chip, and the one at the frontier, with at most
+// lanczos_members(2048) = 43, finds room as soon as those below are done.  The wait is bounded all the same: a member that
+// gives up reports not a number, which the scaling refuses.
+//
+// Bound by the first load (HBM) and by 6 - 8 us a step (exchange, two block sums, the product); figures beside lanczos_by_cluster.
+constexpr int LC_WAVES = 12, LC_THREADS = 64 * LC_WAVES, LC_MAX_N = 2048;
+constexpr uint32_t LC_POLLS = 1u << 21;
+__host__ __device__ inline int lanczos_rows(int n) { return LC_WAVES * (n <= 512 ? 16 : (n <= 1024 ? 8 : 4)); }     // of a member
+__host__ __device__ inline int lanczos_members(int n) { return (n + lanczos_rows(n) - 1) / lanczos_rows(n); }
+// words of a factor's exchange: two buffers of n, and each member's partial sums of squares and of the diagonal as halves of doubles
+__host__ __device__ inline size_t lanczos_words(int n) { return 2 * (size_t)n + 4 * (size_t)lanczos_members(n); }
+
+__device__ __forceinline__ void word_put(ASTERIA_GLOBAL uint64_t *p, uint32_t value, uint32_t tag)
+{
+    __hip_atomic_store(p, (uint64_t)value | ((uint64_t)tag << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t word_get(const ASTERIA_GLOBAL uint64_t *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Exchange words of every factor to zero (no step's number), its members into the map, the ticket to zero.
+__global__ __launch_bounds__(256) void lanczos_prepare_kernel(const FactorDev *fd, uint2 *map, int *ticket)
+{
+    const FactorDev &F = fd[blockIdx.x];
+    const int words = (int)lanczos_words(F.n), members = lanczos_members(F.n);
+    for (int i = threadIdx.x; i < words; i += 256) F.lz_words[i] = 0;
+    for (int m = threadIdx.x; m < members; m += 256) map[F.lz_start + m] = make_uint2(blockIdx.x, (unsigned)m);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
+}
+
+// NI: a lane holds columns 4 lane + 256 i .. + 3 for i < NI of RW consecutive rows (128 registers)
+template <int NI>
+__device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S, int member, float tol2, int steps)
+{
+    constexpr int RW = 32 / NI, RB = RW < 8 ? RW : 8, OWN = (256 * NI + LC_THREADS - 1) / LC_THREADS;
+    __shared__ __align__(16) float v_lds[256 * NI];
+    __shared__ double redd[2][LC_WAVES];
+    __shared__ float la[LZ_MAX], lb[LZ_MAX];
+    __shared__ int done;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = F.n, members = lanczos_members(n), row0 = member * LC_WAVES * RW + wave * RW;
+    ASTERIA_GLOBAL uint64_t *words = (ASTERIA_GLOBAL uint64_t *)F.lz_words, *sums = words + 2 * (size_t)n;
+    float ar[RW][4 * NI];
+    if (!F.a_packed) {
+        // No branches between the loads and no masks: addresses are kept inside the matrix.  What a row beyond it gives is not written,
+        // a column beyond it meets a zero of v
+        typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
+        const ASTERIA_GLOBAL float *A = (const ASTERIA_GLOBAL float *)F.A;
+        const int lda = F.lda, n4 = n & ~3;
+        if (n4 > 0) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int q = 0; q < RW; ++q) {
+                    const floatx4_any t = *(const ASTERIA_GLOBAL floatx4_any *)(A + (size_t)min(row0 + q, n - 1) * lda + min(4 * lane + 256 * i, n4 - 4));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ar[q][4 * i + e] = t[e];
+                }
+        } else {
+#pragma unroll
+            for (int q = 0; q < RW; ++q)
+#pragma unroll
+                for (int e = 0; e < 4 * NI; ++e) ar[q][e] = 0.0f;
+        }
+        if (n4 != n)
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+                if (n4 / 256 == i && 4 * lane + 256 * i == n4)
+#pragma unroll
+                    for (int q = 0; q < RW; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            ar[q][4 * i + e] = n4 + e < n ? A[(size_t)min(row0 + q, n - 1) * lda + n4 + e] : 0.0f;
+    } else {
+        // packed tiles are whole: their padding is read and masked.  Above the diagonal: column c of these rows is row c of the mirror tile
+        const int ti = row0 / PACK_T, rt = row0 % PACK_T;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int c = 4 * lane + 256 * i, tj = c / PACK_T, ct = c % PACK_T;
+            const bool some = row0 < n && c < n, below = tj <= ti;
+            if (some && below) {
+                const ASTERIA_GLOBAL float *t = (const ASTERIA_GLOBAL float *)F.A + ((size_t)(ti * (ti + 1) / 2 + tj) * PACK_T + rt) * PACK_T + ct;
+#pragma unroll
+                for (int q = 0; q < RW; ++q) {
+                    const floatx4 x = *(const ASTERIA_GLOBAL floatx4 *)(t + (size_t)q * PACK_T);
+                    ar[q][4 * i] = x[0]; ar[q][4 * i + 1] = x[1]; ar[q][4 * i + 2] = x[2]; ar[q][4 * i + 3] = x[3];
+                }
+            } else if (some) {
+                const ASTERIA_GLOBAL float *t = (const ASTERIA_GLOBAL float *)F.A + ((size_t)(tj * (tj + 1) / 2 + ti) * PACK_T + ct) * PACK_T + rt;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int q = 0; q < RW; q += 4) {
+                        const floatx4 x = *(const ASTERIA_GLOBAL floatx4 *)(t + (size_t)e * PACK_T + q);
+                        ar[q][4 * i + e] = x[0]; ar[q + 1][4 * i + e] = x[1]; ar[q + 2][4 * i + e] = x[2]; ar[q + 3][4 * i + e] = x[3];
+                    }
+            }
+#pragma unroll
+            for (int q = 0; q < RW; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (row0 + q >= n || c + e >= n) ar[q][4 * i + e] = 0.0f;
+        }
+    }
+    auto wave_sum = [](double x) __attribute__((always_inline)) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        return x;
+    };
+    auto block_sum = [&](double x, double *red) __attribute__((always_inline)) {     // ends with red full and a barrier passed
+        x = wave_sum(x);
+        if (lane == 0) red[wave] = x;
+        __syncthreads();
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < LC_WAVES; ++w) t += red[w];
+        return t;
+    };
+    // the vectors: elements tid + 768 q in registers, v in LDS as well
+    float v[OWN], vp[OWN];
+    double ss = 0.0;
+#pragma unroll
+    for (int q = 0; q < OWN; ++q) {
+        const int i = tid + LC_THREADS * q;
+        // the same start vector for every factor: a factor's result does not depend on its place in the batch
+        v[q] = i < n ? hash_unit(0u, (uint32_t)i) : 0.0f;
+        vp[q] = 0.0f;
+        ss += (double)v[q] * (double)v[q];
+    }
+    if (tid == 0) done = 0;
+    ss = block_sum(ss, redd[0]);
+    const float inv0 = ss > 0.0 ? (float)(1.0 / sqrt(ss)) : 0.0f;
+#pragma unroll
+    for (int q = 0; q < OWN; ++q) {
+        const int i = tid + LC_THREADS * q;
+        v[q] *= inv0;
+        if (i < 256 * NI) v_lds[i] = v[q];
+    }
+    {
+        // ||A||_F^2 and the trace: of this member's rows, collected by the first member
+        double saa = 0.0, str = 0.0;
+#pragma unroll
+        for (int q = 0; q < RW; ++q)
+#pragma unroll
+            for (int e = 0; e < 4 * NI; ++e) {
+                const float x = row0 + q < n && 4 * lane + 64 * (e & ~3) < n ? ar[q][e] : 0.0f;
+                saa += (double)x * (double)x;
+            }
+        if (lane < RW && row0 + lane < n) {
+            const int r = row0 + lane;
+            str = (double)F.A[F.a_packed ? packed_off(r, r) : (size_t)r * F.lda + r];
+        }
+        saa = block_sum(saa, redd[1]);
+        __syncthreads();
+        str = block_sum(str, redd[0]);
+        if (tid == 0 && members > 1) {
+            const uint64_t a = (uint64_t)__double_as_longlong(saa), t = (uint64_t)__double_as_longlong(str);
+            ASTERIA_GLOBAL uint64_t *d = sums + 4 * (size_t)member;
+            word_put(d, (uint32_t)a, 1u); word_put(d + 1, (uint32_t)(a >> 32), 1u);
+            word_put(d + 2, (uint32_t)t, 1u); word_put(d + 3, (uint32_t)(t >> 32), 1u);
+        }
+        if (member == 0 && members > 1) {
+            // (43 members at most: one lane each)
+            double a = 0.0, t = 0.0;
+            if (wave == 0) {
+                if (lane < members) {
+                    const ASTERIA_GLOBAL uint64_t *d = sums + 4 * (size_t)lane;
+                    uint64_t w[4] = {0, 0, 0, 0};
+                    for (uint32_t p = 0; p < LC_POLLS; ++p) {
+                        bool all = true;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { w[e] = word_get(d + e); all = all && (uint32_t)(w[e] >> 32) == 1u; }
+                        if (all) break;
+                        __builtin_amdgcn_s_sleep(1);
+                    }
+                    a = __longlong_as_double((long long)((w[0] & 0xffffffffull) | (w[1] << 32)));
+                    t = __longlong_as_double((long long)((w[2] & 0xffffffffull) | (w[3] << 32)));
+                }
+                a = wave_sum(a); t = wave_sum(t);
+            }
+            saa = a; str = t;
+        }
+        if (member == 0 && tid == 0) { S.fro2 = saa; S.trace = str; S.rho = 0.0f; S.lz_small = 0; }
+    }
+    __syncthreads();
+    float beta_p = 0.0f, rho = 0.0f;
+    int small = 0;
+    bool stop = false, lost = false;
+    for (int j = 0; j < steps; ++j) {
+        // ---- this member's rows of y, RB at a time
+#pragma unroll
+        for (int b = 0; b < RW; b += RB) {
+            float s[RB];
+#pragma unroll
+            for (int q = 0; q < RB; ++q) s[q] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const float4 x = *reinterpret_cast<const float4 *>(v_lds + 4 * lane + 256 * i);
+#pragma unroll
+                for (int q = 0; q < RB; ++q)
+                    s[q] += ar[b + q][4 * i] * x.x + ar[b + q][4 * i + 1] * x.y + ar[b + q][4 * i + 2] * x.z + ar[b + q][4 * i + 3] * x.w;
+            }
+            // a level halves the rows a lane holds a part of
+            int row = row0 + b, off = 32;
+#pragma unroll
+            for (int half = RB / 2; half > 0; half /= 2, off >>= 1) {
+                const bool up = (lane & off) != 0;
+#pragma unroll
+                for (int q = 0; q < half; ++q) {
+                    const float give = up ? s[q] : s[q + half], keep = up ? s[q + half] : s[q];
+                    s[q] = keep + __shfl_xor(give, off, 64);
+                }
+                row += up ? half : 0;
+            }
+            const int others = lane & (2 * off - 1);
+#pragma unroll
+            for (; off > 0; off >>= 1) s[0] += __shfl_xor(s[0], off, 64);
+            if (others == 0 && row < n) word_put(words + (size_t)(j & 1) * n + row, __float_as_uint(s[0]), (uint32_t)j + 1u);
+        }
+        if (tid == 0 && stop) done = 1;
+        // ---- all of y
+        float y[OWN];
+        double yv = 0.0;
+        {
+            uint64_t w[OWN];
+            uint32_t polls = 0;
+            while (true) {
+                bool all = true;
+#pragma unroll
+                for (int q = 0; q < OWN; ++q) {
+                    const int i = tid + LC_THREADS * q;
+                    w[q] = i < n ? word_get(words + (size_t)(j & 1) * n + i) : (uint64_t)(j + 1) << 32;
+                    all = all && (uint32_t)(w[q] >> 32) == (uint32_t)j + 1u;
+                }
+                if (__all(all)) break;
+                if (++polls == LC_POLLS) { lost = true; break; }
+            }
+#pragma unroll
+            for (int q = 0; q < OWN; ++q) {
+                y[q] = lost ? NAN : __uint_as_float((uint32_t)w[q]);
+                yv += (double)(y[q] * v[q]);
+            }
+        }
+        const float alpha = (float)block_sum(yv, redd[0]);
+        if (done) break;
+        double ww = 0.0;
+#pragma unroll
+        for (int q = 0; q < OWN; ++q) {
+            y[q] = y[q] - alpha * v[q] - beta_p * vp[q];
+            ww += (double)y[q] * (double)y[q];
+        }
+        const float beta = (float)sqrt(block_sum(ww, redd[1]));
+        if (!(beta < 3.0e38f) || !(fabsf(alpha) < 3.0e38f)) {         // non-finite input, or a wait that was given up (uniform)
+            rho = NAN;
+            break;
+        }
+        const float inv = beta > 0.0f ? 1.0f / beta : 0.0f;
+#pragma unroll
+        for (int q = 0; q < OWN; ++q) {
+            const int i = tid + LC_THREADS * q;
+            vp[q] = v[q];
+            v[q] = y[q] * inv;
+            if (i < 256 * NI) v_lds[i] = v[q];
+        }
+        beta_p = beta;
+        if (tid == 0) { la[j] = alpha; lb[j] = beta; }
+        __syncthreads();
+        // the recurrence is looked at by one wavefront while the others go on to the next product: they stop one step later
+        // than they could
+        if (wave == 0) stop = lanczos_advance(rho, small, la, lb, j, beta, tol2);
+    }
+    if (member == 0 && tid == 0) { S.rho = rho; S.pm_done = 1; }
+}
+
+__global__ __launch_bounds__(LC_THREADS, 3) void lanczos_cluster_kernel(const FactorDev *fd, FactorScal *fs, const uint2 *map, int *ticket, float tol2, int steps)
+{
+    __shared__ int mine;
+    if (threadIdx.x == 0) mine = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const uint2 m = map[__builtin_amdgcn_readfirstlane(mine)];
+    const FactorDev &F = fd[m.x];
+    FactorScal &S = fs[m.x];
+    if (F.n <= 512) lanczos_member<2>(F, S, (int)m.y, tol2, steps);
+    else if (F.n <= 1024) lanczos_member<4>(F, S, (int)m.y, tol2, steps);
+    else lanczos_member<8>(F, S, (int)m.y, tol2, steps);
 }
 
 // ---- one launch per step -------------------------------------------------------------------------------

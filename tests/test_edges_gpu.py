@@ -65,6 +65,40 @@ def test_roots_at_the_edges(kind, eps, sizes):
         assert torch.equal(Xs[first], Xs[i])                    # the same factor anywhere in the batch
 
 
+# Largest eigenvalue with the matrix in the registers of several workgroups: rows and columns of a member's last wavefront and last
+# chunk, one member and 43, rows of every alignment, packed tiles whose padding is not a number.  The estimate is fp32 arithmetic on a
+# spectrum whose top is a factor of 4 apart: a few units of 2^-24 of a sum of n products, far below the 1e-5 asked here.
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("sizes", [[257, 1, 2, 3, 4, 5], [512, 192, 193, 191], [513, 608, 577], [1024, 300], [1025, 97], [2048, 2047], [333] * 300])
+def test_largest_eigenvalue_from_registers(sizes, packed):
+    made = {n: _with_spectrum(n, _spectrum("power", n), 7, n) for n in set(sizes)}
+    top = {n: float(torch.linalg.eigvalsh(A.double())[-1]) for n, A in made.items()}
+    items = []
+    for n in sizes:
+        X = torch.full((n, n), float("nan"), device=DEV)
+        if packed:
+            P = torch.full((ast.packed_elems(n),), float("nan"), device=DEV)
+            ast.sym_pack([(made[n], P)])
+            items.append((P, X, 1))
+        else:
+            wide = torch.full((n, n + n % 3), float("nan"), device=DEV)      # what lies beyond a row's end is not data
+            wide[:, :n] = made[n]
+            items.append((wide[:, :n], X, 0))
+    info = torch.full((len(sizes),), -1, dtype=torch.int32, device=DEV)
+    lam = torch.zeros(len(sizes), device=DEV)
+    ast.inverse_root(items, 1e-6, info=info, lambda_max=lam)
+    torch.cuda.synchronize()
+    assert bool((info == 0).all())
+    for n, x in zip(sizes, lam.tolist()):
+        assert abs(x - top[n]) <= 1e-5 * top[n], (n, x, top[n])
+    made[max(sizes)][0, 0] = float("nan")                       # reported, by every member alike
+    n = max(sizes)
+    X = torch.zeros(n, n, device=DEV)
+    ast.inverse_root([(made[n], X)], 1e-6, info=info[:1])
+    torch.cuda.synchronize()
+    assert int(info[0]) == 2
+
+
 # mostly small factors, for which small tiles pay, beside one that is too large for them
 def test_roots_of_small_factors_beside_a_large_one():
     sizes = [2700] + [64] * 1100
