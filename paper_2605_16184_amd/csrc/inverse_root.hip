@@ -1095,7 +1095,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     };
     hipLaunchKernelGGL(plane_setup_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, d_state, pl.margin, control(0), d_map,
                        edge == 128 ? nullptr : d_map_p, edge);
-    hipLaunchKernelGGL(plane_init_kernel, dim3(tri_total), dim3(256), 0, stream, d_fd, d_fs, d_state, d_map, linear0 ? 1 : 0);
+    hipLaunchKernelGGL(plane_init_kernel, dim3(tri_total, 4), dim3(256), 0, stream, d_fd, d_fs, d_state, d_map, linear0 ? 1 : 0);
     ASTERIA_HIP_TRY(hipGetLastError());
     for (int k = 0; k < K; ++k) {
         if (k > 0) hipLaunchKernelGGL(plane_control_kernel, dim3(cnt), dim3(64), 0, stream, d_fd, d_fs, d_state, control(k));
@@ -1104,34 +1104,41 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         auto pair = [&](int op0, int op1) -> hipError_t {
             switch (edge) {
             case 64: return launch_pair_product<2, 2, 2, 2, 4>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
-            case 128: return launch_pair_product<2, 2, 4, 4, 2>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
+            case 128:
+                // one workgroup per CU at most: eight wavefronts hide more of each other's waits than four (252 tiles of 6 factors
+                // of n = 1000 and 333: 35 us a product, 40); with two workgroups per CU four are better (8 of 1024 x 1024 2475 us, 2650)
+                if ((op1 >= 0 ? 2 : 1) * pair_total <= PLANE_CUS)
+                    return launch_pair_product<4, 2, 2, 4, 4>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
+                return launch_pair_product<2, 2, 4, 4, 2>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
             default: return launch_pair_product<4, 2, 4, 8, 2>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
             }
-        };
-        auto chain = [&](int op, int tab) -> hipError_t {       // digit and fp64 products of the prefix
-            hipError_t e = hipSuccess;
-            if (pl.i8_slices > 0) e = launch_digit_product<4>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
-            if (e == hipSuccess && pl.i8_slices > 4) e = launch_digit_product<5>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
-            if (e == hipSuccess && f64)
-                e = launch_gemm_grouped<double, double, double, false, false>(ft.t[tab], cnt, tri_total, d_state, stream);
-            return e;
         };
         auto from_f64 = [&](int what) {
             if (f64)
                 hipLaunchKernelGGL(plane_from_f64_kernel, dim3((unsigned)(((size_t)n_max * plane_groups(n_max) * 2 + 255) / 256), (unsigned)cnt),
                                    dim3(256), 0, stream, d_fd, d_fs, d_state, k, what);
         };
+        // a product of the chain in every storage it can be in, and a second one on pair planes; planes: what is made of the fp64 result
+        auto product = [&](int op, int tab, int op1, int planes) -> hipError_t {
+            hipError_t e = hipSuccess;
+            if (pre && f64) {
+                e = launch_gemm_grouped<double, double, double, false, false>(ft.t[tab], cnt, tri_total, d_state, stream);
+                if (planes >= 0) from_f64(planes);
+            }
+            if (e == hipSuccess && pre && pl.i8_slices > 4 && edge != 256) {
+                e = launch_digit_product<0>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
+            } else {
+                if (e == hipSuccess && pre && pl.i8_slices > 0) e = launch_digit_product<4>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
+                if (e == hipSuccess && pre && pl.i8_slices > 4) e = launch_digit_product<5>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
+            }
+            return e == hipSuccess ? pair(op, op1) : e;
+        };
         if (pre && k > 0 && pl.i8_slices > 0) from_f64(2);
-        if (pre && d == 2) { ASTERIA_HIP_TRY(chain(OP_SQ, 0)); from_f64(0); }
-        if (d == 2) ASTERIA_HIP_TRY(pair(OP_SQ, -1));
+        if (d == 2) ASTERIA_HIP_TRY(product(OP_SQ, 0, -1, 0));
         if (d == 3) { ASTERIA_HIP_TRY(pair(OP_SQ3, -1)); ASTERIA_HIP_TRY(pair(OP_CUBE, -1)); }
-        if (pre) ASTERIA_HIP_TRY(chain(OP_E2, 1));
-        if (k > 0) ASTERIA_HIP_TRY(pair(OP_E2, OP_X));
-        else ASTERIA_HIP_TRY(pair(OP_E2, -1));
-        if (pre) ASTERIA_HIP_TRY(chain(OP_W, 2));
-        ASTERIA_HIP_TRY(pair(OP_W, -1));
-        if (pre) { ASTERIA_HIP_TRY(chain(OP_M, 3)); from_f64(1); }
-        ASTERIA_HIP_TRY(pair(OP_M, -1));
+        ASTERIA_HIP_TRY(product(OP_E2, 1, k > 0 ? (int)OP_X : -1, -1));
+        ASTERIA_HIP_TRY(product(OP_W, 2, -1, -1));
+        ASTERIA_HIP_TRY(product(OP_M, 3, -1, 1));
         ASTERIA_HIP_TRY(hipGetLastError());
     }
     hipLaunchKernelGGL(plane_control_kernel, dim3(cnt), dim3(64), 0, stream, d_fd, d_fs, d_state, control(K));

@@ -301,8 +301,8 @@ __global__ __launch_bounds__(64) void plane_control_kernel(const FactorDev *fd, 
 }
 
 // M_0 = s (A + eps I) of one 128 x 128 tile and its mirror image in the storage of the factor's tier, and where T
-// is linear X_1 = X_0 T_0.  64 x 64 sub-tiles of A and of its transposed position through LDS; a thread then owns
-// 16 consecutive columns of a row.  HBM-bound: 4 bytes read, 4 or 5 written per element (8 or 9 with X_1).
+// is linear X_1 = X_0 T_0.  A workgroup takes a 64 x 64 sub-tile of A (blockIdx.y) and its transposed position through LDS; a thread then
+// owns 16 consecutive columns of a row.  HBM-bound: 4 bytes read, 4 or 5 written per element (8 or 9 with X_1).
 __global__ __launch_bounds__(256) void plane_init_kernel(const FactorDev *fd, const FactorScal *fs, const int *state, const uint2 *map, int linear)
 {
     const uint2 tile = map[blockIdx.x];
@@ -376,47 +376,46 @@ __global__ __launch_bounds__(256) void plane_init_kernel(const FactorDev *fd, co
             put_pair(F.X[1]);
         }
     };
-    for (int sub = 0; sub < 4; ++sub) {
-        const int si = sub >> 1, sj = sub & 1;
-        if (ti == tj && si < sj) continue;                       // covered by the mirrored sub-tile
-        const int r0 = ti * 128 + si * 64, c0 = tj * 128 + sj * 64;
-        if (r0 >= n || c0 >= n) continue;
-        __syncthreads();
-        {
-            const int g = tid & 15, rw = tid >> 4;               // 16 groups of 4 columns x 16 rows
-            for (int rr = rw; rr < 64; rr += 16) {
-                // P[rr][..] = A(r0 + rr, c0 ..), Q[rr][..] = A(c0 + rr, r0 ..)
-                const int pr = r0 + rr, pc = c0 + 4 * g, qr = c0 + rr, qc = r0 + 4 * g;
-                const float *ps = packed ? Ap + (size_t)(si * 64 + rr) * PACK_T + sj * 64 + 4 * g : F.A + (size_t)pr * lda + pc;
-                if (vec && pr < n && pc + 4 <= n) {
-                    const float4 v = *reinterpret_cast<const float4 *>(ps);
-                    Pw[rr][4 * g] = v.x; Pw[rr][4 * g + 1] = v.y; Pw[rr][4 * g + 2] = v.z; Pw[rr][4 * g + 3] = v.w;
+    const int si = (int)blockIdx.y >> 1, sj = (int)blockIdx.y & 1;
+    if (ti == tj && si < sj) return;                             // covered by the mirrored sub-tile
+    const int r0 = ti * 128 + si * 64, c0 = tj * 128 + sj * 64;
+    if (r0 >= n || c0 >= n) return;
+    {
+        const int g = tid & 15, rw = tid >> 4;               // 16 groups of 4 columns x 16 rows
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            // P[rr][..] = A(r0 + rr, c0 ..), Q[rr][..] = A(c0 + rr, r0 ..)
+            const int rr = rw + 16 * t;
+            const int pr = r0 + rr, pc = c0 + 4 * g, qr = c0 + rr, qc = r0 + 4 * g;
+            const float *ps = packed ? Ap + (size_t)(si * 64 + rr) * PACK_T + sj * 64 + 4 * g : F.A + (size_t)pr * lda + pc;
+            if (vec && pr < n && pc + 4 <= n) {
+                const float4 v = *reinterpret_cast<const float4 *>(ps);
+                Pw[rr][4 * g] = v.x; Pw[rr][4 * g + 1] = v.y; Pw[rr][4 * g + 2] = v.z; Pw[rr][4 * g + 3] = v.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Pw[rr][4 * g + e] = (pr < n && pc + e < n) ? ps[e] : 0.0f;
+            }
+            if (!packed) {
+                const float *qs = F.A + (size_t)qr * lda + qc;
+                if (vec && qr < n && qc + 4 <= n) {
+                    const float4 v = *reinterpret_cast<const float4 *>(qs);
+                    Qw[rr][4 * g] = v.x; Qw[rr][4 * g + 1] = v.y; Qw[rr][4 * g + 2] = v.z; Qw[rr][4 * g + 3] = v.w;
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) Pw[rr][4 * g + e] = (pr < n && pc + e < n) ? ps[e] : 0.0f;
-                }
-                if (!packed) {
-                    const float *qs = F.A + (size_t)qr * lda + qc;
-                    if (vec && qr < n && qc + 4 <= n) {
-                        const float4 v = *reinterpret_cast<const float4 *>(qs);
-                        Qw[rr][4 * g] = v.x; Qw[rr][4 * g + 1] = v.y; Qw[rr][4 * g + 2] = v.z; Qw[rr][4 * g + 3] = v.w;
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) Qw[rr][4 * g + e] = (qr < n && qc + e < n) ? qs[e] : 0.0f;
-                    }
+                    for (int e = 0; e < 4; ++e) Qw[rr][4 * g + e] = (qr < n && qc + e < n) ? qs[e] : 0.0f;
                 }
             }
         }
-        __syncthreads();
-        const int rr = tid >> 2, cg = (tid & 3) * 16;
-        emit(r0 + rr, c0 + cg, [&](int e) {
-            return packed ? (double)Pw[rr][cg + e] : 0.5 * ((double)Pw[rr][cg + e] + (double)Qw[cg + e][rr]);
-        });
-        if (!(ti == tj && si == sj))
-            emit(c0 + rr, r0 + cg, [&](int e) {
-                return packed ? (double)Pw[cg + e][rr] : 0.5 * ((double)Pw[cg + e][rr] + (double)Qw[rr][cg + e]);
-            });
     }
+    __syncthreads();
+    const int rr = tid >> 2, cg = (tid & 3) * 16;
+    emit(r0 + rr, c0 + cg, [&](int e) {
+        return packed ? (double)Pw[rr][cg + e] : 0.5 * ((double)Pw[rr][cg + e] + (double)Qw[cg + e][rr]);
+    });
+    if (!(ti == tj && si == sj))
+        emit(c0 + rr, r0 + cg, [&](int e) {
+            return packed ? (double)Pw[cg + e][rr] : 0.5 * ((double)Pw[cg + e][rr] + (double)Qw[rr][cg + e]);
+        });
     if (over) F.flags[0] = 1;
 }
 
@@ -539,6 +538,7 @@ __global__ __launch_bounds__(256) void plane_finalize_kernel(const FactorDev *fd
 // 900 1.01, 1002 1.04; n = 900 560 0.97, 650 1.00, 700 1.01, 800 0.99, 850 0.99, 900 1.01, 1000 1.04; n = 1024 500 1.06, 560 0.99, 600
 // 1.00, 650 1.01, 700 1.02, 750 1.06, 800 1.01, 900 1.04, 1000 1.06; n = 2048 396 1.01, 504 1.09, 612 1.06, 684 1.07, 900 1.05; n = 4096
 // 408 1.06, 680 1.08; but n = 600 700 0.88, 1000 0.90 (a quarter more work), and n = 512 1800 0.96 (short K: the stores weigh more).
+constexpr int PLANE_CUS = 256;
 constexpr int PLANE_SMALL_TILES = 250, PLANE_LARGE_TILES = 700, PLANE_LARGE_N = 512;   // the first: of a factor that small tiles can serve
 inline int pair_tile_edge(int tri64, int tri128, int tri256, int tri128_max, double work128, double work256, double n_mean)
 {

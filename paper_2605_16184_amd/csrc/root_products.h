@@ -69,6 +69,7 @@ __device__ __forceinline__ int xcd_tile(int total)
     const int per = (total + NUM_XCD - 1) / NUM_XCD;
     return (int)(blockIdx.x % NUM_XCD) * per + (int)(blockIdx.x / NUM_XCD);
 }
+inline int xcd_blocks(int total) { return (total + NUM_XCD - 1) / NUM_XCD * NUM_XCD; }
 
 __device__ __forceinline__ void store_partial(float rsum, float *red, float *dst, int lane, int wave, int tid, int waves)
 {
@@ -159,10 +160,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void pair_product_kernel(const F
     const uint2 tile = map[op1 >= 0 ? w >> 1 : w];
     const int f = (int)tile.x;
     const FactorScal &S = fs[f];
-    if (op != OP_X && S.tier != TIER_PAIR) return;
     const FactorDev &F = fd[f];
+    const int tier = S.tier, st0 = state[f];
+    if (op != OP_X && tier != TIER_PAIR) return;
     const bool makes_e = op == OP_SQ || op == OP_SQ3 || op == OP_CUBE;
-    const int st = __builtin_amdgcn_readfirstlane(makes_e ? state[f] : state_after_test(F, S, state[f]));
+    const int st = __builtin_amdgcn_readfirstlane(makes_e ? st0 : state_after_test(F, S, st0));
     if (st != ST_RUN && !(st == ST_LAST && (makes_e || op == OP_X))) return;
     const int ti = (int)(tile.y >> 16), tj = (int)(tile.y & 0xffffu);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -608,9 +610,8 @@ inline hipError_t launch_pair_product(const FactorDev *fd, const FactorScal *fs,
     auto kern = pair_product_kernel<WGM, WGN, MI, NJ, ST>;
     static bool configured[MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), SH::LDS, configured); e != hipSuccess) return e;
-    const int all = op1 >= 0 ? 2 * total : total, per = (all + NUM_XCD - 1) / NUM_XCD;
     profile_begin(224, stream);
-    hipLaunchKernelGGL(kern, dim3(per * NUM_XCD), dim3(64 * SH::NW), SH::LDS, stream, fd, fs, state, map, total, op0, op1, k, degree);
+    hipLaunchKernelGGL(kern, dim3(xcd_blocks(op1 >= 0 ? 2 * total : total)), dim3(64 * SH::NW), SH::LDS, stream, fd, fs, state, map, total, op0, op1, k, degree);
     profile_end(stream);
     return hipGetLastError();
 }
@@ -798,7 +799,23 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
     }
 }
 
-// One launch per class of factors: NS = 4 (levels 4 or 5) and NS = 5 (levels 5 or 6).
+// One half of a tile, by the digits of its factor (NS = 4: levels 4 or 5; NS = 5: levels 5 or 6).
+template <int NS>
+__device__ __forceinline__ void digit_half(const FactorDev &F, const FactorScal &S, int op, int k, int degree, uint2 tile, int half, unsigned char *smem)
+{
+    const int ti = (int)(tile.y >> 16), tj = (int)(tile.y & 0xffffu);
+    auto run = [&](auto bi) __attribute__((always_inline)) {
+        constexpr int BI = decltype(bi)::value;
+        if (S.levels == NS) digit_tile<NS, NS, BI>(F, S, op, k, degree, ti, tj, half, smem);
+        else digit_tile<NS, NS + 1, BI>(F, S, op, k, degree, ti, tj, half, smem);
+    };
+    if (F.n - ti * 128 <= 64) run(std::integral_constant<int, 1>{});
+    else run(std::integral_constant<int, 2>{});
+}
+
+// One launch for factors of either number of digits (NS = 0) or one for each.  Where the launches themselves count - most find no
+// factor of their class, and cost 2.5 to 4.5 us in the chain - one; a batch of large tiles does not notice them, and its four digits run
+// without the registers that the fifth spills.
 template <int NS>
 __global__ __launch_bounds__(256, 2) void digit_product_kernel(const FactorDev *__restrict__ fd, const FactorScal *__restrict__ fs,
                                                                const int *__restrict__ state, const uint2 *__restrict__ map, int total,
@@ -808,33 +825,26 @@ __global__ __launch_bounds__(256, 2) void digit_product_kernel(const FactorDev *
     const int w = xcd_tile(2 * total);
     if (w >= 2 * total) return;
     const uint2 tile = map[w >> 1];
-    const int f = (int)tile.x, st = state[f];
-    if (st != ST_RUN && !(st == ST_LAST && op == OP_SQ)) return;
-    const FactorScal &S = fs[f];
-    if (S.tier != TIER_DIGIT || S.ns != NS) return;
-    const int ti = (int)(tile.y >> 16), tj = (int)(tile.y & 0xffffu), half = w & 1;
-    const FactorDev &F = fd[f];
-    auto run = [&](auto bi) __attribute__((always_inline)) {
-        constexpr int BI = decltype(bi)::value;
-        if (S.levels == NS) digit_tile<NS, NS, BI>(F, S, op, k, degree, ti, tj, half, plane_smem);
-        else digit_tile<NS, NS + 1, BI>(F, S, op, k, degree, ti, tj, half, plane_smem);
-    };
-    if (F.n - ti * 128 <= 64) run(std::integral_constant<int, 1>{});
-    else run(std::integral_constant<int, 2>{});
+    const FactorScal &S = fs[tile.x];
+    const int st = state[tile.x], ns = S.ns;
+    if (S.tier != TIER_DIGIT || (st != ST_RUN && !(st == ST_LAST && op == OP_SQ))) return;
+    if (NS == 4 || (NS == 0 && ns == 4)) { if (ns == 4) digit_half<4>(fd[tile.x], S, op, k, degree, tile, w & 1, plane_smem); }
+    else if (ns == 5) digit_half<5>(fd[tile.x], S, op, k, degree, tile, w & 1, plane_smem);
 }
+
+constexpr size_t digit_lds(int ns) { return 2 * (size_t)(128 + 64) * (2 * ns) * 16; }     // two stages
+static_assert(digit_lds(4) >= 4 * (size_t)PLANE_SCRATCH_BYTES, "store scratch fits the stages");
 
 template <int NS>
 inline hipError_t launch_digit_product(const FactorDev *fd, const FactorScal *fs, const int *state, const uint2 *map, int total,
                                        int op, int k, int degree, hipStream_t stream)
 {
     if (total <= 0) return hipSuccess;
-    constexpr size_t lds = 2 * (size_t)PlaneLoader<2 * NS, 128, 64, 4>::STAGE;
-    static_assert(lds >= 4 * (size_t)PLANE_SCRATCH_BYTES, "store scratch fits the stages");
+    constexpr size_t lds = digit_lds(NS == 0 ? 5 : NS);
     static bool configured[MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(digit_product_kernel<NS>), lds, configured); e != hipSuccess) return e;
-    const int per = (2 * total + NUM_XCD - 1) / NUM_XCD;
-    profile_begin(300 + NS, stream);
-    hipLaunchKernelGGL(digit_product_kernel<NS>, dim3(per * NUM_XCD), dim3(256), lds, stream, fd, fs, state, map, total, op, k, degree);
+    profile_begin(NS == 0 ? 304 : 300 + NS, stream);
+    hipLaunchKernelGGL(digit_product_kernel<NS>, dim3(xcd_blocks(2 * total)), dim3(256), lds, stream, fd, fs, state, map, total, op, k, degree);
     profile_end(stream);
     return hipGetLastError();
 }
