@@ -168,16 +168,12 @@ __device__ __forceinline__ double lane_value(double v, int lane)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// 1 / sqrt(x) for positive normal x: two steps of the third-order iteration from the hardware's estimate
+// 1 / sqrt(x) for positive normal x: one step of the third-order iteration from the hardware's estimate (measured: 5.2e-8 of relative
+// error before it, 1.4e-16 after it and after a second one)
 __device__ __forceinline__ double inv_sqrt(double x)
 {
-    double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const double e = fma(-x * y, y, 1.0);
-        y = fma(y * e, fma(0.375, e, 0.5), y);
-    }
-    return y;
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 // where element (row, k) of W lies: the order in which the lanes of panel_apply_kernel read it
@@ -202,25 +198,36 @@ __global__ __launch_bounds__(256, 2) void panel_chol_kernel(QrFactor *fs, int pa
     {
         const int splits = gram_splits(F.n);
         const ASTERIA_GLOBAL double *g = (const ASTERIA_GLOBAL double *)F.gram;
+        // The loads of a range stand side by side, blocks beyond the diagonal included (a copy of the last one): a branch around each
+        // block waits for each, nine times a memory latency
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int i = q == 0 ? 7 - w : w, slot0 = q == 0 ? 9 * w : 9 * w + 8 - w;
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
-            for (int j = 0; j < (q == 0 ? 8 : 4); ++j) {
-                doublex4 t = {0.0, 0.0, 0.0, 0.0};
-                if (j <= i) {
-                    for (int s = 0; s < splits; ++s)
-                        t += *(const ASTERIA_GLOBAL doublex4 *)(g + ((size_t)(s * GRAM_BLOCKS + slot0 + j) * 64 + lane) * 4);
+            for (int j = 0; j < (q == 0 ? 8 : 4); ++j) acc[q][j] = (doublex4){0.0, 0.0, 0.0, 0.0};
+        for (int s = 0; s < splits; ++s) {
+            doublex4 t[12];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int j = 0; j < (q == 0 ? 8 : 4); ++j) {
+                    const int i = q == 0 ? 7 - w : w, slot = (q == 0 ? 9 * w : 9 * w + 8 - w) + min(j, i);
+                    t[8 * q + j] = *(const ASTERIA_GLOBAL doublex4 *)(g + ((size_t)(s * GRAM_BLOCKS + slot) * 64 + lane) * 4);
                 }
-                // rows and columns beyond `rows` are those of the identity: the blocks need no edge cases
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int j = 0; j < (q == 0 ? 8 : 4); ++j) acc[q][j] += t[8 * q + j];
+        }
+        // rows and columns beyond `rows` are those of the identity: the blocks need no edge cases
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int j = 0; j < (q == 0 ? 8 : 4); ++j)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int row = 16 * i + 4 * v + h, col = 16 * j + r;
-                    if (row >= rows || col >= rows) t[v] = row == col ? 1.0 : 0.0;
+                    const int row = 16 * (q == 0 ? 7 - w : w) + 4 * v + h, col = 16 * j + r;
+                    if (row >= rows || col >= rows) acc[q][j][v] = row == col ? 1.0 : 0.0;
                 }
-                acc[q][j] = t;
-            }
-        }
     }
     // block column kb (rows below) and the finished columns of block row kb, one vector of 16 per lane of the pass
     auto hand_out = [&](int kb) __attribute__((always_inline)) {
@@ -278,8 +285,15 @@ __global__ __launch_bounds__(256, 2) void panel_chol_kernel(QrFactor *fs, int pa
                 // the next pivot first: its square root runs beside the other updates
                 v[k + 1] = fma(-t, lane_value(t, k + 1), v[k + 1]);
                 rd = scale_of(k + 1);
+                // (four multipliers at a time: a scalar can be used two instructions after it was fetched)
 #pragma unroll
-                for (int i = k + 2; i < CHOL_NB; ++i) v[i] = fma(-t, lane_value(t, i), v[i]);
+                for (int i0 = k + 2; i0 < CHOL_NB; i0 += 4) {
+                    double m[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) if (i0 + e < CHOL_NB) m[e] = lane_value(t, i0 + e);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) if (i0 + e < CHOL_NB) v[i0 + e] = fma(-t, m[e], v[i0 + e]);
+                }
                 // without this the multipliers of several columns are fetched ahead and spill
                 __builtin_amdgcn_sched_barrier(0);
             }
