@@ -56,6 +56,12 @@ struct MmaBf16 {
     __device__ static __forceinline__ int acc_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
 };
 
+// A quarter (64 x 64) of a tile per workgroup: the same wavefronts with one 32 x 32 block each, at their places in the whole tile.
+struct MmaBf16Quarter : MmaBf16 {
+    static constexpr int WAVES_M = 4, WAVES_N = 4;
+    static constexpr int WTM = 1, WTN = 1;
+};
+
 // hi / lo bf16 split of four fp32 values with round-to-nearest in both terms: hi = bf16(x),
 // lo = bf16(x - hi) (that difference is exact in fp32), so hi + lo keeps x to 2^-18 relative.
 // gfx950 converts two fp32 to a packed bf16 pair in one instruction (v_cvt_pk_bf16_f32), which
@@ -101,13 +107,13 @@ __device__ __forceinline__ void split4_f16(u32x4 x, u32x2 &hi, u32x2 &lo, float 
     }
 }
 
-// One operand tile (128 rows x BK) of input type TI staged as bf16 (or fp16) terms in LDS.
-template <typename TI, int NT, int BK, bool F16 = false>
+// One operand tile (ROWS rows x BK) of input type TI staged as bf16 (or fp16) terms in LDS.
+template <typename TI, int NT, int BK, bool F16 = false, int ROWS = BM>
 struct Bf16Stage {
     static_assert(!F16 || sizeof(TI) == 4, "fp16 terms: fp32 source");
     static constexpr int EPV = Elem<TI>::EPV;              // 8 (bf16) or 4 (fp32) elements per 16 bytes
     static constexpr int VPR = BK / EPV;
-    static constexpr int NV = BM * VPR / 256;
+    static constexpr int NV = ROWS * VPR / 256;
     // LDS rows are unpadded (BK elements); the 16-byte chunks of a row are XOR-swizzled by the row
     // index instead: the loader's lanes then write whole contiguous rows (4 rows = 256 bytes = all
     // 64 banks per 32 lanes), and the 16 rows a quarter-wavefront reads for one fragment chunk fall
@@ -117,7 +123,7 @@ struct Bf16Stage {
     static constexpr int CPR = BK / 8;                     // 16-byte chunks per row
     __device__ static __forceinline__ int swz(int row) { return (row / (16 / CPR)) % CPR; }
     static_assert(CPR == 4 || CPR == 8, "swizzle geometry");
-    static constexpr int TERM_ELEMS = BM * PITCH;
+    static constexpr int TERM_ELEMS = ROWS * PITCH;
     static constexpr int LDS_ELEMS = NT * TERM_ELEMS;      // per stage
     static_assert(NV >= 1, "slab too small");
     static_assert(sizeof(TI) == 2 ? NT == 1 : true, "bf16 operands are exact: one term");
@@ -161,16 +167,16 @@ struct Bf16Stage {
 };
 
 // TRI: which 32 x 32 blocks (i, j) of the wavefront's 64 x 64 sub-tile are multiplied (TRI_ALL,
-// TRI_NONE, or those with j - i <= TRI), as in gemm_mainloop
-template <typename TA, typename TB, int NTA, int NTB, bool GUARD, int TRI = TRI_ALL, bool F16 = false>
-__device__ __forceinline__ void gemm_bf16_mainloop(floatx16 (&acc)[2][2], const TA *Ab, const TB *Bb, int lda,
+// TRI_NONE, or those with j - i <= TRI), as in gemm_mainloop.  WT: blocks of a wavefront along either side, of a tile of 64 WT
+template <typename TA, typename TB, int NTA, int NTB, bool GUARD, int TRI = TRI_ALL, bool F16 = false, int WT = 2>
+__device__ __forceinline__ void gemm_bf16_mainloop(floatx16 (&acc)[WT][WT], const TA *Ab, const TB *Bb, int lda,
                                                    int ldb, int row0, int col0, int rowsA, int rowsB, int K,
                                                    bool vecA, bool vecB, ASTERIA_LDS uint16_t *smem, int tid,
                                                    int wm, int wn, int r, int h, float sca = 1.0f, float scb = 1.0f)
 {
     constexpr int BK = (NTA + NTB > 2) ? ASTERIA_SPLIT_BK : 64;
-    using StA = Bf16Stage<TA, NTA, BK, F16>;
-    using StB = Bf16Stage<TB, NTB, BK, F16>;
+    using StA = Bf16Stage<TA, NTA, BK, F16, 64 * WT>;
+    using StB = Bf16Stage<TB, NTB, BK, F16, 64 * WT>;
     auto mma = [](u32x4 a, u32x4 b, floatx16 c) __attribute__((always_inline)) {
         return F16 ? MmaBf16::mma_f16(a, b, c) : MmaBf16::mma(a, b, c);
     };
@@ -198,34 +204,34 @@ __device__ __forceinline__ void gemm_bf16_mainloop(floatx16 (&acc)[2][2], const 
 #pragma unroll
         for (int s = 0; s < (TRI == TRI_NONE ? 0 : STEPS); ++s) {
             const int ck = h * (KPL / 8) + s;    // the lane half owns a contiguous k range of the slab: chunk index
-            u32x4 ah[2], al[2], bh[2], bl[2];
+            u32x4 ah[WT], al[WT], bh[WT], bl[WT];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int rr = wm * 64 + i * 32 + r;
+            for (int i = 0; i < WT; ++i) {
+                const int rr = wm * 32 * WT + i * 32 + r;
                 const int kk = (ck ^ StA::swz(rr)) << 3;
                 ah[i] = *(const ASTERIA_LDS u32x4 *)(as + rr * StA::PITCH + kk);
                 if (NTA == 2) al[i] = *(const ASTERIA_LDS u32x4 *)(as + StA::TERM_ELEMS + rr * StA::PITCH + kk);
             }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int cc = wn * 64 + j * 32 + r;
+            for (int j = 0; j < WT; ++j) {
+                const int cc = wn * 32 * WT + j * 32 + r;
                 const int kk = (ck ^ StB::swz(cc)) << 3;
                 bh[j] = *(const ASTERIA_LDS u32x4 *)(bs + cc * StB::PITCH + kk);
                 if (NTB == 2) bl[j] = *(const ASTERIA_LDS u32x4 *)(bs + StB::TERM_ELEMS + cc * StB::PITCH + kk);
             }
             // small cross terms first, the leading product last
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < WT; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < WT; ++j) {
                     if (TRI != TRI_ALL && j - i > TRI) continue;
                     if (NTA == 2) acc[i][j] = mma(al[i], bh[j], acc[i][j]);
                     if (NTB == 2) acc[i][j] = mma(ah[i], bl[j], acc[i][j]);
                 }
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < WT; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < WT; ++j)
                     if (TRI == TRI_ALL || j - i <= TRI) acc[i][j] = mma(ah[i], bh[j], acc[i][j]);
         }
         if (STAGES == 1) __syncthreads();      // every wavefront has read the slab before it is overwritten
@@ -238,20 +244,21 @@ __device__ __forceinline__ void gemm_bf16_mainloop(floatx16 (&acc)[2][2], const 
     }
 }
 
-template <typename TA, typename TB, int NTA, int NTB>
+template <typename TA, typename TB, int NTA, int NTB, int ROWS = BM>
 constexpr size_t gemm_bf16_lds()
 {
     constexpr int BK = (NTA + NTB > 2) ? ASTERIA_SPLIT_BK : 64;
     return sizeof(uint16_t) * ((NTA + NTB > 2) ? ASTERIA_SPLIT_STAGES : 2) *
-           (size_t)(Bf16Stage<TA, NTA, BK>::LDS_ELEMS + Bf16Stage<TB, NTB, BK>::LDS_ELEMS);
+           (size_t)(Bf16Stage<TA, NTA, BK, false, ROWS>::LDS_ELEMS + Bf16Stage<TB, NTB, BK, false, ROWS>::LDS_ELEMS);
 }
 
-// tile t_global of a launch, 256 threads; gemm_bf16_lds() bytes at smem_raw
-template <typename TA, typename TB, int NTA, int NTB, bool F16>
+// tile t_global of a launch, or its quarter (row, column) `quarter`, 256 threads; gemm_bf16_lds() bytes at smem_raw
+template <typename TA, typename TB, int NTA, int NTB, bool F16, bool QUARTER = false>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmProblem *__restrict__ probs, int nprobs, int t_global, const int *__restrict__ state,
-                                               unsigned char *smem_raw)
+                                               unsigned char *smem_raw, int quarter = 0)
 {
-    using MM = MmaBf16;
+    using MM = std::conditional_t<QUARTER, MmaBf16Quarter, MmaBf16>;
+    constexpr int WT = MM::WTM;
     constexpr int BK = (NTA + NTB > 2) ? ASTERIA_SPLIT_BK : 64;
     ASTERIA_LDS uint16_t *smem = (ASTERIA_LDS uint16_t *)smem_raw;
     // the reduction scratch of the epilogue reuses the operand buffer (free after the K loop): with
@@ -284,11 +291,11 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmProblem *__restrict__ p
     const int wm = wave >> 1, wn = wave & 1;
     const int r = lane & 31, h = lane >> 5;
 
-    floatx16 acc[2][2];
+    floatx16 acc[WT][WT];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < WT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < WT; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
@@ -303,7 +310,18 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmProblem *__restrict__ p
     // fp16 terms: the operands are scaled into the fp16 range before the split, the sums scaled back
     float sca = 1.0f, scb = 1.0f;
     if (F16) { sca = P.sa_dev ? *P.sa_dev : P.sa; scb = P.sb_dev ? *P.sb_dev : P.sb; }
-    if (fast && d == 0)
+    int em = wm, en = wn;                             // place of the wavefront in the whole tile
+    if constexpr (QUARTER) {
+        const int qr = quarter >> 1, qc = quarter & 1;
+        if (64 * qr >= rowsA || 64 * qc >= rowsB || ((P.flags & GEMM_SYM) && ti == tj && qr < qc)) return;
+        em += 2 * qr; en += 2 * qc;
+        if (fast)
+            gemm_bf16_mainloop<TA, TB, NTA, NTB, false, TRI_ALL, F16, 1>(acc, Ab, Bb, lda, ldb, row0 + 64 * qr, col0 + 64 * qc, 64, 64, K,
+                                                                         vecA, vecB, smem, tid, wm, wn, r, h, sca, scb);
+        else
+            gemm_bf16_mainloop<TA, TB, NTA, NTB, true, TRI_ALL, F16, 1>(acc, Ab, Bb, lda, ldb, row0 + 64 * qr, col0 + 64 * qc, rowsA - 64 * qr,
+                                                                        rowsB - 64 * qc, K, vecA, vecB, smem, tid, wm, wn, r, h, sca, scb);
+    } else if (fast && d == 0)
         gemm_bf16_mainloop<TA, TB, NTA, NTB, false, 0, F16>(acc, Ab, Bb, lda, ldb, row0, col0, rowsA, rowsB, K, vecA,
                                                             vecB, smem, tid, wm, wn, r, h, sca, scb);
     else if (fast && d < 0)
@@ -318,13 +336,13 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmProblem *__restrict__ p
     if (F16) {
         const float inv = 1.0f / (sca * scb);     // powers of two: exact
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < WT; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < WT; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][j][v] *= inv;
     }
-    gemm_epilogue<MM, float>(P, acc, lt, ti, tj, row0, col0, rowsA, rowsB, wm, wn, r, h, lane, wave, tid, red);
+    gemm_epilogue<MM, float>(P, acc, lt, ti, tj, row0, col0, rowsA, rowsB, em, en, r, h, lane, wave, tid, red);
 }
 
 template <typename TA, typename TB, int NTA, int NTB, bool F16 = false>
@@ -338,16 +356,36 @@ __global__ __launch_bounds__(256, ASTERIA_BF16_MIN_WAVES) void gemm_bf16_grouped
     gemm_bf16_tile<TA, TB, NTA, NTB, F16>(probs, nprobs, t_global, state, smem_raw);
 }
 
+// Few tiles leave most of the chip idle and a wavefront alone on its SIMD, where it waits for every slab: 1.3 us of 0.35 of
+// products.  A quarter per workgroup then, up to four workgroups on a CU.  The sums of an element and their order are those of the
+// whole tile.  Not for problems with a partial sum per tile.
+// The line: us of a call, whole tiles / quarters, by tiles of its launches: update of matrices of 300 x 500 24 tiles 77 / 40, 120
+// 89 / 51, 240 95 / 73, 480 118 / 142, 960 205 / 256; of 900 x 1000 128 104 / 61, 256 106 / 83, 512 125 / 157; SOAP step of 900 x 700 96
+// 248 / 133, 384 298 / 322; SOAP refresh of 4 of 700 x 900 2657 / 2097, of 20 of 300 x 500 2286 / 1827.
+template <typename TA, typename TB, int NTA, int NTB, bool F16>
+__global__ __launch_bounds__(256, 4) void gemm_bf16_quarter_kernel(const GemmProblem *__restrict__ probs, int nprobs, int total_tiles,
+                                                                   const int *__restrict__ state)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int total = 4 * total_tiles, per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
+    const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
+    if (t < total) gemm_bf16_tile<TA, TB, NTA, NTB, F16, true>(probs, nprobs, t >> 2, state, smem_raw, t & 3);
+}
+
+constexpr int BF16_QUARTER_TILES = 256;
+
+// whole: never in quarters
 template <typename TA, typename TB, int NTA, int NTB, bool F16 = false>
 inline hipError_t launch_gemm_bf16_grouped(const GemmProblem *probs, int nprobs, int total_tiles,
-                                           const int *state, hipStream_t stream)
+                                           const int *state, hipStream_t stream, bool whole = false)
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
-    auto kern = gemm_bf16_grouped_kernel<TA, TB, NTA, NTB, F16>;
-    constexpr size_t lds = gemm_bf16_lds<TA, TB, NTA, NTB>();
-    static bool configured[MAX_DEVICES] = {};
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured); e != hipSuccess) return e;
-    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
+    const bool quarters = !whole && total_tiles <= BF16_QUARTER_TILES;
+    auto kern = quarters ? gemm_bf16_quarter_kernel<TA, TB, NTA, NTB, F16> : gemm_bf16_grouped_kernel<TA, TB, NTA, NTB, F16>;
+    const size_t lds = quarters ? gemm_bf16_lds<TA, TB, NTA, NTB, 64>() : gemm_bf16_lds<TA, TB, NTA, NTB>();
+    static bool configured[2][MAX_DEVICES] = {};
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured[quarters]); e != hipSuccess) return e;
+    const int per_xcd = ((quarters ? 4 : 1) * total_tiles + NUM_XCD - 1) / NUM_XCD;
     constexpr int kind = 32 | (sizeof(TA) == 2 ? 2 : 0) | (sizeof(TB) == 2 ? 4 : 0) | (NTA == 2 ? 64 : 0) | (NTB == 2 ? 128 : 0);
     profile_begin(kind, stream);
     hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(256), lds, stream, probs, nprobs, total_tiles, state);

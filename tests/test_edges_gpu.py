@@ -382,6 +382,26 @@ def test_two_sided_products_at_the_edges(blocks, out):
         assert float(torch.linalg.norm(M.double() - rot) / torch.linalg.norm(rot)) <= 3 * 2.0 ** -16, P.shape
 
 
+# Few tiles are computed in quarters, many whole: the same sums in the same order, so the same bits.  Sizes with remainders in the
+# first, the second and no quarter of a tile, rows of every alignment, k within one slab and over several.
+@pytest.mark.parametrize("grad", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("m, n", [(1, 1), (63, 65), (64, 64), (65, 127), (129, 31), (191, 193), (300, 517)])
+def test_products_in_quarters_are_those_of_whole_tiles(m, n, grad):
+    g = torch.Generator(device=DEV).manual_seed(m * 1000 + n)
+    XL, XR = (X + X.T for X in (torch.randn(k, k, device=DEV, generator=g) for k in (m, n)))
+    G = torch.randn(m, n, device=DEV, generator=g).to(grad)
+    alone = torch.empty(m, n, device=DEV)
+    ast.precondition([(XL, G, XR, alone)])
+    count = 257 // (((m + 127) // 128) * ((n + 127) // 128)) + 1
+    Ps = [torch.empty(m, n, device=DEV) for _ in range(count)]
+    ast.precondition([(XL, G, XR, P) for P in Ps])
+    torch.cuda.synchronize()
+    assert all(torch.equal(P, alone) for P in Ps)
+    ref = XL.double() @ G.double() @ XR.double()
+    # both terms kept to 2^-16 of every fp32 operand, products of random sign
+    assert float(torch.linalg.norm(alone.double() - ref) / torch.linalg.norm(ref)) <= 4 * 2.0 ** -16
+
+
 @pytest.mark.parametrize("opts", [None, dict(int8_slices=0), dict(lowp_from=40)])
 @pytest.mark.parametrize("power", [-100, -80, -64, 48])
 @pytest.mark.parametrize("sizes", [
