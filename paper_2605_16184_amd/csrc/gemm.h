@@ -140,6 +140,7 @@ template <typename TC> struct Mma;
 // v_mfma_f32_32x32x2_f32: A[i][k] in lane i + 32 k, B[k][j] in lane j + 32 k,
 // D[i][j] in lane j + 32 ((i / 4) % 2), register 4 (i / 8) + i % 4.
 template <> struct Mma<float> {
+    static constexpr int TILE = 128;   // edge of a workgroup's tile
     static constexpr int T = 32;       // MFMA tile edge
     static constexpr int KG = 2;       // lane groups along k
     static constexpr int NACC = 16;    // accumulator values per lane per tile
@@ -171,6 +172,7 @@ template <> struct Mma<float> {
 // v_mfma_f64_16x16x4_f64: A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
 // D[i][j] in lane j + 16 (i % 4), register i / 4.
 template <> struct Mma<double> {
+    static constexpr int TILE = 128;
     static constexpr int T = 16;
     static constexpr int KG = 4;
     static constexpr int NACC = 4;
@@ -197,6 +199,16 @@ template <> struct Mma<double> {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
     __device__ static __forceinline__ int acc_row(int v, int h) { return 4 * v + h; }
+};
+
+// A quarter (64 x 64) of a tile per workgroup of four wavefronts, one block each; and where these lie in the whole tile.
+struct MmaF32Quarter : Mma<float> {
+    static constexpr int TILE = 64;
+    static constexpr int WAVES_M = 2, WAVES_N = 2, NTHR = 256, WTM = 1, WTN = 1;
+    static constexpr int PITCH_KM = TILE + 4;
+};
+struct MmaF32Place : MmaF32Quarter {
+    static constexpr int WAVES_M = 4, WAVES_N = 4;
 };
 
 // ---- global -> register staging -------------------------------------------------------------
@@ -265,23 +277,23 @@ template <> struct StoreLds<float, bf16_t> {
     }
 };
 
-// One operand tile (128 rows x BK) staged per thread as NV 16-byte vectors.
-template <typename TC, typename TI, bool KMAJOR>
+// One operand tile (MM::TILE rows x BK) staged per thread as NV 16-byte vectors.
+template <typename TC, typename TI, bool KMAJOR, typename MM = Mma<TC>>
 struct OperandStage {
     static constexpr int EPV = Elem<TI>::EPV;
-    static constexpr int BK = Mma<TC>::BK;
-    static constexpr int VPR = KMAJOR ? (BM / EPV) : (BK / EPV);       // vectors per stored row
-    static constexpr int NTHREADS = Mma<TC>::NTHR;
-    static constexpr int TOTAL = (KMAJOR ? BK : BM) * VPR;             // vectors per tile
+    static constexpr int BK = MM::BK;
+    static constexpr int VPR = KMAJOR ? (MM::TILE / EPV) : (BK / EPV);       // vectors per stored row
+    static constexpr int NTHREADS = MM::NTHR;
+    static constexpr int TOTAL = (KMAJOR ? BK : MM::TILE) * VPR;             // vectors per tile
     static constexpr int NV = (TOTAL + NTHREADS - 1) / NTHREADS;       // vectors per thread
     // a tile with fewer vectors than threads (bf16 data under the 16-wide fp64 slab): the threads
     // beyond the tile stage nothing
     static constexpr bool PARTIAL = (TOTAL % NTHREADS) != 0;
-    static constexpr int LDS_ELEMS = KMAJOR ? BK * Mma<TC>::PITCH_KM : BM * Mma<TC>::PITCH_KC;
+    static constexpr int LDS_ELEMS = KMAJOR ? BK * MM::PITCH_KM : MM::TILE * MM::PITCH_KC;
 
     u32x4 r[NV];
 
-    // rows: number of valid rows of this tile (<= 128); k_left: valid k from k0 on.
+    // rows: number of valid rows of this tile (<= MM::TILE); k_left: valid k from k0 on.
     // GUARD = false: the tile is full, the slab is full and every vector is 16-byte aligned.
     template <bool GUARD>
     __device__ __forceinline__ void load(const TI *base, int ld, int row0, int rows, int k0, int k_left,
@@ -312,7 +324,7 @@ struct OperandStage {
 
     __device__ __forceinline__ void store(ASTERIA_LDS TC *lds, int tid) const
     {
-        constexpr int PITCH = KMAJOR ? Mma<TC>::PITCH_KM : Mma<TC>::PITCH_KC;
+        constexpr int PITCH = KMAJOR ? MM::PITCH_KM : MM::PITCH_KC;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int idx = tid + NTHREADS * v;
@@ -358,7 +370,7 @@ template <> __device__ __forceinline__ void store_c<double>(void *C, size_t off,
     else reinterpret_cast<double *>(C)[off] = v;
 }
 
-// K loop of one 128 x 128 tile: two LDS stages, the next slab is fetched into registers while
+// K loop of one tile: two LDS stages, the next slab is fetched into registers while
 // the current one feeds the matrix cores.
 // TRI selects which MFMA blocks (i, j) of the wavefront's sub-tile are multiplied: TRI_ALL all,
 // TRI_NONE none (the wavefront still stages its share of the operands), any other value d the
@@ -366,20 +378,19 @@ template <> __device__ __forceinline__ void store_c<double>(void *C, size_t off,
 // diagonal are never stored; for the wavefront at (wm, wn) those are the blocks with
 // j - i > d = (wm WROWS - wn WCOLS) / T.
 constexpr int TRI_ALL = 1000, TRI_NONE = -1000;
-template <typename TC, typename TA, typename TB, bool AKM, bool BKM, bool GUARD, int TRI = TRI_ALL>
-__device__ __forceinline__ void gemm_mainloop(typename Mma<TC>::acc_t (&acc)[Mma<TC>::WTM][Mma<TC>::WTN],
+template <typename TC, typename TA, typename TB, bool AKM, bool BKM, bool GUARD, int TRI = TRI_ALL, typename MM = Mma<TC>>
+__device__ __forceinline__ void gemm_mainloop(typename MM::acc_t (&acc)[MM::WTM][MM::WTN],
                                               const TA *Ab, const TB *Bb, int lda, int ldb, int row0, int col0,
                                               int rowsA, int rowsB, int K, bool vecA, bool vecB,
                                               ASTERIA_LDS TC *smem,
                                               int tid, int wm, int wn, int r, int h)
 {
-    using MM = Mma<TC>;
     constexpr int BK = MM::BK;
     constexpr int WTM = MM::WTM, WTN = MM::WTN;
-    constexpr int WROWS = BM / MM::WAVES_M, WCOLS = BN / MM::WAVES_N;
+    constexpr int WROWS = MM::TILE / MM::WAVES_M, WCOLS = MM::TILE / MM::WAVES_N;
     constexpr int T = MM::T;
-    using StA = OperandStage<TC, TA, AKM>;
-    using StB = OperandStage<TC, TB, BKM>;
+    using StA = OperandStage<TC, TA, AKM, MM>;
+    using StB = OperandStage<TC, TB, BKM, MM>;
     // LDS map: A stage 0 | A stage 1 | B stage 0 | B stage 1
     ASTERIA_LDS TC *const smemB = smem + 2 * StA::LDS_ELEMS;
     const int nk = (K + BK - 1) / BK;
@@ -792,28 +803,89 @@ __global__ __launch_bounds__(Mma<TC>::NTHR, Mma<TC>::MIN_WAVES) void gemm_groupe
     gemm_epilogue<MM, TC>(P, acc, lt, ti, tj, row0, col0, rowsA, rowsB, wm, wn, r, h, lane, wave, tid, red);
 }
 
-template <typename TC, typename TA, typename TB, bool AKM, bool BKM>
+// Few tiles of fp32 products: a quarter per workgroup (see gemm_bf16_quarter_kernel).  The sums of an element and their order are
+// those of the whole tile.  Not for problems with a partial sum per tile.
+// The line, us of a call, whole tiles / quarters: statistics of fp32 matrices of 500 x 300 (10 and 6 tiles in two launches) 1 98.6 / 49.0, 8
+// 93.6 / 53.1, 16 97.8 / 73.5, 24 108.9 / 97.3; update (12 and 12 tiles) 1 79.6 / 38.4, 10 86.5 / 60.1, 17 88.1 / 90.9, 20 90.6 / 95.5, 36 151 /
+// 163, 200 709 / 743; one-sided SOAP step of 3001 x 1024 (192 tiles) in a cycle of 2492 / 2456.  (Beyond the line it goes either way with
+// how the rounds fill: 30 149 / 146, 43 213 / 184.)
+template <typename TA, typename TB, bool AKM, bool BKM>
+__global__ __launch_bounds__(256, 4) void gemm_f32_quarter_kernel(const GemmProblem *__restrict__ probs, int nprobs, int total_tiles,
+                                                                  const int *__restrict__ state)
+{
+    using MM = MmaF32Quarter;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int total = 4 * total_tiles, per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
+    const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
+    if (t >= total) return;
+    const int t_global = t >> 2, qr = (t >> 1) & 1, qc = t & 1;
+    int lo = 0, hi = nprobs - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (probs[mid].tile_start <= t_global) lo = mid; else hi = mid - 1;
+    }
+    const GemmProblem &P = probs[lo];
+    if (P.state_idx >= 0 && !((1 << state[P.state_idx]) & P.state_mask)) return;
+    if (P.gate && *P.gate != 0) return;
+    const bool sym = (P.flags & GEMM_SYM) != 0;
+    const int lt = t_global - P.tile_start;
+    int ti, tj;
+    if (sym) tri_decode(lt, ti, tj);
+    else { ti = lt / P.tiles_n; tj = lt % P.tiles_n; }
+    const int row0 = ti * BM, col0 = tj * BN, rowsA = min(BM, P.M - row0), rowsB = min(BN, P.N - col0), K = P.K;
+    if (64 * qr >= rowsA || 64 * qc >= rowsB || (sym && ti == tj && qr < qc)) return;
+    const TA *Ab = reinterpret_cast<const TA *>(P.A);
+    const TB *Bb = reinterpret_cast<const TB *>(P.B);
+    const int lda = P.lda, ldb = P.ldb;
+    const bool vecA = ((reinterpret_cast<uintptr_t>(Ab) & 15u) == 0) && ((((size_t)lda * sizeof(TA)) & 15u) == 0);
+    const bool vecB = ((reinterpret_cast<uintptr_t>(Bb) & 15u) == 0) && ((((size_t)ldb * sizeof(TB)) & 15u) == 0);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
+    MM::acc_t acc[1][1];
+#pragma unroll
+    for (int v = 0; v < MM::NACC; ++v) acc[0][0][v] = 0.0f;
+    if (vecA && vecB && rowsA == BM && rowsB == BN && K % MM::BK == 0)
+        gemm_mainloop<float, TA, TB, AKM, BKM, false, TRI_ALL, MM>(acc, Ab, Bb, lda, ldb, row0 + 64 * qr, col0 + 64 * qc, 64, 64, K, vecA, vecB,
+                                                                   (ASTERIA_LDS float *)smem_raw, tid, wm, wn, r, h);
+    else
+        gemm_mainloop<float, TA, TB, AKM, BKM, true, TRI_ALL, MM>(acc, Ab, Bb, lda, ldb, row0 + 64 * qr, col0 + 64 * qc, min(64, rowsA - 64 * qr),
+                                                                  min(64, rowsB - 64 * qc), K, vecA, vecB, (ASTERIA_LDS float *)smem_raw, tid,
+                                                                  wm, wn, r, h);
+    gemm_epilogue<MmaF32Place, float>(P, acc, lt, ti, tj, row0, col0, rowsA, rowsB, 2 * qr + wm, 2 * qc + wn, r, h, lane, wave, tid, nullptr);
+}
+
+constexpr int F32_QUARTER_TILES = 200;
+
+template <typename TC, typename TA, typename TB, bool AKM, bool BKM, typename MM = Mma<TC>>
 constexpr size_t gemm_lds_bytes()
 {
-    return sizeof(TC) * 2 * (size_t)(OperandStage<TC, TA, AKM>::LDS_ELEMS + OperandStage<TC, TB, BKM>::LDS_ELEMS);
+    return sizeof(TC) * 2 * (size_t)(OperandStage<TC, TA, AKM, MM>::LDS_ELEMS + OperandStage<TC, TB, BKM, MM>::LDS_ELEMS);
 }
 
 // Enqueue one grouped launch.  probs / state are device pointers (state may be null when no
-// problem refers to it).
+// problem refers to it).  quarters: few tiles of fp32 products may be computed in quarters.
 template <typename TC, typename TA, typename TB, bool AKM, bool BKM>
 inline hipError_t launch_gemm_grouped(const GemmProblem *probs, int nprobs, int total_tiles,
-                                      const int *state, hipStream_t stream)
+                                      const int *state, hipStream_t stream, bool quarters = false)
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
     auto kern = gemm_grouped_kernel<TC, TA, TB, AKM, BKM>;
-    constexpr size_t lds = gemm_lds_bytes<TC, TA, TB, AKM, BKM>();
-    static bool configured[MAX_DEVICES] = {};
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured); e != hipSuccess) return e;
-    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
+    size_t lds = gemm_lds_bytes<TC, TA, TB, AKM, BKM>();
+    int threads = Mma<TC>::NTHR, parts = 1;
+    if constexpr (sizeof(TC) == 4) {
+        if (quarters && total_tiles <= F32_QUARTER_TILES) {
+            kern = gemm_f32_quarter_kernel<TA, TB, AKM, BKM>;
+            lds = gemm_lds_bytes<TC, TA, TB, AKM, BKM, MmaF32Quarter>();
+            threads = MmaF32Quarter::NTHR; parts = 4;
+        }
+    }
+    static bool configured[2][MAX_DEVICES] = {};
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured[parts == 4]); e != hipSuccess) return e;
+    const int per_xcd = (parts * total_tiles + NUM_XCD - 1) / NUM_XCD;
     constexpr int kind = (sizeof(TC) == 8 ? 1 : 0) | (sizeof(TA) == 2 ? 2 : 0) | (sizeof(TB) == 2 ? 4 : 0) |
                          (AKM ? 8 : 0) | (BKM ? 16 : 0);
     profile_begin(kind, stream);
-    hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(Mma<TC>::NTHR), lds, stream, probs, nprobs,
+    hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(threads), lds, stream, probs, nprobs,
                        total_tiles, state);
     profile_end(stream);
     return hipGetLastError();
