@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256) void pm_lanczos_kernel(const FactorDev *fd, Fa
     // unit vectors throughout: A times an unnormalised one would be of the size of A squared
     const float inv = beta > 0.0f ? 1.0f / beta : 0.0f;
     for (int i = tid; i < F.n; i += 256) w[i] *= inv;
-    __shared__ float la[LZ_MAX], lb[LZ_MAX];
+    __shared__ __align__(16) float la[LZ_MAX], lb[LZ_MAX];
     if (tid < it) { la[tid] = S.lz_a[tid]; lb[tid] = S.lz_b[tid]; }
     if (tid == 0) { S.lz_a[it] = la[it] = alpha; S.lz_b[it] = lb[it] = beta; }
     __syncthreads();

@@ -44,8 +44,10 @@ __device__ __forceinline__ double square_sum(const float4 &t)
 // One wavefront: largest eigenvalue of the symmetric tridiagonal matrix with diagonal a[0 .. m) and off-diagonal
 // b[0 .. m - 1), given `before`, that of the leading m - 1 rows (ignored for m = 1).  It lies in
 // [max(before, a_m), max(before, a_m) + |b_{m-1}|]; every lane tests one point of the bracket (all leading minors
-// of x I - T positive, by the three-term recurrence of the characteristic polynomials), so a round narrows it
-// 65-fold: 4 or 5 rounds to 1e-8 instead of 40 bisections.
+// of x I - T positive, by the three-term recurrence of the characteristic polynomials).  The first round's points lie
+// in powers of 1.38 from the lower end, 9 decades of what the last step may have raised the value by; every further round narrows
+// the bracket 65-fold: 2 to 4 rounds to 1e-8.
+// a, b: 16-byte aligned arrays of LZ_MAX in LDS, read eight rows at a time (what lies beyond row m is not used).
 __device__ inline double tridiag_largest(const float *a, const float *b, int m, double before)
 {
     const int lane = threadIdx.x & 63;
@@ -55,22 +57,36 @@ __device__ inline double tridiag_largest(const float *a, const float *b, int m, 
     hi += 1e-9 * hi;
     const double inv = 1.0 / hi;
     for (int round = 0; round < 7 && hi - lo > 1e-8 * hi; ++round) {
-        const double x = lo + (hi - lo) * ((double)(lane + 1) * (1.0 / 65.0)), xs = x * inv;
+        auto share = [&](int i) __attribute__((always_inline)) {
+            return round == 0 ? (double)exp2f(-0.46875f * (float)(63 - i)) : (double)(i + 1) * (1.0 / 65.0);
+        };
+        const double w = hi - lo, x = lo + w * share(lane), xs = x * inv;
         double p = 1.0, q = 0.0, b2 = 0.0;             // minors of x I - T, of order i and i - 1
         bool above = true;
-        for (int i = 0; i < m; ++i) {
-            const double t = (xs - (double)a[i] * inv) * p - b2 * q;
-            q = p; p = t;
-            above = above && p > 0.0;
-            const double bi = (double)b[i] * inv;
-            b2 = bi * bi;
-            if ((i & 15) == 15 && fabs(p) < 1e-60 && fabs(q) < 1e-60) { p *= 1e60; q *= 1e60; }
+        for (int i0 = 0; i0 < m; i0 += 8) {
+            float4 va[2], vb[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                va[e] = *reinterpret_cast<const float4 *>(a + i0 + 4 * e);
+                vb[e] = *reinterpret_cast<const float4 *>(b + i0 + 4 * e);
+            }
+            const float ra[8] = {va[0].x, va[0].y, va[0].z, va[0].w, va[1].x, va[1].y, va[1].z, va[1].w};
+            const float rb[8] = {vb[0].x, vb[0].y, vb[0].z, vb[0].w, vb[1].x, vb[1].y, vb[1].z, vb[1].w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                // rows beyond the last leave the minor as it is
+                const double t = (i0 + e < m ? xs - (double)ra[e] * inv : 1.0) * p - (i0 + e < m ? b2 : 0.0) * q;
+                q = p; p = t;
+                above = above && p > 0.0;
+                const double bi = (double)rb[e] * inv;
+                b2 = bi * bi;
+            }
+            if (fabs(p) < 1e-60 && fabs(q) < 1e-60) { p *= 1e60; q *= 1e60; }
         }
         const uint64_t mask = __ballot(above);
         const int first = mask ? __ffsll((long long)mask) - 1 : 64;     // first point at or above the largest eigenvalue
-        const double d = (hi - lo) * (1.0 / 65.0);
-        if (first < 64) hi = lo + d * (first + 1);
-        lo = lo + d * first;
+        if (first < 64) hi = lo + w * share(first);
+        if (first > 0) lo = lo + w * share(first - 1);
     }
     return 0.5 * (lo + hi);
 }
@@ -121,7 +137,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
     float *v = lz_smem, *vp = v + ld, *y = vp + ld;          // ld: n of the largest factor, padded to 256
     __shared__ float red[LZ_WAVES];
     __shared__ double redd[2][LZ_WAVES];
-    __shared__ float la[LZ_MAX], lb[LZ_MAX];
+    __shared__ __align__(16) float la[LZ_MAX], lb[LZ_MAX];
     __shared__ int done;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool vec = ((reinterpret_cast<uintptr_t>(A) & 15u) == 0) && ((lda & 3) == 0);
@@ -355,7 +371,7 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
     constexpr int RW = 32 / NI, RB = RW < 8 ? RW : 8, OWN = (256 * NI + LC_THREADS - 1) / LC_THREADS;
     __shared__ __align__(16) float v_lds[256 * NI];
     __shared__ double redd[2][LC_WAVES];
-    __shared__ float la[LZ_MAX], lb[LZ_MAX];
+    __shared__ __align__(16) float la[LZ_MAX], lb[LZ_MAX];
     __shared__ int done;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = F.n, members = lanczos_members(n), row0 = member * LC_WAVES * RW + wave * RW;
@@ -668,7 +684,7 @@ __global__ __launch_bounds__(256) void lanczos_step_kernel(const FactorDev *fd, 
             if (tid == 0) { S.rho = NAN; S.pm_done = 1; }
             return;
         }
-        __shared__ float la[LZ_MAX], lb[LZ_MAX];
+        __shared__ __align__(16) float la[LZ_MAX], lb[LZ_MAX];
         if (tid < j - 1) { la[tid] = S.lz_a[tid]; lb[tid] = S.lz_b[tid]; }
         if (tid == 0) { S.lz_a[j - 1] = la[j - 1] = alpha; S.lz_b[j - 1] = lb[j - 1] = beta; }
         __syncthreads();
