@@ -220,23 +220,20 @@ __device__ __forceinline__ void store_pair_block(char *C, int rowb, int n, int b
 // word holds digits 1 .. 4, the top digit comes back in `top`.
 constexpr double DIGIT_LIMIT4 = 2139062143.0;                 // 0x7f7f7f7f
 constexpr double DIGIT_LIMIT5 = 2139062143.0 * 256.0 + 127.0;
-__device__ __forceinline__ uint32_t digits4(int v) { return ((uint32_t)v + 0x00808080u) ^ 0x00808080u; }
-__device__ __forceinline__ uint32_t digits5(int64_t v, uint32_t &top)
-{
-    const uint64_t t = (uint64_t)(v + (int64_t)0x80808080ll);
-    top = (uint32_t)(t >> 32) & 0xffu;
-    return (uint32_t)t ^ 0x80808080u;
-}
 __device__ __forceinline__ int undigits4(uint32_t w) { return (int)((w ^ 0x00808080u) - 0x00808080u); }
 
-// integer-valued t in the digit range -> low word (and top digit); values beyond the range saturate and set `over`
+// x rounded to an integer in the digit range -> low word (and top digit); values beyond the range saturate and set `over`.
+// The rounding is that of an addition to 2^52 + 2^51, whose last bit is worth 1: the integer, already in the balanced form's offset,
+// is then the lower part of the sum's mantissa, without a conversion.
 template <int NS>
-__device__ __forceinline__ uint32_t digit_word(double t, uint32_t &top, bool &over)
+__device__ __forceinline__ uint32_t digit_word(double x, uint32_t &top, bool &over)
 {
-    const double lim = NS == 4 ? DIGIT_LIMIT4 : DIGIT_LIMIT5;
-    if (!(fabs(t) <= lim)) { over = true; t = t > 0.0 ? lim : (t < 0.0 ? -lim : 0.0); }
-    if constexpr (NS == 4) { top = 0u; return digits4((int)t); }
-    else return digits5((int64_t)t, top);
+    constexpr double lim = NS == 4 ? DIGIT_LIMIT4 : DIGIT_LIMIT5;
+    constexpr uint32_t offset = NS == 4 ? 0x00808080u : 0x80808080u;
+    if (!(fabs(x) < lim + 0.5)) { over = true; x = x > 0.0 ? lim : (x < 0.0 ? -lim : 0.0); }
+    const uint64_t t = (uint64_t)__double_as_longlong(x + (6755399441055744.0 + (double)offset));
+    top = NS == 4 ? 0u : (uint32_t)(t >> 32) & 0xffu;
+    return (uint32_t)t ^ offset;
 }
 
 // 16 words of 16 consecutive k of one row -> one 16-byte chunk per digit, digit s at p + 32 s
@@ -312,24 +309,33 @@ __device__ __forceinline__ void store_digit_block(char *C, int rowb, int n, int 
     }
 }
 
-// The block of a symmetric digit plane at (br, bc) in accumulator order (integers as doubles), from its mirror image.
+// The block of a symmetric digit plane at (br, bc) in accumulator order (integers as doubles), from its mirror image: groups q and
+// q + 2 of four rows (q = 0 or 1).  p: digit 0 of rows br + 16 h .. of the lane's column, h = lane / 32.  A half wavefront reads 8 bytes
+// of the 16 and trades those the other half needs.
 template <int NS>
-__device__ __forceinline__ void load_digit_group(const char *p, int g, double (&v)[4])
+__device__ __forceinline__ void load_digit_groups(const char *p, int q, double (&v)[2][4])
 {
-    uint32_t b[NS];
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    uint32_t b[2][NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) b[s] = *(const ASTERIA_GLOBAL uint32_t *)(p + 32 * s + 8 * g);
-    const uint32_t in[4] = {b[NS - 1], b[NS - 2], b[NS - 3], b[NS - 4]};
-    uint32_t o[4];
-    transpose4x4(in, o);
+    for (int s = 0; s < NS; ++s) {
+        const u32x2_t w = *(const ASTERIA_GLOBAL u32x2_t *)(p + 32 * s + 8 * q);
+        b[0][s] = w[0]; b[1][s] = w[1];
+        swap_halves(b[0][s], b[1][s]);
+    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if constexpr (NS == 4) v[e] = (double)undigits4(o[e]);
-        else {
-            // low word: four balanced digits, sum in [-0x80808080, 0x7f7f7f7f]
-            const int64_t low = (int64_t)(uint64_t)(o[e] ^ 0x80808080u) - (int64_t)0x80808080ll;
-            const int t = (int)(b[0] << (24 - 8 * e)) >> 24;
-            v[e] = (double)t * 4294967296.0 + (double)low;
+    for (int g = 0; g < 2; ++g) {
+        const uint32_t in[4] = {b[g][NS - 1], b[g][NS - 2], b[g][NS - 3], b[g][NS - 4]};
+        uint32_t o[4];
+        transpose4x4(in, o);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (NS == 4) v[g][e] = (double)undigits4(o[e]);
+            else {
+                // low word: four balanced digits, sum in [-0x80808080, 0x7f7f7f7f]
+                const int t = (int)(b[g][0] << (24 - 8 * e)) >> 24;
+                v[g][e] = fma((double)t, 4294967296.0, (double)(o[e] ^ 0x80808080u)) - 2155905152.0;
+            }
         }
     }
 }

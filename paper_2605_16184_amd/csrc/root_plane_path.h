@@ -348,11 +348,11 @@ __global__ __launch_bounds__(256) void plane_init_kernel(const FactorDev *fd, co
             u32x4 top = {0u, 0u, 0u, 0u};
             if (ns == 4) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) w[e] = digit_word<4>(rint(m[e] * inv_q), t, over);
+                for (int e = 0; e < 16; ++e) w[e] = digit_word<4>(m[e] * inv_q, t, over);
                 store_digit_chunk<4>(F.D[0] + (size_t)r * digit_row_bytes(n, 4) + grp * 128 + hf * 16, w, top);
             } else {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) { w[e] = digit_word<5>(rint(m[e] * inv_q), t, over); top[e >> 2] |= t << (8 * (e & 3)); }
+                for (int e = 0; e < 16; ++e) { w[e] = digit_word<5>(m[e] * inv_q, t, over); top[e >> 2] |= t << (8 * (e & 3)); }
                 store_digit_chunk<5>(F.D[0] + (size_t)r * digit_row_bytes(n, 5) + grp * 160 + hf * 16, w, top);
             }
         } else if (tier == TIER_F64) {
@@ -444,11 +444,11 @@ __global__ __launch_bounds__(256) void plane_from_f64_kernel(const FactorDev *fd
         const int grp = c0 >> 5, hf = (c0 >> 4) & 1;
         if (S.ns == 4) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) wd[e] = digit_word<4>(rint((c0 + e < n ? src[e] : 0.0) * inv_q), t, over);
+            for (int e = 0; e < 16; ++e) wd[e] = digit_word<4>((c0 + e < n ? src[e] : 0.0) * inv_q, t, over);
             store_digit_chunk<4>(F.D[1] + (size_t)r * digit_row_bytes(n, 4) + grp * 128 + hf * 16, wd, top);
         } else {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) { wd[e] = digit_word<5>(rint((c0 + e < n ? src[e] : 0.0) * inv_q), t, over); top[e >> 2] |= t << (8 * (e & 3)); }
+            for (int e = 0; e < 16; ++e) { wd[e] = digit_word<5>((c0 + e < n ? src[e] : 0.0) * inv_q, t, over); top[e >> 2] |= t << (8 * (e & 3)); }
             store_digit_chunk<5>(F.D[1] + (size_t)r * digit_row_bytes(n, 5) + grp * 160 + hf * 16, wd, top);
         }
         if (over) F.flags[0] = 1;

@@ -749,21 +749,21 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
         asm volatile("" : "+v"(ln));            // addresses are made here, not kept through the K loop
         const int r = ln & 31, h = ln >> 5;
         const int col = bc + r;
-        const char *own = digits_of(o.O1) + (size_t)min(col, n - 1) * rowb + (br >> 5) * (32 * NS) + 4 * h;
+        const char *own = digits_of(o.O1) + (size_t)min(col, n - 1) * rowb + (br >> 5) * (32 * NS) + 16 * h;
         // calls use(v, row, value) for the block's elements; used once per output format (the second time
         // the own digits come from L1: cheaper than holding both formats in registers)
         auto values = [&](auto use) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                double ov[4];
-                load_digit_group<NS>(own, g, ov);
+            for (int q = 0; q < 2; ++q) {
+                double ov[2][4];
+                load_digit_groups<NS>(own, q, ov);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int v = 4 * g + e, row = br + 8 * g + 4 * h + e;
+                for (int e = 0; e < 8; ++e) {
+                    const int g = q + 2 * (e >> 2), v = 4 * g + (e & 3), row = br + 8 * g + 4 * h + (e & 3);
                     double t = (double)acc[0][i][v];
 #pragma unroll
                     for (int l = 1; l < L; ++l) t = t * 256.0 + (double)acc[l][i][v];
-                    const double val = c1 * ov[e] + cg * t;
+                    const double val = c1 * ov[e >> 2][e & 3] + cg * t;
                     use(v, row, (row < n && col < n) ? val : 0.0);
                 }
             }
@@ -772,7 +772,7 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
             uint32_t wd[16], tp[4] = {0u, 0u, 0u, 0u};
             values([&](int v, int, double val) {
                 uint32_t top;
-                wd[v] = digit_word<NS>(rint(val * inv_q), top, over);
+                wd[v] = digit_word<NS>(val * inv_q, top, over);
                 tp[v >> 2] |= top << (8 * (v & 3));
             });
             store_digit_block<NS>(digits_of(o.C), rowb, n, br, bc, wd, tp, ln, ws);
