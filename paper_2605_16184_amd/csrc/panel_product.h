@@ -35,12 +35,13 @@ struct PanelProblem {
 constexpr size_t pp_lds_bytes(int ny) { return 2u * PP_ROWS * 64u * (size_t)ny; }
 
 // tile t_global of a launch, 256 threads; pp_lds_bytes at smem_raw
-template <int NY, int NX, int MI>
+// YR: rows of Y, part `part` of the panel's 128
+template <int NY, int NX, int MI, int YR = PP_ROWS>
 __device__ __forceinline__ void panel_product_tile(const PanelProblem *__restrict__ probs, int nprobs, int t_global, const int *__restrict__ state,
-                                                   unsigned char *smem_raw)
+                                                   unsigned char *smem_raw, int part = 0)
 {
-    constexpr int NJ = PP_ROWS / 16, TX = 64 * MI, WSEL = MI == 4 ? 1 : 0;
-    constexpr uint32_t ROWB = 64u * NY, STAGE = PP_ROWS * ROWB;
+    constexpr int NJ = YR / 16, TX = 64 * MI, WSEL = MI == 4 ? 1 : 0, NV = YR / 32;    // NV: loads of Y per wavefront and slab
+    constexpr uint32_t ROWB = 64u * NY, STAGE = YR * ROWB;
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem_raw;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
@@ -58,18 +59,18 @@ __device__ __forceinline__ void panel_product_tile(const PanelProblem *__restric
     const int x0 = (lt / P.slots) * TX + wave * (16 * MI), nk = P.K / PP_BK;
     const float scx = P.x_scale, scy = uniform(*P.y_scale);
 
-    // ---- Y: memory -> registers -> LDS.  A load instruction brings 8 rows of 32 values, a wavefront its 32 rows.  An LDS row is
+    // ---- Y: memory -> registers -> LDS.  A load instruction brings 8 rows of 32 values, a wavefront its quarter of the rows.  An LDS row is
     // [32 hi][32 lo] in 16-byte chunks swizzled by row; chunk g holds k = 4 g .. 4 g + 3 and 16 + 4 g .. 19 + 4 g, as X does
-    const char *gy = reinterpret_cast<const char *>(P.Y) + (size_t)(panel * PP_ROWS + wave * 32) * P.ldy * 4;
+    const char *gy = reinterpret_cast<const char *>(P.Y) + (size_t)(panel * PP_ROWS + part * YR + wave * (YR / 4)) * P.ldy * 4;
     const uint32_t vy = (uint32_t)(lane >> 3) * (uint32_t)P.ldy * 4u + (uint32_t)(lane & 7) * 16u;
     const size_t sy = (size_t)P.ldy * 32;
-    u32x4 ry[4];
+    u32x4 ry[NV];
     auto load_y = [&](int s) __attribute__((always_inline)) {
         const size_t slab = (size_t)min(s, nk - 1);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) ry[v] = *(const ASTERIA_GLOBAL u32x4 *)(gy + (v * sy + slab * 128) + vy);
+        for (int v = 0; v < NV; ++v) ry[v] = *(const ASTERIA_GLOBAL u32x4 *)(gy + (v * sy + slab * 128) + vy);
     };
-    const uint32_t wrow = lds0 + (uint32_t)(wave * 32 + (lane >> 3)) * ROWB + (uint32_t)((lane >> 2) & 1) * 8u;
+    const uint32_t wrow = lds0 + (uint32_t)(wave * (YR / 4) + (lane >> 3)) * ROWB + (uint32_t)((lane >> 2) & 1) * 8u;
     const uint32_t wy = wrow + (uint32_t)((NY == 2 ? (lane & 3) ^ (lane >> 4) : (lane & 3) ^ (lane >> 5)) * 16);
     auto split = [](u32x4 x, float scale, uint32_t (&hi)[2], uint32_t (&lo)[2]) __attribute__((always_inline)) {
         pg_split_f16(__uint_as_float(x[0]), __uint_as_float(x[1]), scale, hi[0], lo[0]);
@@ -78,7 +79,7 @@ __device__ __forceinline__ void panel_product_tile(const PanelProblem *__restric
     auto stage = [&](uint32_t o, int v) __attribute__((always_inline)) {
         uint32_t hi[2], lo[2];
         split(ry[v], scy, hi, lo);
-        const uint32_t at = ((v & 1) ? (wy + o) ^ (NY == 2 ? 64u : 32u) : wy + o);   // rows 8 on: the swizzle's top bit
+        const uint32_t at = (((YR == 32 ? wave : v) & 1) ? (wy + o) ^ (NY == 2 ? 64u : 32u) : wy + o);   // rows 8 on: the swizzle's top bit
         *(ASTERIA_LDS u32x2_t *)(uintptr_t)(at + v * (8 * ROWB)) = (u32x2_t){hi[0], hi[1]};
         if constexpr (NY == 2) *(ASTERIA_LDS u32x2_t *)(uintptr_t)((at ^ 64u) + v * (8 * ROWB)) = (u32x2_t){lo[0], lo[1]};
     };
@@ -88,7 +89,7 @@ __device__ __forceinline__ void panel_product_tile(const PanelProblem *__restric
     };
     load_y(0);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) stage(0, v);
+    for (int v = 0; v < NV; ++v) stage(0, v);
     load_y(1);
 
     // wavefronts beyond the last row of X stage their part of Y and leave
@@ -97,7 +98,7 @@ __device__ __forceinline__ void panel_product_tile(const PanelProblem *__restric
         lds_barrier();
         for (int kt = 0; kt < nk; ++kt) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) stage(o, v);
+            for (int v = 0; v < NV; ++v) stage(o, v);
             load_y(kt + 2);
             o ^= STAGE;
             lds_barrier();
@@ -150,7 +151,7 @@ __device__ __forceinline__ void panel_product_tile(const PanelProblem *__restric
     read_y(0, 0);
     for (int kt = 0; kt < nk; ++kt) {
         const uint32_t no = o ^ STAGE;
-        // column blocks 0 .. 6: small cross terms first, the leading product last
+        // all column blocks but the last: small cross terms first, the leading product last
 #pragma unroll
         for (int j = 0; j + 1 < NJ; ++j) {
             const int q = j & 1;
@@ -163,8 +164,8 @@ __device__ __forceinline__ void panel_product_tile(const PanelProblem *__restric
                 for (int i = 0; i < MI; ++i) acc[i][j] = mma(xh[i], y[q][1], acc[i][j]);
 #pragma unroll
             for (int i = 0; i < MI; ++i) acc[i][j] = mma(xh[i], y[q][0], acc[i][j]);
-            if (j < 4) stage(no, j);
-            if (j == 4) load_y(kt + 2);
+            if (j < NV) stage(no, j);
+            if (j == (NV < NJ - 2 ? NV : NJ - 2)) load_y(kt + 2);
             __builtin_amdgcn_sched_barrier(0);
         }
         // the last one: the next slab is staged and everyone has read this one; two row blocks at a time, whose lanes then take
@@ -195,7 +196,7 @@ __device__ __forceinline__ void panel_product_tile(const PanelProblem *__restric
     int ln = lane;
     asm volatile("" : "+v"(ln));                     // addresses are made here, not kept through the K loop
     const int rr = ln >> 3, e8 = ln & 7;
-    ASTERIA_GLOBAL float *C = (ASTERIA_GLOBAL float *)P.C + (size_t)(panel * PP_ROWS + rr) * P.ldc + x0 + 4 * e8;
+    ASTERIA_GLOBAL float *C = (ASTERIA_GLOBAL float *)P.C + (size_t)(panel * PP_ROWS + part * YR + rr) * P.ldc + x0 + 4 * e8;
 #pragma unroll
     for (int jj = 0; jj < NJ / 2; ++jj)
 #pragma unroll
@@ -226,31 +227,33 @@ __device__ __forceinline__ void panel_product_tile(const PanelProblem *__restric
         }
 }
 
-template <int NY, int NX, int MI>
+template <int NY, int NX, int MI, int YR = PP_ROWS>
 __global__ __launch_bounds__(256, 2) void panel_product_kernel(const PanelProblem *__restrict__ probs, int nprobs, int total_tiles,
                                                                const int *__restrict__ state)
 {
+    constexpr int PARTS = PP_ROWS / YR;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
-    const int t_global = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
-    if (t_global < total_tiles) panel_product_tile<NY, NX, MI>(probs, nprobs, t_global, state, smem_raw);
+    const int total = PARTS * total_tiles, per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
+    const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
+    if (t < total) panel_product_tile<NY, NX, MI, YR>(probs, nprobs, t / PARTS, state, smem_raw, t % PARTS);
 }
 
 // `tiles` tiles of whole panels and the tiles of gemm_bf16.h of panels with a remainder, in one launch.  Either kind is spread over
 // the XCDs (joint_tile); the slower ones, with guards, come first.  SOAP refresh in us, joint / apart: matrices of 899 x 1405 in blocks of
 // 256 (38 of 256, 6 of 131, 4 of 125 each), 1: 685 / 768, 5: 809 / 929, 20: 1720 / 1869, 50: 4551 / 4705; of 1100 x 1405 in blocks of 512, 4: 1441
 // / 1574, 50: 5627 / 5853; of 1100 x 2500 in blocks of 1024, 4: 3165 / 3454, 40: 12409 / 12764.
-template <int NY, int NX, int MI>
+template <int NY, int NX, int MI, bool PARTS = false>
 __global__ __launch_bounds__(256, 2) void joint_product_kernel(const PanelProblem *__restrict__ probs, int nprobs, int tiles,
                                                                const GemmProblem *__restrict__ ragged, int nragged, int ragged_tiles,
                                                                const int *__restrict__ state)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
+    constexpr int P = PARTS ? 4 : 1;
     bool second;
-    const int t = joint_tile(ragged_tiles, tiles, second);
+    const int t = joint_tile(P * ragged_tiles, P * tiles, second);
     if (t < 0) return;
-    if (second) panel_product_tile<NY, NX, MI>(probs, nprobs, t, state, smem_raw);
-    else gemm_bf16_tile<float, float, NY, NX, true>(ragged, nragged, t, state, smem_raw);
+    if (second) panel_product_tile<NY, NX, MI, PP_ROWS / P>(probs, nprobs, t / P, state, smem_raw, t % P);
+    else gemm_bf16_tile<float, float, NY, NX, true, PARTS>(ragged, nragged, t / P, state, smem_raw, t % P);
 }
 
 // Whether a launch takes 256 rows of X per tile (MI = 4) or 128 (MI = 2: 150 registers, three workgroups on a CU);
@@ -263,14 +266,24 @@ inline bool pp_take_wide_tiles(int tiles_256)
     return tiles_256 >= 512;
 }
 
+// Few tiles of 128 rows of X: a quarter of the panel's rows per workgroup, whose products of a slab take less time than its loads.  The
+// sums of an element and their order stay.  SOAP refresh in us, whole / quarters up to 64 tiles / up to 128: 1 factor of n = 2048 (and 256) 5571
+// / 5131 / 5129, 4 of 640 and 1024 2133 / 2068 / 2067, 16 of 1024 2497 / 2368 / 2415, 32 of 1024 2772 / 2691 / 2875, 20 of 512 and 384 1040 /
+// 1008 / 1017.  Launches of both kinds of tiles, up to 200 (whose guarded tiles wait longest): whole / quarters, 1 matrix of 899 x 1405 in
+// blocks of 1024 2694 / 2160, of 256 902 / 802, 4 of 1100 x 2500 4740 / 4420 (up to 64: 4638), 4 of 1100 x 1405 in blocks of 512 1264 / 1176, 10 of
+// 1300 x 1500 3319 / 3228, 20 of 600 x 400 1215 / 1120.
+constexpr int PP_PART_TILES = 64, PP_JOINT_TILES = 200;
+
 template <int NY, int NX, int MI>
 inline hipError_t launch_panel_product(const PanelProblem *probs, int nprobs, int total_tiles, const int *state, hipStream_t stream)
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
     constexpr size_t lds = pp_lds_bytes(NY);
-    const int per_xcd = (total_tiles + NUM_XCD - 1) / NUM_XCD;
+    const bool parts = MI == 2 && total_tiles <= PP_PART_TILES;
+    const int per_xcd = ((parts ? 4 : 1) * total_tiles + NUM_XCD - 1) / NUM_XCD;
+    auto kern = parts ? panel_product_kernel<NY, NX, 2, PP_ROWS / 4> : panel_product_kernel<NY, NX, MI>;
     profile_begin(515, stream);
-    hipLaunchKernelGGL((panel_product_kernel<NY, NX, MI>), dim3(per_xcd * NUM_XCD), dim3(256), lds, stream, probs, nprobs, total_tiles, state);
+    hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(256), lds, stream, probs, nprobs, total_tiles, state);
     profile_end(stream);
     return hipGetLastError();
 }
@@ -280,14 +293,16 @@ inline hipError_t launch_joint_product(const PanelProblem *probs, int nprobs, in
                                        const int *state, hipStream_t stream)
 {
     if (tiles + ragged_tiles <= 0) return hipSuccess;
-    auto kern = joint_product_kernel<NY, NX, MI>;
+    const bool parts = MI == 2 && tiles + ragged_tiles <= PP_JOINT_TILES;
+    auto kern = parts ? joint_product_kernel<NY, NX, 2, true> : joint_product_kernel<NY, NX, MI>;
     constexpr size_t lds = gemm_bf16_lds<float, float, NY, NX>();
     static_assert(lds >= pp_lds_bytes(NY), "either kind of tile");
-    static bool configured[MAX_DEVICES] = {};
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured); e != hipSuccess) return e;
+    static bool configured[2][MAX_DEVICES] = {};
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured[parts]); e != hipSuccess) return e;
+    const int p = parts ? 4 : 1;
     profile_begin(515, stream);
-    hipLaunchKernelGGL(kern, dim3(joint_grid(ragged_tiles, tiles)), dim3(256), lds, stream, probs, nprobs, tiles, ragged, nragged, ragged_tiles,
-                       state);
+    hipLaunchKernelGGL(kern, dim3(joint_grid(p * ragged_tiles, p * tiles)), dim3(256), lds, stream, probs, nprobs, tiles, ragged, nragged,
+                       ragged_tiles, state);
     profile_end(stream);
     return hipGetLastError();
 }
