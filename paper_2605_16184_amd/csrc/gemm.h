@@ -201,13 +201,13 @@ template <> struct Mma<double> {
     __device__ static __forceinline__ int acc_row(int v, int h) { return 4 * v + h; }
 };
 
-// A quarter (64 x 64) of a tile per workgroup of four wavefronts, one block each; and where these lie in the whole tile.
-struct MmaF32Quarter : Mma<float> {
+// A quarter (64 x 64) of a tile per workgroup of four wavefronts of 32 x 32; and where these lie in the whole tile.
+template <typename TC> struct MmaQuarter : Mma<TC> {
     static constexpr int TILE = 64;
-    static constexpr int WAVES_M = 2, WAVES_N = 2, NTHR = 256, WTM = 1, WTN = 1;
-    static constexpr int PITCH_KM = TILE + 4;
+    static constexpr int WAVES_M = 2, WAVES_N = 2, NTHR = 256, WTM = 32 / Mma<TC>::T, WTN = WTM;
+    static constexpr int PITCH_KM = TILE + 16 / (int)sizeof(TC);
 };
-struct MmaF32Place : MmaF32Quarter {
+template <typename TC> struct MmaQuarterPlace : MmaQuarter<TC> {
     static constexpr int WAVES_M = 4, WAVES_N = 4;
 };
 
@@ -803,17 +803,19 @@ __global__ __launch_bounds__(Mma<TC>::NTHR, Mma<TC>::MIN_WAVES) void gemm_groupe
     gemm_epilogue<MM, TC>(P, acc, lt, ti, tj, row0, col0, rowsA, rowsB, wm, wn, r, h, lane, wave, tid, red);
 }
 
-// Few tiles of fp32 products: a quarter per workgroup (see gemm_bf16_quarter_kernel).  The sums of an element and their order are
+// Few tiles: a quarter per workgroup (see gemm_bf16_quarter_kernel).  The sums of an element and their order are
 // those of the whole tile.  Not for problems with a partial sum per tile.
 // The line, us of a call, whole tiles / quarters: statistics of fp32 matrices of 500 x 300 (10 and 6 tiles in two launches) 1 98.6 / 49.0, 8
 // 93.6 / 53.1, 16 97.8 / 73.5, 24 108.9 / 97.3; update (12 and 12 tiles) 1 79.6 / 38.4, 10 86.5 / 60.1, 17 88.1 / 90.9, 20 90.6 / 95.5, 36 151 /
 // 163, 200 709 / 743; one-sided SOAP step of 3001 x 1024 (192 tiles) in a cycle of 2492 / 2456.  (Beyond the line it goes either way with
-// how the rounds fill: 30 149 / 146, 43 213 / 184.)
-template <typename TA, typename TB, bool AKM, bool BKM>
-__global__ __launch_bounds__(256, 4) void gemm_f32_quarter_kernel(const GemmProblem *__restrict__ probs, int nprobs, int total_tiles,
+// how the rounds fill: 30 149 / 146, 43 213 / 184.)  Statistics with fp64 sums of 500 x 300: 1 226.6 / 139.1, 10 231 / 153, 20 (200 and 120) 235 / 228,
+// 24 (240) 237 / 255, 40 334 / 348; of 1024 x 1024 (36 tiles) 1 328 / 133, 3 337 / 202, 6 (216) 340 / 358.
+template <typename TC, typename TA, typename TB, bool AKM, bool BKM>
+__global__ __launch_bounds__(256, sizeof(TC) == 4 ? 4 : 2) void gemm_quarter_kernel(const GemmProblem *__restrict__ probs, int nprobs, int total_tiles,
                                                                   const int *__restrict__ state)
 {
-    using MM = MmaF32Quarter;
+    using MM = MmaQuarter<TC>;
+    constexpr int T = MM::T;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int total = 4 * total_tiles, per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
     const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
@@ -840,21 +842,25 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_quarter_kernel(const GemmProb
     const bool vecA = ((reinterpret_cast<uintptr_t>(Ab) & 15u) == 0) && ((((size_t)lda * sizeof(TA)) & 15u) == 0);
     const bool vecB = ((reinterpret_cast<uintptr_t>(Bb) & 15u) == 0) && ((((size_t)ldb * sizeof(TB)) & 15u) == 0);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
-    MM::acc_t acc[1][1];
+    const int wm = wave >> 1, wn = wave & 1, r = lane % T, h = lane / T;
+    typename MM::acc_t acc[MM::WTM][MM::WTN];
 #pragma unroll
-    for (int v = 0; v < MM::NACC; ++v) acc[0][0][v] = 0.0f;
+    for (int i = 0; i < MM::WTM; ++i)
+#pragma unroll
+        for (int j = 0; j < MM::WTN; ++j)
+#pragma unroll
+            for (int v = 0; v < MM::NACC; ++v) acc[i][j][v] = (TC)0;
     if (vecA && vecB && rowsA == BM && rowsB == BN && K % MM::BK == 0)
-        gemm_mainloop<float, TA, TB, AKM, BKM, false, TRI_ALL, MM>(acc, Ab, Bb, lda, ldb, row0 + 64 * qr, col0 + 64 * qc, 64, 64, K, vecA, vecB,
-                                                                   (ASTERIA_LDS float *)smem_raw, tid, wm, wn, r, h);
+        gemm_mainloop<TC, TA, TB, AKM, BKM, false, TRI_ALL, MM>(acc, Ab, Bb, lda, ldb, row0 + 64 * qr, col0 + 64 * qc, 64, 64, K, vecA, vecB,
+                                                                   (ASTERIA_LDS TC *)smem_raw, tid, wm, wn, r, h);
     else
-        gemm_mainloop<float, TA, TB, AKM, BKM, true, TRI_ALL, MM>(acc, Ab, Bb, lda, ldb, row0 + 64 * qr, col0 + 64 * qc, min(64, rowsA - 64 * qr),
-                                                                  min(64, rowsB - 64 * qc), K, vecA, vecB, (ASTERIA_LDS float *)smem_raw, tid,
+        gemm_mainloop<TC, TA, TB, AKM, BKM, true, TRI_ALL, MM>(acc, Ab, Bb, lda, ldb, row0 + 64 * qr, col0 + 64 * qc, min(64, rowsA - 64 * qr),
+                                                                  min(64, rowsB - 64 * qc), K, vecA, vecB, (ASTERIA_LDS TC *)smem_raw, tid,
                                                                   wm, wn, r, h);
-    gemm_epilogue<MmaF32Place, float>(P, acc, lt, ti, tj, row0, col0, rowsA, rowsB, 2 * qr + wm, 2 * qc + wn, r, h, lane, wave, tid, nullptr);
+    gemm_epilogue<MmaQuarterPlace<TC>, TC>(P, acc, lt, ti, tj, row0, col0, rowsA, rowsB, 2 * qr + wm, 2 * qc + wn, r, h, lane, wave, tid, nullptr);
 }
 
-constexpr int F32_QUARTER_TILES = 200;
+constexpr int QUARTER_TILES = 200;
 
 template <typename TC, typename TA, typename TB, bool AKM, bool BKM, typename MM = Mma<TC>>
 constexpr size_t gemm_lds_bytes()
@@ -863,7 +869,7 @@ constexpr size_t gemm_lds_bytes()
 }
 
 // Enqueue one grouped launch.  probs / state are device pointers (state may be null when no
-// problem refers to it).  quarters: few tiles of fp32 products may be computed in quarters.
+// problem refers to it).  quarters: few tiles may be computed in quarters.
 template <typename TC, typename TA, typename TB, bool AKM, bool BKM>
 inline hipError_t launch_gemm_grouped(const GemmProblem *probs, int nprobs, int total_tiles,
                                       const int *state, hipStream_t stream, bool quarters = false)
@@ -872,12 +878,10 @@ inline hipError_t launch_gemm_grouped(const GemmProblem *probs, int nprobs, int 
     auto kern = gemm_grouped_kernel<TC, TA, TB, AKM, BKM>;
     size_t lds = gemm_lds_bytes<TC, TA, TB, AKM, BKM>();
     int threads = Mma<TC>::NTHR, parts = 1;
-    if constexpr (sizeof(TC) == 4) {
-        if (quarters && total_tiles <= F32_QUARTER_TILES) {
-            kern = gemm_f32_quarter_kernel<TA, TB, AKM, BKM>;
-            lds = gemm_lds_bytes<TC, TA, TB, AKM, BKM, MmaF32Quarter>();
-            threads = MmaF32Quarter::NTHR; parts = 4;
-        }
+    if (quarters && total_tiles <= QUARTER_TILES) {
+        kern = gemm_quarter_kernel<TC, TA, TB, AKM, BKM>;
+        lds = gemm_lds_bytes<TC, TA, TB, AKM, BKM, MmaQuarter<TC>>();
+        threads = MmaQuarter<TC>::NTHR; parts = 4;
     }
     static bool configured[2][MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured[parts == 4]); e != hipSuccess) return e;

@@ -37,6 +37,13 @@ __host__ __device__ inline double digit_dropped(int n, int ns, int levels, int e
     return 2.0 * n * sqrt((double)pairs) * 5461.0 * ldexp(1.0, ea + eb - 2 * (8 * ns - 1) + 8 * (2 * (ns - 1) - levels));
 }
 
+// least e with x <= 2^e, x > 0
+__device__ inline int ceil_log2(double x)
+{
+    int e;
+    return frexp(x, &e) == 0.5 ? e - 1 : e;
+}
+
 // diagonal of M_0 above which a second prefix iteration of degree 2 is kept on digits: two fp16 terms are too
 // coarse for entries of that size while the spectrum still reaches down to 4e-5
 constexpr double DIGIT_WIDE_DIAG = 0.25;
@@ -100,10 +107,12 @@ __device__ inline void plane_advance(const FactorDev &F, FactorScal &S, int *sta
     // matrices, and every norm by the scalar map) and from them the quanta of the digits
     const double dm = S.dmax, de = lin ? dm : fmin(b * dm, a), de2 = fmin(2.0 * a * (lin ? b * dm : de), a * a);
     const double dw = fmin(a * a * dm, sqrt(T.image.hi * hi) * 1.001), dm1 = fmin(a * a * a * a * dm, T.image.hi * 1.001);
-    const int ge = (int)ceil(log2(de * 1.02)), ge2 = (int)ceil(log2(de2 * 1.02)), gw = (int)ceil(log2(dw * 1.02));
-    const int gm1 = (int)ceil(log2(dm1 * 1.02));
-    int gm = (int)ceil(log2(dm * 1.02));
-    if (c.k > 0 && S.next_tier == TIER_DIGIT) gm = S.dexp[4] + 8 * S.ns - 1;      // the range the last M-update was stored with
+    // (beyond the prefix nothing runs on digits)
+    int ge = 0, ge2 = 0, gw = 0, gm1 = 0, gm = 0;
+    if (c.k < c.prefix) {
+        ge = ceil_log2(de * 1.02); ge2 = ceil_log2(de2 * 1.02); gw = ceil_log2(dw * 1.02); gm1 = ceil_log2(dm1 * 1.02);
+        gm = c.k > 0 && S.next_tier == TIER_DIGIT ? S.dexp[4] + 8 * S.ns - 1 : ceil_log2(dm * 1.02);      // the range the last M-update was stored with
+    }
     // error of the dropped levels of E2 W and E2 M relative to the bottom of M'
     auto dropped = [&](int ns, int levels) {
         return (digit_dropped(F.n, ns, levels, ge2, gw) + a * a * digit_dropped(F.n, ns, levels, ge2, gm)) / T.image.lo;

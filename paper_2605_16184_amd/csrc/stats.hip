@@ -262,11 +262,11 @@ extern "C" asteria_status asteria_stats_update(const asteria_block *blocks, int 
         }
         ASTERIA_HIP_TRY(up.flush());
         if (d == ASTERIA_F32) {
-            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, false, false>(dL, (int)t.L64[d].size(), t.tilesL64[d], nullptr, stream)));
-            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, true, true>(dR, (int)t.R64[d].size(), t.tilesR64[d], nullptr, stream)));
+            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, false, false>(dL, (int)t.L64[d].size(), t.tilesL64[d], nullptr, stream, true)));
+            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, true, true>(dR, (int)t.R64[d].size(), t.tilesR64[d], nullptr, stream, true)));
         } else {
-            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<double, bf16_t, bf16_t, false, false>(dL, (int)t.L64[d].size(), t.tilesL64[d], nullptr, stream)));
-            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<double, bf16_t, bf16_t, true, true>(dR, (int)t.R64[d].size(), t.tilesR64[d], nullptr, stream)));
+            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<double, bf16_t, bf16_t, false, false>(dL, (int)t.L64[d].size(), t.tilesL64[d], nullptr, stream, true)));
+            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<double, bf16_t, bf16_t, true, true>(dR, (int)t.R64[d].size(), t.tilesR64[d], nullptr, stream, true)));
         }
     }
     return ASTERIA_OK;
