@@ -1126,7 +1126,9 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
                 if (planes >= 0) from_f64(planes);
             }
             if (e == hipSuccess && pre && pl.i8_slices > 4 && edge != 256) {
-                e = launch_digit_product<0>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
+                e = 2 * tri_total <= PLANE_QUARTERS
+                        ? launch_digit_product<0, true>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream)
+                        : launch_digit_product<0>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
             } else {
                 if (e == hipSuccess && pre && pl.i8_slices > 0) e = launch_digit_product<4>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);
                 if (e == hipSuccess && pre && pl.i8_slices > 4) e = launch_digit_product<5>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream);

@@ -548,6 +548,10 @@ __global__ __launch_bounds__(256) void plane_finalize_kernel(const FactorDev *fd
 // 1.00, 650 1.01, 700 1.02, 750 1.06, 800 1.01, 900 1.04, 1000 1.06; n = 2048 396 1.01, 504 1.09, 612 1.06, 684 1.07, 900 1.05; n = 4096
 // 408 1.06, 680 1.08; but n = 600 700 0.88, 1000 0.90 (a quarter more work), and n = 512 1800 0.96 (short K: the stores weigh more).
 constexpr int PLANE_CUS = 256;
+// Digit products in quarters of a tile up to as many halves.  Refresh in us, halves / quarters, by halves: 1 factor of n = 128 and one of 100 (4)
+// 299.5 / 276.0, 512 and 400 (40) 441.5 / 412.7, 2 of 1024 (144) 682.9 / 656.1, 8 of 512 (160) 515.6 / 497.2, 120 of 128 (240) 446.8 / 430.8, 16 of 500 and
+// 400 (320) 596 / 601, 240 of 128 and 100 (480) 644 / 657, 22 of 512 (440) 770 / 773.
+constexpr int PLANE_QUARTERS = 256;
 constexpr int PLANE_SMALL_TILES = 250, PLANE_LARGE_TILES = 700, PLANE_LARGE_N = 512;   // the first: of a factor that small tiles can serve
 inline int pair_tile_edge(int tri64, int tri128, int tri256, int tri128_max, double work128, double work256, double n_mean)
 {

@@ -635,17 +635,18 @@ inline hipError_t launch_pair_product(const FactorDev *fd, const FactorScal *fs,
 // Measured, kind E2: 8 of n = 4096 (5, 6) 4.24 ms = 2540 TOP/s issued, the matrix pipe full at the 1.75 GHz that power
 // leaves (5.87 before, of which 1.1 went with the order of the tiles); 300 of n = 1024 (4, 4) 1.84 ms, 2.07 before, the
 // epilogue a fifth of it; (5, 6) 3.22, 3.45 before.
+// lower: 0 or 1 where a workgroup takes 64 rows of the half (BI = 1), -1 otherwise
 template <int NS, int L, int BI>
 __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal &S, int op, int k, int degree, int ti, int tj, int half,
-                                           unsigned char *smem)
+                                           int lower, unsigned char *smem)
 {
     constexpr int CPR = 2 * NS, ROWL = CPR * 16, RB = 64 * BI;
     using Loader = PlaneLoader<CPR, RB, 64, 4>;
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
-    const int n = F.n, col0 = tj * 128 + half * 64;
-    if (col0 >= n) return;                            // nothing to store; the half's partial sum was cleared when it was last read
+    const int n = F.n, row0 = ti * 128 + (lower > 0 ? 64 : 0), col0 = tj * 128 + half * 64;
+    if (col0 >= n || row0 >= n || (lower >= 0 && col0 > row0)) return;   // nothing to store; its partial sum was cleared when it was last read
     const int rowb = digit_row_bytes(n, NS);
     const RootOperands o = root_operands(op, degree == 1);
     auto digits_of = [&](int slot) { return F.D[slot < 2 ? slot ^ S.swapped : slot]; };
@@ -666,7 +667,6 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
     const double pd = uniform(first_x ? (double)S.x1a : 0.0), inv_x = uniform(1.0 / (double)S.x_scale);
     float rsum = 0.0f;
     bool over = false;
-    const int row0 = ti * 128;
     Loader ld;
     ld.init(digits_of(o.A), digits_of(o.B), rowb, n, row0, col0, wave, lane);
     i32x16 acc[L][BI];
@@ -794,57 +794,64 @@ __device__ __forceinline__ void digit_tile(const FactorDev &F, const FactorScal 
     }
     if (over) F.flags[0] = 1;                         // an entry beyond the bound of a positive semi-definite matrix
     if (op == OP_M) {
+        // by tiles of 64 x 64, or by tile and half
+        const int r64 = 2 * ti + max(lower, 0), at = lower >= 0 ? r64 * (r64 + 1) / 2 + 2 * tj + half : ti * (ti + 1) / 2 + tj + half * F.ntri;
         __syncthreads();
-        store_partial(rsum, reinterpret_cast<float *>(smem), F.partial + ti * (ti + 1) / 2 + tj + half * F.ntri, lane, wave, tid, 4);
+        store_partial(rsum, reinterpret_cast<float *>(smem), F.partial + at, lane, wave, tid, 4);
     }
 }
 
-// One half of a tile, by the digits of its factor (NS = 4: levels 4 or 5; NS = 5: levels 5 or 6).
-template <int NS>
-__device__ __forceinline__ void digit_half(const FactorDev &F, const FactorScal &S, int op, int k, int degree, uint2 tile, int half, unsigned char *smem)
+// One half of a tile, or 64 rows of it (lower >= 0), by the digits of its factor (NS = 4: levels 4 or 5; NS = 5: levels 5 or 6).
+template <int NS, bool QUARTER>
+__device__ __forceinline__ void digit_half(const FactorDev &F, const FactorScal &S, int op, int k, int degree, uint2 tile, int half, int lower,
+                                           unsigned char *smem)
 {
     const int ti = (int)(tile.y >> 16), tj = (int)(tile.y & 0xffffu);
     auto run = [&](auto bi) __attribute__((always_inline)) {
         constexpr int BI = decltype(bi)::value;
-        if (S.levels == NS) digit_tile<NS, NS, BI>(F, S, op, k, degree, ti, tj, half, smem);
-        else digit_tile<NS, NS + 1, BI>(F, S, op, k, degree, ti, tj, half, smem);
+        if (S.levels == NS) digit_tile<NS, NS, BI>(F, S, op, k, degree, ti, tj, half, lower, smem);
+        else digit_tile<NS, NS + 1, BI>(F, S, op, k, degree, ti, tj, half, lower, smem);
     };
-    if (F.n - ti * 128 <= 64) run(std::integral_constant<int, 1>{});
+    if constexpr (QUARTER) run(std::integral_constant<int, 1>{});
+    else if (F.n - ti * 128 <= 64) run(std::integral_constant<int, 1>{});
     else run(std::integral_constant<int, 2>{});
 }
 
-// One launch for factors of either number of digits (NS = 0) or one for each.  Where the launches themselves count - most find no
-// factor of their class, and cost 2.5 to 4.5 us in the chain - one; a batch of large tiles does not notice them, and its four digits run
-// without the registers that the fifth spills.
-template <int NS>
+// One launch for factors of either number of digits (NS = 0) or one for each.  Where the launches themselves count one; a batch of
+// large tiles does not notice them, and its four digits run without the registers that the fifth spills.
+// QUARTER: 64 x 64 per workgroup.  With few tiles the epilogue of two blocks one after the other is what a product waits for.  The line, us
+// of the refresh, halves / quarters, by halves of tiles: figures beside PLANE_QUARTERS.
+template <int NS, bool QUARTER>
 __global__ __launch_bounds__(256, 2) void digit_product_kernel(const FactorDev *__restrict__ fd, const FactorScal *__restrict__ fs,
                                                                const int *__restrict__ state, const uint2 *__restrict__ map, int total,
                                                                int op, int k, int degree)
 {
+    constexpr int PARTS = QUARTER ? 4 : 2;
     extern __shared__ __align__(16) unsigned char plane_smem[];
-    const int w = xcd_tile(2 * total);
-    if (w >= 2 * total) return;
-    const uint2 tile = map[w >> 1];
+    const int w = xcd_tile(PARTS * total);
+    if (w >= PARTS * total) return;
+    const uint2 tile = map[w / PARTS];
     const FactorScal &S = fs[tile.x];
-    const int st = state[tile.x], ns = S.ns;
+    const int st = state[tile.x], ns = S.ns, half = w & 1, lower = QUARTER ? (w >> 1) & 1 : -1;
     if (S.tier != TIER_DIGIT || (st != ST_RUN && !(st == ST_LAST && op == OP_SQ))) return;
-    if (NS == 4 || (NS == 0 && ns == 4)) { if (ns == 4) digit_half<4>(fd[tile.x], S, op, k, degree, tile, w & 1, plane_smem); }
-    else if (ns == 5) digit_half<5>(fd[tile.x], S, op, k, degree, tile, w & 1, plane_smem);
+    if (NS == 4 || (NS == 0 && ns == 4)) { if (ns == 4) digit_half<4, QUARTER>(fd[tile.x], S, op, k, degree, tile, half, lower, plane_smem); }
+    else if (ns == 5) digit_half<5, QUARTER>(fd[tile.x], S, op, k, degree, tile, half, lower, plane_smem);
 }
 
 constexpr size_t digit_lds(int ns) { return 2 * (size_t)(128 + 64) * (2 * ns) * 16; }     // two stages
 static_assert(digit_lds(4) >= 4 * (size_t)PLANE_SCRATCH_BYTES, "store scratch fits the stages");
 
-template <int NS>
+template <int NS, bool QUARTER = false>
 inline hipError_t launch_digit_product(const FactorDev *fd, const FactorScal *fs, const int *state, const uint2 *map, int total,
                                        int op, int k, int degree, hipStream_t stream)
 {
     if (total <= 0) return hipSuccess;
     constexpr size_t lds = digit_lds(NS == 0 ? 5 : NS);
+    auto kern = digit_product_kernel<NS, QUARTER>;
     static bool configured[MAX_DEVICES] = {};
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(digit_product_kernel<NS>), lds, configured); e != hipSuccess) return e;
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured); e != hipSuccess) return e;
     profile_begin(NS == 0 ? 304 : 300 + NS, stream);
-    hipLaunchKernelGGL(digit_product_kernel<NS>, dim3(xcd_blocks(2 * total)), dim3(256), lds, stream, fd, fs, state, map, total, op, k, degree);
+    hipLaunchKernelGGL(kern, dim3(xcd_blocks((QUARTER ? 4 : 2) * total)), dim3(256), lds, stream, fd, fs, state, map, total, op, k, degree);
     profile_end(stream);
     return hipGetLastError();
 }

@@ -99,6 +99,24 @@ def test_largest_eigenvalue_from_registers(sizes, packed):
     assert int(info[0]) == 2
 
 
+# Few digit tiles are computed in quarters, many in halves: the same integers.  (The sums of the residual have another order; it enters the
+# interval of a factor off the schedule only, a few units of 2^-24.)  Remainders in either half of a tile, and none.
+@pytest.mark.parametrize("eps", [1e-6, 1e-8])
+@pytest.mark.parametrize("n", [65, 128, 130, 192, 200, 300])
+def test_digit_products_in_quarters_are_those_of_halves(n, eps):
+    A = _with_spectrum(n, _spectrum("power", n), 7, n)
+    count = 129 // (((n + 127) // 128) * ((n + 127) // 128 + 1) // 2) + 1
+    alone, Xs = torch.full_like(A, float("nan")), [torch.full_like(A, float("nan")) for _ in range(count)]
+    info = torch.full((count,), -1, dtype=torch.int32, device=DEV)
+    ast.inverse_root([(A, alone)], eps, info=info[:1])
+    ast.inverse_root([(A, X) for X in Xs], eps, info=info)
+    torch.cuda.synchronize()
+    assert bool((info == 0).all())
+    for X in Xs:
+        assert float(torch.linalg.norm(X - alone) / torch.linalg.norm(alone)) <= 1e-5
+    assert _root_error(A, alone, eps)[0] <= 2e-3
+
+
 # mostly small factors, for which small tiles pay, beside one that is too large for them
 def test_roots_of_small_factors_beside_a_large_one():
     sizes = [2700] + [64] * 1100
