@@ -903,7 +903,9 @@ asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int 
     }
     if (lanczos_by_factor(elems, n_max, any_packed)) {
         if (any_packed) hipLaunchKernelGGL(lanczos_unpack_kernel, dim3(tri_max, cnt), dim3(256), 0, stream, d_fd);
-        if (n_max <= 256) {
+        if (n_max <= LZ_FEW_N) {
+            hipLaunchKernelGGL((lanczos_factor_kernel<true, LZ_FEW_THREADS>), dim3(cnt), dim3(LZ_FEW_THREADS), lds, stream, d_fd, d_fs, tol2, steps, -1, ld);
+        } else if (n_max <= 256) {
             hipLaunchKernelGGL(lanczos_factor_kernel<true>, dim3(cnt), dim3(LZ_THREADS), lds, stream, d_fd, d_fs, tol2, steps, -1, ld);
         } else {
             ASTERIA_HIP_TRY(ensure_dynamic_lds(reinterpret_cast<const void *>(lanczos_factor_kernel<false>), 3 * sizeof(float) * LZ_WG_MAX_N, cfg_f));

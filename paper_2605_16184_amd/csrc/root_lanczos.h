@@ -113,7 +113,7 @@ __device__ inline bool lanczos_advance(FactorScal &S, const float *a, const floa
 }
 
 // ---- one workgroup per factor --------------------------------------------------------------------------
-constexpr int LZ_THREADS = 1024, LZ_WAVES = LZ_THREADS / 64;
+constexpr int LZ_THREADS = 1024, LZ_FEW_THREADS = 512, LZ_FEW_N = 128;
 
 __device__ __forceinline__ float row_sum16(float v)       // sum over 16 consecutive lanes
 {
@@ -122,11 +122,13 @@ __device__ __forceinline__ float row_sum16(float v)       // sum over 16 consecu
     return v;
 }
 
-// RESIDENT: every factor has n <= 256 and is held in registers.  resume >= 0: continue after that many launches
+// RESIDENT: every factor has n <= 256 and is held in registers; on 512 threads where all have n <= 128 (the same sums in the same order,
+// fewer wavefronts to wait for at a barrier; refresh of one factor of 128 and one of 100 274 -> 264 us, of 600 of n = 128 1380 -> 1332).  resume >= 0: continue after that many launches
 // of lanczos_step_kernel.
-template <bool RESIDENT>
-__global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const FactorDev *fd, FactorScal *fs, float tol2, int steps, int resume, int ld)
+template <bool RESIDENT, int THREADS = LZ_THREADS>
+__global__ __launch_bounds__(THREADS) void lanczos_factor_kernel(const FactorDev *fd, FactorScal *fs, float tol2, int steps, int resume, int ld)
 {
+    constexpr int WAVES = THREADS / 64, NI = THREADS == LZ_FEW_THREADS ? 2 : 4;     // NI: of 64 columns each
     const int f = blockIdx.x;
     FactorScal &S = fs[f];
     if (resume >= 0 && S.pm_done) return;
@@ -135,8 +137,8 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
     const float *__restrict__ A = F.Aw;
     extern __shared__ __align__(16) float lz_smem[];
     float *v = lz_smem, *vp = v + ld, *y = vp + ld;          // ld: n of the largest factor, padded to 256
-    __shared__ float red[LZ_WAVES];
-    __shared__ double redd[2][LZ_WAVES];
+    __shared__ float red[WAVES];
+    __shared__ double redd[2][WAVES];
     __shared__ __align__(16) float la[LZ_MAX], lb[LZ_MAX];
     __shared__ int done;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -148,17 +150,17 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
         if (lane == 0) redd[0][wave] = x;
         __syncthreads();
         double t = 0.0;
-        for (int w = 0; w < LZ_WAVES; ++w) t += redd[0][w];
+        for (int w = 0; w < WAVES; ++w) t += redd[0][w];
         return t;
     };
     // n <= 256: lane group g of 16 in wavefront w holds rows 16 w + 4 g .. + 3, lane c of it the columns 4 (c + 16 i) .. + 3
-    float ar[RESIDENT ? 4 : 1][16];
+    float ar[RESIDENT ? 4 : 1][4 * NI];
     const int rg = 16 * wave + 4 * (lane >> 4), cl = lane & 15;
     if constexpr (RESIDENT) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < NI; ++i) {
                 const int r = rg + q, c = 4 * (cl + 16 * i);
                 if (vec && r < n && c + 4 <= n) {
                     const float4 t = *reinterpret_cast<const float4 *>(A + (size_t)r * lda + c);
@@ -174,7 +176,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
     if (tid == 0) done = 0;
     if (resume < 0) {
         double s = 0.0;
-        for (int i = tid; i < ld; i += LZ_THREADS) {
+        for (int i = tid; i < ld; i += THREADS) {
             // the same start vector for every factor: a factor's result does not depend on its place in the batch
             const float x = i < n ? hash_unit(0u, (uint32_t)i) : 0.0f;
             v[i] = x; vp[i] = 0.0f;
@@ -182,21 +184,21 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
         }
         s = block_sum(s);
         const float inv = s > 0.0 ? (float)(1.0 / sqrt(s)) : 0.0f;
-        for (int i = tid; i < ld; i += LZ_THREADS) v[i] *= inv;
+        for (int i = tid; i < ld; i += THREADS) v[i] *= inv;
         double saa = 0.0, str = 0.0;
         if constexpr (RESIDENT) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) saa += (double)ar[q][e] * (double)ar[q][e];
+                for (int e = 0; e < 4 * NI; ++e) saa += (double)ar[q][e] * (double)ar[q][e];
         }
-        for (int i = tid; i < n; i += LZ_THREADS) str += (double)A[(size_t)i * lda + i];
+        for (int i = tid; i < n; i += THREADS) str += (double)A[(size_t)i * lda + i];
         saa = block_sum(saa);                                // streamed factors: gathered in the first product
         str = block_sum(str);
         if (tid == 0) { S.fro2 = saa; S.trace = str; S.rho = 0.0f; S.lz_small = 0; S.pm_done = 0; }
     } else {
         j0 = resume - 1;                                     // its y is there, its alpha is not
-        for (int i = tid; i < ld; i += LZ_THREADS) {
+        for (int i = tid; i < ld; i += THREADS) {
             v[i] = i < n ? F.pv[j0 % 3][i] : 0.0f;
             vp[i] = (i < n && j0 > 0) ? F.pv[(j0 + 2) % 3][i] : 0.0f;
             y[i] = i < n ? F.py[j0 & 1][i] : 0.0f;
@@ -209,14 +211,14 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
     for (int j = j0; j < steps; ++j) {
         float yv = 0.0f;
         if (j == j0 && resume >= 0) {
-            for (int i = tid; i < n; i += LZ_THREADS) yv += y[i] * v[i];
+            for (int i = tid; i < n; i += THREADS) yv += y[i] * v[i];
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) yv += __shfl_xor(yv, off, 64);
         } else if constexpr (RESIDENT) {
             float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
             if (16 * wave < n) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < NI; ++i) {
                     const float4 x = *reinterpret_cast<const float4 *>(v + 4 * (cl + 16 * i));
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
         } else {
             double saa = 0.0;
             auto product = [&](auto first) {
-                for (int r0 = 4 * wave; r0 < n; r0 += 4 * LZ_WAVES) {
+                for (int r0 = 4 * wave; r0 < n; r0 += 4 * WAVES) {
                     float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
                     double q[4] = {0.0, 0.0, 0.0, 0.0};
                     const float *ap[4];
@@ -288,10 +290,10 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
         __syncthreads();
         if (done) break;
         double alpha_d = 0.0;
-        for (int w = 0; w < LZ_WAVES; ++w) alpha_d += (double)red[w];
+        for (int w = 0; w < WAVES; ++w) alpha_d += (double)red[w];
         const float alpha = (float)alpha_d;
         double ww = 0.0;
-        for (int i = tid; i < n; i += LZ_THREADS) {
+        for (int i = tid; i < n; i += THREADS) {
             const float x = y[i] - alpha * v[i] - beta_p * vp[i];
             y[i] = x;
             ww += (double)x * (double)x;
@@ -301,14 +303,14 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_factor_kernel(const Factor
         if (lane == 0) redd[1][wave] = ww;
         __syncthreads();
         double ww_d = 0.0;
-        for (int w = 0; w < LZ_WAVES; ++w) ww_d += redd[1][w];
+        for (int w = 0; w < WAVES; ++w) ww_d += redd[1][w];
         const float beta = (float)sqrt(ww_d);
         if (!(beta < 3.0e38f) || !(fabsf(alpha) < 3.0e38f)) {         // non-finite input (uniform)
             if (tid == 0) S.rho = NAN;
             break;
         }
         const float inv = beta > 0.0f ? 1.0f / beta : 0.0f;
-        for (int i = tid; i < n; i += LZ_THREADS) {
+        for (int i = tid; i < n; i += THREADS) {
             const float t = v[i];
             v[i] = y[i] * inv;
             vp[i] = t;
