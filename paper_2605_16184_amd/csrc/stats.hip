@@ -224,7 +224,8 @@ extern "C" asteria_status asteria_stats_update(const asteria_block *blocks, int 
         ASTERIA_HIP_TRY(upload_async(dF, t.fast.data(), t.fast.size() * sizeof(StatsEntry), stream));
         const int per_xcd = (t.tiles_fast + NUM_XCD - 1) / NUM_XCD;
         profile_begin(512, stream);
-        hipLaunchKernelGGL(stats_product_kernel, dim3(per_xcd * NUM_XCD), dim3(256), 0, stream, dF, (int)t.fast.size(), t.tiles_fast, beta);
+        auto kern = t.tiles_fast <= STATS_FEW_TILES ? stats_product_kernel<2> : stats_product_kernel<1>;
+        hipLaunchKernelGGL(kern, dim3(per_xcd * NUM_XCD), dim3(256), 0, stream, dF, (int)t.fast.size(), t.tiles_fast, beta);
         profile_end(stream);
         ASTERIA_HIP_TRY(hipGetLastError());
     }

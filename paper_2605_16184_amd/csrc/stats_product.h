@@ -25,13 +25,15 @@ inline bool stats_operand_ok(const void *p, int rows, int cols, int ld)
     return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld % 8) == 0 && (cols % 8) == 0 && (size_t)rows * (size_t)ld * 2 < 0x70000000u;
 }
 
+// ST: slabs of LDS; with two the next slab is on its way while one is multiplied.
 // The K loop: acc += A B^T over the rows row0 .. and col0 .. of an operand of n rows (columns when KM), K long.
-template <bool KM>
+template <bool KM, int ST>
 __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16_t *G, int ldg, int n, int K, int row0, int col0,
                                              ASTERIA_LDS char *lds, int wave, int lane)
 {
     constexpr int OP = 128 * 128;                             // bytes of an operand's slab
     const bool diag = row0 == col0;
+    ASTERIA_LDS char *const first = lds;
     const int wm = wave >> 1, wn = wave & 1, r = lane & 31, h = lane >> 5;
     // wavefront w stages instructions 4 w .. 4 w + 3 of each operand's 16 (64 chunks of 16 bytes each)
     constexpr uint32_t OUTSIDE = 0x7ffffff0u;
@@ -55,9 +57,9 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
         }
     }
     const uint32_t slab_bytes = KM ? 64u * ldb : 128u;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)lds + (uint32_t)wave * 4096u;
+    const uint32_t lds_first = (uint32_t)(uintptr_t)lds + (uint32_t)wave * 4096u;
     auto issue = [&](int slab) __attribute__((always_inline)) {
-        const uint32_t off = (uint32_t)slab * slab_bytes;
+        const uint32_t off = (uint32_t)slab * slab_bytes, lds0 = lds_first + (uint32_t)(slab & (ST - 1)) * (2u * OP);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const bool in = slab * 64 + kof[v] < K;
@@ -135,13 +137,19 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
             }
         }
     };
+    if (ST == 2) issue(0);
     for (int kt = 0; kt < nk; ++kt) {
-        issue(kt);
-        wait_lds_loads<0>();
+        if (ST == 1) issue(kt);
+        if (ST == 2 && kt + 1 < nk) {
+            issue(kt + 1);
+            if (diag) wait_lds_loads<4>(); else wait_lds_loads<8>();
+        } else wait_lds_loads<0>();
+        lds = first + (kt & (ST - 1)) * (2 * OP);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");                        // the reads stay behind the barrier
         if (diag_d >= 0) compute();
-        wait_lds_loads<0>();                                  // this wavefront has read the slab
+        if (ST == 1) wait_lds_loads<0>();                     // this wavefront has read the slab
+        else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
     }
 }
@@ -160,10 +168,14 @@ __device__ __forceinline__ void stats_k_loop(floatx16 (&acc)[2][2], const uint16
 // 128 consecutive bytes of a row, the mirror image is four consecutive floats per lane -, no pass through LDS.  In a
 // whole tile they are read two pieces of 16 values ahead, and the fragments of a slab one step ahead: statistics of the 1.1B model,
 // packed, 3.57 -> 3.43 ms; of one layer, full storage, 239 -> 231 us.  Two stages of 32 k with loads a slab ahead: 3.59 ms, 238 us.
-__global__ __launch_bounds__(256, 4) void stats_product_kernel(const StatsEntry *__restrict__ entries, int count, int total,
+// Up to two tiles per CU nothing overlaps a workgroup's waits but itself: two slabs of LDS then (ST = 2).  Us of a call, one / two: blocks of
+// 1024 x 1024 (72 tiles) 1 20.5 / 19.4, 3 26.7 / 22.7, 5 33.2 / 30.8, 7 (504) 37.0 / 35.3, 9 (648) 47.8 / 52.0; packed 1000 x 2000 28.6 / 26.1.
+constexpr int STATS_FEW_TILES = 512;
+template <int ST>
+__global__ __launch_bounds__(256, ST == 1 ? 4 : 2) void stats_product_kernel(const StatsEntry *__restrict__ entries, int count, int total,
                                                                              float beta)
 {
-    __shared__ __align__(16) unsigned char smem[32768];
+    __shared__ __align__(16) unsigned char smem[32768 * ST];
     ASTERIA_LDS char *lds = (ASTERIA_LDS char *)smem;
     const int per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
     const int t = (int)(blockIdx.x % NUM_XCD) * per_xcd + (int)(blockIdx.x / NUM_XCD);
@@ -200,8 +212,8 @@ __global__ __launch_bounds__(256, 4) void stats_product_kernel(const StatsEntry 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    if (kmajor) stats_k_loop<true>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
-    else stats_k_loop<false>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
+    if (kmajor) stats_k_loop<true, ST>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
+    else stats_k_loop<false, ST>(acc, E.G, E.ldg, n, K, row0, col0, lds, wave, lane);
     const int diag_d = diag ? wm - wn : 1;                    // < 0: above the diagonal
     if (diag_d < 0) return;
 

@@ -400,6 +400,24 @@ def test_two_sided_products_at_the_edges(blocks, out):
         assert float(torch.linalg.norm(M.double() - rot) / torch.linalg.norm(rot)) <= 3 * 2.0 ** -16, P.shape
 
 
+# Few tiles stage two slabs, many one: the same sums in the same order
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("m, n", [(8, 8), (136, 264), (264, 56), (128, 1024)])
+def test_statistics_of_few_tiles_are_those_of_many(m, n, packed):
+    g = torch.Generator(device=DEV).manual_seed(m + n)
+    G = torch.randn(m, n, device=DEV, generator=g).bfloat16()
+
+    def fresh():
+        return [torch.zeros(ast.packed_elems(k) if packed else (k, k), device=DEV) for k in (m, n)]
+    one, layout = fresh(), 1 if packed else 0
+    tiles = sum(((k + 127) // 128) * ((k + 127) // 128 + 1) // 2 for k in (m, n))
+    many = [fresh() for _ in range(512 // tiles + 1)]
+    ast.stats_update([(G, one[0], one[1], 0, layout)], 0.95)
+    ast.stats_update([(G, L, R, 0, layout) for L, R in many], 0.95)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for s in many for a, b in zip(s, one))
+
+
 # Few tiles are computed in quarters, many whole: the same sums in the same order, so the same bits.  Sizes with remainders in the
 # first, the second and no quarter of a tile, rows of every alignment, k within one slab and over several.
 @pytest.mark.parametrize("grad", [torch.float32, torch.bfloat16])
