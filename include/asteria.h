@@ -445,7 +445,7 @@ asteria_status asteria_soap_reproject(const asteria_rblock *blocks, int nblocks,
  * fp32 split in two terms (the products on two-term storage too) and 96 = A split, B one term; 512 the
  * statistics; 513 and 514 whole tiles of a split fp32 matrix with another one or with a bf16 matrix, 515 the
  * panel products of the SOAP refresh;
- * 300 + NS the int8 kernels on NS slices or digits (304, 305).  Not thread safe.                    */
+ * 300 + NS the int8 kernels on NS slices or digits (304, 305; 304 too where one launch serves both). Not thread safe. */
 asteria_status asteria_profile_enable(int max_launches);
 int asteria_profile_collect(float *ms, int32_t *kind, int cap);
 /* Algorithmic flops (n^2 (n + 1) per symmetric product) of the products of the fp64 iterations since
