@@ -628,7 +628,7 @@ inline hipError_t launch_pair_product(const FactorDev *fd, const FactorScal *fs,
 // half of a tile, slabs of 32 k, two LDS stages of 24 (NS = 4) or 30 KiB: two workgroups per CU, so that one multiplies
 // while the other assembles and stores.  In a slab the lower digits of A come first; the products of its top digit, most of
 // all, cover the turn to the next slab.  Addresses and uniform factors of the epilogue are kept out of vector registers: nothing
-// spills at four digits; at five, where 192 registers are sums at L = 6, 33 do (120 bytes of scratch a lane).
+// spills at four digits; at five, where 192 registers are sums at L = 6, 40 do (136 bytes of scratch a lane).
 // Where at most 64 rows are left (BI = 1) a wavefront takes 32 of them: the epilogue of a block, an fp64 sum per level and element,
 // is longer than its products there.  A product of 226 factors of n = 64, (5, 6): 14.0 us, 20.1 with half of the wavefronts taking 64
 // rows each.

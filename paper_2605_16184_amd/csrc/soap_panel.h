@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256, 2) void panel_gram_kernel(const QrFactor *__re
 // of the four wavefronts with its own copy of that block - no barrier inside.  What remains, A and W to the right
 // and below, lives in MFMA accumulators (block rows 7 - w and w of the lower triangle in wavefront w; block
 // (i, j) is A for j > kb and W for j <= kb) and takes one rank-16 update per block column.
-// One panel: 190 us before (LDS, serial inner loops), 50 now.
+// One panel: 190 us before (LDS, serial inner loops), 36 now.
 constexpr double CHOL_REPEAT_MIN = 0.1;
 constexpr int CHOL_NB = 16;
 constexpr int CHOL_PITCH = CHOL_NB + 2;              // doubles; rows stay 16-byte aligned
