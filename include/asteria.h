@@ -457,6 +457,16 @@ asteria_status asteria_profile_i8_flops(double *out3);
  * Waits for the device.                                                                           */
 asteria_status asteria_profile_root_work(double *out2);
 
+/* ---- for tests -------------------------------------------------------------------------------
+ * Where several workgroups share the lambda_max estimate of a factor they wait for each other's sums and, in every step, for
+ * each other's part of the product; the waits are bounded.  asteria_inverse_root with these bounds in looks at memory: 0 gives up
+ * at once.                                                                                          */
+asteria_status asteria_inverse_root_waits(const asteria_factor *f, int nfactors, int root,
+                                          asteria_eps_mode mode, const float *eps, int eps_count,
+                                          const asteria_root_opts *opts,
+                                          int32_t *info, int32_t *iters, float *resid, float *lambda_max,
+                                          void *ws, size_t ws_bytes, void *stream, uint32_t looks_sums, uint32_t looks_y);
+
 #ifdef __cplusplus
 }
 #endif

@@ -121,6 +121,8 @@ def lib():
         L.asteria_inverse_root.argtypes = [POINTER(_Factor), c_int, c_int, c_int, POINTER(c_float), c_int,
                                            POINTER(RootOpts), c_void_p, c_void_p, c_void_p, c_void_p,
                                            c_void_p, c_size_t, c_void_p]
+        L.asteria_inverse_root_waits.restype = c_int
+        L.asteria_inverse_root_waits.argtypes = L.asteria_inverse_root.argtypes + [ctypes.c_uint32, ctypes.c_uint32]
         L.asteria_static_scratch_bytes.restype = c_size_t
         L.asteria_static_scratch_bytes.argtypes = []
         L.asteria_inverse_root_static.restype = c_int

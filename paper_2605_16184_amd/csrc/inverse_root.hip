@@ -641,6 +641,7 @@ struct Plan {
     int i8_slices;     // 0, or the number of int8 slices the products of the fp64 iterations are computed with
     bool xt_lowp;      // fully automatic precision: X updates on the fp16 cores (split operands) from the
                        // first product on, and the look-ahead stop rule (accuracy class 1e-3)
+    LanczosWaits waits;
 };
 
 // Host mirror of the device-side schedule for a spectrum of M_0 in [lo0, 1]:
@@ -897,7 +898,8 @@ asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int 
     static bool cfg_f[MAX_DEVICES] = {}, cfg_s[MAX_DEVICES] = {};
     if (cluster_total > 0) {
         hipLaunchKernelGGL(lanczos_prepare_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, cluster_map, cluster_ticket);
-        hipLaunchKernelGGL(lanczos_cluster_kernel, dim3(cluster_total), dim3(LC_THREADS), 0, stream, d_fd, d_fs, cluster_map, cluster_ticket, tol2, steps);
+        hipLaunchKernelGGL(lanczos_cluster_kernel, dim3(cluster_total), dim3(LC_THREADS), 0, stream, d_fd, d_fs, cluster_map, cluster_ticket, tol2, steps,
+                           pl.waits);
         ASTERIA_HIP_TRY(hipGetLastError());
         return ASTERIA_OK;
     }
@@ -1420,11 +1422,10 @@ extern "C" size_t asteria_inverse_root_workspace_bytes(const asteria_factor *f, 
     return total;
 }
 
-extern "C" asteria_status asteria_inverse_root(const asteria_factor *f, int nfactors, int root,
-                                               asteria_eps_mode mode, const float *eps, int eps_count,
-                                               const asteria_root_opts *opts,
-                                               int32_t *info, int32_t *iters, float *resid, float *lambda_max,
-                                               void *ws, size_t ws_bytes, void *stream_)
+namespace {
+asteria_status inverse_root(const asteria_factor *f, int nfactors, int root, asteria_eps_mode mode, const float *eps, int eps_count,
+                            const asteria_root_opts *opts, int32_t *info, int32_t *iters, float *resid, float *lambda_max,
+                            void *ws, size_t ws_bytes, void *stream_, LanczosWaits waits)
 {
     asteria_status st = validate(f, nfactors, root, eps, eps_count);
     if (st != ASTERIA_OK) return st;
@@ -1432,6 +1433,7 @@ extern "C" asteria_status asteria_inverse_root(const asteria_factor *f, int nfac
     Plan pl;
     st = make_plan(opts, mode, eps, eps_count, root, pl);
     if (st != ASTERIA_OK) return st;
+    pl.waits = waits;
     if (!ws) return ASTERIA_WORKSPACE_TOO_SMALL;
     if (reinterpret_cast<uintptr_t>(ws) & 255u) return ASTERIA_INVALID_ARG;   // workspace must be 256-byte aligned
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_);
@@ -1457,6 +1459,26 @@ extern "C" asteria_status asteria_inverse_root(const asteria_factor *f, int nfac
         first += cnt;
     }
     return ASTERIA_OK;
+}
+}  // namespace
+
+extern "C" asteria_status asteria_inverse_root(const asteria_factor *f, int nfactors, int root,
+                                               asteria_eps_mode mode, const float *eps, int eps_count,
+                                               const asteria_root_opts *opts,
+                                               int32_t *info, int32_t *iters, float *resid, float *lambda_max,
+                                               void *ws, size_t ws_bytes, void *stream)
+{
+    return inverse_root(f, nfactors, root, mode, eps, eps_count, opts, info, iters, resid, lambda_max, ws, ws_bytes, stream, LanczosWaits{});
+}
+
+extern "C" asteria_status asteria_inverse_root_waits(const asteria_factor *f, int nfactors, int root,
+                                                     asteria_eps_mode mode, const float *eps, int eps_count,
+                                                     const asteria_root_opts *opts,
+                                                     int32_t *info, int32_t *iters, float *resid, float *lambda_max,
+                                                     void *ws, size_t ws_bytes, void *stream, uint32_t looks_sums, uint32_t looks_y)
+{
+    return inverse_root(f, nfactors, root, mode, eps, eps_count, opts, info, iters, resid, lambda_max, ws, ws_bytes, stream,
+                        LanczosWaits{looks_sums, looks_y});
 }
 
 // ---- the same call for callers that cannot allocate ---------------------------------------------

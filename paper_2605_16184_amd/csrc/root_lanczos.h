@@ -336,12 +336,14 @@ __global__ __launch_bounds__(THREADS) void lanczos_factor_kernel(const FactorDev
 //
 // Progress: a workgroup takes its (factor, member) by a ticket, so whoever waits waits for the holders of tickets next to its own;
 // unfinished factors below the last ticket taken have all their members on the chip, and the one at the frontier, with at most
-// lanczos_members(2048) = 43, finds room as soon as those below are done.  The wait is bounded all the same: a member that
-// gives up reports not a number, which the scaling refuses.
+// lanczos_members(2048) = 43, finds room as soon as those below are done.  Both waits, of the first member for the others' sums and of
+// every member for y, are bounded all the same: a member that gives up goes on with y not a number, and what the first member then
+// reports as the estimate is refused by the scaling.
 //
 // Bound by the first load (HBM) and by 6 - 8 us a step (exchange, two block sums, the product); figures beside lanczos_by_cluster.
 constexpr int LC_WAVES = 12, LC_THREADS = 64 * LC_WAVES, LC_MAX_N = 2048;
 constexpr uint32_t LC_POLLS = 1u << 21;
+struct LanczosWaits { uint32_t sums = LC_POLLS, y = LC_POLLS; };      // looks at what others have to write before a member gives up
 __host__ __device__ inline int lanczos_rows(int n) { return LC_WAVES * (n <= 512 ? 16 : (n <= 1024 ? 8 : 4)); }     // of a member
 __host__ __device__ inline int lanczos_members(int n) { return (n + lanczos_rows(n) - 1) / lanczos_rows(n); }
 // words of a factor's exchange: two buffers of n, and each member's partial sums of squares and of the diagonal as halves of doubles
@@ -368,7 +370,7 @@ __global__ __launch_bounds__(256) void lanczos_prepare_kernel(const FactorDev *f
 
 // NI: a lane holds columns 4 lane + 256 i .. + 3 for i < NI of RW consecutive rows (128 registers)
 template <int NI>
-__device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S, int member, float tol2, int steps)
+__device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S, int member, float tol2, int steps, LanczosWaits waits)
 {
     constexpr int RW = 32 / NI, RB = RW < 8 ? RW : 8, OWN = (256 * NI + LC_THREADS - 1) / LC_THREADS;
     __shared__ __align__(16) float v_lds[256 * NI];
@@ -468,6 +470,7 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
     if (tid == 0) done = 0;
     ss = block_sum(ss, redd[0]);
     const float inv0 = ss > 0.0 ? (float)(1.0 / sqrt(ss)) : 0.0f;
+    bool lost = false;                                       // this wavefront gave up a wait
 #pragma unroll
     for (int q = 0; q < OWN; ++q) {
         const int i = tid + LC_THREADS * q;
@@ -501,11 +504,12 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
             // (43 members at most: one lane each)
             double a = 0.0, t = 0.0;
             if (wave == 0) {
-                if (lane < members) {
+                bool all = lane >= members;
+                if (!all) {
                     const ASTERIA_GLOBAL uint64_t *d = sums + 4 * (size_t)lane;
                     uint64_t w[4] = {0, 0, 0, 0};
-                    for (uint32_t p = 0; p < LC_POLLS; ++p) {
-                        bool all = true;
+                    for (uint32_t p = 0; p < waits.sums; ++p) {
+                        all = true;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) { w[e] = word_get(d + e); all = all && (uint32_t)(w[e] >> 32) == 1u; }
                         if (all) break;
@@ -514,6 +518,7 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
                     a = __longlong_as_double((long long)((w[0] & 0xffffffffull) | (w[1] << 32)));
                     t = __longlong_as_double((long long)((w[2] & 0xffffffffull) | (w[3] << 32)));
                 }
+                lost = !__all(all);
                 a = wave_sum(a); t = wave_sum(t);
             }
             saa = a; str = t;
@@ -523,7 +528,7 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
     __syncthreads();
     float beta_p = 0.0f, rho = 0.0f;
     int small = 0;
-    bool stop = false, lost = false;
+    bool stop = false;
     for (int j = 0; j < steps; ++j) {
         // ---- this member's rows of y, RB at a time
 #pragma unroll
@@ -560,9 +565,9 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
         float y[OWN];
         double yv = 0.0;
         {
-            uint64_t w[OWN];
-            uint32_t polls = 0;
-            while (true) {
+            uint64_t w[OWN] = {};
+            for (uint32_t polls = 0; !lost; ++polls) {
+                if (polls == waits.y) { lost = true; break; }
                 bool all = true;
 #pragma unroll
                 for (int q = 0; q < OWN; ++q) {
@@ -571,7 +576,6 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
                     all = all && (uint32_t)(w[q] >> 32) == (uint32_t)j + 1u;
                 }
                 if (__all(all)) break;
-                if (++polls == LC_POLLS) { lost = true; break; }
             }
 #pragma unroll
             for (int q = 0; q < OWN; ++q) {
@@ -610,7 +614,8 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
     if (member == 0 && tid == 0) { S.rho = rho; S.pm_done = 1; }
 }
 
-__global__ __launch_bounds__(LC_THREADS, 3) void lanczos_cluster_kernel(const FactorDev *fd, FactorScal *fs, const uint2 *map, int *ticket, float tol2, int steps)
+__global__ __launch_bounds__(LC_THREADS, 3) void lanczos_cluster_kernel(const FactorDev *fd, FactorScal *fs, const uint2 *map, int *ticket, float tol2, int steps,
+                                                                        LanczosWaits waits)
 {
     __shared__ int mine;
     if (threadIdx.x == 0) mine = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -618,9 +623,9 @@ __global__ __launch_bounds__(LC_THREADS, 3) void lanczos_cluster_kernel(const Fa
     const uint2 m = map[__builtin_amdgcn_readfirstlane(mine)];
     const FactorDev &F = fd[m.x];
     FactorScal &S = fs[m.x];
-    if (F.n <= 512) lanczos_member<2>(F, S, (int)m.y, tol2, steps);
-    else if (F.n <= 1024) lanczos_member<4>(F, S, (int)m.y, tol2, steps);
-    else lanczos_member<8>(F, S, (int)m.y, tol2, steps);
+    if (F.n <= 512) lanczos_member<2>(F, S, (int)m.y, tol2, steps, waits);
+    else if (F.n <= 1024) lanczos_member<4>(F, S, (int)m.y, tol2, steps, waits);
+    else lanczos_member<8>(F, S, (int)m.y, tol2, steps, waits);
 }
 
 // ---- one launch per step -------------------------------------------------------------------------------

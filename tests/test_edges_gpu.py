@@ -1,9 +1,12 @@
 """Kernels at the sizes where their tiles, remainders and dispatch lines lie, against fp64 results."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2605_16184_amd as ast
+from paper_2605_16184_amd import binding as B
 from paper_2605_16184_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -97,6 +100,35 @@ def test_largest_eigenvalue_from_registers(sizes, packed):
     ast.inverse_root([(made[n], X)], 1e-6, info=info[:1])
     torch.cuda.synchronize()
     assert int(info[0]) == 2
+
+
+# Roots with bounds on the waits of the estimate that several workgroups share: how often a member looks for the others' sums and for y.
+def _roots_with_waits(items, eps, looks_sums, looks_y, info, lam):
+    f = ast.Factors(items)
+    ws = torch.empty(ast.inverse_root_workspace_bytes(f)[0], dtype=torch.uint8, device=DEV)
+    st = ast.lib().asteria_inverse_root_waits(f.array, f.count, 4, B.EPS_RELATIVE, (ctypes.c_float * 1)(eps), 1, None, info.data_ptr(), None, None,
+                                              lam.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream, looks_sums, looks_y)
+    assert st == B.OK
+    torch.cuda.synchronize()
+
+
+# Sums of squares that did not arrive must not pass for small ones: with a trace of half of n lambda_max (and the matrix itself far from a
+# multiple of the identity) they would make the iteration end after one update, with a root that is none.
+@pytest.mark.parametrize("n", [320, 1000])
+def test_sums_that_a_wait_gave_up_are_not_used(n):
+    trace = 0.5 * 1.01 * (n - 0.05)                             # n - 2 tr / (1.01 lambda_max) = 0.05, the squares left out
+    lam = torch.full((n,), 1e-5, device=DEV, dtype=torch.float64)
+    lam[:int(trace)] = 1.0
+    lam[int(trace)] = 0.0
+    lam[int(trace)] = trace - float(lam.sum())
+    A = _with_spectrum(n, lam, 7, n)
+    X, top = torch.full_like(A, float("nan")), torch.zeros(1, device=DEV)
+    info = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+    _roots_with_waits([(A, X)], 1e-6, 1 << 21, 1 << 21, info, top)
+    assert int(info[0]) == 0 and _root_error(A, X, 1e-6)[0] <= 2e-3
+    X.fill_(float("nan"))
+    _roots_with_waits([(A, X)], 1e-6, 0, 1 << 21, info, top)
+    assert int(info[0]) != 0 or _root_error(A, X, 1e-6)[0] <= 2e-3, (info, top)
 
 
 # Few digit tiles are computed in quarters, many in halves: the same integers.  (The sums of the residual have another order; it enters the
