@@ -31,7 +31,10 @@ struct FactorDev {
     float *T432;
     double *M64[2];
     double *T64;
-    double *T464;
+    union {
+        double *T464;
+        uint64_t *lz_words;   // plane path: exchange of lanczos_cluster_kernel
+    };
     // both
     const float *Aw;    // A in full storage as the lambda_max estimate reads it: A, or a copy of packed statistics
     int ldw;
@@ -41,14 +44,16 @@ struct FactorDev {
     double2 *pm_partial2; // per mat-vec workgroup, first step only: (sum a_ij^2, sum a_ii)
     float *partial;     // per lower-triangle tile: sum (M - I)^2 (2 ntri entries: a second one per tile for kernels that split tiles)
     int n, lda, ldx;
-    int ld32, ld64;
+    union {
+        int ld32;           // fp32 / fp64 path
+        int lz_start;       // plane path: first of this factor's workgroups in lanczos_cluster_kernel
+    };
+    int ld64;
     int ntri;           // lower-triangle tiles
     int tile_start;     // first tile of this factor in tile-indexed launches
     int pm_blocks;
     float eps_in;
     int a_packed;       // A lies in packed lower tiles (gemm.h, packed_off): lda unused
-    uint64_t *lz_words; // exchange of lanczos_cluster_kernel
-    int lz_start;       // first of this factor's workgroups there
     float *pm_tile;     // packed A: per lower tile 2 x 128 partial products of the mat-vec and the sum of a^2 as a double
 };
 

@@ -99,6 +99,19 @@ def test_inverse_root_rejects_bad_arguments_without_launching():
     assert f(*args(wb=64)) == B.WORKSPACE_TOO_SMALL
 
 
+# Callers keep workspaces and their sizes: what was enough for a batch stays enough.  (bytes for one pass, least bytes) by sizes of factors
+@pytest.mark.parametrize("sizes, full, least", [
+    ([1], 121200, 121200), ([64], 283248, 283248), ([300], 4914288, 4914288), ([128] * 5, 4164400, 841072), ([1024], 52781680, 52781680),
+    ([1100], 61777008, 61777008), ([2048, 7, 300], 215487568, 210471792), ([64] * 1000, 273018240, 283248), ([4096], 840624496, 840624496)])
+def test_roots_ask_for_no_larger_workspace_than_before(sizes, full, least):
+    f = (B._Factor * len(sizes))()
+    for a, n in zip(f, sizes):
+        a.A, a.X, a.n, a.lda, a.ldx = 0x1000, 0x2000, n, n, n
+    got = ctypes.c_size_t(0)
+    assert ast.lib().asteria_inverse_root_workspace_bytes(f, len(sizes), None, ctypes.byref(got)) <= full
+    assert got.value <= least
+
+
 def test_precondition_and_soap_reject_bad_arguments_without_launching():
     lib = ast.lib()
     ws = ctypes.c_void_p(0x10000)
