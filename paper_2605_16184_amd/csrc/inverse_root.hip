@@ -889,7 +889,7 @@ constexpr int LZ_LAUNCHES = 32, LZ_LAUNCH_N = 2048;
 
 asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int cnt, double elems, const Plan &pl, bool any_full, bool any_packed,
                                    int tri_max, int n_max, hipStream_t stream, int cluster_total = 0, uint2 *cluster_map = nullptr,
-                                   int *cluster_ticket = nullptr)      // workgroups of lanczos_cluster_kernel, 0: one of the other ways
+                                   int *cluster_ticket = nullptr)      // workgroups of lanczos_cluster_kernel (two words), 0: one of the other ways
 {
     const int steps = std::min(pl.power_iters, LZ_MAX);
     const float tol2 = pl.power_tol * pl.power_tol;
@@ -897,7 +897,7 @@ asteria_status lambda_max_launches(const FactorDev *d_fd, FactorScal *d_fs, int 
     const size_t lds = 3 * (size_t)ld * sizeof(float);
     static bool cfg_f[MAX_DEVICES] = {}, cfg_s[MAX_DEVICES] = {};
     if (cluster_total > 0) {
-        hipLaunchKernelGGL(lanczos_prepare_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, cluster_map, cluster_ticket);
+        hipLaunchKernelGGL(lanczos_prepare_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, cluster_map, cluster_ticket);
         hipLaunchKernelGGL(lanczos_cluster_kernel, dim3(cluster_total), dim3(LC_THREADS), 0, stream, d_fd, d_fs, cluster_map, cluster_ticket, tol2, steps,
                            pl.waits);
         ASTERIA_HIP_TRY(hipGetLastError());
@@ -1032,7 +1032,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     const int edge = pair_tile_edge(tri64_total, tri_total, tri256_total, tri_tiles(n_max), work128, work256, rows / cnt);
     int pair_total = 0;
     for (FactorDev &F : fd) { F.tile_start_p = pair_total; pair_total += tri_tiles_of(F.n, edge); }
-    // (until the tiles are written there d_map holds the members of lanczos_cluster_kernel, fewer than tiles, and d_state its ticket)
+    // (until the tiles are written there d_map holds the members of lanczos_cluster_kernel, fewer than tiles, and d_state, with room for 64, its two words)
     uint2 *d_map = cv.take<uint2>(tri_total), *d_map_p = edge == 128 ? d_map : cv.take<uint2>(pair_total);
     PlaneF64Tables ft = {};
     if (f64)
@@ -1076,8 +1076,9 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     ASTERIA_HIP_TRY(upload_async(d_fd, fd.data(), sizeof(FactorDev) * cnt, stream));
     if (f64)
         hipLaunchKernelGGL(plane_f64_tables_kernel, dim3((cnt + 127) / 128), dim3(128), 0, stream, d_fd, d_fs, cnt, linear0 ? 1 : 0, ft);
-    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, elems, pl, any_full, any_packed, tri_max, n_max, stream, lanczos_by_cluster(n_max) ? cluster_total : 0,
-                                    d_map, d_state));
+    const bool by_cluster = lanczos_by_cluster(n_max);
+    ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, elems, pl, any_full, any_packed, tri_max, n_max, stream, by_cluster ? cluster_total : 0, d_map,
+                                    d_state));
 
     // intervals and T of a factor that follows the schedule (the device works in fp32 for the scaling: 1e-5 of slack)
     std::vector<PlaneControl> ctl(K + 1);
@@ -1098,7 +1099,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
         return c;
     };
     hipLaunchKernelGGL(plane_setup_kernel, dim3(cnt), dim3(256), 0, stream, d_fd, d_fs, d_state, pl.margin, control(0), d_map,
-                       edge == 128 ? nullptr : d_map_p, edge);
+                       edge == 128 ? nullptr : d_map_p, edge, pl.power_tol * pl.power_tol, by_cluster ? std::min(pl.power_iters, LZ_MAX) : 0);
     hipLaunchKernelGGL(plane_init_kernel, dim3(tri_total, 4), dim3(256), 0, stream, d_fd, d_fs, d_state, d_map, linear0 ? 1 : 0);
     ASTERIA_HIP_TRY(hipGetLastError());
     for (int k = 0; k < K; ++k) {

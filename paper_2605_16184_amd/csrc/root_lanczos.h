@@ -336,9 +336,10 @@ __global__ __launch_bounds__(THREADS) void lanczos_factor_kernel(const FactorDev
 //
 // Progress: a workgroup takes its (factor, member) by a ticket, so whoever waits waits for the holders of tickets next to its own;
 // unfinished factors below the last ticket taken have all their members on the chip, and the one at the frontier, with at most
-// lanczos_members(2048) = 43, finds room as soon as those below are done.  Both waits, of the first member for the others' sums and of
-// every member for y, are bounded all the same: a member that gives up goes on with y not a number, and what the first member then
-// reports as the estimate is refused by the scaling.
+// lanczos_members(2048) = 43, finds room as soon as those below are done.  That room may be taken: by a mask of the stream's CUs, by kernels
+// of other processes that do not end.  So both waits, of the first member for the others' sums and of every member for y, are bounded, and a
+// member that gives up sets a word for the launch that ends all waits in it.  A factor whose first member has not settled is left to
+// lanczos_alone, one workgroup that waits for nobody.
 //
 // Bound by the first load (HBM) and by 6 - 8 us a step (exchange, two block sums, the product); figures beside lanczos_by_cluster.
 constexpr int LC_WAVES = 12, LC_THREADS = 64 * LC_WAVES, LC_MAX_N = 2048;
@@ -358,25 +359,26 @@ __device__ __forceinline__ uint64_t word_get(const ASTERIA_GLOBAL uint64_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Exchange words of every factor to zero (no step's number), its members into the map, the ticket to zero.
-__global__ __launch_bounds__(256) void lanczos_prepare_kernel(const FactorDev *fd, uint2 *map, int *ticket)
+// Exchange words of every factor to zero (no step's number), its members into the map, the ticket and the word of a wait given up to zero.
+__global__ __launch_bounds__(256) void lanczos_prepare_kernel(const FactorDev *fd, FactorScal *fs, uint2 *map, int *ticket)
 {
     const FactorDev &F = fd[blockIdx.x];
     const int words = (int)lanczos_words(F.n), members = lanczos_members(F.n);
     for (int i = threadIdx.x; i < words; i += 256) F.lz_words[i] = 0;
     for (int m = threadIdx.x; m < members; m += 256) map[F.lz_start + m] = make_uint2(blockIdx.x, (unsigned)m);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
+    if (threadIdx.x == 0) fs[blockIdx.x].pm_done = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 2) ticket[threadIdx.x] = 0;
 }
 
 // NI: a lane holds columns 4 lane + 256 i .. + 3 for i < NI of RW consecutive rows (128 registers)
 template <int NI>
-__device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S, int member, float tol2, int steps, LanczosWaits waits)
+__device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S, int member, float tol2, int steps, LanczosWaits waits, int *given_up)
 {
     constexpr int RW = 32 / NI, RB = RW < 8 ? RW : 8, OWN = (256 * NI + LC_THREADS - 1) / LC_THREADS;
     __shared__ __align__(16) float v_lds[256 * NI];
     __shared__ double redd[2][LC_WAVES];
     __shared__ __align__(16) float la[LZ_MAX], lb[LZ_MAX];
-    __shared__ int done;
+    __shared__ int done, gave_up;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = F.n, members = lanczos_members(n), row0 = member * LC_WAVES * RW + wave * RW;
     ASTERIA_GLOBAL uint64_t *words = (ASTERIA_GLOBAL uint64_t *)F.lz_words, *sums = words + 2 * (size_t)n;
@@ -467,10 +469,14 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
         vp[q] = 0.0f;
         ss += (double)v[q] * (double)v[q];
     }
-    if (tid == 0) done = 0;
+    if (tid == 0) done = gave_up = 0;
     ss = block_sum(ss, redd[0]);
     const float inv0 = ss > 0.0 ? (float)(1.0 / sqrt(ss)) : 0.0f;
     bool lost = false;                                       // this wavefront gave up a wait
+    // every 64th look: somebody gave up
+    auto hopeless = [&](uint32_t looks) __attribute__((always_inline)) {
+        return (looks & 63u) == 63u && __hip_atomic_load(given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    };
 #pragma unroll
     for (int q = 0; q < OWN; ++q) {
         const int i = tid + LC_THREADS * q;
@@ -512,7 +518,7 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
                         all = true;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) { w[e] = word_get(d + e); all = all && (uint32_t)(w[e] >> 32) == 1u; }
-                        if (all) break;
+                        if (all || hopeless(p)) break;
                         __builtin_amdgcn_s_sleep(1);
                     }
                     a = __longlong_as_double((long long)((w[0] & 0xffffffffull) | (w[1] << 32)));
@@ -528,7 +534,7 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
     __syncthreads();
     float beta_p = 0.0f, rho = 0.0f;
     int small = 0;
-    bool stop = false;
+    bool stop = false, settled = true;
     for (int j = 0; j < steps; ++j) {
         // ---- this member's rows of y, RB at a time
 #pragma unroll
@@ -567,7 +573,7 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
         {
             uint64_t w[OWN] = {};
             for (uint32_t polls = 0; !lost; ++polls) {
-                if (polls == waits.y) { lost = true; break; }
+                if (polls == waits.y || __any(hopeless(polls))) { lost = true; break; }
                 bool all = true;
 #pragma unroll
                 for (int q = 0; q < OWN; ++q) {
@@ -583,6 +589,10 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
                 yv += (double)(y[q] * v[q]);
             }
         }
+        if (lost && lane == 0) {
+            gave_up = 1;
+            __hip_atomic_store(given_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         const float alpha = (float)block_sum(yv, redd[0]);
         if (done) break;
         double ww = 0.0;
@@ -593,6 +603,7 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
         }
         const float beta = (float)sqrt(block_sum(ww, redd[1]));
         if (!(beta < 3.0e38f) || !(fabsf(alpha) < 3.0e38f)) {         // non-finite input, or a wait that was given up (uniform)
+            settled = gave_up == 0;
             rho = NAN;
             break;
         }
@@ -611,21 +622,96 @@ __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S
         // than they could
         if (wave == 0) stop = lanczos_advance(rho, small, la, lb, j, beta, tol2);
     }
-    if (member == 0 && tid == 0) { S.rho = rho; S.pm_done = 1; }
+    if (member == 0 && tid == 0) { S.rho = rho; S.pm_done = settled ? 1 : 0; }
 }
 
 __global__ __launch_bounds__(LC_THREADS, 3) void lanczos_cluster_kernel(const FactorDev *fd, FactorScal *fs, const uint2 *map, int *ticket, float tol2, int steps,
                                                                         LanczosWaits waits)
 {
     __shared__ int mine;
-    if (threadIdx.x == 0) mine = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) {
+        const int t = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mine = __hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : t;
+    }
     __syncthreads();
+    if (mine < 0) return;
     const uint2 m = map[__builtin_amdgcn_readfirstlane(mine)];
     const FactorDev &F = fd[m.x];
     FactorScal &S = fs[m.x];
-    if (F.n <= 512) lanczos_member<2>(F, S, (int)m.y, tol2, steps, waits);
-    else if (F.n <= 1024) lanczos_member<4>(F, S, (int)m.y, tol2, steps, waits);
-    else lanczos_member<8>(F, S, (int)m.y, tol2, steps, waits);
+    if (F.n <= 512) lanczos_member<2>(F, S, (int)m.y, tol2, steps, waits, ticket + 1);
+    else if (F.n <= 1024) lanczos_member<4>(F, S, (int)m.y, tol2, steps, waits, ticket + 1);
+    else lanczos_member<8>(F, S, (int)m.y, tol2, steps, waits, ticket + 1);
+}
+
+// All steps of a factor of at most LC_MAX_N rows by one workgroup of 256 threads, dense or packed, from memory: for what
+// lanczos_cluster_kernel left.  Rare, so short rather than fast; the vectors lie where the exchange did.
+__device__ inline void lanczos_alone(const FactorDev &F, FactorScal &S, float tol2, int steps)
+{
+    __shared__ double red[4];
+    __shared__ __align__(16) float la[LZ_MAX], lb[LZ_MAX];
+    __shared__ int done;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = F.n;
+    float *v = reinterpret_cast<float *>(F.lz_words), *vp = v + n, *y = vp + n;
+    auto block_sum = [&](double x) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        __syncthreads();
+        if (lane == 0) red[wave] = x;
+        __syncthreads();
+        return red[0] + red[1] + red[2] + red[3];
+    };
+    double s = 0.0;
+    for (int i = tid; i < n; i += 256) {
+        v[i] = hash_unit(0u, (uint32_t)i); vp[i] = 0.0f;
+        s += (double)v[i] * (double)v[i];
+    }
+    s = block_sum(s);
+    const float inv0 = s > 0.0 ? (float)(1.0 / sqrt(s)) : 0.0f;
+    for (int i = tid; i < n; i += 256) v[i] *= inv0;
+    if (tid == 0) { done = 0; S.rho = 0.0f; S.lz_small = 0; }
+    __syncthreads();
+    float beta_p = 0.0f;
+    for (int j = 0; j < steps; ++j) {
+        double saa = 0.0, str = 0.0;
+        for (int r = wave; r < n; r += 4) {
+            float t = 0.0f;
+            for (int c = lane; c < n; c += 64) {
+                const float a = F.A[F.a_packed ? (c / PACK_T <= r / PACK_T ? packed_off(r, c) : packed_off(c, r)) : (size_t)r * F.lda + c];
+                t += a * v[c];
+                saa += (double)a * (double)a;
+                if (c == r) str += (double)a;
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+            if (lane == 0) y[r] = t;
+        }
+        if (j == 0) {
+            saa = block_sum(saa);
+            str = block_sum(str);
+            if (tid == 0) { S.fro2 = saa; S.trace = str; }
+        }
+        __syncthreads();
+        double yv = 0.0, ww = 0.0;
+        for (int i = tid; i < n; i += 256) yv += (double)(y[i] * v[i]);
+        const float alpha = (float)block_sum(yv);
+        for (int i = tid; i < n; i += 256) {
+            y[i] = y[i] - alpha * v[i] - beta_p * vp[i];
+            ww += (double)y[i] * (double)y[i];
+        }
+        const float beta = (float)sqrt(block_sum(ww));
+        if (!(beta < 3.0e38f) || !(fabsf(alpha) < 3.0e38f)) {         // non-finite input (uniform)
+            if (tid == 0) S.rho = NAN;
+            break;
+        }
+        const float inv = beta > 0.0f ? 1.0f / beta : 0.0f;
+        for (int i = tid; i < n; i += 256) { vp[i] = v[i]; v[i] = y[i] * inv; }
+        beta_p = beta;
+        if (tid == 0) { la[j] = alpha; lb[j] = beta; }
+        __syncthreads();
+        if (wave == 0 && lanczos_advance(S, la, lb, j, beta, tol2) && lane == 0) done = 1;
+        __syncthreads();
+        if (done) break;
+    }
 }
 
 // ---- one launch per step -------------------------------------------------------------------------------

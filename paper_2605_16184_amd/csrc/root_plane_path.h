@@ -203,13 +203,15 @@ __device__ __forceinline__ void strip_decode(int t, int tiles, int &ti, int &tj)
     }
 }
 
-// One workgroup per factor: scaling, start of the interval, and the decision about iteration 0.
+// One workgroup per factor: scaling, start of the interval, and the decision about iteration 0.  lz_steps > 0: lambda_max comes from
+// lanczos_cluster_kernel, whose workgroups may have given up.
 __global__ __launch_bounds__(256) void plane_setup_kernel(const FactorDev *fd, FactorScal *fs, int *state, float margin, PlaneControl c,
-                                                          uint2 *map128, uint2 *map_p, int pair_tile)
+                                                          uint2 *map128, uint2 *map_p, int pair_tile, float lz_tol2, int lz_steps)
 {
     const int f = blockIdx.x;
     const FactorDev &F = fd[f];
     FactorScal &S = fs[f];
+    if (lz_steps > 0 && S.pm_done == 0) lanczos_alone(F, S, lz_tol2, lz_steps);
     const int tid = threadIdx.x, n = F.n;
     __shared__ double red[3][4];
     // factor and tile of every workgroup of the tile-indexed launches

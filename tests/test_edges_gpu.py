@@ -27,6 +27,18 @@ def _spectrum(kind, n):
     return 0.05 * W.logspaced_sigma(n, 8.0, DEV).double() ** 2
 
 
+# packed tiles whose padding, the rows and columns beyond n, is not data
+def _packed_with_nan_padding(A):
+    n, T = A.shape[0], 128
+    P = torch.empty(ast.packed_elems(n), device=DEV)
+    ast.sym_pack([(A, P)])
+    if n % T:
+        last = P.view(-1, T, T)[-((n + T - 1) // T):]           # the tiles of the last block row
+        last[:, n % T:] = float("nan")
+        last[-1, :, n % T:] = float("nan")
+    return P
+
+
 def _root_error(A, X, eps):
     w, V = torch.linalg.eigh(A.double())
     e = eps * float(w[-1])
@@ -129,6 +141,28 @@ def test_sums_that_a_wait_gave_up_are_not_used(n):
     X.fill_(float("nan"))
     _roots_with_waits([(A, X)], 1e-6, 0, 1 << 21, info, top)
     assert int(info[0]) != 0 or _root_error(A, X, 1e-6)[0] <= 2e-3, (info, top)
+
+
+# Workgroups that give up a wait leave their factor to one that waits for nobody: the same outcome.  At once, after a few looks (some give
+# up, some do not), by the first one alone; every width of a row's share, one member and 43, packed, a factor that is not finite.
+@pytest.mark.parametrize("looks", [(0, 1 << 21), (1 << 21, 0), (1 << 21, 1), (1 << 21, 4), (2, 2)])
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("sizes", [[257, 1, 2, 3, 129], [513, 100, 641], [333] * 300, [2048, 2047, 1025]])
+def test_roots_where_workgroups_give_up_waiting(sizes, packed, looks):
+    made = {n: _with_spectrum(n, _spectrum("power", n), 7, n) for n in set(sizes)}
+    items = [(_packed_with_nan_padding(made[n]) if packed else made[n], torch.full((n, n), float("nan"), device=DEV), int(packed)) for n in sizes]
+    info = torch.full((len(sizes),), -1, dtype=torch.int32, device=DEV)
+    lam = torch.zeros(len(sizes), device=DEV)
+    _roots_with_waits(items, 1e-6, *looks, info, lam)
+    assert bool((info == 0).all())
+    for n in made:
+        i = max(k for k, m in enumerate(sizes) if m == n)
+        err, top = _root_error(made[n], items[i][1], 1e-6)
+        assert err <= 2e-3, (n, err)
+        assert abs(float(lam[i]) - top) <= 1e-5 * top, (n, float(lam[i]), top)
+    items[0][0].view(-1)[0] = float("inf")
+    _roots_with_waits(items[:1], 1e-6, *looks, info[:1], lam)
+    assert int(info[0]) == 2
 
 
 # Few digit tiles are computed in quarters, many in halves: the same integers.  (The sums of the residual have another order; it enters the
