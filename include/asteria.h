@@ -264,6 +264,11 @@ asteria_status asteria_sym_unpack(const asteria_sympair *items, int nitems, void
  * root where A + eps I is positive definite and to ASTERIA_INFO_NOT_PD where it is not.  X of a factor that
  * ends so is not defined (it holds an intermediate result).
  *
+ * Compute units.  Where every factor of a pass has at most 2048 rows (and one more than 256), the automatic rules let up to 43
+ * workgroups share the lambda_max estimate of a factor and wait for each other.  They do so only on a stream whose compute units
+ * have room for four such groups (all of an MI355X; a stream with a CU mask or a partition may have fewer), and a wait is bounded: what
+ * workgroups gave up - units held for seconds by kernels of other processes - is computed by one, more slowly, to the same accuracy.
+ *
  *   eps        host array, eps_count entries (1 = shared by all factors, else nfactors).
  *   info       device int32[nfactors] or NULL   (ASTERIA_INFO_*)
  *   iters      device int32[nfactors] or NULL   (number of X <- X T updates performed)

@@ -865,13 +865,26 @@ __global__ void root_tables_kernel(const FactorDev *__restrict__ fd, FactorScal 
     }
 }
 
-// Whether the lambda_max estimate of a pass keeps its matrices in registers of several workgroups: wherever they fit, except for
-// factors that one workgroup holds by itself.  The whole refresh in us, before (the ways below) / so: 3 blocks of 777 x 1000 in blocks of 512,
+// Compute units that work on a stream can use, 0 where that cannot be found out.
+int stream_cus(hipStream_t stream)
+{
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(stream, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    int cus = 0;
+    for (uint32_t w : mask) cus += __builtin_popcount(w);
+    return cus;
+}
+
+// Whether the lambda_max estimate of a pass keeps its matrices in registers of several workgroups: wherever they fit and find room side by
+// side, except for factors that one workgroup holds by itself.  The whole refresh in us, before (the ways below) / so: 3 blocks of 777 x 1000 in blocks of 512,
 // evenly dense spectra 1650 / 1345; 6 of 1000 x 333 1197 / 1140; 1 of 512 x 400 579 / 479; 1 of 1024 x 1024 779 / 727; 100 of 512 x 300 3940 / 3920;
 // 64 of 1024 x 1024 17265 / 15980; 3 of 2000 x 1500 4095 / 3976; the 1.1B model 255.4 / 246.1 ms, packed 255.6 / 244.5.
-bool lanczos_by_cluster(int n_max) { return n_max > 256 && n_max <= LC_MAX_N; }
+bool lanczos_by_cluster(int n_max, hipStream_t stream) { return n_max > 256 && n_max <= LC_MAX_N && lanczos_cluster_room(n_max, stream_cus(stream)); }
 
-// The others (larger factors, the general path).  Small factors, and batches that keep every CU busy until the
+// The others (larger factors, little room, the general path).  Small factors, and batches that keep every CU busy until the
 // largest factor is done: one workgroup per factor, one launch.  Otherwise one launch per step - 32 of them, then one
 // workgroup per factor takes what has not settled; from n = 2048 on launches throughout.
 // Refresh in us at eps = 1e-6, a launch per step / a workgroup per factor, power-law spectrum (8 steps):
@@ -1076,7 +1089,7 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
     ASTERIA_HIP_TRY(upload_async(d_fd, fd.data(), sizeof(FactorDev) * cnt, stream));
     if (f64)
         hipLaunchKernelGGL(plane_f64_tables_kernel, dim3((cnt + 127) / 128), dim3(128), 0, stream, d_fd, d_fs, cnt, linear0 ? 1 : 0, ft);
-    const bool by_cluster = lanczos_by_cluster(n_max);
+    const bool by_cluster = lanczos_by_cluster(n_max, stream);
     ASTERIA_TRY(lambda_max_launches(d_fd, d_fs, cnt, elems, pl, any_full, any_packed, tri_max, n_max, stream, by_cluster ? cluster_total : 0, d_map,
                                     d_state));
 

@@ -11,6 +11,17 @@ enum : int { ST_RUN = 0, ST_LAST = 1, ST_DONE = 2, ST_FAIL = 3 };
 // what the chain products of a factor run on in the current iteration
 enum : int { TIER_F64 = 0, TIER_DIGIT = 1, TIER_PAIR = 2 };
 
+// Workgroups of lanczos_cluster_kernel ("members") that share a factor.
+constexpr int LC_WAVES = 12, LC_THREADS = 64 * LC_WAVES, LC_MAX_N = 2048;
+__host__ __device__ inline int lanczos_rows(int n) { return LC_WAVES * (n <= 512 ? 16 : (n <= 1024 ? 8 : 4)); }     // of a member
+__host__ __device__ inline int lanczos_members(int n) { return (n + lanczos_rows(n) - 1) / lanczos_rows(n); }
+// Whether the largest factor's members find room on `cus` compute units (a member fills one) beside those of three other calls, on other
+// streams or of other processes: only what waits at the frontier of each call counts.  A whole MI355X has room for 43; 32 CUs
+// of it for the 8 of n = 768.
+__host__ __device__ inline bool lanczos_cluster_room(int n_max, int cus) { return n_max <= LC_MAX_N && 4 * lanczos_members(n_max) <= cus; }
+// words of a factor's exchange: two buffers of n, and each member's partial sums of squares and of the diagonal as halves of doubles
+__host__ __device__ inline size_t lanczos_words(int n) { return 2 * (size_t)n + 4 * (size_t)lanczos_members(n); }
+
 struct FactorDev {
     const float *A;
     float *Xout;

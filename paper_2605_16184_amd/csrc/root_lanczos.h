@@ -342,13 +342,8 @@ __global__ __launch_bounds__(THREADS) void lanczos_factor_kernel(const FactorDev
 // lanczos_alone, one workgroup that waits for nobody.
 //
 // Bound by the first load (HBM) and by 6 - 8 us a step (exchange, two block sums, the product); figures beside lanczos_by_cluster.
-constexpr int LC_WAVES = 12, LC_THREADS = 64 * LC_WAVES, LC_MAX_N = 2048;
 constexpr uint32_t LC_POLLS = 1u << 21;
 struct LanczosWaits { uint32_t sums = LC_POLLS, y = LC_POLLS; };      // looks at what others have to write before a member gives up
-__host__ __device__ inline int lanczos_rows(int n) { return LC_WAVES * (n <= 512 ? 16 : (n <= 1024 ? 8 : 4)); }     // of a member
-__host__ __device__ inline int lanczos_members(int n) { return (n + lanczos_rows(n) - 1) / lanczos_rows(n); }
-// words of a factor's exchange: two buffers of n, and each member's partial sums of squares and of the diagonal as halves of doubles
-__host__ __device__ inline size_t lanczos_words(int n) { return 2 * (size_t)n + 4 * (size_t)lanczos_members(n); }
 
 __device__ __forceinline__ void word_put(ASTERIA_GLOBAL uint64_t *p, uint32_t value, uint32_t tag)
 {

@@ -84,7 +84,8 @@ def test_roots_at_the_edges(kind, eps, sizes):
 # chunk, one member and 43, rows of every alignment, packed tiles whose padding is not a number.  The estimate is fp32 arithmetic on a
 # spectrum whose top is a factor of 4 apart: a few units of 2^-24 of a sum of n products, far below the 1e-5 asked here.
 @pytest.mark.parametrize("packed", [False, True])
-@pytest.mark.parametrize("sizes", [[257, 1, 2, 3, 4, 5], [512, 192, 193, 191], [513, 608, 577], [1024, 300], [1025, 97], [2048, 2047], [333] * 300])
+@pytest.mark.parametrize("sizes", [[257, 1, 2, 3, 4, 5], [512, 192, 193, 191], [513, 608, 577], [1024, 300], [1025, 97], [2048, 2047], [333] * 300,
+                                   [2049, 1500, 700, 300, 100]])      # beside a factor that does not fit: all by the other ways
 def test_largest_eigenvalue_from_registers(sizes, packed):
     made = {n: _with_spectrum(n, _spectrum("power", n), 7, n) for n in set(sizes)}
     top = {n: float(torch.linalg.eigvalsh(A.double())[-1]) for n, A in made.items()}
@@ -163,6 +164,71 @@ def test_roots_where_workgroups_give_up_waiting(sizes, packed, looks):
     items[0][0].view(-1)[0] = float("inf")
     _roots_with_waits(items[:1], 1e-6, *looks, info[:1], lam)
     assert int(info[0]) == 2
+
+
+# Refreshes on several streams at once, each with factors whose workgroups wait for each other, beside other work: as one after the other
+def test_roots_on_several_streams_at_once():
+    batches = [[2048, 1100, 700, 300] * 4, [1500, 2047] * 6, [600, 1024] * 20]
+    made = {n: _with_spectrum(n, _spectrum("power", n), 7, n) for n in {n for b in batches for n in b}}
+    streams = [torch.cuda.Stream() for _ in batches]
+    busy = torch.randn(4096, 4096, device=DEV)
+    want, got, infos, ws = [], [], [], []
+    for b in batches:
+        want.append([torch.full_like(made[n], float("nan")) for n in b])
+        got.append([torch.full_like(made[n], float("nan")) for n in b])
+        infos.append(torch.full((len(b),), -1, dtype=torch.int32, device=DEV))
+        f = ast.Factors([(made[n], X) for n, X in zip(b, want[-1])])
+        ws.append(torch.empty(ast.inverse_root_workspace_bytes(f)[0], dtype=torch.uint8, device=DEV))
+        ast.inverse_root(f, 1e-6, info=infos[-1], ws=ws[-1])
+    torch.cuda.synchronize()
+    assert all(bool((i == 0).all()) for i in infos)
+    for _ in range(4):
+        for s, b, X, i, w in zip(streams, batches, got, infos, ws):
+            i.fill_(-1)
+            s.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(s):
+                ast.inverse_root([(made[n], x) for n, x in zip(b, X)], 1e-6, info=i, ws=w)
+        for _ in range(4):
+            busy = busy @ busy * 1e-3
+        torch.cuda.synchronize()
+        assert all(bool((i == 0).all()) for i in infos)
+        for X, Y in zip(want, got):
+            assert all(torch.equal(x, y) for x, y in zip(X, Y))
+            for y in Y:
+                y.fill_(float("nan"))
+
+
+# Captured into a graph, the stream asked for its compute units while it captures: every replay on new statistics as the eager call
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("sizes", [[300, 700], [64, 100]])
+def test_roots_in_a_captured_graph(sizes, static):
+    made = [[_with_spectrum(n, _spectrum("power", n), seed, n) for n in sizes] for seed in (7, 8, 9)]
+    As = [A.clone() for A in made[0]]
+    Xs, eager = ([torch.full_like(A, float("nan")) for A in As] for _ in range(2))
+    info = torch.full((len(sizes),), -1, dtype=torch.int32, device=DEV)
+    f = ast.Factors(list(zip(As, Xs)))
+    ws = torch.empty(ast.inverse_root_workspace_bytes(f)[0], dtype=torch.uint8, device=DEV)
+
+    def call(factors):
+        if static:
+            ast.inverse_root_static(factors, 1e-6, info=info)
+        else:
+            ast.inverse_root(factors, 1e-6, info=info, ws=ws)
+    call(f)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(f)
+    for statistics in made + made[:1]:
+        for A, new, X in zip(As, statistics, Xs):
+            A.copy_(new)
+            X.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert bool((info == 0).all())
+        call(ast.Factors(list(zip(As, eager))))
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(Xs, eager))
 
 
 # Few digit tiles are computed in quarters, many in halves: the same integers.  (The sums of the residual have another order; it enters the
