@@ -869,19 +869,21 @@ constexpr size_t gemm_lds_bytes()
 }
 
 // Enqueue one grouped launch.  probs / state are device pointers (state may be null when no
-// problem refers to it).  quarters: few tiles may be computed in quarters.
-template <typename TC, typename TA, typename TB, bool AKM, bool BKM>
+// problem refers to it).  QUARTERS: few tiles are computed in quarters (no problem has a partial sum per tile).
+template <typename TC, typename TA, typename TB, bool AKM, bool BKM, bool QUARTERS = false>
 inline hipError_t launch_gemm_grouped(const GemmProblem *probs, int nprobs, int total_tiles,
-                                      const int *state, hipStream_t stream, bool quarters = false)
+                                      const int *state, hipStream_t stream)
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
     auto kern = gemm_grouped_kernel<TC, TA, TB, AKM, BKM>;
     size_t lds = gemm_lds_bytes<TC, TA, TB, AKM, BKM>();
     int threads = Mma<TC>::NTHR, parts = 1;
-    if (quarters && total_tiles <= QUARTER_TILES) {
-        kern = gemm_quarter_kernel<TC, TA, TB, AKM, BKM>;
-        lds = gemm_lds_bytes<TC, TA, TB, AKM, BKM, MmaQuarter<TC>>();
-        threads = MmaQuarter<TC>::NTHR; parts = 4;
+    if constexpr (QUARTERS) {
+        if (total_tiles <= QUARTER_TILES) {
+            kern = gemm_quarter_kernel<TC, TA, TB, AKM, BKM>;
+            lds = gemm_lds_bytes<TC, TA, TB, AKM, BKM, MmaQuarter<TC>>();
+            threads = MmaQuarter<TC>::NTHR; parts = 4;
+        }
     }
     static bool configured[2][MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured[parts == 4]); e != hipSuccess) return e;

@@ -374,14 +374,15 @@ __global__ __launch_bounds__(256, 4) void gemm_bf16_quarter_kernel(const GemmPro
 
 constexpr int BF16_QUARTER_TILES = 256;
 
-// whole: never in quarters
-template <typename TA, typename TB, int NTA, int NTB, bool F16 = false>
+// QUARTERS: few tiles are computed in quarters (no problem has a partial sum per tile)
+template <typename TA, typename TB, int NTA, int NTB, bool F16 = false, bool QUARTERS = true>
 inline hipError_t launch_gemm_bf16_grouped(const GemmProblem *probs, int nprobs, int total_tiles,
-                                           const int *state, hipStream_t stream, bool whole = false)
+                                           const int *state, hipStream_t stream)
 {
     if (total_tiles <= 0 || nprobs <= 0) return hipSuccess;
-    const bool quarters = !whole && total_tiles <= BF16_QUARTER_TILES;
-    auto kern = quarters ? gemm_bf16_quarter_kernel<TA, TB, NTA, NTB, F16> : gemm_bf16_grouped_kernel<TA, TB, NTA, NTB, F16>;
+    const bool quarters = QUARTERS && total_tiles <= BF16_QUARTER_TILES;
+    auto kern = gemm_bf16_grouped_kernel<TA, TB, NTA, NTB, F16>;
+    if constexpr (QUARTERS) if (quarters) kern = gemm_bf16_quarter_kernel<TA, TB, NTA, NTB, F16>;
     const size_t lds = quarters ? gemm_bf16_lds<TA, TB, NTA, NTB, 64>() : gemm_bf16_lds<TA, TB, NTA, NTB>();
     static bool configured[2][MAX_DEVICES] = {};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured[quarters]); e != hipSuccess) return e;

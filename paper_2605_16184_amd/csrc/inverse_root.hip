@@ -1314,15 +1314,15 @@ asteria_status run_pass(const asteria_factor *f, int first, int cnt, int root, a
         // tier is chosen automatically, from the first product on; otherwise with the tier of M.
         if (k > 0) {
             if (pl.xt_lowp || lowp)
-                ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(d_xt[pa], cnt, tri_total, d_state, stream, true)));
+                ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true, false>(d_xt[pa], cnt, tri_total, d_state, stream)));
             else
                 ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(d_xt[pa], cnt, tri_total, d_state, stream)));
         }
         if (lowp) {
-            ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(d_tab[0][pa][0], cnt, tri_total, d_state, stream, true)));
+            ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true, false>(d_tab[0][pa][0], cnt, tri_total, d_state, stream)));
             if (root == 4)
-                ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(d_tab[0][pa][1], cnt, tri_total, d_state, stream, true)));
-            ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true>(d_tab[0][pa][2], cnt, tri_total, d_state, stream, true)));
+                ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true, false>(d_tab[0][pa][1], cnt, tri_total, d_state, stream)));
+            ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2, true, false>(d_tab[0][pa][2], cnt, tri_total, d_state, stream)));
         } else if (p32) {
             ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(d_tab[0][pa][0], cnt, tri_total, d_state, stream)));
             if (root == 4)

@@ -158,8 +158,8 @@ extern "C" asteria_status asteria_precondition(const asteria_pblock *blocks, int
     ASTERIA_HIP_TRY(up.add(d2f, p2f.data(), p2f.size() * sizeof(PlaneProblem)));
     ASTERIA_HIP_TRY(up.flush());
     if (!p1[0].empty()) {
-        ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(d1, (int)p1[0].size(), tiles1[0], nullptr, stream, true)));
-        ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true>(d2, (int)p2[0].size(), tiles2[0], nullptr, stream, true)));
+        ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false, true>(d1, (int)p1[0].size(), tiles1[0], nullptr, stream)));
+        ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true, true>(d2, (int)p2[0].size(), tiles2[0], nullptr, stream)));
     }
     ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, bf16_t, 2, 1>(d1b, (int)p1[1].size(), tiles1[1], nullptr, stream)));
     ASTERIA_HIP_TRY((launch_pgemm<1>(d1f, (int)p1f.size(), tiles1f, stream, 514)));

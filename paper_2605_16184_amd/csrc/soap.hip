@@ -675,10 +675,10 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
         ASTERIA_HIP_TRY(hipGetLastError());
     }
     // one-sided rotations into the eigenbasis
-    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, true, true>(d_oL1[0], (int)oL1[0].size(), tL1[0], nullptr, stream, true)));
-    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, bf16_t, true, true>(d_oL1[1], (int)oL1[1].size(), tL1[1], nullptr, stream, true)));
-    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true>(d_oR1[0], (int)oR1[0].size(), tR1[0], nullptr, stream, true)));
-    ASTERIA_HIP_TRY((launch_gemm_grouped<float, bf16_t, float, false, true>(d_oR1[1], (int)oR1[1].size(), tR1[1], nullptr, stream, true)));
+    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, true, true, true>(d_oL1[0], (int)oL1[0].size(), tL1[0], nullptr, stream)));
+    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, bf16_t, true, true, true>(d_oL1[1], (int)oL1[1].size(), tL1[1], nullptr, stream)));
+    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true, true>(d_oR1[0], (int)oR1[0].size(), tR1[0], nullptr, stream)));
+    ASTERIA_HIP_TRY((launch_gemm_grouped<float, bf16_t, float, false, true, true>(d_oR1[1], (int)oR1[1].size(), tR1[1], nullptr, stream)));
     if (!g1[0].empty())
         ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[0], (int)g1[0].size(), tiles1[0], nullptr, stream)));
     if (!g1[1].empty())
@@ -695,8 +695,8 @@ extern "C" asteria_status asteria_soap_step(const asteria_sblock *blocks, int nb
     if (!g2.empty()) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<float, float, 2, 2>(d_g[3], (int)g4.size(), tiles, nullptr, stream)));
     if (!f2.empty()) ASTERIA_HIP_TRY((launch_pgemm<2>(d_f[2], (int)f4.size(), tilesf, stream, 513)));
     // one-sided rotations back
-    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true>(d_oL2, (int)oL2.size(), tL2, nullptr, stream, true)));
-    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(d_oR2, (int)oR2.size(), tR2, nullptr, stream, true)));
+    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, true, true>(d_oL2, (int)oL2.size(), tL2, nullptr, stream)));
+    ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false, true>(d_oR2, (int)oR2.size(), tR2, nullptr, stream)));
     return ASTERIA_OK;
 }
 

@@ -242,8 +242,8 @@ extern "C" asteria_status asteria_stats_update(const asteria_block *blocks, int 
         }
         ASTERIA_HIP_TRY(up.flush());
         if (d == ASTERIA_F32) {
-            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false>(dL, (int)t.L[d].size(), t.tilesL[d], nullptr, stream, true)));
-            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, true, true>(dR, (int)t.R[d].size(), t.tilesR[d], nullptr, stream, true)));
+            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, false, false, true>(dL, (int)t.L[d].size(), t.tilesL[d], nullptr, stream)));
+            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<float, float, float, true, true, true>(dR, (int)t.R[d].size(), t.tilesR[d], nullptr, stream)));
         } else {
             if (dL) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<bf16_t, bf16_t, 1, 1>(dL, (int)t.L[d].size(), t.tilesL[d], nullptr, stream)));
             if (dR) ASTERIA_HIP_TRY((launch_gemm_bf16_grouped<bf16_t, bf16_t, 1, 1>(dR, (int)t.R[d].size(), t.tilesR[d], nullptr, stream)));
@@ -263,11 +263,11 @@ extern "C" asteria_status asteria_stats_update(const asteria_block *blocks, int 
         }
         ASTERIA_HIP_TRY(up.flush());
         if (d == ASTERIA_F32) {
-            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, false, false>(dL, (int)t.L64[d].size(), t.tilesL64[d], nullptr, stream, true)));
-            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, true, true>(dR, (int)t.R64[d].size(), t.tilesR64[d], nullptr, stream, true)));
+            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, false, false, true>(dL, (int)t.L64[d].size(), t.tilesL64[d], nullptr, stream)));
+            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<double, float, float, true, true, true>(dR, (int)t.R64[d].size(), t.tilesR64[d], nullptr, stream)));
         } else {
-            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<double, bf16_t, bf16_t, false, false>(dL, (int)t.L64[d].size(), t.tilesL64[d], nullptr, stream, true)));
-            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<double, bf16_t, bf16_t, true, true>(dR, (int)t.R64[d].size(), t.tilesR64[d], nullptr, stream, true)));
+            if (dL) ASTERIA_HIP_TRY((launch_gemm_grouped<double, bf16_t, bf16_t, false, false, true>(dL, (int)t.L64[d].size(), t.tilesL64[d], nullptr, stream)));
+            if (dR) ASTERIA_HIP_TRY((launch_gemm_grouped<double, bf16_t, bf16_t, true, true, true>(dR, (int)t.R64[d].size(), t.tilesR64[d], nullptr, stream)));
         }
     }
     return ASTERIA_OK;
