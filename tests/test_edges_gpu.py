@@ -49,10 +49,10 @@ def _root_error(A, X, eps):
 @pytest.mark.parametrize("kind", ["flat", "power", "log"])
 @pytest.mark.parametrize("eps", [1e-3, 1e-6, 1e-8])
 @pytest.mark.parametrize("sizes", [
-    [1, 2, 31, 33, 64, 65, 127, 128, 129, 255, 256, 257],       # 64-wide tiles; recurrence in registers and streamed
-    [513, 640],                                                 # one launch per step of the recurrence
+    [1, 2, 31, 33, 64, 65, 127, 128, 129, 255, 256, 257],       # 64-wide tiles; recurrence of all in the registers of one or two workgroups
+    [513, 640],                                                 # ... of six and seven
     [130] * 190 + [97, 128, 256],                               # 128-wide tiles
-    [514] * 192,                                                # a batch whose recurrences run one workgroup each
+    [514] * 192,                                                # more workgroups that share a factor than find room at once
     [761] * 118 + [33, 520, 768, 770],                          # 256-wide tiles: remainders of 249, 8 and 2, transposed panels
     [76, 80, 520] * 60, [900] * 70 + [1040] * 4,                # 128- and 256-wide tiles: a block row beyond the last row
     [64, 33] * 150, [200, 333] * 32, [200, 333] * 40,           # many small tiles: as many as large ones; below four per CU; beyond
@@ -93,9 +93,7 @@ def test_largest_eigenvalue_from_registers(sizes, packed):
     for n in sizes:
         X = torch.full((n, n), float("nan"), device=DEV)
         if packed:
-            P = torch.full((ast.packed_elems(n),), float("nan"), device=DEV)
-            ast.sym_pack([(made[n], P)])
-            items.append((P, X, 1))
+            items.append((_packed_with_nan_padding(made[n]), X, 1))
         else:
             wide = torch.full((n, n + n % 3), float("nan"), device=DEV)      # what lies beyond a row's end is not data
             wide[:, :n] = made[n]
@@ -107,10 +105,10 @@ def test_largest_eigenvalue_from_registers(sizes, packed):
     assert bool((info == 0).all())
     for n, x in zip(sizes, lam.tolist()):
         assert abs(x - top[n]) <= 1e-5 * top[n], (n, x, top[n])
-    made[max(sizes)][0, 0] = float("nan")                       # reported, by every member alike
     n = max(sizes)
-    X = torch.zeros(n, n, device=DEV)
-    ast.inverse_root([(made[n], X)], 1e-6, info=info[:1])
+    made[n][n - 1, n - 1] = float("nan")                        # reported, by every member alike
+    A = _packed_with_nan_padding(made[n]) if packed else made[n]
+    ast.inverse_root([(A, torch.zeros(n, n, device=DEV), int(packed))], 1e-6, info=info[:1])
     torch.cuda.synchronize()
     assert int(info[0]) == 2
 
@@ -339,13 +337,14 @@ def test_roots_of_a_batch_with_an_eps_per_factor():
         assert _root_error(A, X, e)[0] <= 2e-3, (A.shape[0], e)
 
 
+@pytest.mark.parametrize("opts", [None, dict(lowp_from=40)])
 @pytest.mark.parametrize("sizes", [[128] * 200 + [1500], [700] * 191 + [513], [700] * 192, [700] * 191 + [1000]])
-def test_roots_of_uneven_batches(sizes):
-    # either side of the line between a workgroup per factor and a launch per step for the largest eigenvalue
+def test_roots_of_uneven_batches(sizes, opts):
+    # the general path: either side of the line between a workgroup per factor and a launch per step for the largest eigenvalue
     made = {n: _with_spectrum(n, _spectrum("power", n), 7, n) for n in set(sizes)}
     Xs = [torch.empty_like(made[n]) for n in sizes]
     lam = torch.zeros(len(sizes), device=DEV)
-    ast.inverse_root([(made[n], X) for n, X in zip(sizes, Xs)], 1e-6, lambda_max=lam)
+    ast.inverse_root([(made[n], X) for n, X in zip(sizes, Xs)], 1e-6, opts=None if opts is None else ast.RootOpts(**opts), lambda_max=lam)
     torch.cuda.synchronize()
     last = {n: i for i, n in enumerate(sizes)}
     for n, i in last.items():
@@ -570,11 +569,93 @@ def test_products_in_quarters_are_those_of_whole_tiles(m, n, grad):
     assert float(torch.linalg.norm(alone.double() - ref) / torch.linalg.norm(ref)) <= 4 * 2.0 ** -16
 
 
+def _pitched(A, extra):
+    wide = torch.full((A.shape[0], A.shape[1] + extra), float("nan"), dtype=A.dtype, device=DEV)
+    wide[:, :A.shape[1]] = A
+    return wide[:, :A.shape[1]]
+
+
+# ... and the statistics on the fp32 and fp64 cores, and on the bf16 cores where the rows of the gradient are no whole 16-byte pieces: dense and
+# packed, with aligned rows and without.  The error is that of sums of k products of random sign, rounded to fp32 (fp64 sums: once).
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("grad, double", [(torch.float32, 0), (torch.float32, 1), (torch.bfloat16, 1), (torch.bfloat16, 0)])
+@pytest.mark.parametrize("m, n, extra", [(1, 1, 1), (63, 65, 0), (64, 128, 0), (65, 127, 3), (129, 31, 1), (191, 193, 0), (256, 128, 0), (300, 517, 2)])
+def test_statistics_in_quarters_are_those_of_whole_tiles(m, n, extra, grad, double, packed):
+    g = torch.Generator(device=DEV).manual_seed(m * 1000 + n)
+    G = _pitched(torch.randn(m, n, device=DEV, generator=g).to(grad), extra + (1 if grad == torch.bfloat16 and not double and (n + extra) % 8 == 0 else 0))
+    old = [X + X.T for X in (torch.randn(k, k, device=DEV, generator=g) for k in (m, n))]
+
+    def fresh():
+        if not packed:
+            return [_pitched(X, extra) for X in old]
+        Ps = [torch.empty(ast.packed_elems(k), device=DEV) for k in (m, n)]
+        ast.sym_pack(list(zip(old, Ps)))
+        return Ps
+    one = fresh()
+    ast.stats_update([(G, one[0], one[1], double, int(packed))], 0.75)
+    count = 257 // min(((k + 127) // 128) * ((k + 127) // 128 + 1) // 2 for k in (m, n)) + 1
+    many = [fresh() for _ in range(count)]
+    ast.stats_update([(G, L, R, double, int(packed)) for L, R in many], 0.75)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for s in many for a, b in zip(s, one))
+    for new, before, H in zip(one, old, (G.double(), G.double().T)):
+        if packed:
+            full = torch.empty_like(before)
+            ast.sym_unpack([(full, new)])
+            new = full
+        ref = 0.75 * before.double() + 0.25 * (H.contiguous() @ H.T.contiguous())
+        assert float(torch.linalg.norm(new.double() - ref) / torch.linalg.norm(ref)) <= (2.0 ** -24 if double else 2.0 ** -24 * (2 + H.shape[1] ** 0.5))
+
+
+# ... and the rotations of the SOAP step, with a basis on both sides and on one
+@pytest.mark.parametrize("grad", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("sides", ["L", "R", "LR"])
+@pytest.mark.parametrize("m, n, extra", [(1, 1, 0), (63, 65, 0), (64, 128, 0), (65, 127, 3), (129, 31, 1), (191, 193, 0), (256, 128, 0), (300, 517, 2)])
+def test_soap_steps_in_quarters_are_those_of_whole_tiles(m, n, extra, sides, grad):
+    g = torch.Generator(device=DEV).manual_seed(m * 1000 + n)
+    QL, QR = (_pitched(W.haar(k, DEV, 3, k), extra) if side in sides else None for side, k in (("L", m), ("R", n)))
+    G = _pitched(torch.randn(m, n, device=DEV, generator=g).to(grad), extra)
+    M, V = torch.randn(m, n, device=DEV, generator=g), torch.rand(m, n, device=DEV, generator=g) + 0.5
+
+    def fresh():
+        return [_pitched(M, extra), _pitched(V, extra), _pitched(torch.zeros_like(M), extra)]
+    one = fresh()
+    ast.soap_step([(G, QL, QR, *one)], 0.5, 0.75, 1e-8, 3)
+    many = [fresh() for _ in range(257 // (((m + 127) // 128) * ((n + 127) // 128)) + 1)]
+    ast.soap_step([(G, QL, QR, *s) for s in many], 0.5, 0.75, 1e-8, 3)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for s in many for a, b in zip(s, one))
+    ql, qr = (torch.eye(k, device=DEV, dtype=torch.float64) if Q is None else Q.double() for Q, k in ((QL, m), (QR, n)))
+    rot = ql.T.contiguous() @ G.double() @ qr
+    mom, var = 0.5 * M.double() + 0.5 * rot, 0.75 * V.double() + 0.25 * rot ** 2
+    step = (mom / (1 - 0.5 ** 3)) / ((var / (1 - 0.75 ** 3)).sqrt() + 1e-8)
+    ref = ql @ step @ qr.T.contiguous()
+    for got, want in zip(one, (mom, var, ref)):
+        # both terms kept to 2^-16 of every operand of the four rotations
+        assert float(torch.linalg.norm(got.double() - want) / torch.linalg.norm(want)) <= 8 * 2.0 ** -16
+
+
+# ... and of the moments under new bases
+@pytest.mark.parametrize("m, n, extra", [(1, 1, 0), (65, 127, 3), (191, 193, 0), (256, 128, 0), (300, 517, 2)])
+def test_moments_under_new_bases_in_quarters_are_those_of_whole_tiles(m, n, extra):
+    Q = [_pitched(W.haar(k, DEV, key, k), extra) for k in (m, n) for key in (3, 4)]      # L old, L new, R old, R new
+    M = torch.randn(m, n, device=DEV, generator=torch.Generator(device=DEV).manual_seed(m * 1000 + n))
+    one = _pitched(M, extra)
+    ast.soap_reproject([(Q[0], Q[1], Q[2], Q[3], one, None, None, None)])
+    many = [_pitched(M, extra) for _ in range(257 // (((m + 127) // 128) * ((n + 127) // 128)) + 1)]
+    ast.soap_reproject([(Q[0], Q[1], Q[2], Q[3], X, None, None, None) for X in many])
+    torch.cuda.synchronize()
+    assert all(torch.equal(X, one) for X in many)
+    d = [q.double() for q in Q]
+    ref = d[1].T.contiguous() @ d[0] @ M.double() @ d[2].T.contiguous() @ d[3]
+    assert float(torch.linalg.norm(one.double() - ref) / torch.linalg.norm(ref)) <= 8 * 2.0 ** -16
+
+
 @pytest.mark.parametrize("opts", [None, dict(int8_slices=0), dict(lowp_from=40)])
 @pytest.mark.parametrize("power", [-100, -80, -64, 48])
 @pytest.mark.parametrize("sizes", [
-    [33, 128, 257],                                             # one workgroup per recurrence: in registers, streamed
-    [513, 640],                                                 # one launch per step
+    [33, 128, 257],                                             # recurrences in registers of workgroups (general path: one, streamed)
+    [513, 640],                                                 # ... of several (general path: a launch per step)
     [96] * 192,                                                 # a full batch
 ])
 def test_roots_do_not_depend_on_the_magnitude_of_the_statistics(sizes, power, opts):
