@@ -879,21 +879,21 @@ int stream_cus(hipStream_t stream)
 }
 
 // Whether the lambda_max estimate of a pass keeps its matrices in registers of several workgroups: wherever they fit and find room side by
-// side, except for factors that one workgroup holds by itself.  The whole refresh in us, before (the ways below) / so: 3 blocks of 777 x 1000 in blocks of 512,
-// evenly dense spectra 1650 / 1345; 6 of 1000 x 333 1197 / 1140; 1 of 512 x 400 579 / 479; 1 of 1024 x 1024 779 / 727; 100 of 512 x 300 3940 / 3920;
-// 64 of 1024 x 1024 17265 / 15980; 3 of 2000 x 1500 4095 / 3976; the 1.1B model 255.4 / 246.1 ms, packed 255.6 / 244.5.
+// side, except for factors that one workgroup holds by itself.  The whole refresh in us, by the ways below / so, taken in turn: 3 blocks of 777 x 1000 in
+// blocks of 512, evenly dense spectra 1621 / 1265; 6 of 1000 x 333 1106 / 1036; 1 of 512 x 400 487 / 406; 1 of 1024 x 1024 712 / 654; 100 of
+// 512 x 300 3811 / 3802; 64 of 1024 x 1024 16837 / 15807; 3 of 2000 x 1500 4001 / 3876; the 1.1B model 248.7 / 243.2 ms, packed 251.6 / 243.7.
 bool lanczos_by_cluster(int n_max, hipStream_t stream) { return n_max > 256 && n_max <= LC_MAX_N && lanczos_cluster_room(n_max, stream_cus(stream)); }
 
 // The others (larger factors, little room, the general path).  Small factors, and batches that keep every CU busy until the
 // largest factor is done: one workgroup per factor, one launch.  Otherwise one launch per step - 32 of them, then one
 // workgroup per factor takes what has not settled; from n = 2048 on launches throughout.
-// Refresh in us at eps = 1e-6, a launch per step / a workgroup per factor, power-law spectrum (8 steps):
-//   1 factor    n = 320 488 / 486, 448 512 / 545, 512 525 / 560, 768 633 / 767 (packed ones need three launches a step)
-//   n = 1024    64 factors 9224 / 9310, 128: 17665 / 17507, 192: 26027 / 25588; n = 640 and 1536 alike
-//   200 factors of n = 128 and one of 4096: 11.6 ms / 18.2 (evenly spaced spectrum, 128 steps: 18.1 / 86.2), which is
+// General path with one fp32 iteration, us, launches of steps / a workgroup per factor, power-law spectrum (8 steps):
+//   1 factor    n = 320 309 / 298, 448 328 / 347, 512 322 / 340, 640 368 / 452, 768 390 / 507 (packed ones need three launches a step)
+//   n = 1024    64 factors 2790 / 2871, 128 5295 / 5147, 192 7830 / 7475, 256 10367 / 9777
+//   200 factors of n = 128 and one of 4096: 4326 / 10584 (evenly spaced spectrum, 128 steps: 7701 / 72139), which is
 //   why the rule counts elements against those of the largest factor
-// 32 launches and a workgroup / launches throughout: power law n = 1024 743 / 998, 1536 1065 / 1314, 2000 1710 / 1921;
-// evenly spaced n = 1024 3762 / 3537, 1536 10374 / 6035, 2000 20121 / 7651: most spectra settle within the 32.
+// 32 launches and a workgroup / launches throughout: power law n = 320 309 / 491, 1024 446 / 636, 1536 572 / 763, 2000 844 / 1021, 3000 1832 /
+// 1849; evenly spaced n = 512 1224 / 1020, 1024 1955 / 1147, 1536 5916 / 1568, 2000 14702 / 2314: most spectra settle within the 32.
 bool lanczos_by_factor(double elems, int n_max, bool any_packed)
 {
     return n_max <= LZ_WG_N || (elems >= (double)LZ_WG_BATCH * n_max * n_max && n_max <= LZ_WG_MAX_N && !any_packed);
@@ -1123,8 +1123,9 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
             switch (edge) {
             case 64: return launch_pair_product<2, 2, 2, 2, 4>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
             case 128:
-                // one workgroup per CU at most: eight wavefronts hide more of each other's waits than four (252 tiles of 6 factors
-                // of n = 1000 and 333: 35 us a product, 40); with two workgroups per CU four are better (8 of 1024 x 1024 2475 us, 2650)
+                // one workgroup per CU at most: eight wavefronts hide more of each other's waits than four; with two workgroups per CU four
+                // are better.  Refresh in us, eight / four, by tiles: n = 1024 216 1007 / 1079, 288 1572 / 1454, 360 1684 / 1557, 504 1991 /
+                // 1812; n = 333 240 726 / 757, 300 1052 / 984; n = 512 400 1321 / 1199; n = 2048 and 64 274 2526 / 2355
                 if ((op1 >= 0 ? 2 : 1) * pair_total <= PLANE_CUS)
                     return launch_pair_product<4, 2, 2, 4, 4>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
                 return launch_pair_product<2, 2, 4, 4, 2>(d_fd, d_fs, d_state, d_map_p, pair_total, op0, op1, k, d, stream);
@@ -1143,6 +1144,10 @@ asteria_status run_pass_planes(const asteria_factor *f, int first, int cnt, cons
                 e = launch_gemm_grouped<double, double, double, false, false>(ft.t[tab], cnt, tri_total, d_state, stream);
                 if (planes >= 0) from_f64(planes);
             }
+            // One launch for either number of digits, refresh in us, one / one each (both in quarters up to PLANE_QUARTERS), by halves of tiles:
+            // n = 128 720 873 / 890, n = 1024 432 1006 / 1019, 720 1531 / 1545, 1152 2297 / 2317, 1728 3159 / 3181, eps = 1e-8 1152 5049 /
+            // 5072; n = 512 640 1073 / 1091, 2400 3244 / 3361.  Beside 256-wide tiles within what runs differ by: n = 1024 5760 9758 / 9809,
+            // 14400 22961 / 22981, n = 768 at eps = 1e-8 5880 18915 / 18968; there the launches stay apart, as a profile reports them.
             if (e == hipSuccess && pre && pl.i8_slices > 4 && edge != 256) {
                 e = 2 * tri_total <= PLANE_QUARTERS
                         ? launch_digit_product<0, true>(d_fd, d_fs, d_state, d_map, tri_total, op, k, d, stream)

@@ -341,7 +341,11 @@ __global__ __launch_bounds__(THREADS) void lanczos_factor_kernel(const FactorDev
 // member that gives up sets a word for the launch that ends all waits in it.  A factor whose first member has not settled is left to
 // lanczos_alone, one workgroup that waits for nobody.
 //
-// Bound by the first load (HBM) and by 6 - 8 us a step (exchange, two block sums, the product); figures beside lanczos_by_cluster.
+// Bound by the first load (HBM) and by a step's chain: exchange, two block sums, the product, the tridiagonal problem, which grows with the
+// steps.  n = 257 .. 1500, evenly spaced spectrum: 8 us from the 8th to the 16th step, 9 to the 24th, 10 to the 48th; n = 2048 10 - 13.
+// 168 registers are all that 12 wavefronts leave each other; with 128 for the matrix 168 values spill (148 bytes of scratch a
+// lane, written once and read in part in every step): the estimate of the 1.1B model, 7.1 ms, moves 10.8 GB in and 1.8 out where the
+// matrices are 7.2 (mean of full and packed).  Whole refreshes beside lanczos_by_cluster.
 constexpr uint32_t LC_POLLS = 1u << 21;
 struct LanczosWaits { uint32_t sums = LC_POLLS, y = LC_POLLS; };      // looks at what others have to write before a member gives up
 
@@ -365,7 +369,7 @@ __global__ __launch_bounds__(256) void lanczos_prepare_kernel(const FactorDev *f
     if (blockIdx.x == 0 && threadIdx.x < 2) ticket[threadIdx.x] = 0;
 }
 
-// NI: a lane holds columns 4 lane + 256 i .. + 3 for i < NI of RW consecutive rows (128 registers)
+// NI: a lane holds columns 4 lane + 256 i .. + 3 for i < NI of RW consecutive rows (128 values)
 template <int NI>
 __device__ __forceinline__ void lanczos_member(const FactorDev &F, FactorScal &S, int member, float tol2, int steps, LanczosWaits waits, int *given_up)
 {

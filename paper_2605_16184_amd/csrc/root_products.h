@@ -817,8 +817,8 @@ __device__ __forceinline__ void digit_half(const FactorDev &F, const FactorScal 
     else run(std::integral_constant<int, 2>{});
 }
 
-// One launch for factors of either number of digits (NS = 0) or one for each.  Where the launches themselves count one; a batch of
-// large tiles does not notice them, and its four digits run without the registers that the fifth spills.
+// One launch for factors of either number of digits (NS = 0) or one for each: figures where they are launched.  (NS = 0 spills what five
+// digits do, NS = 4 nothing.)
 // QUARTER: 64 x 64 per workgroup.  With few tiles the epilogue of two blocks one after the other is what a product waits for.  The line, us
 // of the refresh, halves / quarters, by halves of tiles: figures beside PLANE_QUARTERS.
 template <int NS, bool QUARTER>
