@@ -275,8 +275,8 @@ asteria_status asteria_sym_unpack(const asteria_sympair *items, int nitems, void
  *   resid      device float[nfactors] or NULL   (last measured ||M - I||_F)
  *   lambda_max device float[nfactors] or NULL   (the estimate used)
  * Workspace: the call splits the batch into passes that fit ws_bytes; *min_bytes is the size
- * needed for the largest single factor, for any eps and root.  The result does not depend on ws_bytes from
- * there on.  A call with less is still accepted where its own eps and options need less; under the automatic
+ * needed for the largest single factor, for any eps and root.  From there on ws_bytes decides only which factors
+ * share a pass (and with that in which order lambda_max and the residuals are summed: round-off, not accuracy).  A call with less is still accepted where its own eps and options need less; under the automatic
  * rules it may then run as with pinned options (the second table above: more iterations, the same accuracy).
  * Errors: NULL A or X, n <= 0, ld < n, unsupported root or int8_slices, eps < 0 or non-finite,
  * eps_count not in {1, nfactors} -> INVALID_ARG / UNSUPPORTED; ws too small ->
